@@ -384,7 +384,7 @@ int ada_cascade_report(int L, int T, const int32_t* counts_all, const uint64_t* 
  * kernel, so these figures are upper bounds of the durations a kernel trace reports.
  */
 enum { ADA_K_NORM_PREP = 0, ADA_K_GRAM_FULL = 1, ADA_K_GRAM_REP = 2, ADA_K_GRAM_CROSS = 3, ADA_K_UPDATE = 4,
-       ADA_K_CASCADE_FUSED = 5, ADA_K_MFMA_PROBE = 6, ADA_K_ASSIGN = 7, ADA_K_ATTN = 8, ADA_K_COUNT = 9 };
+       ADA_K_CASCADE_FUSED = 5, ADA_K_MFMA_PROBE = 6, ADA_K_ASSIGN = 7, ADA_K_ATTN = 8, ADA_K_SCREEN = 9, ADA_K_COUNT = 10 };
 int ada_profile_enable(int on);
 int ada_profile_collect(double* ms_sum, int* launches);
 /* A plain device-to-device copy kernel (bytes: multiple of 16, both pointers 16-byte aligned): it reads and writes
@@ -409,6 +409,7 @@ int ada_profile_mfma_probe(int workgroups, int iters, float* sink, void* stream)
  *   ADA_CASCADE_TILE=64|64x128|128|256x128   tile shape of the one-launch cascade step
  *   ADA_NO_DMA=1                  operands through registers instead of straight into LDS
  *   ADA_ATTN=lds                  the first attention kernel
+ *   ADA_SCREEN=0                  layer loops: one launch per layer instead of the screened selection
  *   ADA_SPIN_LIMIT=n              bound of the resident pass's wait between layers (polls)
  */
 

@@ -32,7 +32,7 @@ SYMBOLS = ("ada_status_string", "ada_workspace_bytes", "ada_workspace_init", "ad
            "ada_profile_collect", "ada_profile_copy_probe", "ada_profile_mfma_probe", "ada_assign_nearest",
            "ada_attention_compressed", "ada_cascade_step_static")
 
-KERNEL_CLASSES = ("norm_prep", "gram_full", "gram_rep", "gram_cross", "update", "cascade_fused", "mfma_probe", "assign", "attn")
+KERNEL_CLASSES = ("norm_prep", "gram_full", "gram_rep", "gram_cross", "update", "cascade_fused", "mfma_probe", "assign", "attn", "screen")
 
 
 class AdaGroups(ctypes.Structure):

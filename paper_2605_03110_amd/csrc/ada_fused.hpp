@@ -25,6 +25,11 @@ __device__ unsigned long long g_phase_clk[64];
 #define ADA_CLK_LAST(i) do { } while (0)
 #endif
 
+// LIST_COHERENT: the list was written earlier in this same launch by another workgroup (k_cascade_pass, k_cascade_rest):
+// it is read past the caches instead of invalidating them.  LIST_IDENTITY: every token is inherited (entry j is j); a step
+// on that list is the full selection, and its counts are reported as one.
+enum { LIST_PLAIN = 0, LIST_COHERENT = 1, LIST_IDENTITY = 2 };
+
 struct FusedParams {
     const void* X;
     long long ld;
@@ -48,9 +53,7 @@ struct FusedParams {
     unsigned long long* best;       // [T], zero on entry and on exit: (bits of the max |cos|) << 32 | (INT_MAX - token id)
     int32_t* assign;                // [T]
     float* corr;                    // [T], may be NULL
-    // the list was written earlier in this same launch by another workgroup (k_cascade_pass): read it past the
-    // caches instead of invalidating them
-    int coherent_list;
+    int list_mode;                  // how prev_idx is read: LIST_*
     // tile shape of the two-group direct-to-LDS form: n > 0 = choose per step for a chip of n CUs (cascade_tile_shape);
     // 0, -1, -2 = always shape 0, 1, 2
     int tile_pick;
@@ -162,7 +165,8 @@ __device__ inline void reset_tickets(int32_t* ticket) {   // by the last arriver
 }
 
 __device__ inline int list_at(const FusedParams& p, int j) {
-    return p.coherent_list ? __hip_atomic_load(p.prev_idx + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : p.prev_idx[j];
+    if (p.list_mode == LIST_IDENTITY) return j;
+    return p.list_mode == LIST_COHERENT ? __hip_atomic_load(p.prev_idx + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : p.prev_idx[j];
 }
 
 // DMA = operands go global -> LDS directly (global_load_lds, 16 bytes per lane) through a ring of NS stages per
@@ -1386,7 +1390,8 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
         if (f[2][i]) { if (p.removes) p.removes[o_rem] = t; ++o_rem; }
     }
     if (tid == 0) {
-        p.counts[0] = n_idx; p.counts[1] = n_add; p.counts[2] = n_rem; p.counts[3] = ADA_OK;
+        const bool full = p.list_mode == LIST_IDENTITY;
+        p.counts[0] = n_idx; p.counts[1] = full ? n_idx : n_add; p.counts[2] = full ? 0 : n_rem; p.counts[3] = ADA_OK;
         adapt_tau(p, r, n_add, n_rem, true);
         if (p.gram_ops) {
             const unsigned long long TT = (unsigned long long)T, rr = (unsigned long long)r;
@@ -1553,7 +1558,8 @@ __device__ inline int fused_update(const FusedParams& p, int r, bool r_ok, int q
         if (f == 1) { if (p.removes) p.removes[o_rem] = t; ++o_rem; }
     }
     if (tid == 0) {
-        p.counts[0] = n_idx; p.counts[1] = n_add; p.counts[2] = n_rem; p.counts[3] = ADA_OK;
+        const bool full = p.list_mode == LIST_IDENTITY;
+        p.counts[0] = n_idx; p.counts[1] = full ? n_idx : n_add; p.counts[2] = full ? 0 : n_rem; p.counts[3] = ADA_OK;
         adapt_tau(p, r, n_add, n_rem, true);
         if (p.gram_ops) {
             const unsigned long long TT = (unsigned long long)T, rr = (unsigned long long)r;
@@ -1632,6 +1638,8 @@ __device__ inline void fused_step_tiles(const FusedParams& p, int r, char* lds, 
         const unsigned tile = base + slot;
         if (tile >= ntiles) break;
         const int tb = (int)(tile / nbS), sb = (int)(tile - (unsigned)tb * nbS);
+        // (every token inherited, and the update reads first-hit records only: a tile above the diagonal has nothing to say)
+        if (p.list_mode == LIST_IDENTITY && p.first && (sb << sr) >= (tb + 1) << st) continue;
         if constexpr (ALIGNED && KG == 2 && DMA) {
             if constexpr (sizeof(In) == 2) {
                 // (measured both ways: loader waves gain 10% at 128 x 128; at 128 x 256 the eight multiplying waves of
@@ -1748,7 +1756,7 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_pass(PassParams pp) {
     const int T = p.T;
     // No cache is invalidated between layers.  X is read-only.  A row of the set is written (and written back) before
     // anybody reads it and is never read before that, so plain loads are safe when rows do not share cache lines;
-    // otherwise (coherent_list, set by the launcher) the list is read past the caches.
+    // otherwise (LIST_COHERENT, set by the launcher) the list is read past the caches.
     for (int i = 0; i < pp.n; ++i) {
         PASS_CLK(0);
         // ---- the inherited set: from the previous launch for the first layer, from this launch's previous layer after

@@ -40,9 +40,11 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 enum { MODE_FULL = 0, MODE_REP = 1, MODE_CROSS = 2 };
-// meta: 8 words of scalars, then (from word META_TICKET + 64 on, one per 128-byte line) the per-XCD ticket counters
+// meta: a few words of scalars, then (from word META_TICKET + 64 on, one per 128-byte line) the per-XCD ticket counters
 constexpr size_t META_BYTES = 2048;
-enum { META_R = 0, META_NONREP = 1, META_STATUS = 2, META_SPARE = 3, META_TICKET = 4, META_QUEUE = 5 /* and 6 */, META_EPOCH = 7, META_WORDS = 8 };
+enum { META_R = 0, META_NONREP = 1, META_STATUS = 2, META_SPARE = 3, META_TICKET = 4, META_QUEUE = 5 /* and 6 */, META_EPOCH = 7,
+       // screened selection: layers done so far; work queue, hand-over word and sign-off counter of k_cascade_rest (zero between calls)
+       META_PROGRESS = 8, META_REST_QUEUE = 9, META_REST_EPOCH = 10, META_REST_LEFT = 11, META_WORDS = 12 };
 
 // The one-launch cascade step keeps one hit word per token and per 32 inherited representatives; beyond this T
 // the table would dominate the workspace and the two-launch path is used instead.
@@ -54,9 +56,9 @@ struct Workspace {
     int32_t* nonrep_idx; // [T]
     uint8_t* is_rep;     // [T]
     int32_t* meta;       // [META_WORDS]; meta[META_TICKET], the META_QUEUE pair and meta[META_EPOCH] are zero between calls
-    uint32_t* hits;      // [T][hit_words(T)] (only for T <= FUSED_MAX_T)
     unsigned long long* best;   // [T] arg-max keys (assignment; cascade step with a gamma output); zero between calls
     uint32_t* first;            // [T] first-hit records of the one-launch cascade step; zero between calls
+    uint32_t* hits;             // [T][hit_words(T)] (only for T <= FUSED_MAX_T); the screened selection's units share the place
 };
 
 __host__ __device__ constexpr size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -64,11 +66,18 @@ constexpr int hit_words(int r_cap) {                         // whole 64- or 128
     return 2 * ((r_cap + 63) / 64) > 4 * ((r_cap + 127) / 128) ? 2 * ((r_cap + 63) / 64) : 4 * ((r_cap + 127) / 128);
 }
 
-constexpr size_t ws_bytes_for(int T) {
-    return align_up((size_t)T * 4, 256) * 3 + align_up((size_t)T, 256) + META_BYTES +
-           (T <= FUSED_MAX_T ? align_up((size_t)T * hit_words(T) * 4, 256) : 0) + align_up((size_t)T * 8, 256) +
-           align_up((size_t)T * 4, 256);
+constexpr size_t ws_fixed_bytes(int T) {                    // everything in front of the hit table
+    return align_up((size_t)T * 4, 256) * 4 + align_up((size_t)T, 256) + META_BYTES + align_up((size_t)T * 8, 256);
 }
+constexpr size_t ws_hit_bytes(int T) { return T <= FUSED_MAX_T ? align_up((size_t)T * hit_words(T) * 4, 256) : 0; }
+// Where the hit table lies the screened selection keeps its units (sketches, clusters: about 200 bytes per token and layer
+// at d = 4096), as many layers at a time as fit: 8 KB per token is 32 layers and more, 15.5 MB in all bounds it for long T.
+constexpr size_t ws_screen_bytes(int T) {
+    return T > FUSED_MAX_T ? 0
+         : (size_t)T * 8192 + 16384 < ((size_t)31 << 19) ? align_up((size_t)T * 8192 + 16384, 256) : ((size_t)31 << 19);
+}
+constexpr size_t ws_area_bytes(int T) { return ws_hit_bytes(T) > ws_screen_bytes(T) ? ws_hit_bytes(T) : ws_screen_bytes(T); }
+constexpr size_t ws_bytes_for(int T) { return ws_fixed_bytes(T) + ws_area_bytes(T); }
 
 inline Workspace carve(void* ws, int T) {
     char* p = (char*)ws;
@@ -79,9 +88,9 @@ inline Workspace carve(void* ws, int T) {
     w.nonrep_idx = (int32_t*)p; p += t4;
     w.is_rep = (uint8_t*)p; p += t1;
     w.meta = (int32_t*)p; p += META_BYTES;
-    w.hits = (uint32_t*)p; p += T <= FUSED_MAX_T ? align_up((size_t)T * hit_words(T) * 4, 256) : 0;
     w.best = (unsigned long long*)p; p += align_up((size_t)T * 8, 256);
-    w.first = (uint32_t*)p;
+    w.first = (uint32_t*)p; p += t4;
+    w.hits = (uint32_t*)p;
     return w;
 }
 
@@ -743,6 +752,7 @@ __global__ __launch_bounds__(256) void k_copy_probe(u32x4* __restrict__ dst, con
 }
 
 #include "ada_fused.hpp"
+#include "ada_screen.hpp"
 #include "ada_gram_dma.hpp"
 #include "ada_attn.hpp"
 
@@ -1383,7 +1393,7 @@ int run_cascade_pass(const void* const* X_layers, int first, int n, int T, int d
             0, nullptr, nullptr, nullptr, 0, cascade_tile_pick()};
     pp.f.first = T % 4 == 0 ? w.first : nullptr;              // (two K-groups: T <= 16384 fits)
     // rows of idx_all that share a 128-byte line with their neighbour could be cached half-written
-    pp.f.coherent_list = ((uintptr_t)idx_all % 128 != 0 || T % 32 != 0) ? 1 : 0;
+    pp.f.list_mode = ((uintptr_t)idx_all % 128 != 0 || T % 32 != 0) ? LIST_COHERENT : LIST_PLAIN;
     for (int i = 0; i < n; ++i) pp.X[i] = X_layers[first + i];
     for (int i = n; i < PASS_MAX_LAYERS; ++i) pp.X[i] = nullptr;
     pp.n = n;
@@ -1402,6 +1412,155 @@ int run_cascade_pass(const void* const* X_layers, int first, int n, int T, int d
     const hipError_t e = dtype == ADA_BF16 ? launch_pass<uint16_t, true, 2, true>(pp, st)
                                            : launch_pass<float, true, 2, true>(pp, st);
     return e == hipSuccess ? ADA_OK : ADA_ERR_DEVICE;
+}
+
+// ------------------------------------------------------------------------------------------------
+// Screened selection (ada_screen.hpp): L layers of G sequences, full selection at layer 0, Algorithm 1 afterwards.
+
+template <typename In, int LPR>
+hipError_t launch_screen_exact(const ScreenParams& sp, hipStream_t st) {
+    const int rb = (sp.T + EXACT_ROWS - 1) / EXACT_ROWS;
+    ProfScope ps(ADA_K_SCREEN, st);
+    hipLaunchKernelGGL((k_screen_exact<In, LPR>), dim3((unsigned)(rb * sp.G * sp.L)), dim3(256), 0, st, sp, rb);
+    return hipGetLastError();
+}
+
+// The graph of near pairs of every unit of sp.
+template <typename In>
+hipError_t launch_screen(const ScreenParams& sp, hipStream_t st) {
+    const int units = sp.G * sp.L;
+    const int rb = (sp.T + SKETCH_ROWS - 1) / SKETCH_ROWS;
+    const int nb = (sp.T + 127) / 128, ntile = nb * (nb + 1) / 2, total = ntile * units;
+    {
+        ProfScope ps(ADA_K_SCREEN, st);
+        hipLaunchKernelGGL((k_screen_sketch<In>), dim3((unsigned)(rb * units)), dim3(256), 0, st, sp, rb);
+        hipLaunchKernelGGL(k_screen_pairs, dim3((unsigned)((total + 7) / 8 * 8)), dim3(256), 0, st, sp, ntile, total);
+    }
+    // four pieces of a row in flight per lane, at least eight lanes (a cache line) side by side
+    const int np = (sp.d * (int)sizeof(In) + 15) / 16;
+    hipError_t e = np >= 256 ? launch_screen_exact<In, 64>(sp, st) : np >= 128 ? launch_screen_exact<In, 32>(sp, st)
+                 : np >= 64 ? launch_screen_exact<In, 16>(sp, st) : launch_screen_exact<In, 8>(sp, st);
+    if (e != hipSuccess) return e;
+    // (a unit with nothing to do takes its workgroups one read each; a busy one should have enough of them)
+    int k = 1024 / units;
+    k = k < 8 ? 8 : k;
+    k = k > ntile ? ntile : k;
+    ProfScope ps(ADA_K_SCREEN, st);
+    hipLaunchKernelGGL((k_screen_rest<In>), dim3((unsigned)(k * units)), dim3(256), 0, st, sp, ntile);
+    return hipGetLastError();
+}
+
+template <int THREADS, int U>
+hipError_t launch_screen_chain(const ChainParams& c, hipStream_t st) {
+    const int lds = c.s.T * 5 + 16;
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(once, [] {
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_screen_chain<THREADS, U>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, THREADS * U * 5 + 16);
+    });
+    if (attr_err != hipSuccess) return attr_err;
+    ProfScope ps(ADA_K_UPDATE, st);
+    hipLaunchKernelGGL((k_screen_chain<THREADS, U>), dim3((unsigned)c.s.G), dim3(THREADS), lds, st, c);
+    return hipGetLastError();
+}
+
+template <typename In, bool ALIGNED, bool DMA>
+hipError_t launch_cascade_rest(const RestParams& rp, hipStream_t st) {
+    constexpr int lds = FusedGeom<2, DMA>::LDS;
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(once, [] {
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cascade_rest<In, ALIGNED, 2, DMA>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    });
+    if (attr_err != hipSuccess) return attr_err;
+    ProfScope ps(ADA_K_CASCADE_FUSED, st);
+    const int grid = rp.f.groups > 1 ? rp.f.groups * rp.f.wpg : rp.f.grid;
+    hipLaunchKernelGGL((k_cascade_rest<In, ALIGNED, 2, DMA>), dim3((unsigned)grid), dim3(512), lds, st, rp);
+    return hipGetLastError();
+}
+
+// Whether a call over layers is screened: every layer at the one threshold (known here), T within the range of the
+// one-launch step (cluster ids and list positions in 16 bits), and a sketch that is a saving.
+bool screen_eligible(int T, int d, float tau, unsigned flags, ScreenPlan* plan) {
+    if ((flags & (ADA_FLAG_TWO_PASS | ADA_FLAG_RESIDENT_PASS)) || T > FUSED_MAX_T) return false;
+    const char* e = dev_switch("ADA_SCREEN");
+    if (e && e[0] == '0') return false;
+    return screen_plan(d, tau, plan) && ScreenUnit(T, plan->nch).bytes <= (long long)ws_screen_bytes(T);
+}
+
+// Arguments checked by the caller; x_gs in bytes; list_gs, counts_gs, ops_gs in elements (rows of one sequence are T, 4
+// and 1 apart).
+int run_layers_screened(const ScreenPlan& plan, const void* const* X_layers, int L, int G, long long x_gs, int T, int d,
+                        long long ld, int dtype, float tau, int32_t* idx, int32_t* counts, uint64_t* gram_ops,
+                        int32_t* adds, int32_t* removes, long long list_gs, long long counts_gs, long long ops_gs,
+                        void* ws, hipStream_t st, unsigned flags) {
+    const Workspace w = carve(ws, T);
+    const ScreenUnit U(T, plan.nch);
+    ChainParams c;
+    ScreenParams& sp = c.s;
+    sp.ld = ld; sp.T = T; sp.d = d; sp.G = G; sp.x_gs = G > 1 ? x_gs : 0;
+    sp.area = reinterpret_cast<char*>(w.hits);
+    sp.area_gs = (long long)ws_bytes_for(T);
+    sp.meta = w.meta;
+    sp.nch = plan.nch;
+    sp.nk = (d + 63) / 64;
+    sp.kap = plan.kappa * SCREEN_SCALE * SCREEN_SCALE;
+    sp.kap1 = plan.kappa + (float)SCREEN_EPS;
+    sp.f2 = plan.f2; sp.safe = plan.safe; sp.thr = threshold_of(tau); sp.cos_tight = plan.cos_tight;
+    c.earlier_only = (flags & ADA_FLAG_CROSS_EARLIER_ONLY) ? 1 : 0;
+    c.idx = idx; c.counts = counts; c.ops = reinterpret_cast<unsigned long long*>(gram_ops); c.adds = adds; c.removes = removes;
+    c.list_gs = list_gs; c.counts_gs = counts_gs; c.ops_gs = ops_gs;
+
+    long long fit = (long long)ws_screen_bytes(T) / U.bytes;   // layers at a time, in launches of equal size
+    if (fit > SCREEN_MAX_LAYERS) fit = SCREEN_MAX_LAYERS;
+    const int batches = (int)((L + fit - 1) / fit), per = (L + batches - 1) / batches;
+    for (int first = 0; first < L; first += per) {
+        sp.first = first;
+        sp.L = L - first < per ? L - first : per;
+        for (int i = 0; i < SCREEN_MAX_LAYERS; ++i) sp.X[i] = i < sp.L ? X_layers[first + i] : nullptr;
+        hipError_t e = dtype == ADA_BF16 ? launch_screen<uint16_t>(sp, st) : launch_screen<float>(sp, st);
+        if (e != hipSuccess) return ADA_ERR_DEVICE;
+        e = T <= 256 ? launch_screen_chain<256, 1>(c, st) : T <= 512 ? launch_screen_chain<512, 1>(c, st)
+          : T <= 1024 ? launch_screen_chain<1024, 1>(c, st) : T <= 2048 ? launch_screen_chain<1024, 2>(c, st)
+          : T <= 4096 ? launch_screen_chain<1024, 4>(c, st) : T <= 8192 ? launch_screen_chain<1024, 8>(c, st)
+                      : launch_screen_chain<1024, 16>(c, st);
+        if (e != hipSuccess) return ADA_ERR_DEVICE;
+    }
+    // what the chain left
+    RestParams rp;
+    rp.f = {nullptr, ld, T, d, nullptr, nullptr, T, sp.thr, c.earlier_only, w.hits, hit_words(T), nullptr, w.meta + META_TICKET,
+            nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr, nullptr, LIST_COHERENT, cascade_tile_pick()};
+    rp.f.first = T % 4 == 0 ? w.first : nullptr;               // (two K-groups: T <= 16384 fits)
+    rp.f.grid = device_cus();
+    if (G > 1) {
+        rp.f.groups = G;
+        rp.f.wpg = rp.f.grid / G < 1 ? 1 : rp.f.grid / G;
+        rp.f.x_gs = x_gs; rp.f.list_gs = list_gs; rp.f.counts_gs = counts_gs; rp.f.ops_gs = ops_gs;
+        rp.f.ws_gs = sp.area_gs;
+    }
+    rp.idx = idx; rp.counts = counts; rp.ops = c.ops; rp.adds = adds; rp.removes = removes; rp.meta = w.meta;
+    rp.spin_limit = 1 << 24;
+    const char* no_dma = dev_switch("ADA_NO_DMA");
+    bool base16 = true;
+    for (int l = 0; l < L; ++l) base16 = base16 && (uintptr_t)X_layers[l] % 16 == 0;
+    const long long ld_seen = ((G > 1 && x_gs % 16 != 0) || !base16) ? 1 : ld;
+    for (int first = 0; first < L; first += SCREEN_MAX_LAYERS) {
+        rp.first = first;
+        rp.n = L - first < SCREEN_MAX_LAYERS ? L - first : SCREEN_MAX_LAYERS;
+        for (int i = 0; i < SCREEN_MAX_LAYERS; ++i) rp.X[i] = i < rp.n ? X_layers[first + i] : nullptr;
+        const hipError_t e = dispatch(dtype, X_layers[0], ld_seen, d, [&](auto v) {
+            using V = decltype(v);
+            using In = typename V::In;
+            if constexpr (V::aligned) {
+                if (d % (128 / (int)sizeof(In)) == 0 && !(no_dma && no_dma[0] == '1')) return launch_cascade_rest<In, true, true>(rp, st);
+            }
+            return launch_cascade_rest<In, V::aligned, false>(rp, st);
+        });
+        if (e != hipSuccess) return ADA_ERR_DEVICE;
+    }
+    return ADA_OK;
 }
 
 // Algorithm 1 in separate launches (norms + lists, r x r Gram, cross-Gram against the valid representatives, update):
@@ -1562,7 +1721,7 @@ int ada_cascade_step(const void* X, int T, int d, int64_t ld, int dtype, float t
 // ------------------------------------------------------------------------------------------------
 // ada_cascade_step_static: the same step on a workspace that lives in this library's image, for callers that cannot
 // allocate.  `scratch` is a host-side stand-in for the array; its device address is looked up once per device.
-static __device__ __align__(256) unsigned char scratch[ws_bytes_for(ADA_STATIC_MAX_T)];
+static __device__ __align__(256) unsigned char scratch[ws_fixed_bytes(ADA_STATIC_MAX_T) + ws_hit_bytes(ADA_STATIC_MAX_T)];
 
 namespace {
 constexpr int STATIC_MAX_DEVICES = 64;
@@ -1590,7 +1749,7 @@ int ada_cascade_step_static(const void* X, int T, int d, int64_t ld, int dtype, 
     if (T > ADA_STATIC_MAX_T) return ADA_ERR_SHAPE;            // beyond what the array holds
     void* ws = static_scratch();
     if (!ws) return ADA_ERR_DEVICE;
-    const size_t ws_bytes = ws_bytes_for(ADA_STATIC_MAX_T);
+    const size_t ws_bytes = ws_bytes_for(ADA_STATIC_MAX_T);   // (what a step uses of a workspace is what the array holds)
     if (int e = check_common(X, T, d, ld, dtype, tau, ws, ws_bytes)) return e;
     if (r < 1 || r > T) return ADA_ERR_SHAPE;
     // The counters a step relies on being zero (tickets, queue, hand-over word) are cleared by a fill kernel, so the
@@ -1666,6 +1825,11 @@ int ada_cascade_layers_grouped(const ada_groups* groups, const void* const* X_la
     // the outputs are [G][L][...] blocks, so a group's rows are L rows apart
     const ada_groups g = {groups->G, groups->x_gstride, (int64_t)L * T, (int64_t)L * 4, (int64_t)L};
     const size_t esz = dtype == ADA_BF16 ? 2 : 4;
+    ScreenPlan plan;
+    if (screen_eligible(T, d, tau, flags, &plan))
+        return run_layers_screened(plan, X_layers, L, g.G, (long long)g.x_gstride * (long long)esz, T, d, ld, dtype, tau, idx_all,
+                                   counts_all, gram_ops_all, adds_all, removes_all, g.list_gstride, g.counts_gstride,
+                                   g.ops_gstride, ws, st, flags);
     // layer 0: every group's full selection in the same three launches
     {
         const GroupOff go = {g.G > 1 ? (long long)g.x_gstride * (long long)esz : 0, g.G > 1 ? (long long)one : 0,
@@ -1695,6 +1859,10 @@ int ada_cascade_layers(const void* const* X_layers, int L, int T, int d, int64_t
         if (!X_layers[l]) return ADA_ERR_NULL;
     if (int e = check_common(X_layers[0], T, d, ld, dtype, tau, ws, ws_bytes)) return e;
     hipStream_t st = (hipStream_t)stream;
+    ScreenPlan plan;
+    if (screen_eligible(T, d, tau, flags, &plan))
+        return run_layers_screened(plan, X_layers, L, 1, 0, T, d, ld, dtype, tau, idx_all, counts_all, gram_ops_all, adds_all,
+                                   removes_all, 0, 0, 0, ws, st, flags);
     // layer 0: the full T x T selection; layers >= 1 inherit the previous layer's set on the device (Section 4.1)
     int e = run_full(X_layers[0], T, d, ld, dtype, tau, nullptr, idx_all, counts_all, gram_ops_all, nullptr, ws, st);
     if (e == ADA_OK && pass_eligible(X_layers, L, T, d, ld, dtype, flags)) {
@@ -1743,7 +1911,15 @@ int ada_cascade_layers_batched(const void* const* X_layers, int B, int L, int T,
     // needs the whole device for one sequence and is not used here
     const unsigned fl = flags & ~ADA_FLAG_RESIDENT_PASS;
     int rc = ADA_OK;
-    for (int l = 0; l < L && rc == ADA_OK; ++l) {
+    ScreenPlan plan;
+    const bool screened = screen_eligible(T, d, tau, fl, &plan);
+    for (int b = 0; screened && b < B && rc == ADA_OK; ++b) {
+        const size_t row = (size_t)b * L, o = row * (size_t)T;
+        rc = run_layers_screened(plan, X_layers + row, L, 1, 0, T, d, ld, dtype, tau, idx_all + o, counts_all + row * 4,
+                                 gram_ops_all + row, adds_all ? adds_all + o : nullptr, removes_all ? removes_all + o : nullptr,
+                                 0, 0, 0, (char*)ws + (size_t)b * one, streams ? (hipStream_t)streams[b] : main, fl);
+    }
+    for (int l = 0; !screened && l < L && rc == ADA_OK; ++l) {
         for (int b = 0; b < B && rc == ADA_OK; ++b) {
             hipStream_t st = streams ? (hipStream_t)streams[b] : main;
             const size_t row = (size_t)b * L + l, o = row * (size_t)T;

@@ -1,0 +1,808 @@
+// Screened selection: the sets of many layers from the GRAPH of near pairs.  Included by ada_kernels.hip after
+// ada_fused.hpp.
+//
+// Definition 2.2 and Algorithm 1 only ask of a product whether |cos| reaches 1 - tau^2, and that question does not depend
+// on the inherited set: the pairs of tokens within the threshold of each other are a property of a layer's X alone.  So
+// they are found for all layers of a call at once, where the chip is full, and what stays sequential from layer to layer
+// is a walk over that graph by one workgroup.  Finding them does not take T^2 / 2 full products either:
+//
+//   sketch  n1 of the d columns (whole groups of 64, spread evenly over the row) of every row, scaled to unit length and
+//           rounded to 8-bit floats.  For a pair (s, t) with the cosine c1 of its two sketches,
+//               |cos(s,t)| <= rho_s rho_t |c1| + sqrt(1 - rho_s^2) sqrt(1 - rho_t^2)        (Cauchy-Schwarz on the rest)
+//           where rho^2 is the share of a row's squared norm that the sketch holds.  A pair whose sketch product stays
+//           below kappa is therefore within the threshold ONLY IF a row holds unusually little in the sketch; with every
+//           rho^2 at least f2 it is certainly not: the bound over all such rows is 1 - (1 - kappa') f2, kappa' = kappa plus
+//           the worst rounding of both sketches (see ScreenPlan).  What is left are the CANDIDATE pairs.
+//   pairs   all sketch products on MFMA; every token keeps its earliest candidate, its PIVOT.
+//   exact   one full product per token, with its pivot, in the precision of the other paths, and every row's norm: one
+//           pass over X.  A token close to its pivot (angle at most 0.45 of the threshold's) joins the pivot's CLUSTER:
+//           acos |cos| is a metric, so all members of a cluster are within the threshold of each other.
+//   rest    candidate pairs that no cluster explains are multiplied out one by one and become EDGES.  Whether there are
+//           any is a matter of counting: with every rho^2 >= f2 all pairs inside clusters are candidates, so if there are
+//           exactly as many candidates as pairs inside clusters there is nothing else, and the launch leaves at once.
+//   chain   one workgroup per sequence walks through the layers: Definition 2.2 at layer 0, Algorithm 1 afterwards, on the
+//           clusters and edges alone.
+// Nothing here is approximate: a pair is decided by its full product, by the metric or by the bound, with margins
+// (1e-4 on |cos| and more) far above the rounding of any of them.  Where the data do not cooperate -- so many pairs near the
+// threshold that listing them is no saving -- a layer is marked DENSE and the launch behind the chain runs it and the
+// layers after it on the tiles of the other path.
+//
+// Measured (bf16, tau = 0.1): see the kernels below.
+#pragma once
+
+constexpr int SCREEN_MAX_LAYERS = 64;                         // layers per launch (their pointers travel as arguments)
+constexpr int SCREEN_TILE_PAIRS = 256;                        // unexplained candidates a 128 x 128 tile may hold before its layer is dense
+constexpr float SCREEN_SCALE = 256.f;                         // sketches are stored as 8-bit floats of 256 x (unit vector)
+
+// header of a unit (one layer of one sequence); zeroed by the sketch launch
+enum { SU_CAND = 0, SU_PAIRS = 1, SU_FLAGS = 2, SU_EDGES = 3, SU_DENSE = 4, SU_WORDS = 64 };
+enum { SF_LOW = 1, SF_MESH = 2 };                             // SU_FLAGS: a row below f2; a pivot that has a pivot itself
+
+// How a problem is screened (host): columns of the sketch and the constants of the bound.
+struct ScreenPlan {
+    int nch;            // column groups of 64 in the sketch
+    float kappa;        // candidate: sketch product at least this (before rounding allowance)
+    float f2;           // rows must hold at least this share of their squared norm in the sketch
+    float safe;         // 1 - tau^2 minus the margin
+    float cos_tight;    // cosine of 0.45 of the threshold's angle
+};
+constexpr double SCREEN_EPS = 0.13;                           // 2 d + d^2 for a rounding of d = 2^-4 on each side (0.1289), and what underflows
+
+// nch: the smallest sketch for which ordinary rows pass.  kappa is where two unrelated rows stop to occur among all pairs of
+// a long sequence (the cosine of two independent directions in n dimensions exceeds k with probability about
+// (1 - k^2)^((n-1)/2); 3e-10 here), f2 follows from it, and n1 is taken where the share of the norm that n1 of d columns
+// of independent entries hold lies above f2 with 4.3 standard deviations (Wilson-Hilferty).  More than half of the
+// columns, or a threshold no bound reaches: not screened.
+inline bool screen_plan(int d, float tau, ScreenPlan* out) {
+    const double thr = 1.0 - (double)tau * (double)tau, safe = thr - 2e-4;
+    const int nk = (d + 63) / 64;
+    if (d < 64) return false;
+    for (int nch = 1; nch <= nk; ++nch) {
+        const int n = 64 * nch, ne = n < d ? n : d;
+        double k = sqrt(1.0 - exp(-44.0 / (ne - 1)));
+        if (k < 0.3) k = 0.3;
+        const double kap = k + SCREEN_EPS;
+        double f2 = 0.0;
+        if (nch == nk) {                                       // the sketch is the row: the product itself, rounded
+            if (nch > 4 || kap > safe - 5e-3) return false;
+        } else {
+            if (kap > 0.93) continue;
+            f2 = (1.0 - safe) / (1.0 - kap);
+            const double wh = 1.0 - 2.0 / (9.0 * n) - 4.3 * sqrt(2.0 / (9.0 * n));
+            if ((double)n / d * wh * wh * wh < f2) continue;
+            if (n > 512 && 2 * n > d) return false;
+        }
+        out->nch = nch;
+        out->kappa = (float)k;
+        out->f2 = (float)f2;
+        out->safe = (float)safe;
+        out->cos_tight = (float)cos(0.45 * acos(thr));
+        return true;
+    }
+    return false;
+}
+
+// Memory of a unit inside the workspace's screen area, in bytes from the unit's start.
+struct ScreenUnit {
+    int o_piv, o_size, o_rho, o_cl, o_edge, o_z, edge_cap;
+    long long bytes;
+    __host__ __device__ ScreenUnit(int T, int nch) {
+        const long long t4 = (long long)align_up((size_t)T * 4, 256);
+        edge_cap = T / 2 + 64;
+        long long o = SU_WORDS * 4;
+        o_piv = (int)o; o += t4;
+        o_size = (int)o; o += t4;
+        o_rho = (int)o; o += t4;
+        o_cl = (int)o; o += (long long)align_up((size_t)T * 2, 256);
+        o_edge = (int)o; o += (long long)align_up((size_t)edge_cap * 4, 256);
+        o_z = (int)o; o += (long long)align_up((size_t)T * 64 * nch, 256);
+        bytes = o;
+    }
+};
+
+struct ScreenParams {
+    long long ld;
+    int T, d;
+    int G, L;                  // sequences (or heads), layers of this launch
+    long long x_gs;            // bytes between sequences' X
+    char* area;                // sequence 0's screen area; the others area_gs bytes apart
+    long long area_gs;
+    int32_t* meta;             // sequence 0's scalars (likewise area_gs apart)
+    int first;                 // layer number of the launch's first layer
+    int nch, nk;
+    float kap, kap1;           // candidate threshold on the raw accumulator; kappa with the rounding allowance
+    float f2, safe, thr, cos_tight;
+    const void* X[SCREEN_MAX_LAYERS];
+};
+
+__device__ inline char* screen_unit(const ScreenParams& p, const ScreenUnit& U, int unit, int* layer, int* group) {
+    const int l = unit / p.G, g = unit - l * p.G;
+    *layer = l;
+    *group = g;
+    return p.area + (long long)g * p.area_gs + (long long)l * U.bytes;
+}
+
+template <typename In>
+__device__ inline const In* screen_x(const ScreenParams& p, int layer, int group) {
+    return reinterpret_cast<const In*>(reinterpret_cast<const char*>(p.X[layer]) + (long long)group * p.x_gs);
+}
+
+// 16 bytes of a row at any alignment (the memory pipe takes them; rows here need not start on 16 bytes)
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+
+// Eight consecutive elements from column e0 on, as floats; columns at or beyond d are zero.  The load is pulled back
+// into the row and what it repeats is cleared, so rows of any length and alignment are read in whole pieces (d >= 8).
+template <typename In> __device__ inline void screen_load8(const In* row, int e0, int d, float (&v)[8]);
+template <> __device__ inline void screen_load8<uint16_t>(const uint16_t* row, int e0, int d, float (&v)[8]) {
+    const int e = min(e0, d - 8), cut = e0 - e;
+    const u32x4 r = *reinterpret_cast<const u32x4_any*>(row + e);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[2 * i] = 2 * i >= cut ? __uint_as_float(r[i] << 16) : 0.f;
+        v[2 * i + 1] = 2 * i + 1 >= cut ? __uint_as_float(r[i] & 0xFFFF0000u) : 0.f;
+    }
+}
+template <> __device__ inline void screen_load8<float>(const float* row, int e0, int d, float (&v)[8]) {
+    const int e = min(e0, d - 8), cut = e0 - e;
+    const u32x4 a = *reinterpret_cast<const u32x4_any*>(row + e), b = *reinterpret_cast<const u32x4_any*>(row + e + 4);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[i] = i >= cut ? __uint_as_float(a[i]) : 0.f;
+        v[4 + i] = 4 + i >= cut ? __uint_as_float(b[i]) : 0.f;
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// k_screen_sketch: eight lanes per row, eight columns per lane and column group.  Reads n1 / d of X, one cache line (two
+// for fp32) per row and group; the groups of a row are all requested before the first is used (up to four).
+constexpr int SKETCH_ROWS = 32;                               // rows per workgroup
+template <typename In>
+__global__ __launch_bounds__(256) void k_screen_sketch(ScreenParams p, int row_blocks) {
+    const ScreenUnit U(p.T, p.nch);
+    const int unit = blockIdx.x / row_blocks, rb = blockIdx.x - unit * row_blocks;
+    int layer, group;
+    char* base = screen_unit(p, U, unit, &layer, &group);
+    const In* X = screen_x<In>(p, layer, group);
+    if (rb == 0) {
+        if (threadIdx.x < SU_WORDS) reinterpret_cast<uint32_t*>(base)[threadIdx.x] = 0u;
+        // words of the call (not of the unit): layers done so far; the last launch's queue is left at zero by itself
+        if (layer == 0 && p.first == 0 && threadIdx.x == 0)
+            reinterpret_cast<int32_t*>(reinterpret_cast<char*>(p.meta) + (long long)group * p.area_gs)[META_PROGRESS] = 0;
+    }
+    const int lane = threadIdx.x & 63, c8 = lane & 7;
+    const int t = rb * SKETCH_ROWS + (threadIdx.x >> 6) * 8 + (lane >> 3);
+    const In* row = X + (size_t)min(t, p.T - 1) * (size_t)p.ld;
+    auto col = [&](int j) { return (int)((unsigned)j * (unsigned)p.nk / (unsigned)p.nch) * 64 + c8 * 8; };
+    constexpr int KEEP = 4;
+    float v[KEEP][8];
+    float ss = 0.f;
+#pragma unroll
+    for (int j = 0; j < KEEP; ++j) {
+        const int jc = min(j, p.nch - 1);
+        screen_load8<In>(row, col(jc), p.d, v[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < KEEP; ++j)
+        if (j < p.nch) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) ss = fmaf(v[j][i], v[j][i], ss);
+        }
+    for (int j = KEEP; j < p.nch; ++j) {
+        float x[8];
+        screen_load8<In>(row, col(j), p.d, x);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) ss = fmaf(x[i], x[i], ss);
+    }
+    ss += __shfl_xor(ss, 1, 64);
+    ss += __shfl_xor(ss, 2, 64);
+    ss += __shfl_xor(ss, 4, 64);
+    const float sc = ss > 0.f ? SCREEN_SCALE / sqrtf(ss) : 0.f;
+    if (t >= p.T) return;
+    uint8_t* z = reinterpret_cast<uint8_t*>(base + U.o_z) + (size_t)t * (size_t)(64 * p.nch) + c8 * 8;
+    auto put = [&](int j, const float (&x)[8]) {
+        int lo = 0, hi = 0;
+        lo = __builtin_amdgcn_cvt_pk_fp8_f32(x[0] * sc, x[1] * sc, lo, false);
+        lo = __builtin_amdgcn_cvt_pk_fp8_f32(x[2] * sc, x[3] * sc, lo, true);
+        hi = __builtin_amdgcn_cvt_pk_fp8_f32(x[4] * sc, x[5] * sc, hi, false);
+        hi = __builtin_amdgcn_cvt_pk_fp8_f32(x[6] * sc, x[7] * sc, hi, true);
+        *reinterpret_cast<int2*>(z + j * 64) = int2{lo, hi};
+    };
+#pragma unroll
+    for (int j = 0; j < KEEP; ++j)
+        if (j < p.nch) put(j, v[j]);
+    for (int j = KEEP; j < p.nch; ++j) {
+        float x[8];
+        screen_load8<In>(row, col(j), p.d, x);
+        put(j, x);
+    }
+    if (c8 == 0) {
+        reinterpret_cast<float*>(base + U.o_rho)[t] = ss;
+        reinterpret_cast<int32_t*>(base + U.o_piv)[t] = t;
+        reinterpret_cast<int32_t*>(base + U.o_size)[t] = 0;
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Sketch products of a 128 x 128 tile: four waves in a 2 x 2 grid of 64 x 64, fragments straight from global memory (a
+// tile's sketches are a few tens of KB that its waves share through the L1; there is too little to multiply for staging
+// through LDS to pay).  The order of a fragment's columns does not matter as long as both sides use the same one: lane l
+// holds row l % 32, columns 32 (l / 32) .. + 31 of a group.
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+
+struct ScreenTile { int s0, t0; bool any; };                  // this wave's first rows; any: some s < t
+__device__ inline ScreenTile screen_tile(const uint8_t* Z, int T, int nch, int sb, int tb, f32x16 (&acc)[2][2]) {
+    const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int s0 = sb * 128 + (wave >> 1) * 64, t0 = tb * 128 + (wave & 1) * 64;
+    const ScreenTile me = {s0, t0, s0 <= t0 && t0 < T};
+    if (!me.any) return me;                                   // (above the diagonal, or past the end)
+    const size_t n1 = (size_t)(64 * nch);
+    const uint8_t *pa[2], *pb[2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        pa[a] = Z + (size_t)min(s0 + a * 32 + l32, T - 1) * n1 + half * 32;
+        pb[a] = Z + (size_t)min(t0 + a * 32 + l32, T - 1) * n1 + half * 32;
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+    }
+    i32x8 fa[2][2], fb[2][2];
+    auto rd = [&](int set, int j) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            const u32x4* qa = reinterpret_cast<const u32x4*>(pa[a] + j * 64);
+            const u32x4* qb = reinterpret_cast<const u32x4*>(pb[a] + j * 64);
+            const u32x4 a0 = qa[0], a1 = qa[1], b0 = qb[0], b1 = qb[1];
+            fa[set][a] = i32x8{(int)a0[0], (int)a0[1], (int)a0[2], (int)a0[3], (int)a1[0], (int)a1[1], (int)a1[2], (int)a1[3]};
+            fb[set][a] = i32x8{(int)b0[0], (int)b0[1], (int)b0[2], (int)b0[3], (int)b1[0], (int)b1[1], (int)b1[2], (int)b1[3]};
+        }
+    };
+    auto mma = [&](int set) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)                       // (formats 0: e4m3 on both sides; block scales 127 = 1)
+                acc[a][b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa[set][a], fb[set][b], acc[a][b], 0, 0, 0,
+                                                                            0x7F7F7F7F, 0, 0x7F7F7F7F);
+    };
+    rd(0, 0);
+    for (int j = 0; j < nch; j += 2) {
+        if (j + 1 < nch) rd(1, j + 1);
+        mma(0);
+        if (j + 1 < nch) {
+            if (j + 2 < nch) rd(0, j + 2);
+            mma(1);
+        }
+    }
+    return me;
+}
+
+// lower-triangular 128-block tile number -> blocks 0 <= sb <= tb
+__device__ inline void screen_blocks(int tile, int* sb, int* tb) {
+    int n = (int)((sqrtf(8.f * (float)tile + 1.f) - 1.f) * 0.5f);
+    while ((n + 1) * (n + 2) / 2 <= tile) ++n;
+    while (n * (n + 1) / 2 > tile) --n;
+    *tb = n;
+    *sb = tile - n * (n + 1) / 2;
+}
+
+// k_screen_pairs: every token's earliest candidate, and how many candidate pairs there are.  Tiles of one unit are dealt to
+// one XCD (workgroup b runs on XCD b % 8), so that its sketches are read by one L2.
+__global__ __launch_bounds__(256) void k_screen_pairs(ScreenParams p, int ntile, int total) {
+    __shared__ int s_cand;
+    const int per = (total + 7) >> 3;
+    const int w = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if (w >= total || (int)(blockIdx.x >> 3) >= per) return;
+    const ScreenUnit U(p.T, p.nch);
+    const int unit = w / ntile;
+    int layer, group, sb, tb;
+    char* base = screen_unit(p, U, unit, &layer, &group);
+    screen_blocks(w - unit * ntile, &sb, &tb);
+    if (threadIdx.x == 0) s_cand = 0;
+    __syncthreads();
+    f32x16 acc[2][2];
+    const ScreenTile me = screen_tile(reinterpret_cast<const uint8_t*>(base + U.o_z), p.T, p.nch, sb, tb, acc);
+    const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+    if (me.any) {
+        int cand = 0;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int t = me.t0 + b * 32 + l32;
+            int piv = INT_MAX;
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const bool near = fabsf(acc[a][b][i]) >= p.kap;
+                    if (__builtin_amdgcn_ballot_w64(near) != 0ull) {     // few registers of a block hold one: scalar branch
+                        const int s = me.s0 + a * 32 + (i & 3) + 4 * half + 8 * (i >> 2);
+                        const bool is = near && s < t && t < p.T;
+                        cand += is ? 1 : 0;
+                        piv = min(piv, is ? s : INT_MAX);
+                    }
+                }
+            piv = min(piv, __shfl_xor(piv, 32, 64));
+            if (half == 0 && piv != INT_MAX) atomicMin(reinterpret_cast<int32_t*>(base + U.o_piv) + t, piv);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) cand += __shfl_xor(cand, o, 64);
+        if (lane == 0 && cand) atomicAdd(&s_cand, cand);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && s_cand) atomicAdd(reinterpret_cast<uint32_t*>(base) + SU_CAND, (uint32_t)s_cand);
+}
+
+// ------------------------------------------------------------------------------------------------
+// Products of whole rows.  A piece is 16 bytes; the last one is pulled back into the row and what it repeats is cleared.
+template <typename In> __device__ inline u32x4 screen_mask(u32x4 v, int cut);
+template <> __device__ inline u32x4 screen_mask<uint16_t>(u32x4 v, int cut) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        v[i] = 2 * i + 1 < cut ? 0u : 2 * i < cut ? v[i] & 0xFFFF0000u : v[i];
+    return v;
+}
+template <> __device__ inline u32x4 screen_mask<float>(u32x4 v, int cut) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = i < cut ? 0u : v[i];
+    return v;
+}
+template <typename In> __device__ inline float screen_dot(u32x4 a, u32x4 b, float s);
+template <> __device__ inline float screen_dot<float>(u32x4 a, u32x4 b, float s) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s = fmaf(__uint_as_float(a[i]), __uint_as_float(b[i]), s);
+    return s;
+}
+template <> __device__ inline float screen_dot<uint16_t>(u32x4 a, u32x4 b, float s) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const uint32_t a0 = a[0], a1 = a[1], a2 = a[2], a3 = a[3], b0 = b[0], b1 = b[1], b2 = b[2], b3 = b[3];
+    s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a0), __builtin_bit_cast(bf16x2, b0), s, false);
+    s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a1), __builtin_bit_cast(bf16x2, b1), s, false);
+    s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a2), __builtin_bit_cast(bf16x2, b2), s, false);
+    s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a3), __builtin_bit_cast(bf16x2, b3), s, false);
+    return s;
+}
+
+// <x, y>, <x, x> and <y, y> by LPR neighbouring lanes (li: this lane's place among them); every lane gets the sums.
+// Four pieces of each row are requested before the first is used.
+template <typename In, int LPR>
+__device__ inline void screen_products(const In* x, const In* y, bool two, int d, int li, float* xy, float* xx, float* yy) {
+    constexpr int EPP = 16 / (int)sizeof(In), UN = 4;
+    const int np = (d + EPP - 1) / EPP;
+    float sxy = 0.f, sxx = 0.f, syy = 0.f;
+    for (int p0 = li; p0 < np; p0 += LPR * UN) {
+        u32x4 a[UN], b[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int e = min(min(p0 + u * LPR, np - 1) * EPP, d - EPP);
+            a[u] = *reinterpret_cast<const u32x4_any*>(x + e);
+        }
+        if (two) {
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const int e = min(min(p0 + u * LPR, np - 1) * EPP, d - EPP);
+                b[u] = *reinterpret_cast<const u32x4_any*>(y + e);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int pc = p0 + u * LPR;
+            if (pc < np) {
+                const int cut = pc * EPP - min(pc * EPP, d - EPP);
+                const u32x4 va = cut > 0 ? screen_mask<In>(a[u], cut) : a[u];
+                sxx = screen_dot<In>(va, va, sxx);
+                if (two) {
+                    sxy = screen_dot<In>(va, b[u], sxy);
+                    const u32x4 vb = cut > 0 ? screen_mask<In>(b[u], cut) : b[u];
+                    syy = screen_dot<In>(vb, vb, syy);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int o = LPR / 2; o > 0; o >>= 1) {
+        sxy += __shfl_xor(sxy, o, 64);
+        sxx += __shfl_xor(sxx, o, 64);
+        syy += __shfl_xor(syy, o, 64);
+    }
+    *xy = sxy;
+    *xx = sxx;
+    *yy = syy;
+}
+
+__device__ inline float screen_cos(float xy, float xx, float yy) {
+    const float ix = xx > 0.f ? 1.0f / sqrtf(xx) : 0.f, iy = yy > 0.f ? 1.0f / sqrtf(yy) : 0.f;
+    return (fabsf(xy) * ix) * iy;                             // a zero row normalises to zero: all its cosines are 0
+}
+
+// k_screen_exact: norm of every row, product with its pivot, cluster.  HBM: X once; the pivots' rows (few) come from the L2s.
+constexpr int EXACT_ROWS = 16;                                // rows per workgroup
+template <typename In, int LPR>
+__global__ __launch_bounds__(256) void k_screen_exact(ScreenParams p, int row_blocks) {
+    __shared__ uint32_t s_pairs, s_flags;
+    const ScreenUnit U(p.T, p.nch);
+    const int unit = blockIdx.x / row_blocks, rb = blockIdx.x - unit * row_blocks;
+    int layer, group;
+    char* base = screen_unit(p, U, unit, &layer, &group);
+    const In* X = screen_x<In>(p, layer, group);
+    const int32_t* piv = reinterpret_cast<const int32_t*>(base + U.o_piv);
+    int32_t* size = reinterpret_cast<int32_t*>(base + U.o_size);
+    float* rho = reinterpret_cast<float*>(base + U.o_rho);
+    uint16_t* cl = reinterpret_cast<uint16_t*>(base + U.o_cl);
+    if (threadIdx.x == 0) { s_pairs = 0u; s_flags = 0u; }
+    __syncthreads();
+    const int li = threadIdx.x & (LPR - 1);
+    for (int r = threadIdx.x / LPR; r < EXACT_ROWS; r += 256 / LPR) {
+        const int t = rb * EXACT_ROWS + r;
+        if (t >= p.T) break;
+        const int q = piv[t];
+        float xy, xx, yy;
+        screen_products<In, LPR>(X + (size_t)t * (size_t)p.ld, X + (size_t)q * (size_t)p.ld, q != t, p.d, li, &xy, &xx, &yy);
+        if (li == 0) {
+            const float r2 = xx > 0.f ? rho[t] / xx : 1.f;    // (a zero row has no cosines: nothing to bound)
+            rho[t] = r2;
+            uint32_t fl = r2 < p.f2 ? (uint32_t)SF_LOW : 0u;
+            int c = t;
+            if (q != t && screen_cos(xy, xx, yy) >= p.cos_tight) {
+                c = q;
+                if (piv[q] != q) fl |= SF_MESH;               // the pivot may not be a member of its own cluster
+                atomicAdd(&s_pairs, (uint32_t)atomicAdd(size + q, 1) + 1u);   // pairs with the pivot and with earlier arrivals
+            }
+            cl[t] = (uint16_t)c;
+            if (fl) atomicOr(&s_flags, fl);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t* hdr = reinterpret_cast<uint32_t*>(base);
+        if (s_pairs) atomicAdd(hdr + SU_PAIRS, s_pairs);
+        if (s_flags) atomicOr(hdr + SU_FLAGS, s_flags);
+    }
+}
+
+// k_screen_rest: the candidates that no cluster explains.  Units without any (the counts agree) are left at once.
+template <typename In>
+__global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) {
+    __shared__ int s_n;
+    __shared__ uint32_t s_pair[SCREEN_TILE_PAIRS];
+    __shared__ float s_rho[256];
+    __shared__ uint16_t s_cl[256];
+    const ScreenUnit U(p.T, p.nch);
+    const int units = p.G * p.L, unit = (int)blockIdx.x % units;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    int layer, group;
+    char* base = screen_unit(p, U, unit, &layer, &group);
+    uint32_t* hdr = reinterpret_cast<uint32_t*>(base);
+    const uint32_t flags = hdr[SU_FLAGS];
+    if (flags == 0u && hdr[SU_CAND] == hdr[SU_PAIRS]) return;
+    const bool low = (flags & SF_LOW) != 0u;
+    const In* X = screen_x<In>(p, layer, group);
+    const float* rho = reinterpret_cast<const float*>(base + U.o_rho);
+    const uint16_t* cl = reinterpret_cast<const uint16_t*>(base + U.o_cl);
+    uint32_t* edge = reinterpret_cast<uint32_t*>(base + U.o_edge);
+    for (int tile = (int)blockIdx.x / units; tile < ntile; tile += (int)gridDim.x / units) {
+        int sb, tb;
+        screen_blocks(tile, &sb, &tb);
+        __syncthreads();
+        if (tid == 0) s_n = __hip_atomic_load(hdr + SU_DENSE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? -1 : 0;
+        {
+            const int tok = min(tid < 128 ? sb * 128 + tid : tb * 128 + tid - 128, p.T - 1);
+            s_rho[tid] = fminf(rho[tok], 1.f);
+            s_cl[tid] = cl[tok];
+        }
+        __syncthreads();
+        if (s_n < 0) break;                               // given up already (uniform)
+        f32x16 acc[2][2];
+        const ScreenTile me = screen_tile(reinterpret_cast<const uint8_t*>(base + U.o_z), p.T, p.nch, sb, tb, acc);
+        if (me.any) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const int tl = me.t0 - tb * 128 + b * 32 + l32, t = tb * 128 + tl;
+                const float rt = s_rho[128 + tl];
+                const int ct = s_cl[128 + tl];
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const int sl = me.s0 - sb * 128 + a * 32 + (i & 3) + 4 * half + 8 * (i >> 2), s = sb * 128 + sl;
+                        bool near = fabsf(acc[a][b][i]) >= p.kap;
+                        if (low) {                        // some row holds little in its sketch: the pair's own bound
+                            const float rs = s_rho[sl];
+                            near |= p.kap1 * sqrtf(rs * rt) + sqrtf((1.f - rs) * (1.f - rt)) + 1e-5f >= p.safe;
+                        }
+                        if (__builtin_amdgcn_ballot_w64(near) != 0ull) {
+                            if (near && s < t && t < p.T && s_cl[sl] != ct) {
+                                const int n = atomicAdd(&s_n, 1);
+                                if (n < SCREEN_TILE_PAIRS) s_pair[n] = (uint32_t)s << 16 | (uint32_t)t;
+                            }
+                        }
+                    }
+            }
+        }
+        __syncthreads();
+        const int n = s_n;
+        if (n > SCREEN_TILE_PAIRS) {                      // no saving in listing these (uniform)
+            if (tid == 0) __hip_atomic_store(hdr + SU_DENSE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            break;
+        }
+        for (int k = tid >> 6; k < n; k += 4) {           // one wave per pair
+            const uint32_t e = s_pair[k];
+            const int s = (int)(e >> 16), t = (int)(e & 0xFFFFu);
+            float xy, xx, yy;
+            screen_products<In, 64>(X + (size_t)t * (size_t)p.ld, X + (size_t)s * (size_t)p.ld, true, p.d, lane, &xy, &xx, &yy);
+            if (lane == 0 && screen_cos(xy, xx, yy) >= p.thr) {
+                const uint32_t at = atomicAdd(hdr + SU_EDGES, 1u);
+                if (at < (uint32_t)U.edge_cap) edge[at] = e;
+                else __hip_atomic_store(hdr + SU_DENSE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// k_screen_chain: the layers, one after the other, on clusters and edges.  One workgroup per sequence; thread tid owns the
+// U consecutive tokens from U tid on, their membership stays in registers from layer to layer, the next layer's clusters
+// are requested before this layer's are used.  Without edges a layer is: every inherited token puts its id under an integer
+// minimum of its cluster (the earliest inherited member is the only valid one), barrier, every token looks its cluster up,
+// ranks from ballots, one more barrier.  Cluster slots carry a layer stamp that falls from layer to layer, so they need no
+// clearing.
+struct ChainParams {
+    ScreenParams s;
+    int earlier_only;
+    int32_t* idx;              // row 0 of the call's outputs (sequence 0); rows T apart
+    int32_t* counts;
+    unsigned long long* ops;
+    int32_t* adds;             // may be NULL
+    int32_t* removes;          // may be NULL
+    long long list_gs, counts_gs, ops_gs;   // elements between sequences
+};
+
+template <int THREADS, int U>
+__global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
+    extern __shared__ __align__(16) char lds[];
+    __shared__ __align__(16) int scratch[64];
+    const ScreenParams& p = c.s;
+    const ScreenUnit SU(p.T, p.nch);
+    const int tid = threadIdx.x, T = p.T, g = blockIdx.x;
+    uint32_t* slot = reinterpret_cast<uint32_t*>(lds);        // [T] stamp << 14 | earliest inherited member of the cluster
+    uint8_t* mark = reinterpret_cast<uint8_t*>(slot + T);     // [T] bits: 1 inherited, 2 hit by an earlier inherited one, 4 valid, 8 covered
+    int32_t* meta = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(p.meta) + (long long)g * p.area_gs);
+    if (meta[META_PROGRESS] != p.first) return;               // an earlier layer is left to the other path
+    char* area = p.area + (long long)g * p.area_gs;
+    int32_t* idx = c.idx + (long long)g * c.list_gs;
+    int32_t* adds = c.adds ? c.adds + (long long)g * c.list_gs : nullptr;
+    int32_t* removes = c.removes ? c.removes + (long long)g * c.list_gs : nullptr;
+    int32_t* counts = c.counts + (long long)g * c.counts_gs;
+    unsigned long long* ops = c.ops + (long long)g * c.ops_gs;
+
+    for (int t = tid; t < T; t += THREADS) { slot[t] = 0xFFFFFFFFu; mark[t] = 0; }
+    bool in[U];
+    int r = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) in[u] = false;
+    if (p.first > 0) {                                        // go on from the set an earlier launch left
+        __syncthreads();
+        r = counts[(size_t)(p.first - 1) * 4];
+        for (int j = tid; j < r; j += THREADS) mark[idx[(size_t)(p.first - 1) * T + j]] = 1;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u) in[u] = U * tid + u < T && mark[U * tid + u] != 0;
+    }
+    uint16_t nx[U];
+    uint32_t nx_edges, nx_dense;
+    auto request = [&](int i) {
+        const char* unit = area + (long long)min(i, p.L - 1) * SU.bytes;
+        nx_edges = reinterpret_cast<const uint32_t*>(unit)[SU_EDGES];
+        nx_dense = reinterpret_cast<const uint32_t*>(unit)[SU_DENSE];
+        const uint16_t* cl = reinterpret_cast<const uint16_t*>(unit + SU.o_cl);
+#pragma unroll
+        for (int u = 0; u < U; ++u) nx[u] = cl[min(U * tid + u, T - 1)];
+    };
+    request(0);
+    __syncthreads();
+    int i = 0;
+    for (; i < p.L; ++i) {
+        int cid[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) cid[u] = nx[u];
+        const uint32_t n_edge = nx_edges;
+        const uint32_t* edge = reinterpret_cast<const uint32_t*>(area + (long long)i * SU.bytes + SU.o_edge);
+        if (nx_dense) break;                                  // uniform
+        request(i + 1);
+        const bool full = p.first + i == 0;
+        const uint32_t stamp = (uint32_t)(0x3FFFE - i) << 14;   // (the empty slot's own stamp is 0x3FFFF)
+        bool f[3][U];                                         // in R^(l+1) | added | removed
+        if (full) {                                           // Definition 2.2: no earlier token within the threshold
+            if (n_edge) {
+                for (uint32_t e = tid; e < n_edge; e += THREADS) mark[edge[e] & 0xFFFFu] = 2;
+                __syncthreads();
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int t = U * tid + u;
+                const bool hit = n_edge && t < T && (mark[t] & 2);
+                f[0][u] = t < T && cid[u] == t && !hit;       // (a cluster's pivot is earlier than its other members)
+                f[1][u] = f[2][u] = false;
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (in[u]) atomicMin(&slot[cid[u]], stamp | (uint32_t)(U * tid + u));
+            if (n_edge) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (U * tid + u < T) mark[U * tid + u] = in[u] ? 1 : 0;
+                __syncthreads();
+                // step 5 along edges: an earlier inherited token hits a later one (only bit 1 is read, only bit 2 set here)
+                for (uint32_t e = tid; e < n_edge; e += THREADS) {
+                    const uint32_t v = edge[e];
+                    const int s = (int)(v >> 16), t = (int)(v & 0xFFFFu);
+                    if ((mark[s] & 1) && (mark[t] & 1)) mark[t] = 3;
+                }
+            }
+            __syncthreads();
+            bool valid[U];
+            uint32_t low[U];                                  // earliest inherited member of the token's cluster (or none)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int t = U * tid + u;
+                const uint32_t v = slot[min(cid[u], T - 1)];
+                low[u] = (v & 0xFFFFC000u) == stamp ? v & 0x3FFFu : 0xFFFFFFFFu;
+                valid[u] = in[u] && low[u] == (uint32_t)t && !(n_edge && mark[t] == 3);   // step 5
+            }
+            if (n_edge) {                                     // steps 7-8 along edges
+                __syncthreads();
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (U * tid + u < T) mark[U * tid + u] = valid[u] ? 4 : 0;
+                __syncthreads();
+#pragma unroll
+                for (int u = 0; u < U; ++u)                   // the cluster's earliest inherited member covers only if valid
+                    if (!in[u] && low[u] != 0xFFFFFFFFu && mark[low[u]] != 4) low[u] = 0xFFFFFFFFu;
+                __syncthreads();
+                for (uint32_t e = tid; e < n_edge; e += THREADS) {
+                    const uint32_t v = edge[e];
+                    const int s = (int)(v >> 16), t = (int)(v & 0xFFFFu);
+                    if (mark[s] & 4) { if (!(mark[t] & 4)) mark[t] = 8; }             // (valid tokens keep their mark)
+                    if ((mark[t] & 4) && !c.earlier_only) { if (!(mark[s] & 4)) mark[s] = 8; }
+                }
+                __syncthreads();
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int t = U * tid + u;
+                bool covered = low[u] != 0xFFFFFFFFu && !(c.earlier_only && low[u] > (uint32_t)t);
+                if (n_edge && t < T) covered |= mark[t] == 8;
+                f[1][u] = t < T && !in[u] && !covered;        // step 9
+                f[2][u] = in[u] && !valid[u];
+                f[0][u] = valid[u] || f[1][u];                // step 10
+            }
+        }
+        int below[3], tot[3];
+        block_rank3<THREADS, U>(f, below, tot, scratch);
+        const size_t row = (size_t)(p.first + i);
+        int o_idx = below[0], o_add = below[1], o_rem = below[2];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int t = U * tid + u;
+            if (f[0][u]) idx[row * T + o_idx++] = t;
+            if (f[1][u] && adds) adds[row * T + o_add++] = t;
+            if (f[2][u] && removes) removes[row * T + o_rem++] = t;
+            in[u] = f[0][u];
+        }
+        if (tid == 0) {
+            const unsigned long long TT = (unsigned long long)T, rr = (unsigned long long)r;
+            *reinterpret_cast<int4*>(counts + row * 4) = full ? int4{tot[0], tot[0], 0, ADA_OK} : int4{tot[0], tot[1], tot[2], ADA_OK};
+            ops[row] = full ? TT * TT : rr * rr + (TT - rr) * (unsigned long long)(r - tot[2]);   // Table 6 / eq. (6)
+        }
+        r = tot[0];
+        if (n_edge) {
+            __syncthreads();
+            for (int t = tid; t < T; t += THREADS) mark[t] = 0;
+            __syncthreads();
+        }
+    }
+    if (tid == 0) meta[META_PROGRESS] = p.first + i;
+}
+
+// ------------------------------------------------------------------------------------------------
+// k_cascade_rest: the layers that the chain left (the first dense one and all after it), on the tiles of k_cascade_fused,
+// in one launch that leaves at once when there are none.  Work items (layer, worker) are handed out in order by a counter,
+// and an item waits for the previous layer's set before it starts: every item of an earlier layer is by then with a
+// workgroup that runs, so the wait ends however few workgroups are resident, and nothing is assumed about that.  Layer 0
+// is a step that inherits every token: Algorithm 1's step 5 on the identity list is Definition 2.2.
+struct RestParams {
+    FusedParams f;             // shape, threshold, workspace of sequence 0; the per-layer pointers are set in the kernel
+    const void* X[SCREEN_MAX_LAYERS];
+    int first, n;              // layers first .. first + n - 1
+    int32_t* idx;              // row 0 of the call's outputs, as in ChainParams
+    int32_t* counts;
+    unsigned long long* ops;
+    int32_t* adds;
+    int32_t* removes;
+    int32_t* meta;
+    int spin_limit;
+};
+
+template <typename In, bool ALIGNED, int KG, bool DMA>
+__global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
+    extern __shared__ __align__(16) char lds[];
+    using G = FusedGeom<KG, DMA>;
+    __shared__ int s_item, s_word, s_last;
+    FusedParams p = rp.f;
+    const int T = p.T;
+    const int groups = p.groups > 1 ? p.groups : 1, g = (int)blockIdx.x % groups;
+    const int workers = p.groups > 1 ? p.wpg : p.grid;
+    int32_t* meta = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(rp.meta) + (long long)g * p.ws_gs);
+    const int done = meta[META_PROGRESS];
+    if (done >= rp.first + rp.n) return;
+    const int start = max(done, rp.first);
+    p.hits = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(p.hits) + (long long)g * p.ws_gs);
+    p.ticket = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(p.ticket) + (long long)g * p.ws_gs);
+    if (p.first) p.first = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(p.first) + (long long)g * p.ws_gs);
+    int32_t* idx0 = rp.idx + (long long)g * p.list_gs;
+    int32_t* adds0 = rp.adds ? rp.adds + (long long)g * p.list_gs : nullptr;
+    int32_t* rem0 = rp.removes ? rp.removes + (long long)g * p.list_gs : nullptr;
+    int32_t* cnt0 = rp.counts + (long long)g * p.counts_gs;
+    unsigned long long* ops0 = rp.ops + (long long)g * p.ops_gs;
+    for (;;) {
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const int item = atomicAdd(meta + META_REST_QUEUE, 1);
+            const int i = start + item / workers;
+            int word = -1;                                    // set size inherited by layer i
+            if (i < rp.first + rp.n) {
+                if (i == 0) word = T;
+                else if (i == start) word = cnt0[(size_t)(i - 1) * 4];
+                else
+                    for (int n = 0; n < rp.spin_limit; ++n) {
+                        const int v = __hip_atomic_load(meta + META_REST_EPOCH, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        if ((v >> 15) == i - rp.first) { word = v & 0x7FFF; break; }
+                        __builtin_amdgcn_s_sleep(2);
+                    }
+                if (word < 0) cnt0[(size_t)i * 4 + 3] = ADA_ERR_DEVICE;   // (not reached: see above)
+            }
+            s_item = item;
+            s_word = word;
+        }
+        __syncthreads();
+        const int item = s_item, r = s_word;
+        const int i = start + item / workers, local = item - (item / workers) * workers;
+        if (i >= rp.first + rp.n || r < 0) break;             // uniform
+        const size_t row = (size_t)i * (size_t)T;
+        p.X = reinterpret_cast<const char*>(rp.X[i - rp.first]) + (long long)g * p.x_gs;
+        p.list_mode = i == 0 ? LIST_IDENTITY : LIST_COHERENT;
+        p.prev_idx = idx0 + row - (i == 0 ? 0 : T);
+        p.idx = idx0 + row;
+        p.adds = i > 0 && adds0 ? adds0 + row : nullptr;
+        p.removes = i > 0 && rem0 ? rem0 + row : nullptr;
+        p.counts = cnt0 + (size_t)i * 4;
+        p.gram_ops = ops0 + i;
+        const bool r_ok = r >= 1 && r <= T;
+        if (r_ok) fused_step_tiles<In, ALIGNED, KG, DMA>(p, r, lds, (unsigned)local, (unsigned)workers);
+        const int jq = min((int)threadIdx.x, T - 1);
+        const int q0 = list_at(p, jq), qp0 = list_at(p, max(jq - 1, 0));
+        drain_stores();
+        __syncthreads();
+        if (threadIdx.x == 0) s_last = atomicAdd(p.ticket, 1) == workers - 1 ? 1 : 0;
+        __syncthreads();
+        if (s_last) {                                         // uniform
+            if (threadIdx.x == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            __syncthreads();
+            const int r_new = fused_update<G::THREADS>(p, r, r_ok, q0, qp0, lds + G::META, reinterpret_cast<int*>(lds + G::OFF_SCAN));
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                __hip_atomic_store(meta + META_REST_EPOCH, ((i + 1 - rp.first) << 15) | (r_new & 0x7FFF), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    }
+    // the last workgroup of the sequence to leave puts the counters back to zero
+    if (threadIdx.x == 0 && atomicAdd(meta + META_REST_LEFT, 1) == workers - 1) {
+        __hip_atomic_store(meta + META_REST_QUEUE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(meta + META_REST_EPOCH, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(meta + META_REST_LEFT, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(meta + META_PROGRESS, rp.first + rp.n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}

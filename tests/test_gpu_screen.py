@@ -1,0 +1,113 @@
+"""The layer loops on the graph of near pairs (csrc/ada_screen.hpp) against the float64 oracle, layer by layer on the
+library's own previous set: tile edges, ragged and unaligned rows, rows and pairs that the bound cannot exclude, pairs
+that no cluster explains, and layers that are left to the tiles."""
+import os
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2605_03110_amd as pa
+from paper_2605_03110_amd import workloads as wl
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+import parity  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def activations(kind, T, d, L, dtype, seed):
+    """L host matrices.  clusters: the usual recipe; loose: members of a cluster lie at all angles up to and beyond the
+    threshold's; common: every pair's cosine is about 0.95 (no bound on a part of the row excludes it); collapsed: all
+    tokens within the threshold of each other; outliers: a few columns hold most of some rows; signs: duplicates, negated
+    duplicates and zero rows."""
+    rng = np.random.default_rng(seed)
+    if kind == "clusters":
+        return wl.layer_list(wl.small(T=T, d=d, K=max(1, T // 6), L=L, dtype=dtype, seed=seed, p=0.1))
+    K = max(1, T // 6)
+    C = rng.standard_normal((K, d))
+    C /= np.linalg.norm(C, axis=1, keepdims=True)
+    out = []
+    for _ in range(L):
+        a = rng.integers(0, K, T)
+        e = rng.standard_normal((T, d)) / np.sqrt(d)
+        if kind == "loose":
+            X = C[a] + e * rng.uniform(0.0, 0.13, (T, 1))
+        elif kind == "common":
+            X = C[0] + 0.22 * e
+        elif kind == "collapsed":
+            X = C[0] + 0.004 * e
+        elif kind == "outliers":
+            X = C[a] + 0.004 * e
+            rows = rng.random(T) < 0.05
+            X[np.ix_(rows, [d - 3, d // 2])] += 40.0 * rng.choice([-1.0, 1.0], (int(rows.sum()), 2))
+        else:
+            X = C[a] * rng.choice([-1.0, 1.0], (T, 1))
+            X[rng.random(T) < 0.1] = 0.0
+        out.append(wl.to_dtype(X.astype(np.float32), dtype))
+    return out
+
+
+def check(xs_cpu, tau, idx, counts, ops, adds, removes, flags, what):
+    """One sequence's outputs (host) against the oracle; correlations come from the single calls on the same inputs."""
+    T = xs_cpu[0].shape[0]
+    prev = None
+    for l, x in enumerate(xs_cpu):
+        r, na, nr, status = (int(v) for v in counts[l])
+        assert status == 0, "%s layer %d status %d" % (what, l, status)
+        got = dict(idx=idx[l, :r].numpy(), r=r, n_adds=na, n_removes=nr, gram_ops=int(ops[l]))
+        if l == 0:
+            single = pa.fetch(pa.ada_select_full(x.to(DEV), tau))
+            got["gamma"], got["mask"] = single["gamma"], np.isin(np.arange(T), got["idx"]).astype(np.uint8)
+            parity.check_full(x, tau, got, "%s layer 0" % what)
+            assert (na, nr, got["gram_ops"]) == (r, 0, T * T)
+        else:
+            got["adds"], got["removes"] = adds[l, :na].numpy(), removes[l, :nr].numpy()
+            single = pa.ada_cascade_step(x.to(DEV), tau, torch.from_numpy(prev).to(DEV), flags=flags)
+            got["gamma"] = single["gamma"].cpu().numpy()
+            parity.check_cascade(x, tau, prev, got, flags=oracle.CROSS_EARLIER_ONLY if flags else 0, what="%s layer %d" % (what, l))
+        prev = got["idx"]
+
+
+CASES = [
+    # kind, T, d, L, dtype, tau
+    ("clusters", 1, 64, 3, "bf16", 0.1), ("clusters", 127, 64, 3, "f32", 0.1), ("clusters", 128, 200, 3, "bf16", 0.1),
+    ("clusters", 129, 1001, 3, "bf16", 0.1),      # rows of odd length: nothing is aligned
+    ("clusters", 700, 770, 4, "f32", 0.3), ("clusters", 1025, 4096, 3, "bf16", 0.1), ("clusters", 2050, 192, 3, "bf16", 0.2),
+    ("clusters", 130, 64, 70, "bf16", 0.1),       # more layers than one launch takes
+    ("clusters", 4100, 128, 3, "bf16", 0.1), ("clusters", 8200, 72, 2, "f32", 0.1),
+    ("loose", 300, 256, 4, "bf16", 0.1), ("loose", 1000, 1024, 3, "f32", 0.1), ("loose", 600, 768, 3, "bf16", 0.3),
+    ("common", 300, 512, 3, "bf16", 0.1), ("common", 301, 320, 3, "f32", 0.1), ("collapsed", 500, 768, 3, "bf16", 0.1),
+    ("outliers", 400, 1024, 3, "bf16", 0.1), ("outliers", 900, 2048, 3, "f32", 0.1),
+    ("signs", 333, 256, 3, "bf16", 0.1),
+]
+
+
+@pytest.mark.parametrize("kind,T,d,L,dtype,tau", CASES)
+def test_layer_loop_on_the_graph_of_near_pairs(kind, T, d, L, dtype, tau):
+    print("[case] screened layers: %s T=%d d=%d L=%d %s tau=%g" % (kind, T, d, L, dtype, tau), flush=True)
+    xs_cpu = activations(kind, T, d, L, dtype, seed=T + d)
+    xs = [x.to(DEV) for x in xs_cpu]
+    ws = pa.workspace(T, DEV)
+    for flags in ((0, pa.FLAG_CROSS_EARLIER_ONLY) if T <= 700 else (0,)):
+        for _ in range(2):                        # the second call finds the workspace as the first left it
+            res = pa.ada_cascade_layers(xs, tau, ws=ws, flags=flags)
+        check(xs_cpu, tau, *(res[k].cpu() for k in ("idx", "counts", "gram_ops", "adds", "removes")), flags, kind)
+    single = pa.ada_select_full(xs[0], tau, ws=ws)     # ... and so do the other calls
+    assert int(single["counts"][0]) == int(res["counts"][0, 0])
+
+
+@pytest.mark.parametrize("kinds,T,d,dtype", [(("clusters", "clusters", "clusters"), 200, 96, "bf16"), (("clusters", "common", "loose"), 260, 320, "bf16"),
+                                             (("outliers", "signs"), 131, 1001, "f32")])
+def test_stacked_sequences_that_need_different_treatment(kinds, T, d, dtype):
+    print("[case] screened groups: %s T=%d d=%d %s" % (kinds, T, d, dtype), flush=True)
+    L = 3
+    per = [activations(k, T, d, L, dtype, seed=17 + i) for i, k in enumerate(kinds)]
+    xg = [torch.stack([p[l] for p in per]).to(DEV) for l in range(L)]
+    res = pa.ada_cascade_layers_grouped(xg, 0.1, want_lists=True)
+    for g, kind in enumerate(kinds):
+        check(per[g], 0.1, *(res[k][g].cpu() for k in ("idx", "counts", "gram_ops", "adds", "removes")), 0, "group %d %s" % (g, kind))
