@@ -227,12 +227,29 @@ def _check_x(X: torch.Tensor):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+def _stream(stream) -> int:
+    return torch.cuda.current_stream().cuda_stream if stream is None else stream.cuda_stream
+
+
+def _check_layers(Xs: Sequence[torch.Tensor], check):
+    """Every layer like the first one: the calls over layers look at dozens of tensors, and looking is most of what they
+    cost on the host, so only a tensor that differs at first sight is looked at closely."""
+    X0 = Xs[0]
+    check(X0)
+    shape, stride, dtype = X0.shape, X0.stride(), X0.dtype
+    for X in Xs:
+        if X.shape != shape or X.stride() != stride or X.dtype is not dtype or not X.is_cuda:
+            check(X)
+            if X.shape != shape or X.stride()[:-1] != stride[:-1] or X.dtype is not dtype:
+                raise ValueError("all layers must share shape, dtype and strides")
+
+
+def _ptrs(ts: Sequence[torch.Tensor]):
+    """A host array of device pointers."""
+    return (ctypes.c_void_p * len(ts))(*[t.data_ptr() for t in ts])
 
 
 def ada_select_full(X: torch.Tensor, tau: float, *, ws: Optional[torch.Tensor] = None, stream=None,
@@ -389,10 +406,7 @@ def ada_cascade_layers(Xs: Sequence[torch.Tensor], tau: float, *, want_lists: bo
     L = len(Xs)
     if L < 1:
         raise ValueError("need at least one layer")
-    for X in Xs:
-        _check_x(X)
-        if X.shape != Xs[0].shape or X.dtype != Xs[0].dtype or X.stride(0) != Xs[0].stride(0):
-            raise ValueError("all layers must share shape, dtype and leading dimension")
+    _check_layers(Xs, _check_x)
     T, d = Xs[0].shape
     dev = Xs[0].device
     ws = workspace(T, dev) if ws is None else ws
@@ -403,7 +417,7 @@ def ada_cascade_layers(Xs: Sequence[torch.Tensor], tau: float, *, want_lists: bo
         if want_lists:
             out["adds"] = torch.empty((L, T), dtype=torch.int32, device=dev)
             out["removes"] = torch.empty((L, T), dtype=torch.int32, device=dev)
-    ptrs = (ctypes.c_void_p * L)(*[X.data_ptr() for X in Xs])
+    ptrs = _ptrs(Xs)
     rc = lib().ada_cascade_layers(ptrs, L, T, d, Xs[0].stride(0), _dtype_code(Xs[0]), float(tau), _ptr(out["idx"]),
                                   _ptr(out["counts"]), _ptr(out["gram_ops"]), _ptr(out.get("adds")),
                                   _ptr(out.get("removes")), _ptr(ws), ws.numel(), _stream(stream), int(flags))
@@ -537,10 +551,7 @@ def ada_cascade_layers_grouped(Xgs: Sequence[torch.Tensor], tau: float, *, want_
     L = len(Xgs)
     if L < 1:
         raise ValueError("need at least one layer")
-    for Xg in Xgs:
-        _check_xg(Xg)
-        if Xg.shape != Xgs[0].shape or Xg.dtype != Xgs[0].dtype or Xg.stride() != Xgs[0].stride():
-            raise ValueError("all layers must share shape, dtype and strides")
+    _check_layers(Xgs, _check_xg)
     G, T, d = Xgs[0].shape
     dev = Xgs[0].device
     ws = workspace_batched(T, G, dev) if ws is None else ws
@@ -552,7 +563,7 @@ def ada_cascade_layers_grouped(Xgs: Sequence[torch.Tensor], tau: float, *, want_
             out["adds"] = torch.empty((G, L, T), dtype=torch.int32, device=dev)
             out["removes"] = torch.empty((G, L, T), dtype=torch.int32, device=dev)
     g = AdaGroups(G, Xgs[0].stride(0) if G > 1 else d, 0, 0, 0)
-    ptrs = (ctypes.c_void_p * L)(*[X.data_ptr() for X in Xgs])
+    ptrs = _ptrs(Xgs)
     rc = lib().ada_cascade_layers_grouped(ctypes.byref(g), ptrs, L, T, d, Xgs[0].stride(1), _dtype_code(Xgs[0]), float(tau),
                                           _ptr(out["idx"]), _ptr(out["counts"]), _ptr(out["gram_ops"]),
                                           _ptr(out.get("adds")), _ptr(out.get("removes")), _ptr(ws), ws.numel(),
@@ -574,10 +585,10 @@ def ada_pipeline_layers(Xs: Sequence[torch.Tensor], Qs: Sequence[torch.Tensor], 
     if L < 1 or not (len(Qs) == len(Ks) == len(Vs) == L):
         raise ValueError("need the same number (>= 1) of X, Q, K and V matrices")
     X0 = Xs[0]
-    for M in list(Xs) + list(Qs) + list(Ks) + list(Vs):
-        _check_x(M)
-        if M.shape != X0.shape or M.dtype != X0.dtype or M.stride(0) != X0.stride(0) or M.device != X0.device:
-            raise ValueError("all matrices must share shape, dtype, leading dimension and device")
+    everything = [*Xs, *Qs, *Ks, *Vs]
+    _check_layers(everything, _check_x)
+    if any(M.device != X0.device for M in everything):
+        raise ValueError("all matrices must share their device")
     T, d = X0.shape
     if d % H != 0:
         raise ValueError("d must be a multiple of the head count")
@@ -590,11 +601,10 @@ def ada_pipeline_layers(Xs: Sequence[torch.Tensor], Qs: Sequence[torch.Tensor], 
                    assign=torch.empty((L, T), dtype=torch.int32, device=dev),
                    info=torch.empty((L, 8), dtype=torch.int32, device=dev),
                    out=[torch.empty((T, d), dtype=torch.float32, device=dev) for _ in range(L)])
-    arr = lambda ms: (ctypes.c_void_p * L)(*[m.data_ptr() for m in ms])
-    sp = lambda s_: None if s_ is None else ctypes.c_void_p(s_.cuda_stream)
-    rc = lib().ada_pipeline_layers(arr(Xs), arr(Qs), arr(Ks), arr(Vs), L, T, H, d // H, X0.stride(0), _dtype_code(X0),
+    sp = lambda s_: None if s_ is None else s_.cuda_stream
+    rc = lib().ada_pipeline_layers(_ptrs(Xs), _ptrs(Qs), _ptrs(Ks), _ptrs(Vs), L, T, H, d // H, X0.stride(0), _dtype_code(X0),
                                    float(tau), _ptr(out["idx"]), _ptr(out["counts"]), _ptr(out["gram_ops"]),
-                                   _ptr(out["assign"]), _ptr(out["info"]), arr(out["out"]), out["out"][0].stride(0),
+                                   _ptr(out["assign"]), _ptr(out["info"]), _ptrs(out["out"]), out["out"][0].stride(0),
                                    _ptr(ws), ws.numel(), sp(stream_sel), sp(stream_attn), _stream(stream), int(flags))
     if rc != OK:
         raise AdaError(rc, "ada_pipeline_layers")
@@ -610,10 +620,7 @@ def ada_cascade_layers_adaptive(Xs: Sequence[torch.Tensor], tau0: float, kappa: 
     L = len(Xs)
     if L < 1:
         raise ValueError("need at least one layer")
-    for X in Xs:
-        _check_x(X)
-        if X.shape != Xs[0].shape or X.dtype != Xs[0].dtype or X.stride(0) != Xs[0].stride(0):
-            raise ValueError("all layers must share shape, dtype and leading dimension")
+    _check_layers(Xs, _check_x)
     T, d = Xs[0].shape
     dev = Xs[0].device
     ws = workspace(T, dev) if ws is None else ws
@@ -625,7 +632,7 @@ def ada_cascade_layers_adaptive(Xs: Sequence[torch.Tensor], tau0: float, kappa: 
         out["adds"] = torch.empty((L, T), dtype=torch.int32, device=dev)
         out["removes"] = torch.empty((L, T), dtype=torch.int32, device=dev)
     ctl = AdaTauControl(float(kappa), float(eta_target), float(tau_min), float(tau_max))
-    ptrs = (ctypes.c_void_p * L)(*[X.data_ptr() for X in Xs])
+    ptrs = _ptrs(Xs)
     rc = lib().ada_cascade_layers_adaptive(ptrs, L, T, d, Xs[0].stride(0), _dtype_code(Xs[0]), float(tau0), ctypes.byref(ctl),
                                            _ptr(out["idx"]), _ptr(out["counts"]), _ptr(out["gram_ops"]),
                                            _ptr(out.get("adds")), _ptr(out.get("removes")), _ptr(out["tau"]),

@@ -1419,9 +1419,12 @@ int run_cascade_pass(const void* const* X_layers, int first, int n, int T, int d
 
 template <typename In, int LPR>
 hipError_t launch_screen_exact(const ScreenParams& sp, hipStream_t st) {
-    const int rb = (sp.T + EXACT_ROWS - 1) / EXACT_ROWS;
+    // four rows per lane group where that leaves enough workgroups to fill the chip, one where it does not
+    const int rows = 256 / LPR, units = sp.G * sp.L;
+    const int passes = (long long)(sp.T / (4 * rows)) * units >= 2048 ? 4 : 1;
+    const int rb = (sp.T + rows * passes - 1) / (rows * passes), total = rb * units;
     ProfScope ps(ADA_K_SCREEN, st);
-    hipLaunchKernelGGL((k_screen_exact<In, LPR>), dim3((unsigned)(rb * sp.G * sp.L)), dim3(256), 0, st, sp, rb);
+    hipLaunchKernelGGL((k_screen_exact<In, LPR>), dim3((unsigned)((total + 7) / 8 * 8)), dim3(256), 0, st, sp, passes, rb, total);
     return hipGetLastError();
 }
 
@@ -1430,11 +1433,23 @@ template <typename In>
 hipError_t launch_screen(const ScreenParams& sp, hipStream_t st) {
     const int units = sp.G * sp.L;
     const int rb = (sp.T + SKETCH_ROWS - 1) / SKETCH_ROWS;
-    const int nb = (sp.T + 127) / 128, ntile = nb * (nb + 1) / 2, total = ntile * units;
+    const int nb = (sp.T + 127) / 128, ntile = nb * (nb + 1) / 2;
     {
         ProfScope ps(ADA_K_SCREEN, st);
         hipLaunchKernelGGL((k_screen_sketch<In>), dim3((unsigned)(rb * units)), dim3(256), 0, st, sp, rb);
-        hipLaunchKernelGGL(k_screen_pairs, dim3((unsigned)((total + 7) / 8 * 8)), dim3(256), 0, st, sp, ntile, total);
+    }
+    {
+        const PairItems it(sp.T, units);
+        const int total = it.per_unit * units;
+        const dim3 grid((unsigned)((total + 7) / 8 * 8));
+        ProfScope ps(ADA_K_SCREEN, st);
+        switch (sp.nch) {
+            case 1: hipLaunchKernelGGL(k_screen_pairs<1>, grid, dim3(256), 0, st, sp, it, total); break;
+            case 2: hipLaunchKernelGGL(k_screen_pairs<2>, grid, dim3(256), 0, st, sp, it, total); break;
+            case 3: hipLaunchKernelGGL(k_screen_pairs<3>, grid, dim3(256), 0, st, sp, it, total); break;
+            case 4: hipLaunchKernelGGL(k_screen_pairs<4>, grid, dim3(256), 0, st, sp, it, total); break;
+            default: hipLaunchKernelGGL(k_screen_pairs<0>, grid, dim3(256), 0, st, sp, it, total);
+        }
     }
     // four pieces of a row in flight per lane, at least eight lanes (a cache line) side by side
     const int np = (sp.d * (int)sizeof(In) + 15) / 16;
@@ -1450,18 +1465,17 @@ hipError_t launch_screen(const ScreenParams& sp, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <int THREADS, int U>
+template <int THREADS, int U, bool TWO>
 hipError_t launch_screen_chain(const ChainParams& c, hipStream_t st) {
-    const int lds = c.s.T * 5 + 16;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_screen_chain<THREADS, U>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, THREADS * U * 5 + 16);
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_screen_chain<THREADS, U, TWO>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, CHAIN_LDS);
     });
     if (attr_err != hipSuccess) return attr_err;
     ProfScope ps(ADA_K_UPDATE, st);
-    hipLaunchKernelGGL((k_screen_chain<THREADS, U>), dim3((unsigned)c.s.G), dim3(THREADS), lds, st, c);
+    hipLaunchKernelGGL((k_screen_chain<THREADS, U, TWO>), dim3((unsigned)c.s.G), dim3(THREADS), ChainGeom(c.s.T, c.s.L, TWO).bytes, st, c);
     return hipGetLastError();
 }
 
@@ -1513,22 +1527,7 @@ int run_layers_screened(const ScreenPlan& plan, const void* const* X_layers, int
     c.idx = idx; c.counts = counts; c.ops = reinterpret_cast<unsigned long long*>(gram_ops); c.adds = adds; c.removes = removes;
     c.list_gs = list_gs; c.counts_gs = counts_gs; c.ops_gs = ops_gs;
 
-    long long fit = (long long)ws_screen_bytes(T) / U.bytes;   // layers at a time, in launches of equal size
-    if (fit > SCREEN_MAX_LAYERS) fit = SCREEN_MAX_LAYERS;
-    const int batches = (int)((L + fit - 1) / fit), per = (L + batches - 1) / batches;
-    for (int first = 0; first < L; first += per) {
-        sp.first = first;
-        sp.L = L - first < per ? L - first : per;
-        for (int i = 0; i < SCREEN_MAX_LAYERS; ++i) sp.X[i] = i < sp.L ? X_layers[first + i] : nullptr;
-        hipError_t e = dtype == ADA_BF16 ? launch_screen<uint16_t>(sp, st) : launch_screen<float>(sp, st);
-        if (e != hipSuccess) return ADA_ERR_DEVICE;
-        e = T <= 256 ? launch_screen_chain<256, 1>(c, st) : T <= 512 ? launch_screen_chain<512, 1>(c, st)
-          : T <= 1024 ? launch_screen_chain<1024, 1>(c, st) : T <= 2048 ? launch_screen_chain<1024, 2>(c, st)
-          : T <= 4096 ? launch_screen_chain<1024, 4>(c, st) : T <= 8192 ? launch_screen_chain<1024, 8>(c, st)
-                      : launch_screen_chain<1024, 16>(c, st);
-        if (e != hipSuccess) return ADA_ERR_DEVICE;
-    }
-    // what the chain left
+    // what the chain leaves
     RestParams rp;
     rp.f = {nullptr, ld, T, d, nullptr, nullptr, T, sp.thr, c.earlier_only, w.hits, hit_words(T), nullptr, w.meta + META_TICKET,
             nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr, nullptr, LIST_COHERENT, cascade_tile_pick()};
@@ -1540,17 +1539,28 @@ int run_layers_screened(const ScreenPlan& plan, const void* const* X_layers, int
         rp.f.x_gs = x_gs; rp.f.list_gs = list_gs; rp.f.counts_gs = counts_gs; rp.f.ops_gs = ops_gs;
         rp.f.ws_gs = sp.area_gs;
     }
-    rp.idx = idx; rp.counts = counts; rp.ops = c.ops; rp.adds = adds; rp.removes = removes; rp.meta = w.meta;
     rp.spin_limit = 1 << 24;
     const char* no_dma = dev_switch("ADA_NO_DMA");
     bool base16 = true;
     for (int l = 0; l < L; ++l) base16 = base16 && (uintptr_t)X_layers[l] % 16 == 0;
     const long long ld_seen = ((G > 1 && x_gs % 16 != 0) || !base16) ? 1 : ld;
-    for (int first = 0; first < L; first += SCREEN_MAX_LAYERS) {
-        rp.first = first;
-        rp.n = L - first < SCREEN_MAX_LAYERS ? L - first : SCREEN_MAX_LAYERS;
-        for (int i = 0; i < SCREEN_MAX_LAYERS; ++i) rp.X[i] = i < rp.n ? X_layers[first + i] : nullptr;
-        const hipError_t e = dispatch(dtype, X_layers[0], ld_seen, d, [&](auto v) {
+
+    long long fit = (long long)ws_screen_bytes(T) / U.bytes;   // layers at a time, in launches of equal size
+    if (fit > SCREEN_MAX_LAYERS) fit = SCREEN_MAX_LAYERS;
+    const int batches = (int)((L + fit - 1) / fit), per = (L + batches - 1) / batches;
+    for (int first = 0; first < L; first += per) {
+        sp.first = first;
+        sp.L = L - first < per ? L - first : per;
+        for (int i = 0; i < SCREEN_MAX_LAYERS; ++i) sp.X[i] = i < sp.L ? X_layers[first + i] : nullptr;
+        hipError_t e = dtype == ADA_BF16 ? launch_screen<uint16_t>(sp, st) : launch_screen<float>(sp, st);
+        if (e != hipSuccess) return ADA_ERR_DEVICE;
+        e = T <= 256 ? launch_screen_chain<256, 1, true>(c, st) : T <= 512 ? launch_screen_chain<512, 1, true>(c, st)
+          : T <= 1024 ? launch_screen_chain<512, 2, true>(c, st) : T <= 2048 ? launch_screen_chain<512, 4, true>(c, st)
+          : T <= 4096 ? launch_screen_chain<512, 8, true>(c, st) : T <= 8192 ? launch_screen_chain<1024, 8, true>(c, st)
+                      : launch_screen_chain<1024, 16, false>(c, st);
+        if (e != hipSuccess) return ADA_ERR_DEVICE;
+        rp.c = c;
+        e = dispatch(dtype, X_layers[0], ld_seen, d, [&](auto v) {
             using V = decltype(v);
             using In = typename V::In;
             if constexpr (V::aligned) {

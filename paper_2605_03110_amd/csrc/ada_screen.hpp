@@ -32,6 +32,7 @@
 
 constexpr int SCREEN_MAX_LAYERS = 64;                         // layers per launch (their pointers travel as arguments)
 constexpr int SCREEN_TILE_PAIRS = 256;                        // unexplained candidates a 128 x 128 tile may hold before its layer is dense
+constexpr int CHAIN_LDS = 160 * 1024 - 2048;                  // what the walk may use of a CU's LDS
 constexpr float SCREEN_SCALE = 256.f;                         // sketches are stored as 8-bit floats of 256 x (unit vector)
 
 // header of a unit (one layer of one sequence); zeroed by the sketch launch
@@ -82,9 +83,12 @@ inline bool screen_plan(int d, float tau, ScreenPlan* out) {
     return false;
 }
 
-// Memory of a unit inside the workspace's screen area, in bytes from the unit's start.
+// Memory of a unit inside the workspace's screen area, in bytes from the unit's start.  Sketches lie in the order in which
+// a wave loads them as matrix operands: blocks of 32 rows, in a block column group after column group, a group as two
+// runs of 64 lanes x 16 bytes (lane l: row l % 32, columns 32 (l / 32) + 16 run .. + 15), so that every operand load is one
+// kilobyte without gaps.
 struct ScreenUnit {
-    int o_piv, o_size, o_rho, o_cl, o_edge, o_z, edge_cap;
+    int o_piv, o_size, o_rho, o_cl, o_mask, o_edge, o_z, edge_cap;
     long long bytes;
     __host__ __device__ ScreenUnit(int T, int nch) {
         const long long t4 = (long long)align_up((size_t)T * 4, 256);
@@ -94,9 +98,10 @@ struct ScreenUnit {
         o_size = (int)o; o += t4;
         o_rho = (int)o; o += t4;
         o_cl = (int)o; o += (long long)align_up((size_t)T * 2, 256);
+        o_mask = (int)o; o += (long long)align_up((size_t)((T + 63) / 64) * 16, 256);   // the set, and the one inherited by a launch's first layer
         o_edge = (int)o; o += (long long)align_up((size_t)edge_cap * 4, 256);
-        o_z = (int)o; o += (long long)align_up((size_t)T * 64 * nch, 256);
-        bytes = o;
+        o_z = (int)o; o += (long long)((T + 31) / 32) * nch * 2048;
+        bytes = (long long)align_up((size_t)o, 256);
     }
 };
 
@@ -198,14 +203,15 @@ __global__ __launch_bounds__(256) void k_screen_sketch(ScreenParams p, int row_b
     ss += __shfl_xor(ss, 4, 64);
     const float sc = ss > 0.f ? SCREEN_SCALE / sqrtf(ss) : 0.f;
     if (t >= p.T) return;
-    uint8_t* z = reinterpret_cast<uint8_t*>(base + U.o_z) + (size_t)t * (size_t)(64 * p.nch) + c8 * 8;
+    uint8_t* z = reinterpret_cast<uint8_t*>(base + U.o_z) + (size_t)(t >> 5) * (size_t)(2048 * p.nch) +
+                 ((c8 >> 1) & 1) * 1024 + ((c8 >> 2) * 32 + (t & 31)) * 16 + (c8 & 1) * 8;
     auto put = [&](int j, const float (&x)[8]) {
         int lo = 0, hi = 0;
         lo = __builtin_amdgcn_cvt_pk_fp8_f32(x[0] * sc, x[1] * sc, lo, false);
         lo = __builtin_amdgcn_cvt_pk_fp8_f32(x[2] * sc, x[3] * sc, lo, true);
         hi = __builtin_amdgcn_cvt_pk_fp8_f32(x[4] * sc, x[5] * sc, hi, false);
         hi = __builtin_amdgcn_cvt_pk_fp8_f32(x[6] * sc, x[7] * sc, hi, true);
-        *reinterpret_cast<int2*>(z + j * 64) = int2{lo, hi};
+        *reinterpret_cast<int2*>(z + j * 2048) = int2{lo, hi};
     };
 #pragma unroll
     for (int j = 0; j < KEEP; ++j)
@@ -223,62 +229,18 @@ __global__ __launch_bounds__(256) void k_screen_sketch(ScreenParams p, int row_b
 }
 
 // ------------------------------------------------------------------------------------------------
-// Sketch products of a 128 x 128 tile: four waves in a 2 x 2 grid of 64 x 64, fragments straight from global memory (a
-// tile's sketches are a few tens of KB that its waves share through the L1; there is too little to multiply for staging
-// through LDS to pay).  The order of a fragment's columns does not matter as long as both sides use the same one: lane l
-// holds row l % 32, columns 32 (l / 32) .. + 31 of a group.
+// Sketch products.  The order of an operand's columns does not matter as long as both sides use the same one.
 typedef int i32x8 __attribute__((ext_vector_type(8)));
-
-struct ScreenTile { int s0, t0; bool any; };                  // this wave's first rows; any: some s < t
-__device__ inline ScreenTile screen_tile(const uint8_t* Z, int T, int nch, int sb, int tb, f32x16 (&acc)[2][2]) {
-    const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int s0 = sb * 128 + (wave >> 1) * 64, t0 = tb * 128 + (wave & 1) * 64;
-    const ScreenTile me = {s0, t0, s0 <= t0 && t0 < T};
-    if (!me.any) return me;                                   // (above the diagonal, or past the end)
-    const size_t n1 = (size_t)(64 * nch);
-    const uint8_t *pa[2], *pb[2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        pa[a] = Z + (size_t)min(s0 + a * 32 + l32, T - 1) * n1 + half * 32;
-        pb[a] = Z + (size_t)min(t0 + a * 32 + l32, T - 1) * n1 + half * 32;
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
-    }
-    i32x8 fa[2][2], fb[2][2];
-    auto rd = [&](int set, int j) {
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            const u32x4* qa = reinterpret_cast<const u32x4*>(pa[a] + j * 64);
-            const u32x4* qb = reinterpret_cast<const u32x4*>(pb[a] + j * 64);
-            const u32x4 a0 = qa[0], a1 = qa[1], b0 = qb[0], b1 = qb[1];
-            fa[set][a] = i32x8{(int)a0[0], (int)a0[1], (int)a0[2], (int)a0[3], (int)a1[0], (int)a1[1], (int)a1[2], (int)a1[3]};
-            fb[set][a] = i32x8{(int)b0[0], (int)b0[1], (int)b0[2], (int)b0[3], (int)b1[0], (int)b1[1], (int)b1[2], (int)b1[3]};
-        }
-    };
-    auto mma = [&](int set) {
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b)                       // (formats 0: e4m3 on both sides; block scales 127 = 1)
-                acc[a][b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa[set][a], fb[set][b], acc[a][b], 0, 0, 0,
-                                                                            0x7F7F7F7F, 0, 0x7F7F7F7F);
-    };
-    rd(0, 0);
-    for (int j = 0; j < nch; j += 2) {
-        if (j + 1 < nch) rd(1, j + 1);
-        mma(0);
-        if (j + 1 < nch) {
-            if (j + 2 < nch) rd(0, j + 2);
-            mma(1);
-        }
-    }
-    return me;
+__device__ inline i32x8 screen_operand(const u32x4* z) {      // this lane's 32 bytes of a (row block, column group)
+    const u32x4 a = z[0], b = z[64];
+    return i32x8{(int)a[0], (int)a[1], (int)a[2], (int)a[3], (int)b[0], (int)b[1], (int)b[2], (int)b[3]};
+}
+__device__ inline void screen_mma(f32x16& acc, const i32x8& a, const i32x8& b) {
+    // (formats 0: e4m3 on both sides; block scales 127 = 1)
+    acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc, 0, 0, 0, 0x7F7F7F7F, 0, 0x7F7F7F7F);
 }
 
-// lower-triangular 128-block tile number -> blocks 0 <= sb <= tb
+// lower-triangular block number -> blocks 0 <= sb <= tb
 __device__ inline void screen_blocks(int tile, int* sb, int* tb) {
     int n = (int)((sqrtf(8.f * (float)tile + 1.f) - 1.f) * 0.5f);
     while ((n + 1) * (n + 2) / 2 <= tile) ++n;
@@ -287,50 +249,188 @@ __device__ inline void screen_blocks(int tile, int* sb, int* tb) {
     *sb = tile - n * (n + 1) / 2;
 }
 
-// k_screen_pairs: every token's earliest candidate, and how many candidate pairs there are.  Tiles of one unit are dealt to
-// one XCD (workgroup b runs on XCD b % 8), so that its sketches are read by one L2.
-__global__ __launch_bounds__(256) void k_screen_pairs(ScreenParams p, int ntile, int total) {
+// The candidates of a 32 x 32 block, shifted into `bits` from the right: register i of the accumulator holds a row that
+// grows with i, so of what is shifted in the highest bit is the earliest row.  Two instructions per product (the sign of
+// kappa - |product|), no branches and no condition registers: at the redundancy this method is for, nearly every block
+// holds a candidate.
+__device__ inline uint32_t screen_bits(uint32_t bits, const f32x16& acc, float kap) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(kap - fabsf(acc[i])), 31u);
+    return bits;
+}
+__device__ inline int screen_row(int i) { return (i & 3) + 8 * ((i >> 2) & 3); }   // row of register i (lanes of the first half)
+
+// Work items of a unit: strips of 256 tokens, each against its earlier tokens in pieces.  A piece is 256 x `wide` tokens, or
+// 256 / `cut` of them: long pieces spend less of their time on starting up (a piece of 256 took about half of it for
+// that), short ones are needed to fill the chip.  Strips come in groups of `wide` with the same number of pieces.
+struct PairItems {
+    int wide, cut, per_unit;
+    __host__ __device__ PairItems(int T, int units) {
+        const int nb = (T + 255) / 256;
+        const long long tiles = (long long)nb * (nb + 1) / 2 * units;
+        wide = tiles >= 12288 ? 4 : tiles >= 6144 ? 2 : 1;
+        cut = tiles >= 1024 ? 1 : tiles >= 512 ? 2 : 4;
+        const int q = (nb + wide - 1) / wide;
+        per_unit = wide * (q * (q + 1) / 2) * cut;
+    }
+    // item -> strip, first block of 32 earlier tokens, number of blocks (clipped by the caller)
+    __device__ void get(int i, int* tb, int* s_lo, int* sblk) const {
+        if (cut > 1) {
+            int a, b;
+            screen_blocks(i / cut, &a, &b);
+            *tb = b;
+            *sblk = 8 / cut;
+            *s_lo = a * 8 + (i % cut) * (8 / cut);
+            return;
+        }
+        int a, q;
+        screen_blocks(i / wide, &a, &q);                      // group q: wide (q + 1) items from wide q (q + 1) / 2 on
+        const int r = i - wide * (q * (q + 1) / 2);
+        *tb = wide * q + r / (q + 1);
+        *sblk = 8 * wide;
+        *s_lo = (r % (q + 1)) * 8 * wide;
+    }
+};
+
+// k_screen_pairs: every token's earliest candidate, and how many candidate pairs there are.  A workgroup holds 256 tokens
+// (64 per wave: two 32-row blocks) and walks over blocks of 32 earlier tokens; a wave keeps its tokens' sketches in
+// registers (NCH > 0) and reads the earlier tokens' one block ahead.  Its four waves read the same blocks at about the
+// same time, so they come from the L1; there is nothing to stage and no barrier.  The work of one unit is dealt to one
+// XCD (workgroup b runs on XCD b % 8), so that its sketches are read by one L2.
+// NCH: column groups of the sketch (1 .. 4), or 0: any number, both operands read as they are used.
+// (the second launch bound keeps the accumulators in ordinary registers: the epilogue reads each of them once)
+template <int NCH>
+__global__ __launch_bounds__(256, NCH == 4 ? 2 : 3) void k_screen_pairs(ScreenParams p, PairItems it, int total) {
     __shared__ int s_cand;
     const int per = (total + 7) >> 3;
     const int w = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
     if (w >= total || (int)(blockIdx.x >> 3) >= per) return;
     const ScreenUnit U(p.T, p.nch);
-    const int unit = w / ntile;
-    int layer, group, sb, tb;
+    const int unit = w / it.per_unit;
+    int layer, group, tb, s_lo, sblk;
     char* base = screen_unit(p, U, unit, &layer, &group);
-    screen_blocks(w - unit * ntile, &sb, &tb);
+    it.get(w - unit * it.per_unit, &tb, &s_lo, &sblk);
     if (threadIdx.x == 0) s_cand = 0;
     __syncthreads();
-    f32x16 acc[2][2];
-    const ScreenTile me = screen_tile(reinterpret_cast<const uint8_t*>(base + U.o_z), p.T, p.nch, sb, tb, acc);
+    const int T = p.T, nch = NCH > 0 ? NCH : p.nch;
     const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
-    if (me.any) {
-        int cand = 0;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int nblk = (T + 31) >> 5;
+    const int tb0 = tb * 8 + wave * 2;                        // this wave's first row block
+    const int s_hi = min(s_lo + sblk, min(tb0 + 2, nblk));
+    const u32x4* Z = reinterpret_cast<const u32x4*>(base + U.o_z) + lane;     // a (block, group) is 128 of these
+    int cand[2] = {0, 0}, piv[2] = {INT_MAX, INT_MAX};
+    if (tb0 < nblk && s_lo < s_hi) {
+        constexpr int HELD = NCH > 0 ? NCH : 1;
+        i32x8 fb[2][HELD], fa[2][HELD];
+        const int tb1 = min(tb0 + 1, nblk - 1);
+        auto rd = [&](i32x8 (&f)[HELD], int blk) {
+            if constexpr (NCH > 0) {
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int t = me.t0 + b * 32 + l32;
-            int piv = INT_MAX;
+                for (int j = 0; j < NCH; ++j) f[j] = screen_operand(Z + (size_t)(blk * NCH + j) * 128);
+            }
+        };
+        rd(fb[0], tb0);
+        rd(fb[1], tb1);
+        rd(fa[0], s_lo);
+        uint32_t bits[2];
+        auto block = [&](int set, int s) {                    // earlier tokens of block s, in set
+            if constexpr (NCH > 0) rd(fa[set ^ 1], min(s + 1, s_hi - 1));
+            f32x16 acc[2];
 #pragma unroll
-            for (int a = 0; a < 2; ++a)
+            for (int b = 0; b < 2; ++b)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const bool near = fabsf(acc[a][b][i]) >= p.kap;
-                    if (__builtin_amdgcn_ballot_w64(near) != 0ull) {     // few registers of a block hold one: scalar branch
-                        const int s = me.s0 + a * 32 + (i & 3) + 4 * half + 8 * (i >> 2);
-                        const bool is = near && s < t && t < p.T;
-                        cand += is ? 1 : 0;
-                        piv = min(piv, is ? s : INT_MAX);
-                    }
+                for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
+            if constexpr (NCH > 0) {
+#pragma unroll
+                for (int j = 0; j < NCH; ++j)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) screen_mma(acc[b], fa[set][j], fb[b][j]);
+            } else {
+                for (int j = 0; j < nch; ++j) {
+                    const i32x8 a = screen_operand(Z + (size_t)(s * nch + j) * 128);
+                    const i32x8 b0 = screen_operand(Z + (size_t)(tb0 * nch + j) * 128), b1 = screen_operand(Z + (size_t)(tb1 * nch + j) * 128);
+                    screen_mma(acc[0], a, b0);
+                    screen_mma(acc[1], a, b1);
                 }
-            piv = min(piv, __shfl_xor(piv, 32, 64));
-            if (half == 0 && piv != INT_MAX) atomicMin(reinterpret_cast<int32_t*>(base + U.o_piv) + t, piv);
+            }
+#pragma unroll
+            for (int b = 0; b < 2; ++b) bits[b] = screen_bits(bits[b], acc[b], p.kap);
+        };
+        // what blocks s and s + 1 (upper and lower half of a word) hold; diag: rows that are not earlier have to be taken out
+        auto take = [&](int s, bool diag) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const int row0 = s * 32 + 4 * half, t = (tb0 + b) * 32 + l32;
+                uint32_t v = bits[b];
+                if (diag) {
+#pragma unroll
+                    for (int i = 0; i < 32; ++i) v &= row0 + (i >> 4) * 32 + screen_row(i) < t ? 0xFFFFFFFFu : ~(0x80000000u >> i);
+                }
+                cand[b] += __popc(v);
+                const int i = __clz((int)v);
+                piv[b] = min(piv[b], v ? row0 + (i >> 4) * 32 + screen_row(i) : INT_MAX);
+            }
+        };
+        int s = s_lo;
+        for (; s + 1 < min(s_hi, tb0); s += 2) {              // whole blocks of earlier tokens
+            bits[0] = bits[1] = 0u;
+            block(0, s);
+            block(1, s + 1);
+            take(s, false);
+        }
+        for (; s < s_hi; s += 2) {                            // the last one or two, on the diagonal or not
+            bits[0] = bits[1] = 0u;
+            block(0, s);
+            if (s + 1 < s_hi) block(1, s + 1);
+            else { bits[0] <<= 16; bits[1] <<= 16; }
+            take(s, true);
         }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) cand += __shfl_xor(cand, o, 64);
-        if (lane == 0 && cand) atomicAdd(&s_cand, cand);
+        for (int b = 0; b < 2; ++b) {
+            const int t = (tb0 + b) * 32 + l32;
+            const int q = min(piv[b], __shfl_xor(piv[b], 32, 64));
+            if (half == 0 && t < T && q != INT_MAX) atomicMin(reinterpret_cast<int32_t*>(base + U.o_piv) + t, q);
+            if (t >= T) cand[b] = 0;                          // (rows of the last block that do not exist)
+        }
+        int n = cand[0] + (tb0 + 1 < nblk ? cand[1] : 0);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
+        if (lane == 0 && n) atomicAdd(&s_cand, n);
     }
     __syncthreads();
     if (threadIdx.x == 0 && s_cand) atomicAdd(reinterpret_cast<uint32_t*>(base) + SU_CAND, (uint32_t)s_cand);
+}
+
+// Sketch products of a 128 x 128 tile: four waves in a 2 x 2 grid of 64 x 64.
+struct ScreenTile { int s0, t0; bool any; };                  // this wave's first rows; any: some s < t
+__device__ inline ScreenTile screen_tile(const char* z, int T, int nch, int sb, int tb, f32x16 (&acc)[2][2]) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int s0 = sb * 128 + (wave >> 1) * 64, t0 = tb * 128 + (wave & 1) * 64;
+    const ScreenTile me = {s0, t0, s0 <= t0 && t0 < T};
+    if (!me.any) return me;                                   // (above the diagonal, or past the end)
+    const u32x4* Z = reinterpret_cast<const u32x4*>(z) + lane;
+    const int last = (T - 1) >> 5;
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+    for (int j = 0; j < nch; ++j) {
+        i32x8 fa[2], fb[2];
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            fa[a] = screen_operand(Z + (size_t)(min((s0 >> 5) + a, last) * nch + j) * 128);
+            fb[a] = screen_operand(Z + (size_t)(min((t0 >> 5) + a, last) * nch + j) * 128);
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) screen_mma(acc[a][b], fa[a], fb[b]);
+    }
+    return me;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -364,7 +464,8 @@ template <> __device__ inline float screen_dot<uint16_t>(u32x4 a, u32x4 b, float
 }
 
 // <x, y>, <x, x> and <y, y> by LPR neighbouring lanes (li: this lane's place among them); every lane gets the sums.
-// Four pieces of each row are requested before the first is used.
+// Four pieces of each row are requested before the first is used (eight leave fewer waves room: 465 us instead of 444 at
+// 32 units of T = 8192, d = 4096).
 template <typename In, int LPR>
 __device__ inline void screen_products(const In* x, const In* y, bool two, int d, int li, float* xy, float* xx, float* yy) {
     constexpr int EPP = 16 / (int)sizeof(In), UN = 4;
@@ -415,13 +516,16 @@ __device__ inline float screen_cos(float xy, float xx, float yy) {
     return (fabsf(xy) * ix) * iy;                             // a zero row normalises to zero: all its cosines are 0
 }
 
-// k_screen_exact: norm of every row, product with its pivot, cluster.  HBM: X once; the pivots' rows (few) come from the L2s.
-constexpr int EXACT_ROWS = 16;                                // rows per workgroup
+// k_screen_exact: norm of every row, product with its pivot, cluster.  HBM: X once.  Every XCD takes a contiguous range of
+// the rows of all units, so that a unit's pivots (a few hundred rows, a few MB) are read into one L2 and not into eight.
 template <typename In, int LPR>
-__global__ __launch_bounds__(256) void k_screen_exact(ScreenParams p, int row_blocks) {
+__global__ __launch_bounds__(256) void k_screen_exact(ScreenParams p, int passes, int row_blocks, int total) {
     __shared__ uint32_t s_pairs, s_flags;
+    const int per = (total + 7) >> 3;
+    const int w = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if (w >= total || (int)(blockIdx.x >> 3) >= per) return;
     const ScreenUnit U(p.T, p.nch);
-    const int unit = blockIdx.x / row_blocks, rb = blockIdx.x - unit * row_blocks;
+    const int unit = w / row_blocks, rb = w - unit * row_blocks;
     int layer, group;
     char* base = screen_unit(p, U, unit, &layer, &group);
     const In* X = screen_x<In>(p, layer, group);
@@ -432,8 +536,8 @@ __global__ __launch_bounds__(256) void k_screen_exact(ScreenParams p, int row_bl
     if (threadIdx.x == 0) { s_pairs = 0u; s_flags = 0u; }
     __syncthreads();
     const int li = threadIdx.x & (LPR - 1);
-    for (int r = threadIdx.x / LPR; r < EXACT_ROWS; r += 256 / LPR) {
-        const int t = rb * EXACT_ROWS + r;
+    for (int k = 0; k < passes; ++k) {
+        const int t = (rb * passes + k) * (256 / LPR) + (int)threadIdx.x / LPR;
         if (t >= p.T) break;
         const int q = piv[t];
         float xy, xx, yy;
@@ -493,7 +597,7 @@ __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) 
         __syncthreads();
         if (s_n < 0) break;                               // given up already (uniform)
         f32x16 acc[2][2];
-        const ScreenTile me = screen_tile(reinterpret_cast<const uint8_t*>(base + U.o_z), p.T, p.nch, sb, tb, acc);
+        const ScreenTile me = screen_tile(base + U.o_z, p.T, p.nch, sb, tb, acc);
         if (me.any) {
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
@@ -505,7 +609,7 @@ __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) 
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
                         const int sl = me.s0 - sb * 128 + a * 32 + (i & 3) + 4 * half + 8 * (i >> 2), s = sb * 128 + sl;
-                        bool near = fabsf(acc[a][b][i]) >= p.kap;
+                        bool near = fabsf(acc[a][b][i]) > p.kap;
                         if (low) {                        // some row holds little in its sketch: the pair's own bound
                             const float rs = s_rho[sl];
                             near |= p.kap1 * sqrtf(rs * rt) + sqrtf((1.f - rs) * (1.f - rt)) + 1e-5f >= p.safe;
@@ -541,11 +645,13 @@ __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) 
 
 // ------------------------------------------------------------------------------------------------
 // k_screen_chain: the layers, one after the other, on clusters and edges.  One workgroup per sequence; thread tid owns the
-// U consecutive tokens from U tid on, their membership stays in registers from layer to layer, the next layer's clusters
-// are requested before this layer's are used.  Without edges a layer is: every inherited token puts its id under an integer
-// minimum of its cluster (the earliest inherited member is the only valid one), barrier, every token looks its cluster up,
-// ranks from ballots, one more barrier.  Cluster slots carry a layer stamp that falls from layer to layer, so they need no
-// clearing.
+// tokens tid + u THREADS, their membership stays in registers from layer to layer.  The clusters of as many layers as fit
+// are brought into LDS at once, so the walk itself does not touch memory.  Without edges a layer is: every inherited
+// token puts its id under an integer minimum of its cluster (the earliest inherited member is the only valid one), one
+// barrier, every token looks its cluster up, and the new set leaves as ballots (one bit per token).  Cluster slots carry a
+// layer stamp that falls from layer to layer, so they need no clearing, and there are two sets of them in turns (TWO), so
+// that one barrier per layer is enough.  Index lists, counts and Gram operations follow from the bits of a layer and the
+// one before: the launch behind writes them, for all layers at once.
 struct ChainParams {
     ScreenParams s;
     int earlier_only;
@@ -557,170 +663,279 @@ struct ChainParams {
     long long list_gs, counts_gs, ops_gs;   // elements between sequences
 };
 
-template <int THREADS, int U>
-__global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
-    extern __shared__ __align__(16) char lds[];
-    __shared__ __align__(16) int scratch[64];
-    const ScreenParams& p = c.s;
-    const ScreenUnit SU(p.T, p.nch);
-    const int tid = threadIdx.x, T = p.T, g = blockIdx.x;
-    uint32_t* slot = reinterpret_cast<uint32_t*>(lds);        // [T] stamp << 14 | earliest inherited member of the cluster
-    uint8_t* mark = reinterpret_cast<uint8_t*>(slot + T);     // [T] bits: 1 inherited, 2 hit by an earlier inherited one, 4 valid, 8 covered
-    int32_t* meta = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(p.meta) + (long long)g * p.area_gs);
-    if (meta[META_PROGRESS] != p.first) return;               // an earlier layer is left to the other path
-    char* area = p.area + (long long)g * p.area_gs;
-    int32_t* idx = c.idx + (long long)g * c.list_gs;
-    int32_t* adds = c.adds ? c.adds + (long long)g * c.list_gs : nullptr;
-    int32_t* removes = c.removes ? c.removes + (long long)g * c.list_gs : nullptr;
-    int32_t* counts = c.counts + (long long)g * c.counts_gs;
-    unsigned long long* ops = c.ops + (long long)g * c.ops_gs;
+constexpr int LIST_SCRATCH = 3 * 257 * 4;                     // LDS that writing a layer's lists takes
 
-    for (int t = tid; t < T; t += THREADS) { slot[t] = 0xFFFFFFFFu; mark[t] = 0; }
-    bool in[U];
-    int r = 0;
-#pragma unroll
-    for (int u = 0; u < U; ++u) in[u] = false;
-    if (p.first > 0) {                                        // go on from the set an earlier launch left
-        __syncthreads();
-        r = counts[(size_t)(p.first - 1) * 4];
-        for (int j = tid; j < r; j += THREADS) mark[idx[(size_t)(p.first - 1) * T + j]] = 1;
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < U; ++u) in[u] = U * tid + u < T && mark[U * tid + u] != 0;
+// LDS of the walk: cluster slots, marks (edges only), and the clusters of the layers in flight.
+struct ChainGeom {
+    int words, off_mark, off_layer, layer_bytes, layers, bytes;
+    __host__ __device__ ChainGeom(int T, int L, bool two) {
+        words = (T + 63) / 64;
+        const int Tp = words * 64;
+        off_mark = (two ? 2 : 1) * Tp * 4;
+        off_layer = off_mark + Tp;
+        layer_bytes = Tp * 2;
+        layers = (CHAIN_LDS - off_layer) / layer_bytes;
+        layers = layers < L ? layers : L;
+        bytes = off_layer + layers * layer_bytes;
+        bytes = bytes < LIST_SCRATCH ? LIST_SCRATCH : bytes;
     }
-    uint16_t nx[U];
-    uint32_t nx_edges, nx_dense;
-    auto request = [&](int i) {
-        const char* unit = area + (long long)min(i, p.L - 1) * SU.bytes;
-        nx_edges = reinterpret_cast<const uint32_t*>(unit)[SU_EDGES];
-        nx_dense = reinterpret_cast<const uint32_t*>(unit)[SU_DENSE];
-        const uint16_t* cl = reinterpret_cast<const uint16_t*>(unit + SU.o_cl);
+};
+
+// All waves' LDS operations done, and everybody here.  (A fenced barrier would also wait for the stores to memory.)
+__device__ inline void chain_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// One layer's lists, counts and Gram operations from the bits of its set and of the one before (any workgroup size up to
+// 1024; scratch: LIST_SCRATCH bytes of LDS).
+__device__ inline void screen_lists(const ChainParams& c, const ScreenUnit& SU, int l, int g, int* scratch) {
+    const ScreenParams& p = c.s;
+    const int T = p.T, words = (T + 63) >> 6, tid = threadIdx.x, lane = tid & 63;
+    const char* unit = p.area + (long long)g * p.area_gs + (long long)l * SU.bytes;
+    const unsigned long long* now = reinterpret_cast<const unsigned long long*>(unit + SU.o_mask);
+    const unsigned long long* was = l > 0 ? reinterpret_cast<const unsigned long long*>(unit - SU.bytes + SU.o_mask) : now + words;
+    const bool full = p.first + l == 0;
+    const size_t row = (size_t)(p.first + l);
+    int32_t* idx = c.idx + (long long)g * c.list_gs + row * T;
+    int32_t* adds = c.adds && !full ? c.adds + (long long)g * c.list_gs + row * T : nullptr;
+    int32_t* removes = c.removes && !full ? c.removes + (long long)g * c.list_gs + row * T : nullptr;
+    int* start = scratch;                                     // [3][words + 1]: members in the words before
+    if (tid < 64) {                                           // one wave: prefix sums over the words
+        int tot[3] = {0, 0, 0}, r_was = 0;
+        for (int w0 = 0; w0 < words; w0 += 64) {
+            const int w = w0 + lane;
+            const unsigned long long a = w < words ? now[w] : 0ull, b = w < words && !full ? was[w] : 0ull;
+            const unsigned long long m[3] = {a, a & ~b, b & ~a};
+            int rw = __popcll(b);
 #pragma unroll
-        for (int u = 0; u < U; ++u) nx[u] = cl[min(U * tid + u, T - 1)];
-    };
-    request(0);
-    __syncthreads();
-    int i = 0;
-    for (; i < p.L; ++i) {
-        int cid[U];
+            for (int k = 0; k < 3; ++k) {
+                const int pc = __popcll(m[k]);
+                int inc = pc;
 #pragma unroll
-        for (int u = 0; u < U; ++u) cid[u] = nx[u];
-        const uint32_t n_edge = nx_edges;
-        const uint32_t* edge = reinterpret_cast<const uint32_t*>(area + (long long)i * SU.bytes + SU.o_edge);
-        if (nx_dense) break;                                  // uniform
-        request(i + 1);
-        const bool full = p.first + i == 0;
-        const uint32_t stamp = (uint32_t)(0x3FFFE - i) << 14;   // (the empty slot's own stamp is 0x3FFFF)
-        bool f[3][U];                                         // in R^(l+1) | added | removed
-        if (full) {                                           // Definition 2.2: no earlier token within the threshold
-            if (n_edge) {
-                for (uint32_t e = tid; e < n_edge; e += THREADS) mark[edge[e] & 0xFFFFu] = 2;
-                __syncthreads();
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int t = U * tid + u;
-                const bool hit = n_edge && t < T && (mark[t] & 2);
-                f[0][u] = t < T && cid[u] == t && !hit;       // (a cluster's pivot is earlier than its other members)
-                f[1][u] = f[2][u] = false;
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (in[u]) atomicMin(&slot[cid[u]], stamp | (uint32_t)(U * tid + u));
-            if (n_edge) {
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (U * tid + u < T) mark[U * tid + u] = in[u] ? 1 : 0;
-                __syncthreads();
-                // step 5 along edges: an earlier inherited token hits a later one (only bit 1 is read, only bit 2 set here)
-                for (uint32_t e = tid; e < n_edge; e += THREADS) {
-                    const uint32_t v = edge[e];
-                    const int s = (int)(v >> 16), t = (int)(v & 0xFFFFu);
-                    if ((mark[s] & 1) && (mark[t] & 1)) mark[t] = 3;
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int x = __shfl_up(inc, o, 64);
+                    if (lane >= o) inc += x;
                 }
-            }
-            __syncthreads();
-            bool valid[U];
-            uint32_t low[U];                                  // earliest inherited member of the token's cluster (or none)
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int t = U * tid + u;
-                const uint32_t v = slot[min(cid[u], T - 1)];
-                low[u] = (v & 0xFFFFC000u) == stamp ? v & 0x3FFFu : 0xFFFFFFFFu;
-                valid[u] = in[u] && low[u] == (uint32_t)t && !(n_edge && mark[t] == 3);   // step 5
-            }
-            if (n_edge) {                                     // steps 7-8 along edges
-                __syncthreads();
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (U * tid + u < T) mark[U * tid + u] = valid[u] ? 4 : 0;
-                __syncthreads();
-#pragma unroll
-                for (int u = 0; u < U; ++u)                   // the cluster's earliest inherited member covers only if valid
-                    if (!in[u] && low[u] != 0xFFFFFFFFu && mark[low[u]] != 4) low[u] = 0xFFFFFFFFu;
-                __syncthreads();
-                for (uint32_t e = tid; e < n_edge; e += THREADS) {
-                    const uint32_t v = edge[e];
-                    const int s = (int)(v >> 16), t = (int)(v & 0xFFFFu);
-                    if (mark[s] & 4) { if (!(mark[t] & 4)) mark[t] = 8; }             // (valid tokens keep their mark)
-                    if ((mark[t] & 4) && !c.earlier_only) { if (!(mark[s] & 4)) mark[s] = 8; }
-                }
-                __syncthreads();
+                if (w < words) start[k * 257 + w] = tot[k] + inc - pc;
+                tot[k] += __builtin_amdgcn_readlane(inc, 63);
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int t = U * tid + u;
-                bool covered = low[u] != 0xFFFFFFFFu && !(c.earlier_only && low[u] > (uint32_t)t);
-                if (n_edge && t < T) covered |= mark[t] == 8;
-                f[1][u] = t < T && !in[u] && !covered;        // step 9
-                f[2][u] = in[u] && !valid[u];
-                f[0][u] = valid[u] || f[1][u];                // step 10
-            }
+            for (int o = 32; o > 0; o >>= 1) rw += __shfl_xor(rw, o, 64);
+            r_was += rw;
         }
-        int below[3], tot[3];
-        block_rank3<THREADS, U>(f, below, tot, scratch);
-        const size_t row = (size_t)(p.first + i);
-        int o_idx = below[0], o_add = below[1], o_rem = below[2];
+        if (lane == 0) {
+            const unsigned long long TT = (unsigned long long)T, rr = (unsigned long long)r_was;
+            *reinterpret_cast<int4*>(c.counts + (long long)g * c.counts_gs + row * 4) =
+                full ? int4{tot[0], tot[0], 0, ADA_OK} : int4{tot[0], tot[1], tot[2], ADA_OK};
+            c.ops[(long long)g * c.ops_gs + row] = full ? TT * TT : rr * rr + (TT - rr) * (rr - (unsigned long long)tot[2]);   // Table 6 / eq. (6)
+        }
+    }
+    __syncthreads();
+    for (int t = tid; t < words * 64; t += blockDim.x) {
+        const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+        const unsigned long long a = now[w], b = full ? 0ull : was[w];
+        auto put = [&](int32_t* dst, int k, unsigned long long m) {
+            if (dst && ((m >> lane) & 1ull))
+                dst[start[k * 257 + w] + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = t;
+        };
+        put(idx, 0, a);
+        put(adds, 1, a & ~b);
+        put(removes, 2, b & ~a);
+    }
+    __syncthreads();
+}
+
+// A layer that has edges (all threads; the marks are zero on entry, barriers inside; on return some marks are set).
+template <int THREADS, int U>
+__device__ inline void chain_edges(bool full, int earlier_only, uint32_t n_edge, const uint32_t* edge, uint32_t stamp,
+                                   uint32_t* slot, uint8_t* mark, const int (&cid)[U], unsigned long long (&in)[U], int T) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (full) {                                               // Definition 2.2: no earlier token within the threshold
+        for (uint32_t e = tid; e < n_edge; e += THREADS) mark[edge[e] & 0xFFFFu] = 2;
+        __syncthreads();
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int t = U * tid + u;
-            if (f[0][u]) idx[row * T + o_idx++] = t;
-            if (f[1][u] && adds) adds[row * T + o_add++] = t;
-            if (f[2][u] && removes) removes[row * T + o_rem++] = t;
-            in[u] = f[0][u];
+            const int t = u * THREADS + tid;
+            in[u] = __ballot(t < T && cid[u] == t && !(mark[min(t, T - 1)] & 2));
         }
-        if (tid == 0) {
-            const unsigned long long TT = (unsigned long long)T, rr = (unsigned long long)r;
-            *reinterpret_cast<int4*>(counts + row * 4) = full ? int4{tot[0], tot[0], 0, ADA_OK} : int4{tot[0], tot[1], tot[2], ADA_OK};
-            ops[row] = full ? TT * TT : rr * rr + (TT - rr) * (unsigned long long)(r - tot[2]);   // Table 6 / eq. (6)
+        __syncthreads();
+        return;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int t = u * THREADS + tid;
+        const bool inh = (in[u] >> lane) & 1ull;
+        if (inh) atomicMin(&slot[cid[u]], stamp | (uint32_t)t);
+        if (t < T) mark[t] = inh ? 1 : 0;
+    }
+    __syncthreads();
+    // step 5 along edges: an earlier inherited token hits a later one (only bit 1 is read, only bit 2 set here)
+    for (uint32_t e = tid; e < n_edge; e += THREADS) {
+        const uint32_t v = edge[e];
+        const int s = (int)(v >> 16), t = (int)(v & 0xFFFFu);
+        if ((mark[s] & 1) && (mark[t] & 1)) mark[t] = 3;
+    }
+    __syncthreads();
+    uint32_t low[U];                                          // earliest inherited member of the token's cluster (or none)
+    unsigned long long keep[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int t = u * THREADS + tid;
+        const uint32_t v = slot[cid[u]];
+        low[u] = (v & 0xFFFFC000u) == stamp ? v & 0x3FFFu : 0xFFFFFFFFu;
+        keep[u] = __ballot(((in[u] >> lane) & 1ull) && low[u] == (uint32_t)t && mark[min(t, T - 1)] != 3);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (u * THREADS + tid < T) mark[u * THREADS + tid] = (keep[u] >> lane) & 1ull ? 4 : 0;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u)                               // the cluster's earliest inherited member covers only if valid
+        if (low[u] != 0xFFFFFFFFu && mark[low[u]] != 4) low[u] = 0xFFFFFFFFu;
+    __syncthreads();
+    for (uint32_t e = tid; e < n_edge; e += THREADS) {        // steps 7-8 along edges
+        const uint32_t v = edge[e];
+        const int s = (int)(v >> 16), t = (int)(v & 0xFFFFu);
+        if (mark[s] & 4) { if (!(mark[t] & 4)) mark[t] = 8; }             // (valid tokens keep their mark)
+        if ((mark[t] & 4) && !earlier_only) { if (!(mark[s] & 4)) mark[s] = 8; }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int t = u * THREADS + tid;
+        const bool covered = (low[u] != 0xFFFFFFFFu && !(earlier_only && low[u] > (uint32_t)t)) || mark[min(t, T - 1)] == 8;
+        in[u] = keep[u] | (__ballot(t < T && !covered) & ~in[u]);        // steps 9 and 10
+    }
+    __syncthreads();
+}
+
+template <int THREADS, int U, bool TWO>
+__global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
+    extern __shared__ __align__(16) char lds[];
+    __shared__ uint32_t s_edges[SCREEN_MAX_LAYERS], s_dense[SCREEN_MAX_LAYERS];
+    const ScreenParams& p = c.s;
+    const ScreenUnit SU(p.T, p.nch);
+    const int tid = threadIdx.x, T = p.T, g = blockIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const ChainGeom CG(T, p.L, TWO);
+    const int Tp = CG.words * 64;
+    uint32_t* slots = reinterpret_cast<uint32_t*>(lds);       // [TWO ? 2 : 1][Tp] stamp << 14 | earliest inherited member
+    uint8_t* mark = reinterpret_cast<uint8_t*>(lds + CG.off_mark);   // bits: 1 inherited, 2 hit by an earlier inherited token, 4 valid, 8 covered
+    int32_t* meta = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(p.meta) + (long long)g * p.area_gs);
+    char* area = p.area + (long long)g * p.area_gs;
+    auto cl_of = [&](int k) { return reinterpret_cast<uint16_t*>(lds + CG.off_layer + k * CG.layer_bytes); };
+    auto mask_of = [&](int l) { return reinterpret_cast<unsigned long long*>(area + (long long)l * SU.bytes + SU.o_mask); };
+
+    const int progress = meta[META_PROGRESS];
+    if (tid < p.L) {
+        const uint32_t* hdr = reinterpret_cast<const uint32_t*>(area + (long long)tid * SU.bytes);
+        s_edges[tid] = hdr[SU_EDGES];
+        s_dense[tid] = hdr[SU_DENSE];
+    }
+    for (int t = tid; t < (TWO ? 2 : 1) * Tp; t += THREADS) slots[t] = 0xFFFFFFFFu;
+    for (int t = tid; t < Tp; t += THREADS) mark[t] = 0;
+    // membership, one bit per lane and u; a lane whose token does not exist is a member of nothing
+    unsigned long long in[U], exists[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        in[u] = 0ull;
+        exists[u] = __ballot(u * THREADS + tid < T);
+    }
+    if (p.first > 0) {                                        // go on from the set an earlier launch left
+        if (progress != p.first) return;
+        __syncthreads();
+        const int32_t* idx = c.idx + (long long)g * c.list_gs + (size_t)(p.first - 1) * T;
+        const int r = c.counts[(long long)g * c.counts_gs + (size_t)(p.first - 1) * 4];
+        for (int j = tid; j < r; j += THREADS) mark[idx[j]] = 1;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            in[u] = __ballot(u * THREADS + tid < T && mark[u * THREADS + tid] != 0);
+            const int w = u * (THREADS / 64) + wave;
+            if (lane == 0 && w < CG.words) mask_of(0)[CG.words + w] = in[u];
         }
-        r = tot[0];
-        if (n_edge) {
-            __syncthreads();
-            for (int t = tid; t < T; t += THREADS) mark[t] = 0;
-            __syncthreads();
+    }
+    int i = 0;
+    bool stop = false;
+    for (int i0 = 0; i0 < p.L && !stop; i0 += CG.layers) {
+        const int n = min(CG.layers, p.L - i0);
+        if (i0 > 0) __syncthreads();
+        {   // clusters of the coming layers (rows of the units are 256-byte aligned), eight loads in flight per thread
+            const int vpl = (T + 7) >> 3, total = n * vpl;
+            for (int v0 = tid; v0 < total; v0 += THREADS * 8) {
+                u32x4 x[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int v = min(v0 + e * THREADS, total - 1), k = v / vpl;
+                    x[e] = *reinterpret_cast<const u32x4*>(area + (long long)(i0 + k) * SU.bytes + SU.o_cl + (v - k * vpl) * 16);
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int v = min(v0 + e * THREADS, total - 1), k = v / vpl;
+                    *reinterpret_cast<u32x4*>(cl_of(k) + (v - k * vpl) * 8) = x[e];
+                }
+            }
         }
+        __syncthreads();
+        int cid[U];                                           // clusters of the layer at hand
+#pragma unroll
+        for (int u = 0; u < U; ++u) cid[u] = cl_of(0)[min(u * THREADS + tid, T - 1)];
+        for (int k = 0; k < n; ++k, ++i) {
+            if (s_dense[i]) { stop = true; break; }           // uniform
+            const uint32_t n_edge = s_edges[i];
+            const uint32_t stamp = (uint32_t)(0x3FFFE - i) << 14;   // (the empty slot's own stamp is 0x3FFFF)
+            uint32_t* slot = slots + (TWO && (i & 1) ? Tp : 0);
+            const uint16_t* next = cl_of(min(k + 1, n - 1));
+            if (n_edge) {
+                const uint32_t* edge = reinterpret_cast<const uint32_t*>(area + (long long)i * SU.bytes + SU.o_edge);
+                chain_edges<THREADS, U>(p.first + i == 0, c.earlier_only, n_edge, edge, stamp, slot, mark, cid, in, T);
+                for (int t = tid; t < Tp; t += THREADS) mark[t] = 0;
+                __syncthreads();
+            } else if (p.first + i == 0) {                    // Definition 2.2: a cluster's pivot is earlier than its other members
+#pragma unroll
+                for (int u = 0; u < U; ++u) in[u] = __ballot(cid[u] == u * THREADS + tid) & exists[u];
+            } else {
+                uint32_t v[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (__builtin_amdgcn_inverse_ballot_w64(in[u])) atomicMin(&slot[cid[u]], stamp | (uint32_t)(u * THREADS + tid));
+                chain_barrier();
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[u] = slot[cid[u]];   // this layer's stamp is the smallest so far
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t key = stamp | (uint32_t)(u * THREADS + tid);
+                    const unsigned long long valid = __ballot(v[u] == key);                        // step 5 (if inherited)
+                    const unsigned long long covered = __ballot(c.earlier_only ? v[u] < key : v[u] <= (stamp | 0x3FFFu));   // steps 7-8
+                    in[u] = (in[u] & valid) | (exists[u] & ~in[u] & ~covered);                      // steps 9 and 10
+                }
+                if (!TWO) chain_barrier();                    // nobody reads this layer's slots any more
+            }
+            unsigned long long* mask = mask_of(i);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                cid[u] = next[min(u * THREADS + tid, T - 1)];
+                const int w = u * (THREADS / 64) + wave;
+                if (lane == 0 && w < CG.words) mask[w] = in[u];
+            }
+        }
+    }
+    if (stop) {                                               // the launch behind needs the units' memory for its hit table
+        __syncthreads();
+        for (int l = 0; l < i; ++l) screen_lists(c, SU, l, g, reinterpret_cast<int*>(lds));
     }
     if (tid == 0) meta[META_PROGRESS] = p.first + i;
 }
 
 // ------------------------------------------------------------------------------------------------
-// k_cascade_rest: the layers that the chain left (the first dense one and all after it), on the tiles of k_cascade_fused,
-// in one launch that leaves at once when there are none.  Work items (layer, worker) are handed out in order by a counter,
+// k_cascade_rest: the lists of all layers, one workgroup per layer -- or, when the chain stopped at a dense layer (and wrote
+// the lists before it), that layer and all after it on the tiles of k_cascade_fused.
+// Work items (layer, worker) are handed out in order by a counter,
 // and an item waits for the previous layer's set before it starts: every item of an earlier layer is by then with a
 // workgroup that runs, so the wait ends however few workgroups are resident, and nothing is assumed about that.  Layer 0
 // is a step that inherits every token: Algorithm 1's step 5 on the identity list is Definition 2.2.
 struct RestParams {
+    ChainParams c;             // layers c.s.first .. + c.s.L - 1, outputs
     FusedParams f;             // shape, threshold, workspace of sequence 0; the per-layer pointers are set in the kernel
-    const void* X[SCREEN_MAX_LAYERS];
-    int first, n;              // layers first .. first + n - 1
-    int32_t* idx;              // row 0 of the call's outputs, as in ChainParams
-    int32_t* counts;
-    unsigned long long* ops;
-    int32_t* adds;
-    int32_t* removes;
-    int32_t* meta;
     int spin_limit;
 };
 
@@ -730,34 +945,37 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
     using G = FusedGeom<KG, DMA>;
     __shared__ int s_item, s_word, s_last;
     FusedParams p = rp.f;
-    const int T = p.T;
-    const int groups = p.groups > 1 ? p.groups : 1, g = (int)blockIdx.x % groups;
+    const int T = p.T, first = rp.c.s.first, n_layers = rp.c.s.L;
+    const int groups = p.groups > 1 ? p.groups : 1, g = (int)blockIdx.x % groups, worker = (int)blockIdx.x / groups;
     const int workers = p.groups > 1 ? p.wpg : p.grid;
-    int32_t* meta = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(rp.meta) + (long long)g * p.ws_gs);
-    const int done = meta[META_PROGRESS];
-    if (done >= rp.first + rp.n) return;
-    const int start = max(done, rp.first);
+    int32_t* meta = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(rp.c.s.meta) + (long long)g * p.ws_gs);
+    const int start = meta[META_PROGRESS];
+    if (start >= first + n_layers) {
+        const ScreenUnit SU(T, rp.c.s.nch);
+        for (int l = worker; l < n_layers; l += workers) screen_lists(rp.c, SU, l, g, reinterpret_cast<int*>(lds));
+        return;
+    }
     p.hits = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(p.hits) + (long long)g * p.ws_gs);
     p.ticket = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(p.ticket) + (long long)g * p.ws_gs);
     if (p.first) p.first = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(p.first) + (long long)g * p.ws_gs);
-    int32_t* idx0 = rp.idx + (long long)g * p.list_gs;
-    int32_t* adds0 = rp.adds ? rp.adds + (long long)g * p.list_gs : nullptr;
-    int32_t* rem0 = rp.removes ? rp.removes + (long long)g * p.list_gs : nullptr;
-    int32_t* cnt0 = rp.counts + (long long)g * p.counts_gs;
-    unsigned long long* ops0 = rp.ops + (long long)g * p.ops_gs;
+    int32_t* idx0 = rp.c.idx + (long long)g * p.list_gs;
+    int32_t* adds0 = rp.c.adds ? rp.c.adds + (long long)g * p.list_gs : nullptr;
+    int32_t* rem0 = rp.c.removes ? rp.c.removes + (long long)g * p.list_gs : nullptr;
+    int32_t* cnt0 = rp.c.counts + (long long)g * p.counts_gs;
+    unsigned long long* ops0 = rp.c.ops + (long long)g * p.ops_gs;
     for (;;) {
         __syncthreads();
         if (threadIdx.x == 0) {
             const int item = atomicAdd(meta + META_REST_QUEUE, 1);
             const int i = start + item / workers;
             int word = -1;                                    // set size inherited by layer i
-            if (i < rp.first + rp.n) {
+            if (i < first + n_layers) {
                 if (i == 0) word = T;
                 else if (i == start) word = cnt0[(size_t)(i - 1) * 4];
                 else
                     for (int n = 0; n < rp.spin_limit; ++n) {
                         const int v = __hip_atomic_load(meta + META_REST_EPOCH, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        if ((v >> 15) == i - rp.first) { word = v & 0x7FFF; break; }
+                        if ((v >> 15) == i - first) { word = v & 0x7FFF; break; }
                         __builtin_amdgcn_s_sleep(2);
                     }
                 if (word < 0) cnt0[(size_t)i * 4 + 3] = ADA_ERR_DEVICE;   // (not reached: see above)
@@ -768,9 +986,9 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
         __syncthreads();
         const int item = s_item, r = s_word;
         const int i = start + item / workers, local = item - (item / workers) * workers;
-        if (i >= rp.first + rp.n || r < 0) break;             // uniform
+        if (i >= first + n_layers || r < 0) break;             // uniform
         const size_t row = (size_t)i * (size_t)T;
-        p.X = reinterpret_cast<const char*>(rp.X[i - rp.first]) + (long long)g * p.x_gs;
+        p.X = reinterpret_cast<const char*>(rp.c.s.X[i - first]) + (long long)g * p.x_gs;
         p.list_mode = i == 0 ? LIST_IDENTITY : LIST_COHERENT;
         p.prev_idx = idx0 + row - (i == 0 ? 0 : T);
         p.idx = idx0 + row;
@@ -793,7 +1011,7 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
             __syncthreads();
             if (threadIdx.x == 0) {
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-                __hip_atomic_store(meta + META_REST_EPOCH, ((i + 1 - rp.first) << 15) | (r_new & 0x7FFF), __ATOMIC_RELAXED,
+                __hip_atomic_store(meta + META_REST_EPOCH, ((i + 1 - first) << 15) | (r_new & 0x7FFF), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
             }
         }
@@ -803,6 +1021,6 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
         __hip_atomic_store(meta + META_REST_QUEUE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(meta + META_REST_EPOCH, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(meta + META_REST_LEFT, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(meta + META_PROGRESS, rp.first + rp.n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(meta + META_PROGRESS, first + n_layers, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
