@@ -32,6 +32,22 @@ struct AttnParams {
     int nerr;
 };
 
+// Several layers in one launch (blockIdx.z): what differs between them.  The other pointers of AttnParams are layer 0's; idx
+// and pos rows lie T apart, set sizes 4 and infos 8 integers.
+constexpr int ATTN_LAYERS = 16;
+struct AttnLayers {
+    const void *Q[ATTN_LAYERS], *K[ATTN_LAYERS], *V[ATTN_LAYERS];
+    float* out[ATTN_LAYERS];
+};
+__device__ inline void attn_layer(AttnParams& p, const AttnLayers& a) {
+    const int z = blockIdx.z;
+    p.Q = a.Q[z]; p.K = a.K[z]; p.V = a.V[z]; p.out = a.out[z];
+    p.idx += (size_t)z * p.T;
+    p.pos += (size_t)z * p.T;
+    if (p.r_dev) p.r_dev += 4 * z;
+    p.info += 8 * z;
+}
+
 // position of every token's representative in R, by binary search; validates R (strictly ascending, in range) and
 // assign (a member of R).  Every workgroup leaves ONE status word (its own, written whatever it found: nothing has
 // to be cleared beforehand); the attention kernel reads them all.
@@ -83,14 +99,16 @@ __device__ inline int attn_status(const AttnParams& p, int r) {
 // Workgroup -> (head, first query block).  Workgroups go to the eight XCDs in turn by their linear index, and every
 // XCD has an L2 of its own: with the launch's natural order the query blocks of one head would sit on eight different
 // XCDs and each of them would pull that head's K and V rows from memory.  When the head count is a multiple of 8 the
-// index is re-read so that a head's workgroups share an XCD (head % 8).
+// index is re-read so that a head's workgroups share an XCD (head % 8).  Query blocks run slowest, so that under the
+// causal mask, which takes them from the last one down (attn_block), the long ones start first.
 struct AttnWho { int h, qblk; };
 __device__ inline AttnWho attn_who(int H) {
-    const int gx = gridDim.x, lin = blockIdx.y * gx + blockIdx.x;
-    if (H % 8 != 0) return {(int)blockIdx.y, (int)blockIdx.x};
-    const int xcd = lin & 7, slot = lin >> 3;
-    return {(slot / gx) * 8 + xcd, slot % gx};
+    const int lin = blockIdx.y * gridDim.x + blockIdx.x;
+    if (H % 8 != 0) return {lin % H, lin / H};
+    const int xcd = lin & 7, slot = lin >> 3, hx = H >> 3;
+    return {(slot % hx) * 8 + xcd, slot / hx};
 }
+__device__ inline int attn_block(int b, int nq, int causal) { return causal ? nq - 1 - b : b; }
 
 __device__ inline int attn_off(int row, int piece, int ppr) {
     const int swz = ppr >= 16 ? (row & 15) : lds_swz(row);
@@ -127,7 +145,8 @@ template <typename In, int DH> struct AttnGeom {
 #endif
 
 template <typename In, int DH>
-__global__ __launch_bounds__(256) void k_attn_rep(AttnParams p) {
+__global__ __launch_bounds__(256) void k_attn_rep(AttnParams p, AttnLayers layers) {
+    attn_layer(p, layers);
     using G = AttnGeom<In, DH>;
     constexpr int EPP = G::EPP, PPR = G::PPR, PPRV = G::PPRV, NB = DH / 64;
     extern __shared__ __align__(16) char lds[];
@@ -151,7 +170,9 @@ __global__ __launch_bounds__(256) void k_attn_rep(AttnParams p) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // query blocks are dealt round-robin over gridDim.x: with the set size known only on the device the launcher
     // sizes the grid for the chip, not for the largest possible set (idle workgroups of this LDS size are not free)
-    for (int q0 = who.qblk * 64; q0 < r; q0 += gridDim.x * 64) {
+    const int nq = (r + 63) / 64;
+    for (int b = who.qblk; b < nq; b += gridDim.x) {
+    const int q0 = attn_block(b, nq, p.causal) * 64;
     __syncthreads();                                       // a previous query block's hand-over is done with the LDS
     const In* Qh = reinterpret_cast<const In*>(p.Q) + (size_t)h * DH;
     const In* Kh = reinterpret_cast<const In*>(p.K) + (size_t)h * DH;
@@ -426,7 +447,8 @@ template <int DH> struct AttnGeom2 {
 //   B(kb): V^T(kb) is written; the multipliers have left K(kb).  Then the loaders ask for K(kb + 2) into the stage just
 //          left and for the indices of block kb + 3; the multipliers add weights x V^T(kb) to their rows.
 template <int DH>
-__global__ __launch_bounds__(512) void k_attn_rep2(AttnParams p) {
+__global__ __launch_bounds__(512) void k_attn_rep2(AttnParams p, AttnLayers layers) {
+    attn_layer(p, layers);
     using In = uint16_t;
     using G = AttnGeom2<DH>;
     constexpr int EPP = 8, PPR = G::PPR, NB = DH / 32, KS = DH / 16, NP = PPR / 4;
@@ -451,7 +473,9 @@ __global__ __launch_bounds__(512) void k_attn_rep2(AttnParams p) {
     const int wave = wave8 & 3;                            // place among the waves of its kind
     const int qb = wave & 1, kh = wave >> 1;
     ATTN_CLK(0);
-    for (int q0 = who.qblk * 64; q0 < r; q0 += gridDim.x * 64) {
+    const int nq = (r + 63) / 64;
+    for (int b = who.qblk; b < nq; b += gridDim.x) {
+    const int q0 = attn_block(b, nq, p.causal) * 64;
     __syncthreads();                                       // a previous query block's hand-over is done with the LDS
     const In* Qh = reinterpret_cast<const In*>(p.Q) + (size_t)h * DH;
     const In* Kh = reinterpret_cast<const In*>(p.K) + (size_t)h * DH;

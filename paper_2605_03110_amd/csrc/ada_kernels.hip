@@ -1069,9 +1069,18 @@ hipError_t dispatch(int dtype, const void* X, long long ld, int d, F&& f) {
     return al ? f(Variant<float, true>{}) : f(Variant<float, false>{});
 }
 
+// Query blocks side by side per head and layer.  With the size known on the device only: about one workgroup per CU for one
+// layer, two for several (those that find no block are not free: they wait for a CU's LDS like the others).
+inline int attn_grid_x(const AttnParams& p, int n_layers) {
+    const int all = (p.r_host + 63) / 64;
+    if (!p.r_dev) return all;
+    const int share = p.H * n_layers, fit = ((n_layers > 1 ? 2 : 1) * device_cus() + share - 1) / share;
+    return all < fit ? all : fit;
+}
+
 // bf16: the kernel that keeps scores and weights in registers (eight waves: four multiply, four fetch)
 template <int DH>
-hipError_t launch_attn_regs(const AttnParams& p, hipStream_t st) {
+hipError_t launch_attn_regs(const AttnParams& p, const AttnLayers& layers, int n_layers, hipStream_t st) {
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     constexpr int lds = AttnGeom2<DH>::LDS;
@@ -1081,25 +1090,22 @@ hipError_t launch_attn_regs(const AttnParams& p, hipStream_t st) {
     });
     if (attr_err != hipSuccess) return attr_err;
     ProfScope ps(ADA_K_ATTN, st);
-    int gx = (p.r_host + 63) / 64;
-    if (p.r_dev) {
-        const int fit = (device_cus() + p.H - 1) / p.H;
-        gx = gx < fit ? gx : fit;
-    }
-    hipLaunchKernelGGL((k_attn_rep2<DH>), dim3(gx, p.H), dim3(512), lds, st, p);
+    const int gx = attn_grid_x(p, n_layers);
+    hipLaunchKernelGGL((k_attn_rep2<DH>), dim3(gx, p.H, n_layers), dim3(512), lds, st, p, layers);
     return hipGetLastError();
 }
 
 template <typename In, int DH>
-hipError_t launch_attn(const AttnParams& p, hipStream_t st) {
+hipError_t launch_attn(const AttnParams& p, const AttnLayers& layers, int n_layers, hipStream_t st) {
     if constexpr (sizeof(In) == 2) {
         static const bool first_kernel = [] {             // development switch: ADA_ATTN=lds keeps the first kernel
             const char* e = dev_switch("ADA_ATTN");
             return e && std::string(e) == "lds";
         }();
         // its hand-over stores 16 bytes per lane
-        const bool out16 = (uintptr_t)p.out % 16 == 0 && p.ld_out % 4 == 0;
-        if (!first_kernel && out16) return launch_attn_regs<DH>(p, st);
+        bool out16 = p.ld_out % 4 == 0;
+        for (int l = 0; l < n_layers; ++l) out16 = out16 && (uintptr_t)layers.out[l] % 16 == 0;
+        if (!first_kernel && out16) return launch_attn_regs<DH>(p, layers, n_layers, st);
     }
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
@@ -1110,12 +1116,8 @@ hipError_t launch_attn(const AttnParams& p, hipStream_t st) {
     });
     if (attr_err != hipSuccess) return attr_err;
     ProfScope ps(ADA_K_ATTN, st);
-    int gx = (p.r_host + 63) / 64;
-    if (p.r_dev) {                                         // size known on the device only: about one workgroup per CU
-        const int fit = (device_cus() + p.H - 1) / p.H;
-        gx = gx < fit ? gx : fit;
-    }
-    hipLaunchKernelGGL((k_attn_rep<In, DH>), dim3(gx, p.H), dim3(256), lds, st, p);
+    const int gx = attn_grid_x(p, n_layers);
+    hipLaunchKernelGGL((k_attn_rep<In, DH>), dim3(gx, p.H, n_layers), dim3(256), lds, st, p, layers);
     return hipGetLastError();
 }
 
@@ -1505,14 +1507,18 @@ bool screen_eligible(int T, int d, float tau, unsigned flags, ScreenPlan* plan) 
 }
 
 // Arguments checked by the caller; x_gs in bytes; list_gs, counts_gs, ops_gs in elements (rows of one sequence are T, 4
-// and 1 apart).
+// and 1 apart).  assign, pos, info (one sequence): the nearest representatives of every layer as well.
+// Layers layer0 .. layer0 + L - 1 of the call (X_layers and the outputs are those of layer 0; layer0 > 0 goes on from the
+// set in the row before).
 int run_layers_screened(const ScreenPlan& plan, const void* const* X_layers, int L, int G, long long x_gs, int T, int d,
                         long long ld, int dtype, float tau, int32_t* idx, int32_t* counts, uint64_t* gram_ops,
                         int32_t* adds, int32_t* removes, long long list_gs, long long counts_gs, long long ops_gs,
-                        void* ws, hipStream_t st, unsigned flags) {
+                        void* ws, hipStream_t st, unsigned flags, int32_t* assign = nullptr, int32_t* pos = nullptr,
+                        int32_t* info = nullptr, int layer0 = 0) {
     const Workspace w = carve(ws, T);
     const ScreenUnit U(T, plan.nch);
     ChainParams c;
+    c.assign = assign; c.pos = pos; c.info = info; c.f32 = dtype == ADA_F32;
     ScreenParams& sp = c.s;
     sp.ld = ld; sp.T = T; sp.d = d; sp.G = G; sp.x_gs = G > 1 ? x_gs : 0;
     sp.area = reinterpret_cast<char*>(w.hits);
@@ -1539,18 +1545,20 @@ int run_layers_screened(const ScreenPlan& plan, const void* const* X_layers, int
         rp.f.x_gs = x_gs; rp.f.list_gs = list_gs; rp.f.counts_gs = counts_gs; rp.f.ops_gs = ops_gs;
         rp.f.ws_gs = sp.area_gs;
     }
+    rp.f.best = w.best;
     rp.spin_limit = 1 << 24;
     const char* no_dma = dev_switch("ADA_NO_DMA");
     bool base16 = true;
-    for (int l = 0; l < L; ++l) base16 = base16 && (uintptr_t)X_layers[l] % 16 == 0;
+    for (int l = layer0; l < layer0 + L; ++l) base16 = base16 && (uintptr_t)X_layers[l] % 16 == 0;
     const long long ld_seen = ((G > 1 && x_gs % 16 != 0) || !base16) ? 1 : ld;
 
     long long fit = (long long)ws_screen_bytes(T) / U.bytes;   // layers at a time, in launches of equal size
     if (fit > SCREEN_MAX_LAYERS) fit = SCREEN_MAX_LAYERS;
     const int batches = (int)((L + fit - 1) / fit), per = (L + batches - 1) / batches;
-    for (int first = 0; first < L; first += per) {
+    const int end = layer0 + L;
+    for (int first = layer0; first < end; first += per) {
         sp.first = first;
-        sp.L = L - first < per ? L - first : per;
+        sp.L = end - first < per ? end - first : per;
         for (int i = 0; i < SCREEN_MAX_LAYERS; ++i) sp.X[i] = i < sp.L ? X_layers[first + i] : nullptr;
         hipError_t e = dtype == ADA_BF16 ? launch_screen<uint16_t>(sp, st) : launch_screen<float>(sp, st);
         if (e != hipSuccess) return ADA_ERR_DEVICE;
@@ -1666,6 +1674,16 @@ int ada_select_full_grouped(const ada_groups* groups, const void* X, int T, int 
     return run_full(X, T, d, ld, dtype, tau, mask, idx, counts, nullptr, nullptr, ws, (hipStream_t)stream, G, go);
 }
 
+static int attention_launch(const AttnParams& p, const AttnLayers& layers, int n_layers, int d_h, int dtype, hipStream_t st) {
+    hipError_t e;
+    if (dtype == ADA_BF16)
+        e = d_h == 64 ? launch_attn<uint16_t, 64>(p, layers, n_layers, st) : d_h == 128 ? launch_attn<uint16_t, 128>(p, layers, n_layers, st)
+                                                                                        : launch_attn<uint16_t, 256>(p, layers, n_layers, st);
+    else
+        e = d_h == 64 ? launch_attn<float, 64>(p, layers, n_layers, st) : launch_attn<float, 128>(p, layers, n_layers, st);
+    return e == hipSuccess ? ADA_OK : ADA_ERR_DEVICE;
+}
+
 // pos_given: the positions of the tokens' representatives are already in the workspace's position array (left there
 // by the assignment of the same workspace): the position pass and its validation are skipped.
 static int attention_run(const void* Q, const void* K, const void* V, int T, int H, int d_h, int64_t ld, int dtype,
@@ -1692,13 +1710,9 @@ static int attention_run(const void* Q, const void* K, const void* V, int T, int
     }
     const AttnParams p = {Q, K, V, ld, T, H, idx, r_dev, r, w.nonrep_idx, out, ld_out,
                           (float)(1.0 / sqrt((double)d_h)), (flags & ADA_FLAG_ATTN_CAUSAL) ? 1 : 0, info, err, nerr};
-    hipError_t e;
-    if (dtype == ADA_BF16)
-        e = d_h == 64 ? launch_attn<uint16_t, 64>(p, st) : d_h == 128 ? launch_attn<uint16_t, 128>(p, st)
-                                                                      : launch_attn<uint16_t, 256>(p, st);
-    else
-        e = d_h == 64 ? launch_attn<float, 64>(p, st) : launch_attn<float, 128>(p, st);
-    return e == hipSuccess ? ADA_OK : ADA_ERR_DEVICE;
+    AttnLayers one = {};
+    one.Q[0] = Q; one.K[0] = K; one.V[0] = V; one.out[0] = out;
+    return attention_launch(p, one, 1, d_h, dtype, st);
 }
 
 int ada_attention_compressed(const void* Q, const void* K, const void* V, int T, int H, int d_h, int64_t ld, int dtype,
@@ -1993,8 +2007,41 @@ int ada_pipeline_layers(const void* const* X_layers, const void* const* Q_layers
         (void)hipEventDestroy(ev);                               // released by the runtime once it has completed
         return ok;
     };
-    if (!fork(main, ss) || !fork(main, sa)) return ADA_ERR_DEVICE;
+    if (!fork(main, ss)) return ADA_ERR_DEVICE;
     int rc = ADA_OK;
+    // Screened: the sets and assignments of many layers come together, and so does the attention on them (a layer of 16
+    // heads and 400 representatives has 112 workgroups for 256 CUs; several layers in one launch fill the chip).  The
+    // positions go where the second workspace would have its hit table.
+    ScreenPlan plan;
+    const bool screened = screen_eligible(T, d, tau, flags, &plan);
+    const size_t fit_pos = ws_area_bytes(T) / ((size_t)T * 4);
+    const int batch = fit_pos < (size_t)ATTN_LAYERS ? (int)fit_pos : ATTN_LAYERS;
+    int32_t* pos = reinterpret_cast<int32_t*>(carve(ws_attn, T).hits);
+    for (int first = 0; screened && first < L && rc == ADA_OK; first += batch) {
+        const int n = L - first < batch ? L - first : batch;
+        const size_t o = (size_t)first * (size_t)T;
+        // (later batches go on from the set that the one before left)
+        rc = run_layers_screened(plan, X_layers, n, 1, 0, T, d, ld, dtype, tau, idx_all, counts_all, gram_ops_all, nullptr,
+                                 nullptr, 0, 0, 0, ws, ss, flags & ADA_FLAG_CROSS_EARLIER_ONLY, assign_all, pos - (ptrdiff_t)o,
+                                 info_all, first);
+        if (rc != ADA_OK) break;
+        if (!fork(ss, sa)) { rc = ADA_ERR_DEVICE; break; }
+        AttnLayers al = {};
+        for (int i = 0; i < n; ++i) {
+            al.Q[i] = Q_layers[first + i]; al.K[i] = K_layers[first + i]; al.V[i] = V_layers[first + i]; al.out[i] = out_layers[first + i];
+        }
+        const AttnParams p = {al.Q[0], al.K[0], al.V[0], ld, T, H, idx_all + o, counts_all + (size_t)first * 4, T, pos, al.out[0], ld_out,
+                              (float)(1.0 / sqrt((double)d_h)), (flags & ADA_FLAG_ATTN_CAUSAL) ? 1 : 0, info_all + (size_t)first * 8 + 4,
+                              nullptr, 0};
+        rc = attention_launch(p, al, n, d_h, dtype, sa);
+        if (first + n < L && !fork(sa, ss)) rc = ADA_ERR_DEVICE;   // (the next batch's positions take the place of these)
+    }
+    if (screened) {                                               // (stream_attn has waited for the whole selection)
+        if (!fork(sa, main)) return ADA_ERR_DEVICE;
+        if (rc != ADA_OK && !fork(ss, main)) return ADA_ERR_DEVICE;
+        return rc;
+    }
+    if (!fork(main, sa)) return ADA_ERR_DEVICE;
     for (int l = 0; l < L && rc == ADA_OK; ++l) {
         const size_t o = (size_t)l * (size_t)T;
         // selection of layer l (Section 4.1): needs only the previous layer's set

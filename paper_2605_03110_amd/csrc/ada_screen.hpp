@@ -17,7 +17,8 @@
 //   exact   one full product per token, with its pivot, in the precision of the other paths, and every row's norm: one
 //           pass over X.  A token close to its pivot (angle at most 0.45 of the threshold's) joins the pivot's CLUSTER:
 //           acos |cos| is a metric, so all members of a cluster are within the threshold of each other.
-//   rest    candidate pairs that no cluster explains are multiplied out one by one and become EDGES.  Whether there are
+//   rest    candidate pairs that no cluster explains are multiplied out one by one and become EDGES (a pair
+//           and its cosine).  Whether there are
 //           any is a matter of counting: with every rho^2 >= f2 all pairs inside clusters are candidates, so if there are
 //           exactly as many candidates as pairs inside clusters there is nothing else, and the launch leaves at once.
 //   chain   one workgroup per sequence walks through the layers: Definition 2.2 at layer 0, Algorithm 1 afterwards, on the
@@ -99,7 +100,7 @@ struct ScreenUnit {
         o_rho = (int)o; o += t4;
         o_cl = (int)o; o += (long long)align_up((size_t)T * 2, 256);
         o_mask = (int)o; o += (long long)align_up((size_t)((T + 63) / 64) * 16, 256);   // the set, and the one inherited by a launch's first layer
-        o_edge = (int)o; o += (long long)align_up((size_t)edge_cap * 4, 256);
+        o_edge = (int)o; o += (long long)align_up((size_t)edge_cap * 8, 256);
         o_z = (int)o; o += (long long)((T + 31) / 32) * nch * 2048;
         bytes = (long long)align_up((size_t)o, 256);
     }
@@ -583,7 +584,7 @@ __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) 
     const In* X = screen_x<In>(p, layer, group);
     const float* rho = reinterpret_cast<const float*>(base + U.o_rho);
     const uint16_t* cl = reinterpret_cast<const uint16_t*>(base + U.o_cl);
-    uint32_t* edge = reinterpret_cast<uint32_t*>(base + U.o_edge);
+    uint2* edge = reinterpret_cast<uint2*>(base + U.o_edge);
     for (int tile = (int)blockIdx.x / units; tile < ntile; tile += (int)gridDim.x / units) {
         int sb, tb;
         screen_blocks(tile, &sb, &tb);
@@ -634,9 +635,10 @@ __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) 
             const int s = (int)(e >> 16), t = (int)(e & 0xFFFFu);
             float xy, xx, yy;
             screen_products<In, 64>(X + (size_t)t * (size_t)p.ld, X + (size_t)s * (size_t)p.ld, true, p.d, lane, &xy, &xx, &yy);
-            if (lane == 0 && screen_cos(xy, xx, yy) >= p.thr) {
+            const float c = screen_cos(xy, xx, yy);
+            if (lane == 0 && c >= p.thr) {
                 const uint32_t at = atomicAdd(hdr + SU_EDGES, 1u);
-                if (at < (uint32_t)U.edge_cap) edge[at] = e;
+                if (at < (uint32_t)U.edge_cap) edge[at] = uint2{e, __float_as_uint(c)};
                 else __hip_atomic_store(hdr + SU_DENSE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
@@ -661,6 +663,12 @@ struct ChainParams {
     int32_t* adds;             // may be NULL
     int32_t* removes;          // may be NULL
     long long list_gs, counts_gs, ops_gs;   // elements between sequences
+    // nearest representative of every token (Section 2.3), if wanted (one sequence): row 0 of the call's outputs, rows T and
+    // 8 apart; pos: the representative's position in its set
+    int32_t* assign;
+    int32_t* pos;
+    int32_t* info;
+    int f32;                   // rows are fp32 (else bf16)
 };
 
 constexpr int LIST_SCRATCH = 3 * 257 * 4;                     // LDS that writing a layer's lists takes
@@ -677,7 +685,8 @@ struct ChainGeom {
         layers = (CHAIN_LDS - off_layer) / layer_bytes;
         layers = layers < L ? layers : L;
         bytes = off_layer + layers * layer_bytes;
-        bytes = bytes < LIST_SCRATCH ? LIST_SCRATCH : bytes;
+        const int lists = Tp * 8 + LIST_SCRATCH;              // (see screen_assign)
+        bytes = bytes < lists ? lists : bytes;
     }
 };
 
@@ -745,11 +754,11 @@ __device__ inline void screen_lists(const ChainParams& c, const ScreenUnit& SU, 
 
 // A layer that has edges (all threads; the marks are zero on entry, barriers inside; on return some marks are set).
 template <int THREADS, int U>
-__device__ inline void chain_edges(bool full, int earlier_only, uint32_t n_edge, const uint32_t* edge, uint32_t stamp,
+__device__ inline void chain_edges(bool full, int earlier_only, uint32_t n_edge, const uint2* edge, uint32_t stamp,
                                    uint32_t* slot, uint8_t* mark, const int (&cid)[U], unsigned long long (&in)[U], int T) {
     const int tid = threadIdx.x, lane = tid & 63;
     if (full) {                                               // Definition 2.2: no earlier token within the threshold
-        for (uint32_t e = tid; e < n_edge; e += THREADS) mark[edge[e] & 0xFFFFu] = 2;
+        for (uint32_t e = tid; e < n_edge; e += THREADS) mark[edge[e].x & 0xFFFFu] = 2;
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -769,7 +778,7 @@ __device__ inline void chain_edges(bool full, int earlier_only, uint32_t n_edge,
     __syncthreads();
     // step 5 along edges: an earlier inherited token hits a later one (only bit 1 is read, only bit 2 set here)
     for (uint32_t e = tid; e < n_edge; e += THREADS) {
-        const uint32_t v = edge[e];
+        const uint32_t v = edge[e].x;
         const int s = (int)(v >> 16), t = (int)(v & 0xFFFFu);
         if ((mark[s] & 1) && (mark[t] & 1)) mark[t] = 3;
     }
@@ -793,7 +802,7 @@ __device__ inline void chain_edges(bool full, int earlier_only, uint32_t n_edge,
         if (low[u] != 0xFFFFFFFFu && mark[low[u]] != 4) low[u] = 0xFFFFFFFFu;
     __syncthreads();
     for (uint32_t e = tid; e < n_edge; e += THREADS) {        // steps 7-8 along edges
-        const uint32_t v = edge[e];
+        const uint32_t v = edge[e].x;
         const int s = (int)(v >> 16), t = (int)(v & 0xFFFFu);
         if (mark[s] & 4) { if (!(mark[t] & 4)) mark[t] = 8; }             // (valid tokens keep their mark)
         if ((mark[t] & 4) && !earlier_only) { if (!(mark[s] & 4)) mark[s] = 8; }
@@ -804,6 +813,108 @@ __device__ inline void chain_edges(bool full, int earlier_only, uint32_t n_edge,
         const int t = u * THREADS + tid;
         const bool covered = (low[u] != 0xFFFFFFFFu && !(earlier_only && low[u] > (uint32_t)t)) || mark[min(t, T - 1)] == 8;
         in[u] = keep[u] | (__ballot(t < T && !covered) & ~in[u]);        // steps 9 and 10
+    }
+    __syncthreads();
+}
+
+// The nearest representative of every token of a layer: all representatives within the threshold of a token are members
+// of its cluster or joined to it by an edge, and a token outside the set is within the threshold of one (it is covered), so
+// the largest |cos| is among these; usually there is just one and nothing has to be multiplied.  (any workgroup size up to
+// 1024; scratch: LIST_SCRATCH + 8 bytes per token, rounded up to 64 tokens, of LDS)
+__device__ inline void screen_assign(const ChainParams& c, const ScreenUnit& SU, int l, int g, int* scratch) {
+    const ScreenParams& p = c.s;
+    const int T = p.T, words = (T + 63) >> 6, tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;
+    char* unit = p.area + (long long)g * p.area_gs + (long long)l * SU.bytes;
+    const unsigned long long* now = reinterpret_cast<const unsigned long long*>(unit + SU.o_mask);
+    const uint16_t* cl = reinterpret_cast<const uint16_t*>(unit + SU.o_cl);
+    const uint2* edge = reinterpret_cast<const uint2*>(unit + SU.o_edge);
+    const int n_edge = (int)reinterpret_cast<const uint32_t*>(unit)[SU_EDGES];
+    const size_t row = (size_t)(p.first + l);
+    int32_t* assign = c.assign + row * T;
+    int32_t* pos = c.pos + row * T;
+    int* start = scratch;                                     // [words]: representatives in the words before
+    uint32_t* member = reinterpret_cast<uint32_t*>(scratch) + LIST_SCRATCH / 4;    // [64 words] earliest representative of a cluster
+    uint32_t* n_member = member + words * 64;                 // [64 words] how many it has
+    for (int t = tid; t < words * 64; t += nthr) { member[t] = 0xFFFFFFFFu; n_member[t] = 0u; }
+    if (tid < 64) {
+        int tot = 0;
+        for (int w0 = 0; w0 < words; w0 += 64) {
+            const int pc = w0 + lane < words ? __popcll(now[w0 + lane]) : 0;
+            int inc = pc;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int x = __shfl_up(inc, o, 64);
+                if (lane >= o) inc += x;
+            }
+            if (w0 + lane < words) start[w0 + lane] = tot + inc - pc;
+            tot += __builtin_amdgcn_readlane(inc, 63);
+        }
+        if (lane == 0) *reinterpret_cast<int4*>(c.info + row * 8) = int4{T - tot, 0, 0, ADA_OK};
+    }
+    __syncthreads();
+    auto is_in = [&](int t) { return (now[t >> 6] >> (t & 63)) & 1ull; };
+    auto put = [&](int t, int a) {
+        assign[t] = a;
+        pos[t] = start[a >> 6] + __popcll(now[a >> 6] & ((1ull << (a & 63)) - 1ull));
+    };
+    for (int t = tid; t < T; t += nthr)
+        if (is_in(t)) {
+            atomicMin(&member[cl[t]], (uint32_t)t);
+            if (n_edge) atomicAdd(&n_member[cl[t]], 1u);
+        }
+    __syncthreads();
+    if (n_edge == 0) {
+        for (int t = tid; t < T; t += nthr) put(t, is_in(t) ? t : (int)min(member[cl[t]], (uint32_t)(T - 1)));
+        __syncthreads();
+        return;
+    }
+    // With edges: the usual packed key per token, (bits of |cos|) << 32 | INT_MAX - id, in the unit's memory for sizes and rho
+    unsigned long long* key = reinterpret_cast<unsigned long long*>(unit + SU.o_size);
+    for (int t = tid; t < T; t += nthr) __hip_atomic_store(key + t, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    for (int e = tid; e < n_edge; e += nthr) {
+        const uint2 v = edge[e];
+        const int s = (int)(v.x >> 16), t = (int)(v.x & 0xFFFFu);
+        const unsigned long long hi = (unsigned long long)v.y << 32;
+        if (is_in(s) && !is_in(t)) atomicMax(key + t, hi | (uint32_t)(INT_MAX - s));
+        if (is_in(t) && !is_in(s)) atomicMax(key + s, hi | (uint32_t)(INT_MAX - t));
+    }
+    drain_stores();
+    __syncthreads();
+    // tokens that an edge or several members of their cluster compete for: the members' products, one wave per token
+    for (int w = tid >> 6; w < words; w += nthr >> 6) {
+        const int tt = w * 64 + lane;
+        const bool mine = tt < T && !is_in(min(tt, T - 1));
+        const uint32_t nm = tt < T ? n_member[cl[tt]] : 0u;
+        const unsigned long long k = mine ? __hip_atomic_load(key + tt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+        if (tt < T && !mine) put(tt, tt);
+        if (mine && nm == 0u) put(tt, INT_MAX - (int)(uint32_t)k);
+        if (mine && nm == 1u && k == 0ull) put(tt, (int)member[cl[tt]]);
+        unsigned long long open = __ballot(mine && nm > 0u && (nm > 1u || k != 0ull));
+        while (open) {
+            const int j = __builtin_amdgcn_readfirstlane(__ffsll((long long)open) - 1), t = w * 64 + j;
+            open &= open - 1ull;
+            unsigned long long best = ((unsigned long long)(uint32_t)__shfl((int)(k >> 32), j, 64) << 32) | (uint32_t)__shfl((int)(uint32_t)k, j, 64);
+            const int ct = cl[t];
+            for (int v = 0; v < words; ++v) {
+                const int s = v * 64 + lane;
+                unsigned long long m = __ballot(s < T && is_in(min(s, T - 1)) && cl[min(s, T - 1)] == ct);
+                for (; m; m &= m - 1ull) {
+                    const int q = v * 64 + __ffsll((long long)m) - 1;
+                    float xy, xx, yy;
+                    if (c.f32) {
+                        const float* X = screen_x<float>(p, l, g);
+                        screen_products<float, 64>(X + (size_t)t * (size_t)p.ld, X + (size_t)q * (size_t)p.ld, true, p.d, lane, &xy, &xx, &yy);
+                    } else {
+                        const uint16_t* X = screen_x<uint16_t>(p, l, g);
+                        screen_products<uint16_t, 64>(X + (size_t)t * (size_t)p.ld, X + (size_t)q * (size_t)p.ld, true, p.d, lane, &xy, &xx, &yy);
+                    }
+                    const unsigned long long cand = ((unsigned long long)__float_as_uint(screen_cos(xy, xx, yy)) << 32) | (uint32_t)(INT_MAX - q);
+                    best = cand > best ? cand : best;
+                }
+            }
+            if (lane == 0) put(t, INT_MAX - (int)(uint32_t)best);
+        }
     }
     __syncthreads();
 }
@@ -886,7 +997,7 @@ __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
             uint32_t* slot = slots + (TWO && (i & 1) ? Tp : 0);
             const uint16_t* next = cl_of(min(k + 1, n - 1));
             if (n_edge) {
-                const uint32_t* edge = reinterpret_cast<const uint32_t*>(area + (long long)i * SU.bytes + SU.o_edge);
+                const uint2* edge = reinterpret_cast<const uint2*>(area + (long long)i * SU.bytes + SU.o_edge);
                 chain_edges<THREADS, U>(p.first + i == 0, c.earlier_only, n_edge, edge, stamp, slot, mark, cid, in, T);
                 for (int t = tid; t < Tp; t += THREADS) mark[t] = 0;
                 __syncthreads();
@@ -921,18 +1032,20 @@ __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
     }
     if (stop) {                                               // the launch behind needs the units' memory for its hit table
         __syncthreads();
-        for (int l = 0; l < i; ++l) screen_lists(c, SU, l, g, reinterpret_cast<int*>(lds));
+        for (int l = 0; l < i; ++l) {
+            screen_lists(c, SU, l, g, reinterpret_cast<int*>(lds));
+            if (c.assign) screen_assign(c, SU, l, g, reinterpret_cast<int*>(lds));
+        }
     }
     if (tid == 0) meta[META_PROGRESS] = p.first + i;
 }
 
 // ------------------------------------------------------------------------------------------------
 // k_cascade_rest: the lists of all layers, one workgroup per layer -- or, when the chain stopped at a dense layer (and wrote
-// the lists before it), that layer and all after it on the tiles of k_cascade_fused.
-// Work items (layer, worker) are handed out in order by a counter,
-// and an item waits for the previous layer's set before it starts: every item of an earlier layer is by then with a
-// workgroup that runs, so the wait ends however few workgroups are resident, and nothing is assumed about that.  Layer 0
-// is a step that inherits every token: Algorithm 1's step 5 on the identity list is Definition 2.2.
+// the lists before it), that layer and all after it on the tiles of k_cascade_fused.  Work items (step, worker) are handed
+// out in order by a counter, and an item waits for the previous step's set before it starts: every item of an earlier step
+// is by then with a workgroup that runs, so the wait ends however few workgroups are resident, and nothing is assumed
+// about that.  Layer 0 is a step that inherits every token: Algorithm 1's step 5 on the identity list is Definition 2.2.
 struct RestParams {
     ChainParams c;             // layers c.s.first .. + c.s.L - 1, outputs
     FusedParams f;             // shape, threshold, workspace of sequence 0; the per-layer pointers are set in the kernel
@@ -952,7 +1065,10 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
     const int start = meta[META_PROGRESS];
     if (start >= first + n_layers) {
         const ScreenUnit SU(T, rp.c.s.nch);
-        for (int l = worker; l < n_layers; l += workers) screen_lists(rp.c, SU, l, g, reinterpret_cast<int*>(lds));
+        for (int j = worker; j < n_layers * (rp.c.assign ? 2 : 1); j += workers) {
+            if (j < n_layers) screen_lists(rp.c, SU, j, g, reinterpret_cast<int*>(lds));
+            else screen_assign(rp.c, SU, j - n_layers, g, reinterpret_cast<int*>(lds));
+        }
         return;
     }
     p.hits = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(p.hits) + (long long)g * p.ws_gs);
@@ -963,19 +1079,18 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
     int32_t* rem0 = rp.c.removes ? rp.c.removes + (long long)g * p.list_gs : nullptr;
     int32_t* cnt0 = rp.c.counts + (long long)g * p.counts_gs;
     unsigned long long* ops0 = rp.c.ops + (long long)g * p.ops_gs;
+    const int per_layer = rp.c.assign ? 2 : 1;                // steps of a layer: the set, and the assignment to it if wanted
     for (;;) {
         __syncthreads();
         if (threadIdx.x == 0) {
-            const int item = atomicAdd(meta + META_REST_QUEUE, 1);
-            const int i = start + item / workers;
-            int word = -1;                                    // set size inherited by layer i
+            const int item = atomicAdd(meta + META_REST_QUEUE, 1), step = item / workers, i = start + step / per_layer;
+            int word = -1;                                    // size of the set that the step works with
             if (i < first + n_layers) {
-                if (i == 0) word = T;
-                else if (i == start) word = cnt0[(size_t)(i - 1) * 4];
+                if (step == 0) word = i == 0 ? T : cnt0[(size_t)(i - 1) * 4];
                 else
                     for (int n = 0; n < rp.spin_limit; ++n) {
                         const int v = __hip_atomic_load(meta + META_REST_EPOCH, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        if ((v >> 15) == i - first) { word = v & 0x7FFF; break; }
+                        if ((v >> 15) == step) { word = v & 0x7FFF; break; }
                         __builtin_amdgcn_s_sleep(2);
                     }
                 if (word < 0) cnt0[(size_t)i * 4 + 3] = ADA_ERR_DEVICE;   // (not reached: see above)
@@ -985,17 +1100,26 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
         }
         __syncthreads();
         const int item = s_item, r = s_word;
-        const int i = start + item / workers, local = item - (item / workers) * workers;
-        if (i >= first + n_layers || r < 0) break;             // uniform
+        const int step = item / workers, local = item - step * workers, i = start + step / per_layer;
+        if (i >= first + n_layers || r < 0) break;            // uniform
         const size_t row = (size_t)i * (size_t)T;
         p.X = reinterpret_cast<const char*>(rp.c.s.X[i - first]) + (long long)g * p.x_gs;
-        p.list_mode = i == 0 ? LIST_IDENTITY : LIST_COHERENT;
-        p.prev_idx = idx0 + row - (i == 0 ? 0 : T);
-        p.idx = idx0 + row;
-        p.adds = i > 0 && adds0 ? adds0 + row : nullptr;
-        p.removes = i > 0 && rem0 ? rem0 + row : nullptr;
-        p.counts = cnt0 + (size_t)i * 4;
-        p.gram_ops = ops0 + i;
+        p.assign_mode = per_layer == 2 && (step & 1);
+        if (p.assign_mode) {
+            p.list_mode = LIST_COHERENT;
+            p.prev_idx = idx0 + row;
+            p.assign = rp.c.assign + row;
+            p.pos_out = rp.c.pos + row;
+            p.counts = rp.c.info + (size_t)i * 8;
+        } else {
+            p.list_mode = i == 0 ? LIST_IDENTITY : LIST_COHERENT;
+            p.prev_idx = idx0 + row - (i == 0 ? 0 : T);
+            p.idx = idx0 + row;
+            p.adds = i > 0 && adds0 ? adds0 + row : nullptr;
+            p.removes = i > 0 && rem0 ? rem0 + row : nullptr;
+            p.counts = cnt0 + (size_t)i * 4;
+            p.gram_ops = ops0 + i;
+        }
         const bool r_ok = r >= 1 && r <= T;
         if (r_ok) fused_step_tiles<In, ALIGNED, KG, DMA>(p, r, lds, (unsigned)local, (unsigned)workers);
         const int jq = min((int)threadIdx.x, T - 1);
@@ -1007,11 +1131,13 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
         if (s_last) {                                         // uniform
             if (threadIdx.x == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             __syncthreads();
-            const int r_new = fused_update<G::THREADS>(p, r, r_ok, q0, qp0, lds + G::META, reinterpret_cast<int*>(lds + G::OFF_SCAN));
+            int r_new = r;
+            if (p.assign_mode) assign_finish<G::THREADS>(p, r, r_ok, q0, qp0);
+            else r_new = fused_update<G::THREADS>(p, r, r_ok, q0, qp0, lds + G::META, reinterpret_cast<int*>(lds + G::OFF_SCAN));
             __syncthreads();
             if (threadIdx.x == 0) {
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-                __hip_atomic_store(meta + META_REST_EPOCH, ((i + 1 - first) << 15) | (r_new & 0x7FFF), __ATOMIC_RELAXED,
+                __hip_atomic_store(meta + META_REST_EPOCH, ((step + 1) << 15) | (r_new & 0x7FFF), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
             }
         }

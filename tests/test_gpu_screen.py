@@ -111,3 +111,35 @@ def test_stacked_sequences_that_need_different_treatment(kinds, T, d, dtype):
     res = pa.ada_cascade_layers_grouped(xg, 0.1, want_lists=True)
     for g, kind in enumerate(kinds):
         check(per[g], 0.1, *(res[k][g].cpu() for k in ("idx", "counts", "gram_ops", "adds", "removes")), 0, "group %d %s" % (g, kind))
+
+
+@pytest.mark.parametrize("kind,T,d,L,dtype", [("clusters", 333, 128, 3, "bf16"), ("clusters", 200, 128, 18, "f32"), ("loose", 300, 256, 3, "bf16"),
+                                              ("loose", 1000, 1024, 2, "f32"), ("common", 300, 512, 3, "bf16"), ("signs", 260, 256, 2, "bf16"),
+                                              ("outliers", 400, 1024, 2, "bf16")])
+def test_assignment_and_attention_on_the_graph_of_near_pairs(kind, T, d, L, dtype):
+    """The pipelined layers take every token's representative from clusters and edges: within 2e-4 of the float64
+    maximum, and the attention on it as for any assignment."""
+    print("[case] screened pipeline: %s T=%d d=%d L=%d %s" % (kind, T, d, L, dtype), flush=True)
+    H, tau = d // 64, 0.1
+    xs_cpu = activations(kind, T, d, L, dtype, seed=3 * T + d)
+    rng = np.random.default_rng(5)
+    qkv = [wl.to_dtype(rng.standard_normal((T, d), dtype=np.float32), dtype) for _ in range(3)]
+    q, k, v = ([m.to(DEV)] * L for m in qkv)
+    ws = pa.workspace_batched(T, 2, DEV)
+    for streams in ((None, None), (torch.cuda.Stream(), torch.cuda.Stream())):
+        res = pa.ada_pipeline_layers([x.to(DEV) for x in xs_cpu], q, k, v, H, tau, ws=ws, stream_sel=streams[0], stream_attn=streams[1])
+        torch.cuda.synchronize()
+        layers = pa.ada_cascade_layers([x.to(DEV) for x in xs_cpu], tau)
+        assert torch.equal(res["counts"], layers["counts"]) and torch.equal(res["gram_ops"], layers["gram_ops"])
+        for l in range(L):
+            r = int(res["counts"][l, 0])
+            idx, assign = res["idx"][l, :r].cpu().numpy(), res["assign"][l].cpu().numpy()
+            assert torch.equal(res["idx"][l, :r], layers["idx"][l, :r])
+            assert res["info"][l].cpu().tolist() == [T - r, 0, 0, 0, r, 0, 0, 0]
+            ref = oracle.assign_nearest(wl.as_f64(xs_cpu[l]), idx)
+            Xn, _ = oracle.normalize(wl.as_f64(xs_cpu[l]))
+            assert np.array_equal(assign[idx], idx) and np.isin(assign, idx).all()
+            other = np.setdiff1d(np.arange(T), idx)
+            chosen = np.abs(np.einsum("ij,ij->i", Xn[other], Xn[assign[other]]))
+            assert (chosen >= ref["corr"][other] - 2e-4).all(), "%s layer %d" % (kind, l)
+            parity.check_attention(*qkv, H, idx, assign, res["out"][l].cpu().numpy(), what="%s layer %d" % (kind, l))
