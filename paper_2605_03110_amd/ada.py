@@ -57,7 +57,7 @@ class AdaError(RuntimeError):
 # them costs every launch microseconds (k_cascade_fused once lost 10 us per step to a 64-byte array in its last
 # workgroup's code), so the build refuses it instead of letting a benchmark find out.
 SCRATCH_BUDGET = {
-    "k_cascade_fusedItLb1ELi2ELb1E": 64,       # bf16, aligned rows, two K-groups, direct-to-LDS: the cascade step
+    "k_cascade_fusedItLb1ELi2ELi1E": 64,       # bf16, aligned rows, two K-groups, direct-to-LDS: the cascade step
     "k_gram_dmaILb1E": 0,                      # one-launch full selection
     "k_gram_dmaILb0E": 0,                      # full Gram beyond T = 4096
     "k_attn_rep2ILi256E": 64,                  # attention on the representative set, d_h = 256

@@ -41,7 +41,7 @@ struct FusedParams {
     int earlier_only;
     uint32_t* hits;          // [W][T] word-major: word w of token t covers inherited representatives 32w .. 32w+31
     int W;                   // hit words per token (covers r_host)
-    float* gamma;            // optional, zero on entry: max |cos| over the columns that count for the token
+    float* gamma;            // optional: max |cos| over the columns that count for the token
     int32_t* ticket;         // zero on entry, zero again on exit; ticket[TICKET_XCD0 + 32 x] (x < 8): first-level counters
     int32_t* idx;
     int32_t* adds;           // may be NULL
@@ -85,13 +85,15 @@ struct FusedParams {
     // none does: what the set update needs of a token's hit words in all but rare cases (see fused_update_rec).
     uint32_t* first;
     // cascade step with a gamma output: Algorithm 1's gamma^cross is the maximum over the VALID representatives, which are
-    // known only after all products.  The tiles therefore also keep, per non-inherited token, the arg max over all
-    // inherited representatives (p.best, keyed by list position); the workgroup that updates the set lists the tokens
+    // known only after all products.  The tiles therefore keep, per token, the arg max over all inherited
+    // representatives that count for it (p.best, keyed by list position); the workgroup that updates the set lists the tokens
     // whose nearest representative was removed (fix_list), clears their gamma and leaves the list's length, the set size
     // and a status in the workspace's scalars (fix_meta: META_NONREP, META_R, META_STATUS) for the launch that recomputes
     // those tokens' maxima against the valid representatives: the cross-Gram tiles of the step's other form, on that list.
+    // inv_norm: the tiles against the first representatives leave the tested tokens' 1/norm for that launch.
     int32_t* fix_list;
     int32_t* fix_meta;
+    float* inv_norm;
 };
 
 // Section 8.1's rule as read here: the turnover eta = (adds + removes) / r of the step just made (eq. (8)) moves tau
@@ -169,26 +171,36 @@ __device__ inline int list_at(const FusedParams& p, int j) {
     return p.list_mode == LIST_COHERENT ? __hip_atomic_load(p.prev_idx + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : p.prev_idx[j];
 }
 
+// How operands travel.  DMA_RAGGED: rows of whole 16-byte pieces whose last 128-byte chunk is a part of one; what it misses is
+// loaded from a page of zeros (a select of the address per load, which the whole-chunk form does without).
+enum { DMA_NONE = 0, DMA_WHOLE = 1, DMA_RAGGED = 2 };
+__device__ const u32x4 g_zero_piece = {0u, 0u, 0u, 0u};
+template <bool RAGGED>
+__device__ inline const void __attribute__((address_space(1)))* dma_source(const void* at, bool inside) {
+    const void* from = RAGGED && !inside ? (const void*)&g_zero_piece : at;
+    return (const void __attribute__((address_space(1)))*)from;
+}
+
 // DMA = operands go global -> LDS directly (global_load_lds, 16 bytes per lane) through a ring of NS stages per
 // K-group; otherwise they pass through registers (needed when a row chunk can be ragged or unaligned).
-template <int KG, bool DMA> struct FusedGeom {
+template <int KG, int DMA> struct FusedGeom {
     static constexpr int THREADS = 256 * KG;
     static constexpr int D = 4;                           // register path: prefetch depth (steps of one group), even
     static constexpr int NS = 4;                          // DMA path: LDS stages per K-group
     static constexpr int LPT = 4;                         // 16-byte pieces per thread per chunk
     static constexpr int STAGE = 128 * 128;               // one chunk of 128 rows
-    static constexpr int NPART = DMA ? 2 * KG : KG;       // partial sums of squares per row
+    static constexpr int NPART = DMA != DMA_NONE ? 2 * KG : KG;       // partial sums of squares per row
     static constexpr int OFF_STOK = 0;                    // int[64]   token id of each "against" row (INT_MAX: none)
     static constexpr int OFF_REPF = 256;                  // int[64]   tested token is inherited
     static constexpr int OFF_SS = 512;                    // float[NPART][128] partial sums of squares
     static constexpr int OFF_SCALE = OFF_SS + NPART * 512;   // float[128] 1/norm (0 for rows that do not exist)
     static constexpr int OFF_SCAN = OFF_SCALE + 512;      // scan scratch of the update phase
     static constexpr int META = OFF_SCAN + 512;
-    static constexpr int RING = DMA ? KG * NS * STAGE : KG * 2 * STAGE;
+    static constexpr int RING = DMA != DMA_NONE ? KG * NS * STAGE : KG * 2 * STAGE;
     static constexpr int RINGMAX = 3 * 384 * 128;         // the widest ring tile: three stages of 384 rows (144 KB)
-    static constexpr int BODY = (KG == 2 && DMA) ? RINGMAX : (RING > 65536 ? RING : 65536);   // stages / reduction scratch (64 KB) / update state
+    static constexpr int BODY = (KG == 2 && DMA != DMA_NONE) ? RINGMAX : (RING > 65536 ? RING : 65536);   // stages / reduction scratch (64 KB) / update state
     static constexpr int OFF_BIG = META + BODY;           // metadata of the wide tiles (two-group direct-to-LDS form)
-    static constexpr int LDS = META + BODY + ((KG == 2 && DMA) ? 8192 : 0);
+    static constexpr int LDS = META + BODY + ((KG == 2 && DMA != DMA_NONE) ? 8192 : 0);
     static_assert(LDS <= 160 * 1024, "one workgroup's LDS");
 };
 
@@ -221,7 +233,6 @@ template <> __device__ inline float piece_sumsq_fast<uint16_t>(u32x4 v) {
 __device__ inline void finish_block(const FusedParams& p, const f32x16& tot, const int* s_tok32, const float* scale32,
                                     float tsc, int mode, int t, int word, int half) {
     const bool ordered = (mode & 1) != 0;             // only earlier representatives count for this token
-    const bool inherited = (mode & 2) != 0;           // the token is itself an inherited representative
     // accumulator register 4q+e of a 32x32 MFMA block is row 8q + 4*half + e: four consecutive rows per q
     f32x4 sc4[4];
     i32x4 tk4[4];
@@ -278,18 +289,15 @@ __device__ inline void finish_block(const FusedParams& p, const f32x16& tot, con
         // the earliest representative that hits t, over all tiles: an integer max of the inverted position (exact and
         // order-independent); few tokens have hits in more than one or two blocks of 32
         if (bits != 0u && p.first) atomicMax(p.first + t, 0xFFFFFFFFu - (uint32_t)(word * 32 + __builtin_ctz(bits)));
-        if (p.gamma && m > 0.f) {
-            atomicMax(reinterpret_cast<uint32_t*>(p.gamma) + t, __float_as_uint(m));
-            // step 8 needs to know WHO holds a non-inherited token's maximum: the assignment's packed key (value bits,
-            // then the smaller list position), exact and order-independent
-            if (!inherited && p.fix_list)
-                atomicMax(p.best + t, ((unsigned long long)__float_as_uint(m) << 32) |
-                                      (unsigned long long)(uint32_t)(INT_MAX - (word * 32 + who)));
-        }
+        // gamma: the value and WHO holds it (step 8 needs to know whether that one is valid), as the assignment's packed key
+        // (value bits, then the smaller list position), exact and order-independent
+        if (p.gamma && m > 0.f)
+            atomicMax(p.best + t, ((unsigned long long)__float_as_uint(m) << 32) |
+                                  (unsigned long long)(uint32_t)(INT_MAX - (word * 32 + who)));
     }
 }
 
-template <typename In, bool ALIGNED, int KG, bool DMA>
+template <typename In, bool WIDE, int KG, int DMA>
 __device__ inline void fused_tile(const FusedParams& p, int r, int s0, int t0, int sb, char* lds) {
     using G = FusedGeom<KG, DMA>;
     constexpr int B = 64;
@@ -373,7 +381,7 @@ __device__ inline void fused_tile(const FusedParams& p, int r, int s0, int t0, i
         for (int ks = 0; ks < 4; ++ks) Mfma<In>::run(acc[ks & 1], fa[f][ks], fb[f][ks]);
     };
 
-    if constexpr (DMA) {
+    if constexpr (DMA != DMA_NONE) {
         // ---- operands go straight from global memory into LDS.  One wave instruction moves 64 x 16 bytes to 1 KB of
         // contiguous LDS = 8 rows of a stage; lane l serves row l / 8, slot l % 8 and therefore fetches piece
         // (l % 8) ^ lds_swz(row), which reproduces the XOR-swizzled layout the fragment reads expect.  The waits are
@@ -390,7 +398,7 @@ __device__ inline void fused_tile(const FusedParams& p, int r, int s0, int t0, i
             for (int j = 0; j < LPT; ++j) {
                 char* dst = ring + stage * G::STAGE + (wave * 8 + 32 * j) * 128;      // wave-uniform
                 __builtin_amdgcn_global_load_lds(
-                    (const void __attribute__((address_space(1)))*)(rowp[j] + chunk * EPC + pcd * EPP),
+                    dma_source<DMA == DMA_RAGGED>(rowp[j] + chunk * EPC + pcd * EPP, chunk * EPC + pcd * EPP < p.d),
                     (void __attribute__((address_space(3)))*)dst, 16, 0, 0);
             }
         };
@@ -469,12 +477,12 @@ __device__ inline void fused_tile(const FusedParams& p, int r, int s0, int t0, i
     auto fetch = [&](int set, int k) {
 #pragma unroll
         for (int j = 0; j < LPT; ++j)
-            pre[set][j] = fetch_piece<In, ALIGNED>(rowp[j], (k * KG + g) * EPC + pc * EPP, p.d);
+            pre[set][j] = fetch_piece<In, WIDE>(rowp[j], (k * KG + g) * EPC + pc * EPP, p.d);
     };
     auto store = [&](char* stage, int set, int k) {
 #pragma unroll
         for (int j = 0; j < LPT; ++j) {
-            const u32x4 v = finish_piece<ALIGNED>(pre[set][j], (k * KG + g) * EPC + pc * EPP, p.d);
+            const u32x4 v = finish_piece<In, WIDE>(pre[set][j], (k * KG + g) * EPC + pc * EPP, p.d);
             *reinterpret_cast<u32x4*>(stage + woff[j]) = v;
             ss[j] += piece_sumsq_fast<In>(v);            // Section 2.1: ||x||^2 from the registers already in hand
         }
@@ -545,6 +553,7 @@ __device__ inline void fused_tile(const FusedParams& p, int r, int s0, int t0, i
         float sc = sum > 0.f ? 1.0f / sqrtf(sum) : 0.f;   // a zero row normalises to zero: all its cosines are 0
         if (tid < B ? (s_tok[tid] == INT_MAX) : (t0 + tid - B >= p.T)) sc = 0.f;
         scale[tid] = sc;
+        if (p.inv_norm && s0 == 0 && tid >= B && t0 + tid - B < p.T) p.inv_norm[t0 + tid - B] = sc;
     }
     if (KG == 2 && g == 0) {
 #pragma unroll
@@ -573,9 +582,9 @@ __device__ inline void fused_tile(const FusedParams& p, int r, int s0, int t0, i
 // the CUs busy anyway.  The 32 x 32 blocks are dealt to the waves in row-major order, NBW = RB / 2 token blocks per
 // wave: wave w owns representative block wa = w / WPB and token blocks NBW (w % WPB) ... (WPB = 8 / RB waves share
 // a representative block).
-template <typename In, int RB>
+template <typename In, int RB, bool RAGGED>
 __device__ inline void fused_tile_wide(const FusedParams& p, int r, int s0, int t0, char* lds) {
-    using G = FusedGeom<2, true>;
+    using G = FusedGeom<2, DMA_WHOLE>;
     static_assert(RB == 2 || RB == 4, "64 or 128 representatives per tile");
     constexpr int BR = 32 * RB, BT = 128, ROWS = BR + BT, EPP = 16 / (int)sizeof(In), EPC = 8 * EPP;
     constexpr int LPT = ROWS / 64, LR = BR / 64, NS = 4, STAGE = ROWS * 128, NBW = RB / 2, WPB = 8 / RB;
@@ -618,13 +627,14 @@ __device__ inline void fused_tile_wide(const FusedParams& p, int r, int s0, int 
         else tok = min(t0 + row - BR, p.T - 1);
         rowp[j] = X + (size_t)tok * (size_t)p.ld + pcd * EPP;
     }
-    const int nk = p.d / EPC;
+    const int nk = (p.d + EPC - 1) / EPC;
     auto issue = [&](int stage, int k) {
         const int chunk = min(k, nk - 1);                        // surplus issues repeat the last chunk into a dead stage
+        const bool inside = chunk * EPC + pcd * EPP < p.d;
 #pragma unroll
         for (int j = 0; j < LPT; ++j) {
             char* dst = ring + stage * STAGE + (wave * 8 + 64 * j) * 128;      // wave-uniform
-            __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(rowp[j] + chunk * EPC),
+            __builtin_amdgcn_global_load_lds(dma_source<RAGGED>(rowp[j] + chunk * EPC, inside),
                                              (void __attribute__((address_space(3)))*)dst, 16, 0, 0);
         }
     };
@@ -735,6 +745,7 @@ __device__ inline void fused_tile_wide(const FusedParams& p, int r, int s0, int 
         float sc = sum > 0.f ? 1.0f / sqrtf(sum) : 0.f;           // a zero row normalises to zero: all its cosines are 0
         if (tid < BR ? (s_tok[tid] == INT_MAX) : (t0 + tid - BR >= p.T)) sc = 0.f;
         scale[tid] = sc;
+        if (p.inv_norm && s0 == 0 && tid >= BR && t0 + tid - BR < p.T) p.inv_norm[t0 + tid - BR] = sc;
     }
     __syncthreads();
 #pragma unroll
@@ -757,9 +768,9 @@ constexpr int waitcnt_vm_lgkm0(int n) { return 0x0070 | (n & 15) | ((n >> 4) << 
 // is one barrier per chunk (four k-steps).  Operand requests per Gram entry fall as 1 / tokens + 1 / representatives,
 // which is why the tile is as large as the step's tile count allows.  Sums of squares (Section 2.1) come from the
 // fragments in hand, every 32-row block summed by exactly one of the waves that hold it.
-template <int NT, int NR>
+template <int NT, int NR, bool RAGGED>
 __device__ inline void fused_tile_ring(const FusedParams& p, int r, int s0, int t0, char* lds) {
-    using G = FusedGeom<2, true>;
+    using G = FusedGeom<2, DMA_WHOLE>;
     constexpr int BR = 64 * NR, BT = 128 * NT, ROWS = BR + BT, EPC = 64, STAGE = ROWS * 128;
     constexpr int NS = 4 * STAGE <= G::BODY ? 4 : 3;
     static_assert(ROWS % 64 == 0, "every wave issues the same number of 8-row loads per stage");
@@ -806,13 +817,14 @@ __device__ inline void fused_tile_ring(const FusedParams& p, int r, int s0, int 
         const int tok = row < BR ? min(max(ptok[j], 0), T - 1) : min(t0 + row - BR, T - 1);
         rowp[j] = X + (size_t)tok * (size_t)p.ld + pcd * 8;
     }
-    const int nk = p.d / EPC;
+    const int nk = (p.d + EPC - 1) / EPC;
     auto issue = [&](int stage_off, int k) {
         const int chunk = min(k, nk - 1);                        // surplus issues repeat the last chunk into a dead stage
+        const bool inside = chunk * EPC + pcd * 8 < p.d;
 #pragma unroll
         for (int j = 0; j < LPT; ++j) {
             char* dst = ring + stage_off + (j * 8 + wave) * 1024;                // wave-uniform
-            __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(rowp[j] + chunk * EPC),
+            __builtin_amdgcn_global_load_lds(dma_source<RAGGED>(rowp[j] + chunk * EPC, inside),
                                              (void __attribute__((address_space(3)))*)dst, 16, 0, 0);
         }
     };
@@ -945,6 +957,7 @@ __device__ inline void fused_tile_ring(const FusedParams& p, int r, int s0, int 
         float sc = sum > 0.f ? 1.0f / sqrtf(sum) : 0.f;          // a zero row normalises to zero: all its cosines are 0
         if (i < BR ? (s_tok[i] == INT_MAX) : (t0 + i - BR >= T)) sc = 0.f;
         scale[i] = sc;
+        if (p.inv_norm && s0 == 0 && i >= BR && t0 + i - BR < T) p.inv_norm[t0 + i - BR] = sc;
     }
     __syncthreads();
 #pragma unroll
@@ -970,7 +983,7 @@ constexpr int SPLIT_EPC = 64;                                 // elements per ch
 
 // The loader waves' K loop: LPT instructions of 1 KB (8 rows x 128 bytes) per wave and chunk; instruction j of loader
 // wave w fills rows 8 (4 j + w) .. + 7 of the stage, lane l row l / 8 of them; tok_of(j, row): the row of X to fetch.
-template <int NS, int LPT, int STAGE, typename TokOf>
+template <int NS, int LPT, int STAGE, bool RAGGED, typename TokOf>
 __device__ inline void split_loader(const uint16_t* X, long long ld, int d, char* ring, int wave, int lane, TokOf tok_of) {
     static_assert(NS >= 3 && (NS - 1) * LPT < 64, "the loads in flight can be counted");
     const int r8 = lane >> 3;
@@ -978,13 +991,14 @@ __device__ inline void split_loader(const uint16_t* X, long long ld, int d, char
     const uint16_t* rowp[LPT];
 #pragma unroll
     for (int j = 0; j < LPT; ++j) rowp[j] = X + (size_t)tok_of(j, (j * 4 + wave) * 8 + r8) * (size_t)ld + pcd * 8;
-    const int nk = d / SPLIT_EPC;
+    const int nk = (d + SPLIT_EPC - 1) / SPLIT_EPC;
     auto issue = [&](int stage_off, int k) {
         const int chunk = min(k, nk - 1);                      // surplus issues repeat the last chunk into a dead stage
+        const bool inside = chunk * SPLIT_EPC + pcd * 8 < d;
 #pragma unroll
         for (int j = 0; j < LPT; ++j) {
             char* dst = ring + stage_off + (j * 4 + wave) * 1024;               // wave-uniform
-            __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(rowp[j] + chunk * SPLIT_EPC),
+            __builtin_amdgcn_global_load_lds(dma_source<RAGGED>(rowp[j] + chunk * SPLIT_EPC, inside),
                                              (void __attribute__((address_space(3)))*)dst, 16, 0, 0);
         }
     };
@@ -1046,9 +1060,9 @@ __device__ inline void split_multiplier(int nk, Read read, Mma mma) {
 // step's tile count allows.  Sums of squares (Section 2.1) come from the fragments in hand: a 32-row block is held by
 // two waves, each wave sums the blocks at its even local positions, and the local order of a wave's blocks is permuted
 // (block a ^ parity) so that those positions cover every block and the K loop stays straight-line code.
-template <int NT, int NR>
+template <int NT, int NR, bool RAGGED>
 __device__ inline void fused_tile_split(const FusedParams& p, int r, int s0, int t0, char* lds) {
-    using G = FusedGeom<2, true>;
+    using G = FusedGeom<2, DMA_WHOLE>;
     constexpr int BR = 64 * NR, BT = 128 * NT, ROWS = BR + BT, STAGE = ROWS * 128;
     constexpr int NS = 4 * STAGE <= G::BODY ? 4 : 3;
     constexpr int LPT = ROWS / 32, NA = NR, NB = 2 * NT;
@@ -1091,7 +1105,7 @@ __device__ inline void fused_tile_split(const FusedParams& p, int r, int s0, int
     constexpr int DA = (NA + 1) / 2, DB = NB / 2;                // blocks a wave sums on each side
     float ssa[DA], ssb[DB];
     if (loader) {
-        split_loader<NS, LPT, STAGE>(reinterpret_cast<const uint16_t*>(p.X), p.ld, p.d, ring, wave, lane,
+        split_loader<NS, LPT, STAGE, RAGGED>(reinterpret_cast<const uint16_t*>(p.X), p.ld, p.d, ring, wave, lane,
             [&](int j, int row) { return row < BR ? min(max(ptok[j], 0), T - 1) : min(t0 + row - BR, T - 1); });
     } else {
         if (!p.assign_mode) {                                     // which tested tokens are inherited (read in the epilogue)
@@ -1118,7 +1132,7 @@ __device__ inline void fused_tile_split(const FusedParams& p, int r, int s0, int
         const uint32_t abase = (uint32_t)lds_off((wr * NA + pa) * 32 + l32, half);
         const uint32_t bbase = (uint32_t)lds_off(BR + (wt * NB + pb) * 32 + l32, half);
         u32x4 fa[2][NA], fb[2][NB];
-        split_multiplier<NS, STAGE>(p.d / SPLIT_EPC,
+        split_multiplier<NS, STAGE>((p.d + SPLIT_EPC - 1) / SPLIT_EPC,
             [&](int set, int stage_off, int ks) {
                 uint32_t ab = abase, bb = bbase;               // (opaque: the XORs are redone here, not kept in 24 registers)
                 asm volatile("" : "+v"(ab), "+v"(bb));
@@ -1160,6 +1174,7 @@ __device__ inline void fused_tile_split(const FusedParams& p, int r, int s0, int
         float sc = sum > 0.f ? 1.0f / sqrtf(sum) : 0.f;          // a zero row normalises to zero: all its cosines are 0
         if (i < BR ? (s_tok[i] == INT_MAX) : (t0 + i - BR >= T)) sc = 0.f;
         scale[i] = sc;
+        if (p.inv_norm && s0 == 0 && i >= BR && t0 + i - BR < T) p.inv_norm[t0 + i - BR] = sc;
     }
     __syncthreads();
     if (loader) return;                                           // (no barrier follows inside the tile)
@@ -1235,33 +1250,36 @@ __device__ inline void block_rank3(const bool (&f)[3][U], int (&below)[3], int (
 }
 
 // Algorithm 1 steps 5, 9, 10 and the bookkeeping (run by one workgroup).  Two forms: from the first-hit records
-// (fused_update_rec, whenever T is a multiple of 4) and from the hit words alone (fused_update's general path).
+// (fused_update_rec, wherever they are kept) and from the hit words alone (fused_update's general path).
 // In the general path per-token state lives in LDS (T <= FUSED_MAX_T bytes): bit 0 = inherited, bit 1 = kept.  The hit
 // table is word-major (hits[w * T + t]), so a thread that owns token t reads its words with loads that are coalesced
 // across the workgroup, independent of each other and branch-free (indices are clamped, results masked): a whole batch
 // is in flight before the first use.
 
-// Algorithm 1 step 8 for callers that ask for gamma: once validity is known (vmask: one bit per list position), list the
-// non-inherited tokens whose nearest inherited representative was removed -- their maximum over the VALID
-// representatives is not the one the tiles accumulated -- and clear their gamma for the recomputation.  The arg-max
-// keys are cleared on the way (the table is zero between calls).  ok == false: a rejected step, only the clearing is
-// done and the list is empty.
-template <int THREADS>
-__device__ inline void gamma_fix_collect(const FusedParams& p, int r, const uint32_t* vmask, bool ok) {
+// gamma for callers that ask for it: unpack the tiles' keys (the table is zero between calls, so they are cleared on the
+// way), and, once validity is known (vmask: one bit per list position), list the non-inherited tokens whose nearest
+// inherited representative was removed -- their maximum over the VALID representatives (step 8) is not the one the tiles
+// accumulated -- and clear their gamma for the recomputation.  inherited(t): the token is on the list.  ok == false: a
+// rejected step, gamma is cleared and the list is empty.
+template <int THREADS, typename Inherited>
+__device__ inline void gamma_fix_collect(const FusedParams& p, int r, const uint32_t* vmask, bool ok, Inherited inherited) {
     if (!p.fix_list) return;                             // uniform
     __shared__ int s_fix;
     const int tid = threadIdx.x;
     if (tid == 0) s_fix = 0;
     __syncthreads();
     auto one = [&](int t, unsigned long long key) {
-        if (t >= p.T || key == 0ull) return;
-        p.best[t] = 0ull;
-        if (!ok) return;
-        const int pos = min(max(INT_MAX - (int)(uint32_t)key, 0), r - 1);
-        if (!((vmask[pos >> 5] >> (pos & 31)) & 1u)) {
-            p.fix_list[atomicAdd(&s_fix, 1)] = t;
-            p.gamma[t] = 0.f;                            // empty max: the recomputation accumulates into it
+        if (t >= p.T) return;
+        if (key != 0ull) p.best[t] = 0ull;
+        float m = ok ? __uint_as_float((uint32_t)(key >> 32)) : 0.f;
+        if (ok && key != 0ull && !inherited(t)) {
+            const int pos = min(max(INT_MAX - (int)(uint32_t)key, 0), r - 1);
+            if (!((vmask[pos >> 5] >> (pos & 31)) & 1u)) {
+                p.fix_list[atomicAdd(&s_fix, 1)] = t;
+                m = 0.f;                                 // empty max: the recomputation accumulates into it
+            }
         }
+        p.gamma[t] = m;
     };
     for (int base = tid; base < p.T; base += 4 * THREADS) {                 // four keys per thread in flight per trip
         const int t0 = base, t1 = base + THREADS, t2 = base + 2 * THREADS, t3 = base + 3 * THREADS;
@@ -1287,13 +1305,13 @@ __device__ inline void gamma_fix_collect(const FusedParams& p, int r, const uint
 // Only a token whose earliest hit turns out invalid needs its hit words (is one of the later hits valid?): a chain
 // t ~ s1 ~ s0 with t not ~ s0, which clustered activations produce rarely.  So the workgroup reads 4 T bytes instead of
 // the whole hit table (T x ceil(r / 32) words: 114 KB at T = 2048, r = 435; 720 KB at T = 8192, r = 700), which was most
-// of this phase.  Thread tid owns the 4 NV consecutive tokens from 4 NV tid on (T a multiple of 4, T <= 4 NV THREADS);
+// of this phase.  Thread tid owns the 4 NV consecutive tokens from 4 NV tid on (T <= 4 NV THREADS);
 // the records are cleared as they are read, so the table is zero again for the next call.
 template <int THREADS, int NV>
 __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int qp0, char* lds, int* scan_scratch) {
     constexpr int U = 4 * NV;
     const int tid = threadIdx.x;
-    const int T = p.T, T4 = T >> 2;
+    const int T = p.T, T4 = (T + 3) >> 2;               // (up to three records past the end: padding, always zero)
     const int Wa = (r + 31) >> 5;
     uint16_t* pos = reinterpret_cast<uint16_t*>(lds);                        // [T] list position of an inherited token
     uint32_t* vmask = reinterpret_cast<uint32_t*>(lds + FUSED_MAX_T * 2);    // [Wa] valid bits by list position
@@ -1325,7 +1343,7 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
     }
     ok = __syncthreads_and(ok);
     if (!ok) {
-        gamma_fix_collect<THREADS>(p, r, vmask, false);
+        gamma_fix_collect<THREADS>(p, r, vmask, false, [](int) { return false; });
         if (tid == 0) {
             p.counts[0] = 0; p.counts[1] = 0; p.counts[2] = 0; p.counts[3] = ADA_ERR_INDEX;
             if (p.gram_ops) *p.gram_ops = 0ull;
@@ -1349,7 +1367,7 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
         }
     }
     __syncthreads();
-    gamma_fix_collect<THREADS>(p, r, vmask, true);       // (gamma output only)
+    gamma_fix_collect<THREADS>(p, r, vmask, true, [&](int t) { return pos[t] != 0xFFFF; });   // (gamma output only)
     // step 9: any other token with a hit on a VALID representative is covered
     bool f[3][U];                                        // in R^(l+1) | added | removed
 #pragma unroll
@@ -1358,7 +1376,7 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int i = 4 * v + u;
-            const bool own = t4 < T4, inh = jpos[i] != 0xFFFF;
+            const bool own = 4 * t4 + u < T, inh = jpos[i] != 0xFFFF;
             const uint32_t k = key[v][u];
             bool covered = false;
             if (own && !inh && k != 0u) {
@@ -1408,8 +1426,8 @@ __device__ inline int fused_update(const FusedParams& p, int r, bool r_ok, int q
     constexpr int WU = 11;                              // hit words fetched per batch by one thread (22, 33, ... words: whole batches)
     const int tid = threadIdx.x, lane = tid & 63;
     const int T = p.T;
-    if (r_ok && p.first && (T & 3) == 0 && T <= 32 * THREADS) {             // uniform
-        const int t4 = T >> 2;
+    if (r_ok && p.first && T <= 32 * THREADS) {                             // uniform
+        const int t4 = (T + 3) >> 2;
         if (t4 <= THREADS) return fused_update_rec<THREADS, 1>(p, r, q0, qp0, lds, scan_scratch);
         if (t4 <= 2 * THREADS) return fused_update_rec<THREADS, 2>(p, r, q0, qp0, lds, scan_scratch);
         if (t4 <= 4 * THREADS) return fused_update_rec<THREADS, 4>(p, r, q0, qp0, lds, scan_scratch);
@@ -1474,7 +1492,7 @@ __device__ inline int fused_update(const FusedParams& p, int r, bool r_ok, int q
     }
     ok = __syncthreads_and(ok);
     const int status = !r_ok ? ADA_ERR_SHAPE : (!ok ? ADA_ERR_INDEX : ADA_OK);
-    gamma_fix_collect<THREADS>(p, r, vmask, status == ADA_OK);               // (gamma output only)
+    gamma_fix_collect<THREADS>(p, r, vmask, status == ADA_OK, [&](int t) { return (flag[t] & 1) != 0; });   // (gamma output only)
     if (status != ADA_OK) {
         if (tid == 0) {
             p.counts[0] = 0; p.counts[1] = 0; p.counts[2] = 0; p.counts[3] = status;
@@ -1613,11 +1631,12 @@ __device__ inline void assign_finish(const FusedParams& p, int r, bool r_ok, int
 
 // The tiles of one step, dealt to the workgroups in contiguous ranges per XCD (blockIdx % 8), the representative block
 // fastest, so that one XCD's L2 serves a contiguous range of tested rows.
-template <typename In, bool ALIGNED, int KG, bool DMA>
+template <typename In, bool WIDE, int KG, int DMA>
 __device__ inline void fused_step_tiles(const FusedParams& p, int r, char* lds, unsigned local, unsigned workers) {
     int shape = 0;
     constexpr int NSHAPES = sizeof(In) == 2 ? 4 : 3;                      // the ring tiles are bf16 only
-    if constexpr (ALIGNED && KG == 2 && DMA)
+    constexpr bool RAGGED = DMA == DMA_RAGGED;
+    if constexpr (WIDE && KG == 2 && DMA != DMA_NONE)
         shape = cascade_tile_shape(r, p.T, p.d, p.tile_pick, p.groups > 1 ? (int)workers : p.tile_pick, NSHAPES);
     const int sr = shape >= 2 ? 7 : 6, st = shape == 0 ? 6 : shape == 3 ? 8 : 7;   // log2 of the tile's rows
     const unsigned nbS = (unsigned)(r + (1 << sr) - 1) >> sr;
@@ -1640,21 +1659,21 @@ __device__ inline void fused_step_tiles(const FusedParams& p, int r, char* lds, 
         const int tb = (int)(tile / nbS), sb = (int)(tile - (unsigned)tb * nbS);
         // (every token inherited, and the update reads first-hit records only: a tile above the diagonal has nothing to say)
         if (p.list_mode == LIST_IDENTITY && p.first && (sb << sr) >= (tb + 1) << st) continue;
-        if constexpr (ALIGNED && KG == 2 && DMA) {
+        if constexpr (WIDE && KG == 2 && DMA != DMA_NONE) {
             if constexpr (sizeof(In) == 2) {
                 // (measured both ways: loader waves gain 10% at 128 x 128; at 128 x 256 the eight multiplying waves of
                 // the ring tile are 3% ahead for one sequence and level for stacked ones)
-                if (shape == 3) fused_tile_ring<2, 2>(p, r, sb * 128, tb * 256, lds);
-                else if (shape == 2) fused_tile_split<1, 2>(p, r, sb * 128, tb * 128, lds);
-                else if (shape == 1) fused_tile_wide<In, 2>(p, r, sb * 64, tb * 128, lds);   // (loader waves: no gain here)
-                else fused_tile<In, ALIGNED, KG, DMA>(p, r, sb * 64, tb * 64, sb, lds);
+                if (shape == 3) fused_tile_ring<2, 2, RAGGED>(p, r, sb * 128, tb * 256, lds);
+                else if (shape == 2) fused_tile_split<1, 2, RAGGED>(p, r, sb * 128, tb * 128, lds);
+                else if (shape == 1) fused_tile_wide<In, 2, RAGGED>(p, r, sb * 64, tb * 128, lds);   // (loader waves: no gain here)
+                else fused_tile<In, WIDE, KG, DMA>(p, r, sb * 64, tb * 64, sb, lds);
             } else {
-                if (shape == 2) fused_tile_wide<In, 4>(p, r, sb * 128, tb * 128, lds);
-                else if (shape == 1) fused_tile_wide<In, 2>(p, r, sb * 64, tb * 128, lds);
-                else fused_tile<In, ALIGNED, KG, DMA>(p, r, sb * 64, tb * 64, sb, lds);
+                if (shape == 2) fused_tile_wide<In, 4, RAGGED>(p, r, sb * 128, tb * 128, lds);
+                else if (shape == 1) fused_tile_wide<In, 2, RAGGED>(p, r, sb * 64, tb * 128, lds);
+                else fused_tile<In, WIDE, KG, DMA>(p, r, sb * 64, tb * 64, sb, lds);
             }
         } else {
-            fused_tile<In, ALIGNED, KG, DMA>(p, r, sb * 64, tb * 64, sb, lds);
+            fused_tile<In, WIDE, KG, DMA>(p, r, sb * 64, tb * 64, sb, lds);
         }
         __syncthreads();
     }
@@ -1662,7 +1681,7 @@ __device__ inline void fused_step_tiles(const FusedParams& p, int r, char* lds, 
 
 // Grid: a multiple of 8 workgroups (see k_gram for the XCD-aware tile ranges); tiles with the representative
 // block fastest, so one XCD's L2 serves a contiguous range of tested rows.
-template <typename In, bool ALIGNED, int KG, bool DMA>
+template <typename In, bool WIDE, int KG, int DMA>
 __global__ __launch_bounds__(256 * KG) void k_cascade_fused(FusedParams p) {
     extern __shared__ __align__(16) char lds[];
     using G = FusedGeom<KG, DMA>;
@@ -1688,7 +1707,7 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_fused(FusedParams p) {
     if (p.thr_in) p.thr = *p.thr_in;                         // adaptive threshold: travels with the set size
     const int r = p.r_dev ? *p.r_dev : p.r_host;
     const bool r_ok = r >= 1 && r <= p.r_host && r <= p.T;
-    if (r_ok) fused_step_tiles<In, ALIGNED, KG, DMA>(p, r, lds, local, workers);
+    if (r_ok) fused_step_tiles<In, WIDE, KG, DMA>(p, r, lds, local, workers);
     // The workgroup that takes the last ticket finishes the step.  Hit words and row maxima leave the CU as
     // device-scope atomics (written through the L2), so once every thread's stores are acknowledged (vmcnt(0)) and
     // the workgroup has met at the barrier, the ticket can be taken: nothing is left in the L2 to write back.
@@ -1747,7 +1766,7 @@ __device__ unsigned long long g_pass_clk[512 * 8];
 #define PASS_CLK(k) do { } while (0)
 #endif
 
-template <typename In, bool ALIGNED, int KG, bool DMA>
+template <typename In, bool WIDE, int KG, int DMA>
 __global__ __launch_bounds__(256 * KG) void k_cascade_pass(PassParams pp) {
     extern __shared__ __align__(16) char lds[];
     using G = FusedGeom<KG, DMA>;
@@ -1787,7 +1806,7 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_pass(PassParams pp) {
         p.counts = pp.counts_row0 + (size_t)(i + 1) * 4;
         p.gram_ops = pp.gram_ops_row0 + (i + 1);
         const bool r_ok = r >= 1 && r <= T;
-        if (r_ok) fused_step_tiles<In, ALIGNED, KG, DMA>(p, r, lds, blockIdx.x, (unsigned)p.grid);
+        if (r_ok) fused_step_tiles<In, WIDE, KG, DMA>(p, r, lds, blockIdx.x, (unsigned)p.grid);
         PASS_CLK(2);
         const int jq = min((int)threadIdx.x, T - 1);         // the row has T entries whatever r is
         const int q0 = list_at(p, jq), qp0 = list_at(p, max(jq - 1, 0));

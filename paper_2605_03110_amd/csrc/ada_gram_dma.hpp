@@ -230,7 +230,7 @@ __device__ inline void gram_tile_split(const GramParams& p, int s0, int t0, bool
     float ssa[DA], ssb[DB];
     if (loader) {
         // rows past the end re-read row T - 1 (and are never published)
-        split_loader<SplitGeom::NS, LPT, STAGE>(reinterpret_cast<const uint16_t*>(p.X), p.ld, p.d, ring, wave, lane,
+        split_loader<SplitGeom::NS, LPT, STAGE, false>(reinterpret_cast<const uint16_t*>(p.X), p.ld, p.d, ring, wave, lane,
             [&](int, int row) { return min(row < BS ? s0 + row : t0 + (row - BS), T - 1); });
     } else {
 #pragma unroll
@@ -339,7 +339,7 @@ __device__ inline void gram_tile_diag(const GramParams& p, int t0, char* lds) {
     f32x16 acc[3];
     float ssP = 0.f, ssR = 0.f;                                // waves 0 and 1 cover the four blocks; 2 and 3 repeat two
     if (loader) {
-        split_loader<SplitGeom::NS, LPT, STAGE>(reinterpret_cast<const uint16_t*>(p.X), p.ld, p.d, ring, wave, lane,
+        split_loader<SplitGeom::NS, LPT, STAGE, false>(reinterpret_cast<const uint16_t*>(p.X), p.ld, p.d, ring, wave, lane,
             [&](int, int row) { return min(t0 + row, T - 1); });
     } else {
 #pragma unroll

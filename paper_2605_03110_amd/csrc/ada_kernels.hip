@@ -101,17 +101,34 @@ template <typename In> __device__ inline float to_f32(In v);
 template <> __device__ inline float to_f32<float>(float v) { return v; }
 template <> __device__ inline float to_f32<uint16_t>(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
 
+// 16 bytes of a row at any alignment (the memory pipe takes them; rows need not start on 16 bytes)
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+
+// The first `cut` elements of a piece cleared.
+template <typename In> __device__ inline u32x4 clear_head(u32x4 v, int cut);
+template <> __device__ inline u32x4 clear_head<uint16_t>(u32x4 v, int cut) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = 2 * i + 1 < cut ? 0u : 2 * i < cut ? v[i] & 0xFFFF0000u : v[i];
+    return v;
+}
+template <> __device__ inline u32x4 clear_head<float>(u32x4 v, int cut) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = i < cut ? 0u : v[i];
+    return v;
+}
+
 // One 16-byte piece of a row starting at element e0; elements at or beyond d read as zero.
-// The aligned form is split in two so that loads can run ahead of their use: fetch_piece issues a branch-free
-// load from an address clamped into the row (a run of them stays in one basic block, which lets the compiler keep
-// several chunks in flight with counted waits), finish_piece zeroes an out-of-range piece when it is consumed.
-// The element-wise form does both in fetch_piece.
-template <typename In, bool ALIGNED>
+// WIDE (rows of at least one piece, any alignment): one 16-byte load.  It is split in two so that loads can run ahead of
+// their use: fetch_piece issues a branch-free load, pulled back into the row where it would pass its end (a run of them
+// stays in one basic block, which lets the compiler keep several chunks in flight with counted waits), finish_piece clears
+// what the pulled-back load repeats when the piece is consumed; the order of a row's elements inside the last piece is then
+// another one, the same for every row.
+// Shorter rows take the element-wise form, which does both in fetch_piece.
+template <typename In, bool WIDE>
 __device__ inline u32x4 fetch_piece(const In* row, int e0, int d) {
     constexpr int EPP = 16 / (int)sizeof(In);
-    if (ALIGNED) {
-        const int e = min(e0, d - EPP);                     // d is a positive multiple of EPP here
-        return *reinterpret_cast<const u32x4*>(row + e);
+    if (WIDE) {
+        return *reinterpret_cast<const u32x4_any*>(row + min(e0, d - EPP));
     } else {
         union { u32x4 v; In e[EPP]; } u;
         u.v = u32x4{0u, 0u, 0u, 0u};
@@ -122,15 +139,16 @@ __device__ inline u32x4 fetch_piece(const In* row, int e0, int d) {
     }
 }
 
-template <bool ALIGNED>
+template <typename In, bool WIDE>
 __device__ inline u32x4 finish_piece(u32x4 v, int e0, int d) {
-    if (ALIGNED && e0 >= d) v = u32x4{0u, 0u, 0u, 0u};
+    constexpr int EPP = 16 / (int)sizeof(In);
+    if (WIDE && e0 + EPP > d) v = clear_head<In>(v, e0 + EPP - d);
     return v;
 }
 
-template <typename In, bool ALIGNED>
+template <typename In, bool WIDE>
 __device__ inline u32x4 load_piece(const In* row, int e0, int d) {
-    return finish_piece<ALIGNED>(fetch_piece<In, ALIGNED>(row, e0, d), e0, d);
+    return finish_piece<In, WIDE>(fetch_piece<In, WIDE>(row, e0, d), e0, d);
 }
 
 template <typename In>
@@ -203,7 +221,7 @@ struct PrepParams {
     int enabled;
 };
 
-template <typename In, bool ALIGNED>
+template <typename In, bool WIDE>
 __global__ __launch_bounds__(256) void k_norm_prep(const In* __restrict__ X, long long ld, int T, int d,
                                                    float* __restrict__ inv_norm, float* __restrict__ gamma,
                                                    Workspace w, PrepParams prep, int n_norm_blocks, GroupOff go) {
@@ -223,12 +241,12 @@ __global__ __launch_bounds__(256) void k_norm_prep(const In* __restrict__ X, lon
         const int np = (d + EPP - 1) / EPP;
         int pi = lane;
         for (; pi + 64 < np; pi += 128) {
-            u32x4 a = load_piece<In, ALIGNED>(row, pi * EPP, d);
-            u32x4 b = load_piece<In, ALIGNED>(row, (pi + 64) * EPP, d);
+            u32x4 a = load_piece<In, WIDE>(row, pi * EPP, d);
+            u32x4 b = load_piece<In, WIDE>(row, (pi + 64) * EPP, d);
             s0 += piece_sumsq<In>(a);
             s1 += piece_sumsq<In>(b);
         }
-        if (pi < np) s0 += piece_sumsq<In>(load_piece<In, ALIGNED>(row, pi * EPP, d));
+        if (pi < np) s0 += piece_sumsq<In>(load_piece<In, WIDE>(row, pi * EPP, d));
         float ss = wave_sum(s0 + s1);
         if (lane == 0) {
             inv_norm[t] = ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;   // a zero row normalises to zero: all its cosines are 0
@@ -376,7 +394,7 @@ __device__ inline void publish_hits(const f32x16& v, const float* s_scale, const
     if (half == 0 && ttok >= 0 && s_glob0 < T) hits[(size_t)(s_glob0 >> 5) * (size_t)T + ttok] = bits;
 }
 
-template <typename In, int B, bool ALIGNED>
+template <typename In, int B, bool WIDE>
 __device__ inline void gram_tile(const GramParams& p, const int32_t* listS, const int32_t* listT, int s0, int t0,
                                  int nS, int nT, bool need_order, char* lds) {
     using G = TileGeom<B>;
@@ -453,12 +471,12 @@ __device__ inline void gram_tile(const GramParams& p, const int32_t* listS, cons
 
     auto fetch = [&](int set, int kc) {
 #pragma unroll
-        for (int j = 0; j < LPT; ++j) pre[set][j] = fetch_piece<In, ALIGNED>(rowp[j], kc * EPC + pc * EPP, p.d);
+        for (int j = 0; j < LPT; ++j) pre[set][j] = fetch_piece<In, WIDE>(rowp[j], kc * EPC + pc * EPP, p.d);
     };
     auto store = [&](char* stage, int set, int kc) {
 #pragma unroll
         for (int j = 0; j < LPT; ++j)
-            *reinterpret_cast<u32x4*>(stage + woff[j]) = finish_piece<ALIGNED>(pre[set][j], kc * EPC + pc * EPP, p.d);
+            *reinterpret_cast<u32x4*>(stage + woff[j]) = finish_piece<In, WIDE>(pre[set][j], kc * EPC + pc * EPP, p.d);
     };
     auto read_frags = [&](const char* stage, int f) {
 #pragma unroll
@@ -573,7 +591,7 @@ __device__ inline void gram_tile(const GramParams& p, const int32_t* listS, cons
 // Grid: a multiple of 8 workgroups.  Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2, so
 // XCD x = blockIdx % 8 takes the contiguous tile range [x * per, (x + 1) * per): tiles that share operand rows run
 // on one L2.  Tiles are numbered with the "against" block fastest.
-template <typename In, int B, bool ALIGNED>
+template <typename In, int B, bool WIDE>
 __global__ __launch_bounds__(256) void k_gram(GramParams p) {
     extern __shared__ __align__(16) char lds[];
     gram_group_offset(p);
@@ -610,7 +628,7 @@ __global__ __launch_bounds__(256) void k_gram(GramParams p) {
             sb = (int)(tile % nbS);
         }
         const bool need_order = p.order_mask && (!tri || sb == tb);
-        gram_tile<In, B, ALIGNED>(p, listS, listT, sb * B, tb * B, nS, nT, need_order, lds);
+        gram_tile<In, B, WIDE>(p, listS, listT, sb * B, tb * B, nS, nT, need_order, lds);
         __syncthreads();
     }
 }
@@ -894,20 +912,20 @@ __global__ __launch_bounds__(GREEDY_THREADS) void k_greedy_resolve(GreedyParams 
 
 template <int B> constexpr int gram_lds_bytes() { return TileGeom<B>::LDS; }
 
-template <typename In, int B, bool ALIGNED>
+template <typename In, int B, bool WIDE>
 hipError_t launch_gram(const GramParams& p, long long tiles_upper, hipStream_t st, int groups = 1) {
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     constexpr int lds = gram_lds_bytes<B>();
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gram<In, B, ALIGNED>),
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gram<In, B, WIDE>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     if (attr_err != hipSuccess) return attr_err;
     if (tiles_upper < 1) return hipSuccess;
     const unsigned grid = (unsigned)((tiles_upper < 65528 ? tiles_upper : 65528) + 7) / 8 * 8;   // multiple of 8 (XCDs)
     ProfScope ps(p.mode == MODE_FULL ? ADA_K_GRAM_FULL : p.mode == MODE_REP ? ADA_K_GRAM_REP : ADA_K_GRAM_CROSS, st);
-    hipLaunchKernelGGL((k_gram<In, B, ALIGNED>), dim3(grid, groups), dim3(256), lds, st, p);
+    hipLaunchKernelGGL((k_gram<In, B, WIDE>), dim3(grid, groups), dim3(256), lds, st, p);
     return hipGetLastError();
 }
 
@@ -1032,21 +1050,21 @@ hipError_t launch_gram_dma(const GramParams& p, int32_t* meta, int mode, hipStre
 // nS_upper / nT_upper: host-known upper bounds of the list lengths (the kernel reads the actual ones).
 // 128-tiles need half the operand traffic per flop but only pay off when they still fill the chip; with sizes
 // known only on the device (exact == false) the 64-tile, which suits every skinny cascade shape, is used.
-template <typename In, bool ALIGNED>
+template <typename In, bool WIDE>
 hipError_t launch_gram_any(const GramParams& p, int nS_upper, int nT_upper, bool exact, hipStream_t st, int groups = 1) {
     int B = (exact && tiles_for(p.mode, nS_upper, nT_upper, 128) * groups >= 192) ? 128 : 64;
     if (int o = tile_override()) B = o;
-    if (B == 128) return launch_gram<In, 128, ALIGNED>(p, tiles_for(p.mode, nS_upper, nT_upper, 128), st, groups);
-    return launch_gram<In, 64, ALIGNED>(p, tiles_for(p.mode, nS_upper, nT_upper, 64), st, groups);
+    if (B == 128) return launch_gram<In, 128, WIDE>(p, tiles_for(p.mode, nS_upper, nT_upper, 128), st, groups);
+    return launch_gram<In, 64, WIDE>(p, tiles_for(p.mode, nS_upper, nT_upper, 64), st, groups);
 }
 
-template <typename In, bool ALIGNED>
+template <typename In, bool WIDE>
 hipError_t launch_norm_prep(const void* X, long long ld, int T, int d, float* gamma, const Workspace& w,
                             const PrepParams& prep, hipStream_t st, const GroupOff& go = GroupOff{0, 0, 0, 0, 0},
                             int groups = 1) {
     const int nb = (T + 3) / 4;
     ProfScope ps(ADA_K_NORM_PREP, st);
-    hipLaunchKernelGGL((k_norm_prep<In, ALIGNED>), dim3(nb + (prep.enabled ? 1 : 0), groups), dim3(256), 0, st,
+    hipLaunchKernelGGL((k_norm_prep<In, WIDE>), dim3(nb + (prep.enabled ? 1 : 0), groups), dim3(256), 0, st,
                        reinterpret_cast<const In*>(X), ld, T, d, w.inv_norm, gamma, w, prep, nb, go);
     return hipGetLastError();
 }
@@ -1057,16 +1075,18 @@ int launch_update(const UpdateParams& u, hipStream_t st, int groups = 1) {
     return hipGetLastError() == hipSuccess ? ADA_OK : ADA_ERR_DEVICE;
 }
 
-template <typename In_, bool A_> struct Variant { using In = In_; static constexpr bool aligned = A_; };
+template <typename In_, bool W_> struct Variant { using In = In_; static constexpr bool wide = W_; };
 
-// 16-byte vector loads need an aligned base, ld and d that are multiples of the piece size; anything else
-// takes the element-wise loader.
+// Rows of at least 16 bytes are loaded 16 bytes at a time, whatever their alignment; shorter ones element by element.
 template <typename F>
-hipError_t dispatch(int dtype, const void* X, long long ld, int d, F&& f) {
-    const int epp = dtype == ADA_BF16 ? 8 : 4;
-    const bool al = ((uintptr_t)X % 16 == 0) && (ld % epp == 0) && (d % epp == 0);
-    if (dtype == ADA_BF16) return al ? f(Variant<uint16_t, true>{}) : f(Variant<uint16_t, false>{});
-    return al ? f(Variant<float, true>{}) : f(Variant<float, false>{});
+hipError_t dispatch(int dtype, int d, F&& f) {
+    if (dtype == ADA_BF16) return d >= 8 ? f(Variant<uint16_t, true>{}) : f(Variant<uint16_t, false>{});
+    return d >= 4 ? f(Variant<float, true>{}) : f(Variant<float, false>{});
+}
+
+// Every row of the matrix (of every problem, gs bytes apart) starts on 16 bytes: what loads straight into LDS need.
+inline bool rows16(int dtype, const void* X, long long ld, long long gs = 0) {
+    return (uintptr_t)X % 16 == 0 && ld % (dtype == ADA_BF16 ? 8 : 4) == 0 && gs % 16 == 0;
 }
 
 // Query blocks side by side per head and layer.  With the size known on the device only: about one workgroup per CU for one
@@ -1157,13 +1177,12 @@ int run_full(const void* X, int T, int d, long long ld, int dtype, float tau, ui
     bool finished = false;
     const char* path_env = dev_switch("ADA_GRAM");               // development switch: tile, dma0, dma1, dma2
     const std::string path = path_env ? path_env : "";
-    const long long ld_seen = (groups > 1 && go.x % 16 != 0) ? 1 : ld;   // every problem's rows must suit the loader
-    hipError_t e = dispatch(dtype, X, ld_seen, d, [&](auto v) {
+    hipError_t e = dispatch(dtype, d, [&](auto v) {
         using V = decltype(v);
         using In = typename V::In;
-        if constexpr (V::aligned && sizeof(In) == 2) {
+        if constexpr (V::wide && sizeof(In) == 2) {
             // whole 64-byte pieces of bf16 rows: the direct-to-LDS kernel
-            const bool can = d % DmaGeom::HC == 0 && go.x % 64 == 0;
+            const bool can = d % DmaGeom::HC == 0 && go.x % 64 == 0 && rows16(dtype, X, ld);
             if (can && (path == "dma0" || path == "dma1" || path == "dma2" || (path.empty() && T >= 1536))) {
                 const int mode = path.empty() ? -1 : path == "dma1" ? 1 : path == "dma2" ? 2 : 0;
                 if (finish_in_kernel && d % SplitGeom::EPC == 0) {
@@ -1176,14 +1195,14 @@ int run_full(const void* X, int T, int d, long long ld, int dtype, float tau, ui
                     finished = true;
                     return launch_gram_dma<true>(q, w.meta, mode, st, groups, in_kernel, gamma);
                 }
-                hipError_t e0 = launch_norm_prep<In, V::aligned>(X, ld, T, d, g, w, prep, st, go, groups);
+                hipError_t e0 = launch_norm_prep<In, V::wide>(X, ld, T, d, g, w, prep, st, go, groups);
                 if (e0 != hipSuccess) return e0;
                 return launch_gram_dma<false>(p, w.meta, mode, st, groups, in_kernel);
             }
         }
-        hipError_t e1 = launch_norm_prep<In, V::aligned>(X, ld, T, d, g, w, prep, st, go, groups);
+        hipError_t e1 = launch_norm_prep<In, V::wide>(X, ld, T, d, g, w, prep, st, go, groups);
         if (e1 != hipSuccess) return e1;
-        return launch_gram_any<In, V::aligned>(p, T, T, true, st, groups);
+        return launch_gram_any<In, V::wide>(p, T, T, true, st, groups);
     });
     if (e != hipSuccess) return ADA_ERR_DEVICE;
     if (greedy) {
@@ -1206,13 +1225,13 @@ hipError_t fill_u32(void* p, size_t n_words, uint32_t v, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <typename In, bool ALIGNED, int KG, bool DMA>
+template <typename In, bool WIDE, int KG, int DMA>
 hipError_t launch_fused(const FusedParams& p, hipStream_t st, int prof_class = ADA_K_CASCADE_FUSED) {
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     constexpr int lds = FusedGeom<KG, DMA>::LDS;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cascade_fused<In, ALIGNED, KG, DMA>),
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cascade_fused<In, WIDE, KG, DMA>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     if (attr_err != hipSuccess) return attr_err;
@@ -1229,7 +1248,7 @@ hipError_t launch_fused(const FusedParams& p, hipStream_t st, int prof_class = A
     } else {
         // with the set size known here the tile shape is too (the kernel makes the same choice from the same numbers)
         int shape = 0;
-        if (ALIGNED && KG == 2 && DMA && !p.r_dev)
+        if (WIDE && KG == 2 && DMA != DMA_NONE && !p.r_dev)
             shape = cascade_tile_shape(p.r_host, p.T, p.d, p.tile_pick, p.tile_pick, sizeof(In) == 2 ? 4 : 3);
         long long tiles = tile_count(p.r_host, p.T, shape);
         // Workgroups loop over tiles, so any grid is correct.  With the set size known only on the device the bound
@@ -1240,10 +1259,10 @@ hipError_t launch_fused(const FusedParams& p, hipStream_t st, int prof_class = A
         grid = (unsigned)(tiles + 7) / 8 * 8;                        // multiple of 8 (XCDs)
     }
     q.grid = (int)grid;
-    // first-hit records are kept only where the update can take them (four tokens per 16-byte load, 32 per thread)
-    if (p.T % 4 != 0 || p.T > 32 * 256 * KG) q.first = nullptr;
+    // first-hit records are kept only where the update can take them (32 tokens per thread)
+    if (p.T > 32 * 256 * KG) q.first = nullptr;
     ProfScope ps(prof_class, st);
-    hipLaunchKernelGGL((k_cascade_fused<In, ALIGNED, KG, DMA>), dim3(grid), dim3(256 * KG), lds, st, q);
+    hipLaunchKernelGGL((k_cascade_fused<In, WIDE, KG, DMA>), dim3(grid), dim3(256 * KG), lds, st, q);
     return hipGetLastError();
 }
 
@@ -1268,25 +1287,25 @@ int cascade_tile_pick() {
 }
 
 // Picks the form of the one-launch kernel: two K-groups unless overridden; direct-to-LDS operand loads when rows come
-// in whole, aligned 128-byte chunks.
+// in aligned 16-byte pieces (of every group: the strides count).
 int launch_fused_any(const FusedParams& p, int dtype, int prof_class, hipStream_t st) {
     int kg = 2;
     if (int o = kgroups_override()) kg = o;
     const char* no_dma = dev_switch("ADA_NO_DMA");
-    // the form of the kernel must suit every group's rows: a group stride off the 16-byte grid takes the element-wise
-    // loader for all of them (dispatch looks at base, ld and d)
-    const long long ld_seen = (p.groups > 1 && p.x_gs % 16 != 0) ? 1 : p.ld;
-    hipError_t e = dispatch(dtype, p.X, ld_seen, p.d, [&](auto v) {
+    const bool dma = rows16(dtype, p.X, p.ld, p.groups > 1 ? p.x_gs : 0) && p.d % (dtype == ADA_BF16 ? 8 : 4) == 0 &&
+                     !(no_dma && no_dma[0] == '1');
+    hipError_t e = dispatch(dtype, p.d, [&](auto v) {
         using V = decltype(v);
         using In = typename V::In;
         constexpr int epc = 128 / (int)sizeof(In);
-        if constexpr (V::aligned) {
-            if (p.d % epc == 0 && !(no_dma && no_dma[0] == '1'))
-                return kg == 2 ? launch_fused<In, true, 2, true>(p, st, prof_class)
-                               : launch_fused<In, true, 1, true>(p, st, prof_class);
+        if constexpr (V::wide) {
+            if (dma && p.d % epc == 0)
+                return kg == 2 ? launch_fused<In, true, 2, DMA_WHOLE>(p, st, prof_class)
+                               : launch_fused<In, true, 1, DMA_WHOLE>(p, st, prof_class);
+            if (dma && kg == 2) return launch_fused<In, true, 2, DMA_RAGGED>(p, st, prof_class);
         }
-        return kg == 2 ? launch_fused<In, V::aligned, 2, false>(p, st, prof_class)
-                       : launch_fused<In, V::aligned, 1, false>(p, st, prof_class);
+        return kg == 2 ? launch_fused<In, V::wide, 2, DMA_NONE>(p, st, prof_class)
+                       : launch_fused<In, V::wide, 1, DMA_NONE>(p, st, prof_class);
     });
     return e == hipSuccess ? ADA_OK : ADA_ERR_DEVICE;
 }
@@ -1294,21 +1313,21 @@ int launch_fused_any(const FusedParams& p, int dtype, int prof_class, hipStream_
 // Algorithm 1 in one launch (ada_fused.hpp).  gamma, if given, receives for an inherited token gamma^rep and for any
 // other token gamma^cross.  The tiles accumulate a token's maximum over ALL inherited representatives; for the tokens
 // whose nearest one turned out removed (listed by the workgroup that updates the set) the maximum over the VALID ones is
-// recomputed by the cross-Gram tiles of the step's other form on that list: a norm launch and a tile launch more.
+// recomputed by the cross-Gram tiles of the step's other form on that list, with the norms the first launch's tiles left: one
+// launch more.
 int run_cascade_fused(const void* X, int T, int d, long long ld, int dtype, float tau, const int32_t* prev_idx, int r,
                       const int32_t* r_dev, int32_t* idx, int32_t* adds, int32_t* removes, int32_t* counts,
                       uint64_t* gram_ops, float* gamma, void* ws, hipStream_t st, unsigned flags,
                       const ada_groups* grp = nullptr, const ada_tau_control* ctl = nullptr, const double* tau_in = nullptr,
                       const float* thr_in = nullptr, double* tau_out = nullptr, float* thr_out = nullptr) {
     const Workspace w = carve(ws, T);
-    if (gamma && fill_u32(gamma, (size_t)T, 0u, st) != hipSuccess) return ADA_ERR_DEVICE;
     FusedParams p = {X, ld, T, d, prev_idx, r_dev, r, threshold_of(tau),
                      (flags & ADA_FLAG_CROSS_EARLIER_ONLY) ? 1 : 0, w.hits, hit_words(r), gamma,
                      w.meta + META_TICKET, idx, adds, removes, counts,
                      reinterpret_cast<unsigned long long*>(gram_ops), 0, nullptr, nullptr, nullptr, 0, cascade_tile_pick()};
     p.first = w.first;
     if (gamma && !(grp && grp->G > 1)) {                          // Algorithm 1's gamma^cross: see above
-        p.best = w.best; p.fix_list = w.nonrep_idx; p.fix_meta = w.meta;
+        p.best = w.best; p.fix_list = w.nonrep_idx; p.fix_meta = w.meta; p.inv_norm = w.inv_norm;
     }
     if (ctl) {                                                   // Section 8.1: threshold carried on the device
         p.tau_in = tau_in; p.thr_in = thr_in; p.tau_out = tau_out; p.thr_out = thr_out;
@@ -1328,12 +1347,9 @@ int run_cascade_fused(const void* X, int T, int d, long long ld, int dtype, floa
     //  as in the step's other form)
     GramParams cross = {X, ld, T, d, prev_idx, w.nonrep_idx, w.meta, w.inv_norm, gamma, threshold_of(tau), MODE_CROSS,
                         (flags & ADA_FLAG_CROSS_EARLIER_ONLY) ? 1 : 0};
-    const PrepParams norms_only = {nullptr, nullptr, 0, 0};
-    const hipError_t e = dispatch(dtype, X, ld, d, [&](auto v) {
+    const hipError_t e = dispatch(dtype, d, [&](auto v) {
         using V = decltype(v);
-        hipError_t e1 = launch_norm_prep<typename V::In, V::aligned>(X, ld, T, d, w.gamma, w, norms_only, st);
-        if (e1 != hipSuccess) return e1;
-        return launch_gram_any<typename V::In, V::aligned>(cross, r, T - 1 > 0 ? T - 1 : 1, false, st);
+        return launch_gram_any<typename V::In, V::wide>(cross, r, T - 1 > 0 ? T - 1 : 1, false, st);
     });
     return e == hipSuccess ? ADA_OK : ADA_ERR_DEVICE;
 }
@@ -1354,21 +1370,21 @@ __global__ void k_fill_status(int32_t* counts, int rows, int status) {
     if (i < rows * 4) counts[i] = (i & 3) == 3 ? status : 0;
 }
 
-template <typename In, bool ALIGNED, int KG, bool DMA>
+template <typename In, bool WIDE, int KG, int DMA>
 hipError_t launch_pass(const PassParams& pp, hipStream_t st) {
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     constexpr int lds = FusedGeom<KG, DMA>::LDS;
     static_assert(lds > 80 * 1024, "the pass kernel relies on one workgroup per CU");
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cascade_pass<In, ALIGNED, KG, DMA>),
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cascade_pass<In, WIDE, KG, DMA>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     if (attr_err != hipSuccess) return attr_err;
     PassParams q = pp;
     q.f.grid = device_cus();
     ProfScope ps(ADA_K_CASCADE_FUSED, st);
-    hipLaunchKernelGGL((k_cascade_pass<In, ALIGNED, KG, DMA>), dim3(q.f.grid), dim3(256 * KG), lds, st, q);
+    hipLaunchKernelGGL((k_cascade_pass<In, WIDE, KG, DMA>), dim3(q.f.grid), dim3(256 * KG), lds, st, q);
     return hipGetLastError();
 }
 
@@ -1393,7 +1409,7 @@ int run_cascade_pass(const void* const* X_layers, int first, int n, int T, int d
     pp.f = {nullptr, ld, T, d, nullptr, nullptr, T, threshold_of(tau), (flags & ADA_FLAG_CROSS_EARLIER_ONLY) ? 1 : 0,
             w.hits, hit_words(T), nullptr, w.meta + META_TICKET, nullptr, nullptr, nullptr, nullptr, nullptr,
             0, nullptr, nullptr, nullptr, 0, cascade_tile_pick()};
-    pp.f.first = T % 4 == 0 ? w.first : nullptr;              // (two K-groups: T <= 16384 fits)
+    pp.f.first = w.first;                                     // (two K-groups: T <= 16384 fits)
     // rows of idx_all that share a 128-byte line with their neighbour could be cached half-written
     pp.f.list_mode = ((uintptr_t)idx_all % 128 != 0 || T % 32 != 0) ? LIST_COHERENT : LIST_PLAIN;
     for (int i = 0; i < n; ++i) pp.X[i] = X_layers[first + i];
@@ -1411,8 +1427,8 @@ int run_cascade_pass(const void* const* X_layers, int first, int n, int T, int d
     // a layer that is never finished (a workgroup gave up waiting) keeps this status
     hipLaunchKernelGGL(k_fill_status, dim3((n * 4 + 255) / 256), dim3(256), 0, st, pp.counts_row0 + 4, n, (int)ADA_ERR_DEVICE);
     if (hipGetLastError() != hipSuccess) return ADA_ERR_DEVICE;
-    const hipError_t e = dtype == ADA_BF16 ? launch_pass<uint16_t, true, 2, true>(pp, st)
-                                           : launch_pass<float, true, 2, true>(pp, st);
+    const hipError_t e = dtype == ADA_BF16 ? launch_pass<uint16_t, true, 2, DMA_WHOLE>(pp, st)
+                                           : launch_pass<float, true, 2, DMA_WHOLE>(pp, st);
     return e == hipSuccess ? ADA_OK : ADA_ERR_DEVICE;
 }
 
@@ -1481,19 +1497,19 @@ hipError_t launch_screen_chain(const ChainParams& c, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <typename In, bool ALIGNED, bool DMA>
+template <typename In, bool WIDE, int DMA>
 hipError_t launch_cascade_rest(const RestParams& rp, hipStream_t st) {
     constexpr int lds = FusedGeom<2, DMA>::LDS;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cascade_rest<In, ALIGNED, 2, DMA>),
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cascade_rest<In, WIDE, 2, DMA>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     if (attr_err != hipSuccess) return attr_err;
     ProfScope ps(ADA_K_CASCADE_FUSED, st);
     const int grid = rp.f.groups > 1 ? rp.f.groups * rp.f.wpg : rp.f.grid;
-    hipLaunchKernelGGL((k_cascade_rest<In, ALIGNED, 2, DMA>), dim3((unsigned)grid), dim3(512), lds, st, rp);
+    hipLaunchKernelGGL((k_cascade_rest<In, WIDE, 2, DMA>), dim3((unsigned)grid), dim3(512), lds, st, rp);
     return hipGetLastError();
 }
 
@@ -1537,7 +1553,7 @@ int run_layers_screened(const ScreenPlan& plan, const void* const* X_layers, int
     RestParams rp;
     rp.f = {nullptr, ld, T, d, nullptr, nullptr, T, sp.thr, c.earlier_only, w.hits, hit_words(T), nullptr, w.meta + META_TICKET,
             nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr, nullptr, LIST_COHERENT, cascade_tile_pick()};
-    rp.f.first = T % 4 == 0 ? w.first : nullptr;               // (two K-groups: T <= 16384 fits)
+    rp.f.first = w.first;                                      // (two K-groups: T <= 16384 fits)
     rp.f.grid = device_cus();
     if (G > 1) {
         rp.f.groups = G;
@@ -1548,9 +1564,8 @@ int run_layers_screened(const ScreenPlan& plan, const void* const* X_layers, int
     rp.f.best = w.best;
     rp.spin_limit = 1 << 24;
     const char* no_dma = dev_switch("ADA_NO_DMA");
-    bool base16 = true;
-    for (int l = layer0; l < layer0 + L; ++l) base16 = base16 && (uintptr_t)X_layers[l] % 16 == 0;
-    const long long ld_seen = ((G > 1 && x_gs % 16 != 0) || !base16) ? 1 : ld;
+    bool dma = !(no_dma && no_dma[0] == '1') && d % (dtype == ADA_BF16 ? 8 : 4) == 0;
+    for (int l = layer0; l < layer0 + L; ++l) dma = dma && rows16(dtype, X_layers[l], ld, G > 1 ? x_gs : 0);
 
     long long fit = (long long)ws_screen_bytes(T) / U.bytes;   // layers at a time, in launches of equal size
     if (fit > SCREEN_MAX_LAYERS) fit = SCREEN_MAX_LAYERS;
@@ -1568,14 +1583,8 @@ int run_layers_screened(const ScreenPlan& plan, const void* const* X_layers, int
                       : launch_screen_chain<1024, 16, false>(c, st);
         if (e != hipSuccess) return ADA_ERR_DEVICE;
         rp.c = c;
-        e = dispatch(dtype, X_layers[0], ld_seen, d, [&](auto v) {
-            using V = decltype(v);
-            using In = typename V::In;
-            if constexpr (V::aligned) {
-                if (d % (128 / (int)sizeof(In)) == 0 && !(no_dma && no_dma[0] == '1')) return launch_cascade_rest<In, true, true>(rp, st);
-            }
-            return launch_cascade_rest<In, V::aligned, false>(rp, st);
-        });
+        e = dtype == ADA_BF16 ? (dma ? launch_cascade_rest<uint16_t, true, DMA_RAGGED>(rp, st) : launch_cascade_rest<uint16_t, true, DMA_NONE>(rp, st))
+                              : (dma ? launch_cascade_rest<float, true, DMA_RAGGED>(rp, st) : launch_cascade_rest<float, true, DMA_NONE>(rp, st));
         if (e != hipSuccess) return ADA_ERR_DEVICE;
     }
     return ADA_OK;
@@ -1599,16 +1608,16 @@ int run_cascade(const void* X, int T, int d, long long ld, int dtype, float tau,
     GramParams cross = rep;
     cross.mode = MODE_CROSS;
     cross.order_mask = (flags & ADA_FLAG_CROSS_EARLIER_ONLY) ? 1 : 0;
-    hipError_t e = dispatch(dtype, X, ld, d, [&](auto v) {
+    hipError_t e = dispatch(dtype, d, [&](auto v) {
         using V = decltype(v);
         // step 1 (norms) + steps 2, 6 (index lists)
-        hipError_t e1 = launch_norm_prep<typename V::In, V::aligned>(X, ld, T, d, g, w, prep, st);
+        hipError_t e1 = launch_norm_prep<typename V::In, V::wide>(X, ld, T, d, g, w, prep, st);
         if (e1 != hipSuccess) return e1;
         // steps 3-5: r x r Gram among the inherited rows, strict lower triangle in token order
-        e1 = launch_gram_any<typename V::In, V::aligned>(rep, nS_up, nS_up, r_dev == nullptr, st);
+        e1 = launch_gram_any<typename V::In, V::wide>(rep, nS_up, nS_up, r_dev == nullptr, st);
         if (e1 != hipSuccess || nT_up < 1) return e1;
         // steps 6-9: every other token against the valid representatives
-        return launch_gram_any<typename V::In, V::aligned>(cross, nS_up, nT_up, r_dev == nullptr, st);
+        return launch_gram_any<typename V::In, V::wide>(cross, nS_up, nT_up, r_dev == nullptr, st);
     });
     if (e != hipSuccess) return ADA_ERR_DEVICE;
     // step 10 and the bookkeeping of eq. (6) / eq. (8)
@@ -1778,10 +1787,9 @@ int ada_cascade_step_static(const void* X, int T, int d, int64_t ld, int dtype, 
     if (r < 1 || r > T) return ADA_ERR_SHAPE;
     // The counters a step relies on being zero (tickets, queue, hand-over word) are cleared by a fill kernel, so the
     // array is good whatever an earlier call left behind; everything else a step reads it writes first.
+    // (scalars, arg-max keys and first-hit records lie side by side: one launch)
     const Workspace w = carve(ws, T);
-    if (fill_u32(w.meta, META_BYTES / 4, 0u, (hipStream_t)stream) != hipSuccess) return ADA_ERR_DEVICE;
-    if (fill_u32(w.best, (size_t)T * 2, 0u, (hipStream_t)stream) != hipSuccess ||                       // arg-max keys
-        fill_u32(w.first, (size_t)T, 0u, (hipStream_t)stream) != hipSuccess) return ADA_ERR_DEVICE;         // first-hit records
+    if (fill_u32(w.meta, (size_t)(w.first + T - (uint32_t*)w.meta), 0u, (hipStream_t)stream) != hipSuccess) return ADA_ERR_DEVICE;
     return run_cascade(X, T, d, ld, dtype, tau, prev_idx, r, r_dev, idx, adds, removes, counts, gram_ops, gamma, ws,
                        (hipStream_t)stream, flags);
 }

@@ -133,9 +133,6 @@ __device__ inline const In* screen_x(const ScreenParams& p, int layer, int group
     return reinterpret_cast<const In*>(reinterpret_cast<const char*>(p.X[layer]) + (long long)group * p.x_gs);
 }
 
-// 16 bytes of a row at any alignment (the memory pipe takes them; rows here need not start on 16 bytes)
-typedef u32x4 u32x4_any __attribute__((aligned(2)));
-
 // Eight consecutive elements from column e0 on, as floats; columns at or beyond d are zero.  The load is pulled back
 // into the row and what it repeats is cleared, so rows of any length and alignment are read in whole pieces (d >= 8).
 template <typename In> __device__ inline void screen_load8(const In* row, int e0, int d, float (&v)[8]);
@@ -435,19 +432,7 @@ __device__ inline ScreenTile screen_tile(const char* z, int T, int nch, int sb, 
 }
 
 // ------------------------------------------------------------------------------------------------
-// Products of whole rows.  A piece is 16 bytes; the last one is pulled back into the row and what it repeats is cleared.
-template <typename In> __device__ inline u32x4 screen_mask(u32x4 v, int cut);
-template <> __device__ inline u32x4 screen_mask<uint16_t>(u32x4 v, int cut) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        v[i] = 2 * i + 1 < cut ? 0u : 2 * i < cut ? v[i] & 0xFFFF0000u : v[i];
-    return v;
-}
-template <> __device__ inline u32x4 screen_mask<float>(u32x4 v, int cut) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = i < cut ? 0u : v[i];
-    return v;
-}
+// Products of whole rows, piece by piece (see fetch_piece).
 template <typename In> __device__ inline float screen_dot(u32x4 a, u32x4 b, float s);
 template <> __device__ inline float screen_dot<float>(u32x4 a, u32x4 b, float s) {
 #pragma unroll
@@ -491,11 +476,11 @@ __device__ inline void screen_products(const In* x, const In* y, bool two, int d
             const int pc = p0 + u * LPR;
             if (pc < np) {
                 const int cut = pc * EPP - min(pc * EPP, d - EPP);
-                const u32x4 va = cut > 0 ? screen_mask<In>(a[u], cut) : a[u];
+                const u32x4 va = cut > 0 ? clear_head<In>(a[u], cut) : a[u];
                 sxx = screen_dot<In>(va, va, sxx);
                 if (two) {
                     sxy = screen_dot<In>(va, b[u], sxy);
-                    const u32x4 vb = cut > 0 ? screen_mask<In>(b[u], cut) : b[u];
+                    const u32x4 vb = cut > 0 ? clear_head<In>(b[u], cut) : b[u];
                     syy = screen_dot<In>(vb, vb, syy);
                 }
             }
@@ -1052,7 +1037,7 @@ struct RestParams {
     int spin_limit;
 };
 
-template <typename In, bool ALIGNED, int KG, bool DMA>
+template <typename In, bool WIDE, int KG, int DMA>
 __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
     extern __shared__ __align__(16) char lds[];
     using G = FusedGeom<KG, DMA>;
@@ -1121,7 +1106,7 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
             p.gram_ops = ops0 + i;
         }
         const bool r_ok = r >= 1 && r <= T;
-        if (r_ok) fused_step_tiles<In, ALIGNED, KG, DMA>(p, r, lds, (unsigned)local, (unsigned)workers);
+        if (r_ok) fused_step_tiles<In, WIDE, KG, DMA>(p, r, lds, (unsigned)local, (unsigned)workers);
         const int jq = min((int)threadIdx.x, T - 1);
         const int q0 = list_at(p, jq), qp0 = list_at(p, max(jq - 1, 0));
         drain_stores();
