@@ -409,7 +409,7 @@ int ada_profile_mfma_probe(int workgroups, int iters, float* sink, void* stream)
  *   ADA_CASCADE_TILE=64|64x128|128|256x128   tile shape of the one-launch cascade step
  *   ADA_NO_DMA=1                  operands through registers instead of straight into LDS
  *   ADA_ATTN=lds                  the first attention kernel
- *   ADA_SCREEN=0                  layer loops: one launch per layer instead of the screened selection
+ *   ADA_SCREEN=0                  layer loops: one launch per layer, full selection: every product, instead of the screened form
  *   ADA_SPIN_LIMIT=n              bound of the resident pass's wait between layers (polls)
  */
 

@@ -39,9 +39,10 @@ struct DmaGeom {
 #endif
 
 // One WM*2 x WM*2 tile: "against" rows s0.. on the MFMA M side, tested rows t0.. on the N side; the rows' inverse norms
-// come from p.inv_norm.
-template <int WM>
-__device__ inline void gram_tile_dma(const GramParams& p, int s0, int t0, bool need_order, char* lds) {
+// come from p.inv_norm.  LIST: the tested rows are listT[t0 ..] of nT.
+template <int WM, bool LIST = false>
+__device__ inline void gram_tile_dma(const GramParams& p, int s0, int t0, bool need_order, char* lds,
+                                     const int32_t* listT = nullptr, int nT = 0) {
     using G = DmaGeom;
     constexpr int BT = 2 * WM, ROWS = 2 * BT, NB = WM / 32, LPT = ROWS / 64, NS = G::NS, HC = G::HC;
     constexpr int STAGE = ROWS * 64;
@@ -58,11 +59,13 @@ __device__ inline void gram_tile_dma(const GramParams& p, int s0, int t0, bool n
     DMA_CLK(4);
     const int T = p.T;
     const uint16_t* X = reinterpret_cast<const uint16_t*>(p.X);
+    const int n_t = LIST ? nT : T;
+    auto tested = [&](int i) { return LIST ? listT[min(i, n_t - 1)] : i; };
 
     for (int i = tid; i < ROWS; i += G::THREADS) {
         const bool isS = i < BT;
-        const int tok = isS ? s0 + i : t0 + (i - BT);
-        const bool ok = tok < T;
+        const int tok = isS ? s0 + i : tested(t0 + (i - BT));
+        const bool ok = isS ? tok < T : t0 + (i - BT) < n_t;
         const float sc = ok ? p.inv_norm[ok ? tok : 0] : 0.f;
         if (isS) { s_tok[i] = ok ? tok : INT_MAX; s_scale[i] = sc; }
         else { t_tok[i - BT] = ok ? tok : -1; t_scale[i - BT] = sc; }
@@ -76,7 +79,7 @@ __device__ inline void gram_tile_dma(const GramParams& p, int s0, int t0, bool n
 #pragma unroll
     for (int j = 0; j < LPT; ++j) {
         const int row = (j * 4 + wave) * 16 + (lane >> 2);
-        const int tok = min(row < BT ? s0 + row : t0 + (row - BT), T - 1);
+        const int tok = min(row < BT ? s0 + row : tested(t0 + (row - BT)), T - 1);
         rowp[j] = X + (size_t)tok * (size_t)p.ld + (((lane & 3) ^ ((lane >> 4) & 3)) << 3);
     }
     const int nh = p.d / HC;
@@ -520,6 +523,7 @@ __global__ __launch_bounds__(NORMS ? SplitGeom::THREADS : DmaGeom::THREADS) void
     extern __shared__ __align__(16) char lds[];
     __shared__ long long s_next;
     __shared__ int s_last, s_scan[32];
+    if (p.gate && *p.gate == 0) return;                        // (uniform, before the queue and the tickets)
     gram_group_offset(p);
     if (p.ws_gs) meta = reinterpret_cast<int*>(reinterpret_cast<char*>(meta) + (long long)blockIdx.y * p.ws_gs);
     int* queue = meta + META_QUEUE;                            // the workspace's unit counter and its sign-off tickets

@@ -42,7 +42,7 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 enum { MODE_FULL = 0, MODE_REP = 1, MODE_CROSS = 2 };
 // meta: a few words of scalars, then (from word META_TICKET + 64 on, one per 128-byte line) the per-XCD ticket counters
 constexpr size_t META_BYTES = 2048;
-enum { META_R = 0, META_NONREP = 1, META_STATUS = 2, META_SPARE = 3, META_TICKET = 4, META_QUEUE = 5 /* and 6 */, META_EPOCH = 7,
+enum { META_R = 0, META_NONREP = 1, META_STATUS = 2, META_GATE = 3 /* k_screen_sort */, META_TICKET = 4, META_QUEUE = 5 /* and 6 */, META_EPOCH = 7,
        // screened selection: layers done so far; work queue, hand-over word and sign-off counter of k_cascade_rest (zero between calls)
        META_PROGRESS = 8, META_REST_QUEUE = 9, META_REST_EPOCH = 10, META_REST_LEFT = 11, META_WORDS = 12 };
 
@@ -305,6 +305,7 @@ struct GramParams {
     long long x_gs, ws_gs;   // MODE_FULL with blockIdx.y = problem: bytes between problems' X / workspaces (0: one problem)
     uint32_t* hits;          // MODE_FULL, optional: word-major bit table, bit (s mod 32) of hits[(s div 32) * T + t] =
                              // "|G_st| >= threshold and s < t" (the greedy covering of Section 2.5 is resolved from it)
+    const int32_t* gate;     // MODE_FULL, optional: a word that is 0 where an earlier launch has done the work
 };
 
 __device__ inline void gram_group_offset(GramParams& p) {
@@ -594,6 +595,7 @@ __device__ inline void gram_tile(const GramParams& p, const int32_t* listS, cons
 template <typename In, int B, bool WIDE>
 __global__ __launch_bounds__(256) void k_gram(GramParams p) {
     extern __shared__ __align__(16) char lds[];
+    if (p.gate && *p.gate == 0) return;
     gram_group_offset(p);
     int nS, nT;
     const int32_t *listS = nullptr, *listT = nullptr;
@@ -649,11 +651,13 @@ struct UpdateParams {
     int32_t* counts;         // [4]
     unsigned long long* gram_ops;   // may be NULL
     GroupOff go;             // full selection of several problems: blockIdx.x is the problem
+    const int32_t* gate;     // optional, as in GramParams
 };
 
 __global__ __launch_bounds__(1024) void k_update(UpdateParams u) {
     __shared__ int sh[3][32];
     const int tid = threadIdx.x;
+    if (u.gate && *u.gate == 0) return;
     if (u.go.ws) {
         const long long g = blockIdx.x;
         u.gamma = reinterpret_cast<const float*>(reinterpret_cast<const char*>(u.gamma) + g * u.go.ws);
@@ -772,6 +776,7 @@ __global__ __launch_bounds__(256) void k_copy_probe(u32x4* __restrict__ dst, con
 #include "ada_fused.hpp"
 #include "ada_screen.hpp"
 #include "ada_gram_dma.hpp"
+#include "ada_screen_full.hpp"
 #include "ada_attn.hpp"
 
 // ------------------------------------------------------------------------------------------------
@@ -819,6 +824,7 @@ struct GreedyParams {
     int32_t* idx;            // [T], may be NULL
     int32_t* counts;         // [4] = {r, r, 0, 0}
     unsigned long long* gram_ops;   // may be NULL
+    const int32_t* gate;     // optional, as in GramParams
 };
 
 constexpr int GREEDY_THREADS = 1024;
@@ -832,6 +838,7 @@ __global__ __launch_bounds__(GREEDY_THREADS) void k_greedy_resolve(GreedyParams 
     __shared__ uint32_t repw[TPT * GREEDY_THREADS / 32];
     __shared__ uint32_t own_lo[64], own_hi[64];
     __shared__ int sh[32];
+    if (g.gate && *g.gate == 0) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int T = g.T, nblk = (T + 63) >> 6;
     for (int t = tid; t < T; t += GREEDY_THREADS) covered[t] = 0;
@@ -1153,6 +1160,10 @@ int check_common(const void* X, int T, int d, int64_t ld, int dtype, float tau, 
 // 1 - tau^2 evaluated in double and rounded once to the fp32 the comparisons run in
 inline float threshold_of(float tau) { return (float)(1.0 - (double)tau * (double)tau); }
 
+bool screen_full_eligible(const void* X, int T, int d, long long ld, int dtype, float tau, bool greedy, ScreenPlan* plan);
+int screen_full(const ScreenPlan& plan, const void* X, int T, int d, long long ld, int dtype, float tau, uint8_t* mask,
+                int32_t* idx, int32_t* counts, uint64_t* gram_ops, float* gamma, const Workspace& w, bool greedy, hipStream_t st);
+
 // Definition "Gram threshold": norms, lower-triangular Gram tiles, threshold + compaction.  Arguments checked by the caller.
 int run_full(const void* X, int T, int d, long long ld, int dtype, float tau, uint8_t* mask, int32_t* idx,
              int32_t* counts, uint64_t* gram_ops, float* gamma, void* ws, hipStream_t st,
@@ -1163,16 +1174,23 @@ int run_full(const void* X, int T, int d, long long ld, int dtype, float tau, ui
     float* g = gamma ? gamma : w.gamma;
     const float thr = threshold_of(tau);
     const PrepParams prep = {nullptr, nullptr, 0, 0};
+    // Long sequences: from the graph of near pairs.  The launches below are then gated: they do the work where the graph
+    // turned out not to decide (norms and cleared maxima are there), and leave at once elsewhere.
+    ScreenPlan plan;
+    const bool screened = groups == 1 && screen_full_eligible(X, T, d, ld, dtype, tau, greedy, &plan);
+    if (screened)
+        if (int e = screen_full(plan, X, T, d, ld, dtype, tau, mask, idx, counts, gram_ops, gamma, w, greedy, st)) return e;
+    const int32_t* gate = screened ? w.meta + META_GATE : nullptr;
     // greedy covering (Section 2.5): the tiles also leave the threshold bits of every pair s < t, and the set is
     // resolved from them in token order (one problem, T <= FUSED_MAX_T: checked by the caller)
     const GramParams p = {X, ld, T, d, nullptr, nullptr, nullptr, w.inv_norm, g, thr, MODE_FULL, 1, go.x, go.ws,
-                          greedy ? w.hits : nullptr};
+                          greedy ? w.hits : nullptr, gate};
     const UpdateParams u = {g, nullptr, nullptr, T, thr, mask, idx, nullptr, nullptr, counts,
-                            reinterpret_cast<unsigned long long*>(gram_ops), go};
+                            reinterpret_cast<unsigned long long*>(gram_ops), go, gate};
     // Up to T = 4096 a launch is mostly latency, and the direct-to-LDS kernel finishes the selection itself (its last
     // workgroup applies the threshold and compacts): one launch and one gap less.  Beyond that the tiles keep the
     // chip busy for hundreds of microseconds and the update stays a launch of its own.
-    const bool finish_in_kernel = !greedy && T <= 4096;
+    const bool finish_in_kernel = !greedy && (screened || T <= 4096);
     const UpdateParams in_kernel = finish_in_kernel ? u : UpdateParams{};
     bool finished = false;
     const char* path_env = dev_switch("ADA_GRAM");               // development switch: tile, dma0, dma1, dma2
@@ -1185,7 +1203,7 @@ int run_full(const void* X, int T, int d, long long ld, int dtype, float tau, ui
             const bool can = d % DmaGeom::HC == 0 && go.x % 64 == 0 && rows16(dtype, X, ld);
             if (can && (path == "dma0" || path == "dma1" || path == "dma2" || (path.empty() && T >= 1536))) {
                 const int mode = path.empty() ? -1 : path == "dma1" ? 1 : path == "dma2" ? 2 : 0;
-                if (finish_in_kernel && d % SplitGeom::EPC == 0) {
+                if (finish_in_kernel && !screened && d % SplitGeom::EPC == 0) {
                     // ONE launch: the norms come from the tiles' own fragments, and the row maxima are accumulated in a
                     // workspace array that is zero between calls (the workgroup that finishes hands them over and
                     // clears it again), so nothing has to be computed or cleared ahead of the tiles.
@@ -1195,18 +1213,19 @@ int run_full(const void* X, int T, int d, long long ld, int dtype, float tau, ui
                     finished = true;
                     return launch_gram_dma<true>(q, w.meta, mode, st, groups, in_kernel, gamma);
                 }
-                hipError_t e0 = launch_norm_prep<In, V::wide>(X, ld, T, d, g, w, prep, st, go, groups);
+                hipError_t e0 = screened ? hipSuccess : launch_norm_prep<In, V::wide>(X, ld, T, d, g, w, prep, st, go, groups);
                 if (e0 != hipSuccess) return e0;
+                finished = finish_in_kernel;
                 return launch_gram_dma<false>(p, w.meta, mode, st, groups, in_kernel);
             }
         }
-        hipError_t e1 = launch_norm_prep<In, V::wide>(X, ld, T, d, g, w, prep, st, go, groups);
+        hipError_t e1 = screened ? hipSuccess : launch_norm_prep<In, V::wide>(X, ld, T, d, g, w, prep, st, go, groups);
         if (e1 != hipSuccess) return e1;
         return launch_gram_any<In, V::wide>(p, T, T, true, st, groups);
     });
     if (e != hipSuccess) return ADA_ERR_DEVICE;
     if (greedy) {
-        const GreedyParams gp = {w.hits, T, mask, idx, counts, reinterpret_cast<unsigned long long*>(gram_ops)};
+        const GreedyParams gp = {w.hits, T, mask, idx, counts, reinterpret_cast<unsigned long long*>(gram_ops), gate};
         ProfScope ps(ADA_K_UPDATE, st);
         if (T <= 2 * GREEDY_THREADS) hipLaunchKernelGGL((k_greedy_resolve<2, 4>), dim3(1), dim3(GREEDY_THREADS), 0, st, gp);
         else if (T <= 4 * GREEDY_THREADS) hipLaunchKernelGGL((k_greedy_resolve<4, 3>), dim3(1), dim3(GREEDY_THREADS), 0, st, gp);
@@ -1435,6 +1454,21 @@ int run_cascade_pass(const void* const* X_layers, int first, int n, int T, int d
 // ------------------------------------------------------------------------------------------------
 // Screened selection (ada_screen.hpp): L layers of G sequences, full selection at layer 0, Algorithm 1 afterwards.
 
+// All but the layers and their pointers.
+ScreenParams screen_params(const ScreenPlan& plan, const Workspace& w, int T, int d, long long ld, float tau, int G, long long x_gs) {
+    ScreenParams sp = {};
+    sp.ld = ld; sp.T = T; sp.d = d; sp.G = G; sp.x_gs = G > 1 ? x_gs : 0;
+    sp.area = reinterpret_cast<char*>(w.hits);
+    sp.area_gs = (long long)ws_bytes_for(T);
+    sp.meta = w.meta;
+    sp.nch = plan.nch;
+    sp.nk = (d + 63) / 64;
+    sp.kap = plan.kappa * SCREEN_SCALE * SCREEN_SCALE;
+    sp.kap1 = plan.kappa + (float)SCREEN_EPS;
+    sp.f2 = plan.f2; sp.safe = plan.safe; sp.thr = threshold_of(tau); sp.cos_tight = plan.cos_tight;
+    return sp;
+}
+
 template <typename In, int LPR>
 hipError_t launch_screen_exact(const ScreenParams& sp, hipStream_t st) {
     // four rows per lane group where that leaves enough workgroups to fill the chip, one where it does not
@@ -1481,6 +1515,78 @@ hipError_t launch_screen(const ScreenParams& sp, hipStream_t st) {
     ProfScope ps(ADA_K_SCREEN, st);
     hipLaunchKernelGGL((k_screen_rest<In>), dim3((unsigned)(k * units)), dim3(256), 0, st, sp, ntile);
     return hipGetLastError();
+}
+
+// The full selection of one sequence (ada_screen_full.hpp).
+template <typename In, bool DMA>
+hipError_t launch_screen_gram(const ScreenParams& sp, const GramParams& p, hipStream_t st) {
+    constexpr int big = DMA ? DmaGeom::META + DmaGeom::NS * 256 * 64 : gram_lds_bytes<128>();
+    constexpr int lds = big > gram_lds_bytes<64>() ? big : gram_lds_bytes<64>();
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(once, [] {
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_screen_gram<In, DMA>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    });
+    if (attr_err != hipSuccess) return attr_err;
+    ProfScope ps(ADA_K_SCREEN, st);                           // (two workgroups per CU: LDS)
+    hipLaunchKernelGGL((k_screen_gram<In, DMA>), dim3(2 * device_cus()), dim3(256), lds, st, sp, p);
+    return hipGetLastError();
+}
+
+// Where the graph is the better way: seven launches and two single-workgroup passes cost 40 to 50 us whatever the products,
+// so the triangle has to be worth more, at the rate of the tiles that would run it.  Measured, us, full Gram -> graph (K =
+// distinct rows):
+//   bf16, whole 64-byte pieces, T > 4096 (a norm and an update launch as well): T=8192 d=512 65 -> 58 (3.4e10), d=256
+//     48 -> 56 (1.7e10), 6000 x 512 54 -> 56 (1.8e10), 6000 x 1024 75 -> 66 (3.7e10), 8192 x 4096 297 -> 105 (K = T / 20), 284 -> 210 (T / 2)
+//   the same, T <= 4096 (one launch): 4096 x 4096 107 -> 65 and 108 -> 98 (6.9e10), 3500 x 4096 84 -> 60 and 85 -> 87 (5e10)
+//   other bf16 rows: 3001 x 1000 49 -> 43 (9e9), 8191 x 130 99 -> 65 (8.7e9), 2400 x 1000 37 -> 50 (5.8e9)
+//   fp32: 2048 x 768 63 -> 52 (3.2e9), 1500 x 768 44 -> 50 (1.7e9); T=1100 d=4096 105 -> 123 (one tile takes 100)
+//   greedy covering, which also saves its resolution: 1536 x 768 59 -> 37, 2048 x 4096 93 -> 54, 1100 x 4096 53 -> 51
+bool screen_full_eligible(const void* X, int T, int d, long long ld, int dtype, float tau, bool greedy, ScreenPlan* plan) {
+    if (T < 1500 || T > FUSED_MAX_T) return false;
+    const char* e = dev_switch("ADA_SCREEN");
+    if ((e && e[0] == '0') || dev_switch("ADA_GRAM") || dev_switch("ADA_TILE")) return false;
+    const bool pieces = dtype == ADA_BF16 && d % DmaGeom::HC == 0 && rows16(dtype, X, ld);
+    const double least = dtype == ADA_F32 ? 2.5e9 : !pieces ? 8e9 : T > 4096 ? 3e10 : 5.5e10;
+    if (!greedy && (double)T * T * d < least) return false;
+    return screen_plan(d, tau, plan) && ScreenUnit(T, plan->nch).bytes <= (long long)ws_screen_bytes(T);
+}
+
+int screen_full(const ScreenPlan& plan, const void* X, int T, int d, long long ld, int dtype, float tau, uint8_t* mask,
+                int32_t* idx, int32_t* counts, uint64_t* gram_ops, float* gamma, const Workspace& w, bool greedy, hipStream_t st) {
+    ScreenFullParams f;
+    f.s = screen_params(plan, w, T, d, ld, tau, 1, 0);
+    ScreenParams& sp = f.s;
+    sp.L = 1;
+    sp.X[0] = X;
+    sp.gamma = gamma ? gamma : w.gamma;                        // (without one they are there for the full Gram)
+    sp.inv_norm = w.inv_norm;
+    f.want_gamma = gamma != nullptr;
+    f.greedy = greedy;
+    f.big_tiles = 1024;
+    f.gate = w.meta + META_GATE;
+    f.mask = mask; f.idx = idx; f.counts = counts; f.ops = reinterpret_cast<unsigned long long*>(gram_ops);
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(once, [] {
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_screen_sort), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       screen_sort_lds(FUSED_MAX_T));
+    });
+    if (attr_err != hipSuccess) return ADA_ERR_DEVICE;
+    hipError_t e = dtype == ADA_BF16 ? launch_screen<uint16_t>(sp, st) : launch_screen<float>(sp, st);
+    if (e != hipSuccess) return ADA_ERR_DEVICE;
+    {
+        ProfScope ps(ADA_K_UPDATE, st);
+        hipLaunchKernelGGL(k_screen_sort, dim3(1), dim3(SCREEN_SORT_THREADS), screen_sort_lds(T), st, f);
+        if (hipGetLastError() != hipSuccess) return ADA_ERR_DEVICE;
+    }
+    if (!gamma) return ADA_OK;
+    const GramParams p = {X, ld, T, d, nullptr, nullptr, nullptr, w.inv_norm, gamma, sp.thr, MODE_FULL, 1};
+    const bool dma = dtype == ADA_BF16 && d % DmaGeom::HC == 0 && rows16(dtype, X, ld);
+    e = dtype == ADA_F32 ? launch_screen_gram<float, false>(sp, p, st) : dma ? launch_screen_gram<uint16_t, true>(sp, p, st)
+                                                                             : launch_screen_gram<uint16_t, false>(sp, p, st);
+    return e == hipSuccess ? ADA_OK : ADA_ERR_DEVICE;
 }
 
 template <int THREADS, int U, bool TWO>
@@ -1536,15 +1642,7 @@ int run_layers_screened(const ScreenPlan& plan, const void* const* X_layers, int
     ChainParams c;
     c.assign = assign; c.pos = pos; c.info = info; c.f32 = dtype == ADA_F32;
     ScreenParams& sp = c.s;
-    sp.ld = ld; sp.T = T; sp.d = d; sp.G = G; sp.x_gs = G > 1 ? x_gs : 0;
-    sp.area = reinterpret_cast<char*>(w.hits);
-    sp.area_gs = (long long)ws_bytes_for(T);
-    sp.meta = w.meta;
-    sp.nch = plan.nch;
-    sp.nk = (d + 63) / 64;
-    sp.kap = plan.kappa * SCREEN_SCALE * SCREEN_SCALE;
-    sp.kap1 = plan.kappa + (float)SCREEN_EPS;
-    sp.f2 = plan.f2; sp.safe = plan.safe; sp.thr = threshold_of(tau); sp.cos_tight = plan.cos_tight;
+    sp = screen_params(plan, w, T, d, ld, tau, G, x_gs);
     c.earlier_only = (flags & ADA_FLAG_CROSS_EARLIER_ONLY) ? 1 : 0;
     c.idx = idx; c.counts = counts; c.ops = reinterpret_cast<unsigned long long*>(gram_ops); c.adds = adds; c.removes = removes;
     c.list_gs = list_gs; c.counts_gs = counts_gs; c.ops_gs = ops_gs;

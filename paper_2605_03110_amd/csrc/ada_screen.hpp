@@ -37,8 +37,24 @@ constexpr int CHAIN_LDS = 160 * 1024 - 2048;                  // what the walk m
 constexpr float SCREEN_SCALE = 256.f;                         // sketches are stored as 8-bit floats of 256 x (unit vector)
 
 // header of a unit (one layer of one sequence); zeroed by the sketch launch
-enum { SU_CAND = 0, SU_PAIRS = 1, SU_FLAGS = 2, SU_EDGES = 3, SU_DENSE = 4, SU_WORDS = 64 };
+enum { SU_EDGES = 3, SU_DENSE = 4, SU_PART = 32, SU_WORDS = SU_PART + 8 * 32 };
+// What every workgroup of the pair and exact passes adds to is kept once per XCD, a cache line each, from word SU_PART on:
+// one address takes an atomic every 25 ns from the whole chip, which was most of these passes where one unit has all the
+// workgroups (T = 8192, d = 4096: pairs 18.6 -> 13.6 us, exact 35.4 -> 20.7 us; T = 2048: 5.6 -> 5.2 and 11.8 -> 9.0).
+enum { SU_CAND = 0, SU_PAIRS = 1, SU_FLAGS = 2 };
 enum { SF_LOW = 1, SF_MESH = 2 };                             // SU_FLAGS: a row below f2; a pivot that has a pivot itself
+
+struct ScreenCounts { uint32_t cand, pairs, flags; };
+__device__ inline ScreenCounts screen_counts(const uint32_t* hdr) {
+    ScreenCounts n = {0u, 0u, 0u};
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+        n.cand += hdr[SU_PART + x * 32 + SU_CAND];
+        n.pairs += hdr[SU_PART + x * 32 + SU_PAIRS];
+        n.flags |= hdr[SU_PART + x * 32 + SU_FLAGS];
+    }
+    return n;
+}
 
 // How a problem is screened (host): columns of the sketch and the constants of the bound.
 struct ScreenPlan {
@@ -118,6 +134,8 @@ struct ScreenParams {
     int nch, nk;
     float kap, kap1;           // candidate threshold on the raw accumulator; kappa with the rounding allowance
     float f2, safe, thr, cos_tight;
+    float* gamma;              // one unit: largest |cos| of the pairs multiplied out (bits under an integer max), or NULL
+    float* inv_norm;           // one unit: inverse norms of the rows, or NULL
     const void* X[SCREEN_MAX_LAYERS];
 };
 
@@ -167,7 +185,7 @@ __global__ __launch_bounds__(256) void k_screen_sketch(ScreenParams p, int row_b
     char* base = screen_unit(p, U, unit, &layer, &group);
     const In* X = screen_x<In>(p, layer, group);
     if (rb == 0) {
-        if (threadIdx.x < SU_WORDS) reinterpret_cast<uint32_t*>(base)[threadIdx.x] = 0u;
+        for (int i = threadIdx.x; i < SU_WORDS; i += 256) reinterpret_cast<uint32_t*>(base)[i] = 0u;
         // words of the call (not of the unit): layers done so far; the last launch's queue is left at zero by itself
         if (layer == 0 && p.first == 0 && threadIdx.x == 0)
             reinterpret_cast<int32_t*>(reinterpret_cast<char*>(p.meta) + (long long)group * p.area_gs)[META_PROGRESS] = 0;
@@ -223,6 +241,7 @@ __global__ __launch_bounds__(256) void k_screen_sketch(ScreenParams p, int row_b
         reinterpret_cast<float*>(base + U.o_rho)[t] = ss;
         reinterpret_cast<int32_t*>(base + U.o_piv)[t] = t;
         reinterpret_cast<int32_t*>(base + U.o_size)[t] = 0;
+        if (p.gamma) p.gamma[t] = 0.f;
     }
 }
 
@@ -397,7 +416,8 @@ __global__ __launch_bounds__(256, NCH == 4 ? 2 : 3) void k_screen_pairs(ScreenPa
         if (lane == 0 && n) atomicAdd(&s_cand, n);
     }
     __syncthreads();
-    if (threadIdx.x == 0 && s_cand) atomicAdd(reinterpret_cast<uint32_t*>(base) + SU_CAND, (uint32_t)s_cand);
+    if (threadIdx.x == 0 && s_cand)
+        atomicAdd(reinterpret_cast<uint32_t*>(base) + SU_PART + (blockIdx.x & 7) * 32 + SU_CAND, (uint32_t)s_cand);
 }
 
 // Sketch products of a 128 x 128 tile: four waves in a 2 x 2 grid of 64 x 64.
@@ -531,6 +551,7 @@ __global__ __launch_bounds__(256) void k_screen_exact(ScreenParams p, int passes
         if (li == 0) {
             const float r2 = xx > 0.f ? rho[t] / xx : 1.f;    // (a zero row has no cosines: nothing to bound)
             rho[t] = r2;
+            if (p.inv_norm) p.inv_norm[t] = xx > 0.f ? 1.0f / sqrtf(xx) : 0.f;
             uint32_t fl = r2 < p.f2 ? (uint32_t)SF_LOW : 0u;
             int c = t;
             if (q != t && screen_cos(xy, xx, yy) >= p.cos_tight) {
@@ -544,7 +565,7 @@ __global__ __launch_bounds__(256) void k_screen_exact(ScreenParams p, int passes
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        uint32_t* hdr = reinterpret_cast<uint32_t*>(base);
+        uint32_t* hdr = reinterpret_cast<uint32_t*>(base) + SU_PART + (blockIdx.x & 7) * 32;
         if (s_pairs) atomicAdd(hdr + SU_PAIRS, s_pairs);
         if (s_flags) atomicOr(hdr + SU_FLAGS, s_flags);
     }
@@ -563,9 +584,9 @@ __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) 
     int layer, group;
     char* base = screen_unit(p, U, unit, &layer, &group);
     uint32_t* hdr = reinterpret_cast<uint32_t*>(base);
-    const uint32_t flags = hdr[SU_FLAGS];
-    if (flags == 0u && hdr[SU_CAND] == hdr[SU_PAIRS]) return;
-    const bool low = (flags & SF_LOW) != 0u;
+    const ScreenCounts n_unit = screen_counts(hdr);
+    if (n_unit.flags == 0u && n_unit.cand == n_unit.pairs) return;
+    const bool low = (n_unit.flags & SF_LOW) != 0u;
     const In* X = screen_x<In>(p, layer, group);
     const float* rho = reinterpret_cast<const float*>(base + U.o_rho);
     const uint16_t* cl = reinterpret_cast<const uint16_t*>(base + U.o_cl);
@@ -621,6 +642,7 @@ __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) 
             float xy, xx, yy;
             screen_products<In, 64>(X + (size_t)t * (size_t)p.ld, X + (size_t)s * (size_t)p.ld, true, p.d, lane, &xy, &xx, &yy);
             const float c = screen_cos(xy, xx, yy);
+            if (p.gamma && lane == 0 && c > 0.f) atomicMax(reinterpret_cast<uint32_t*>(p.gamma) + t, __float_as_uint(c));
             if (lane == 0 && c >= p.thr) {
                 const uint32_t at = atomicAdd(hdr + SU_EDGES, 1u);
                 if (at < (uint32_t)U.edge_cap) edge[at] = uint2{e, __float_as_uint(c)};

@@ -1,0 +1,221 @@
+// The full selection of one long sequence from the graph of near pairs (ada_screen.hpp), with every token's largest
+// correlation.  Included by ada_kernels.hip after ada_gram_dma.hpp.
+//
+// The set follows from clusters and edges alone.  A token's largest |cos| to an earlier token does as well, up to the few
+// products that compete for it: a token of a cluster is closer to its pivot than any pair that is no candidate can be, so
+// its maximum lies among the earlier members of its cluster (and the pairs k_screen_rest multiplies out); only a token
+// that is in no earlier token's cluster, a HEAD, has to meet all earlier tokens.  With K centres among T tokens heads come
+// early -- a new centre is met for the first time after about K tokens -- so their rows of the triangle are short:
+// 0.5% of it at T = 8192, K = 400, a third at K = T / 2.
+//
+//   k_screen_sort  one workgroup: the set; the members of clusters of two and more, cluster by cluster; the heads;
+//                  and the tiles that follow from both, or the word that sends the call to the full Gram instead.
+//   k_screen_gram  tiles of two kinds: the members' list against itself, a block against the blocks that its clusters reach
+//                  back to (products between clusters are wasted but not wrong: every product is one of the row's), and
+//                  the heads against the tokens before them.  64 x 64; 128 x 128 for the heads where there are many.
+#pragma once
+
+// Words of the work list (in the unit's memory for pivots, which nobody reads any more)
+enum { SW_MEMBERS = 0, SW_HEADS = 1, SW_TILES = 2, SW_TILES128 = 3, SW_FIRST = 16, SW_PRE = SW_FIRST + 256, SW_PRE128 = SW_PRE + 513,
+       SW_WORDS = SW_PRE128 + 129 };
+constexpr int SCREEN_FULL_MIN_T = 1024;                       // the work list fits the pivots' memory
+static_assert(SW_WORDS <= SCREEN_FULL_MIN_T && FUSED_MAX_T / 64 <= 256, "work list");
+// Pairs inside clusters per token above which their tiles are no saving (clusters of about 128 and more)
+constexpr uint32_t SCREEN_FULL_PAIRS = 64;
+
+struct ScreenFullParams {
+    ScreenParams s;            // one unit
+    int want_gamma, greedy, big_tiles;   // big_tiles: 64 x 64 tiles of heads from which on they are cut into 128 x 128
+    int32_t* gate;             // out: 1 = the graph does not decide, the launches behind run the full Gram
+    uint8_t* mask;             // may be NULL
+    int32_t* idx;              // may be NULL
+    int32_t* counts;
+    unsigned long long* ops;   // may be NULL
+};
+
+struct ScreenLists { int32_t *work, *member, *head; };
+__device__ inline ScreenLists screen_full_lists(const ScreenParams& p, const ScreenUnit& U) {
+    return {reinterpret_cast<int32_t*>(p.area + U.o_piv), reinterpret_cast<int32_t*>(p.area + U.o_size),
+            reinterpret_cast<int32_t*>(p.area + U.o_rho)};
+}
+
+constexpr int SCREEN_SORT_THREADS = 1024;
+inline int screen_sort_lds(int T) { return (T + 63) / 64 * 64 * 8; }   // counts (4 bytes), clusters and members (2 bytes each)
+
+// Exclusive sums of two words over the workgroup (sums: one int2 per wave, not used before).
+__device__ inline int2 screen_scan(int2 v, int2* total, int2* sums) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    int2 inc = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_up(inc.x, o, 64), y = __shfl_up(inc.y, o, 64);
+        if (lane >= o) { inc.x += x; inc.y += y; }
+    }
+    if (lane == 63) sums[wave] = inc;
+    __syncthreads();
+    int2 before = {0, 0}, all = {0, 0};
+#pragma unroll
+    for (int w = 0; w < SCREEN_SORT_THREADS / 64; ++w) {
+        const int2 x = sums[w];
+        if (w < wave) { before.x += x.x; before.y += x.y; }
+        all.x += x.x;
+        all.y += x.y;
+    }
+    *total = all;
+    return int2{before.x + inc.x - v.x, before.y + inc.y - v.y};
+}
+
+// Latency of one workgroup: everything but the lists themselves stays in LDS.  T = 8192: 17.9 us with clusters of twenty, 14.0
+// with clusters of two; T = 2048: 6.8.
+__global__ __launch_bounds__(SCREEN_SORT_THREADS) void k_screen_sort(ScreenFullParams f) {
+    extern __shared__ __align__(16) char lds[];
+    __shared__ int s_first[256], s_last[256];                 // start of the cluster a block of members starts with; last head of a block
+    __shared__ int2 s_sum[2][SCREEN_SORT_THREADS / 64];
+    const ScreenParams& p = f.s;
+    const ScreenUnit U(p.T, p.nch);
+    const int tid = threadIdx.x, T = p.T, Tp = (T + 63) & ~63;
+    const uint32_t* hdr = reinterpret_cast<const uint32_t*>(p.area);
+    const ScreenLists L = screen_full_lists(p, U);
+    uint32_t* cnt = reinterpret_cast<uint32_t*>(lds);         // members of a cluster; then the next free place in the list
+    uint32_t* cl2 = cnt + Tp;                                 // two clusters per word; bit 15: an edge to an earlier token
+    uint16_t* cl = reinterpret_cast<uint16_t*>(cl2);
+    uint16_t* list = cl + Tp;
+    const uint32_t n_edge = hdr[SU_EDGES];
+    const bool dense = hdr[SU_DENSE] != 0u;
+    const uint32_t pairs = screen_counts(hdr).pairs;
+    for (int t = tid; t < Tp; t += SCREEN_SORT_THREADS) cnt[t] = 0u;
+    for (int w = tid; w < Tp / 2; w += SCREEN_SORT_THREADS) cl2[w] = reinterpret_cast<const uint32_t*>(p.area + U.o_cl)[w];
+    // (the greedy covering takes a token that only covered tokens cover: with edges it is resolved from the pair bits)
+    if (dense || (f.greedy && n_edge) || (f.want_gamma && pairs > SCREEN_FULL_PAIRS * (uint32_t)T)) {
+        if (tid == 0) { *f.gate = 1; L.work[SW_TILES] = 0; L.work[SW_TILES128] = 0; }
+        return;
+    }
+    __syncthreads();
+    for (int t = tid; t < T; t += SCREEN_SORT_THREADS) atomicAdd(&cnt[cl[t]], 1u);
+    __syncthreads();
+    if (n_edge) {
+        for (uint32_t e = tid; e < n_edge; e += SCREEN_SORT_THREADS) {
+            const uint32_t t = reinterpret_cast<const uint2*>(p.area + U.o_edge)[e].x & 0xFFFFu;
+            atomicOr(&cl2[t >> 1], 0x8000u << (16 * (t & 1)));
+        }
+        __syncthreads();
+    }
+    const int chunk = (T + SCREEN_SORT_THREADS - 1) / SCREEN_SORT_THREADS;
+    const int lo = min(T, tid * chunk), hi = min(T, lo + chunk);
+    int n_mem = 0, n_head = 0, n_set = 0;
+    for (int t = lo; t < hi; ++t) {
+        const int n = (int)cnt[t], c = cl[t];
+        n_mem += n > 1 ? n : 0;
+        n_head += (c & 0x7FFF) == t;
+        n_set += c == t;                                      // in the set: no earlier token within the threshold
+    }
+    int2 all;                                                 // (x: members and, from bit 16 on, heads; each at most 2^14)
+    const int2 at = screen_scan(int2{n_mem | n_head << 16, n_set}, &all, s_sum[0]);
+    const int mem = all.x & 0xFFFF, heads = all.x >> 16;
+    int o_mem = at.x & 0xFFFF, o_head = at.x >> 16, o_set = at.y;
+    for (int t = lo; t < hi; ++t) {
+        const int n = (int)cnt[t], c = cl[t];
+        if (n > 1) {
+            cnt[t] = 0x80000000u | (uint32_t)o_mem;
+            for (int b = (o_mem + 63) >> 6; b * 64 < o_mem + n; ++b) s_first[b] = o_mem;
+            o_mem += n;
+        }
+        if ((c & 0x7FFF) == t) {
+            if ((o_head & 63) == 63 || o_head == heads - 1) s_last[o_head >> 6] = t;
+            L.head[o_head++] = t;
+        }
+        if (f.mask) f.mask[t] = c == t;
+        if (c == t) { if (f.idx) f.idx[o_set] = t; ++o_set; }
+    }
+    if (tid == 0) {
+        *f.gate = 0;
+        *reinterpret_cast<int4*>(f.counts) = int4{all.y, all.y, 0, ADA_OK};
+        if (f.ops) *f.ops = (unsigned long long)T * (unsigned long long)T;   // Table 6 / eq. (6)
+    }
+    if (!f.want_gamma) return;                                // uniform
+    __syncthreads();
+    for (int t = tid; t < T; t += SCREEN_SORT_THREADS) {
+        uint32_t* c = &cnt[cl[t] & 0x7FFF];
+        if (*c & 0x80000000u) {
+            const uint32_t place = atomicAdd(c, 1u) & 0x7FFFFFFFu;
+            list[place] = (uint16_t)t;
+            L.member[place] = t;
+        }
+    }
+    // tiles: threads 0 .. 255 a block of members each, 256 .. 511 a block of heads
+    int n = 0, n128 = 0;
+    if (tid < 256) {
+        if (tid * 64 < mem) {
+            n = tid - (s_first[tid] >> 6) + 1;
+            L.work[SW_FIRST + tid] = s_first[tid] >> 6;
+        }
+        if (tid < 128 && tid * 128 < heads) n128 = (s_last[min(2 * tid + 1, (heads - 1) >> 6)] + 127) >> 7;
+    } else if (tid < 512) {
+        const int b = tid - 256;
+        if (b * 64 < heads) n = (s_last[b] + 63) >> 6;
+    }
+    drain_stores();                                           // (members are placed: the clusters below are written a second time)
+    int2 tiles;
+    const int2 o = screen_scan(int2{n, n128}, &tiles, s_sum[1]);
+    if (tid <= 512) L.work[SW_PRE + tid] = o.x;               // (thread 512 has none: the total)
+    if (tid <= 128) L.work[SW_PRE128 + tid] = o.y;
+    if (tid == 256) {
+        const bool big = tiles.x - o.x >= f.big_tiles;
+        L.work[SW_MEMBERS] = mem;
+        L.work[SW_HEADS] = heads;
+        L.work[SW_TILES] = big ? o.x : tiles.x;
+        L.work[SW_TILES128] = big ? tiles.y : 0;
+    }
+    // a block meets the blocks before it only: clusters that cross from one block into the next go into token order
+    // (sixteen lanes per cluster, a member's place is the number of smaller ones)
+    for (int b = 1 + (tid >> 4); b * 64 < mem; b += SCREEN_SORT_THREADS / 16) {
+        const int st = s_first[b];
+        if ((st >> 6) + 1 != b) continue;                     // (starts with this block; seen at an earlier one)
+        const int en = (int)(cnt[cl[list[st]] & 0x7FFF] & 0x7FFFFFFFu);
+        for (int j = st + (tid & 15); j < en; j += 16) {
+            const int v = list[j];
+            int rank = 0;
+#pragma unroll 8
+            for (int i = st; i < en; ++i) rank += list[i] < v;
+            L.member[st + rank] = v;
+        }
+    }
+}
+
+// Tile u -> the block it belongs to: the one that starts at or before it (256 threads; pre: n + 1 ascending words).
+__device__ inline int screen_find(const int32_t* pre, int n, int u, int* s_found) {
+    __syncthreads();                                          // (the tile before is done with *s_found)
+    for (int i = threadIdx.x; i < n; i += 256)
+        if (pre[i] <= u && u < pre[i + 1]) *s_found = i;
+    __syncthreads();
+    return *s_found;
+}
+
+// Bound by what a CU pulls out of the L2 (1 MB per 64 x 64 tile at d = 4096 in bf16).  XCD x takes a contiguous range of the
+// heads' 128 x 128 tiles, then one of the 64 x 64 tiles.  T = 8192, d = 4096: 33 us at K = T / 20 (340 small tiles), 150 us
+// at K = T / 2, where 128 x 128 tiles replace 2600 small ones; the whole triangle takes 264 us.  DMA: whole 64-byte pieces of bf16 rows (see ada_gram_dma.hpp).
+template <typename In, bool DMA>
+__global__ __launch_bounds__(256) void k_screen_gram(ScreenParams sp, GramParams p) {
+    extern __shared__ __align__(16) char lds[];
+    __shared__ int s_found;
+    const ScreenUnit U(sp.T, sp.nch);
+    const ScreenLists L = screen_full_lists(sp, U);
+    const int total = L.work[SW_TILES], total128 = L.work[SW_TILES128], mem = L.work[SW_MEMBERS], heads = L.work[SW_HEADS];
+    const int per = (total + 7) >> 3, per128 = (total128 + 7) >> 3, xcd = (int)(blockIdx.x & 7);
+    for (int slot = (int)(blockIdx.x >> 3); slot < per128 + per; slot += (int)(gridDim.x >> 3)) {
+        if (slot < per128) {
+            const int u = xcd * per128 + slot;
+            if (u >= total128) continue;                      // uniform
+            const int i = screen_find(L.work + SW_PRE128, 128, u, &s_found), s0 = (u - L.work[SW_PRE128 + i]) * 128;
+            if constexpr (DMA) gram_tile_dma<64, true>(p, s0, i * 128, true, lds, L.head, heads);
+            else gram_tile<In, 128, true>(p, nullptr, L.head, s0, i * 128, sp.T, heads, true, lds);
+        } else {
+            const int u = xcd * per + slot - per128;
+            if (u >= total) break;                            // uniform
+            const int i = screen_find(L.work + SW_PRE, 512, u, &s_found), k = u - L.work[SW_PRE + i];
+            const bool m = i < 256;
+            const int s0 = (m ? L.work[SW_FIRST + i] + k : k) * 64, t0 = (m ? i : i - 256) * 64;
+            gram_tile<In, 64, true>(p, m ? L.member : nullptr, m ? L.member : L.head, s0, t0, m ? mem : sp.T, m ? mem : heads, true, lds);
+        }
+    }
+}

@@ -14,17 +14,18 @@ from paper_2605_03110_amd import workloads as wl
 
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 import parity  # noqa: E402
+from test_gpu_parity import greedy_reference  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
 DEV = "cuda:0"
 
 
-def activations(kind, T, d, L, dtype, seed):
+def activations(kind, T, d, L, dtype, seed, big=0):
     """L host matrices.  clusters: the usual recipe; loose: members of a cluster lie at all angles up to and beyond the
     threshold's; common: every pair's cosine is about 0.95 (no bound on a part of the row excludes it); collapsed: all
     tokens within the threshold of each other; outliers: a few columns hold most of some rows; signs: duplicates, negated
-    duplicates and zero rows."""
+    duplicates and zero rows; uneven: one cluster of `big` tokens, small ones and single tokens; single: no two tokens near."""
     rng = np.random.default_rng(seed)
     if kind == "clusters":
         return wl.layer_list(wl.small(T=T, d=d, K=max(1, T // 6), L=L, dtype=dtype, seed=seed, p=0.1))
@@ -35,7 +36,14 @@ def activations(kind, T, d, L, dtype, seed):
     for _ in range(L):
         a = rng.integers(0, K, T)
         e = rng.standard_normal((T, d)) / np.sqrt(d)
-        if kind == "loose":
+        if kind == "single":
+            X = rng.standard_normal((T, d))
+        elif kind == "uneven":
+            a[rng.permutation(T)[:big]] = 0
+            X = C[a] + 0.004 * e
+            alone = rng.random(T) < 0.2
+            X[alone] = rng.standard_normal((int(alone.sum()), d))
+        elif kind == "loose":
             X = C[a] + e * rng.uniform(0.0, 0.13, (T, 1))
         elif kind == "common":
             X = C[0] + 0.22 * e
@@ -143,3 +151,37 @@ def test_assignment_and_attention_on_the_graph_of_near_pairs(kind, T, d, L, dtyp
             chosen = np.abs(np.einsum("ij,ij->i", Xn[other], Xn[assign[other]]))
             assert (chosen >= ref["corr"][other] - 2e-4).all(), "%s layer %d" % (kind, l)
             parity.check_attention(*qkv, H, idx, assign, res["out"][l].cpu().numpy(), what="%s layer %d" % (kind, l))
+
+
+FULL = [
+    # kind, T, d, dtype, tau, greedy, big: long enough for the graph, by one rule each (greedy / fp32 / other bf16 rows / whole pieces)
+    ("clusters", 1500, 64, "bf16", 0.1, True, 0), ("clusters", 2049, 1001, "bf16", 0.1, True, 0), ("clusters", 4100, 96, "f32", 0.2, True, 0),
+    ("uneven", 1600, 200, "bf16", 0.1, True, 63), ("uneven", 1601, 128, "bf16", 0.1, True, 64), ("uneven", 1999, 96, "f32", 0.1, True, 65),
+    ("uneven", 2050, 130, "bf16", 0.1, True, 450),                     # crosses several blocks of members
+    ("uneven", 2050, 130, "bf16", 0.1, True, 700),                     # too many pairs in one cluster: the full Gram
+    ("single", 3000, 96, "bf16", 0.1, True, 0), ("single", 3000, 97, "bf16", 0.1, True, 0), ("single", 3001, 96, "f32", 0.1, True, 0),   # heads in 128 x 128
+    ("loose", 1700, 512, "bf16", 0.1, True, 0), ("signs", 1536, 256, "bf16", 0.1, True, 0), ("collapsed", 1536, 256, "f32", 0.1, True, 0),
+    ("clusters", 1536, 1088, "f32", 0.1, False, 0), ("loose", 1600, 1024, "f32", 0.1, False, 0), ("common", 1600, 1024, "f32", 0.1, False, 0),
+    ("outliers", 1600, 1024, "f32", 0.1, False, 0), ("signs", 1600, 1024, "f32", 0.1, False, 0),
+    ("clusters", 8200, 130, "bf16", 0.1, False, 0), ("loose", 3003, 1000, "bf16", 0.1, False, 0), ("single", 4999, 1280, "bf16", 0.1, False, 0),
+    ("outliers", 5000, 1280, "bf16", 0.1, False, 0),
+]
+
+
+@pytest.mark.parametrize("kind,T,d,dtype,tau,greedy,big", FULL)
+def test_full_selection_on_the_graph_of_near_pairs(kind, T, d, dtype, tau, greedy, big):
+    """Set and every token's largest correlation; also behind calls of another kind on the same workspace."""
+    print("[case] screened full selection: %s T=%d d=%d %s tau=%g greedy=%s" % (kind, T, d, dtype, tau, greedy), flush=True)
+    x_cpu = activations(kind, T, d, 1, dtype, seed=T + d, big=big)[0]
+    x, ws = x_cpu.to(DEV), pa.workspace(T, DEV)
+    for _ in range(2):
+        got = pa.fetch(pa.ada_select_full(x, tau, ws=ws, flags=pa.FLAG_GREEDY_COVER if greedy else 0))
+        if greedy:
+            ref, dfn = greedy_reference(x_cpu, tau, got["mask"]), oracle.select_full(wl.as_f64(x_cpu), tau)
+            assert np.array_equal(got["mask"], ref["mask"]) and np.array_equal(got["idx"], ref["idx"]) and got["r"] == ref["r"]
+            assert float(np.max(np.abs(got["gamma"].astype(np.float64) - dfn["gamma"]))) <= parity.GAMMA_TOL
+        else:
+            parity.check_full(x_cpu, tau, got, kind)
+        step = pa.fetch(pa.ada_cascade_step(x, tau, torch.from_numpy(got["idx"]).to(DEV), ws=ws))
+        if not greedy:
+            assert np.array_equal(step["idx"], got["idx"]) or kind in ("loose", "common")   # (chains: a removed token covers nobody)
