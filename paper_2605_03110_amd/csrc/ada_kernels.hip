@@ -1475,8 +1475,10 @@ hipError_t launch_screen_exact(const ScreenParams& sp, hipStream_t st) {
     const int rows = 256 / LPR, units = sp.G * sp.L;
     const int passes = (long long)(sp.T / (4 * rows)) * units >= 2048 ? 4 : 1;
     const int rb = (sp.T + rows * passes - 1) / (rows * passes), total = rb * units;
+    const dim3 grid((unsigned)((total + 7) / 8 * 8));
     ProfScope ps(ADA_K_SCREEN, st);
-    hipLaunchKernelGGL((k_screen_exact<In, LPR>), dim3((unsigned)((total + 7) / 8 * 8)), dim3(256), 0, st, sp, passes, rb, total);
+    if (passes == 4) hipLaunchKernelGGL((k_screen_exact<In, LPR, 4>), grid, dim3(256), 0, st, sp, rb, total);
+    else hipLaunchKernelGGL((k_screen_exact<In, LPR, 1>), grid, dim3(256), 0, st, sp, rb, total);
     return hipGetLastError();
 }
 

@@ -524,8 +524,10 @@ __device__ inline float screen_cos(float xy, float xx, float yy) {
 
 // k_screen_exact: norm of every row, product with its pivot, cluster.  HBM: X once.  Every XCD takes a contiguous range of
 // the rows of all units, so that a unit's pivots (a few hundred rows, a few MB) are read into one L2 and not into eight.
-template <typename In, int LPR>
-__global__ __launch_bounds__(256) void k_screen_exact(ScreenParams p, int passes, int row_blocks, int total) {
+// What a row needs besides X (pivot, sketch norm, the pivot's own pivot) is requested for all of a lane group's rows at
+// once, and the places that the cluster sizes hand back are summed after the last row: a row waits for X alone.
+template <typename In, int LPR, int PASSES>
+__global__ __launch_bounds__(256) void k_screen_exact(ScreenParams p, int row_blocks, int total) {
     __shared__ uint32_t s_pairs, s_flags;
     const int per = (total + 7) >> 3;
     const int w = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
@@ -542,26 +544,45 @@ __global__ __launch_bounds__(256) void k_screen_exact(ScreenParams p, int passes
     if (threadIdx.x == 0) { s_pairs = 0u; s_flags = 0u; }
     __syncthreads();
     const int li = threadIdx.x & (LPR - 1);
-    for (int k = 0; k < passes; ++k) {
-        const int t = (rb * passes + k) * (256 / LPR) + (int)threadIdx.x / LPR;
-        if (t >= p.T) break;
-        const int q = piv[t];
-        float xy, xx, yy;
-        screen_products<In, LPR>(X + (size_t)t * (size_t)p.ld, X + (size_t)q * (size_t)p.ld, q != t, p.d, li, &xy, &xx, &yy);
-        if (li == 0) {
-            const float r2 = xx > 0.f ? rho[t] / xx : 1.f;    // (a zero row has no cosines: nothing to bound)
-            rho[t] = r2;
-            if (p.inv_norm) p.inv_norm[t] = xx > 0.f ? 1.0f / sqrtf(xx) : 0.f;
-            uint32_t fl = r2 < p.f2 ? (uint32_t)SF_LOW : 0u;
-            int c = t;
-            if (q != t && screen_cos(xy, xx, yy) >= p.cos_tight) {
-                c = q;
-                if (piv[q] != q) fl |= SF_MESH;               // the pivot may not be a member of its own cluster
-                atomicAdd(&s_pairs, (uint32_t)atomicAdd(size + q, 1) + 1u);   // pairs with the pivot and with earlier arrivals
+    const int t0 = rb * PASSES * (256 / LPR) + (int)threadIdx.x / LPR;
+    int q[PASSES], qq[PASSES];
+    float ss[PASSES];
+    uint32_t place[PASSES], fl = 0u;
+#pragma unroll
+    for (int k = 0; k < PASSES; ++k) {
+        const int t = min(t0 + k * (256 / LPR), p.T - 1);
+        q[k] = piv[t];
+        ss[k] = rho[t];
+    }
+#pragma unroll
+    for (int k = 0; k < PASSES; ++k) { qq[k] = piv[q[k]]; place[k] = 0u; }
+#pragma unroll
+    for (int k = 0; k < PASSES; ++k) {
+        const int t = t0 + k * (256 / LPR);
+        if (t < p.T) {
+            float xy, xx, yy;
+            screen_products<In, LPR>(X + (size_t)t * (size_t)p.ld, X + (size_t)q[k] * (size_t)p.ld, q[k] != t, p.d, li, &xy, &xx, &yy);
+            if (li == 0) {
+                const float r2 = xx > 0.f ? ss[k] / xx : 1.f;     // (a zero row has no cosines: nothing to bound)
+                rho[t] = r2;
+                if (p.inv_norm) p.inv_norm[t] = xx > 0.f ? 1.0f / sqrtf(xx) : 0.f;
+                fl |= r2 < p.f2 ? (uint32_t)SF_LOW : 0u;
+                int c = t;
+                if (q[k] != t && screen_cos(xy, xx, yy) >= p.cos_tight) {
+                    c = q[k];
+                    if (qq[k] != q[k]) fl |= SF_MESH;             // the pivot may not be a member of its own cluster
+                    place[k] = (uint32_t)atomicAdd(size + q[k], 1) + 1u;   // pairs with the pivot and with earlier arrivals
+                }
+                cl[t] = (uint16_t)c;
             }
-            cl[t] = (uint16_t)c;
-            if (fl) atomicOr(&s_flags, fl);
         }
+    }
+    if (li == 0) {
+        uint32_t n = 0u;
+#pragma unroll
+        for (int k = 0; k < PASSES; ++k) n += place[k];
+        if (n) atomicAdd(&s_pairs, n);
+        if (fl) atomicOr(&s_flags, fl);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
