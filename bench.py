@@ -83,6 +83,11 @@ def cpu_baseline_extras():
     return out
 
 
+def device_us(kern, calls):
+    """Time of all kernels of a call (ada_profile_collect over that many calls)."""
+    return 1e3 * sum(v["ms"] for v in kern.values()) / calls
+
+
 def recorded_traffic(name):
     """HBM bytes per launch from the committed rocprofv3 --pmc summary of this kernel and workload (FETCH_SIZE and
     WRITE_SIZE scaled by the copy probe), or None if no summary is there."""
@@ -195,7 +200,6 @@ def main():
     assert counts[:, 3].tolist() == [0] * L, "device status reported an error"
     rep = pa.ada_cascade_report(counts, ops, T)
     r_per_layer = counts[:, 0].tolist()
-    r_prev_mean = sum(r_per_layer[:-1]) / max(L - 1, 1)
 
     result = {
         "metric": "cascade_select_layers_per_s", "value": layers_per_s, "unit": "layers/s", "n_gpus": 1,
@@ -225,27 +229,14 @@ def main():
         kern = pa.ada_profile_collect()
         pa.ada_profile_enable(False)
         avg_us = {k: (1e3 * v["ms"] / v["launches"] if v["launches"] else None) for k, v in kern.items()}
-        casc_s = 1e-6 * avg_us["cascade_fused"]
-        # The cascade layers of a pass run in one resident launch (k_cascade_pass) when the shape allows, else one
-        # launch per layer: the units of a launch are the layers it processes.
-        layers_per_launch = (L - 1) * args.steps / kern["cascade_fused"]["launches"]
-        # algorithmic bytes per layer: every row of X once (all T rows are tested rows, the r inherited rows are also
-        # the resident operand) = T*d*e bytes; the O(T*r/8) hit words and O(T) outputs are neglected
+        # The layers of a pass share their launches (sketches, pairs, exact products, rest, walk, lists), so the unit is the
+        # pass: every row of every layer once; the sketches' share read twice and the O(T) outputs are neglected.
+        pass_us = device_us(kern, args.steps)
         layer_bytes = T * d * esz
-        casc_bytes = layers_per_launch * layer_bytes
-        casc_flops = layers_per_launch * 2.0 * d * T * r_prev_mean   # T x r Gram entries of eq. (6), 2d flops each
-        traffic_layer = recorded_traffic("cascade_fused_c%d_pmc.txt" % args.config)
-        result["roofline"] = {"bound": "hbm",
-                              "kernel": "k_cascade_pass (Algorithm 1, %g layers per resident launch)" % layers_per_launch
-                                        if layers_per_launch > 1 else "k_cascade_fused (Algorithm 1 in one launch)",
-                              "achieved": casc_bytes / casc_s / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                              "frac": casc_bytes / casc_s / 1e9 / HBM_PEAK_GBS,
-                              "traffic": None if traffic_layer is None else int(traffic_layer * layers_per_launch),
-                              "avg_launch_us": avg_us["cascade_fused"], "layers_per_launch": layers_per_launch,
-                              "us_per_layer": avg_us["cascade_fused"] / layers_per_launch,
-                              "bytes_per_launch": casc_bytes,
-                              "mfma_tflops": casc_flops / casc_s / 1e12,
-                              "mfma_frac": casc_flops / casc_s / 1e12 / MFMA_BF16_PEAK_TFLOPS}
+        result["roofline"] = {"bound": "hbm", "kernel": "layer loop (all kernels of a pass)",
+                              "achieved": L * layer_bytes / (1e-6 * pass_us) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                              "frac": L * layer_bytes / (1e-6 * pass_us) / 1e9 / HBM_PEAK_GBS, "traffic": None,
+                              "us_per_pass": pass_us, "us_per_layer": pass_us / L, "bytes_per_pass": L * layer_bytes}
         result["kernel_avg_us"] = avg_us
         result["ms_per_step_with_events"] = 1e3 * prof_elapsed / args.steps
     if args.roofline_only:
@@ -443,7 +434,7 @@ def main():
         result["batched"]["stacked_one_launch_per_step"] = {
             "ms_per_batch_pass": 1e3 * g_elapsed / nb, "layers_per_s": Bq * L * nb / g_elapsed,
             "tokens_per_s": Bq * L * nb / g_elapsed * T,
-            "cascade_launch_us": 1e3 * kg["cascade_fused"]["ms"] / kg["cascade_fused"]["launches"]}
+            "us_per_layer": device_us(kg, 1) / L}
         del xg
         # ---- sixteen stacked sequences (four layers each): the regime in which a launch's fixed chain of memory round
         # trips is shared by enough tiles to matter little, i.e. what the tile engine itself sustains
@@ -462,15 +453,13 @@ def main():
         torch.cuda.synchronize()
         k16 = pa.ada_profile_collect()
         pa.ada_profile_enable(False)
-        us16 = 1e3 * k16["cascade_fused"]["ms"] / k16["cascade_fused"]["launches"]
-        r16 = float(o16["counts"][:, :-1, 0].float().mean())
+        us16 = device_us(k16, 5) / L16
         result["batched"]["stacked_16_sequences"] = {
-            "sequences": B16, "layers": L16, "cascade_launch_us": us16, "us_per_layer_and_sequence": us16 / B16,
-            "roofline": {"bound": "hbm", "kernel": "k_cascade_fused (16 problems per launch)",
+            "sequences": B16, "layers": L16, "us_per_layer": us16, "us_per_layer_and_sequence": us16 / B16,
+            "roofline": {"bound": "hbm", "kernel": "layer loop (16 sequences per launch)",
                          "achieved": B16 * layer_bytes / (1e-6 * us16) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": B16 * layer_bytes / (1e-6 * us16) / 1e9 / HBM_PEAK_GBS,
-                         "bytes_per_launch": B16 * layer_bytes,
-                         "mfma_frac": B16 * 2.0 * d * T * r16 / (1e-6 * us16) / 1e12 / MFMA_BF16_PEAK_TFLOPS}}
+                         "bytes_per_layer": B16 * layer_bytes}}
         del x16, ws16, o16
         # ---- a representative set per head (Section 8.5): the H column blocks of X as H problems in one launch
         Hh = 16 if d % 16 == 0 else 1
@@ -496,7 +485,7 @@ def main():
         assert ch[:, :, 3].flatten().tolist() == [0] * (Hh * L), "per-head pass reported an error"
         result["per_head"] = {"heads": Hh, "d_h": d // Hh, "ms_per_pass": 1e3 * h_elapsed / nb,
                               "layers_per_s": L * nb / h_elapsed,
-                              "cascade_launch_us_all_heads": 1e3 * kh["cascade_fused"]["ms"] / kh["cascade_fused"]["launches"],
+                              "us_per_layer_all_heads": device_us(kh, 1) / L,
                               "mean_r_h": float(ch[:, 1:, 0].float().mean())}
         del wsb, outb, hv, wsh, outh
 
@@ -518,17 +507,12 @@ def main():
             torch.cuda.synchronize()
             ko = pa.ada_profile_collect()
             pa.ada_profile_enable(False)
-            us_o = 1e3 * ko["cascade_fused"]["ms"] / ko["cascade_fused"]["launches"]
+            us_o = device_us(ko, 5) / len(xo)
             by = wo.T * wo.d * (2 if wo.dtype == "bf16" else 4)
             r_in = float(oo["counts"][:-1, 0].float().mean())         # the sets the timed steps inherited
-            fl = 2.0 * wo.d * wo.T * r_in                             # T x r Gram entries of eq. (6), 2 d flops each
             other[wo.name] = {"T": wo.T, "d": wo.d, "mean_r": float(oo["counts"][1:, 0].float().mean()),
-                              "mean_r_inherited": r_in, "cascade_launch_us": us_o,
-                              "hbm_frac": by / (1e-6 * us_o) / 1e9 / HBM_PEAK_GBS,
-                              "mfma_tflops": fl / (1e-6 * us_o) / 1e12,
-                              "mfma_frac": fl / (1e-6 * us_o) / 1e12 / MFMA_BF16_PEAK_TFLOPS,
-                              "bound": "mfma" if fl / (MFMA_BF16_PEAK_TFLOPS * 1e12) > by / (HBM_PEAK_GBS * 1e9) else "hbm",
-                              "traffic": recorded_traffic("cascade_fused_c%d_pmc.txt" % ci)}
+                              "mean_r_inherited": r_in, "us_per_layer": us_o,
+                              "hbm_frac": by / (1e-6 * us_o) / 1e9 / HBM_PEAK_GBS}
             del xo, wso, oo
         # configs[4] as the configuration states it: a batch of four sequences, here stacked in one tensor with one
         # launch per step for all four (three layers of each)
@@ -549,15 +533,12 @@ def main():
             torch.cuda.synchronize()
             k4g = pa.ada_profile_collect()
             pa.ada_profile_enable(False)
-            us_g = 1e3 * k4g["cascade_fused"]["ms"] / k4g["cascade_fused"]["launches"]
+            us_g = device_us(k4g, 4) / L4
             by4 = B4 * w4b.T * w4b.d * 2
-            r4 = float(o4["counts"][:, :-1, 0].float().mean())
-            fl4 = 2.0 * w4b.d * w4b.T * r4 * B4
             other[w4b.name + "_batch4_stacked"] = {"T": w4b.T, "d": w4b.d, "sequences": B4,
                                                    "mean_r": float(o4["counts"][:, 1:, 0].float().mean()),
-                                                   "cascade_launch_us": us_g, "us_per_layer_and_sequence": us_g / B4,
-                                                   "hbm_frac": by4 / (1e-6 * us_g) / 1e9 / HBM_PEAK_GBS,
-                                                   "mfma_frac": fl4 / (1e-6 * us_g) / 1e12 / MFMA_BF16_PEAK_TFLOPS}
+                                                   "us_per_layer": us_g, "us_per_layer_and_sequence": us_g / B4,
+                                                   "hbm_frac": by4 / (1e-6 * us_g) / 1e9 / HBM_PEAK_GBS}
             # the configuration's own schedule on these layers: the cascade at every layer, and the full T x T selection
             # of all four sequences at layer 0 and at every 8th layer (here: layers 0 and L4 - 1 stand for 0 and 8)
             m4 = torch.empty((B4, w4b.T), dtype=torch.uint8, device=dev)
@@ -583,8 +564,7 @@ def main():
             del x4g, ws4g, o4
         result["cascade_other_shapes"] = other
 
-        # ---- the greedy covering of Section 2.5 on layer 0 (pair bits from the register-staged Gram tiles, then the
-        # sequential resolution by one workgroup)
+        # ---- the greedy covering of Section 2.5 on layer 0
         if T <= 16384:
             for _ in range(2):
                 gsel = pa.ada_select_full(xs[0], w.tau, ws=ws, stream=stream, flags=pa.FLAG_GREEDY_COVER)
@@ -596,11 +576,10 @@ def main():
             kgr = pa.ada_profile_collect()
             pa.ada_profile_enable(False)
             result["greedy_cover"] = {"r": int(gsel["counts"][0]),
-                                      "gram_us": 1e3 * kgr["gram_full"]["ms"] / kgr["gram_full"]["launches"],
-                                      "resolve_us": 1e3 * kgr["update"]["ms"] / kgr["update"]["launches"]}
+                                      "us": device_us(kgr, 5)}
 
-        # ---- the same selection at the long-context shape (configs[4]: T=8192, d=4096, one sequence), where the
-        # triangle has enough tiles to fill the chip and the kernel is bound by the matrix pipes
+        # ---- the same selection at the long-context shape (T=8192, d=4096, one sequence), every token's correlation
+        # included: from the graph of near pairs
         w4 = wl.config(4)
         x4 = next(iter(wl.layers(w4, 0, 1))).to(dev)
         ws4 = pa.workspace(w4.T, dev)
@@ -613,15 +592,12 @@ def main():
         torch.cuda.synchronize()
         k4 = pa.ada_profile_collect()
         pa.ada_profile_enable(False)
-        us4 = 1e3 * k4["gram_full"]["ms"] / k4["gram_full"]["launches"]
-        flops4 = float(w4.T) * (w4.T - 1) * w4.d
+        us4, bytes4 = device_us(k4, 5), w4.T * w4.d * (2 if w4.dtype == "bf16" else 4)
         result["full_select_long"] = {"workload": "%s layer 0: T=%d d=%d %s, one sequence" % (w4.name, w4.T, w4.d, w4.dtype),
-                                      "roofline": {"bound": "mfma", "kernel": "k_gram_dma (full lower-triangular Gram)",
-                                                   "achieved": flops4 / (1e-6 * us4) / 1e12, "peak": MFMA_BF16_PEAK_TFLOPS,
-                                                   "unit": "TFLOP/s", "frac": flops4 / (1e-6 * us4) / 1e12 / MFMA_BF16_PEAK_TFLOPS,
-                                                   "frac_of_sustained": flops4 / (1e-6 * us4) / 1e12 / mfma_sustained,
-                                                   "avg_launch_us": us4, "flops_per_launch": flops4,
-                                                   "traffic": recorded_traffic("gram_full_c4_pmc.txt")}}
+                                      "roofline": {"bound": "hbm", "kernel": "full selection (all kernels of a call)",
+                                                   "achieved": bytes4 / (1e-6 * us4) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                                                   "frac": bytes4 / (1e-6 * us4) / 1e9 / HBM_PEAK_GBS, "traffic": None,
+                                                   "us_per_call": us4, "bytes_per_call": bytes4}}
 
     if not args.no_cpu_baseline:
         result["cpu_baseline"] = cpu_baseline(w, xs_cpu)
