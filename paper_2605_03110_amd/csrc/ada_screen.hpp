@@ -279,14 +279,16 @@ __device__ inline int screen_row(int i) { return (i & 3) + 8 * ((i >> 2) & 3); }
 
 // Work items of a unit: strips of 256 tokens, each against its earlier tokens in pieces.  A piece is 256 x `wide` tokens, or
 // 256 / `cut` of them: long pieces spend less of their time on starting up (a piece of 256 took about half of it for
-// that), short ones are needed to fill the chip.  Strips come in groups of `wide` with the same number of pieces.
+// that), short ones are needed to fill the chip.  Two workgroups per CU fill it: halved pieces up to four per CU cost a layer
+// loop of 12 x T=2048, d=768 50.8 us instead of 48.7, 2 x T=4096, d=512 36.0 instead of 34.0.  Strips come in groups of
+// `wide` with the same number of pieces.
 struct PairItems {
     int wide, cut, per_unit;
     __host__ __device__ PairItems(int T, int units) {
         const int nb = (T + 255) / 256;
         const long long tiles = (long long)nb * (nb + 1) / 2 * units;
         wide = tiles >= 12288 ? 4 : tiles >= 6144 ? 2 : 1;
-        cut = tiles >= 1024 ? 1 : tiles >= 512 ? 2 : 4;
+        cut = tiles >= 512 ? 1 : tiles >= 256 ? 2 : 4;
         const int q = (nb + wide - 1) / wide;
         per_unit = wide * (q * (q + 1) / 2) * cut;
     }
