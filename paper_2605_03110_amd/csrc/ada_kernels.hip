@@ -44,7 +44,8 @@ enum { MODE_FULL = 0, MODE_REP = 1, MODE_CROSS = 2 };
 constexpr size_t META_BYTES = 2048;
 enum { META_R = 0, META_NONREP = 1, META_STATUS = 2, META_GATE = 3 /* k_screen_sort */, META_TICKET = 4, META_QUEUE = 5 /* and 6 */, META_EPOCH = 7,
        // screened selection: layers done so far; work queue, hand-over word and sign-off counter of k_cascade_rest (zero between calls)
-       META_PROGRESS = 8, META_REST_QUEUE = 9, META_REST_EPOCH = 10, META_REST_LEFT = 11, META_WORDS = 12 };
+       META_PROGRESS = 8, META_REST_QUEUE = 9, META_REST_EPOCH = 10, META_REST_LEFT = 11,
+       META_ALONE = 12 /* and 13: layers of a launch whose assignment the graph leaves open, one bit each */, META_WORDS = 14 };
 
 // The one-launch cascade step keeps one hit word per token and per 32 inherited representatives; beyond this T
 // the table would dominate the workspace and the two-launch path is used instead.

@@ -782,6 +782,41 @@ __device__ inline void screen_lists(const ChainParams& c, const ScreenUnit& SU, 
     __syncthreads();
 }
 
+// Whether a layer with edges has a token outside the set that no representative is within the threshold of: neither its
+// cluster nor an edge leads to a member of the set.  (Definition 2.2 compares with all earlier tokens, and step 5 drops an
+// inherited token that any earlier inherited one hits, so on a chain a ~ b ~ c with a not ~ c both b and c leave the set,
+// and so do the members of b's or c's cluster.)  All threads, after the set is known; leaves marks, and slots of this layer
+// that say nothing about it any more.
+template <int THREADS, int U>
+__device__ inline bool chain_alone(uint32_t n_edge, const uint2* edge, uint32_t stamp, uint32_t* slot, uint8_t* mark,
+                                   const int (&cid)[U], const unsigned long long (&in)[U], int T) {
+    const int tid = threadIdx.x, lane = tid & 63;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int t = u * THREADS + tid;
+        slot[cid[u]] = 0xFFFFFFFFu;
+        if (t < T) mark[t] = (in[u] >> lane) & 1ull ? 1 : 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if ((in[u] >> lane) & 1ull) slot[cid[u]] = stamp;
+    for (uint32_t e = tid; e < n_edge; e += THREADS) {        // (a member's mark is read, only the others' are written)
+        const uint32_t v = edge[e].x;
+        const int s = (int)(v >> 16), t = (int)(v & 0xFFFFu);
+        if ((mark[s] & 1) && !(mark[t] & 1)) mark[t] = 2;
+        if ((mark[t] & 1) && !(mark[s] & 1)) mark[s] = 2;
+    }
+    __syncthreads();
+    int alone = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int t = u * THREADS + tid;
+        alone |= t < T && slot[cid[u]] != stamp && mark[min(t, T - 1)] == 0;
+    }
+    return __syncthreads_or(alone) != 0;
+}
+
 // A layer that has edges (all threads; the marks are zero on entry, barriers inside; on return some marks are set).
 template <int THREADS, int U>
 __device__ inline void chain_edges(bool full, int earlier_only, uint32_t n_edge, const uint2* edge, uint32_t stamp,
@@ -848,8 +883,9 @@ __device__ inline void chain_edges(bool full, int earlier_only, uint32_t n_edge,
 }
 
 // The nearest representative of every token of a layer: all representatives within the threshold of a token are members
-// of its cluster or joined to it by an edge, and a token outside the set is within the threshold of one (it is covered), so
-// the largest |cos| is among these; usually there is just one and nothing has to be multiplied.  (any workgroup size up to
+// of its cluster or joined to it by an edge, so if there is one the largest |cos| is among these; usually there is just one
+// and nothing has to be multiplied.  Layers with a token that has none (chain_alone; only layers with edges can) do not come
+// here: their assignment takes the products with the whole set, on the tiles of k_cascade_rest.  (any workgroup size up to
 // 1024; scratch: LIST_SCRATCH + 8 bytes per token, rounded up to 64 tokens, of LDS)
 __device__ inline void screen_assign(const ChainParams& c, const ScreenUnit& SU, int l, int g, int* scratch) {
     const ScreenParams& p = c.s;
@@ -918,7 +954,7 @@ __device__ inline void screen_assign(const ChainParams& c, const ScreenUnit& SU,
         const uint32_t nm = tt < T ? n_member[cl[tt]] : 0u;
         const unsigned long long k = mine ? __hip_atomic_load(key + tt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
         if (tt < T && !mine) put(tt, tt);
-        if (mine && nm == 0u) put(tt, INT_MAX - (int)(uint32_t)k);
+        if (mine && nm == 0u && k != 0ull) put(tt, INT_MAX - (int)(uint32_t)k);
         if (mine && nm == 1u && k == 0ull) put(tt, (int)member[cl[tt]]);
         unsigned long long open = __ballot(mine && nm > 0u && (nm > 1u || k != 0ull));
         while (open) {
@@ -953,6 +989,7 @@ template <int THREADS, int U, bool TWO>
 __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
     extern __shared__ __align__(16) char lds[];
     __shared__ uint32_t s_edges[SCREEN_MAX_LAYERS], s_dense[SCREEN_MAX_LAYERS];
+    unsigned long long alone = 0ull;                          // layers whose assignment is left to the tiles (uniform)
     const ScreenParams& p = c.s;
     const ScreenUnit SU(p.T, p.nch);
     const int tid = threadIdx.x, T = p.T, g = blockIdx.x, lane = tid & 63;
@@ -982,7 +1019,10 @@ __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
         exists[u] = __ballot(u * THREADS + tid < T);
     }
     if (p.first > 0) {                                        // go on from the set an earlier launch left
-        if (progress != p.first) return;
+        if (progress != p.first) {
+            if (tid == 0) *reinterpret_cast<unsigned long long*>(meta + META_ALONE) = 0ull;
+            return;
+        }
         __syncthreads();
         const int32_t* idx = c.idx + (long long)g * c.list_gs + (size_t)(p.first - 1) * T;
         const int r = c.counts[(long long)g * c.counts_gs + (size_t)(p.first - 1) * 4];
@@ -1029,6 +1069,7 @@ __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
             if (n_edge) {
                 const uint2* edge = reinterpret_cast<const uint2*>(area + (long long)i * SU.bytes + SU.o_edge);
                 chain_edges<THREADS, U>(p.first + i == 0, c.earlier_only, n_edge, edge, stamp, slot, mark, cid, in, T);
+                if (c.assign && chain_alone<THREADS, U>(n_edge, edge, stamp, slot, mark, cid, in, T)) alone |= 1ull << i;
                 for (int t = tid; t < Tp; t += THREADS) mark[t] = 0;
                 __syncthreads();
             } else if (p.first + i == 0) {                    // Definition 2.2: a cluster's pivot is earlier than its other members
@@ -1060,20 +1101,26 @@ __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
             }
         }
     }
-    if (stop) {                                               // the launch behind needs the units' memory for its hit table
+    // lists that the launch behind reads; all of them if it needs the units' memory for its hit table
+    if (stop || alone != 0ull) {
         __syncthreads();
         for (int l = 0; l < i; ++l) {
-            screen_lists(c, SU, l, g, reinterpret_cast<int*>(lds));
-            if (c.assign) screen_assign(c, SU, l, g, reinterpret_cast<int*>(lds));
+            const bool tiles = (alone >> l) & 1ull;
+            if (stop || tiles) screen_lists(c, SU, l, g, reinterpret_cast<int*>(lds));
+            if (stop && c.assign && !tiles) screen_assign(c, SU, l, g, reinterpret_cast<int*>(lds));
         }
     }
-    if (tid == 0) meta[META_PROGRESS] = p.first + i;
+    if (tid == 0) {
+        meta[META_PROGRESS] = p.first + i;
+        *reinterpret_cast<unsigned long long*>(meta + META_ALONE) = alone;
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
 // k_cascade_rest: the lists of all layers, one workgroup per layer -- or, when the chain stopped at a dense layer (and wrote
-// the lists before it), that layer and all after it on the tiles of k_cascade_fused.  Work items (step, worker) are handed
-// out in order by a counter, and an item waits for the previous step's set before it starts: every item of an earlier step
+// the lists before it), that layer and all after it on the tiles of k_cascade_fused.  Before those the assignments that the
+// graph leaves open (META_ALONE; the chain wrote these layers' lists), on the same tiles.  Work items (step, worker) are handed
+// out in order by a counter, and an item waits for the previous step before it starts: every item of an earlier step
 // is by then with a workgroup that runs, so the wait ends however few workgroups are resident, and nothing is assumed
 // about that.  Layer 0 is a step that inherits every token: Algorithm 1's step 5 on the identity list is Definition 2.2.
 struct RestParams {
@@ -1093,13 +1140,16 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
     const int workers = p.groups > 1 ? p.wpg : p.grid;
     int32_t* meta = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(rp.c.s.meta) + (long long)g * p.ws_gs);
     const int start = meta[META_PROGRESS];
+    const unsigned long long alone = *reinterpret_cast<const unsigned long long*>(meta + META_ALONE);
     if (start >= first + n_layers) {
         const ScreenUnit SU(T, rp.c.s.nch);
         for (int j = worker; j < n_layers * (rp.c.assign ? 2 : 1); j += workers) {
-            if (j < n_layers) screen_lists(rp.c, SU, j, g, reinterpret_cast<int*>(lds));
-            else screen_assign(rp.c, SU, j - n_layers, g, reinterpret_cast<int*>(lds));
+            const int l = j < n_layers ? j : j - n_layers;
+            if ((alone >> l) & 1ull) continue;
+            if (j < n_layers) screen_lists(rp.c, SU, l, g, reinterpret_cast<int*>(lds));
+            else screen_assign(rp.c, SU, l, g, reinterpret_cast<int*>(lds));
         }
-        return;
+        if (alone == 0ull) return;
     }
     p.hits = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(p.hits) + (long long)g * p.ws_gs);
     p.ticket = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(p.ticket) + (long long)g * p.ws_gs);
@@ -1110,31 +1160,42 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
     int32_t* cnt0 = rp.c.counts + (long long)g * p.counts_gs;
     unsigned long long* ops0 = rp.c.ops + (long long)g * p.ops_gs;
     const int per_layer = rp.c.assign ? 2 : 1;                // steps of a layer: the set, and the assignment to it if wanted
+    const int n_alone = __popcll(alone), steps = n_alone + (first + n_layers - start) * per_layer;
+    auto layer_of = [&](int step) {                           // (the assignments left open come first)
+        if (step >= n_alone) return start + (step - n_alone) / per_layer;
+        unsigned long long m = alone;
+        for (int k = 0; k < step; ++k) m &= m - 1ull;
+        return first + __ffsll((long long)m) - 1;
+    };
     for (;;) {
         __syncthreads();
         if (threadIdx.x == 0) {
-            const int item = atomicAdd(meta + META_REST_QUEUE, 1), step = item / workers, i = start + step / per_layer;
+            const int item = atomicAdd(meta + META_REST_QUEUE, 1), step = item / workers;
             int word = -1;                                    // size of the set that the step works with
-            if (i < first + n_layers) {
-                if (step == 0) word = i == 0 ? T : cnt0[(size_t)(i - 1) * 4];
-                else
-                    for (int n = 0; n < rp.spin_limit; ++n) {
-                        const int v = __hip_atomic_load(meta + META_REST_EPOCH, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        if ((v >> 15) == step) { word = v & 0x7FFF; break; }
-                        __builtin_amdgcn_s_sleep(2);
-                    }
-                if (word < 0) cnt0[(size_t)i * 4 + 3] = ADA_ERR_DEVICE;   // (not reached: see above)
+            if (step < steps) {
+                int before = step == 0 ? 0 : -1;              // size of the set that the step before left
+                for (int n = 0; step > 0 && n < rp.spin_limit; ++n) {
+                    const int v = __hip_atomic_load(meta + META_REST_EPOCH, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if ((v >> 15) == step) { before = v & 0x7FFF; break; }
+                    __builtin_amdgcn_s_sleep(2);
+                }
+                const int i = layer_of(step);
+                if (before < 0) cnt0[(size_t)i * 4 + 3] = ADA_ERR_DEVICE;   // (not reached: see above)
+                else if (step < n_alone) word = cnt0[(size_t)i * 4];        // sets of the launch before
+                else if (step == n_alone) word = i == 0 ? T : cnt0[(size_t)(i - 1) * 4];
+                else word = before;
             }
             s_item = item;
             s_word = word;
         }
         __syncthreads();
         const int item = s_item, r = s_word;
-        const int step = item / workers, local = item - step * workers, i = start + step / per_layer;
-        if (i >= first + n_layers || r < 0) break;            // uniform
+        const int step = item / workers, local = item - step * workers;
+        if (step >= steps || r < 0) break;                    // uniform
+        const int i = layer_of(step);
         const size_t row = (size_t)i * (size_t)T;
         p.X = reinterpret_cast<const char*>(rp.c.s.X[i - first]) + (long long)g * p.x_gs;
-        p.assign_mode = per_layer == 2 && (step & 1);
+        p.assign_mode = step < n_alone || (per_layer == 2 && ((step - n_alone) & 1));
         if (p.assign_mode) {
             p.list_mode = LIST_COHERENT;
             p.prev_idx = idx0 + row;

@@ -25,7 +25,9 @@ def activations(kind, T, d, L, dtype, seed, big=0):
     """L host matrices.  clusters: the usual recipe; loose: members of a cluster lie at all angles up to and beyond the
     threshold's; common: every pair's cosine is about 0.95 (no bound on a part of the row excludes it); collapsed: all
     tokens within the threshold of each other; outliers: a few columns hold most of some rows; signs: duplicates, negated
-    duplicates and zero rows; uneven: one cluster of `big` tokens, small ones and single tokens; single: no two tokens near."""
+    duplicates and zero rows; uneven: one cluster of `big` tokens, small ones and single tokens; single: no two tokens near;
+    strays: tight clusters, one token in ten at any angle up to and beyond the threshold's, and three tokens a ~ b ~ c with a
+    not ~ c: few edges, and tokens outside the set that no representative covers."""
     rng = np.random.default_rng(seed)
     if kind == "clusters":
         return wl.layer_list(wl.small(T=T, d=d, K=max(1, T // 6), L=L, dtype=dtype, seed=seed, p=0.1))
@@ -45,6 +47,11 @@ def activations(kind, T, d, L, dtype, seed, big=0):
             X[alone] = rng.standard_normal((int(alone.sum()), d))
         elif kind == "loose":
             X = C[a] + e * rng.uniform(0.0, 0.13, (T, 1))
+        elif kind == "strays":
+            X = C[a] + e * np.where(rng.random((T, 1)) < 0.1, rng.uniform(0.0, 0.13, (T, 1)), 0.004)
+            u, v = np.linalg.qr(rng.standard_normal((d, 2)))[0].T
+            for i, t in enumerate(np.sort(rng.permutation(T)[:3])):
+                X[t] = np.cos(0.1 * i) * u + np.sin(0.1 * i) * v
         elif kind == "common":
             X = C[0] + 0.22 * e
         elif kind == "collapsed":
@@ -151,6 +158,43 @@ def test_assignment_and_attention_on_the_graph_of_near_pairs(kind, T, d, L, dtyp
             chosen = np.abs(np.einsum("ij,ij->i", Xn[other], Xn[assign[other]]))
             assert (chosen >= ref["corr"][other] - 2e-4).all(), "%s layer %d" % (kind, l)
             parity.check_attention(*qkv, H, idx, assign, res["out"][l].cpu().numpy(), what="%s layer %d" % (kind, l))
+
+
+# T, d, L, tau, seed (tests/test_screen_replay.py shows on the CPU that the graph lists these layers)
+STRAYS = [(512, 768, 4, 0.1, 1), (300, 256, 3, 0.1, 2), (1000, 1024, 6, 0.1, 3)]
+
+
+@pytest.mark.parametrize("T,d,L,tau,seed,dtype,dense", [c + (t, -1) for c in STRAYS for t in ("bf16", "f32")] +
+                         [(300, 256, 19, 0.1, 2, "bf16", -1), (512, 768, 5, 0.1, 1, "bf16", 3), (300, 256, 4, 0.1, 2, "f32", 2)])
+def test_assignment_of_tokens_that_no_representative_covers(T, d, L, tau, seed, dtype, dense):
+    """Their nearest representative is the whole set's, also in front of a layer that is left to the tiles (`dense`) and
+    behind a batch of layers: the choice is a member of R within 2e-4 of the float64 maximum, and the attention follows it."""
+    print("[case] strays: T=%d d=%d L=%d %s dense=%d" % (T, d, L, dtype, dense), flush=True)
+    xs_cpu = activations("strays", T, d, L, dtype, seed=seed)
+    if dense >= 0:
+        xs_cpu[dense] = activations("common", T, d, 1, dtype, seed=seed)[0]
+    H = d // 64
+    rng = np.random.default_rng(5)
+    qkv = [wl.to_dtype(rng.standard_normal((T, d), dtype=np.float32), dtype) for _ in range(3)]
+    ws = pa.workspace_batched(T, 2, DEV)
+    alone = 0
+    for _ in range(2):                            # the second call finds the workspace as the first left it
+        res = pa.ada_pipeline_layers([x.to(DEV) for x in xs_cpu], *([m.to(DEV)] * L for m in qkv), H, tau, ws=ws)
+        torch.cuda.synchronize()
+        layers = pa.ada_cascade_layers([x.to(DEV) for x in xs_cpu], tau)
+        for l in range(L):
+            r = int(res["counts"][l, 0])
+            idx, assign = res["idx"][l, :r].cpu().numpy(), res["assign"][l].cpu().numpy()
+            assert r == int(layers["counts"][l, 0]) and torch.equal(res["idx"][l, :r], layers["idx"][l, :r])
+            assert res["info"][l].cpu().tolist() == [T - r, 0, 0, 0, r, 0, 0, 0]
+            assert np.array_equal(assign[idx], idx) and np.isin(assign, idx).all(), "layer %d" % l
+            Xn, _ = oracle.normalize(wl.as_f64(xs_cpu[l]))
+            chosen = np.abs(np.einsum("ij,ij->i", Xn, Xn[assign]))
+            best = oracle.assign_nearest(wl.as_f64(xs_cpu[l]), idx)["corr"]
+            assert (chosen >= best - 2e-4).all(), "layer %d" % l
+            alone += int((best < 1.0 - tau * tau - 1e-4).sum())
+            parity.check_attention(*qkv, H, idx, assign, res["out"][l].cpu().numpy(), what="strays layer %d" % l)
+    assert alone > 0
 
 
 FULL = [

@@ -1,0 +1,84 @@
+"""The argument of the layer loops on the graph of near pairs (csrc/ada_screen.hpp), replayed in float64 on the CPU: pivots,
+clusters, edges, the walk and the assignment read off them, against the oracle.  The inputs are those of a GPU test: the
+graph lists their layers (none is dense), and they hold tokens that no representative covers."""
+import math
+import os
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2605_03110_amd import workloads as wl
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+from test_gpu_screen import STRAYS, activations  # noqa: E402
+
+
+def plan(d, tau):
+    """screen_plan for rows longer than the sketch: column groups, candidate threshold, cosine of a cluster."""
+    thr = 1.0 - tau * tau
+    nk = (d + 63) // 64
+    for nch in range(1, nk):
+        n = 64 * nch
+        kappa = max(0.3, math.sqrt(1.0 - math.exp(-44.0 / (n - 1))))
+        if kappa + 0.13 > 0.93:
+            continue
+        f2 = (1.0 - (thr - 2e-4)) / (1.0 - kappa - 0.13)
+        if n / d * (1.0 - 2.0 / (9.0 * n) - 4.3 * math.sqrt(2.0 / (9.0 * n))) ** 3 >= f2:
+            return nch, kappa, math.cos(0.45 * math.acos(thr))
+    raise AssertionError("not screened")
+
+
+def graph(X, tau):
+    """|cos| of all pairs, clusters, edges, and whether listing the edges is no saving."""
+    T, d = X.shape
+    nch, kappa, tight = plan(d, tau)
+    G = np.abs(oracle.gram(X))
+    cols = np.concatenate([np.arange(64) + 64 * (j * ((d + 63) // 64) // nch) for j in range(nch)])
+    near = np.abs(oracle.gram(X[:, cols[cols < d]])) >= kappa
+    early = np.tril(np.ones((T, T), dtype=bool), -1)          # [t, s]: s before t
+    cand = near & early
+    piv = np.where(cand.any(axis=1), cand.argmax(axis=1), np.arange(T))
+    cl = np.where(G[np.arange(T), piv] >= tight, piv, np.arange(T))
+    open_ = cand & (cl[:, None] != cl[None, :])
+    edge = open_ & (G >= 1.0 - tau * tau)
+    tiles = np.add.reduceat(np.add.reduceat(open_, np.arange(0, T, 128), axis=0, dtype=int), np.arange(0, T, 128), axis=1)
+    return G, cl, edge | edge.T, bool(tiles.max() > 256 or edge.sum() > T // 2 + 64)
+
+
+def walk(cl, edge, prev):
+    """One layer's set (boolean) from clusters and edges alone; prev None: Definition 2.2."""
+    T = len(cl)
+    same = (cl[:, None] == cl[None, :]) | edge
+    np.fill_diagonal(same, False)
+    early = np.tril(np.ones((T, T), dtype=bool), -1)
+    if prev is None:
+        return ~(same & early).any(axis=1)
+    keep = prev & ~(same & early & prev[None, :]).any(axis=1)
+    return keep | (~prev & ~(same & keep[None, :]).any(axis=1))
+
+
+@pytest.mark.parametrize("T,d,L,tau,seed", STRAYS)
+def test_assignment_read_off_the_graph(T, d, L, tau, seed):
+    """All but the tokens that neither a member of their cluster nor an edge covers get the oracle's representative from
+    clusters and edges; those tokens exist (Definition 2.2 compares with all earlier tokens, and Algorithm 1 drops an
+    inherited token that any earlier one hits), and only the whole set decides about them."""
+    prev, alone_total = None, 0
+    for l, x in enumerate(activations("strays", T, d, L, "bf16", seed=seed)):
+        X = wl.as_f64(x)
+        G, cl, edge, dense = graph(X, tau)
+        assert not dense and edge.any(), "layer %d" % l
+        now = walk(cl, edge, prev)
+        idx = np.flatnonzero(now).astype(np.int32)
+        ref = oracle.select_full(X, tau) if prev is None else oracle.cascade_step(X, tau, np.flatnonzero(prev))
+        assert np.array_equal(idx, ref["idx"]), "layer %d" % l
+        reach = ((cl[:, None] == cl[None, :]) | edge) & now[None, :]
+        alone = ~now & ~reach.any(axis=1)
+        alone_total += int(alone.sum())
+        near = oracle.assign_nearest(X, idx)
+        for t in np.flatnonzero(~now & ~alone):
+            assert reach[t, near["assign"][t]], "layer %d token %d" % (l, t)
+        assert (near["corr"][alone] < 1.0 - tau * tau).all()
+        prev = now
+    assert alone_total > 0, "the inputs are to hold tokens without a near representative"
