@@ -1608,12 +1608,14 @@ hipError_t launch_screen_chain(const ChainParams& c, hipStream_t st) {
 
 template <typename In, bool WIDE, int DMA>
 hipError_t launch_cascade_rest(const RestParams& rp, hipStream_t st) {
-    constexpr int lds = FusedGeom<2, DMA>::LDS;
+    // the tiles' LDS, or what an assignment of this many tokens takes where that is more (register-staged tiles, T > 8064)
+    constexpr int tiles = FusedGeom<2, DMA>::LDS, most = tiles > assign_lds(FUSED_MAX_T) ? tiles : assign_lds(FUSED_MAX_T);
+    const int lds = rp.c.assign && assign_lds(rp.f.T) > tiles ? assign_lds(rp.f.T) : tiles;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
         attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cascade_rest<In, WIDE, 2, DMA>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, most);
     });
     if (attr_err != hipSuccess) return attr_err;
     ProfScope ps(ADA_K_CASCADE_FUSED, st);

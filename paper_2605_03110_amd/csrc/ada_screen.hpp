@@ -702,6 +702,9 @@ struct ChainParams {
 };
 
 constexpr int LIST_SCRATCH = 3 * 257 * 4;                     // LDS that writing a layer's lists takes
+// ... and its assignment (screen_assign): two words per token besides
+constexpr int assign_lds(int T) { return LIST_SCRATCH + (T + 63) / 64 * 64 * 8; }
+static_assert(assign_lds(FUSED_MAX_T) <= CHAIN_LDS && FUSED_MAX_T / 64 + 1 <= 257, "LDS of a layer's lists and assignment");
 
 // LDS of the walk: cluster slots, marks (edges only), and the clusters of the layers in flight.
 struct ChainGeom {
@@ -715,7 +718,7 @@ struct ChainGeom {
         layers = (CHAIN_LDS - off_layer) / layer_bytes;
         layers = layers < L ? layers : L;
         bytes = off_layer + layers * layer_bytes;
-        const int lists = Tp * 8 + LIST_SCRATCH;              // (see screen_assign)
+        const int lists = assign_lds(T);
         bytes = bytes < lists ? lists : bytes;
     }
 };
@@ -886,7 +889,7 @@ __device__ inline void chain_edges(bool full, int earlier_only, uint32_t n_edge,
 // of its cluster or joined to it by an edge, so if there is one the largest |cos| is among these; usually there is just one
 // and nothing has to be multiplied.  Layers with a token that has none (chain_alone; only layers with edges can) do not come
 // here: their assignment takes the products with the whole set, on the tiles of k_cascade_rest.  (any workgroup size up to
-// 1024; scratch: LIST_SCRATCH + 8 bytes per token, rounded up to 64 tokens, of LDS)
+// 1024; scratch: assign_lds(T) bytes of LDS)
 __device__ inline void screen_assign(const ChainParams& c, const ScreenUnit& SU, int l, int g, int* scratch) {
     const ScreenParams& p = c.s;
     const int T = p.T, words = (T + 63) >> 6, tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;

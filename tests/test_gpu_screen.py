@@ -197,6 +197,29 @@ def test_assignment_of_tokens_that_no_representative_covers(T, d, L, tau, seed, 
     assert alone > 0
 
 
+@pytest.mark.parametrize("T", [8000, 8065, 12321, 16384])
+def test_assignment_of_long_sequences_in_unaligned_rows(T):
+    """X starts on no 16 bytes (Q, K and V must, X need not): the register-staged tiles' workgroups keep two words per token
+    in LDS while they assign, more than their tiles take from T = 8065 on."""
+    print("[case] screened pipeline, unaligned X: T=%d" % T, flush=True)
+    d, L, tau = 64, 2, 0.1
+    xs_cpu = activations("clusters", T, d, L, "bf16", seed=T)
+    xs = []
+    for x in xs_cpu:
+        flat = torch.zeros(T * d + 8, dtype=x.dtype, device=DEV)
+        xs.append(flat[1:1 + T * d].view(T, d).copy_(x))
+    qkv = [torch.zeros(T, d, dtype=torch.bfloat16, device=DEV)] * L
+    res = pa.ada_pipeline_layers(xs, qkv, qkv, qkv, 1, tau)
+    for l in range(L):
+        r = int(res["counts"][l, 0])
+        idx, assign = res["idx"][l, :r].cpu().numpy(), res["assign"][l].cpu().numpy()
+        assert res["info"][l].cpu().tolist() == [T - r, 0, 0, 0, r, 0, 0, 0]
+        assert np.array_equal(assign[idx], idx) and np.isin(assign, idx).all()
+        Xn, _ = oracle.normalize(wl.as_f64(xs_cpu[l]))
+        chosen = np.abs(np.einsum("ij,ij->i", Xn, Xn[assign]))
+        assert (chosen >= oracle.assign_nearest(wl.as_f64(xs_cpu[l]), idx)["corr"] - 2e-4).all()
+
+
 FULL = [
     # kind, T, d, dtype, tau, greedy, big: long enough for the graph, by one rule each (greedy / fp32 / other bf16 rows / whole pieces)
     ("clusters", 1500, 64, "bf16", 0.1, True, 0), ("clusters", 2049, 1001, "bf16", 0.1, True, 0), ("clusters", 4100, 96, "f32", 0.2, True, 0),
