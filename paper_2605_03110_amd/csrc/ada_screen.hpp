@@ -71,10 +71,17 @@ constexpr double SCREEN_EPS = 0.13;                           // 2 d + d^2 for a
 // (1 - k^2)^((n-1)/2); 3e-10 here), f2 follows from it, and n1 is taken where the share of the norm that n1 of d columns
 // of independent entries hold lies above f2 with 4.3 standard deviations (Wilson-Hilferty).  More than half of the
 // columns, or a threshold no bound reaches: not screened.
+// Small thresholds: two members of a cluster are not multiplied, each is at most 0.45 of the threshold's angle from the
+// pivot, so their cosine lies above the threshold by cos(0.9 acos(thr)) - thr, about 0.19 tau^2.  A rounding of r on each of
+// the two cosines with the pivot comes off that four-fold (angles add: (a + b)^2 / 2 with a = b and a^2 = 2 (1 - cos)).  r:
+// lane sums of d / 64 products (up to 64 in short rows) and their reduction, of the product and, halved twice, of two
+// squared norms.  What is left has to be 1e-4, as at the other decisions: tau >= 0.027 up to d = 4096.
 inline bool screen_plan(int d, float tau, ScreenPlan* out) {
     const double thr = 1.0 - (double)tau * (double)tau, safe = thr - 2e-4;
     const int nk = (d + 63) / 64;
     if (d < 64) return false;
+    const double rounding = 2.0 * ((d > 4096 ? d / 64.0 : 64.0) + 16.0) / (1 << 24);
+    if (cos(0.9 * acos(thr)) - thr < 1e-4 + 4.0 * rounding) return false;
     for (int nch = 1; nch <= nk; ++nch) {
         const int n = 64 * nch, ne = n < d ? n : d;
         double k = sqrt(1.0 - exp(-44.0 / (ne - 1)));

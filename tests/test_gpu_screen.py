@@ -160,6 +160,31 @@ def test_assignment_and_attention_on_the_graph_of_near_pairs(kind, T, d, L, dtyp
             parity.check_attention(*qkv, H, idx, assign, res["out"][l].cpu().numpy(), what="%s layer %d" % (kind, l))
 
 
+@pytest.mark.parametrize("tau,screened", [(0.001, False), (0.02, False), (0.03, True), (0.1, True)])
+def test_smallest_thresholds_are_decided_by_products(tau, screened):
+    """Two members of a cluster are joined by the metric, whose margin on the cosine, 0.19 tau^2, has to lie far above the
+    rounding of the products with their pivot; below that every pair is multiplied."""
+    print("[case] small threshold: tau=%g" % tau, flush=True)
+    T, d, L = 640, 256, 4
+    rng = np.random.default_rng(7)
+    C = rng.standard_normal((T // 4, d))
+    C /= np.linalg.norm(C, axis=1, keepdims=True)
+    # angles to the centre up to the threshold's: within a cluster there are pairs on both sides of it
+    xs_cpu = []
+    for _ in range(L):
+        e = rng.standard_normal((T, d)) / np.sqrt(d)
+        X = C[rng.integers(0, len(C), T)] + e * rng.uniform(0.0, np.sqrt(2.0) * tau, (T, 1))
+        xs_cpu.append(wl.to_dtype(X.astype(np.float32), "f32"))
+    pa.ada_profile_enable(True)
+    try:
+        res = pa.ada_cascade_layers([x.to(DEV) for x in xs_cpu], tau)
+        launches = pa.ada_profile_collect()["screen"]["launches"]
+    finally:
+        pa.ada_profile_enable(False)
+    assert (launches > 0) == screened
+    check(xs_cpu, tau, *(res[k].cpu() for k in ("idx", "counts", "gram_ops", "adds", "removes")), 0, "tau=%g" % tau)
+
+
 # T, d, L, tau, seed (tests/test_screen_replay.py shows on the CPU that the graph lists these layers)
 STRAYS = [(512, 768, 4, 0.1, 1), (300, 256, 3, 0.1, 2), (1000, 1024, 6, 0.1, 3)]
 
