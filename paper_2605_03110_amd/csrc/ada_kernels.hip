@@ -1624,12 +1624,24 @@ hipError_t launch_cascade_rest(const RestParams& rp, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Whether a call over layers is screened: every layer at the one threshold (known here), T within the range of the
-// one-launch step (cluster ids and list positions in 16 bits), and a sketch that is a saving.
-bool screen_eligible(int T, int d, float tau, unsigned flags, ScreenPlan* plan) {
+// Whether a call over L layers of G problems is screened: every layer at the one threshold (known here), T within the range
+// of the one-launch step (cluster ids and list positions in 16 bits), a sketch that is a saving, and more to do than six
+// launches take (23 to 27 us): two layers always are, one layer unless its Gram is a single short round of the chip.
+// Measured, us, one layer, full Gram -> graph:
+//   64 x 64 tiles, one round of them (T <= 1536), bf16: d=128 15 -> 23, 768 16 -> 23, 2304 22 -> 24, 4096 29 -> 23;
+//     four at a time, T=512 d=768: 16 -> 24; fp32: d=128 15 -> 23, 768 28 -> 23; two rounds, 2048 x 770: 30 -> 25
+//   bf16 in whole 64-byte pieces from T = 1536 on: 1536 x 2304 21 -> 24 (5.4e9), 2048 x 768 14 -> 25, 2048 x 4096 32 -> 26
+//     (1.7e10), 3000 x 768 25 -> 25 (6.9e9), 4096 x 128 20 -> 27, 4096 x 768 33 -> 26 (1.3e10)
+//   two layers: T=197 d=768 30 -> 24, T=2048 d=768 28 -> 28
+bool screen_eligible(const void* X, int L, int G, int T, int d, long long ld, int dtype, float tau, unsigned flags, ScreenPlan* plan) {
     if ((flags & (ADA_FLAG_TWO_PASS | ADA_FLAG_RESIDENT_PASS)) || T > FUSED_MAX_T) return false;
     const char* e = dev_switch("ADA_SCREEN");
     if (e && e[0] == '0') return false;
+    if (L == 1) {
+        const long long nb = (T + 63) / 64;
+        const bool pieces = dtype == ADA_BF16 && T >= 1536 && d % DmaGeom::HC == 0 && rows16(dtype, X, ld);
+        if (pieces ? (double)G * T * T * d <= 6.5e9 : G * nb * (nb + 1) / 2 <= 300 && d <= (dtype == ADA_F32 ? 448 : 2400)) return false;
+    }
     return screen_plan(d, tau, plan) && ScreenUnit(T, plan->nch).bytes <= (long long)ws_screen_bytes(T);
 }
 
@@ -1961,7 +1973,7 @@ int ada_cascade_layers_grouped(const ada_groups* groups, const void* const* X_la
     const ada_groups g = {groups->G, groups->x_gstride, (int64_t)L * T, (int64_t)L * 4, (int64_t)L};
     const size_t esz = dtype == ADA_BF16 ? 2 : 4;
     ScreenPlan plan;
-    if (screen_eligible(T, d, tau, flags, &plan))
+    if (screen_eligible(X_layers[0], L, g.G, T, d, ld, dtype, tau, flags, &plan))
         return run_layers_screened(plan, X_layers, L, g.G, (long long)g.x_gstride * (long long)esz, T, d, ld, dtype, tau, idx_all,
                                    counts_all, gram_ops_all, adds_all, removes_all, g.list_gstride, g.counts_gstride,
                                    g.ops_gstride, ws, st, flags);
@@ -1995,7 +2007,7 @@ int ada_cascade_layers(const void* const* X_layers, int L, int T, int d, int64_t
     if (int e = check_common(X_layers[0], T, d, ld, dtype, tau, ws, ws_bytes)) return e;
     hipStream_t st = (hipStream_t)stream;
     ScreenPlan plan;
-    if (screen_eligible(T, d, tau, flags, &plan))
+    if (screen_eligible(X_layers[0], L, 1, T, d, ld, dtype, tau, flags, &plan))
         return run_layers_screened(plan, X_layers, L, 1, 0, T, d, ld, dtype, tau, idx_all, counts_all, gram_ops_all, adds_all,
                                    removes_all, 0, 0, 0, ws, st, flags);
     // layer 0: the full T x T selection; layers >= 1 inherit the previous layer's set on the device (Section 4.1)
@@ -2047,7 +2059,7 @@ int ada_cascade_layers_batched(const void* const* X_layers, int B, int L, int T,
     const unsigned fl = flags & ~ADA_FLAG_RESIDENT_PASS;
     int rc = ADA_OK;
     ScreenPlan plan;
-    const bool screened = screen_eligible(T, d, tau, fl, &plan);
+    const bool screened = screen_eligible(X_layers[0], L, 1, T, d, ld, dtype, tau, fl, &plan);
     for (int b = 0; screened && b < B && rc == ADA_OK; ++b) {
         const size_t row = (size_t)b * L, o = row * (size_t)T;
         rc = run_layers_screened(plan, X_layers + row, L, 1, 0, T, d, ld, dtype, tau, idx_all + o, counts_all + row * 4,
@@ -2124,7 +2136,7 @@ int ada_pipeline_layers(const void* const* X_layers, const void* const* Q_layers
     // heads and 400 representatives has 112 workgroups for 256 CUs; several layers in one launch fill the chip).  The
     // positions go where the second workspace would have its hit table.
     ScreenPlan plan;
-    const bool screened = screen_eligible(T, d, tau, flags, &plan);
+    const bool screened = screen_eligible(X_layers[0], L, 1, T, d, ld, dtype, tau, flags, &plan);
     const size_t fit_pos = ws_area_bytes(T) / ((size_t)T * 4);
     const int batch = fit_pos < (size_t)ATTN_LAYERS ? (int)fit_pos : ATTN_LAYERS;
     int32_t* pos = reinterpret_cast<int32_t*>(carve(ws_attn, T).hits);

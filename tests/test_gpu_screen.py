@@ -185,6 +185,26 @@ def test_smallest_thresholds_are_decided_by_products(tau, screened):
     check(xs_cpu, tau, *(res[k].cpu() for k in ("idx", "counts", "gram_ops", "adds", "removes")), 0, "tau=%g" % tau)
 
 
+@pytest.mark.parametrize("T,d,G,L,dtype,screened", [
+    (197, 768, 1, 1, "bf16", False), (197, 768, 1, 2, "bf16", True), (1536, 770, 1, 1, "bf16", False), (1537, 770, 1, 1, "bf16", True),
+    (512, 2400, 1, 1, "bf16", False), (512, 2464, 1, 1, "bf16", True), (512, 448, 1, 1, "f32", False), (512, 452, 1, 1, "f32", True),
+    (1600, 2528, 1, 1, "bf16", False), (1600, 2560, 1, 1, "bf16", True), (512, 96, 8, 1, "bf16", False), (512, 96, 9, 1, "bf16", True)])
+def test_one_small_layer_takes_the_full_gram(T, d, G, L, dtype, screened):
+    """Both sides of the lines below which a single layer is not screened."""
+    print("[case] few layers: T=%d d=%d G=%d L=%d %s" % (T, d, G, L, dtype), flush=True)
+    per = [activations("clusters", T, d, L, dtype, seed=T + d + g) for g in range(G)]
+    xs = [torch.stack([p[l] for p in per]).to(DEV) for l in range(L)]
+    pa.ada_profile_enable(True)
+    try:
+        res = pa.ada_cascade_layers_grouped(xs, 0.1, want_lists=True) if G > 1 else pa.ada_cascade_layers([x[0] for x in xs], 0.1)
+        launches = pa.ada_profile_collect()["screen"]["launches"]
+    finally:
+        pa.ada_profile_enable(False)
+    assert (launches > 0) == screened
+    for g in (0, G - 1):
+        check(per[g], 0.1, *((res[k][g] if G > 1 else res[k]).cpu() for k in ("idx", "counts", "gram_ops", "adds", "removes")), 0, "group %d" % g)
+
+
 # T, d, L, tau, seed (tests/test_screen_replay.py shows on the CPU that the graph lists these layers)
 STRAYS = [(512, 768, 4, 0.1, 1), (300, 256, 3, 0.1, 2), (1000, 1024, 6, 0.1, 3)]
 
