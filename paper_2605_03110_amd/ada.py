@@ -58,6 +58,9 @@ class AdaError(RuntimeError):
 # workgroup's code), so the build refuses it instead of letting a benchmark find out.
 SCRATCH_BUDGET = {
     "k_cascade_fusedItLb1ELi2ELi1E": 64,       # bf16, aligned rows, two K-groups, direct-to-LDS: the cascade step
+    "k_cascade_passI": 0,                      # all steps in one launch: what is spilled there is paid for at every step
+    "k_cascade_restItLb1ELi2ELi2E": 0,         # layers that the graph of near pairs leaves to the tiles
+    "k_cascade_restIfLb1ELi2ELi2E": 16,
     "k_gram_dmaILb1E": 0,                      # one-launch full selection
     "k_gram_dmaILb0E": 0,                      # full Gram beyond T = 4096
     "k_attn_rep2ILi256E": 64,                  # attention on the representative set, d_h = 256

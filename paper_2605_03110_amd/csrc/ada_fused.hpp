@@ -64,6 +64,7 @@ struct FusedParams {
     // allocation): groups > 1.  Workgroup b serves group b % groups as its worker b / groups of wpg (grid = groups x
     // wpg); the pointers above are group 0's, group g's lie g strides further on.
     int groups, wpg;
+    int steps;               // set by the kernels: this one loops over steps (see step_tid)
     long long x_gs;          // bytes between consecutive groups' X
     long long list_gs;       // int32 elements between groups in prev_idx, idx, adds, removes
     long long counts_gs;     // int32 elements between groups in counts and r_dev
@@ -147,6 +148,15 @@ __host__ __device__ inline int cascade_tile_shape(int r, int T, int d, int pick,
         if (shape == 0 || cost < best_cost) { best = shape; best_cost = cost; }
     }
     return best;
+}
+
+// The thread's number; in a kernel that loops over steps (p.steps, a constant there) computed anew at each use.  What the tiles
+// and the update derive from it does not depend on the step, and the compiler moved all of it out of that loop: 263 registers per
+// lane spilled to memory in k_cascade_rest, 278 in k_cascade_pass (T=2048, d=4096, 27 steps: 867 us, 735 without).
+__device__ inline int step_tid(const FusedParams& p) {
+    int tid = (int)threadIdx.x;
+    if (p.steps) asm volatile("" : "+v"(tid));
+    return tid;
 }
 
 // Last-arriver detection in two levels.  Atomics on one address are served one after the other at the memory side
@@ -311,7 +321,7 @@ __device__ inline void fused_tile(const FusedParams& p, int r, int s0, int t0, i
     float* scale = reinterpret_cast<float*>(lds + G::OFF_SCALE);
     char* body = lds + G::META;
 
-    const int tid = threadIdx.x, t256 = tid & 255;
+    const int tid = step_tid(p), t256 = tid & 255;
     // wave-uniform values are pinned to scalar registers so that code selected by them branches, not predicates
     const int g = __builtin_amdgcn_readfirstlane(tid >> 8);
     const int wave = __builtin_amdgcn_readfirstlane(t256 >> 6);
@@ -595,7 +605,7 @@ __device__ inline void fused_tile_wide(const FusedParams& p, int r, int s0, int 
     float* scale = ssq + 256;                                    // [ROWS]
     char* ring = lds + G::META;
 
-    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int tid = step_tid(p), lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wa = wave / WPB, wp = wave % WPB, b0 = NBW * wp;
     const In* X = reinterpret_cast<const In*>(p.X);
@@ -783,7 +793,7 @@ __device__ inline void fused_tile_ring(const FusedParams& p, int r, int s0, int 
     float* scale = ssq + 512;                                     // [ROWS] 1 / norm (0 for rows that do not exist)
     char* ring = lds + G::META;
 
-    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int tid = step_tid(p), lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wt = wave & 3, wr = wave >> 2;
     const uint16_t* X = reinterpret_cast<const uint16_t*>(p.X);
@@ -1074,7 +1084,7 @@ __device__ inline void fused_tile_split(const FusedParams& p, int r, int s0, int
     float* scale = ssq + 512;                                     // [ROWS] 1 / norm (0 for rows that do not exist)
     char* ring = lds + G::META;
 
-    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int tid = step_tid(p), lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool loader = wave8 >= 4;
     const int wave = wave8 & 3;                                   // place among the waves of its kind
@@ -1265,7 +1275,7 @@ template <int THREADS, typename Inherited>
 __device__ inline void gamma_fix_collect(const FusedParams& p, int r, const uint32_t* vmask, bool ok, Inherited inherited) {
     if (!p.fix_list) return;                             // uniform
     __shared__ int s_fix;
-    const int tid = threadIdx.x;
+    const int tid = step_tid(p);
     if (tid == 0) s_fix = 0;
     __syncthreads();
     auto one = [&](int t, unsigned long long key) {
@@ -1310,7 +1320,7 @@ __device__ inline void gamma_fix_collect(const FusedParams& p, int r, const uint
 template <int THREADS, int NV>
 __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int qp0, char* lds, int* scan_scratch) {
     constexpr int U = 4 * NV;
-    const int tid = threadIdx.x;
+    const int tid = step_tid(p);
     const int T = p.T, T4 = (T + 3) >> 2;               // (up to three records past the end: padding, always zero)
     const int Wa = (r + 31) >> 5;
     uint16_t* pos = reinterpret_cast<uint16_t*>(lds);                        // [T] list position of an inherited token
@@ -1424,7 +1434,7 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
 template <int THREADS>
 __device__ inline int fused_update(const FusedParams& p, int r, bool r_ok, int q0, int qp0, char* lds, int* scan_scratch) {
     constexpr int WU = 11;                              // hit words fetched per batch by one thread (22, 33, ... words: whole batches)
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = step_tid(p), lane = tid & 63;
     const int T = p.T;
     if (r_ok && p.first && T <= 32 * THREADS) {                             // uniform
         const int t4 = (T + 3) >> 2;
@@ -1593,7 +1603,7 @@ __device__ inline int fused_update(const FusedParams& p, int r, bool r_ok, int q
 // info[0] = tokens represented by another token (T - r), info[3] = status.
 template <int THREADS>
 __device__ inline void assign_finish(const FusedParams& p, int r, bool r_ok, int q0, int qp0) {
-    const int tid = threadIdx.x;
+    const int tid = step_tid(p);
     const int T = p.T;
     for (int t = tid; t < T; t += THREADS) {
         const unsigned long long key = p.best[t];
@@ -1687,6 +1697,7 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_fused(FusedParams p) {
     using G = FusedGeom<KG, DMA>;
     __shared__ int s_last;
     ADA_CLK(0);
+    p.steps = 0;
     unsigned local = blockIdx.x, workers = (unsigned)p.grid;
     if (p.groups > 1) {                                      // uniform: this workgroup's problem
         const unsigned g = blockIdx.x % (unsigned)p.groups;
@@ -1772,6 +1783,7 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_pass(PassParams pp) {
     using G = FusedGeom<KG, DMA>;
     __shared__ int s_last, s_word;
     FusedParams p = pp.f;
+    p.steps = 1;
     const int T = p.T;
     // No cache is invalidated between layers.  X is read-only.  A row of the set is written (and written back) before
     // anybody reads it and is never read before that, so plain loads are safe when rows do not share cache lines;

@@ -1145,6 +1145,7 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
     using G = FusedGeom<KG, DMA>;
     __shared__ int s_item, s_word, s_last;
     FusedParams p = rp.f;
+    p.steps = 1;
     const int T = p.T, first = rp.c.s.first, n_layers = rp.c.s.L;
     const int groups = p.groups > 1 ? p.groups : 1, g = (int)blockIdx.x % groups, worker = (int)blockIdx.x / groups;
     const int workers = p.groups > 1 ? p.wpg : p.grid;
