@@ -71,11 +71,11 @@ constexpr size_t ws_fixed_bytes(int T) {                    // everything in fro
     return align_up((size_t)T * 4, 256) * 4 + align_up((size_t)T, 256) + META_BYTES + align_up((size_t)T * 8, 256);
 }
 constexpr size_t ws_hit_bytes(int T) { return T <= FUSED_MAX_T ? align_up((size_t)T * hit_words(T) * 4, 256) : 0; }
-// Where the hit table lies the screened selection keeps its units (sketches, clusters: about 200 bytes per token and layer
-// at d = 4096), as many layers at a time as fit: 8 KB per token is 32 layers and more, 15.5 MB in all bounds it for long T.
+// Where the hit table lies the screened selection keeps its units (sketches, clusters, edges: about 240 bytes per token and layer
+// at d = 4096), as many layers at a time as fit: 8.5 KB per token is 32 layers and more, 17 MB in all bounds it for long T.
 constexpr size_t ws_screen_bytes(int T) {
     return T > FUSED_MAX_T ? 0
-         : (size_t)T * 8192 + 16384 < ((size_t)31 << 19) ? align_up((size_t)T * 8192 + 16384, 256) : ((size_t)31 << 19);
+         : (size_t)T * 8704 + 32768 < ((size_t)34 << 19) ? align_up((size_t)T * 8704 + 32768, 256) : ((size_t)34 << 19);
 }
 constexpr size_t ws_area_bytes(int T) { return ws_hit_bytes(T) > ws_screen_bytes(T) ? ws_hit_bytes(T) : ws_screen_bytes(T); }
 constexpr size_t ws_bytes_for(int T) { return ws_fixed_bytes(T) + ws_area_bytes(T); }
@@ -1466,6 +1466,7 @@ ScreenParams screen_params(const ScreenPlan& plan, const Workspace& w, int T, in
     sp.nk = (d + 63) / 64;
     sp.kap = plan.kappa * SCREEN_SCALE * SCREEN_SCALE;
     sp.kap1 = plan.kappa + (float)SCREEN_EPS;
+    sp.open = (uint32_t)(SCREEN_OPEN * T);
     sp.f2 = plan.f2; sp.safe = plan.safe; sp.thr = threshold_of(tau); sp.cos_tight = plan.cos_tight;
     return sp;
 }
@@ -1483,12 +1484,23 @@ hipError_t launch_screen_exact(const ScreenParams& sp, hipStream_t st) {
     return hipGetLastError();
 }
 
+template <typename In, int LPR>
+hipError_t launch_screen_rest(const ScreenParams& sp, hipStream_t st) {
+    const int nb = (sp.T + 127) / 128, ntile = nb * (nb + 1) / 2, units = sp.G * sp.L;
+    // (a unit with nothing to do takes its workgroups one read each; a busy one should have enough of them)
+    int k = 1024 / units;
+    k = k < 8 ? 8 : k;
+    k = k > ntile ? ntile : k;
+    ProfScope ps(ADA_K_SCREEN, st);
+    hipLaunchKernelGGL((k_screen_rest<In, LPR>), dim3((unsigned)(k * units)), dim3(256), 0, st, sp, ntile);
+    return hipGetLastError();
+}
+
 // The graph of near pairs of every unit of sp.
 template <typename In>
 hipError_t launch_screen(const ScreenParams& sp, hipStream_t st) {
     const int units = sp.G * sp.L;
     const int rb = (sp.T + SKETCH_ROWS - 1) / SKETCH_ROWS;
-    const int nb = (sp.T + 127) / 128, ntile = nb * (nb + 1) / 2;
     {
         ProfScope ps(ADA_K_SCREEN, st);
         hipLaunchKernelGGL((k_screen_sketch<In>), dim3((unsigned)(rb * units)), dim3(256), 0, st, sp, rb);
@@ -1511,13 +1523,8 @@ hipError_t launch_screen(const ScreenParams& sp, hipStream_t st) {
     hipError_t e = np >= 256 ? launch_screen_exact<In, 64>(sp, st) : np >= 128 ? launch_screen_exact<In, 32>(sp, st)
                  : np >= 64 ? launch_screen_exact<In, 16>(sp, st) : launch_screen_exact<In, 8>(sp, st);
     if (e != hipSuccess) return e;
-    // (a unit with nothing to do takes its workgroups one read each; a busy one should have enough of them)
-    int k = 1024 / units;
-    k = k < 8 ? 8 : k;
-    k = k > ntile ? ntile : k;
-    ProfScope ps(ADA_K_SCREEN, st);
-    hipLaunchKernelGGL((k_screen_rest<In>), dim3((unsigned)(k * units)), dim3(256), 0, st, sp, ntile);
-    return hipGetLastError();
+    return np >= 256 ? launch_screen_rest<In, 64>(sp, st) : np >= 128 ? launch_screen_rest<In, 32>(sp, st)
+         : np >= 64 ? launch_screen_rest<In, 16>(sp, st) : launch_screen_rest<In, 8>(sp, st);
 }
 
 // The full selection of one sequence (ada_screen_full.hpp).
@@ -1568,6 +1575,13 @@ int screen_full(const ScreenPlan& plan, const void* X, int T, int d, long long l
     f.want_gamma = gamma != nullptr;
     f.greedy = greedy;
     f.big_tiles = 1024;
+    // A greedy covering goes to the full Gram with its first edge, and a token with unexplained candidates is a head as a rule.
+    sp.open = greedy ? (uint32_t)(T / 16 + 16) : (uint32_t)T;
+    // T=8192, d=4096, the heads' share of the triangle 0.31 / 0.56 / 0.86: 194 / 270 / 360 us, 315 by way of the full Gram; other
+    // rows' full Gram is no faster than the heads' tiles (8191 x 1000: 171 us at 0.86 and 170), and a greedy covering would
+    // have to be resolved as well.
+    const bool dma = dtype == ADA_BF16 && d % DmaGeom::HC == 0 && rows16(dtype, X, ld);
+    f.most_heads = dma && !greedy ? 0.7f : 2.f;
     f.gate = w.meta + META_GATE;
     f.mask = mask; f.idx = idx; f.counts = counts; f.ops = reinterpret_cast<unsigned long long*>(gram_ops);
     static std::once_flag once;
@@ -1586,7 +1600,6 @@ int screen_full(const ScreenPlan& plan, const void* X, int T, int d, long long l
     }
     if (!gamma) return ADA_OK;
     const GramParams p = {X, ld, T, d, nullptr, nullptr, nullptr, w.inv_norm, gamma, sp.thr, MODE_FULL, 1};
-    const bool dma = dtype == ADA_BF16 && d % DmaGeom::HC == 0 && rows16(dtype, X, ld);
     e = dtype == ADA_F32 ? launch_screen_gram<float, false>(sp, p, st) : dma ? launch_screen_gram<uint16_t, true>(sp, p, st)
                                                                              : launch_screen_gram<uint16_t, false>(sp, p, st);
     return e == hipSuccess ? ADA_OK : ADA_ERR_DEVICE;

@@ -33,15 +33,20 @@
 
 constexpr int SCREEN_MAX_LAYERS = 64;                         // layers per launch (their pointers travel as arguments)
 constexpr int SCREEN_TILE_PAIRS = 256;                        // unexplained candidates a 128 x 128 tile may hold before its layer is dense
+// Unexplained candidates per token from which on a layer is dense without looking at them: listing one takes two rows out of the
+// L2 (16 KB at d = 4096, 1.1 ns of the chip), a step on the tiles 27 us at T = 2048, 150 us at T = 8192.  All of them may turn
+// out to be edges, and the walk goes along edges at 2 us per thousand: 28 layers of T=2048, d=4096 with 2.2 unexplained
+// candidates per token take 681 us on the graph and 1265 with one launch per layer.
+constexpr int SCREEN_OPEN = 4;
 constexpr int CHAIN_LDS = 160 * 1024 - 2048;                  // what the walk may use of a CU's LDS
 constexpr float SCREEN_SCALE = 256.f;                         // sketches are stored as 8-bit floats of 256 x (unit vector)
 
 // header of a unit (one layer of one sequence); zeroed by the sketch launch
-enum { SU_EDGES = 3, SU_DENSE = 4, SU_PART = 32, SU_WORDS = SU_PART + 8 * 32 };
-// What every workgroup of the pair and exact passes adds to is kept once per XCD, a cache line each, from word SU_PART on:
-// one address takes an atomic every 25 ns from the whole chip, which was most of these passes where one unit has all the
+enum { SU_EDGES = 3, SU_DENSE = 4, SU_CAND = 32, SU_PART = SU_CAND + 8 * 32, SU_WORDS = SU_PART + 8 * 32 };
+// What every workgroup of the pair and exact passes adds to is kept once per XCD, a cache line each, from words SU_CAND and
+// SU_PART on (lines of their own: the exact pass reads the candidates while it counts the pairs): one address takes an atomic every 25 ns from the whole chip, which was most of these passes where one unit has all the
 // workgroups (T = 8192, d = 4096: pairs 18.6 -> 13.6 us, exact 35.4 -> 20.7 us; T = 2048: 5.6 -> 5.2 and 11.8 -> 9.0).
-enum { SU_CAND = 0, SU_PAIRS = 1, SU_FLAGS = 2 };
+enum { SU_PAIRS = 0, SU_FLAGS = 1 };
 enum { SF_LOW = 1, SF_MESH = 2 };                             // SU_FLAGS: a row below f2; a pivot that has a pivot itself
 
 struct ScreenCounts { uint32_t cand, pairs, flags; };
@@ -49,7 +54,7 @@ __device__ inline ScreenCounts screen_counts(const uint32_t* hdr) {
     ScreenCounts n = {0u, 0u, 0u};
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
-        n.cand += hdr[SU_PART + x * 32 + SU_CAND];
+        n.cand += hdr[SU_CAND + x * 32];
         n.pairs += hdr[SU_PART + x * 32 + SU_PAIRS];
         n.flags |= hdr[SU_PART + x * 32 + SU_FLAGS];
     }
@@ -116,7 +121,7 @@ struct ScreenUnit {
     long long bytes;
     __host__ __device__ ScreenUnit(int T, int nch) {
         const long long t4 = (long long)align_up((size_t)T * 4, 256);
-        edge_cap = T / 2 + 64;
+        edge_cap = SCREEN_OPEN * T + 64;
         long long o = SU_WORDS * 4;
         o_piv = (int)o; o += t4;
         o_size = (int)o; o += t4;
@@ -141,6 +146,7 @@ struct ScreenParams {
     int nch, nk;
     float kap, kap1;           // candidate threshold on the raw accumulator; kappa with the rounding allowance
     float f2, safe, thr, cos_tight;
+    uint32_t open;             // unexplained candidates of a unit above which it is dense (at most SCREEN_OPEN per token)
     float* gamma;              // one unit: largest |cos| of the pairs multiplied out (bits under an integer max), or NULL
     float* inv_norm;           // one unit: inverse norms of the rows, or NULL
     const void* X[SCREEN_MAX_LAYERS];
@@ -426,7 +432,7 @@ __global__ __launch_bounds__(256, NCH == 4 ? 2 : 3) void k_screen_pairs(ScreenPa
     }
     __syncthreads();
     if (threadIdx.x == 0 && s_cand)
-        atomicAdd(reinterpret_cast<uint32_t*>(base) + SU_PART + (blockIdx.x & 7) * 32 + SU_CAND, (uint32_t)s_cand);
+        atomicAdd(reinterpret_cast<uint32_t*>(base) + SU_CAND + (blockIdx.x & 7) * 32, (uint32_t)s_cand);
 }
 
 // Sketch products of a 128 x 128 tile: four waves in a 2 x 2 grid of 64 x 64.
@@ -531,10 +537,25 @@ __device__ inline float screen_cos(float xy, float xx, float yy) {
     return (fabsf(xy) * ix) * iy;                             // a zero row normalises to zero: all its cosines are 0
 }
 
+// (k_screen_rest has to agree: a quarter of the pairs is more than SCREEN_OPEN per token.  The full selection needs the norms
+// in any case.  Nobody writes the counts while they are read here, so scalar loads will do; in short sequences the wait for
+// them is more than the pass they save: 0.8 of 8 us at T=512, d=768 in fp32.)
+__device__ inline bool screen_crowded(const ScreenParams& p, const char* unit) {
+    static_assert(1024 / 8 > SCREEN_OPEN, "crowded units are dense");
+    if (p.T < 1024 || p.inv_norm) return false;
+    const auto* cand = (const __attribute__((address_space(4))) uint32_t*)(unit) + SU_CAND;
+    uint32_t n = 0u;
+#pragma unroll
+    for (int x = 0; x < 8; ++x) n += cand[x * 32];
+    return n > (uint32_t)p.T * (uint32_t)p.T / 8u;
+}
+
 // k_screen_exact: norm of every row, product with its pivot, cluster.  HBM: X once.  Every XCD takes a contiguous range of
 // the rows of all units, so that a unit's pivots (a few hundred rows, a few MB) are read into one L2 and not into eight.
 // What a row needs besides X (pivot, sketch norm, the pivot's own pivot) is requested for all of a lane group's rows at
 // once, and the places that the cluster sizes hand back are summed after the last row: a row waits for X alone.
+// A unit whose candidates are a quarter of all pairs and more is left alone, for k_screen_rest to call dense: its rows share
+// a direction (or a few columns), which the sketch cannot tell from being near.
 template <typename In, int LPR, int PASSES>
 __global__ __launch_bounds__(256) void k_screen_exact(ScreenParams p, int row_blocks, int total) {
     __shared__ uint32_t s_pairs, s_flags;
@@ -550,6 +571,7 @@ __global__ __launch_bounds__(256) void k_screen_exact(ScreenParams p, int row_bl
     int32_t* size = reinterpret_cast<int32_t*>(base + U.o_size);
     float* rho = reinterpret_cast<float*>(base + U.o_rho);
     uint16_t* cl = reinterpret_cast<uint16_t*>(base + U.o_cl);
+    const bool crowded = screen_crowded(p, base);
     if (threadIdx.x == 0) { s_pairs = 0u; s_flags = 0u; }
     __syncthreads();
     const int li = threadIdx.x & (LPR - 1);
@@ -563,6 +585,7 @@ __global__ __launch_bounds__(256) void k_screen_exact(ScreenParams p, int row_bl
         q[k] = piv[t];
         ss[k] = rho[t];
     }
+    if (crowded) return;                                      // uniform
 #pragma unroll
     for (int k = 0; k < PASSES; ++k) { qq[k] = piv[q[k]]; place[k] = 0u; }
 #pragma unroll
@@ -601,11 +624,16 @@ __global__ __launch_bounds__(256) void k_screen_exact(ScreenParams p, int row_bl
     }
 }
 
-// k_screen_rest: the candidates that no cluster explains.  Units without any (the counts agree) are left at once.
-template <typename In>
+// k_screen_rest: the candidates that no cluster explains.  Units without any (the counts agree) are left at once, and so are
+// units with so many that the tiles behind are the better way (p.open).  LPR lanes per product, as
+// in k_screen_exact.  A tile's edges are counted in LDS and take their places in the unit's list with one atomic: one per
+// edge, all to one address at 25 ns each, was most of this launch (T=2048, d=768 in fp32, clusters of five as wide as the
+// threshold: 187 us).
+template <typename In, int LPR>
 __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) {
-    __shared__ int s_n;
+    __shared__ int s_n, s_edges, s_at;
     __shared__ uint32_t s_pair[SCREEN_TILE_PAIRS];
+    __shared__ uint2 s_edge[SCREEN_TILE_PAIRS];
     __shared__ float s_rho[256];
     __shared__ uint16_t s_cl[256];
     const ScreenUnit U(p.T, p.nch);
@@ -616,6 +644,10 @@ __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) 
     uint32_t* hdr = reinterpret_cast<uint32_t*>(base);
     const ScreenCounts n_unit = screen_counts(hdr);
     if (n_unit.flags == 0u && n_unit.cand == n_unit.pairs) return;
+    if (n_unit.cand > n_unit.pairs + p.open) {
+        if ((int)blockIdx.x < units && tid == 0) __hip_atomic_store(hdr + SU_DENSE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
     const bool low = (n_unit.flags & SF_LOW) != 0u;
     const In* X = screen_x<In>(p, layer, group);
     const float* rho = reinterpret_cast<const float*>(base + U.o_rho);
@@ -625,7 +657,7 @@ __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) 
         int sb, tb;
         screen_blocks(tile, &sb, &tb);
         __syncthreads();
-        if (tid == 0) s_n = __hip_atomic_load(hdr + SU_DENSE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? -1 : 0;
+        if (tid == 0) { s_n = __hip_atomic_load(hdr + SU_DENSE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? -1 : 0; s_edges = 0; }
         {
             const int tok = min(tid < 128 ? sb * 128 + tid : tb * 128 + tid - 128, p.T - 1);
             s_rho[tid] = fminf(rho[tok], 1.f);
@@ -639,23 +671,28 @@ __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) 
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
                 const int tl = me.t0 - tb * 128 + b * 32 + l32, t = tb * 128 + tl;
-                const float rt = s_rho[128 + tl];
                 const int ct = s_cl[128 + tl];
+                auto row = [&](int i) { return me.s0 - sb * 128 + (i >> 4) * 32 + 4 * half + screen_row(i); };
+                uint32_t near = 0u;                       // bit 31 - i: register i of the two blocks' 32
+                if (!low) {
 #pragma unroll
-                for (int a = 0; a < 2; ++a)
+                    for (int a = 0; a < 2; ++a) near = screen_bits(near, acc[a][b], p.kap);
+                } else {                                  // some row holds little in its sketch: the pair's own bound
+                    const float rt = s_rho[128 + tl];
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int sl = me.s0 - sb * 128 + a * 32 + (i & 3) + 4 * half + 8 * (i >> 2), s = sb * 128 + sl;
-                        bool near = fabsf(acc[a][b][i]) > p.kap;
-                        if (low) {                        // some row holds little in its sketch: the pair's own bound
-                            const float rs = s_rho[sl];
-                            near |= p.kap1 * sqrtf(rs * rt) + sqrtf((1.f - rs) * (1.f - rt)) + 1e-5f >= p.safe;
-                        }
-                        if (__builtin_amdgcn_ballot_w64(near) != 0ull) {
-                            if (near && s < t && t < p.T && s_cl[sl] != ct) {
-                                const int n = atomicAdd(&s_n, 1);
-                                if (n < SCREEN_TILE_PAIRS) s_pair[n] = (uint32_t)s << 16 | (uint32_t)t;
-                            }
+                    for (int i = 0; i < 32; ++i) {
+                        const float rs = s_rho[row(i)];
+                        if (fabsf(acc[i >> 4][b][i & 15]) > p.kap ||
+                            p.kap1 * sqrtf(rs * rt) + sqrtf((1.f - rs) * (1.f - rt)) + 1e-5f >= p.safe) near |= 0x80000000u >> i;
+                    }
+                }
+                while (__builtin_amdgcn_ballot_w64(near != 0u) != 0ull)
+                    if (near != 0u) {
+                        const int i = __clz((int)near), sl = row(i), s = sb * 128 + sl;
+                        near &= ~(0x80000000u >> i);
+                        if (s < t && t < p.T && s_cl[sl] != ct) {
+                            const int n = atomicAdd(&s_n, 1);
+                            if (n < SCREEN_TILE_PAIRS) s_pair[n] = (uint32_t)s << 16 | (uint32_t)t;
                         }
                     }
             }
@@ -666,19 +703,26 @@ __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) 
             if (tid == 0) __hip_atomic_store(hdr + SU_DENSE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             break;
         }
-        for (int k = tid >> 6; k < n; k += 4) {           // one wave per pair
+        if (n == 0) continue;                             // (uniform)
+        const int li = tid & (LPR - 1);
+        for (int k = tid / LPR; k < n; k += 256 / LPR) {
             const uint32_t e = s_pair[k];
             const int s = (int)(e >> 16), t = (int)(e & 0xFFFFu);
             float xy, xx, yy;
-            screen_products<In, 64>(X + (size_t)t * (size_t)p.ld, X + (size_t)s * (size_t)p.ld, true, p.d, lane, &xy, &xx, &yy);
+            screen_products<In, LPR>(X + (size_t)t * (size_t)p.ld, X + (size_t)s * (size_t)p.ld, true, p.d, li, &xy, &xx, &yy);
             const float c = screen_cos(xy, xx, yy);
-            if (p.gamma && lane == 0 && c > 0.f) atomicMax(reinterpret_cast<uint32_t*>(p.gamma) + t, __float_as_uint(c));
-            if (lane == 0 && c >= p.thr) {
-                const uint32_t at = atomicAdd(hdr + SU_EDGES, 1u);
-                if (at < (uint32_t)U.edge_cap) edge[at] = uint2{e, __float_as_uint(c)};
-                else __hip_atomic_store(hdr + SU_DENSE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+            if (p.gamma && li == 0 && c > 0.f) atomicMax(reinterpret_cast<uint32_t*>(p.gamma) + t, __float_as_uint(c));
+            if (li == 0 && c >= p.thr) s_edge[atomicAdd(&s_edges, 1)] = uint2{e, __float_as_uint(c)};
         }
+        __syncthreads();
+        const int ne = s_edges;
+        if (ne == 0) continue;                            // (uniform)
+        if (tid == 0) s_at = (int)atomicAdd(hdr + SU_EDGES, (uint32_t)ne);
+        __syncthreads();
+        const int at = s_at;
+        for (int k = tid; k < ne; k += 256)
+            if (at + k < U.edge_cap) edge[at + k] = s_edge[k];
+        if (tid == 0 && at + ne > U.edge_cap) __hip_atomic_store(hdr + SU_DENSE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -792,6 +836,15 @@ __device__ inline void screen_lists(const ChainParams& c, const ScreenUnit& SU, 
     __syncthreads();
 }
 
+// f(both ends) for every edge.
+template <int THREADS, typename F>
+__device__ inline void chain_each(uint32_t n_edge, const uint2* edge, F f) {
+    for (uint32_t e = threadIdx.x; e < n_edge; e += THREADS) {
+        const uint32_t v = edge[e].x;
+        f((int)(v >> 16), (int)(v & 0xFFFFu));
+    }
+}
+
 // Whether a layer with edges has a token outside the set that no representative is within the threshold of: neither its
 // cluster nor an edge leads to a member of the set.  (Definition 2.2 compares with all earlier tokens, and step 5 drops an
 // inherited token that any earlier inherited one hits, so on a chain a ~ b ~ c with a not ~ c both b and c leave the set,
@@ -811,12 +864,10 @@ __device__ inline bool chain_alone(uint32_t n_edge, const uint2* edge, uint32_t 
 #pragma unroll
     for (int u = 0; u < U; ++u)
         if ((in[u] >> lane) & 1ull) slot[cid[u]] = stamp;
-    for (uint32_t e = tid; e < n_edge; e += THREADS) {        // (a member's mark is read, only the others' are written)
-        const uint32_t v = edge[e].x;
-        const int s = (int)(v >> 16), t = (int)(v & 0xFFFFu);
+    chain_each<THREADS>(n_edge, edge, [&](int s, int t) {     // (a member's mark is read, only the others' are written)
         if ((mark[s] & 1) && !(mark[t] & 1)) mark[t] = 2;
         if ((mark[t] & 1) && !(mark[s] & 1)) mark[s] = 2;
-    }
+    });
     __syncthreads();
     int alone = 0;
 #pragma unroll
@@ -833,7 +884,7 @@ __device__ inline void chain_edges(bool full, int earlier_only, uint32_t n_edge,
                                    uint32_t* slot, uint8_t* mark, const int (&cid)[U], unsigned long long (&in)[U], int T) {
     const int tid = threadIdx.x, lane = tid & 63;
     if (full) {                                               // Definition 2.2: no earlier token within the threshold
-        for (uint32_t e = tid; e < n_edge; e += THREADS) mark[edge[e].x & 0xFFFFu] = 2;
+        chain_each<THREADS>(n_edge, edge, [&](int, int t) { mark[t] = 2; });
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -852,11 +903,7 @@ __device__ inline void chain_edges(bool full, int earlier_only, uint32_t n_edge,
     }
     __syncthreads();
     // step 5 along edges: an earlier inherited token hits a later one (only bit 1 is read, only bit 2 set here)
-    for (uint32_t e = tid; e < n_edge; e += THREADS) {
-        const uint32_t v = edge[e].x;
-        const int s = (int)(v >> 16), t = (int)(v & 0xFFFFu);
-        if ((mark[s] & 1) && (mark[t] & 1)) mark[t] = 3;
-    }
+    chain_each<THREADS>(n_edge, edge, [&](int s, int t) { if ((mark[s] & 1) && (mark[t] & 1)) mark[t] = 3; });
     __syncthreads();
     uint32_t low[U];                                          // earliest inherited member of the token's cluster (or none)
     unsigned long long keep[U];
@@ -876,12 +923,10 @@ __device__ inline void chain_edges(bool full, int earlier_only, uint32_t n_edge,
     for (int u = 0; u < U; ++u)                               // the cluster's earliest inherited member covers only if valid
         if (low[u] != 0xFFFFFFFFu && mark[low[u]] != 4) low[u] = 0xFFFFFFFFu;
     __syncthreads();
-    for (uint32_t e = tid; e < n_edge; e += THREADS) {        // steps 7-8 along edges
-        const uint32_t v = edge[e].x;
-        const int s = (int)(v >> 16), t = (int)(v & 0xFFFFu);
-        if (mark[s] & 4) { if (!(mark[t] & 4)) mark[t] = 8; }             // (valid tokens keep their mark)
+    chain_each<THREADS>(n_edge, edge, [&](int s, int t) {     // steps 7-8 along edges (valid tokens keep their mark)
+        if (mark[s] & 4) { if (!(mark[t] & 4)) mark[t] = 8; }
         if ((mark[t] & 4) && !earlier_only) { if (!(mark[s] & 4)) mark[s] = 8; }
-    }
+    });
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < U; ++u) {

@@ -26,6 +26,7 @@ constexpr uint32_t SCREEN_FULL_PAIRS = 64;
 struct ScreenFullParams {
     ScreenParams s;            // one unit
     int want_gamma, greedy, big_tiles;   // big_tiles: 64 x 64 tiles of heads from which on they are cut into 128 x 128
+    float most_heads;          // share of the triangle above which the heads' tiles are no saving
     int32_t* gate;             // out: 1 = the graph does not decide, the launches behind run the full Gram
     uint8_t* mask;             // may be NULL
     int32_t* idx;              // may be NULL
@@ -160,11 +161,13 @@ __global__ __launch_bounds__(SCREEN_SORT_THREADS) void k_screen_sort(ScreenFullP
     if (tid <= 512) L.work[SW_PRE + tid] = o.x;               // (thread 512 has none: the total)
     if (tid <= 128) L.work[SW_PRE128 + tid] = o.y;
     if (tid == 256) {
-        const bool big = tiles.x - o.x >= f.big_tiles;
+        const int nb = (T + 63) >> 6;
+        const bool big = tiles.x - o.x >= f.big_tiles, most = (float)(tiles.x - o.x) > f.most_heads * (float)(nb * (nb + 1) / 2);
         L.work[SW_MEMBERS] = mem;
         L.work[SW_HEADS] = heads;
-        L.work[SW_TILES] = big ? o.x : tiles.x;
-        L.work[SW_TILES128] = big ? tiles.y : 0;
+        L.work[SW_TILES] = most ? 0 : big ? o.x : tiles.x;
+        L.work[SW_TILES128] = big && !most ? tiles.y : 0;
+        if (most) *f.gate = 1;
     }
     // a block meets the blocks before it only: clusters that cross from one block into the next go into token order
     // (sixteen lanes per cluster, a member's place is the number of smaller ones)

@@ -24,14 +24,14 @@ DEV = "cuda:0"
 def activations(kind, T, d, L, dtype, seed, big=0):
     """L host matrices.  clusters: the usual recipe; loose: members of a cluster lie at all angles up to and beyond the
     threshold's; common: every pair's cosine is about 0.95 (no bound on a part of the row excludes it); collapsed: all
-    tokens within the threshold of each other; outliers: a few columns hold most of some rows; signs: duplicates, negated
-    duplicates and zero rows; uneven: one cluster of `big` tokens, small ones and single tokens; single: no two tokens near;
-    strays: tight clusters, one token in ten at any angle up to and beyond the threshold's, and three tokens a ~ b ~ c with a
+    tokens within the threshold of each other; halves: two tokens per cluster; outliers: a few columns hold most of some
+    rows; signs: duplicates, negated duplicates and zero rows; uneven: one cluster of `big` tokens, small ones and single
+    tokens; single: no two tokens near; strays: tight clusters, one token in ten at any angle up to and beyond the threshold's, and three tokens a ~ b ~ c with a
     not ~ c: few edges, and tokens outside the set that no representative covers."""
     rng = np.random.default_rng(seed)
     if kind == "clusters":
         return wl.layer_list(wl.small(T=T, d=d, K=max(1, T // 6), L=L, dtype=dtype, seed=seed, p=0.1))
-    K = max(1, T // 6)
+    K = max(1, T // 2) if kind == "halves" else max(1, T // 6)
     C = rng.standard_normal((K, d))
     C /= np.linalg.norm(C, axis=1, keepdims=True)
     out = []
@@ -54,6 +54,8 @@ def activations(kind, T, d, L, dtype, seed, big=0):
                 X[t] = np.cos(0.1 * i) * u + np.sin(0.1 * i) * v
         elif kind == "common":
             X = C[0] + 0.22 * e
+        elif kind == "halves":
+            X = C[a] + 0.004 * e
         elif kind == "collapsed":
             X = C[0] + 0.004 * e
         elif kind == "outliers":
@@ -99,6 +101,10 @@ CASES = [
     ("common", 300, 512, 3, "bf16", 0.1), ("common", 301, 320, 3, "f32", 0.1), ("collapsed", 500, 768, 3, "bf16", 0.1),
     ("outliers", 400, 1024, 3, "bf16", 0.1), ("outliers", 900, 2048, 3, "f32", 0.1),
     ("signs", 333, 256, 3, "bf16", 0.1),
+    ("loose", 1700, 512, 4, "bf16", 0.1),         # a few edges per token, listed
+    # rows that share a direction: given up before their exact products, every step on the tiles of every shape
+    ("common", 513, 320, 4, "bf16", 0.1), ("common", 700, 385, 3, "f32", 0.1), ("common", 1100, 1024, 3, "bf16", 0.1),
+    ("common", 2100, 2048, 3, "bf16", 0.1), ("collapsed", 1300, 768, 4, "bf16", 0.1),
 ]
 
 
@@ -117,6 +123,7 @@ def test_layer_loop_on_the_graph_of_near_pairs(kind, T, d, L, dtype, tau):
 
 
 @pytest.mark.parametrize("kinds,T,d,dtype", [(("clusters", "clusters", "clusters"), 200, 96, "bf16"), (("clusters", "common", "loose"), 260, 320, "bf16"),
+                                             (("common", "common", "clusters", "common", "loose"), 600, 256, "bf16"),
                                              (("outliers", "signs"), 131, 1001, "f32")])
 def test_stacked_sequences_that_need_different_treatment(kinds, T, d, dtype):
     print("[case] screened groups: %s T=%d d=%d %s" % (kinds, T, d, dtype), flush=True)
@@ -275,8 +282,10 @@ FULL = [
     ("loose", 1700, 512, "bf16", 0.1, True, 0), ("signs", 1536, 256, "bf16", 0.1, True, 0), ("collapsed", 1536, 256, "f32", 0.1, True, 0),
     ("clusters", 1536, 1088, "f32", 0.1, False, 0), ("loose", 1600, 1024, "f32", 0.1, False, 0), ("common", 1600, 1024, "f32", 0.1, False, 0),
     ("outliers", 1600, 1024, "f32", 0.1, False, 0), ("signs", 1600, 1024, "f32", 0.1, False, 0),
-    ("clusters", 8200, 130, "bf16", 0.1, False, 0), ("loose", 3003, 1000, "bf16", 0.1, False, 0), ("single", 4999, 1280, "bf16", 0.1, False, 0),
+    ("clusters", 8200, 130, "bf16", 0.1, False, 0), ("loose", 3003, 1000, "bf16", 0.1, False, 0), ("single", 4999, 1280, "bf16", 0.1, False, 0),   # too many heads: the full Gram
     ("outliers", 5000, 1280, "bf16", 0.1, False, 0),
+    ("halves", 5300, 96, "bf16", 0.1, True, 0), ("halves", 5299, 1281, "bf16", 0.1, False, 0), ("halves", 5297, 320, "f32", 0.1, False, 0),
+    ("halves", 5312, 1280, "bf16", 0.1, False, 0),
 ]
 
 

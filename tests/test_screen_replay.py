@@ -44,7 +44,7 @@ def graph(X, tau):
     open_ = cand & (cl[:, None] != cl[None, :])
     edge = open_ & (G >= 1.0 - tau * tau)
     tiles = np.add.reduceat(np.add.reduceat(open_, np.arange(0, T, 128), axis=0, dtype=int), np.arange(0, T, 128), axis=1)
-    return G, cl, edge | edge.T, bool(tiles.max() > 256 or edge.sum() > T // 2 + 64)
+    return G, cl, edge | edge.T, bool(tiles.max() > 256 or open_.sum() > 4 * T)
 
 
 def walk(cl, edge, prev):
