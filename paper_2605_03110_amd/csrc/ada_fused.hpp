@@ -1639,18 +1639,34 @@ __device__ inline void assign_finish(const FusedParams& p, int r, bool r_ok, int
     }
 }
 
-// The tiles of one step, dealt to the workgroups in contiguous ranges per XCD (blockIdx % 8), the representative block
-// fastest, so that one XCD's L2 serves a contiguous range of tested rows.
+// How a step's tiles are cut: shape, log2 of a tile's rows, blocks of representatives, tiles.  cus: workgroups that the
+// shape is chosen for if several problems share the chip.  triangle: every token is inherited; with first-hit records a tile above
+// the diagonal has nothing to say, so the tiles are those on and below it, token block tb meeting (tb + 1) << (st - sr) blocks.
+struct StepDeal { int shape, sr, st; unsigned nbS, tiles; bool triangle; };
 template <typename In, bool WIDE, int KG, int DMA>
-__device__ inline void fused_step_tiles(const FusedParams& p, int r, char* lds, unsigned local, unsigned workers) {
-    int shape = 0;
+__device__ inline StepDeal fused_step_deal(const FusedParams& p, int r, bool triangle, unsigned cus) {
     constexpr int NSHAPES = sizeof(In) == 2 ? 4 : 3;                      // the ring tiles are bf16 only
-    constexpr bool RAGGED = DMA == DMA_RAGGED;
+    StepDeal s;
+    s.shape = 0;
     if constexpr (WIDE && KG == 2 && DMA != DMA_NONE)
-        shape = cascade_tile_shape(r, p.T, p.d, p.tile_pick, p.groups > 1 ? (int)workers : p.tile_pick, NSHAPES);
-    const int sr = shape >= 2 ? 7 : 6, st = shape == 0 ? 6 : shape == 3 ? 8 : 7;   // log2 of the tile's rows
-    const unsigned nbS = (unsigned)(r + (1 << sr) - 1) >> sr;
-    const unsigned ntiles = nbS * ((unsigned)(p.T + (1 << st) - 1) >> st);
+        s.shape = cascade_tile_shape(r, p.T, p.d, p.tile_pick, p.groups > 1 ? (int)cus : p.tile_pick, NSHAPES);
+    s.sr = s.shape >= 2 ? 7 : 6;
+    s.st = s.shape == 0 ? 6 : s.shape == 3 ? 8 : 7;
+    s.nbS = (unsigned)(r + (1 << s.sr) - 1) >> s.sr;
+    const unsigned nbT = (unsigned)(p.T + (1 << s.st) - 1) >> s.st;
+    s.triangle = triangle && p.first;
+    s.tiles = s.triangle ? (nbT * (nbT + 1u) / 2u) << (s.st - s.sr) : s.nbS * nbT;
+    return s;
+}
+
+// The tiles of one step, dealt to the workgroups in contiguous ranges per XCD (blockIdx % 8), the representative block
+// fastest, so that one XCD's L2 serves a contiguous range of tested rows.  triangle, cus: as for fused_step_deal.
+template <typename In, bool WIDE, int KG, int DMA>
+__device__ inline void fused_step_tiles(const FusedParams& p, int r, bool triangle, char* lds, unsigned local, unsigned workers, unsigned cus) {
+    constexpr bool RAGGED = DMA == DMA_RAGGED;
+    const StepDeal deal = fused_step_deal<In, WIDE, KG, DMA>(p, r, triangle, cus);
+    const int shape = deal.shape;
+    const unsigned nbS = deal.nbS, ntiles = deal.tiles;
     // Contiguous tile ranges per XCD (workgroup b of the launch runs on XCD b % 8), so that the tiles an L2 serves at
     // one time share their rows.  One problem: worker b is on XCD b % 8.  Groups: worker `local` of group g is
     // workgroup local * groups + g, so a group's workers live on nx = 8 / gcd(8, groups) XCDs, worker `local` on the
@@ -1666,9 +1682,18 @@ __device__ inline void fused_step_tiles(const FusedParams& p, int r, char* lds, 
     for (unsigned slot = li; slot < per; slot += slots) {
         const unsigned tile = base + slot;
         if (tile >= ntiles) break;
-        const int tb = (int)(tile / nbS), sb = (int)(tile - (unsigned)tb * nbS);
-        // (every token inherited, and the update reads first-hit records only: a tile above the diagonal has nothing to say)
-        if (p.list_mode == LIST_IDENTITY && p.first && (sb << sr) >= (tb + 1) << st) continue;
+        int tb, sb;
+        if (deal.triangle) {                                              // (uniform)
+            const int up = deal.st - deal.sr, n = (int)(tile >> up);
+            tb = (int)((sqrtf(8.f * (float)n + 1.f) - 1.f) * 0.5f);
+            while ((tb + 1) * (tb + 2) / 2 <= n) ++tb;
+            while (tb * (tb + 1) / 2 > n) --tb;
+            sb = (int)tile - ((tb * (tb + 1) / 2) << up);
+            if (sb >= (int)nbS) continue;                                 // (the last token block is not whole)
+        } else {
+            tb = (int)(tile / nbS);
+            sb = (int)(tile - (unsigned)tb * nbS);
+        }
         if constexpr (WIDE && KG == 2 && DMA != DMA_NONE) {
             if constexpr (sizeof(In) == 2) {
                 // (measured both ways: loader waves gain 10% at 128 x 128; at 128 x 256 the eight multiplying waves of
@@ -1718,7 +1743,10 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_fused(FusedParams p) {
     if (p.thr_in) p.thr = *p.thr_in;                         // adaptive threshold: travels with the set size
     const int r = p.r_dev ? *p.r_dev : p.r_host;
     const bool r_ok = r >= 1 && r <= p.r_host && r <= p.T;
-    if (r_ok) fused_step_tiles<In, WIDE, KG, DMA>(p, r, lds, local, workers);
+    // (no identity lists here; left to find out by itself the compiler's code for the direct-to-LDS tiles takes 0.6 us less at
+    // T=3001, d=1000, and that for the register-staged ones 2.5 us more at d=1001, where the registers run out)
+    const bool triangle = DMA != DMA_NONE && p.list_mode == LIST_IDENTITY;
+    if (r_ok) fused_step_tiles<In, WIDE, KG, DMA>(p, r, triangle, lds, local, workers, workers);
     // The workgroup that takes the last ticket finishes the step.  Hit words and row maxima leave the CU as
     // device-scope atomics (written through the L2), so once every thread's stores are acknowledged (vmcnt(0)) and
     // the workgroup has met at the barrier, the ticket can be taken: nothing is left in the L2 to write back.
@@ -1818,7 +1846,7 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_pass(PassParams pp) {
         p.counts = pp.counts_row0 + (size_t)(i + 1) * 4;
         p.gram_ops = pp.gram_ops_row0 + (i + 1);
         const bool r_ok = r >= 1 && r <= T;
-        if (r_ok) fused_step_tiles<In, WIDE, KG, DMA>(p, r, lds, blockIdx.x, (unsigned)p.grid);
+        if (r_ok) fused_step_tiles<In, WIDE, KG, DMA>(p, r, false, lds, blockIdx.x, (unsigned)p.grid, (unsigned)p.grid);
         PASS_CLK(2);
         const int jq = min((int)threadIdx.x, T - 1);         // the row has T entries whatever r is
         const int q0 = list_at(p, jq), qp0 = list_at(p, max(jq - 1, 0));

@@ -43,9 +43,12 @@ enum { MODE_FULL = 0, MODE_REP = 1, MODE_CROSS = 2 };
 // meta: a few words of scalars, then (from word META_TICKET + 64 on, one per 128-byte line) the per-XCD ticket counters
 constexpr size_t META_BYTES = 2048;
 enum { META_R = 0, META_NONREP = 1, META_STATUS = 2, META_GATE = 3 /* k_screen_sort */, META_TICKET = 4, META_QUEUE = 5 /* and 6 */, META_EPOCH = 7,
-       // screened selection: layers done so far; work queue, hand-over word and sign-off counter of k_cascade_rest (zero between calls)
-       META_PROGRESS = 8, META_REST_QUEUE = 9, META_REST_EPOCH = 10, META_REST_LEFT = 11,
-       META_ALONE = 12 /* and 13: layers of a launch whose assignment the graph leaves open, one bit each */, META_WORDS = 14 };
+       // screened selection: layers done so far; hand-over word, sign-off counter and claim words (one per XCD, in the lines of the
+       // ticket counters) of k_cascade_rest, zero between calls
+       META_PROGRESS = 8, META_REST_EPOCH = 10, META_REST_LEFT = 11,
+       META_ALONE = 12 /* and 13: layers of a launch whose assignment the graph leaves open, one bit each */, META_WORDS = 14,
+       META_REST_CLAIM = META_TICKET + 64 + 8 /* and 32, 64 .. 224 further on */ };
+static_assert((META_REST_CLAIM + 7 * 32 + 1) * 4 <= META_BYTES, "claim words");
 
 // The one-launch cascade step keeps one hit word per token and per 32 inherited representatives; beyond this T
 // the table would dominate the workspace and the two-launch path is used instead.
@@ -1691,6 +1694,8 @@ int run_layers_screened(const ScreenPlan& plan, const void* const* X_layers, int
     }
     rp.f.best = w.best;
     rp.spin_limit = 1 << 24;
+    // rows of idx that share a 128-byte line with their neighbour could be cached half-written
+    rp.list_mode = ((uintptr_t)idx % 128 != 0 || T % 32 != 0 || list_gs % 32 != 0) ? LIST_COHERENT : LIST_PLAIN;
     const char* no_dma = dev_switch("ADA_NO_DMA");
     bool dma = !(no_dma && no_dma[0] == '1') && d % (dtype == ADA_BF16 ? 8 : 4) == 0;
     for (int l = layer0; l < layer0 + L; ++l) dma = dma && rows16(dtype, X_layers[l], ld, G > 1 ? x_gs : 0);

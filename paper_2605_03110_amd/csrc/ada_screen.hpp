@@ -1174,21 +1174,27 @@ __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
 // ------------------------------------------------------------------------------------------------
 // k_cascade_rest: the lists of all layers, one workgroup per layer -- or, when the chain stopped at a dense layer (and wrote
 // the lists before it), that layer and all after it on the tiles of k_cascade_fused.  Before those the assignments that the
-// graph leaves open (META_ALONE; the chain wrote these layers' lists), on the same tiles.  Work items (step, worker) are handed
-// out in order by a counter, and an item waits for the previous step before it starts: every item of an earlier step
-// is by then with a workgroup that runs, so the wait ends however few workgroups are resident, and nothing is assumed
-// about that.  Layer 0 is a step that inherits every token: Algorithm 1's step 5 on the identity list is Definition 2.2.
+// graph leaves open (META_ALONE; the chain wrote these layers' lists), on the same tiles.  Layer 0 is a step that inherits
+// every token: Algorithm 1's step 5 on the identity list is Definition 2.2.
+// A step is dealt as items, one per workgroup that its tiles can use.  A workgroup takes an item from the claim word of its
+// XCD (step << 16 | items taken), from another XCD's when that is used up, and only then waits for the next step: whoever
+// runs finishes the step, so the waits end however few workgroups are resident, and nothing is assumed about that.  The
+// workgroup that finishes a step moves the claim words on, then the hand-over word (step << 15 | size of the set): a claim
+// carries the step that it is good for, also if its workgroup came for the step before.  (One word for all claims and one
+// for all sign-offs, every step cut for all workgroups, took 42 us per layer at T=2048, d=4096 and 36 us at T=512, d=768
+// in fp32.)
 struct RestParams {
     ChainParams c;             // layers c.s.first .. + c.s.L - 1, outputs
     FusedParams f;             // shape, threshold, workspace of sequence 0; the per-layer pointers are set in the kernel
     int spin_limit;
+    int list_mode;             // how the sets are read back: LIST_PLAIN or LIST_COHERENT
 };
 
 template <typename In, bool WIDE, int KG, int DMA>
 __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
     extern __shared__ __align__(16) char lds[];
     using G = FusedGeom<KG, DMA>;
-    __shared__ int s_item, s_word, s_last;
+    __shared__ int s_step, s_item, s_items, s_word, s_last;
     FusedParams p = rp.f;
     p.steps = 1;
     const int T = p.T, first = rp.c.s.first, n_layers = rp.c.s.L;
@@ -1223,43 +1229,79 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
         for (int k = 0; k < step; ++k) m &= m - 1ull;
         return first + __ffsll((long long)m) - 1;
     };
+    // worker w of a problem is on XCD (w groups + g) % 8, one of nx: the ones with equal w % nx share a claim word
+    const int low = groups & -groups, nx = 8 / (low < 8 ? low : 8);
+    int32_t* claim = meta + META_REST_CLAIM;
+    auto items_of = [&](int r, bool triangle) {               // workgroups that a step on a set of r can use
+        if (groups > 1) return workers;
+        const int n = ((int)fused_step_deal<In, WIDE, KG, DMA>(p, r, triangle, (unsigned)workers).tiles + 7) / 8 * 8;
+        return min(max(n, 8), workers);                       // (a step that is refused still has to be finished)
+    };
+    auto share = [&](int n, int x) { return n > x ? (n - x + nx - 1) / nx : 0; };   // of n items those with index % nx == x
     for (;;) {
         __syncthreads();
         if (threadIdx.x == 0) {
-            const int item = atomicAdd(meta + META_REST_QUEUE, 1), step = item / workers;
-            int word = -1;                                    // size of the set that the step works with
-            if (step < steps) {
-                int before = step == 0 ? 0 : -1;              // size of the set that the step before left
-                for (int n = 0; step > 0 && n < rp.spin_limit; ++n) {
-                    const int v = __hip_atomic_load(meta + META_REST_EPOCH, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if ((v >> 15) == step) { before = v & 0x7FFF; break; }
+            const int home = worker % nx;
+            int step, part = home, item = -1, items = 0, word = -1;
+            // polls a word until its upper bits have come to `least`; -1: given up (not reached: see above)
+            auto wait_for = [&](const int32_t* w, int shift, int least) {
+                for (int n = 0; n < rp.spin_limit; ++n) {
+                    const int v = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if ((v >> shift) >= least) return v;
                     __builtin_amdgcn_s_sleep(2);
                 }
-                const int i = layer_of(step);
-                if (before < 0) cnt0[(size_t)i * 4 + 3] = ADA_ERR_DEVICE;   // (not reached: see above)
-                else if (step < n_alone) word = cnt0[(size_t)i * 4];        // sets of the launch before
-                else if (step == n_alone) word = i == 0 ? T : cnt0[(size_t)(i - 1) * 4];
-                else word = before;
+                return -1;
+            };
+            for (;;) {
+                const int from = part, v = atomicAdd(claim + 32 * from, 1);
+                step = v >> 16;
+                if (step >= steps) break;
+                const int epoch = wait_for(meta + META_REST_EPOCH, 15, step);
+                bool gone = epoch < 0;
+                part = home;
+                if (!gone) {
+                    if ((epoch >> 15) > step) continue;       // (this claim came too late for its step)
+                    // the set that the step works with: of an earlier launch, of the layer before, of the step before
+                    const int i = layer_of(step);
+                    word = step < n_alone ? cnt0[(size_t)i * 4] : step > n_alone ? epoch & 0x7FFF : i == 0 ? T : cnt0[(size_t)(i - 1) * 4];
+                    items = items_of(word, step == n_alone && i == 0);
+                    if ((v & 0xFFFF) < share(items, from)) { item = (v & 0xFFFF) * nx + from; break; }
+                    int u[8], other = -1;                     // what is left of the step elsewhere
+#pragma unroll
+                    for (int x = 0; x < 8; ++x)
+                        u[x] = __hip_atomic_load(claim + 32 * (x < nx ? x : home), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                    for (int x = 0; x < 8; ++x)
+                        if (x < nx && (u[x] >> 16) == step && (u[x] & 0xFFFF) < share(items, x)) other = x;
+                    if (other >= 0) part = other;
+                    else gone = wait_for(claim + 32 * home, 16, step + 1) < 0;
+                }
+                if (gone) {
+                    cnt0[(size_t)layer_of(step) * 4 + 3] = ADA_ERR_DEVICE;
+                    step = steps;
+                    break;
+                }
             }
+            s_step = step;
             s_item = item;
+            s_items = items;
             s_word = word;
         }
         __syncthreads();
-        const int item = s_item, r = s_word;
-        const int step = item / workers, local = item - step * workers;
-        if (step >= steps || r < 0) break;                    // uniform
+        const int step = s_step, local = s_item, items = s_items, r = s_word;
+        if (step >= steps) break;                             // uniform
         const int i = layer_of(step);
         const size_t row = (size_t)i * (size_t)T;
         p.X = reinterpret_cast<const char*>(rp.c.s.X[i - first]) + (long long)g * p.x_gs;
         p.assign_mode = step < n_alone || (per_layer == 2 && ((step - n_alone) & 1));
         if (p.assign_mode) {
-            p.list_mode = LIST_COHERENT;
+            p.list_mode = rp.list_mode;
             p.prev_idx = idx0 + row;
             p.assign = rp.c.assign + row;
             p.pos_out = rp.c.pos + row;
             p.counts = rp.c.info + (size_t)i * 8;
         } else {
-            p.list_mode = i == 0 ? LIST_IDENTITY : LIST_COHERENT;
+            p.list_mode = i == 0 ? LIST_IDENTITY : rp.list_mode;
             p.prev_idx = idx0 + row - (i == 0 ? 0 : T);
             p.idx = idx0 + row;
             p.adds = i > 0 && adds0 ? adds0 + row : nullptr;
@@ -1268,12 +1310,15 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
             p.gram_ops = ops0 + i;
         }
         const bool r_ok = r >= 1 && r <= T;
-        if (r_ok) fused_step_tiles<In, WIDE, KG, DMA>(p, r, lds, (unsigned)local, (unsigned)workers);
+        if (r_ok) fused_step_tiles<In, WIDE, KG, DMA>(p, r, p.list_mode == LIST_IDENTITY, lds, (unsigned)local, (unsigned)items, (unsigned)workers);
         const int jq = min((int)threadIdx.x, T - 1);
         const int q0 = list_at(p, jq), qp0 = list_at(p, max(jq - 1, 0));
         drain_stores();
         __syncthreads();
-        if (threadIdx.x == 0) s_last = atomicAdd(p.ticket, 1) == workers - 1 ? 1 : 0;
+        if (threadIdx.x == 0) {
+            const int x = local % nx, parts = items < nx ? items : nx;
+            s_last = atomicAdd(p.ticket + TICKET_XCD0 + 32 * x, 1) == share(items, x) - 1 && atomicAdd(p.ticket, 1) == parts - 1 ? 1 : 0;
+        }
         __syncthreads();
         if (s_last) {                                         // uniform
             if (threadIdx.x == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
@@ -1283,6 +1328,8 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
             else r_new = fused_update<G::THREADS>(p, r, r_ok, q0, qp0, lds + G::META, reinterpret_cast<int*>(lds + G::OFF_SCAN));
             __syncthreads();
             if (threadIdx.x == 0) {
+                for (int x = 0; x < nx; ++x)
+                    __hip_atomic_store(claim + 32 * x, (step + 1) << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
                 __hip_atomic_store(meta + META_REST_EPOCH, ((step + 1) << 15) | (r_new & 0x7FFF), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
@@ -1291,7 +1338,7 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
     }
     // the last workgroup of the sequence to leave puts the counters back to zero
     if (threadIdx.x == 0 && atomicAdd(meta + META_REST_LEFT, 1) == workers - 1) {
-        __hip_atomic_store(meta + META_REST_QUEUE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int x = 0; x < nx; ++x) __hip_atomic_store(claim + 32 * x, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(meta + META_REST_EPOCH, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(meta + META_REST_LEFT, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(meta + META_PROGRESS, first + n_layers, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -26,8 +26,9 @@ def activations(kind, T, d, L, dtype, seed, big=0):
     threshold's; common: every pair's cosine is about 0.95 (no bound on a part of the row excludes it); collapsed: all
     tokens within the threshold of each other; halves: two tokens per cluster; outliers: a few columns hold most of some
     rows; signs: duplicates, negated duplicates and zero rows; uneven: one cluster of `big` tokens, small ones and single
-    tokens; single: no two tokens near; strays: tight clusters, one token in ten at any angle up to and beyond the threshold's, and three tokens a ~ b ~ c with a
-    not ~ c: few edges, and tokens outside the set that no representative covers."""
+    tokens; single: no two tokens near; strays: tight clusters, one token in ten at any angle up to and beyond the
+    threshold's, and three tokens a ~ b ~ c with a not ~ c: few edges, and tokens outside the set that no representative
+    covers."""
     rng = np.random.default_rng(seed)
     if kind == "clusters":
         return wl.layer_list(wl.small(T=T, d=d, K=max(1, T // 6), L=L, dtype=dtype, seed=seed, p=0.1))

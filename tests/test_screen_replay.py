@@ -82,3 +82,80 @@ def test_assignment_read_off_the_graph(T, d, L, tau, seed):
         assert (near["corr"][alone] < 1.0 - tau * tau).all()
         prev = now
     assert alone_total > 0, "the inputs are to hold tokens without a near representative"
+
+
+def claims(rng, groups, workers, steps, at_once):
+    """The workgroups of k_cascade_rest that serve one problem, one memory access at a time in random order, at_once of them
+    running together: every item is done once and in its step, and all of them leave."""
+    low = groups & -groups
+    nx = 8 // min(low, 8)
+    share = lambda n, x: (n - x + nx - 1) // nx if n > x else 0
+    claim, signed, mem, done = [0] * nx, [0] * nx, dict(parts=0, epoch=0), [[] for _ in steps]
+
+    def workgroup(worker):
+        home = worker % nx
+        while True:
+            part = home
+            while True:
+                source = part
+                v, claim[source] = claim[source], claim[source] + 1
+                yield
+                step = v >> 16
+                if step >= len(steps):
+                    return
+                while mem["epoch"] < step:
+                    yield
+                epoch = mem["epoch"]
+                yield
+                part = home
+                if epoch > step:
+                    continue
+                if (v & 0xFFFF) < share(steps[step], source):
+                    item = (v & 0xFFFF) * nx + source
+                    break
+                seen = []
+                for x in range(nx):
+                    seen.append(claim[x])
+                    yield
+                left = [x for x in range(nx) if seen[x] >> 16 == step and (seen[x] & 0xFFFF) < share(steps[step], x)]
+                if left:
+                    part = left[-1]
+                    continue
+                while claim[home] >> 16 < step + 1:
+                    yield
+            assert mem["epoch"] == step
+            done[step].append(item)
+            yield
+            x = item % nx
+            signed[x] += 1
+            if signed[x] < share(steps[step], x):
+                continue
+            yield
+            mem["parts"] += 1
+            if mem["parts"] < min(steps[step], nx):
+                continue
+            signed[:], mem["parts"] = [0] * nx, 0
+            for y in range(nx):
+                claim[y] = (step + 1) << 16
+                yield
+            mem["epoch"] = step + 1
+            yield
+
+    waiting, running = [workgroup(w) for w in rng.permutation(workers)], []
+    for _ in range(2_000_000):
+        while waiting and len(running) < at_once:
+            running.append(waiting.pop())
+        if not running:
+            break
+        i = int(rng.integers(len(running)))
+        if next(running[i], "left") == "left":
+            running.pop(i)
+    assert not running and [sorted(d) for d in done] == [list(range(n)) for n in steps]
+
+
+@pytest.mark.parametrize("groups,workers,at_once", [(1, 32, 32), (1, 32, 3), (1, 16, 1), (2, 5, 5), (3, 8, 2), (4, 2, 1), (12, 21, 4), (16, 1, 1)])
+def test_steps_behind_a_dense_layer_end_however_few_workgroups_run(groups, workers, at_once):
+    rng = np.random.default_rng(groups * 100 + workers)
+    for _ in range(10):
+        n = int(rng.integers(1, 5))
+        claims(rng, groups, workers, [workers if groups > 1 else int(rng.integers(1, workers // 8 + 1)) * 8 for _ in range(n)], at_once)
