@@ -22,6 +22,7 @@
 #include <limits.h>
 #include <math.h>
 #include <stdlib.h>
+#include <algorithm>
 #include <functional>
 #include <mutex>
 #include <queue>
@@ -74,11 +75,12 @@ constexpr size_t ws_fixed_bytes(int T) {                    // everything in fro
     return align_up((size_t)T * 4, 256) * 4 + align_up((size_t)T, 256) + META_BYTES + align_up((size_t)T * 8, 256);
 }
 constexpr size_t ws_hit_bytes(int T) { return T <= FUSED_MAX_T ? align_up((size_t)T * hit_words(T) * 4, 256) : 0; }
-// Where the hit table lies the screened selection keeps its units (sketches, clusters, edges: about 240 bytes per token and layer
-// at d = 4096), as many layers at a time as fit: 8.5 KB per token is 32 layers and more, 17 MB in all bounds it for long T.
+// Where the hit table lies the screened selection keeps its units (sketches, clusters: about 210 bytes per token and layer
+// at d = 4096), as many layers at a time as fit, and edges in what is left: 8 KB per token is 32 layers and more, 15.5 MB in all
+// bounds it for long T.
 constexpr size_t ws_screen_bytes(int T) {
     return T > FUSED_MAX_T ? 0
-         : (size_t)T * 8704 + 32768 < ((size_t)34 << 19) ? align_up((size_t)T * 8704 + 32768, 256) : ((size_t)34 << 19);
+         : (size_t)T * 8192 + 65536 < ((size_t)31 << 19) ? align_up((size_t)T * 8192 + 65536, 256) : ((size_t)31 << 19);
 }
 constexpr size_t ws_area_bytes(int T) { return ws_hit_bytes(T) > ws_screen_bytes(T) ? ws_hit_bytes(T) : ws_screen_bytes(T); }
 constexpr size_t ws_bytes_for(int T) { return ws_fixed_bytes(T) + ws_area_bytes(T); }
@@ -1469,9 +1471,16 @@ ScreenParams screen_params(const ScreenPlan& plan, const Workspace& w, int T, in
     sp.nk = (d + 63) / 64;
     sp.kap = plan.kappa * SCREEN_SCALE * SCREEN_SCALE;
     sp.kap1 = plan.kappa + (float)SCREEN_EPS;
-    sp.open = (uint32_t)(SCREEN_OPEN * T);
     sp.f2 = plan.f2; sp.safe = plan.safe; sp.thr = threshold_of(tau); sp.cos_tight = plan.cos_tight;
     return sp;
+}
+
+// What a launch of `layers` layers leaves of the area goes to the edge lists, up to all unexplained candidates of a listed unit.
+void screen_room(ScreenParams& sp, const ScreenUnit& U, int layers) {
+    const long long room = ((long long)ws_screen_bytes(sp.T) / layers - U.bytes) / 256 * 256;
+    const long long edges = U.edge_cap + room / 8, most = (long long)SCREEN_OPEN * sp.T + 64;
+    sp.edge_cap = (int)(edges < most ? edges : most) / 2 * 2;
+    sp.open = (uint32_t)std::min(SCREEN_OPEN * sp.T, sp.edge_cap);
 }
 
 template <typename In, int LPR>
@@ -1563,7 +1572,7 @@ bool screen_full_eligible(const void* X, int T, int d, long long ld, int dtype, 
     const bool pieces = dtype == ADA_BF16 && d % DmaGeom::HC == 0 && rows16(dtype, X, ld);
     const double least = dtype == ADA_F32 ? 2.5e9 : !pieces ? 8e9 : T > 4096 ? 3e10 : 5.5e10;
     if (!greedy && (double)T * T * d < least) return false;
-    return screen_plan(d, tau, plan) && ScreenUnit(T, plan->nch).bytes <= (long long)ws_screen_bytes(T);
+    return screen_plan(d, tau, plan) && ScreenUnit(T, plan->nch, screen_edges(T)).bytes <= (long long)ws_screen_bytes(T);
 }
 
 int screen_full(const ScreenPlan& plan, const void* X, int T, int d, long long ld, int dtype, float tau, uint8_t* mask,
@@ -1579,7 +1588,8 @@ int screen_full(const ScreenPlan& plan, const void* X, int T, int d, long long l
     f.greedy = greedy;
     f.big_tiles = 1024;
     // A greedy covering goes to the full Gram with its first edge, and a token with unexplained candidates is a head as a rule.
-    sp.open = greedy ? (uint32_t)(T / 16 + 16) : (uint32_t)T;
+    screen_room(sp, ScreenUnit(T, plan.nch, screen_edges(T)), 1);
+    sp.open = std::min(sp.open, (uint32_t)(greedy ? T / 16 + 16 : T));
     // T=8192, d=4096, the heads' share of the triangle 0.31 / 0.56 / 0.86: 194 / 270 / 360 us, 315 by way of the full Gram; other
     // rows' full Gram is no faster than the heads' tiles (8191 x 1000: 171 us at 0.86 and 170), and a greedy covering would
     // have to be resolved as well.
@@ -1658,7 +1668,7 @@ bool screen_eligible(const void* X, int L, int G, int T, int d, long long ld, in
         const bool pieces = dtype == ADA_BF16 && T >= 1536 && d % DmaGeom::HC == 0 && rows16(dtype, X, ld);
         if (pieces ? (double)G * T * T * d <= 6.5e9 : G * nb * (nb + 1) / 2 <= 300 && d <= (dtype == ADA_F32 ? 448 : 2400)) return false;
     }
-    return screen_plan(d, tau, plan) && ScreenUnit(T, plan->nch).bytes <= (long long)ws_screen_bytes(T);
+    return screen_plan(d, tau, plan) && ScreenUnit(T, plan->nch, screen_edges(T)).bytes <= (long long)ws_screen_bytes(T);
 }
 
 // Arguments checked by the caller; x_gs in bytes; list_gs, counts_gs, ops_gs in elements (rows of one sequence are T, 4
@@ -1671,7 +1681,7 @@ int run_layers_screened(const ScreenPlan& plan, const void* const* X_layers, int
                         void* ws, hipStream_t st, unsigned flags, int32_t* assign = nullptr, int32_t* pos = nullptr,
                         int32_t* info = nullptr, int layer0 = 0) {
     const Workspace w = carve(ws, T);
-    const ScreenUnit U(T, plan.nch);
+    const ScreenUnit U(T, plan.nch, screen_edges(T));
     ChainParams c;
     c.assign = assign; c.pos = pos; c.info = info; c.f32 = dtype == ADA_F32;
     ScreenParams& sp = c.s;
@@ -1703,6 +1713,7 @@ int run_layers_screened(const ScreenPlan& plan, const void* const* X_layers, int
     long long fit = (long long)ws_screen_bytes(T) / U.bytes;   // layers at a time, in launches of equal size
     if (fit > SCREEN_MAX_LAYERS) fit = SCREEN_MAX_LAYERS;
     const int batches = (int)((L + fit - 1) / fit), per = (L + batches - 1) / batches;
+    screen_room(sp, U, per);
     const int end = layer0 + L;
     for (int first = layer0; first < end; first += per) {
         sp.first = first;

@@ -35,9 +35,11 @@ constexpr int SCREEN_MAX_LAYERS = 64;                         // layers per laun
 constexpr int SCREEN_TILE_PAIRS = 256;                        // unexplained candidates a 128 x 128 tile may hold before its layer is dense
 // Unexplained candidates per token from which on a layer is dense without looking at them: listing one takes two rows out of the
 // L2 (16 KB at d = 4096, 1.1 ns of the chip), a step on the tiles 27 us at T = 2048, 150 us at T = 8192.  All of them may turn
-// out to be edges, and the walk goes along edges at 2 us per thousand: 28 layers of T=2048, d=4096 with 2.2 unexplained
-// candidates per token take 681 us on the graph and 1265 with one launch per layer.
+// out to be edges, and the walk goes along edges at about 1 us per thousand: 28 layers of T=2048, d=4096 with 2.2 unexplained
+// candidates per token take 681 us on the graph and 1265 with one launch per layer.  A launch of many layers has room for
+// fewer edges, and then that is the line; screen_edges what it always has.
 constexpr int SCREEN_OPEN = 4;
+constexpr int screen_edges(int T) { return (T / 2 + 65) / 2 * 2; }
 constexpr int CHAIN_LDS = 160 * 1024 - 2048;                  // what the walk may use of a CU's LDS
 constexpr float SCREEN_SCALE = 256.f;                         // sketches are stored as 8-bit floats of 256 x (unit vector)
 
@@ -116,12 +118,13 @@ inline bool screen_plan(int d, float tau, ScreenPlan* out) {
 // a wave loads them as matrix operands: blocks of 32 rows, in a block column group after column group, a group as two
 // runs of 64 lanes x 16 bytes (lane l: row l % 32, columns 32 (l / 32) + 16 run .. + 15), so that every operand load is one
 // kilobyte without gaps.
+// edge_cap: places for edges, as many as the launch has room for (even).
 struct ScreenUnit {
     int o_piv, o_size, o_rho, o_cl, o_mask, o_edge, o_z, edge_cap;
     long long bytes;
-    __host__ __device__ ScreenUnit(int T, int nch) {
+    __host__ __device__ ScreenUnit(int T, int nch, int edges) {
         const long long t4 = (long long)align_up((size_t)T * 4, 256);
-        edge_cap = SCREEN_OPEN * T + 64;
+        edge_cap = edges;
         long long o = SU_WORDS * 4;
         o_piv = (int)o; o += t4;
         o_size = (int)o; o += t4;
@@ -146,7 +149,8 @@ struct ScreenParams {
     int nch, nk;
     float kap, kap1;           // candidate threshold on the raw accumulator; kappa with the rounding allowance
     float f2, safe, thr, cos_tight;
-    uint32_t open;             // unexplained candidates of a unit above which it is dense (at most SCREEN_OPEN per token)
+    uint32_t open;             // unexplained candidates of a unit above which it is dense
+    int edge_cap;              // see ScreenUnit
     float* gamma;              // one unit: largest |cos| of the pairs multiplied out (bits under an integer max), or NULL
     float* inv_norm;           // one unit: inverse norms of the rows, or NULL
     const void* X[SCREEN_MAX_LAYERS];
@@ -192,7 +196,7 @@ template <> __device__ inline void screen_load8<float>(const float* row, int e0,
 constexpr int SKETCH_ROWS = 32;                               // rows per workgroup
 template <typename In>
 __global__ __launch_bounds__(256) void k_screen_sketch(ScreenParams p, int row_blocks) {
-    const ScreenUnit U(p.T, p.nch);
+    const ScreenUnit U(p.T, p.nch, p.edge_cap);
     const int unit = blockIdx.x / row_blocks, rb = blockIdx.x - unit * row_blocks;
     int layer, group;
     char* base = screen_unit(p, U, unit, &layer, &group);
@@ -337,7 +341,7 @@ __global__ __launch_bounds__(256, NCH == 4 ? 2 : 3) void k_screen_pairs(ScreenPa
     const int per = (total + 7) >> 3;
     const int w = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
     if (w >= total || (int)(blockIdx.x >> 3) >= per) return;
-    const ScreenUnit U(p.T, p.nch);
+    const ScreenUnit U(p.T, p.nch, p.edge_cap);
     const int unit = w / it.per_unit;
     int layer, group, tb, s_lo, sblk;
     char* base = screen_unit(p, U, unit, &layer, &group);
@@ -538,8 +542,8 @@ __device__ inline float screen_cos(float xy, float xx, float yy) {
 }
 
 // (k_screen_rest has to agree: a quarter of the pairs is more than SCREEN_OPEN per token.  The full selection needs the norms
-// in any case.  Nobody writes the counts while they are read here, so scalar loads will do; in short sequences the wait for
-// them is more than the pass they save: 0.8 of 8 us at T=512, d=768 in fp32.)
+// in any case.  Nobody writes the counts while they are read here, so scalar loads will do; for short rows and sequences the
+// wait for them is not worth the pass they may save: 0.5 of 8 us at 12 x 512 x 768 in fp32, 1 of 34 us at 128 x 2048 x 256.)
 __device__ inline bool screen_crowded(const ScreenParams& p, const char* unit) {
     static_assert(1024 / 8 > SCREEN_OPEN, "crowded units are dense");
     if (p.T < 1024 || p.inv_norm) return false;
@@ -562,7 +566,7 @@ __global__ __launch_bounds__(256) void k_screen_exact(ScreenParams p, int row_bl
     const int per = (total + 7) >> 3;
     const int w = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
     if (w >= total || (int)(blockIdx.x >> 3) >= per) return;
-    const ScreenUnit U(p.T, p.nch);
+    const ScreenUnit U(p.T, p.nch, p.edge_cap);
     const int unit = w / row_blocks, rb = w - unit * row_blocks;
     int layer, group;
     char* base = screen_unit(p, U, unit, &layer, &group);
@@ -571,7 +575,7 @@ __global__ __launch_bounds__(256) void k_screen_exact(ScreenParams p, int row_bl
     int32_t* size = reinterpret_cast<int32_t*>(base + U.o_size);
     float* rho = reinterpret_cast<float*>(base + U.o_rho);
     uint16_t* cl = reinterpret_cast<uint16_t*>(base + U.o_cl);
-    const bool crowded = screen_crowded(p, base);
+    const bool crowded = LPR == 64 && screen_crowded(p, base);
     if (threadIdx.x == 0) { s_pairs = 0u; s_flags = 0u; }
     __syncthreads();
     const int li = threadIdx.x & (LPR - 1);
@@ -636,7 +640,7 @@ __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) 
     __shared__ uint2 s_edge[SCREEN_TILE_PAIRS];
     __shared__ float s_rho[256];
     __shared__ uint16_t s_cl[256];
-    const ScreenUnit U(p.T, p.nch);
+    const ScreenUnit U(p.T, p.nch, p.edge_cap);
     const int units = p.G * p.L, unit = (int)blockIdx.x % units;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     int layer, group;
@@ -1046,7 +1050,7 @@ __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
     __shared__ uint32_t s_edges[SCREEN_MAX_LAYERS], s_dense[SCREEN_MAX_LAYERS];
     unsigned long long alone = 0ull;                          // layers whose assignment is left to the tiles (uniform)
     const ScreenParams& p = c.s;
-    const ScreenUnit SU(p.T, p.nch);
+    const ScreenUnit SU(p.T, p.nch, p.edge_cap);
     const int tid = threadIdx.x, T = p.T, g = blockIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const ChainGeom CG(T, p.L, TWO);
@@ -1204,7 +1208,7 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
     const int start = meta[META_PROGRESS];
     const unsigned long long alone = *reinterpret_cast<const unsigned long long*>(meta + META_ALONE);
     if (start >= first + n_layers) {
-        const ScreenUnit SU(T, rp.c.s.nch);
+        const ScreenUnit SU(T, rp.c.s.nch, rp.c.s.edge_cap);
         for (int j = worker; j < n_layers * (rp.c.assign ? 2 : 1); j += workers) {
             const int l = j < n_layers ? j : j - n_layers;
             if ((alone >> l) & 1ull) continue;

@@ -73,7 +73,7 @@ __global__ __launch_bounds__(SCREEN_SORT_THREADS) void k_screen_sort(ScreenFullP
     __shared__ int s_first[256], s_last[256];                 // start of the cluster a block of members starts with; last head of a block
     __shared__ int2 s_sum[2][SCREEN_SORT_THREADS / 64];
     const ScreenParams& p = f.s;
-    const ScreenUnit U(p.T, p.nch);
+    const ScreenUnit U(p.T, p.nch, p.edge_cap);
     const int tid = threadIdx.x, T = p.T, Tp = (T + 63) & ~63;
     const uint32_t* hdr = reinterpret_cast<const uint32_t*>(p.area);
     const ScreenLists L = screen_full_lists(p, U);
@@ -201,7 +201,7 @@ template <typename In, bool DMA>
 __global__ __launch_bounds__(256) void k_screen_gram(ScreenParams sp, GramParams p) {
     extern __shared__ __align__(16) char lds[];
     __shared__ int s_found;
-    const ScreenUnit U(sp.T, sp.nch);
+    const ScreenUnit U(sp.T, sp.nch, sp.edge_cap);
     const ScreenLists L = screen_full_lists(sp, U);
     const int total = L.work[SW_TILES], total128 = L.work[SW_TILES128], mem = L.work[SW_MEMBERS], heads = L.work[SW_HEADS];
     const int per = (total + 7) >> 3, per128 = (total128 + 7) >> 3, xcd = (int)(blockIdx.x & 7);

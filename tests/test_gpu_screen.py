@@ -105,7 +105,7 @@ CASES = [
     ("loose", 1700, 512, 4, "bf16", 0.1),         # a few edges per token, listed
     # rows that share a direction: given up before their exact products, every step on the tiles of every shape
     ("common", 513, 320, 4, "bf16", 0.1), ("common", 700, 385, 3, "f32", 0.1), ("common", 1100, 1024, 3, "bf16", 0.1),
-    ("common", 2100, 2048, 3, "bf16", 0.1), ("collapsed", 1300, 768, 4, "bf16", 0.1),
+    ("common", 2100, 2048, 3, "bf16", 0.1), ("collapsed", 1300, 768, 4, "bf16", 0.1), ("common", 1023, 2112, 2, "bf16", 0.1),
 ]
 
 
