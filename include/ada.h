@@ -78,14 +78,24 @@ typedef enum {
 /* Human-readable name of a status code (static storage). */
 const char* ada_status_string(int status);
 
-/* Bytes of device workspace a call with this T needs (256-byte aligned base required). */
+/*
+ * Bytes of device workspace a call with this T needs (256-byte aligned base required): about 8 KB per token (sketches
+ * and candidate pairs of up to 64 layers at a time), no more than 16 MB from T = 2048 on, 34 MB at T = 16384, where a table of
+ * one bit per pair is larger; 25 bytes per token for longer sequences.
+ */
 size_t ada_workspace_bytes(int T);
 
 /*
- * Zero-fills a workspace (one small kernel on the stream).  A workspace must be zero-filled once, by this call or
- * by any memset, before its first use; every library call leaves it ready for the next one (it holds counters that
- * the last workgroup of a launch resets).  If a call is abandoned part-way (device error), initialise it again.
- * Calls that share a workspace must not overlap in time.
+ * Of these the bytes at the front that must be zero before a workspace's first use (scalars, keys and records, 25
+ * to 30 per token); the rest may hold anything.
+ */
+size_t ada_workspace_zero_bytes(int T);
+
+/*
+ * Zero-fills a workspace (one small kernel on the stream).  The front of a workspace (ada_workspace_zero_bytes) must be
+ * zero-filled once, by this call or by any memset, before its first use; every library call leaves it ready for the
+ * next one (it holds counters that the last workgroup of a launch resets).  If a call is abandoned part-way (device
+ * error), initialise it again.  Calls that share a workspace must not overlap in time.
  */
 int ada_workspace_init(void* ws, size_t ws_bytes, void* stream);
 

@@ -1793,6 +1793,8 @@ const char* ada_status_string(int status) {
 
 size_t ada_workspace_bytes(int T) { return (T < 1 || T > ADA_MAX_T) ? 0 : ws_bytes_for(T); }
 
+size_t ada_workspace_zero_bytes(int T) { return (T < 1 || T > ADA_MAX_T) ? 0 : ws_fixed_bytes(T); }
+
 int ada_workspace_init(void* ws, size_t ws_bytes, void* stream) {
     if (!ws) return ADA_ERR_NULL;
     if (((uintptr_t)ws % 256) != 0 || ws_bytes % 4 != 0) return ADA_ERR_WORKSPACE;

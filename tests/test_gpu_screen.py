@@ -273,6 +273,39 @@ def test_assignment_of_long_sequences_in_unaligned_rows(T):
         assert (chosen >= oracle.assign_nearest(wl.as_f64(xs_cpu[l]), idx)["corr"] - 2e-4).all()
 
 
+@pytest.mark.parametrize("kind,T,d", [("clusters", 700, 256), ("strays", 700, 256), ("common", 1100, 256), ("clusters", 2048, 128)])
+def test_only_the_front_of_a_workspace_has_to_be_zero(kind, T, d):
+    """Every call on workspaces whose front is zero and whose rest is all ones bits, bit for bit as on zeroed ones."""
+    print("[case] workspace: %s T=%d d=%d" % (kind, T, d), flush=True)
+    tau, H = 0.1, d // 64
+    xs = [x.to(DEV) for x in activations(kind, T, d, 3, "bf16", seed=T)]
+    qkv = [torch.randn(T, d, device=DEV).bfloat16() for _ in range(3)]
+    pairs = [torch.stack([x, x.flip(0)]) for x in xs]
+
+    def calls():
+        for n, f in ((1, lambda ws: pa.ada_cascade_layers(xs, tau, ws=ws)), (1, lambda ws: pa.ada_cascade_layers(xs, tau, ws=ws, flags=pa.FLAG_TWO_PASS)),
+                     (1, lambda ws: pa.ada_select_full(xs[0], tau, ws=ws)), (1, lambda ws: pa.ada_select_full(xs[0], tau, ws=ws, flags=pa.FLAG_GREEDY_COVER)),
+                     (1, lambda ws: pa.ada_cascade_step(xs[1], tau, torch.arange(0, T, 3, dtype=torch.int32, device=DEV), ws=ws)),
+                     (2, lambda ws: pa.ada_cascade_layers_grouped(pairs, tau, ws=ws)),
+                     (2, lambda ws: pa.ada_pipeline_layers(xs, *([m] * 3 for m in qkv), H, tau, ws=ws))):
+            yield n, f
+
+    for n, f in calls():
+        one, front = pa.workspace_bytes(T), pa.ada_workspace_zero_bytes(T)
+        dirty = torch.full((n, one), 0xFF, dtype=torch.uint8, device=DEV)
+        dirty[:, :front] = 0
+        got, want = f(dirty.view(-1)), f(torch.zeros(n * one, dtype=torch.uint8, device=DEV))
+        torch.cuda.synchronize()
+        assert torch.equal(got["counts"], want["counts"])
+        if "gamma" in got:
+            assert torch.equal(got["gamma"], want["gamma"])
+        if "assign" in got:
+            assert torch.equal(got["assign"], want["assign"]) and all(torch.equal(a, b) for a, b in zip(got["out"], want["out"]))
+        rows = got["counts"].reshape(-1, 4)[:, 0].tolist()
+        for r, a, b in zip(rows, got["idx"].reshape(-1, T), want["idx"].reshape(-1, T)):
+            assert torch.equal(a[:r], b[:r])
+
+
 FULL = [
     # kind, T, d, dtype, tau, greedy, big: long enough for the graph, by one rule each (greedy / fp32 / other bf16 rows / whole pieces)
     ("clusters", 1500, 64, "bf16", 0.1, True, 0), ("clusters", 2049, 1001, "bf16", 0.1, True, 0), ("clusters", 4100, 96, "f32", 0.2, True, 0),
