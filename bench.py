@@ -83,9 +83,17 @@ def cpu_baseline_extras():
     return out
 
 
-def device_us(kern, calls):
-    """Time of all kernels of a call (ada_profile_collect over that many calls)."""
-    return 1e3 * sum(v["ms"] for v in kern.values()) / calls
+def call_us(call, n):
+    """Time of a call among others: one pair of events around n of them (a pair around every kernel of a call adds its own
+    gaps, a third to two thirds of the time where a call is eight short launches)."""
+    import torch
+    first, last = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    first.record()
+    for _ in range(n):
+        call()
+    last.record()
+    last.synchronize()
+    return 1e3 * first.elapsed_time(last) / n
 
 
 def recorded_traffic(name):
@@ -231,9 +239,9 @@ def main():
         avg_us = {k: (1e3 * v["ms"] / v["launches"] if v["launches"] else None) for k, v in kern.items()}
         # The layers of a pass share their launches (sketches, pairs, exact products, rest, walk, lists), so the unit is the
         # pass: every row of every layer once; the sketches' share read twice and the O(T) outputs are neglected.
-        pass_us = device_us(kern, args.steps)
+        pass_us = call_us(step, args.steps)
         layer_bytes = T * d * esz
-        result["roofline"] = {"bound": "hbm", "kernel": "layer loop (all kernels of a pass)",
+        result["roofline"] = {"bound": "hbm", "kernel": "layer loop (a whole pass)",
                               "achieved": L * layer_bytes / (1e-6 * pass_us) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                               "frac": L * layer_bytes / (1e-6 * pass_us) / 1e9 / HBM_PEAK_GBS, "traffic": None,
                               "us_per_pass": pass_us, "us_per_layer": pass_us / L, "bytes_per_pass": L * layer_bytes}
@@ -426,15 +434,11 @@ def main():
         torch.cuda.synchronize()
         g_elapsed = time.perf_counter() - t0
         assert torch.equal(outb["counts"][0], out["counts"]), "grouped sequence 0 differs from the single-sequence pass"
-        pa.ada_profile_enable(True)
-        pa.ada_cascade_layers_grouped(xg, w.tau, ws=wsb, stream=stream, out=outb)
-        torch.cuda.synchronize()
-        kg = pa.ada_profile_collect()
-        pa.ada_profile_enable(False)
+        us_stacked = call_us(lambda: pa.ada_cascade_layers_grouped(xg, w.tau, ws=wsb, stream=stream, out=outb), nb)
         result["batched"]["stacked_one_launch_per_step"] = {
             "ms_per_batch_pass": 1e3 * g_elapsed / nb, "layers_per_s": Bq * L * nb / g_elapsed,
             "tokens_per_s": Bq * L * nb / g_elapsed * T,
-            "us_per_layer": device_us(kg, 1) / L}
+            "us_per_layer": us_stacked / L}
         del xg
         # ---- sixteen stacked sequences (four layers each): the regime in which a launch's fixed chain of memory round
         # trips is shared by enough tiles to matter little, i.e. what the tile engine itself sustains
@@ -447,13 +451,7 @@ def main():
         for _ in range(2):
             o16 = pa.ada_cascade_layers_grouped(x16, w.tau, ws=ws16, stream=stream, out=o16)
         torch.cuda.synchronize()
-        pa.ada_profile_enable(True)
-        for _ in range(5):
-            pa.ada_cascade_layers_grouped(x16, w.tau, ws=ws16, stream=stream, out=o16)
-        torch.cuda.synchronize()
-        k16 = pa.ada_profile_collect()
-        pa.ada_profile_enable(False)
-        us16 = device_us(k16, 5) / L16
+        us16 = call_us(lambda: pa.ada_cascade_layers_grouped(x16, w.tau, ws=ws16, stream=stream, out=o16), 5) / L16
         result["batched"]["stacked_16_sequences"] = {
             "sequences": B16, "layers": L16, "us_per_layer": us16, "us_per_layer_and_sequence": us16 / B16,
             "roofline": {"bound": "hbm", "kernel": "layer loop (16 sequences per launch)",
@@ -476,16 +474,12 @@ def main():
             pa.ada_cascade_layers_grouped(hv, w.tau, ws=wsh, stream=stream, out=outh)
         torch.cuda.synchronize()
         h_elapsed = time.perf_counter() - t0
-        pa.ada_profile_enable(True)
-        pa.ada_cascade_layers_grouped(hv, w.tau, ws=wsh, stream=stream, out=outh)
-        torch.cuda.synchronize()
-        kh = pa.ada_profile_collect()
-        pa.ada_profile_enable(False)
+        us_heads = call_us(lambda: pa.ada_cascade_layers_grouped(hv, w.tau, ws=wsh, stream=stream, out=outh), nb)
         ch = outh["counts"].cpu()
         assert ch[:, :, 3].flatten().tolist() == [0] * (Hh * L), "per-head pass reported an error"
         result["per_head"] = {"heads": Hh, "d_h": d // Hh, "ms_per_pass": 1e3 * h_elapsed / nb,
                               "layers_per_s": L * nb / h_elapsed,
-                              "us_per_layer_all_heads": device_us(kh, 1) / L,
+                              "us_per_layer_all_heads": us_heads / L,
                               "mean_r_h": float(ch[:, 1:, 0].float().mean())}
         del wsb, outb, hv, wsh, outh
 
@@ -501,13 +495,7 @@ def main():
             for _ in range(2):
                 oo = pa.ada_cascade_layers(xo, wo.tau, ws=wso, stream=stream, want_lists=False)
             torch.cuda.synchronize()
-            pa.ada_profile_enable(True)
-            for _ in range(5):
-                oo = pa.ada_cascade_layers(xo, wo.tau, ws=wso, stream=stream, want_lists=False)
-            torch.cuda.synchronize()
-            ko = pa.ada_profile_collect()
-            pa.ada_profile_enable(False)
-            us_o = device_us(ko, 5) / len(xo)
+            us_o = call_us(lambda: pa.ada_cascade_layers(xo, wo.tau, ws=wso, stream=stream, want_lists=False, out=oo), 5) / len(xo)
             by = wo.T * wo.d * (2 if wo.dtype == "bf16" else 4)
             r_in = float(oo["counts"][:-1, 0].float().mean())         # the sets the timed steps inherited
             other[wo.name] = {"T": wo.T, "d": wo.d, "mean_r": float(oo["counts"][1:, 0].float().mean()),
@@ -527,13 +515,7 @@ def main():
             for _ in range(2):
                 o4 = pa.ada_cascade_layers_grouped(x4g, w4b.tau, ws=ws4g, stream=stream, want_lists=False, out=o4)
             torch.cuda.synchronize()
-            pa.ada_profile_enable(True)
-            for _ in range(4):
-                pa.ada_cascade_layers_grouped(x4g, w4b.tau, ws=ws4g, stream=stream, want_lists=False, out=o4)
-            torch.cuda.synchronize()
-            k4g = pa.ada_profile_collect()
-            pa.ada_profile_enable(False)
-            us_g = device_us(k4g, 4) / L4
+            us_g = call_us(lambda: pa.ada_cascade_layers_grouped(x4g, w4b.tau, ws=ws4g, stream=stream, want_lists=False, out=o4), 4) / L4
             by4 = B4 * w4b.T * w4b.d * 2
             other[w4b.name + "_batch4_stacked"] = {"T": w4b.T, "d": w4b.d, "sequences": B4,
                                                    "mean_r": float(o4["counts"][:, 1:, 0].float().mean()),
@@ -569,14 +551,9 @@ def main():
             for _ in range(2):
                 gsel = pa.ada_select_full(xs[0], w.tau, ws=ws, stream=stream, flags=pa.FLAG_GREEDY_COVER)
             torch.cuda.synchronize()
-            pa.ada_profile_enable(True)
-            for _ in range(5):
-                gsel = pa.ada_select_full(xs[0], w.tau, ws=ws, stream=stream, flags=pa.FLAG_GREEDY_COVER)
-            torch.cuda.synchronize()
-            kgr = pa.ada_profile_collect()
-            pa.ada_profile_enable(False)
             result["greedy_cover"] = {"r": int(gsel["counts"][0]),
-                                      "us": device_us(kgr, 5)}
+                                      "us": call_us(lambda: pa.ada_select_full(xs[0], w.tau, ws=ws, stream=stream,
+                                                                               flags=pa.FLAG_GREEDY_COVER), 20)}
 
         # ---- the same selection at the long-context shape (T=8192, d=4096, one sequence), every token's correlation
         # included: from the graph of near pairs
@@ -586,15 +563,10 @@ def main():
         for _ in range(2):
             pa.ada_select_full(x4, w4.tau, ws=ws4, stream=stream)
         torch.cuda.synchronize()
-        pa.ada_profile_enable(True)
-        for _ in range(5):
-            pa.ada_select_full(x4, w4.tau, ws=ws4, stream=stream)
-        torch.cuda.synchronize()
-        k4 = pa.ada_profile_collect()
-        pa.ada_profile_enable(False)
-        us4, bytes4 = device_us(k4, 5), w4.T * w4.d * (2 if w4.dtype == "bf16" else 4)
+        us4 = call_us(lambda: pa.ada_select_full(x4, w4.tau, ws=ws4, stream=stream), 20)
+        bytes4 = w4.T * w4.d * (2 if w4.dtype == "bf16" else 4)
         result["full_select_long"] = {"workload": "%s layer 0: T=%d d=%d %s, one sequence" % (w4.name, w4.T, w4.d, w4.dtype),
-                                      "roofline": {"bound": "hbm", "kernel": "full selection (all kernels of a call)",
+                                      "roofline": {"bound": "hbm", "kernel": "full selection (a whole call)",
                                                    "achieved": bytes4 / (1e-6 * us4) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                                    "frac": bytes4 / (1e-6 * us4) / 1e9 / HBM_PEAK_GBS, "traffic": None,
                                                    "us_per_call": us4, "bytes_per_call": bytes4}}
