@@ -1112,45 +1112,46 @@ inline int attn_grid_x(const AttnParams& p, int n_layers) {
 }
 
 // bf16: the kernel that keeps scores and weights in registers (eight waves: four multiply, four fetch)
-template <int DH>
-hipError_t launch_attn_regs(const AttnParams& p, const AttnLayers& layers, int n_layers, hipStream_t st) {
+template <int DH, typename Layers>
+hipError_t launch_attn_regs(const AttnParams& p, const Layers& layers, int n_layers, hipStream_t st) {
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     constexpr int lds = AttnGeom2<DH>::LDS;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_rep2<DH>),
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_rep2<DH, Layers>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     if (attr_err != hipSuccess) return attr_err;
     ProfScope ps(ADA_K_ATTN, st);
     const int gx = attn_grid_x(p, n_layers);
-    hipLaunchKernelGGL((k_attn_rep2<DH>), dim3(gx, p.H, n_layers), dim3(512), lds, st, p, layers);
+    hipLaunchKernelGGL((k_attn_rep2<DH, Layers>), dim3(gx, p.H, n_layers), dim3(512), lds, st, p, layers);
     return hipGetLastError();
 }
 
-template <typename In, int DH>
-hipError_t launch_attn(const AttnParams& p, const AttnLayers& layers, int n_layers, hipStream_t st) {
+template <typename In, int DH, typename Layers>
+hipError_t launch_attn(const AttnParams& p, const Layers& layers, int n_layers, hipStream_t st) {
     if constexpr (sizeof(In) == 2) {
         static const bool first_kernel = [] {             // development switch: ADA_ATTN=lds keeps the first kernel
             const char* e = dev_switch("ADA_ATTN");
             return e && std::string(e) == "lds";
         }();
         // its hand-over stores 16 bytes per lane
-        bool out16 = p.ld_out % 4 == 0;
-        for (int l = 0; l < n_layers; ++l) out16 = out16 && (uintptr_t)layers.out[l] % 16 == 0;
+        bool out16 = p.ld_out % 4 == 0 && (uintptr_t)p.out % 16 == 0;
+        if constexpr (std::is_same<Layers, AttnLayers>::value)
+            for (int l = 0; l < n_layers; ++l) out16 = out16 && (uintptr_t)layers.out[l] % 16 == 0;
         if (!first_kernel && out16) return launch_attn_regs<DH>(p, layers, n_layers, st);
     }
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     constexpr int lds = AttnGeom<In, DH>::LDS;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_rep<In, DH>),
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_rep<In, DH, Layers>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     if (attr_err != hipSuccess) return attr_err;
     ProfScope ps(ADA_K_ATTN, st);
     const int gx = attn_grid_x(p, n_layers);
-    hipLaunchKernelGGL((k_attn_rep<In, DH>), dim3(gx, p.H, n_layers), dim3(256), lds, st, p, layers);
+    hipLaunchKernelGGL((k_attn_rep<In, DH, Layers>), dim3(gx, p.H, n_layers), dim3(256), lds, st, p, layers);
     return hipGetLastError();
 }
 
@@ -1829,7 +1830,8 @@ int ada_select_full_grouped(const ada_groups* groups, const void* X, int T, int 
     return run_full(X, T, d, ld, dtype, tau, mask, idx, counts, nullptr, nullptr, ws, (hipStream_t)stream, G, go);
 }
 
-static int attention_launch(const AttnParams& p, const AttnLayers& layers, int n_layers, int d_h, int dtype, hipStream_t st) {
+extern "C++" template <typename Layers>
+static int attention_launch(const AttnParams& p, const Layers& layers, int n_layers, int d_h, int dtype, hipStream_t st) {
     hipError_t e;
     if (dtype == ADA_BF16)
         e = d_h == 64 ? launch_attn<uint16_t, 64>(p, layers, n_layers, st) : d_h == 128 ? launch_attn<uint16_t, 128>(p, layers, n_layers, st)
@@ -1865,9 +1867,7 @@ static int attention_run(const void* Q, const void* K, const void* V, int T, int
     }
     const AttnParams p = {Q, K, V, ld, T, H, idx, r_dev, r, w.nonrep_idx, out, ld_out,
                           (float)(1.0 / sqrt((double)d_h)), (flags & ADA_FLAG_ATTN_CAUSAL) ? 1 : 0, info, err, nerr};
-    AttnLayers one = {};
-    one.Q[0] = Q; one.K[0] = K; one.V[0] = V; one.out[0] = out;
-    return attention_launch(p, one, 1, d_h, dtype, st);
+    return attention_launch(p, AttnOne(), 1, d_h, dtype, st);
 }
 
 int ada_attention_compressed(const void* Q, const void* K, const void* V, int T, int H, int d_h, int64_t ld, int dtype,
@@ -2187,7 +2187,7 @@ int ada_pipeline_layers(const void* const* X_layers, const void* const* Q_layers
         const AttnParams p = {al.Q[0], al.K[0], al.V[0], ld, T, H, idx_all + o, counts_all + (size_t)first * 4, T, pos, al.out[0], ld_out,
                               (float)(1.0 / sqrt((double)d_h)), (flags & ADA_FLAG_ATTN_CAUSAL) ? 1 : 0, info_all + (size_t)first * 8 + 4,
                               nullptr, 0};
-        rc = attention_launch(p, al, n, d_h, dtype, sa);
+        rc = n > 1 ? attention_launch(p, al, n, d_h, dtype, sa) : attention_launch(p, AttnOne(), 1, d_h, dtype, sa);
         if (first + n < L && !fork(sa, ss)) rc = ADA_ERR_DEVICE;   // (the next batch's positions take the place of these)
     }
     if (screened) {                                               // (stream_attn has waited for the whole selection)
