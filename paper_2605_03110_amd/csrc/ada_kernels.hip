@@ -2165,15 +2165,20 @@ int ada_pipeline_layers(const void* const* X_layers, const void* const* Q_layers
     int rc = ADA_OK;
     // Screened: the sets and assignments of many layers come together, and so does the attention on them (a layer of 16
     // heads and 400 representatives has 112 workgroups for 256 CUs; several layers in one launch fill the chip).  The
-    // positions go where the second workspace would have its hit table.
+    // positions go where the second workspace would have its hit table, in two places in turns, so that the selection of
+    // a batch of layers runs beside the attention of the batch before and waits for the one before that.
     ScreenPlan plan;
     const bool screened = screen_eligible(X_layers[0], L, 1, T, d, ld, dtype, tau, flags, &plan);
-    const size_t fit_pos = ws_area_bytes(T) / ((size_t)T * 4);
-    const int batch = fit_pos < (size_t)ATTN_LAYERS ? (int)fit_pos : ATTN_LAYERS;
-    int32_t* pos = reinterpret_cast<int32_t*>(carve(ws_attn, T).hits);
-    for (int first = 0; screened && first < L && rc == ADA_OK; first += batch) {
-        const int n = L - first < batch ? L - first : batch;
+    const size_t fit_pos = ws_area_bytes(T) / ((size_t)T * 4) / 2;
+    const int most = fit_pos < (size_t)ATTN_LAYERS ? (int)fit_pos : ATTN_LAYERS;
+    const int batches = (L + most - 1) / most, batch = (L + batches - 1) / batches;
+    hipEvent_t attended[2] = {nullptr, nullptr};                  // behind the attention of the last batches
+    for (int k = 0; screened && k < batches && rc == ADA_OK; ++k) {
+        const int first = k * batch, n = L - first < batch ? L - first : batch;
+        if (n < 1) break;
         const size_t o = (size_t)first * (size_t)T;
+        int32_t* pos = reinterpret_cast<int32_t*>(carve(ws_attn, T).hits) + (size_t)(k & 1) * batch * T;
+        if (attended[k & 1] && hipStreamWaitEvent(ss, attended[k & 1], 0) != hipSuccess) { rc = ADA_ERR_DEVICE; break; }
         // (later batches go on from the set that the one before left)
         rc = run_layers_screened(plan, X_layers, n, 1, 0, T, d, ld, dtype, tau, idx_all, counts_all, gram_ops_all, nullptr,
                                  nullptr, 0, 0, 0, ws, ss, flags & ADA_FLAG_CROSS_EARLIER_ONLY, assign_all, pos - (ptrdiff_t)o,
@@ -2188,8 +2193,13 @@ int ada_pipeline_layers(const void* const* X_layers, const void* const* Q_layers
                               (float)(1.0 / sqrt((double)d_h)), (flags & ADA_FLAG_ATTN_CAUSAL) ? 1 : 0, info_all + (size_t)first * 8 + 4,
                               nullptr, 0};
         rc = n > 1 ? attention_launch(p, al, n, d_h, dtype, sa) : attention_launch(p, AttnOne(), 1, d_h, dtype, sa);
-        if (first + n < L && !fork(sa, ss)) rc = ADA_ERR_DEVICE;   // (the next batch's positions take the place of these)
+        if (rc == ADA_OK && ss != sa && k + 2 < batches &&
+            ((!attended[k & 1] && hipEventCreateWithFlags(&attended[k & 1], hipEventDisableTiming) != hipSuccess) ||
+             hipEventRecord(attended[k & 1], sa) != hipSuccess))
+            rc = ADA_ERR_DEVICE;
     }
+    for (hipEvent_t ev : attended)
+        if (ev) (void)hipEventDestroy(ev);                        // released by the runtime once it has completed
     if (screened) {                                               // (stream_attn has waited for the whole selection)
         if (!fork(sa, main)) return ADA_ERR_DEVICE;
         if (rc != ADA_OK && !fork(ss, main)) return ADA_ERR_DEVICE;

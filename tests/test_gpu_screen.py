@@ -250,6 +250,25 @@ def test_assignment_of_tokens_that_no_representative_covers(T, d, L, tau, seed, 
     assert alone > 0
 
 
+@pytest.mark.parametrize("L", [17, 35, 50])
+def test_batches_of_pipelined_layers_on_two_streams(L):
+    """Selections run beside the attention of the batch before: every output as on one stream, several times over."""
+    print("[case] pipeline batches: L=%d" % L, flush=True)
+    T, d, H, tau = 260, 128, 2, 0.1
+    xs = [x.to(DEV) for x in activations("strays", T, d, L, "bf16", seed=L)]
+    qkv = [[torch.randn(T, d, device=DEV).bfloat16() for _ in range(L)] for _ in range(3)]
+    ws = pa.workspace_batched(T, 2, DEV)
+    want = pa.ada_pipeline_layers(xs, *qkv, H, tau, ws=ws)
+    torch.cuda.synchronize()
+    streams = torch.cuda.Stream(), torch.cuda.Stream()
+    for _ in range(5):
+        got = pa.ada_pipeline_layers(xs, *qkv, H, tau, ws=ws, stream_sel=streams[0], stream_attn=streams[1])
+        torch.cuda.synchronize()
+        for key in ("counts", "assign", "info", "gram_ops"):
+            assert torch.equal(got[key], want[key]), key
+        assert all(torch.equal(a, b) for a, b in zip(got["out"], want["out"]))
+
+
 @pytest.mark.parametrize("T", [8000, 8065, 12321, 16384])
 def test_assignment_of_long_sequences_in_unaligned_rows(T):
     """X starts on no 16 bytes (Q, K and V must, X need not): the register-staged tiles' workgroups keep two words per token
