@@ -39,7 +39,7 @@ struct AttnLayers {
     const void *Q[ATTN_LAYERS], *K[ATTN_LAYERS], *V[ATTN_LAYERS];
     float* out[ATTN_LAYERS];
 };
-struct AttnOne {};            // one layer: AttnParams says it all (500 bytes less of arguments: T=2048, 16 x 256 32.2 -> 31.9 us, 7 x 64 at T=4096 21.3 -> 20.9)
+struct AttnOne {};            // one layer: AttnParams says it all (500 bytes less of arguments: 16 x 128 fp32 at T=2048 67.3 -> 67.0 us)
 __device__ inline void attn_layer(AttnParams&, const AttnOne&) {}
 __device__ inline void attn_layer(AttnParams& p, const AttnLayers& a) {
     const int z = blockIdx.z;
@@ -101,20 +101,16 @@ __device__ inline int attn_status(const AttnParams& p, int r) {
 // Workgroup -> (head, first query block).  Workgroups go to the eight XCDs in turn by their linear index, and every
 // XCD has an L2 of its own: with the launch's natural order the query blocks of one head would sit on eight different
 // XCDs and each of them would pull that head's K and V rows from memory.  When the head count is a multiple of 8 the
-// index is re-read so that a head's workgroups share an XCD (head % 8).  Several layers are more workgroups than CUs: there
-// query blocks run slowest, so that under the causal mask, which takes them from the last one down (attn_block), the long
-// ones start first.
+// index is re-read so that a head's workgroups share an XCD (head % 8).  Query blocks run slowest, so that under the
+// causal mask, which takes them from the last one down (attn_block), the long ones start first.
 struct AttnWho { int h, qblk; };
-template <bool MANY>
 __device__ inline AttnWho attn_who(int H) {
-    const int gx = gridDim.x, lin = blockIdx.y * gx + blockIdx.x;
-    if (!MANY && H % 8 != 0) return {(int)blockIdx.y, (int)blockIdx.x};
+    const int lin = blockIdx.y * gridDim.x + blockIdx.x;
     if (H % 8 != 0) return {lin % H, lin / H};
     const int xcd = lin & 7, slot = lin >> 3, hx = H >> 3;
-    return MANY ? AttnWho{(slot % hx) * 8 + xcd, slot / hx} : AttnWho{(slot / gx) * 8 + xcd, slot % gx};
+    return {(slot % hx) * 8 + xcd, slot / hx};
 }
-template <bool MANY>
-__device__ inline int attn_block(int b, int nq, int causal) { return MANY && causal ? nq - 1 - b : b; }
+__device__ inline int attn_block(int b, int nq, int causal) { return causal ? nq - 1 - b : b; }
 
 __device__ inline int attn_off(int row, int piece, int ppr) {
     const int swz = ppr >= 16 ? (row & 15) : lds_swz(row);
@@ -153,7 +149,6 @@ template <typename In, int DH> struct AttnGeom {
 // Layers: AttnOne or AttnLayers.
 template <typename In, int DH, typename Layers>
 __global__ __launch_bounds__(256) void k_attn_rep(AttnParams p, Layers layers) {
-    constexpr bool MANY = std::is_same<Layers, AttnLayers>::value;
     attn_layer(p, layers);
     using G = AttnGeom<In, DH>;
     constexpr int EPP = G::EPP, PPR = G::PPR, PPRV = G::PPRV, NB = DH / 64;
@@ -172,7 +167,7 @@ __global__ __launch_bounds__(256) void k_attn_rep(AttnParams p, Layers layers) {
     ATTN_CLK(0);
     const int r = p.r_dev ? *p.r_dev : p.r_host;
     if (attn_status(p, r) != ADA_OK) return;               // k_attn_pos rejected the set or the assignment
-    const AttnWho who = attn_who<MANY>(p.H);
+    const AttnWho who = attn_who(p.H);
     const int h = who.h;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -180,7 +175,7 @@ __global__ __launch_bounds__(256) void k_attn_rep(AttnParams p, Layers layers) {
     // sizes the grid for the chip, not for the largest possible set (idle workgroups of this LDS size are not free)
     const int nq = (r + 63) / 64;
     for (int b = who.qblk; b < nq; b += gridDim.x) {
-    const int q0 = attn_block<MANY>(b, nq, p.causal) * 64;
+    const int q0 = attn_block(b, nq, p.causal) * 64;
     __syncthreads();                                       // a previous query block's hand-over is done with the LDS
     const In* Qh = reinterpret_cast<const In*>(p.Q) + (size_t)h * DH;
     const In* Kh = reinterpret_cast<const In*>(p.K) + (size_t)h * DH;
@@ -456,7 +451,6 @@ template <int DH> struct AttnGeom2 {
 //          left and for the indices of block kb + 3; the multipliers add weights x V^T(kb) to their rows.
 template <int DH, typename Layers>
 __global__ __launch_bounds__(512) void k_attn_rep2(AttnParams p, Layers layers) {
-    constexpr bool MANY = std::is_same<Layers, AttnLayers>::value;
     attn_layer(p, layers);
     using In = uint16_t;
     using G = AttnGeom2<DH>;
@@ -474,7 +468,7 @@ __global__ __launch_bounds__(512) void k_attn_rep2(AttnParams p, Layers layers) 
 
     const int r = p.r_dev ? *p.r_dev : p.r_host;
     if (attn_status(p, r) != ADA_OK) return;               // k_attn_pos rejected the set or the assignment
-    const AttnWho who = attn_who<MANY>(p.H);
+    const AttnWho who = attn_who(p.H);
     const int h = who.h;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -484,7 +478,7 @@ __global__ __launch_bounds__(512) void k_attn_rep2(AttnParams p, Layers layers) 
     ATTN_CLK(0);
     const int nq = (r + 63) / 64;
     for (int b = who.qblk; b < nq; b += gridDim.x) {
-    const int q0 = attn_block<MANY>(b, nq, p.causal) * 64;
+    const int q0 = attn_block(b, nq, p.causal) * 64;
     __syncthreads();                                       // a previous query block's hand-over is done with the LDS
     const In* Qh = reinterpret_cast<const In*>(p.Q) + (size_t)h * DH;
     const In* Kh = reinterpret_cast<const In*>(p.K) + (size_t)h * DH;
