@@ -219,6 +219,13 @@ int ada_attention_compressed(const void* Q, const void* K, const void* V, int T,
  *   counts_all   device [L*4] int32   row l as in ada_cascade_step (layer 0: {r, r, 0, 0})
  *   gram_ops_all device [L]   uint64  layer 0: T*T
  *   adds_all / removes_all  device [L*T] int32 each, or NULL to skip reporting them
+ * Up to 64 layers at a time share six launches: which pairs of tokens are within the threshold of each other does not
+ * depend on the inherited set, so it is found for all of them at once (8-bit sketches of the rows and a bound exclude most
+ * pairs, full products decide the rest) and the sets follow from a walk over those pairs.  Layers with too many pairs near
+ * the threshold for a list run on the tiles of ada_cascade_step, with those behind them, in the last of these launches.
+ * One launch per layer: one small layer, d < 64, T > 16384, tau below about 0.03 (decided by products alone) or so
+ * large that a sketch excludes too little (from 0.4 to 0.7 on, depending on d), ADA_FLAG_TWO_PASS,
+ * ADA_FLAG_RESIDENT_PASS.  Same results.
  */
 int ada_cascade_layers(const void* const* X_layers, int L, int T, int d, int64_t ld, int dtype, float tau,
                        int32_t* idx_all, int32_t* counts_all, uint64_t* gram_ops_all,
@@ -227,9 +234,10 @@ int ada_cascade_layers(const void* const* X_layers, int L, int T, int d, int64_t
 
 /*
  * The same layer loop for B independent sequences at once (Section 8.4 suggests keeping selection work in flight next to other
- * work; here the selection work of several sequences is in flight together).  Sequence b runs exactly what ada_cascade_layers runs, on streams[b]; the
- * chains are issued layer by layer across the batch, so that while one sequence's set update runs on a single CU the
- * other sequences' tiles fill the rest of the device.
+ * work; here the selection work of several sequences is in flight together).  Sequence b runs exactly what
+ * ada_cascade_layers runs, on streams[b].  Where all layers of a sequence share their launches (see there) the sequences
+ * are issued one after the other; where every layer has its own, layer by layer across the batch, so that while one
+ * sequence's set update runs on a single CU the other sequences' tiles fill the rest of the device.
  *   X_layers     HOST array of B*L device pointers, sequence-major: X_layers[b*L + l]
  *   idx_all, counts_all, gram_ops_all, adds_all, removes_all   as for ada_cascade_layers, B blocks of L rows
  *   ws           B workspaces back to back, ada_workspace_bytes(T) apart, each initialised; ws_bytes >= B times that
@@ -287,7 +295,8 @@ int ada_select_full_grouped(const ada_groups* groups, const void* X, int T, int 
                             void* ws, size_t ws_bytes, void* stream, unsigned flags);
 
 /*
- * The layer loop for G groups: full selection of every group at layer 0, then one grouped cascade step per layer.
+ * The layer loop for G groups: full selection of every group at layer 0, Algorithm 1 at the others; all groups share the
+ * launches of ada_cascade_layers, or one grouped cascade step per layer.
  *   X_layers   HOST array of L device pointers (group 0's matrix of each layer)
  *   outputs    as for ada_cascade_layers_batched with B = G: idx_all [G][L][T], counts_all [G][L][4], ...
  * Only groups->G and groups->x_gstride are read (the other strides follow from the output layout).
@@ -298,10 +307,12 @@ int ada_cascade_layers_grouped(const ada_groups* groups, const void* const* X_la
                                void* ws, size_t ws_bytes, void* stream, unsigned flags);
 
 /*
- * Selection pipelined against attention (Section 8.4): for every layer l, the selection (full at layer 0,
- * Algorithm 1 afterwards) runs on stream_sel; the layer's nearest-representative assignment (Section 2.3) and
- * its attention on the representative set (eq. (1)) run on stream_attn and wait only for that layer's set.  The
- * selection of layer l+1 needs nothing from the attention of layer l, so the two overlap.
+ * Selection pipelined against attention (Section 8.4): the selection (full at layer 0, Algorithm 1 afterwards) needs
+ * nothing from the attention (eq. (1)).  Where layers share their launches (see ada_cascade_layers), they go in batches
+ * of up to 16: selection and nearest-representative assignment (Section 2.3) of a batch on stream_sel, its attention in
+ * one launch on stream_attn as soon as these are done, beside the selection of the next batch.  With 16 layers and
+ * fewer nothing is left to run side by side, and one stream saves the events between the two (about 35 us a call).
+ * Where every layer has launches of its own, assignment and attention run on stream_attn and wait for that layer's set.
  *   X_layers, Q_layers, K_layers, V_layers   HOST arrays of L device pointers: T x (H * d_h) matrices, leading
  *                dimension ld, dtype as usual; the alignment rules of ada_attention_compressed apply to Q, K, V
  *   idx_all, counts_all, gram_ops_all        as for ada_cascade_layers

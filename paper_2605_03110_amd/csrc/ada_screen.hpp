@@ -35,8 +35,8 @@ constexpr int SCREEN_MAX_LAYERS = 64;                         // layers per laun
 constexpr int SCREEN_TILE_PAIRS = 256;                        // unexplained candidates a 128 x 128 tile may hold before its layer is dense
 // Unexplained candidates per token from which on a layer is dense without looking at them: listing one takes two rows out of the
 // L2 (16 KB at d = 4096, 1.1 ns of the chip), a step on the tiles 27 us at T = 2048, 150 us at T = 8192.  All of them may turn
-// out to be edges, and the walk goes along edges at about 1 us per thousand: 28 layers of T=2048, d=4096 with 2.2 unexplained
-// candidates per token take 681 us on the graph and 1265 with one launch per layer.  A launch of many layers has room for
+// out to be edges, and the walk goes along edges at about 1.5 us per thousand: 28 layers of T=2048, d=4096 with 2.2 unexplained
+// candidates per token take 673 us on the graph and 1270 with one launch per layer.  A launch of many layers has room for
 // fewer edges, and then that is the line; screen_edges what it always has.
 constexpr int SCREEN_OPEN = 4;
 constexpr int screen_edges(int T) { return (T / 2 + 65) / 2 * 2; }
