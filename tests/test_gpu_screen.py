@@ -140,8 +140,8 @@ def test_stacked_sequences_that_need_different_treatment(kinds, T, d, dtype):
                                               ("loose", 1000, 1024, 2, "f32"), ("common", 300, 512, 3, "bf16"), ("signs", 260, 256, 2, "bf16"),
                                               ("outliers", 400, 1024, 2, "bf16")])
 def test_assignment_and_attention_on_the_graph_of_near_pairs(kind, T, d, L, dtype):
-    """The pipelined layers take every token's representative from clusters and edges: within 2e-4 of the float64
-    maximum, and the attention on it as for any assignment."""
+    """The pipelined layers take every token's representative from clusters and edges (loose ones from the tiles, where a token is
+    left that no representative covers): within 2e-4 of the float64 maximum, and the attention on it as for any assignment."""
     print("[case] screened pipeline: %s T=%d d=%d L=%d %s" % (kind, T, d, L, dtype), flush=True)
     H, tau = d // 64, 0.1
     xs_cpu = activations(kind, T, d, L, dtype, seed=3 * T + d)
