@@ -269,6 +269,27 @@ def test_batches_of_pipelined_layers_on_two_streams(L):
         assert all(torch.equal(a, b) for a, b in zip(got["out"], want["out"]))
 
 
+def test_dense_sequences_on_several_streams_at_once():
+    """Steps behind dense layers of several sequences share the chip: no launch has all its workgroups running."""
+    print("[case] dense sequences on streams", flush=True)
+    T, d, L, B, tau = 1500, 512, 5, 6, 0.1
+    seqs = [[x.to(DEV) for x in activations(k, T, d, L, "bf16", seed=40 + b)]
+            for b, k in enumerate(("common", "collapsed", "common", "clusters", "common", "loose"))]
+    want = [pa.ada_cascade_layers(s, tau) for s in seqs]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    ws = pa.workspace_batched(T, B, DEV)
+    for _ in range(5):
+        got = pa.ada_cascade_layers_batched(seqs, tau, ws=ws, streams=[streams[b % 3] for b in range(B)], want_lists=True)
+        torch.cuda.synchronize()
+        for b in range(B):
+            assert torch.equal(got["counts"][b], want[b]["counts"]) and torch.equal(got["gram_ops"][b], want[b]["gram_ops"])
+            for l in range(L):
+                for key, c in (("idx", 0), ("adds", 1), ("removes", 2)):
+                    n = int(want[b]["counts"][l, c]) if l or key == "idx" else 0
+                    assert torch.equal(got[key][b, l, :n], want[b][key][l, :n]), (b, l, key)
+
+
 @pytest.mark.parametrize("T", [8000, 8065, 12321, 16384])
 def test_assignment_of_long_sequences_in_unaligned_rows(T):
     """X starts on no 16 bytes (Q, K and V must, X need not): the register-staged tiles' workgroups keep two words per token

@@ -252,3 +252,11 @@ def test_build_reads_the_compilers_resource_report(ada):
     assert got["_ZN1x15k_cascade_fusedItLb1ELi2ELb1EEEv"] == {"TotalSGPRs": 104, "VGPRs": 239, "ScratchSize": 20}
     assert got["_ZN1x10k_gram_dmaILb1EEEv"] == {"VGPRs": 169, "ScratchSize": 0}
     assert all(isinstance(v, int) and v >= 0 for v in ada.SCRATCH_BUDGET.values())
+
+
+def test_the_part_of_a_workspace_that_must_be_zero(ada):
+    assert ada.ada_workspace_zero_bytes(0) == 0 and ada.ada_workspace_zero_bytes((1 << 20) + 1) == 0
+    for T in (1, 512, 2048, 16384, 16385, 1 << 20):
+        zero, all_ = ada.ada_workspace_zero_bytes(T), ada.workspace_bytes(T)
+        assert 0 < zero <= all_ and zero % 256 == 0
+        assert zero <= 30 * T + 8192                          # the scalars, and arrays of 25 bytes per token
