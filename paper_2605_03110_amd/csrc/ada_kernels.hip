@@ -1484,16 +1484,31 @@ void screen_room(ScreenParams& sp, const ScreenUnit& U, int layers) {
     sp.open = (uint32_t)std::min(SCREEN_OPEN * sp.T, sp.edge_cap);
 }
 
+// Whether the exact pass reads X past the caches: a read alone then runs at 7.0 instead of 6.4 TB/s and leaves the L2 to the
+// pivots, but neither a call on the same X nor one behind a kernel that has just written it finds any of it in the Infinity
+// Cache (256 MB).  Measured with two inputs in turns, us, cached -> streamed: 28 x T=2048, d=4096 (448 MB) 157 -> 143, 16
+// layers 102 -> 95, 12 layers (192 MB) 82 -> 79; 16 heads x 256, 8 layers (128 MB) 105.5 -> 105.1, one T=8192, d=4096 full selection (64 MB,
+// which reads X again) 88 -> 97, 12 x T=2048, d=768 (36 MB) 46.5 -> 48.4.  Rows that are not whole cache lines lose: a line that two
+// pieces share comes twice (32 x T=8192, d=1000: 450 -> 456).
+bool screen_streams(const ScreenParams& sp, size_t esz) {
+    size_t odd = (size_t)sp.ld * esz | (size_t)sp.d * esz | (sp.G > 1 ? (size_t)sp.x_gs : 0);
+    for (int l = 0; l < sp.L; ++l) odd |= (size_t)(uintptr_t)sp.X[l];
+    return odd % 128 == 0 && (double)sp.G * sp.L * sp.T * sp.d * esz >= 192.0 * (1 << 20);
+}
+
 template <typename In, int LPR>
 hipError_t launch_screen_exact(const ScreenParams& sp, hipStream_t st) {
-    // four rows per lane group where that leaves enough workgroups to fill the chip, one where it does not
+    // two rows per lane group where that leaves enough workgroups to fill the chip, one where it does not
     const int rows = 256 / LPR, units = sp.G * sp.L;
-    const int passes = (long long)(sp.T / (4 * rows)) * units >= 2048 ? 4 : 1;
+    const int passes = (long long)(sp.T / (4 * rows)) * units >= 2048 ? 2 : 1;
     const int rb = (sp.T + rows * passes - 1) / (rows * passes), total = rb * units;
     const dim3 grid((unsigned)((total + 7) / 8 * 8));
     ProfScope ps(ADA_K_SCREEN, st);
-    if (passes == 4) hipLaunchKernelGGL((k_screen_exact<In, LPR, 4>), grid, dim3(256), 0, st, sp, rb, total);
-    else hipLaunchKernelGGL((k_screen_exact<In, LPR, 1>), grid, dim3(256), 0, st, sp, rb, total);
+    const bool stream = screen_streams(sp, sizeof(In));
+    if (passes == 2 && stream) hipLaunchKernelGGL((k_screen_exact<In, LPR, 2, true>), grid, dim3(256), 0, st, sp, rb, total);
+    else if (passes == 2) hipLaunchKernelGGL((k_screen_exact<In, LPR, 2, false>), grid, dim3(256), 0, st, sp, rb, total);
+    else if (stream) hipLaunchKernelGGL((k_screen_exact<In, LPR, 1, true>), grid, dim3(256), 0, st, sp, rb, total);
+    else hipLaunchKernelGGL((k_screen_exact<In, LPR, 1, false>), grid, dim3(256), 0, st, sp, rb, total);
     return hipGetLastError();
 }
 

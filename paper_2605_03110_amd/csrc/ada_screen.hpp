@@ -490,8 +490,8 @@ template <> __device__ inline float screen_dot<uint16_t>(u32x4 a, u32x4 b, float
 
 // <x, y>, <x, x> and <y, y> by LPR neighbouring lanes (li: this lane's place among them); every lane gets the sums.
 // Four pieces of each row are requested before the first is used (eight leave fewer waves room: 465 us instead of 444 at
-// 32 units of T = 8192, d = 4096).
-template <typename In, int LPR>
+// 32 units of T = 8192, d = 4096).  STREAM: x is read once and not kept in the caches.
+template <typename In, int LPR, bool STREAM = false>
 __device__ inline void screen_products(const In* x, const In* y, bool two, int d, int li, float* xy, float* xx, float* yy) {
     constexpr int EPP = 16 / (int)sizeof(In), UN = 4;
     const int np = (d + EPP - 1) / EPP;
@@ -501,7 +501,9 @@ __device__ inline void screen_products(const In* x, const In* y, bool two, int d
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
             const int e = min(min(p0 + u * LPR, np - 1) * EPP, d - EPP);
-            a[u] = *reinterpret_cast<const u32x4_any*>(x + e);
+            const auto* piece = reinterpret_cast<const u32x4_any*>(x + e);
+            if constexpr (STREAM) a[u] = __builtin_nontemporal_load(piece);
+            else a[u] = *piece;
         }
         if (two) {
 #pragma unroll
@@ -560,7 +562,11 @@ __device__ inline bool screen_crowded(const ScreenParams& p, const char* unit) {
 // once, and the places that the cluster sizes hand back are summed after the last row: a row waits for X alone.
 // A unit whose candidates are a quarter of all pairs and more is left alone, for k_screen_rest to call dense: its rows share
 // a direction (or a few columns), which the sketch cannot tell from being near.
-template <typename In, int LPR, int PASSES>
+// Two rows per lane group: the rows in flight on an XCD (256 workgroups of 8 at d = 4096) then stay about within one unit, whose
+// pivots its L2 can hold; four rows spread over two units (STREAM, 28 x T=2048, d=4096: call 150 us against 143; 32 x T=8192:
+// 632 against 619), one row starts more workgroups (145, 619).
+// STREAM: see screen_streams.
+template <typename In, int LPR, int PASSES, bool STREAM>
 __global__ __launch_bounds__(256) void k_screen_exact(ScreenParams p, int row_blocks, int total) {
     __shared__ uint32_t s_pairs, s_flags;
     const int per = (total + 7) >> 3;
@@ -597,7 +603,7 @@ __global__ __launch_bounds__(256) void k_screen_exact(ScreenParams p, int row_bl
         const int t = t0 + k * (256 / LPR);
         if (t < p.T) {
             float xy, xx, yy;
-            screen_products<In, LPR>(X + (size_t)t * (size_t)p.ld, X + (size_t)q[k] * (size_t)p.ld, q[k] != t, p.d, li, &xy, &xx, &yy);
+            screen_products<In, LPR, STREAM>(X + (size_t)t * (size_t)p.ld, X + (size_t)q[k] * (size_t)p.ld, q[k] != t, p.d, li, &xy, &xx, &yy);
             if (li == 0) {
                 const float r2 = xx > 0.f ? ss[k] / xx : 1.f;     // (a zero row has no cosines: nothing to bound)
                 rho[t] = r2;
