@@ -1470,7 +1470,7 @@ ScreenParams screen_params(const ScreenPlan& plan, const Workspace& w, int T, in
     sp.meta = w.meta;
     sp.nch = plan.nch;
     sp.nk = (d + 63) / 64;
-    sp.kap = plan.kappa * SCREEN_SCALE * SCREEN_SCALE;
+    sp.scale = (float)sqrt(2.0 / ((double)plan.kappa * pow(2.0, SCREEN_EXP)));
     sp.kap1 = plan.kappa + (float)SCREEN_EPS;
     sp.f2 = plan.f2; sp.safe = plan.safe; sp.thr = threshold_of(tau); sp.cos_tight = plan.cos_tight;
     return sp;
@@ -1524,6 +1524,11 @@ hipError_t launch_screen_rest(const ScreenParams& sp, hipStream_t st) {
     return hipGetLastError();
 }
 
+template <int NCH, int TB>
+void launch_screen_pairs(const ScreenParams& sp, const PairItems& it, dim3 grid, int total, hipStream_t st) {
+    hipLaunchKernelGGL((k_screen_pairs<NCH, TB>), grid, dim3(256), 0, st, sp, it, total);
+}
+
 // The graph of near pairs of every unit of sp.
 template <typename In>
 hipError_t launch_screen(const ScreenParams& sp, hipStream_t st) {
@@ -1538,12 +1543,13 @@ hipError_t launch_screen(const ScreenParams& sp, hipStream_t st) {
         const int total = it.per_unit * units;
         const dim3 grid((unsigned)((total + 7) / 8 * 8));
         ProfScope ps(ADA_K_SCREEN, st);
+        const bool whole = it.cut == 1;                       // (short pieces: two blocks per wave start up sooner)
         switch (sp.nch) {
-            case 1: hipLaunchKernelGGL(k_screen_pairs<1>, grid, dim3(256), 0, st, sp, it, total); break;
-            case 2: hipLaunchKernelGGL(k_screen_pairs<2>, grid, dim3(256), 0, st, sp, it, total); break;
-            case 3: hipLaunchKernelGGL(k_screen_pairs<3>, grid, dim3(256), 0, st, sp, it, total); break;
-            case 4: hipLaunchKernelGGL(k_screen_pairs<4>, grid, dim3(256), 0, st, sp, it, total); break;
-            default: hipLaunchKernelGGL(k_screen_pairs<0>, grid, dim3(256), 0, st, sp, it, total);
+            case 1: launch_screen_pairs<1, 4>(sp, it, grid, total, st); break;
+            case 2: launch_screen_pairs<2, 4>(sp, it, grid, total, st); break;
+            case 3: whole ? launch_screen_pairs<3, 4>(sp, it, grid, total, st) : launch_screen_pairs<3, 2>(sp, it, grid, total, st); break;
+            case 4: launch_screen_pairs<4, 2>(sp, it, grid, total, st); break;
+            default: launch_screen_pairs<0, 4>(sp, it, grid, total, st);
         }
     }
     // four pieces of a row in flight per lane, at least eight lanes (a cache line) side by side

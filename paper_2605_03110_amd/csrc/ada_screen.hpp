@@ -41,7 +41,9 @@ constexpr int SCREEN_TILE_PAIRS = 256;                        // unexplained can
 constexpr int SCREEN_OPEN = 4;
 constexpr int screen_edges(int T) { return (T / 2 + 65) / 2 * 2; }
 constexpr int CHAIN_LDS = 160 * 1024 - 2048;                  // what the walk may use of a CU's LDS
-constexpr float SCREEN_SCALE = 256.f;                         // sketches are stored as 8-bit floats of 256 x (unit vector)
+// Sketches are stored as 8-bit floats of scale x (unit vector), the products multiplied by a power of two so that the
+// accumulators hold 2 c / kappa: scale^2 = 2 / (kappa 2^SCREEN_EXP), below the formats' largest 448 for every kappa >= 0.3.
+constexpr int SCREEN_EXP = -14;
 
 // header of a unit (one layer of one sequence); zeroed by the sketch launch
 enum { SU_EDGES = 3, SU_DENSE = 4, SU_CAND = 32, SU_PART = SU_CAND + 8 * 32, SU_WORDS = SU_PART + 8 * 32 };
@@ -147,7 +149,7 @@ struct ScreenParams {
     int32_t* meta;             // sequence 0's scalars (likewise area_gs apart)
     int first;                 // layer number of the launch's first layer
     int nch, nk;
-    float kap, kap1;           // candidate threshold on the raw accumulator; kappa with the rounding allowance
+    float scale, kap1;         // of the stored sketches; kappa with the rounding allowance
     float f2, safe, thr, cos_tight;
     uint32_t open;             // unexplained candidates of a unit above which it is dense
     int edge_cap;              // see ScreenUnit
@@ -234,7 +236,7 @@ __global__ __launch_bounds__(256) void k_screen_sketch(ScreenParams p, int row_b
     ss += __shfl_xor(ss, 1, 64);
     ss += __shfl_xor(ss, 2, 64);
     ss += __shfl_xor(ss, 4, 64);
-    const float sc = ss > 0.f ? SCREEN_SCALE / sqrtf(ss) : 0.f;
+    const float sc = ss > 0.f ? p.scale / sqrtf(ss) : 0.f;
     if (t >= p.T) return;
     uint8_t* z = reinterpret_cast<uint8_t*>(base + U.o_z) + (size_t)(t >> 5) * (size_t)(2048 * p.nch) +
                  ((c8 >> 1) & 1) * 1024 + ((c8 >> 2) * 32 + (t & 31)) * 16 + (c8 & 1) * 8;
@@ -270,8 +272,9 @@ __device__ inline i32x8 screen_operand(const u32x4* z) {      // this lane's 32 
     return i32x8{(int)a[0], (int)a[1], (int)a[2], (int)a[3], (int)b[0], (int)b[1], (int)b[2], (int)b[3]};
 }
 __device__ inline void screen_mma(f32x16& acc, const i32x8& a, const i32x8& b) {
-    // (formats 0: e4m3 on both sides; block scales 127 = 1)
-    acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc, 0, 0, 0, 0x7F7F7F7F, 0, 0x7F7F7F7F);
+    // (formats 0: e4m3 on both sides; block scale 127 + n: 2^n)
+    constexpr int scale = (127 + SCREEN_EXP / 2) * 0x01010101;
+    acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc, 0, 0, 0, scale, 0, scale);
 }
 
 // lower-triangular block number -> blocks 0 <= sb <= tb
@@ -283,16 +286,23 @@ __device__ inline void screen_blocks(int tile, int* sb, int* tb) {
     *sb = tile - n * (n + 1) / 2;
 }
 
-// The candidates of a 32 x 32 block, shifted into `bits` from the right: register i of the accumulator holds a row that
-// grows with i, so of what is shifted in the highest bit is the earliest row.  Two instructions per product (the sign of
-// kappa - |product|), no branches and no condition registers: at the redundancy this method is for, nearly every block
-// holds a candidate.
-__device__ inline uint32_t screen_bits(uint32_t bits, const f32x16& acc, float kap) {
+// The candidates of a 32 x 32 block: sketches and block scales are such that an accumulator holds 2 c / kappa, so a candidate
+// is an accumulator whose exponent has its top bit set (bit 30).  One instruction per product: it shifts that bit and the
+// sign in from the right; the caller masks the signs away (SCREEN_BITS).  Register i lands in bit 30 - 2 i and holds a row that
+// grows with i, so the highest bit is the earliest row.
+constexpr uint32_t SCREEN_BITS = 0x55555555u;
+__device__ inline uint32_t screen_bits(const f32x16& acc) {
+    uint32_t bits = 0u;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(kap - fabsf(acc[i])), 31u);
+    for (int i = 0; i < 16; ++i) bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(acc[i]), 30u);
     return bits;
 }
 __device__ inline int screen_row(int i) { return (i & 3) + 8 * ((i >> 2) & 3); }   // row of register i (lanes of the first half)
+__device__ inline uint32_t screen_first(uint32_t bits) {      // position of the highest bit from the left; all ones if there is none
+    uint32_t r;
+    asm("v_ffbh_u32 %0, %1" : "=v"(r) : "v"(bits));
+    return r;
+}
 
 // Work items of a unit: strips of 256 tokens, each against its earlier tokens in pieces.  A piece is 256 x `wide` tokens, or
 // 256 / `cut` of them: long pieces spend less of their time on starting up (a piece of 256 took about half of it for
@@ -329,14 +339,21 @@ struct PairItems {
 };
 
 // k_screen_pairs: every token's earliest candidate, and how many candidate pairs there are.  A workgroup holds 256 tokens
-// (64 per wave: two 32-row blocks) and walks over blocks of 32 earlier tokens; a wave keeps its tokens' sketches in
-// registers (NCH > 0) and reads the earlier tokens' one block ahead.  Its four waves read the same blocks at about the
-// same time, so they come from the L1; there is nothing to stage and no barrier.  The work of one unit is dealt to one
-// XCD (workgroup b runs on XCD b % 8), so that its sketches are read by one L2.
+// and walks over blocks of 32 earlier tokens; a wave keeps TB blocks of tokens in registers and reads the earlier tokens'
+// sketches once for all of them, a block ahead.  Waves that read the same blocks do so at about the same time, so they come
+// from the L1; there is nothing to stage and no barrier.  TB = 4: two waves share the tokens, and the other two take the
+// second half of the earlier tokens; TB = 2: four waves share the tokens.  The work of one unit is dealt to one XCD
+// (workgroup b runs on XCD b % 8), so that its sketches are read by one L2.
+// Bound by power: 32 x T=8192 with three column groups keep the 8-bit MFMA busy for 65% of 305 thousand cycles, at 1.7 GHz.
+// Calls, us, with two blocks per wave, two instructions per product and two sets of operands (before) and now: 4 x 8 x T=8192,
+// d=4096 619 -> 596, 128 x T=2048, d=256 105 -> 99, 12 x T=2048, d=768 46.7 -> 45.3.  Slower: sketches by way of LDS (607), two
+// waves per SIMD with the operands a whole step ahead (616).
 // NCH: column groups of the sketch (1 .. 4), or 0: any number, both operands read as they are used.
 // (the second launch bound keeps the accumulators in ordinary registers: the epilogue reads each of them once)
-template <int NCH>
-__global__ __launch_bounds__(256, NCH == 4 ? 2 : 3) void k_screen_pairs(ScreenParams p, PairItems it, int total) {
+constexpr int screen_pair_waves(int nch, int tb) { return nch == 1 ? 5 : nch == 2 && tb == 4 ? 4 : 3; }
+template <int NCH, int TB>
+__global__ __launch_bounds__(256, screen_pair_waves(NCH, TB)) void k_screen_pairs(ScreenParams p, PairItems it, int total) {
+    constexpr int HELD = NCH > 0 ? NCH : 1, ACC = NCH > 0 ? 2 : TB;
     __shared__ int s_cand;
     const int per = (total + 7) >> 3;
     const int w = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
@@ -348,91 +365,91 @@ __global__ __launch_bounds__(256, NCH == 4 ? 2 : 3) void k_screen_pairs(ScreenPa
     it.get(w - unit * it.per_unit, &tb, &s_lo, &sblk);
     if (threadIdx.x == 0) s_cand = 0;
     __syncthreads();
-    const int T = p.T, nch = NCH > 0 ? NCH : p.nch;
+    const int T = p.T, nch = NCH > 0 ? NCH : p.nch, nblk = (T + 31) >> 5;
     const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int nblk = (T + 31) >> 5;
-    const int tb0 = tb * 8 + wave * 2;                        // this wave's first row block
-    const int s_hi = min(s_lo + sblk, min(tb0 + 2, nblk));
-    const u32x4* Z = reinterpret_cast<const u32x4*>(base + U.o_z) + lane;     // a (block, group) is 128 of these
-    int cand[2] = {0, 0}, piv[2] = {INT_MAX, INT_MAX};
-    if (tb0 < nblk && s_lo < s_hi) {
-        constexpr int HELD = NCH > 0 ? NCH : 1;
-        i32x8 fb[2][HELD], fa[2][HELD];
-        const int tb1 = min(tb0 + 1, nblk - 1);
+    const int tb0 = tb * 8 + (TB == 4 ? (wave & 1) * 4 : wave * 2);           // this wave's first row block
+    const int mid = TB == 4 ? s_lo + (sblk >> 1) : s_lo;
+    int s = TB == 4 && wave >> 1 ? mid : s_lo;
+    const int s_hi = min(TB == 4 && !(wave >> 1) ? mid : s_lo + sblk, min(tb0 + TB, nblk));
+    const char* zb = base + U.o_z;                            // a (block, group) is 2 KB
+    const uint32_t l16 = (uint32_t)lane * 16u;
+    auto operand = [&](int n) { return screen_operand(reinterpret_cast<const u32x4*>(zb + (size_t)n * 2048 + l16)); };
+    if (tb0 < nblk && s < s_hi) {
+        i32x8 fb[TB][HELD], fa[HELD];
+        uint32_t first[TB];                                   // block and bit of the earliest candidate: 32 s + position
+        int cand = 0;
         auto rd = [&](i32x8 (&f)[HELD], int blk) {
             if constexpr (NCH > 0) {
 #pragma unroll
-                for (int j = 0; j < NCH; ++j) f[j] = screen_operand(Z + (size_t)(blk * NCH + j) * 128);
+                for (int j = 0; j < NCH; ++j) f[j] = operand(blk * NCH + j);
             }
         };
-        rd(fb[0], tb0);
-        rd(fb[1], tb1);
-        rd(fa[0], s_lo);
-        uint32_t bits[2];
-        auto block = [&](int set, int s) {                    // earlier tokens of block s, in set
-            if constexpr (NCH > 0) rd(fa[set ^ 1], min(s + 1, s_hi - 1));
-            f32x16 acc[2];
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < TB; ++b) {
+            first[b] = 0xFFFFFFFFu;
+            rd(fb[b], min(tb0 + b, nblk - 1));
+        }
+        rd(fa, s);
+        if constexpr (NCH > 0) {
+            if ((tb0 + TB) * 32 > T) {                        // tokens that do not exist have no candidates
 #pragma unroll
-                for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
-            if constexpr (NCH > 0) {
+                for (int b = 0; b < TB; ++b)
+                    if ((tb0 + b) * 32 + l32 >= T) {
 #pragma unroll
-                for (int j = 0; j < NCH; ++j)
+                        for (int j = 0; j < NCH; ++j) fb[b][j] = i32x8{0, 0, 0, 0, 0, 0, 0, 0};
+                    }
+            }
+        }
+        uint32_t earlier = 0u;                                // on the diagonal: rows before this lane's
 #pragma unroll
-                    for (int b = 0; b < 2; ++b) screen_mma(acc[b], fa[set][j], fb[b][j]);
-            } else {
-                for (int j = 0; j < nch; ++j) {
-                    const i32x8 a = screen_operand(Z + (size_t)(s * nch + j) * 128);
-                    const i32x8 b0 = screen_operand(Z + (size_t)(tb0 * nch + j) * 128), b1 = screen_operand(Z + (size_t)(tb1 * nch + j) * 128);
-                    screen_mma(acc[0], a, b0);
-                    screen_mma(acc[1], a, b1);
+        for (int i = 0; i < 16; ++i) earlier |= 4 * half + screen_row(i) < l32 ? 0x40000000u >> (2 * i) : 0u;
+        auto block = [&](int s, bool diag) {
+#pragma unroll
+            for (int b0 = 0; b0 < TB; b0 += ACC) {
+                f32x16 acc[ACC];
+#pragma unroll
+                for (int b = 0; b < ACC; ++b)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
+                if constexpr (NCH > 0) {
+#pragma unroll
+                    for (int j = 0; j < NCH; ++j)
+#pragma unroll
+                        for (int b = 0; b < ACC; ++b) screen_mma(acc[b], fa[j], fb[b0 + b][j]);
+                    if (b0 + ACC == TB) {                     // the next block's operands, where the last product has taken this one's
+                        __builtin_amdgcn_sched_barrier(0);
+                        rd(fa, min(s + 1, s_hi - 1));
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                } else {
+                    for (int j = 0; j < nch; ++j) {
+                        const i32x8 a = operand(s * nch + j);
+#pragma unroll
+                        for (int b = 0; b < ACC; ++b) screen_mma(acc[b], a, operand(min(tb0 + b, nblk - 1) * nch + j));
+                    }
+                }
+#pragma unroll
+                for (int b = 0; b < ACC; ++b) {
+                    uint32_t v = screen_bits(acc[b]) & (!diag || s < tb0 + b0 + b ? SCREEN_BITS : s == tb0 + b0 + b ? earlier : 0u);
+                    if (NCH == 0 && (tb0 + b0 + b) * 32 + l32 >= T) v = 0u;
+                    cand += __popc(v);
+                    first[b0 + b] = min(first[b0 + b], screen_first(v) | (uint32_t)s << 5);
                 }
             }
-#pragma unroll
-            for (int b = 0; b < 2; ++b) bits[b] = screen_bits(bits[b], acc[b], p.kap);
         };
-        // what blocks s and s + 1 (upper and lower half of a word) hold; diag: rows that are not earlier have to be taken out
-        auto take = [&](int s, bool diag) {
+        for (; s < min(s_hi, tb0); ++s) block(s, false);     // whole blocks of earlier tokens
+        for (; s < s_hi; ++s) block(s, true);
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const int row0 = s * 32 + 4 * half, t = (tb0 + b) * 32 + l32;
-                uint32_t v = bits[b];
-                if (diag) {
-#pragma unroll
-                    for (int i = 0; i < 32; ++i) v &= row0 + (i >> 4) * 32 + screen_row(i) < t ? 0xFFFFFFFFu : ~(0x80000000u >> i);
-                }
-                cand[b] += __popc(v);
-                const int i = __clz((int)v);
-                piv[b] = min(piv[b], v ? row0 + (i >> 4) * 32 + screen_row(i) : INT_MAX);
-            }
-        };
-        int s = s_lo;
-        for (; s + 1 < min(s_hi, tb0); s += 2) {              // whole blocks of earlier tokens
-            bits[0] = bits[1] = 0u;
-            block(0, s);
-            block(1, s + 1);
-            take(s, false);
-        }
-        for (; s < s_hi; s += 2) {                            // the last one or two, on the diagonal or not
-            bits[0] = bits[1] = 0u;
-            block(0, s);
-            if (s + 1 < s_hi) block(1, s + 1);
-            else { bits[0] <<= 16; bits[1] <<= 16; }
-            take(s, true);
-        }
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
+        for (int b = 0; b < TB; ++b) {
             const int t = (tb0 + b) * 32 + l32;
-            const int q = min(piv[b], __shfl_xor(piv[b], 32, 64));
+            const int i = (int)(first[b] & 31u) >> 1, row = (int)(first[b] >> 5) * 32 + 4 * half + screen_row(i);
+            const int mine = first[b] == 0xFFFFFFFFu ? INT_MAX : row, q = min(mine, __shfl_xor(mine, 32, 64));
             if (half == 0 && t < T && q != INT_MAX) atomicMin(reinterpret_cast<int32_t*>(base + U.o_piv) + t, q);
-            if (t >= T) cand[b] = 0;                          // (rows of the last block that do not exist)
         }
-        int n = cand[0] + (tb0 + 1 < nblk ? cand[1] : 0);
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
-        if (lane == 0 && n) atomicAdd(&s_cand, n);
+        for (int o = 32; o > 0; o >>= 1) cand += __shfl_xor(cand, o, 64);
+        if (lane == 0 && cand) atomicAdd(&s_cand, cand);
     }
     __syncthreads();
     if (threadIdx.x == 0 && s_cand)
@@ -683,23 +700,22 @@ __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) 
                 const int tl = me.t0 - tb * 128 + b * 32 + l32, t = tb * 128 + tl;
                 const int ct = s_cl[128 + tl];
                 auto row = [&](int i) { return me.s0 - sb * 128 + (i >> 4) * 32 + 4 * half + screen_row(i); };
-                uint32_t near = 0u;                       // bit 31 - i: register i of the two blocks' 32
+                uint64_t near = 0u;                       // bit 62 - 2 i: register i of the two blocks' 32
                 if (!low) {
-#pragma unroll
-                    for (int a = 0; a < 2; ++a) near = screen_bits(near, acc[a][b], p.kap);
+                    near = (uint64_t)(screen_bits(acc[0][b]) & SCREEN_BITS) << 32 | (screen_bits(acc[1][b]) & SCREEN_BITS);
                 } else {                                  // some row holds little in its sketch: the pair's own bound
                     const float rt = s_rho[128 + tl];
 #pragma unroll
                     for (int i = 0; i < 32; ++i) {
                         const float rs = s_rho[row(i)];
-                        if (fabsf(acc[i >> 4][b][i & 15]) > p.kap ||
-                            p.kap1 * sqrtf(rs * rt) + sqrtf((1.f - rs) * (1.f - rt)) + 1e-5f >= p.safe) near |= 0x80000000u >> i;
+                        if (fabsf(acc[i >> 4][b][i & 15]) >= 2.f ||
+                            p.kap1 * sqrtf(rs * rt) + sqrtf((1.f - rs) * (1.f - rt)) + 1e-5f >= p.safe) near |= 1ull << (62 - 2 * i);
                     }
                 }
                 while (__builtin_amdgcn_ballot_w64(near != 0u) != 0ull)
                     if (near != 0u) {
-                        const int i = __clz((int)near), sl = row(i), s = sb * 128 + sl;
-                        near &= ~(0x80000000u >> i);
+                        const int i = __clzll((long long)near) >> 1, sl = row(i), s = sb * 128 + sl;
+                        near &= ~(1ull << (62 - 2 * i));
                         if (s < t && t < p.T && s_cl[sl] != ct) {
                             const int n = atomicAdd(&s_n, 1);
                             if (n < SCREEN_TILE_PAIRS) s_pair[n] = (uint32_t)s << 16 | (uint32_t)t;
