@@ -88,12 +88,14 @@ struct FusedParams {
     // cascade step with a gamma output: Algorithm 1's gamma^cross is the maximum over the VALID representatives, which are
     // known only after all products.  The tiles therefore keep, per token, the arg max over all inherited
     // representatives that count for it (p.best, keyed by list position); the workgroup that updates the set lists the tokens
-    // whose nearest representative was removed (fix_list), clears their gamma and leaves the list's length, the set size
-    // and a status in the workspace's scalars (fix_meta: META_NONREP, META_R, META_STATUS) for the launch that recomputes
-    // those tokens' maxima against the valid representatives: the cross-Gram tiles of the step's other form, on that list.
+    // whose nearest representative was removed (fix_list [T]: from the front those that a valid representative hits, with the
+    // position of their earliest hit in the upper half; from the back the others), clears their gamma and leaves both
+    // lengths, the set size and a status in the workspace's scalars (fix_meta: META_FIX, META_NONREP, META_R, META_STATUS) and
+    // the validity bits by list position (fix_valid) for the launch that recomputes those tokens' maxima (k_gamma_fix).
     // inv_norm: the tiles against the first representatives leave the tested tokens' 1/norm for that launch.
     int32_t* fix_list;
     int32_t* fix_meta;
+    uint32_t* fix_valid;
     float* inv_norm;
 };
 
@@ -1269,25 +1271,27 @@ __device__ inline void block_rank3(const bool (&f)[3][U], int (&below)[3], int (
 // gamma for callers that ask for it: unpack the tiles' keys (the table is zero between calls, so they are cleared on the
 // way), and, once validity is known (vmask: one bit per list position), list the non-inherited tokens whose nearest
 // inherited representative was removed -- their maximum over the VALID representatives (step 8) is not the one the tiles
-// accumulated -- and clear their gamma for the recomputation.  inherited(t): the token is on the list.  ok == false: a
-// rejected step, gamma is cleared and the list is empty.
-template <int THREADS, typename Inherited>
-__device__ inline void gamma_fix_collect(const FusedParams& p, int r, const uint32_t* vmask, bool ok, Inherited inherited) {
+// accumulated -- and clear their gamma for the recomputation.  hit(t): list position of the token's earliest hit, HIT_NONE
+// if it has none (or it is not known), HIT_INHERITED if the token is on the list.  ok == false: a rejected step, gamma is
+// cleared and the lists are empty.
+enum { HIT_NONE = -1, HIT_INHERITED = -2 };
+template <int THREADS, typename Hit>
+__device__ inline void gamma_fix_collect(const FusedParams& p, int r, const uint32_t* vmask, bool ok, Hit hit) {
     if (!p.fix_list) return;                             // uniform
-    __shared__ int s_fix;
+    __shared__ int s_fix, s_far;
     const int tid = step_tid(p);
-    if (tid == 0) s_fix = 0;
+    if (tid == 0) s_fix = s_far = 0;
     __syncthreads();
+    auto valid = [&](int pos) { return (vmask[pos >> 5] >> (pos & 31)) & 1u; };
     auto one = [&](int t, unsigned long long key) {
         if (t >= p.T) return;
         if (key != 0ull) p.best[t] = 0ull;
         float m = ok ? __uint_as_float((uint32_t)(key >> 32)) : 0.f;
-        if (ok && key != 0ull && !inherited(t)) {
-            const int pos = min(max(INT_MAX - (int)(uint32_t)key, 0), r - 1);
-            if (!((vmask[pos >> 5] >> (pos & 31)) & 1u)) {
-                p.fix_list[atomicAdd(&s_fix, 1)] = t;
-                m = 0.f;                                 // empty max: the recomputation accumulates into it
-            }
+        const int h = ok && key != 0ull ? hit(t) : HIT_INHERITED;
+        if (h != HIT_INHERITED && !valid(min(max(INT_MAX - (int)(uint32_t)key, 0), r - 1))) {
+            if (h != HIT_NONE && valid(h)) p.fix_list[atomicAdd(&s_fix, 1)] = t | h << 16;
+            else p.fix_list[p.T - 1 - atomicAdd(&s_far, 1)] = t;
+            m = 0.f;                                     // empty max: the recomputation accumulates into it
         }
         p.gamma[t] = m;
     };
@@ -1300,10 +1304,13 @@ __device__ inline void gamma_fix_collect(const FusedParams& p, int r, const uint
         one(t2, k2);
         one(t3, k3);
     }
+    if (ok)
+        for (int w = tid; w < (r + 31) >> 5; w += THREADS) p.fix_valid[w] = vmask[w];
     __syncthreads();
     if (tid == 0) {
         p.fix_meta[META_R] = ok ? r : 0;
-        p.fix_meta[META_NONREP] = s_fix;
+        p.fix_meta[META_NONREP] = s_far;
+        p.fix_meta[META_FIX] = s_fix;
         p.fix_meta[META_STATUS] = ADA_OK;
     }
 }
@@ -1353,7 +1360,7 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
     }
     ok = __syncthreads_and(ok);
     if (!ok) {
-        gamma_fix_collect<THREADS>(p, r, vmask, false, [](int) { return false; });
+        gamma_fix_collect<THREADS>(p, r, vmask, false, [](int) { return (int)HIT_NONE; });
         if (tid == 0) {
             p.counts[0] = 0; p.counts[1] = 0; p.counts[2] = 0; p.counts[3] = ADA_ERR_INDEX;
             if (p.gram_ops) *p.gram_ops = 0ull;
@@ -1374,10 +1381,16 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
             const int j = (int)((pk >> (16 * u)) & 0xFFFFu);
             jpos[4 * v + u] = j;
             if (j != 0xFFFF && key[v][u] == 0u) atomicOr(&vmask[j >> 5], 1u << (j & 31));
+            // (gamma output: a token's earliest hit, marked by the top bit, where an inherited token has its place)
+            if (p.fix_list && j == 0xFFFF && key[v][u] != 0u)
+                pos[4 * t4 + u] = (uint16_t)(0x8000u | min(0xFFFFFFFFu - key[v][u], (uint32_t)(r - 1)));
         }
     }
     __syncthreads();
-    gamma_fix_collect<THREADS>(p, r, vmask, true, [&](int t) { return pos[t] != 0xFFFF; });   // (gamma output only)
+    gamma_fix_collect<THREADS>(p, r, vmask, true, [&](int t) {                               // (gamma output only)
+        const int j = pos[t];
+        return j == 0xFFFF ? (int)HIT_NONE : j & 0x8000 ? j & 0x7FFF : (int)HIT_INHERITED;
+    });
     // step 9: any other token with a hit on a VALID representative is covered
     bool f[3][U];                                        // in R^(l+1) | added | removed
 #pragma unroll
@@ -1432,7 +1445,7 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
 
 // Returns |R^(l+1)| to every thread (0 if the step is rejected).
 template <int THREADS>
-__device__ inline int fused_update(const FusedParams& p, int r, bool r_ok, int q0, int qp0, char* lds, int* scan_scratch) {
+__device__ __forceinline__ int fused_update(const FusedParams& p, int r, bool r_ok, int q0, int qp0, char* lds, int* scan_scratch) {
     constexpr int WU = 11;                              // hit words fetched per batch by one thread (22, 33, ... words: whole batches)
     const int tid = step_tid(p), lane = tid & 63;
     const int T = p.T;
@@ -1502,7 +1515,7 @@ __device__ inline int fused_update(const FusedParams& p, int r, bool r_ok, int q
     }
     ok = __syncthreads_and(ok);
     const int status = !r_ok ? ADA_ERR_SHAPE : (!ok ? ADA_ERR_INDEX : ADA_OK);
-    gamma_fix_collect<THREADS>(p, r, vmask, status == ADA_OK, [&](int t) { return (flag[t] & 1) != 0; });   // (gamma output only)
+    gamma_fix_collect<THREADS>(p, r, vmask, status == ADA_OK, [&](int t) { return (int)(flag[t] & 1 ? HIT_INHERITED : HIT_NONE); });   // (gamma output only)
     if (status != ADA_OK) {
         if (tid == 0) {
             p.counts[0] = 0; p.counts[1] = 0; p.counts[2] = 0; p.counts[3] = status;

@@ -47,7 +47,7 @@ enum { META_R = 0, META_NONREP = 1, META_STATUS = 2, META_GATE = 3 /* k_screen_s
        // screened selection: layers done so far; hand-over word, sign-off counter and claim words (one per XCD, in the lines of the
        // ticket counters) of k_cascade_rest, zero between calls
        META_PROGRESS = 8, META_REST_EPOCH = 10, META_REST_LEFT = 11,
-       META_ALONE = 12 /* and 13: layers of a launch whose assignment the graph leaves open, one bit each */, META_WORDS = 14,
+       META_ALONE = 12 /* and 13: layers of a launch whose assignment the graph leaves open, one bit each */, META_FIX = 14, META_WORDS = 15,
        META_REST_CLAIM = META_TICKET + 64 + 8 /* and 32, 64 .. 224 further on */ };
 static_assert((META_REST_CLAIM + 7 * 32 + 1) * 4 <= META_BYTES, "claim words");
 
@@ -1336,11 +1336,110 @@ int launch_fused_any(const FusedParams& p, int dtype, int prof_class, hipStream_
     return e == hipSuccess ? ADA_OK : ADA_ERR_DEVICE;
 }
 
+// gamma^cross of the tokens whose nearest inherited representative was removed (gamma_fix_collect's lists).
+//   near  tokens that a valid representative hits: any other is further away than those, so the maximum lies among the hits that
+//         the step's tiles left as bits, one as a rule.  One wave per token.
+//   far   the others (new tokens, chains): all valid representatives.  A few tokens in pieces of FIX_REPS products per wave,
+//         dealt over the launch; more than FIX_FAR on the tiles of the step's other form.
+// A chain of trips (scalars and list entry, hit words, representative, rows).  In a trace, all of them on the tiles -> now: T=3001,
+// d=1000, K=600 11.1 -> 6.3 us, T=197, d=768, K=40 9.2 -> 3.9; whole steps 34.9 -> 28.4 and 23.7 -> 19.7.
+struct GammaFix {
+    const uint32_t* hits;
+    const uint32_t* valid;
+    int waves;                 // of the launch
+};
+constexpr int FIX_FAR = 24, FIX_REPS = 8;
+
+template <typename In, bool WIDE>
+__global__ __launch_bounds__(256) void k_gamma_fix(GramParams p, GammaFix f) {
+    extern __shared__ __align__(16) char lds[];
+    constexpr int EPP = 16 / (int)sizeof(In);
+    const int lane = threadIdx.x & 63, wave = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const In* X = reinterpret_cast<const In*>(p.X);
+    int entry = p.nonrep_idx[min(wave, p.T - 1)];             // (before the length is known: one trip less)
+    const int r = p.meta[META_R], near = p.meta[META_FIX], far = p.meta[META_NONREP];
+    const int np = (p.d + EPP - 1) / EPP, Wa = (r + 31) >> 5;
+    auto row = [&](int t) { return X + (size_t)t * (size_t)p.ld; };
+    for (int i = wave; i < near; i += f.waves) {
+        if (i != wave) entry = p.nonrep_idx[i];
+        const int t = entry & 0xFFFF;
+        float best = 0.f;
+        for (int w0 = 0; w0 < Wa; w0 += 64) {
+            const int w = w0 + lane;
+            uint32_t bits = w < Wa ? f.hits[(size_t)w * p.T + t] & f.valid[w] : 0u;
+            for (unsigned long long any = __ballot(bits != 0u); any; any = __ballot(bits != 0u)) {
+                const int from = __builtin_amdgcn_readfirstlane(__ffsll((long long)any) - 1);
+                const uint32_t word = (uint32_t)__builtin_amdgcn_readlane((int)bits, from);
+                if (lane == from) bits &= bits - 1u;
+                const int q = p.prev_idx[(w0 + from) * 32 + __builtin_ctz(word)];
+                float s = 0.f;
+                for (int c = lane; c < np; c += 64)
+                    s = screen_dot<In>(load_piece<In, WIDE>(row(t), c * EPP, p.d), load_piece<In, WIDE>(row(q), c * EPP, p.d), s);
+                best = fmaxf(best, fabsf(wave_sum(s)) * p.inv_norm[q]);
+            }
+        }
+        if (lane == 0) p.gamma[t] = best * p.inv_norm[t];
+    }
+    if (far == 0) return;                                     // uniform
+    const int32_t* list = p.nonrep_idx + (p.T - far);
+    if (far <= FIX_FAR) {
+        const int pieces = (r + FIX_REPS - 1) / FIX_REPS;
+        for (int i = wave; i < far * pieces; i += f.waves) {
+            const int b = i / pieces, j0 = (i - b * pieces) * FIX_REPS, t = list[b];
+            const uint32_t ok = f.valid[j0 >> 5] >> (j0 & 31);        // (eight positions lie in one word)
+            int q[FIX_REPS];
+            float s[FIX_REPS], best = 0.f;
+#pragma unroll
+            for (int k = 0; k < FIX_REPS; ++k) { q[k] = p.prev_idx[min(j0 + k, r - 1)]; s[k] = 0.f; }
+            for (int c = lane; c < np; c += 64) {
+                const u32x4 x = load_piece<In, WIDE>(row(t), c * EPP, p.d);
+                u32x4 y[FIX_REPS];
+#pragma unroll
+                for (int k = 0; k < FIX_REPS; ++k) y[k] = load_piece<In, WIDE>(row(q[k]), c * EPP, p.d);
+#pragma unroll
+                for (int k = 0; k < FIX_REPS; ++k) s[k] = screen_dot<In>(x, y[k], s[k]);
+            }
+#pragma unroll
+            for (int k = 0; k < FIX_REPS; ++k) {
+                const float c = fabsf(wave_sum(s[k])) * p.inv_norm[q[k]];
+                if (j0 + k < r && (ok >> k & 1u) && !(p.order_mask && q[k] >= t)) best = fmaxf(best, c);
+            }
+            if (lane == 0 && best > 0.f) atomicMax(reinterpret_cast<uint32_t*>(p.gamma) + t, __float_as_uint(best * p.inv_norm[t]));
+        }
+        return;
+    }
+    const int nbS = (r + 63) / 64, ntiles = nbS * ((far + 63) / 64), per = (ntiles + 7) / 8;
+    const int xcd = blockIdx.x & 7, slots = gridDim.x >> 3;
+    for (int slot = blockIdx.x >> 3; slot < per; slot += slots) {
+        const int tile = xcd * per + slot;
+        if (tile >= ntiles) break;
+        gram_tile<In, 64, WIDE>(p, p.prev_idx, list, tile % nbS * 64, tile / nbS * 64, r, far, p.order_mask != 0, lds);
+        __syncthreads();
+    }
+}
+
+template <typename In, bool WIDE>
+hipError_t launch_gamma_fix(const GramParams& p, GammaFix f, int r, hipStream_t st) {
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    constexpr int lds = gram_lds_bytes<64>();
+    std::call_once(once, [] {
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gamma_fix<In, WIDE>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    });
+    if (attr_err != hipSuccess) return attr_err;
+    // a wave per token or a workgroup per tile, as many as two workgroups per CU (LDS) can use
+    const long long most = std::max(tiles_for(MODE_CROSS, r, p.T, 64), (long long)(p.T + 3) / 4), cap = 2 * device_cus();
+    const unsigned grid = (unsigned)((most < cap ? most : cap) + 7) / 8 * 8;
+    f.waves = (int)grid * 4;
+    ProfScope ps(ADA_K_GRAM_CROSS, st);
+    hipLaunchKernelGGL((k_gamma_fix<In, WIDE>), dim3(grid), dim3(256), lds, st, p, f);
+    return hipGetLastError();
+}
+
 // Algorithm 1 in one launch (ada_fused.hpp).  gamma, if given, receives for an inherited token gamma^rep and for any
 // other token gamma^cross.  The tiles accumulate a token's maximum over ALL inherited representatives; for the tokens
 // whose nearest one turned out removed (listed by the workgroup that updates the set) the maximum over the VALID ones is
-// recomputed by the cross-Gram tiles of the step's other form on that list, with the norms the first launch's tiles left: one
-// launch more.
+// recomputed by k_gamma_fix, with the norms the first launch's tiles left: one launch more.
 int run_cascade_fused(const void* X, int T, int d, long long ld, int dtype, float tau, const int32_t* prev_idx, int r,
                       const int32_t* r_dev, int32_t* idx, int32_t* adds, int32_t* removes, int32_t* counts,
                       uint64_t* gram_ops, float* gamma, void* ws, hipStream_t st, unsigned flags,
@@ -1354,6 +1453,7 @@ int run_cascade_fused(const void* X, int T, int d, long long ld, int dtype, floa
     p.first = w.first;
     if (gamma && !(grp && grp->G > 1)) {                          // Algorithm 1's gamma^cross: see above
         p.best = w.best; p.fix_list = w.nonrep_idx; p.fix_meta = w.meta; p.inv_norm = w.inv_norm;
+        p.fix_valid = reinterpret_cast<uint32_t*>(w.is_rep);      // (T / 8 bytes and more; this form keeps no flags there)
     }
     if (ctl) {                                                   // Section 8.1: threshold carried on the device
         p.tau_in = tau_in; p.thr_in = thr_in; p.tau_out = tau_out; p.thr_out = thr_out;
@@ -1369,13 +1469,13 @@ int run_cascade_fused(const void* X, int T, int d, long long ld, int dtype, floa
     }
     const int rc = launch_fused_any(p, dtype, ADA_K_CASCADE_FUSED, st);
     if (rc != ADA_OK || !p.fix_list) return rc;
-    // (a rejected step leaves an empty list; the validity of a representative is read off its own gamma^rep < threshold,
+    // (a rejected step leaves empty lists; the tiles read the validity of a representative off its own gamma^rep < threshold,
     //  as in the step's other form)
-    GramParams cross = {X, ld, T, d, prev_idx, w.nonrep_idx, w.meta, w.inv_norm, gamma, threshold_of(tau), MODE_CROSS,
-                        (flags & ADA_FLAG_CROSS_EARLIER_ONLY) ? 1 : 0};
+    const GramParams cross = {X, ld, T, d, prev_idx, w.nonrep_idx, w.meta, w.inv_norm, gamma, threshold_of(tau), MODE_CROSS,
+                              (flags & ADA_FLAG_CROSS_EARLIER_ONLY) ? 1 : 0};
     const hipError_t e = dispatch(dtype, d, [&](auto v) {
         using V = decltype(v);
-        return launch_gram_any<typename V::In, V::wide>(cross, r, T - 1 > 0 ? T - 1 : 1, false, st);
+        return launch_gamma_fix<typename V::In, V::wide>(cross, GammaFix{w.hits, p.fix_valid, 0}, r, st);
     });
     return e == hipSuccess ? ADA_OK : ADA_ERR_DEVICE;
 }

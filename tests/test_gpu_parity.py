@@ -1383,3 +1383,30 @@ def test_attention_at_config2_size():
     assert res["info"].cpu().tolist()[3] == 0
     parity.check_attention(q, k, v, 16, full["idx"], near["assign"].cpu().numpy(), res["out"].cpu().numpy(), False,
                            "config 2")
+
+
+@pytest.mark.parametrize("far", [0, 3, 24, 25, 70])            # tokens away from every representative: none, by the wave, on the tiles
+@pytest.mark.parametrize("T,d,dtype,flags", [(63, 5, "bf16", 0), (64, 7, "f32", 0), (197, 768, "bf16", 0), (300, 1000, "bf16", pa.FLAG_CROSS_EARLIER_ONLY),
+                                             (2050, 130, "f32", 0), (4500, 72, "bf16", 0)])
+def test_gamma_of_tokens_whose_nearest_representative_is_removed(T, d, dtype, flags, far):
+    """Half of the tokens are inherited, so every cluster keeps one of several representatives and most other tokens' nearest one is
+    removed; `far` tokens lie 0.4 rad from a removed representative and further from all others (in few dimensions some valid one may
+    be nearer), so nothing hits them.  gamma^rep and gamma^cross against the oracle, twice on one workspace."""
+    rng = np.random.default_rng(T + d + far)
+    tau, far = 0.1, min(far, T // 3)
+    K = max(2, T // 8)
+    C = rng.standard_normal((K, d))
+    C /= np.linalg.norm(C, axis=1, keepdims=True)
+    a = rng.integers(0, K, T)
+    X = C[a] + 0.004 * rng.standard_normal((T, d)) / np.sqrt(d)
+    inherited = np.sort(rng.permutation(T)[:T // 2])
+    others = np.setdiff1d(np.arange(T), inherited)
+    for t in rng.permutation(others)[:far]:
+        c = X[inherited[rng.integers(len(inherited))]]
+        v = rng.standard_normal(d)
+        v -= v @ c / (c @ c) * c
+        X[t] = np.cos(0.4) * c / np.linalg.norm(c) + np.sin(0.4) * v / np.linalg.norm(v)
+    x_cpu = wl.to_dtype(X.astype(np.float32), dtype)
+    ws = pa.workspace(T)
+    for _ in range(2):
+        step_and_check(x_cpu.to(DEV), x_cpu, tau, inherited, flags, "T=%d d=%d far=%d" % (T, d, far), ws=ws)

@@ -380,3 +380,62 @@ def test_full_selection_on_the_graph_of_near_pairs(kind, T, d, dtype, tau, greed
         step = pa.fetch(pa.ada_cascade_step(x, tau, torch.from_numpy(got["idx"]).to(DEV), ws=ws))
         if not greedy:
             assert np.array_equal(step["idx"], got["idx"]) or kind in ("loose", "common")   # (chains: a removed token covers nobody)
+
+
+@pytest.mark.parametrize("T,d,L,groups,dtype", [(2050, 4096, 13, 1, "bf16"),   # 64 lanes per row, two rows each, and past the caches
+                                                (2049, 512, 51, 1, "f32"), (4097, 192, 131, 1, "bf16"), (2047, 1024, 52, 1, "bf16"),
+                                                (8190, 128, 60, 2, "bf16")])
+def test_large_inputs_give_what_small_ones_give(T, d, L, groups, dtype):
+    """Layers of a call on 200 MB and more are read past the caches and their pairs in whole strips; the same layers two at a time, each
+    call going on from a full selection, must give the same sets wherever both start from the same one: layers 0 and 1 of every pair."""
+    gen = torch.Generator(device=DEV).manual_seed(T)
+    K = T // 7
+    C = torch.nn.functional.normalize(torch.randn(K, d, generator=gen, device=DEV), dim=1)
+    a = torch.randint(K, (groups, T), generator=gen, device=DEV)
+    xs = []
+    for _ in range(L):
+        a = torch.where(torch.rand(groups, T, generator=gen, device=DEV) < 0.05, torch.randint(K, (groups, T), generator=gen, device=DEV), a)
+        xs.append((C[a] + torch.randn(groups, T, d, generator=gen, device=DEV) * (0.004 / d ** 0.5)).to(torch.bfloat16 if dtype == "bf16" else torch.float32))
+    if groups == 1:
+        xs = [x[0] for x in xs]
+    loop = pa.ada_cascade_layers if groups == 1 else pa.ada_cascade_layers_grouped
+    at = (lambda res, k, l: res[k][l]) if groups == 1 else (lambda res, k, l: res[k][:, l])
+    big = loop(xs, 0.1)
+    first = loop(xs[:2], 0.1)
+    for l in (0, 1):
+        assert torch.equal(at(big, "counts", l), at(first, "counts", l))
+        counts = at(big, "counts", l).reshape(-1, 4)
+        for g in range(groups):
+            r = int(counts[g, 0])
+            i0, i1 = at(big, "idx", l).reshape(groups, T)[g, :r], at(first, "idx", l).reshape(groups, T)[g, :r]
+            assert torch.equal(i0, i1) and 0 < r < T
+    # the layers behind: every step from the call's own previous set (one launch per step, no graph)
+    for l in range(2, L, 7):
+        for g in range(groups):
+            x, c0, c1 = (xs[l] if groups == 1 else xs[l][g]), at(big, "counts", l - 1).reshape(-1, 4)[g], at(big, "counts", l).reshape(-1, 4)[g]
+            step = pa.fetch(pa.ada_cascade_step(x, 0.1, at(big, "idx", l - 1).reshape(groups, T)[g, :int(c0[0])].contiguous()))
+            assert int(c1[3]) == 0
+            assert np.array_equal(step["idx"], at(big, "idx", l).reshape(groups, T)[g, :int(c1[0])].cpu().numpy())
+
+
+@pytest.mark.parametrize("d,tau", [(64, 0.1), (768, 0.1), (4096, 0.1), (768, 0.3), (1000, 0.3), (3000, 0.2)])   # 1, 2, 3, 4, 5 and 6 column groups
+@pytest.mark.parametrize("T,L", [(97, 2), (255, 2), (257, 3), (2049, 2), (2815, 40)])
+def test_pairs_at_the_edges_of_blocks(d, tau, T, L):
+    """Every width of the sketch at token counts around the blocks of 32, 128 and 256, in pieces and in whole strips: each step equals
+    the one that multiplies all products (one launch per step)."""
+    if T * d * L > 1 << 28:
+        L = 3
+    gen = torch.Generator(device=DEV).manual_seed(T + d)
+    K = T // 5
+    C = torch.nn.functional.normalize(torch.randn(K, d, generator=gen, device=DEV), dim=1)
+    a = torch.randint(K, (T,), generator=gen, device=DEV)
+    a[-1] = a[0]                                                # the last token's pivot is in the first block
+    xs = [(C[a[torch.randperm(T, generator=gen, device=DEV)]] + torch.randn(T, d, generator=gen, device=DEV) * (0.004 / d ** 0.5)).bfloat16() for _ in range(L)]
+    res = pa.ada_cascade_layers(xs, tau)
+    full = pa.fetch(pa.ada_select_full(xs[0], tau))
+    assert np.array_equal(full["idx"], res["idx"][0, :int(res["counts"][0, 0])].cpu().numpy())
+    for l in range(1, L, 1 if L < 8 else 9):
+        prev = res["idx"][l - 1, :int(res["counts"][l - 1, 0])].contiguous()
+        step = pa.fetch(pa.ada_cascade_step(xs[l], tau, prev))
+        assert np.array_equal(step["idx"], res["idx"][l, :int(res["counts"][l, 0])].cpu().numpy())
+        assert step["gram_ops"] == int(res["gram_ops"][l])
