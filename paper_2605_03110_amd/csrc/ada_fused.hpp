@@ -88,14 +88,14 @@ struct FusedParams {
     // cascade step with a gamma output: Algorithm 1's gamma^cross is the maximum over the VALID representatives, which are
     // known only after all products.  The tiles therefore keep, per token, the arg max over all inherited
     // representatives that count for it (p.best, keyed by list position); the workgroup that updates the set lists the tokens
-    // whose nearest representative was removed (fix_list [T]: from the front those that a valid representative hits, with the
-    // position of their earliest hit in the upper half; from the back the others), clears their gamma and leaves both
+    // whose nearest representative was removed (fix_list [T]: from the front those whose earliest hit is by a valid representative,
+    // from the back the others), clears their gamma and leaves both
     // lengths, the set size and a status in the workspace's scalars (fix_meta: META_FIX, META_NONREP, META_R, META_STATUS) and
-    // the validity bits by list position (fix_valid) for the launch that recomputes those tokens' maxima (k_gamma_fix).
+    // the validity bits by list position (the workspace's flags, which lie in front of the scalars and which this form does not
+    // use otherwise) for the launch that recomputes those tokens' maxima (k_gamma_fix).
     // inv_norm: the tiles against the first representatives leave the tested tokens' 1/norm for that launch.
     int32_t* fix_list;
     int32_t* fix_meta;
-    uint32_t* fix_valid;
     float* inv_norm;
 };
 
@@ -1272,12 +1272,12 @@ __device__ inline void block_rank3(const bool (&f)[3][U], int (&below)[3], int (
 // way), and, once validity is known (vmask: one bit per list position), list the non-inherited tokens whose nearest
 // inherited representative was removed -- their maximum over the VALID representatives (step 8) is not the one the tiles
 // accumulated -- and clear their gamma for the recomputation.  hit(t): list position of the token's earliest hit, HIT_NONE
-// if it has none (or it is not known), HIT_INHERITED if the token is on the list.  ok == false: a rejected step, gamma is
-// cleared and the lists are empty.
+// if it has none (or it is not known), HIT_INHERITED if the token is on the list.  (Kept out of the way of steps without a
+// gamma output: the update is code that a launch runs once, and what has to be fetched of it is time, 0.6 us when this was
+// woven into it.)
 enum { HIT_NONE = -1, HIT_INHERITED = -2 };
 template <int THREADS, typename Hit>
-__device__ inline void gamma_fix_collect(const FusedParams& p, int r, const uint32_t* vmask, bool ok, Hit hit) {
-    if (!p.fix_list) return;                             // uniform
+__device__ inline void gamma_fix_collect(const FusedParams& p, int r, const uint32_t* vmask, Hit hit) {
     __shared__ int s_fix, s_far;
     const int tid = step_tid(p);
     if (tid == 0) s_fix = s_far = 0;
@@ -1286,12 +1286,14 @@ __device__ inline void gamma_fix_collect(const FusedParams& p, int r, const uint
     auto one = [&](int t, unsigned long long key) {
         if (t >= p.T) return;
         if (key != 0ull) p.best[t] = 0ull;
-        float m = ok ? __uint_as_float((uint32_t)(key >> 32)) : 0.f;
-        const int h = ok && key != 0ull ? hit(t) : HIT_INHERITED;
-        if (h != HIT_INHERITED && !valid(min(max(INT_MAX - (int)(uint32_t)key, 0), r - 1))) {
-            if (h != HIT_NONE && valid(h)) p.fix_list[atomicAdd(&s_fix, 1)] = t | h << 16;
-            else p.fix_list[p.T - 1 - atomicAdd(&s_far, 1)] = t;
-            m = 0.f;                                     // empty max: the recomputation accumulates into it
+        float m = __uint_as_float((uint32_t)(key >> 32));
+        if (key != 0ull && !valid(min(max(INT_MAX - (int)(uint32_t)key, 0), r - 1))) {
+            const int h = hit(t);
+            if (h != HIT_INHERITED) {
+                if (h != HIT_NONE && valid(h)) p.fix_list[atomicAdd(&s_fix, 1)] = t;
+                else p.fix_list[p.T - 1 - atomicAdd(&s_far, 1)] = t;
+                m = 0.f;                                 // empty max: the recomputation accumulates into it
+            }
         }
         p.gamma[t] = m;
     };
@@ -1304,11 +1306,11 @@ __device__ inline void gamma_fix_collect(const FusedParams& p, int r, const uint
         one(t2, k2);
         one(t3, k3);
     }
-    if (ok)
-        for (int w = tid; w < (r + 31) >> 5; w += THREADS) p.fix_valid[w] = vmask[w];
+    uint32_t* flags = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(p.fix_meta) - align_up((size_t)p.T, 256));   // (see carve)
+    for (int w = tid; w < (r + 31) >> 5; w += THREADS) flags[w] = vmask[w];
     __syncthreads();
     if (tid == 0) {
-        p.fix_meta[META_R] = ok ? r : 0;
+        p.fix_meta[META_R] = r;
         p.fix_meta[META_NONREP] = s_far;
         p.fix_meta[META_FIX] = s_fix;
         p.fix_meta[META_STATUS] = ADA_OK;
@@ -1360,7 +1362,7 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
     }
     ok = __syncthreads_and(ok);
     if (!ok) {
-        gamma_fix_collect<THREADS>(p, r, vmask, false, [](int) { return (int)HIT_NONE; });
+        if (p.fix_list) gamma_fix_none<THREADS>(p);
         if (tid == 0) {
             p.counts[0] = 0; p.counts[1] = 0; p.counts[2] = 0; p.counts[3] = ADA_ERR_INDEX;
             if (p.gram_ops) *p.gram_ops = 0ull;
@@ -1381,16 +1383,21 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
             const int j = (int)((pk >> (16 * u)) & 0xFFFFu);
             jpos[4 * v + u] = j;
             if (j != 0xFFFF && key[v][u] == 0u) atomicOr(&vmask[j >> 5], 1u << (j & 31));
-            // (gamma output: a token's earliest hit, marked by the top bit, where an inherited token has its place)
-            if (p.fix_list && j == 0xFFFF && key[v][u] != 0u)
-                pos[4 * t4 + u] = (uint16_t)(0x8000u | min(0xFFFFFFFFu - key[v][u], (uint32_t)(r - 1)));
         }
     }
     __syncthreads();
-    gamma_fix_collect<THREADS>(p, r, vmask, true, [&](int t) {                               // (gamma output only)
-        const int j = pos[t];
-        return j == 0xFFFF ? (int)HIT_NONE : j & 0x8000 ? j & 0x7FFF : (int)HIT_INHERITED;
-    });
+    if (__builtin_expect(p.fix_list != nullptr, 0)) {    // gamma output (uniform)
+        // a token's earliest hit, marked by the top bit, where an inherited token has its place
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+            if (jpos[i] == 0xFFFF && key[i >> 2][i & 3] != 0u)
+                pos[U * tid + i] = (uint16_t)(0x8000u | min(0xFFFFFFFFu - key[i >> 2][i & 3], (uint32_t)(r - 1)));
+        __syncthreads();
+        gamma_fix_collect<THREADS>(p, r, vmask, [&](int t) {
+            const int j = pos[t];
+            return j == 0xFFFF ? (int)HIT_NONE : j & 0x8000 ? j & 0x7FFF : (int)HIT_INHERITED;
+        });
+    }
     // step 9: any other token with a hit on a VALID representative is covered
     bool f[3][U];                                        // in R^(l+1) | added | removed
 #pragma unroll
@@ -1441,6 +1448,14 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
         reset_tickets(p.ticket);
     }
     return n_idx;
+}
+// A rejected step: gamma and the table are cleared, the lists are empty.
+template <int THREADS>
+__device__ inline void gamma_fix_none(const FusedParams& p) {
+    const int tid = step_tid(p);
+#pragma unroll 1
+    for (int t = tid; t < p.T; t += THREADS) { p.best[t] = 0ull; p.gamma[t] = 0.f; }
+    if (tid < 4) p.fix_meta[tid == 0 ? META_R : tid == 1 ? META_NONREP : tid == 2 ? META_FIX : META_STATUS] = tid == 3 ? ADA_OK : 0;
 }
 
 // Returns |R^(l+1)| to every thread (0 if the step is rejected).
@@ -1515,8 +1530,10 @@ __device__ __forceinline__ int fused_update(const FusedParams& p, int r, bool r_
     }
     ok = __syncthreads_and(ok);
     const int status = !r_ok ? ADA_ERR_SHAPE : (!ok ? ADA_ERR_INDEX : ADA_OK);
-    gamma_fix_collect<THREADS>(p, r, vmask, status == ADA_OK, [&](int t) { return (int)(flag[t] & 1 ? HIT_INHERITED : HIT_NONE); });   // (gamma output only)
+    if (p.fix_list && status == ADA_OK)                  // (gamma output only)
+        gamma_fix_collect<THREADS>(p, r, vmask, [&](int t) { return (int)(flag[t] & 1 ? HIT_INHERITED : HIT_NONE); });
     if (status != ADA_OK) {
+        if (p.fix_list) gamma_fix_none<THREADS>(p);
         if (tid == 0) {
             p.counts[0] = 0; p.counts[1] = 0; p.counts[2] = 0; p.counts[3] = status;
             if (p.gram_ops) *p.gram_ops = 0ull;

@@ -1339,75 +1339,97 @@ int launch_fused_any(const FusedParams& p, int dtype, int prof_class, hipStream_
 // gamma^cross of the tokens whose nearest inherited representative was removed (gamma_fix_collect's lists).
 //   near  tokens that a valid representative hits: any other is further away than those, so the maximum lies among the hits that
 //         the step's tiles left as bits, one as a rule.  One wave per token.
-//   far   the others (new tokens, chains): all valid representatives.  A few tokens in pieces of FIX_REPS products per wave,
-//         dealt over the launch; more than FIX_FAR on the tiles of the step's other form.
-// A chain of trips (scalars and list entry, hit words, representative, rows).  In a trace, all of them on the tiles -> now: T=3001,
-// d=1000, K=600 11.1 -> 6.3 us, T=197, d=768, K=40 9.2 -> 3.9; whole steps 34.9 -> 28.4 and 23.7 -> 19.7.
+//   far   the others (new tokens, chains): all valid representatives, in pieces of FIX_REPS products per wave beside the others;
+//         on the tiles of the step's other form where that is more than FIX_PAIRS products (both ways' time grows with the rows'
+//         length; T=4096, d=512, r=980, 17 to 40 such tokens: steps of 33.3 us by products, 36.0 by tiles).
+// A chain of trips (scalars and list entry, hit words, representative, rows), and code that is fetched as it runs: the products of the
+// far ones in straight lines took 2 us longer.  Steps, us, all of them on the tiles -> now: T=3001, d=1000, K=600 34.9 -> 28.5 (31.0 with
+// far ones), T=2048, d=4096, K=400 52 -> 34.5 (38.5), fp32 T=2048, d=768 50 -> 32.5 (34.4), T=4096, d=512, K=1000 34.3 -> 31 (33.3).
 struct GammaFix {
     const uint32_t* hits;
     const uint32_t* valid;
-    int waves;                 // of the launch
+    int grid;                  // of the launch
 };
-constexpr int FIX_FAR = 24, FIX_REPS = 8;
+constexpr int FIX_PAIRS = 49152, FIX_REPS = 8;
+
+// <x, y> by LPR neighbouring lanes, UN pieces of each row in flight per lane; every lane gets it.  (Kept short: a launch of a few
+// microseconds waits for every line of code that it runs for the first time.)
+template <typename In, bool WIDE, int LPR, int UN>
+__device__ inline float fix_product(const In* x, const In* y, int d, int li) {
+    constexpr int EPP = 16 / (int)sizeof(In);
+    const int np = (d + EPP - 1) / EPP;
+    float s = 0.f;
+#pragma unroll 1
+    for (int c = li; c < np; c += LPR * UN) {
+        u32x4 a[UN], b[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            a[u] = fetch_piece<In, WIDE>(x, (c + u * LPR) * EPP, d);
+            b[u] = fetch_piece<In, WIDE>(y, (c + u * LPR) * EPP, d);
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u)                          // (what a pulled-back load repeats counts once: one side is enough)
+            s = screen_dot<In>(finish_piece<In, WIDE>(a[u], (c + u * LPR) * EPP, d), b[u], s);
+    }
+#pragma unroll
+    for (int o = LPR / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    return s;
+}
 
 template <typename In, bool WIDE>
 __global__ __launch_bounds__(256) void k_gamma_fix(GramParams p, GammaFix f) {
     extern __shared__ __align__(16) char lds[];
-    constexpr int EPP = 16 / (int)sizeof(In);
-    const int lane = threadIdx.x & 63, wave = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    __shared__ float s_best[4];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int wg = f.grid - 1 - (int)blockIdx.x;              // (items from the last workgroup on, tiles from the first: side by side)
     const In* X = reinterpret_cast<const In*>(p.X);
-    int entry = p.nonrep_idx[min(wave, p.T - 1)];             // (before the length is known: one trip less)
+    int t = p.nonrep_idx[min(wg * 4 + wave, p.T - 1)];        // (before the length is known: one trip less)
     const int r = p.meta[META_R], near = p.meta[META_FIX], far = p.meta[META_NONREP];
-    const int np = (p.d + EPP - 1) / EPP, Wa = (r + 31) >> 5;
+    const int Wa = (r + 31) >> 5;
     auto row = [&](int t) { return X + (size_t)t * (size_t)p.ld; };
-    for (int i = wave; i < near; i += f.waves) {
-        if (i != wave) entry = p.nonrep_idx[i];
-        const int t = entry & 0xFFFF;
-        float best = 0.f;
-        for (int w0 = 0; w0 < Wa; w0 += 64) {
-            const int w = w0 + lane;
-            uint32_t bits = w < Wa ? f.hits[(size_t)w * p.T + t] & f.valid[w] : 0u;
-            for (unsigned long long any = __ballot(bits != 0u); any; any = __ballot(bits != 0u)) {
-                const int from = __builtin_amdgcn_readfirstlane(__ffsll((long long)any) - 1);
-                const uint32_t word = (uint32_t)__builtin_amdgcn_readlane((int)bits, from);
-                if (lane == from) bits &= bits - 1u;
-                const int q = p.prev_idx[(w0 + from) * 32 + __builtin_ctz(word)];
-                float s = 0.f;
-                for (int c = lane; c < np; c += 64)
-                    s = screen_dot<In>(load_piece<In, WIDE>(row(t), c * EPP, p.d), load_piece<In, WIDE>(row(q), c * EPP, p.d), s);
-                best = fmaxf(best, fabsf(wave_sum(s)) * p.inv_norm[q]);
-            }
-        }
-        if (lane == 0) p.gamma[t] = best * p.inv_norm[t];
-    }
-    if (far == 0) return;                                     // uniform
     const int32_t* list = p.nonrep_idx + (p.T - far);
-    if (far <= FIX_FAR) {
-        const int pieces = (r + FIX_REPS - 1) / FIX_REPS;
-        for (int i = wave; i < far * pieces; i += f.waves) {
-            const int b = i / pieces, j0 = (i - b * pieces) * FIX_REPS, t = list[b];
-            const uint32_t ok = f.valid[j0 >> 5] >> (j0 & 31);        // (eight positions lie in one word)
-            int q[FIX_REPS];
-            float s[FIX_REPS], best = 0.f;
-#pragma unroll
-            for (int k = 0; k < FIX_REPS; ++k) { q[k] = p.prev_idx[min(j0 + k, r - 1)]; s[k] = 0.f; }
-            for (int c = lane; c < np; c += 64) {
-                const u32x4 x = load_piece<In, WIDE>(row(t), c * EPP, p.d);
-                u32x4 y[FIX_REPS];
-#pragma unroll
-                for (int k = 0; k < FIX_REPS; ++k) y[k] = load_piece<In, WIDE>(row(q[k]), c * EPP, p.d);
-#pragma unroll
-                for (int k = 0; k < FIX_REPS; ++k) s[k] = screen_dot<In>(x, y[k], s[k]);
+    const bool tiles = (long long)far * r > FIX_PAIRS;
+    const int pieces = (r + 4 * FIX_REPS - 1) / (4 * FIX_REPS), near4 = (near + 3) / 4, items = near4 + (tiles ? 0 : far * pieces);
+    for (int i = wg; i < items; i += f.grid) {                // (uniform)
+        float best = 0.f;
+        if (i < near4) {
+            if (i * 4 + wave >= near) continue;
+            if (i != wg) t = p.nonrep_idx[i * 4 + wave];
+            const float it = p.inv_norm[t];
+            for (int w0 = 0; w0 < Wa; w0 += 64) {
+                const int w = w0 + lane;
+                uint32_t bits = w < Wa ? f.hits[(size_t)w * p.T + t] & f.valid[w] : 0u;
+                for (unsigned long long any = __ballot(bits != 0u); any; any = __ballot(bits != 0u)) {
+                    const int from = __builtin_amdgcn_readfirstlane(__ffsll((long long)any) - 1);
+                    const uint32_t word = (uint32_t)__builtin_amdgcn_readlane((int)bits, from);
+                    if (lane == from) bits &= bits - 1u;
+                    const int q = p.prev_idx[(w0 + from) * 32 + __builtin_ctz(word)];
+                    const float iq = p.inv_norm[q];
+                    best = fmaxf(best, fabsf(fix_product<In, WIDE, 64, 2>(row(t), row(q), p.d, lane)) * iq);
+                }
             }
-#pragma unroll
-            for (int k = 0; k < FIX_REPS; ++k) {
-                const float c = fabsf(wave_sum(s[k])) * p.inv_norm[q[k]];
-                if (j0 + k < r && (ok >> k & 1u) && !(p.order_mask && q[k] >= t)) best = fmaxf(best, c);
-            }
-            if (lane == 0 && best > 0.f) atomicMax(reinterpret_cast<uint32_t*>(p.gamma) + t, __float_as_uint(best * p.inv_norm[t]));
+            if (lane == 0) p.gamma[t] = best * it;
+            continue;
         }
-        return;
+        const int b = (i - near4) / pieces, j0 = ((i - near4 - b * pieces) * 4 + wave) * FIX_REPS;
+        t = list[b];
+        const float it = p.inv_norm[t];
+        const int j = j0 + (lane >> 3);                       // eight lanes per representative
+        const int q = p.prev_idx[min(j, r - 1)];
+        if (j < r && (f.valid[j >> 5] >> (j & 31) & 1u) && !(p.order_mask && q >= t)) best = p.inv_norm[q];
+        best *= fabsf(fix_product<In, WIDE, 8, 8>(row(t), row(q), p.d, lane & 7));
+#pragma unroll
+        for (int o = 8; o < 64; o <<= 1) best = fmaxf(best, __shfl_xor(best, o, 64));
+        // (one atomic per workgroup: they queue at the token's address, 25 ns each)
+        __syncthreads();
+        if (lane == 0) s_best[wave] = best;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            best = fmaxf(fmaxf(s_best[0], s_best[1]), fmaxf(s_best[2], s_best[3])) * it;
+            if (best > 0.f) atomicMax(reinterpret_cast<uint32_t*>(p.gamma) + t, __float_as_uint(best));
+        }
     }
+    if (!tiles) return;                                       // uniform
     const int nbS = (r + 63) / 64, ntiles = nbS * ((far + 63) / 64), per = (ntiles + 7) / 8;
     const int xcd = blockIdx.x & 7, slots = gridDim.x >> 3;
     for (int slot = blockIdx.x >> 3; slot < per; slot += slots) {
@@ -1430,7 +1452,7 @@ hipError_t launch_gamma_fix(const GramParams& p, GammaFix f, int r, hipStream_t 
     // a wave per token or a workgroup per tile, as many as two workgroups per CU (LDS) can use
     const long long most = std::max(tiles_for(MODE_CROSS, r, p.T, 64), (long long)(p.T + 3) / 4), cap = 2 * device_cus();
     const unsigned grid = (unsigned)((most < cap ? most : cap) + 7) / 8 * 8;
-    f.waves = (int)grid * 4;
+    f.grid = (int)grid;
     ProfScope ps(ADA_K_GRAM_CROSS, st);
     hipLaunchKernelGGL((k_gamma_fix<In, WIDE>), dim3(grid), dim3(256), lds, st, p, f);
     return hipGetLastError();
@@ -1453,7 +1475,6 @@ int run_cascade_fused(const void* X, int T, int d, long long ld, int dtype, floa
     p.first = w.first;
     if (gamma && !(grp && grp->G > 1)) {                          // Algorithm 1's gamma^cross: see above
         p.best = w.best; p.fix_list = w.nonrep_idx; p.fix_meta = w.meta; p.inv_norm = w.inv_norm;
-        p.fix_valid = reinterpret_cast<uint32_t*>(w.is_rep);      // (T / 8 bytes and more; this form keeps no flags there)
     }
     if (ctl) {                                                   // Section 8.1: threshold carried on the device
         p.tau_in = tau_in; p.thr_in = thr_in; p.tau_out = tau_out; p.thr_out = thr_out;
@@ -1475,7 +1496,7 @@ int run_cascade_fused(const void* X, int T, int d, long long ld, int dtype, floa
                               (flags & ADA_FLAG_CROSS_EARLIER_ONLY) ? 1 : 0};
     const hipError_t e = dispatch(dtype, d, [&](auto v) {
         using V = decltype(v);
-        return launch_gamma_fix<typename V::In, V::wide>(cross, GammaFix{w.hits, p.fix_valid, 0}, r, st);
+        return launch_gamma_fix<typename V::In, V::wide>(cross, GammaFix{w.hits, reinterpret_cast<const uint32_t*>(w.is_rep), 0}, r, st);
     });
     return e == hipSuccess ? ADA_OK : ADA_ERR_DEVICE;
 }
