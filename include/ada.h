@@ -365,7 +365,7 @@ int ada_cascade_layers_adaptive(const void* const* X_layers, int L, int T, int d
 /*
  * Which tile shape a one-launch cascade step takes when `workgroups` workgroups share its tiles (the CU count for a
  * single problem; that divided by the number of groups for a grouped call) and the rows come in whole aligned
- * 128-byte chunks of bf16: 0 = 64 x 64, 1 = 64 representatives x 128 tokens, 2 = 128 x 128, 3 = 128 representatives x
+ * 128-byte chunks of bf16: 0 = 64 x 64 (in quarters where each of those has a workgroup of its own), 1 = 64 representatives x 128 tokens, 2 = 128 x 128, 3 = 128 representatives x
  * 256 tokens; -1 for arguments out of range.
  * Host only (no device is touched): the same function the kernel evaluates with the set size it finds.
  */
@@ -427,7 +427,7 @@ int ada_profile_mfma_probe(int workgroups, int iters, float* sink, void* stream)
  *                                 64 x 128 units
  *   ADA_TILE=64|128               register-staged Gram tile size
  *   ADA_KGROUPS=1|2               K-groups of the 64 x 64 one-launch cascade tile
- *   ADA_CASCADE_TILE=64|64x128|128|256x128   tile shape of the one-launch cascade step
+ *   ADA_CASCADE_TILE=32|64|64x128|128|256x128   tile shape of the one-launch cascade step
  *   ADA_NO_DMA=1                  operands through registers instead of straight into LDS
  *   ADA_ATTN=lds                  the first attention kernel
  *   ADA_SCREEN=0                  layer loops: one launch per layer, full selection: every product, instead of the screened form

@@ -120,12 +120,13 @@ __device__ inline void adapt_tau(const FusedParams& p, int r, int n_add, int n_r
     *p.thr_out = (float)(1.0 - sq);
 }
 
-// Tile shapes (representatives x tested tokens): 0 = 64 x 64, 1 = 64 x 128, 2 = 128 x 128.  A step's cost is taken as
+// Tile shapes (representatives x tested tokens): 0 = 64 x 64, 1 = 64 x 128, 2 = 128 x 128, 3 = 128 x 256; and 4 = 32 x 32 where every
+// such tile has a workgroup of its own (small_tiles).  A step's cost is taken as
 // rounds x (operand bytes per tile + a fixed part worth about 56 rows of 4096 two-byte elements: set size, list and
 // first-chunk trips before the K loop, norms and hit words after it), rounds = tiles over the workgroups that share
 // them: operand bytes per Gram entry fall with the tile size, but a tile count below the worker count leaves CUs idle.
-__host__ __device__ inline int tile_rows_r(int shape) { return shape >= 2 ? 128 : 64; }
-__host__ __device__ inline int tile_rows_t(int shape) { return shape == 0 ? 64 : shape == 3 ? 256 : 128; }
+__host__ __device__ inline int tile_rows_r(int shape) { return shape == 4 ? 32 : shape >= 2 ? 128 : 64; }
+__host__ __device__ inline int tile_rows_t(int shape) { return shape == 4 ? 32 : shape == 0 ? 64 : shape == 3 ? 256 : 128; }
 // (T <= FUSED_MAX_T: every count fits 32 bits, and 32-bit divisions are what the start of a launch can afford)
 __host__ __device__ inline int tile_count(int r, int T, int shape) {
     const int br = tile_rows_r(shape), bt = tile_rows_t(shape);
@@ -152,6 +153,16 @@ __host__ __device__ inline int cascade_tile_shape(int r, int T, int d, int pick,
     return best;
 }
 
+// Whether a step takes 32 x 32 tiles (fused_tile_small): a quarter of the products and half of the bytes of a 64 x 64 tile per
+// workgroup, at twice the bytes per product, so only while each has a workgroup of its own.  r: the size of the set, or its
+// bound where only the device knows it.  fp32 gains by the products, bf16 by what it does not wait for, as long as a row is
+// read in one batch.  Measured, us per step, 64 x 64 -> 32 x 32: fp32 T=512, r=100: d=768 25.9 -> 18.2, d=4096 84.5 -> 42.6; T=1024, r=200,
+// d=4096 85.4 -> 44.7; bf16 T=197, r=39, d=768 15.7 -> 14.0; T=1024, r=200: d=768 15.8 -> 14.2, d=4096 26.2 -> 28.4; rows that are no
+// whole pieces, T=1000, d=1001 22.7 -> 25.8; two rounds, T=2048, r=200, d=768 16.0 -> 21.6.
+inline bool small_tiles(int r, int T, int d, size_t esz, int pick, int workers) {
+    return pick == -4 || (pick > 0 && tile_count(r, T, 4) <= workers && (esz == 4 || (d <= 1024 && d % 8 == 0)));
+}
+
 // The thread's number; in a kernel that loops over steps (p.steps, a constant there) computed anew at each use.  What the tiles
 // and the update derive from it does not depend on the step, and the compiler moved all of it out of that loop: 263 registers per
 // lane spilled to memory in k_cascade_rest, 278 in k_cascade_pass (T=2048, d=4096, 27 steps: 867 us, 735 without).
@@ -166,7 +177,10 @@ __device__ inline int step_tid(const FusedParams& p) {
 // Workgroups first count per XCD (blockIdx % 8: eight counters on separate cache lines); the last of each XCD then
 // takes the device-wide ticket.  Called by one thread; true in exactly one workgroup, after all others have called.
 constexpr int TICKET_XCD0 = 64;                          // ints from the device-wide ticket to the first XCD counter
+// (Few workgroups share one counter: the second trip costs more than they wait for each other, and those without a tile
+// come early.)
 __device__ inline bool take_ticket(int32_t* ticket, int grid) {
+    if (grid <= 64) return atomicAdd(ticket, 1) == grid - 1;
     const int per = grid >> 3;                           // grids are multiples of 8
     if (atomicAdd(ticket + TICKET_XCD0 + 32 * (blockIdx.x & 7), 1) != per - 1) return false;
     return atomicAdd(ticket, 1) == 7;
@@ -185,7 +199,8 @@ __device__ inline int list_at(const FusedParams& p, int j) {
 
 // How operands travel.  DMA_RAGGED: rows of whole 16-byte pieces whose last 128-byte chunk is a part of one; what it misses is
 // loaded from a page of zeros (a select of the address per load, which the whole-chunk form does without).
-enum { DMA_NONE = 0, DMA_WHOLE = 1, DMA_RAGGED = 2 };
+// DMA_SMALL: 32 x 32 tiles, which take their operands straight into registers (a kernel of its own: the others' registers are used up).
+enum { DMA_NONE = 0, DMA_WHOLE = 1, DMA_RAGGED = 2, DMA_SMALL = 3 };
 __device__ const u32x4 g_zero_piece = {0u, 0u, 0u, 0u};
 template <bool RAGGED>
 __device__ inline const void __attribute__((address_space(1)))* dma_source(const void* at, bool inside) {
@@ -201,18 +216,19 @@ template <int KG, int DMA> struct FusedGeom {
     static constexpr int NS = 4;                          // DMA path: LDS stages per K-group
     static constexpr int LPT = 4;                         // 16-byte pieces per thread per chunk
     static constexpr int STAGE = 128 * 128;               // one chunk of 128 rows
-    static constexpr int NPART = DMA != DMA_NONE ? 2 * KG : KG;       // partial sums of squares per row
+    static constexpr int NPART = DMA == DMA_WHOLE || DMA == DMA_RAGGED ? 2 * KG : KG;       // partial sums of squares per row
     static constexpr int OFF_STOK = 0;                    // int[64]   token id of each "against" row (INT_MAX: none)
     static constexpr int OFF_REPF = 256;                  // int[64]   tested token is inherited
     static constexpr int OFF_SS = 512;                    // float[NPART][128] partial sums of squares
     static constexpr int OFF_SCALE = OFF_SS + NPART * 512;   // float[128] 1/norm (0 for rows that do not exist)
     static constexpr int OFF_SCAN = OFF_SCALE + 512;      // scan scratch of the update phase
     static constexpr int META = OFF_SCAN + 512;
-    static constexpr int RING = DMA != DMA_NONE ? KG * NS * STAGE : KG * 2 * STAGE;
+    static constexpr bool DIRECT = DMA == DMA_WHOLE || DMA == DMA_RAGGED;
+    static constexpr int RING = DIRECT ? KG * NS * STAGE : KG * 2 * STAGE;
     static constexpr int RINGMAX = 3 * 384 * 128;         // the widest ring tile: three stages of 384 rows (144 KB)
-    static constexpr int BODY = (KG == 2 && DMA != DMA_NONE) ? RINGMAX : (RING > 65536 ? RING : 65536);   // stages / reduction scratch (64 KB) / update state
+    static constexpr int BODY = (KG == 2 && DIRECT) ? RINGMAX : (RING > 65536 ? RING : 65536);   // stages / reduction scratch (64 KB) / update state
     static constexpr int OFF_BIG = META + BODY;           // metadata of the wide tiles (two-group direct-to-LDS form)
-    static constexpr int LDS = META + BODY + ((KG == 2 && DMA != DMA_NONE) ? 8192 : 0);
+    static constexpr int LDS = META + BODY + ((KG == 2 && DIRECT) ? 8192 : 0);
     static_assert(LDS <= 160 * 1024, "one workgroup's LDS");
 };
 
@@ -586,6 +602,102 @@ __device__ inline void fused_tile(const FusedParams& p, int r, int s0, int t0, i
                      sb * 2 + a, half);
     }
     ADA_CLK(5);
+}
+
+// The same step on a 32 x 32 tile for steps that are a few tiles: eight waves share K, wave w taking every eighth pair of 16-byte
+// pieces, and the operands go from memory to registers as the matrix instruction wants them (lane l: row l % 32, piece
+// l / 32 of a pair), a batch of pairs ahead.  No stages, no barriers: a step with rows of up to 1.5 KB waits for its operands
+// once.  The partial blocks and sums of squares meet in LDS, wave 0 finishes.
+template <typename In>
+__device__ inline void fused_tile_small(const FusedParams& p, int r, int s0, int t0, int sb, char* lds) {
+    constexpr int EPP = 16 / (int)sizeof(In), NW = 8, UN = 6;
+    int* s_tok = reinterpret_cast<int*>(lds);                 // [32]
+    int* repf = s_tok + 32;                                   // [32]
+    float* scale = reinterpret_cast<float*>(repf + 32);       // [64]
+    float* ssq = scale + 64;                                  // [NW][64]
+    f32x4* red = reinterpret_cast<f32x4*>(ssq + NW * 64);     // [NW][4][64]
+    const int tid = step_tid(p), lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const In* X = reinterpret_cast<const In*>(p.X);
+    const int li = s0 + l32;
+    const int stok = min(max(list_at(p, li < r ? li : r - 1), 0), p.T - 1);
+    if (tid < 32) {
+        s_tok[tid] = li < r ? stok : INT_MAX;
+        repf[tid] = 0;
+    }
+    __syncthreads();
+    const In* rowa = X + (size_t)stok * (size_t)p.ld;
+    const In* rowb = X + (size_t)min(t0 + l32, p.T - 1) * (size_t)p.ld;
+    const int pairs = ((p.d + EPP - 1) / EPP + 1) >> 1, mine = (pairs + NW - 1) / NW;   // (the last ones may be all zeros)
+    auto e0 = [&](int k) { return ((k * NW + wave) * 2 + half) * EPP; };
+    u32x4 fa[2][UN], fb[2][UN];
+    auto fetch = [&](int set, int k0) {
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            fa[set][u] = fetch_piece<In, true>(rowa, e0(k0 + u), p.d);
+            fb[set][u] = fetch_piece<In, true>(rowb, e0(k0 + u), p.d);
+        }
+    };
+    f32x16 acc[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[c][i] = 0.f;
+    float ssa = 0.f, ssb = 0.f;
+    auto use = [&](int set, int k0) {
+#pragma unroll
+        for (int u = 0; u < UN; ++u)
+            if (k0 + u < mine) {                              // uniform
+                const u32x4 a = finish_piece<In, true>(fa[set][u], e0(k0 + u), p.d), b = finish_piece<In, true>(fb[set][u], e0(k0 + u), p.d);
+                Mfma<In>::run(acc[u & 1], a, b);
+                ssa += piece_sumsq_fast<In>(a);
+                ssb += piece_sumsq_fast<In>(b);
+            }
+    };
+    fetch(0, 0);
+    if (!p.assign_mode)                                       // which tested tokens are inherited (see fused_tile)
+        for (int j = tid; j < r; j += NW * 64) {
+            const unsigned q = (unsigned)(list_at(p, j) - t0);
+            if (q < 32u) repf[q] = 1;
+        }
+    for (int k0 = 0; k0 < mine; k0 += 2 * UN) {
+        if (k0 + UN < mine) fetch(1, k0 + UN);
+        use(0, k0);
+        if (k0 + UN < mine) {
+            if (k0 + 2 * UN < mine) fetch(0, k0 + 2 * UN);
+            use(1, k0 + UN);
+        }
+    }
+    ssa += __shfl_xor(ssa, 32, 64);                           // the two lane halves hold different pieces
+    ssb += __shfl_xor(ssb, 32, 64);
+    ssq[wave * 64 + lane] = half ? ssb : ssa;                 // rows of the set first, then tested rows
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = acc[0][4 * q + e] + acc[1][4 * q + e];
+        red[(wave * 4 + q) * 64 + lane] = v;
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) sum += ssq[w * 64 + lane];
+    float sc = sum > 0.f ? 1.0f / sqrtf(sum) : 0.f;           // a zero row normalises to zero: all its cosines are 0
+    if (half ? t0 + l32 >= p.T : li >= r) sc = 0.f;
+    scale[lane] = sc;
+    if (p.inv_norm && s0 == 0 && half && t0 + l32 < p.T) p.inv_norm[t0 + l32] = sc;
+    f32x16 tot;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        f32x4 v = red[q * 64 + lane];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) v += red[(w * 4 + q) * 64 + lane];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) tot[4 * q + e] = v[e];
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");        // (the scales: written and read by this wave)
+    finish_block(p, tot, s_tok, scale, scale[32 + l32], (repf[l32] != 0 ? 3 : 0) | (p.earlier_only ? 1 : 0), t0 + l32, sb, half);
 }
 
 // The same step on a wider tile: BR = 32 RB representatives (RB = 2 or 4) against 128 tested tokens, 8 waves on one
@@ -1316,6 +1428,14 @@ __device__ inline void gamma_fix_collect(const FusedParams& p, int r, const uint
         p.fix_meta[META_STATUS] = ADA_OK;
     }
 }
+// A rejected step: gamma and the table are cleared, the lists are empty.
+template <int THREADS>
+__device__ inline void gamma_fix_none(const FusedParams& p) {
+    const int tid = step_tid(p);
+#pragma unroll 1
+    for (int t = tid; t < p.T; t += THREADS) { p.best[t] = 0ull; p.gamma[t] = 0.f; }
+    if (tid < 4) p.fix_meta[tid == 0 ? META_R : tid == 1 ? META_NONREP : tid == 2 ? META_FIX : META_STATUS] = tid == 3 ? ADA_OK : 0;
+}
 
 // Algorithm 1 steps 5, 9, 10 from the first-hit records.  For every token the tiles left, next to its hit words, the
 // smallest list position of a representative that hits it (p.first).  That decides almost everything:
@@ -1448,14 +1568,6 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
         reset_tickets(p.ticket);
     }
     return n_idx;
-}
-// A rejected step: gamma and the table are cleared, the lists are empty.
-template <int THREADS>
-__device__ inline void gamma_fix_none(const FusedParams& p) {
-    const int tid = step_tid(p);
-#pragma unroll 1
-    for (int t = tid; t < p.T; t += THREADS) { p.best[t] = 0ull; p.gamma[t] = 0.f; }
-    if (tid < 4) p.fix_meta[tid == 0 ? META_R : tid == 1 ? META_NONREP : tid == 2 ? META_FIX : META_STATUS] = tid == 3 ? ADA_OK : 0;
 }
 
 // Returns |R^(l+1)| to every thread (0 if the step is rejected).
@@ -1678,10 +1790,11 @@ __device__ inline StepDeal fused_step_deal(const FusedParams& p, int r, bool tri
     constexpr int NSHAPES = sizeof(In) == 2 ? 4 : 3;                      // the ring tiles are bf16 only
     StepDeal s;
     s.shape = 0;
-    if constexpr (WIDE && KG == 2 && DMA != DMA_NONE)
+    if constexpr (WIDE && KG == 2 && (DMA == DMA_WHOLE || DMA == DMA_RAGGED))
         s.shape = cascade_tile_shape(r, p.T, p.d, p.tile_pick, p.groups > 1 ? (int)cus : p.tile_pick, NSHAPES);
-    s.sr = s.shape >= 2 ? 7 : 6;
-    s.st = s.shape == 0 ? 6 : s.shape == 3 ? 8 : 7;
+    if constexpr (DMA == DMA_SMALL) s.shape = 4;
+    s.sr = s.shape == 4 ? 5 : s.shape >= 2 ? 7 : 6;
+    s.st = s.shape == 4 ? 5 : s.shape == 0 ? 6 : s.shape == 3 ? 8 : 7;
     s.nbS = (unsigned)(r + (1 << s.sr) - 1) >> s.sr;
     const unsigned nbT = (unsigned)(p.T + (1 << s.st) - 1) >> s.st;
     s.triangle = triangle && p.first;
@@ -1724,7 +1837,9 @@ __device__ inline void fused_step_tiles(const FusedParams& p, int r, bool triang
             tb = (int)(tile / nbS);
             sb = (int)(tile - (unsigned)tb * nbS);
         }
-        if constexpr (WIDE && KG == 2 && DMA != DMA_NONE) {
+        if constexpr (DMA == DMA_SMALL) {
+            fused_tile_small<In>(p, r, sb * 32, tb * 32, sb, lds);
+        } else if constexpr (WIDE && KG == 2 && DMA != DMA_NONE) {
             if constexpr (sizeof(In) == 2) {
                 // (measured both ways: loader waves gain 10% at 128 x 128; at 128 x 256 the eight multiplying waves of
                 // the ring tile are 3% ahead for one sequence and level for stacked ones)

@@ -1265,7 +1265,7 @@ hipError_t launch_fused(const FusedParams& p, hipStream_t st, int prof_class = A
     unsigned grid;
     if (p.groups > 1) {
         // the groups share the chip: about one workgroup per CU in all, and no more per group than it has tiles
-        const long long tiles = tile_count(p.r_host, p.T, 0);
+        const long long tiles = tile_count(p.r_host, p.T, DMA == DMA_SMALL ? 4 : 0);
         long long wpg = device_cus() / p.groups;
         if (wpg < 1) wpg = 1;
         if (wpg > tiles) wpg = tiles;
@@ -1273,8 +1273,8 @@ hipError_t launch_fused(const FusedParams& p, hipStream_t st, int prof_class = A
         grid = (unsigned)(p.groups * wpg);
     } else {
         // with the set size known here the tile shape is too (the kernel makes the same choice from the same numbers)
-        int shape = 0;
-        if (WIDE && KG == 2 && DMA != DMA_NONE && !p.r_dev)
+        int shape = DMA == DMA_SMALL ? 4 : 0;
+        if (WIDE && KG == 2 && (DMA == DMA_WHOLE || DMA == DMA_RAGGED) && !p.r_dev)
             shape = cascade_tile_shape(p.r_host, p.T, p.d, p.tile_pick, p.tile_pick, sizeof(In) == 2 ? 4 : 3);
         long long tiles = tile_count(p.r_host, p.T, shape);
         // Workgroups loop over tiles, so any grid is correct.  With the set size known only on the device the bound
@@ -1299,7 +1299,7 @@ int kgroups_override() {
     return (v == 1 || v == 2) ? v : 0;
 }
 
-// FusedParams::tile_pick: the CU count (automatic choice per step) unless the development switch fixes the shape.
+// FusedParams::tile_pick: the CU count (automatic choice per step) unless the development switch fixes the shape (-4: 32 x 32 tiles).
 int cascade_tile_pick() {
     const char* e = dev_switch("ADA_CASCADE_TILE");          // representatives x tokens: 64, 64x128, 128, 256x128 (tokens x reps)
     if (e) {
@@ -1308,6 +1308,7 @@ int cascade_tile_pick() {
         if (v == "64x128") return -1;
         if (v == "128") return -2;
         if (v == "256x128") return -3;
+        if (v == "32") return -4;
     }
     return device_cus();
 }
@@ -1325,6 +1326,8 @@ int launch_fused_any(const FusedParams& p, int dtype, int prof_class, hipStream_
         using In = typename V::In;
         constexpr int epc = 128 / (int)sizeof(In);
         if constexpr (V::wide) {
+            if (kg == 2 && small_tiles(p.r_host, p.T, p.d, sizeof(In), p.tile_pick, p.groups > 1 ? p.tile_pick / p.groups : p.tile_pick))
+                return launch_fused<In, true, 2, DMA_SMALL>(p, st, prof_class);
             if (dma && p.d % epc == 0)
                 return kg == 2 ? launch_fused<In, true, 2, DMA_WHOLE>(p, st, prof_class)
                                : launch_fused<In, true, 1, DMA_WHOLE>(p, st, prof_class);

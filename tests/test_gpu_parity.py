@@ -1410,3 +1410,19 @@ def test_gamma_of_tokens_whose_nearest_representative_is_removed(T, d, dtype, fl
     ws = pa.workspace(T)
     for _ in range(2):
         step_and_check(x_cpu.to(DEV), x_cpu, tau, inherited, flags, "T=%d d=%d far=%d" % (T, d, far), ws=ws)
+
+
+@pytest.mark.parametrize("T,d,K,dtype", [(1, 8, 1, "bf16"), (31, 9, 5, "bf16"), (33, 4, 6, "f32"), (64, 97, 9, "f32"), (130, 64, 17, "bf16"),
+                                         (333, 1001, 40, "bf16"), (512, 768, 100, "f32"), (700, 4096, 120, "bf16"), (1290, 130, 300, "f32")])
+def test_small_shapes_one_launch_cascade_on_quarter_tiles(T, d, K, dtype, monkeypatch):
+    """32 x 32 tiles with operands straight in registers (steps that are a few tiles take them by themselves), forced: one piece and
+    less than a batch per wave up to several batches, rows that are no whole pieces, a last block of one token."""
+    monkeypatch.setenv("ADA_CASCADE_TILE", "32")
+    w = wl.small(T=T, d=d, K=K, L=3, dtype=dtype, seed=29 + T, p=0.1)
+    xs = wl.layer_list(w)
+    stats = run_layers_teacher_forced(w, xs, what="32 x 32 tiles T=%d d=%d" % (T, d))
+    assert all(e <= parity.GAMMA_TOL for _, _, e in stats)
+    run_layers_teacher_forced(w, xs, flags=pa.FLAG_CROSS_EARLIER_ONLY, what="32 x 32 tiles earlier-only T=%d" % T)
+    full = pa.fetch(pa.ada_select_full(xs[0].to(DEV), w.tau))
+    res = pa.ada_assign_nearest(xs[0].to(DEV), torch.as_tensor(full["idx"]).to(DEV))
+    parity.check_assign(xs[0], full["idx"], res["assign"].cpu().numpy(), res["corr"].cpu().numpy(), "32 x 32 tiles assign")
