@@ -1648,6 +1648,12 @@ hipError_t launch_screen_rest(const ScreenParams& sp, hipStream_t st) {
     return hipGetLastError();
 }
 
+template <typename In, int NCH, int R = 1>
+void launch_screen_sketch(const ScreenParams& sp, int units, hipStream_t st) {
+    const int rows = SKETCH_ROWS * R, rb = (sp.T + rows - 1) / rows;
+    hipLaunchKernelGGL((k_screen_sketch<In, NCH, R>), dim3((unsigned)(rb * units)), dim3(256), 0, st, sp, rb);
+}
+
 template <int NCH, int TB>
 void launch_screen_pairs(const ScreenParams& sp, const PairItems& it, dim3 grid, int total, hipStream_t st) {
     hipLaunchKernelGGL((k_screen_pairs<NCH, TB>), grid, dim3(256), 0, st, sp, it, total);
@@ -1657,10 +1663,18 @@ void launch_screen_pairs(const ScreenParams& sp, const PairItems& it, dim3 grid,
 template <typename In>
 hipError_t launch_screen(const ScreenParams& sp, hipStream_t st) {
     const int units = sp.G * sp.L;
-    const int rb = (sp.T + SKETCH_ROWS - 1) / SKETCH_ROWS;
     {
         ProfScope ps(ADA_K_SCREEN, st);
-        hipLaunchKernelGGL((k_screen_sketch<In>), dim3((unsigned)(rb * units)), dim3(256), 0, st, sp, rb);
+        switch (sp.nch) {
+            case 1:
+                if ((long long)units * sp.T >= 2048 * SKETCH_ROWS) launch_screen_sketch<In, 1, 4>(sp, units, st);
+                else launch_screen_sketch<In, 1>(sp, units, st);
+                break;
+            case 2: launch_screen_sketch<In, 2>(sp, units, st); break;
+            case 3: launch_screen_sketch<In, 3>(sp, units, st); break;
+            case 4: launch_screen_sketch<In, 4>(sp, units, st); break;
+            default: launch_screen_sketch<In, 0>(sp, units, st);
+        }
     }
     {
         const PairItems it(sp.T, units);

@@ -194,9 +194,11 @@ template <> __device__ inline void screen_load8<float>(const float* row, int e0,
 
 // ------------------------------------------------------------------------------------------------
 // k_screen_sketch: eight lanes per row, eight columns per lane and column group.  Reads n1 / d of X, one cache line (two
-// for fp32) per row and group; the groups of a row are all requested before the first is used (up to four).
-constexpr int SKETCH_ROWS = 32;                               // rows per workgroup
-template <typename In>
+// for fp32) per row and group; all that a lane needs is requested before the first of it is used.  NCH: column groups, or 0:
+// more than four (the first four requested together).  R: rows per lane.  Four where a row is one line and there are many of them,
+// or the launch is bound by the dispatch of its workgroups (128 units of T=2048, d=256: 20.4 us with one row, 13.0 with four).
+constexpr int SKETCH_ROWS = 32;                               // rows per workgroup and pass
+template <typename In, int NCH, int R>
 __global__ __launch_bounds__(256) void k_screen_sketch(ScreenParams p, int row_blocks) {
     const ScreenUnit U(p.T, p.nch, p.edge_cap);
     const int unit = blockIdx.x / row_blocks, rb = blockIdx.x - unit * row_blocks;
@@ -209,58 +211,59 @@ __global__ __launch_bounds__(256) void k_screen_sketch(ScreenParams p, int row_b
         if (layer == 0 && p.first == 0 && threadIdx.x == 0)
             reinterpret_cast<int32_t*>(reinterpret_cast<char*>(p.meta) + (long long)group * p.area_gs)[META_PROGRESS] = 0;
     }
+    constexpr int KEEP = NCH > 0 ? NCH : 4;
+    const int nch = NCH > 0 ? NCH : p.nch;
     const int lane = threadIdx.x & 63, c8 = lane & 7;
-    const int t = rb * SKETCH_ROWS + (threadIdx.x >> 6) * 8 + (lane >> 3);
-    const In* row = X + (size_t)min(t, p.T - 1) * (size_t)p.ld;
-    auto col = [&](int j) { return (int)((unsigned)j * (unsigned)p.nk / (unsigned)p.nch) * 64 + c8 * 8; };
-    constexpr int KEEP = 4;
-    float v[KEEP][8];
-    float ss = 0.f;
+    const int t0 = rb * SKETCH_ROWS * R + (threadIdx.x >> 6) * 8 + (lane >> 3);
+    auto row = [&](int k) { return X + (size_t)min(t0 + k * SKETCH_ROWS, p.T - 1) * (size_t)p.ld; };
+    auto col = [&](int j) { return (int)((unsigned)j * (unsigned)p.nk / (unsigned)nch) * 64 + c8 * 8; };
+    float v[R][KEEP][8];
 #pragma unroll
-    for (int j = 0; j < KEEP; ++j) {
-        const int jc = min(j, p.nch - 1);
-        screen_load8<In>(row, col(jc), p.d, v[j]);
-    }
+    for (int k = 0; k < R; ++k)
 #pragma unroll
-    for (int j = 0; j < KEEP; ++j)
-        if (j < p.nch) {
+        for (int j = 0; j < KEEP; ++j) screen_load8<In>(row(k), col(j), p.d, v[k][j]);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) ss = fmaf(v[j][i], v[j][i], ss);
+    for (int k = 0; k < R; ++k) {
+        const int t = t0 + k * SKETCH_ROWS;
+        float ss = 0.f;
+#pragma unroll
+        for (int j = 0; j < KEEP; ++j)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) ss = fmaf(v[k][j][i], v[k][j][i], ss);
+        for (int j = KEEP; j < nch; ++j) {
+            float x[8];
+            screen_load8<In>(row(k), col(j), p.d, x);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) ss = fmaf(x[i], x[i], ss);
         }
-    for (int j = KEEP; j < p.nch; ++j) {
-        float x[8];
-        screen_load8<In>(row, col(j), p.d, x);
+        ss += __shfl_xor(ss, 1, 64);
+        ss += __shfl_xor(ss, 2, 64);
+        ss += __shfl_xor(ss, 4, 64);
+        const float sc = ss > 0.f ? p.scale / sqrtf(ss) : 0.f;
+        if (t >= p.T) return;                                 // (and so are the lane's other rows)
+        uint8_t* z = reinterpret_cast<uint8_t*>(base + U.o_z) + (size_t)(t >> 5) * (size_t)(2048 * nch) +
+                     ((c8 >> 1) & 1) * 1024 + ((c8 >> 2) * 32 + (t & 31)) * 16 + (c8 & 1) * 8;
+        auto put = [&](int j, const float (&x)[8]) {
+            int lo = 0, hi = 0;
+            lo = __builtin_amdgcn_cvt_pk_fp8_f32(x[0] * sc, x[1] * sc, lo, false);
+            lo = __builtin_amdgcn_cvt_pk_fp8_f32(x[2] * sc, x[3] * sc, lo, true);
+            hi = __builtin_amdgcn_cvt_pk_fp8_f32(x[4] * sc, x[5] * sc, hi, false);
+            hi = __builtin_amdgcn_cvt_pk_fp8_f32(x[6] * sc, x[7] * sc, hi, true);
+            *reinterpret_cast<int2*>(z + j * 2048) = int2{lo, hi};
+        };
 #pragma unroll
-        for (int i = 0; i < 8; ++i) ss = fmaf(x[i], x[i], ss);
-    }
-    ss += __shfl_xor(ss, 1, 64);
-    ss += __shfl_xor(ss, 2, 64);
-    ss += __shfl_xor(ss, 4, 64);
-    const float sc = ss > 0.f ? p.scale / sqrtf(ss) : 0.f;
-    if (t >= p.T) return;
-    uint8_t* z = reinterpret_cast<uint8_t*>(base + U.o_z) + (size_t)(t >> 5) * (size_t)(2048 * p.nch) +
-                 ((c8 >> 1) & 1) * 1024 + ((c8 >> 2) * 32 + (t & 31)) * 16 + (c8 & 1) * 8;
-    auto put = [&](int j, const float (&x)[8]) {
-        int lo = 0, hi = 0;
-        lo = __builtin_amdgcn_cvt_pk_fp8_f32(x[0] * sc, x[1] * sc, lo, false);
-        lo = __builtin_amdgcn_cvt_pk_fp8_f32(x[2] * sc, x[3] * sc, lo, true);
-        hi = __builtin_amdgcn_cvt_pk_fp8_f32(x[4] * sc, x[5] * sc, hi, false);
-        hi = __builtin_amdgcn_cvt_pk_fp8_f32(x[6] * sc, x[7] * sc, hi, true);
-        *reinterpret_cast<int2*>(z + j * 2048) = int2{lo, hi};
-    };
-#pragma unroll
-    for (int j = 0; j < KEEP; ++j)
-        if (j < p.nch) put(j, v[j]);
-    for (int j = KEEP; j < p.nch; ++j) {
-        float x[8];
-        screen_load8<In>(row, col(j), p.d, x);
-        put(j, x);
-    }
-    if (c8 == 0) {
-        reinterpret_cast<float*>(base + U.o_rho)[t] = ss;
-        reinterpret_cast<int32_t*>(base + U.o_piv)[t] = t;
-        reinterpret_cast<int32_t*>(base + U.o_size)[t] = 0;
-        if (p.gamma) p.gamma[t] = 0.f;
+        for (int j = 0; j < KEEP; ++j) put(j, v[k][j]);
+        for (int j = KEEP; j < nch; ++j) {
+            float x[8];
+            screen_load8<In>(row(k), col(j), p.d, x);
+            put(j, x);
+        }
+        if (c8 == 0) {
+            reinterpret_cast<float*>(base + U.o_rho)[t] = ss;
+            reinterpret_cast<int32_t*>(base + U.o_piv)[t] = t;
+            reinterpret_cast<int32_t*>(base + U.o_size)[t] = 0;
+            if (p.gamma) p.gamma[t] = 0.f;
+        }
     }
 }
 
