@@ -449,7 +449,8 @@ template <int DH> struct AttnGeom2 {
 //          Then the loaders write V^T(kb) and ask for V(kb + 1); the multipliers form the scores and weights of kb.
 //   B(kb): V^T(kb) is written; the multipliers have left K(kb).  Then the loaders ask for K(kb + 2) into the stage just
 //          left and for the indices of block kb + 3; the multipliers add weights x V^T(kb) to their rows.
-template <int DH, typename Layers>
+// STREAM: outputs are stored past the caches (see launch_attn_regs).
+template <int DH, typename Layers, bool STREAM>
 __global__ __launch_bounds__(512) void k_attn_rep2(AttnParams p, Layers layers) {
     attn_layer(p, layers);
     using In = uint16_t;
@@ -772,8 +773,12 @@ __global__ __launch_bounds__(512) void k_attn_rep2(AttnParams p, Layers layers) 
                     v4[u] = *reinterpret_cast<const float4*>(obuf + (ent[u] & 63) * G::OS + c4);
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
-                    if (kk + u < kend && wave8 * RPI + sub + NW * RPI * (k0 + kk + u) < n)
-                        *reinterpret_cast<float4*>(outh + (size_t)(ent[u] >> 6) * (size_t)p.ld_out + c4) = v4[u];
+                    if (kk + u < kend && wave8 * RPI + sub + NW * RPI * (k0 + kk + u) < n) {
+                        f32x4* at = reinterpret_cast<f32x4*>(outh + (size_t)(ent[u] >> 6) * (size_t)p.ld_out + c4);
+                        const f32x4 v = {v4[u].x, v4[u].y, v4[u].z, v4[u].w};
+                        if constexpr (STREAM) __builtin_nontemporal_store(v, at);
+                        else *at = v;
+                    }
             }
         }
         __syncthreads();

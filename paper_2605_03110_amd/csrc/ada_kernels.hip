@@ -1112,20 +1112,27 @@ inline int attn_grid_x(const AttnParams& p, int n_layers) {
 }
 
 // bf16: the kernel that keeps scores and weights in registers (eight waves: four multiply, four fetch)
-template <int DH, typename Layers>
+template <int DH, bool STREAM, typename Layers>
 hipError_t launch_attn_regs(const AttnParams& p, const Layers& layers, int n_layers, hipStream_t st) {
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     constexpr int lds = AttnGeom2<DH>::LDS;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_rep2<DH, Layers>),
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_rep2<DH, Layers, STREAM>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     if (attr_err != hipSuccess) return attr_err;
     ProfScope ps(ADA_K_ATTN, st);
     const int gx = attn_grid_x(p, n_layers);
-    hipLaunchKernelGGL((k_attn_rep2<DH, Layers>), dim3(gx, p.H, n_layers), dim3(512), lds, st, p, layers);
+    hipLaunchKernelGGL((k_attn_rep2<DH, Layers, STREAM>), dim3(gx, p.H, n_layers), dim3(512), lds, st, p, layers);
     return hipGetLastError();
+}
+
+// Outputs of 96 MB and more (the Infinity Cache has 256, and as many bytes of Q, K and V pass through it beside them) are not
+// kept: whoever reads them next would find little of them.  Whole pipelines, us, cached -> streamed: 3 layers of T=2048, 16 heads x 256
+// (96 MB) 122 -> 112, 4 (128 MB) 152 -> 142, 16 of 32 x 128 (512 MB) 388 -> 360, 2 of T=8192 (256 MB) 234 -> 223.
+inline bool attn_streams(const AttnParams& p, int n_layers, int d_h) {
+    return p.ld_out % 32 == 0 && (double)n_layers * p.T * p.H * d_h * 4 >= 96.0 * (1 << 20);
 }
 
 template <typename In, int DH, typename Layers>
@@ -1139,7 +1146,8 @@ hipError_t launch_attn(const AttnParams& p, const Layers& layers, int n_layers, 
         bool out16 = p.ld_out % 4 == 0 && (uintptr_t)p.out % 16 == 0;
         if constexpr (std::is_same<Layers, AttnLayers>::value)
             for (int l = 0; l < n_layers; ++l) out16 = out16 && (uintptr_t)layers.out[l] % 16 == 0;
-        if (!first_kernel && out16) return launch_attn_regs<DH>(p, layers, n_layers, st);
+        if (!first_kernel && out16)
+            return attn_streams(p, n_layers, DH) ? launch_attn_regs<DH, true>(p, layers, n_layers, st) : launch_attn_regs<DH, false>(p, layers, n_layers, st);
     }
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;

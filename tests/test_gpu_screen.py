@@ -439,3 +439,30 @@ def test_pairs_at_the_edges_of_blocks(d, tau, T, L):
         step = pa.fetch(pa.ada_cascade_step(xs[l], tau, prev))
         assert np.array_equal(step["idx"], res["idx"][l, :int(res["counts"][l, 0])].cpu().numpy())
         assert step["gram_ops"] == int(res["gram_ops"][l])
+
+
+@pytest.mark.parametrize("L,T,H,dh", [(3, 2048, 16, 256), (4, 2049, 26, 128), (1, 6200, 64, 64)])
+def test_large_attention_outputs_and_one_batch_on_two_streams(L, T, H, dh):
+    """Outputs of 96 MB and more are stored past the caches, and one batch of layers runs on one of the two streams: bit for bit what
+    the same calls give on the caller's stream alone, where every layer's attention is a small launch; and work that the caller
+    has enqueued on either stream before the call, and enqueues after it, keeps its order."""
+    gen = torch.Generator(device=DEV).manual_seed(T)
+    K, d = T // 9, H * dh
+    C = torch.nn.functional.normalize(torch.randn(K, d, generator=gen, device=DEV), dim=1)
+    xs = [(C[torch.randint(K, (T,), generator=gen, device=DEV)] + torch.randn(T, d, generator=gen, device=DEV) * (0.004 / d ** 0.5)).bfloat16() for _ in range(L)]
+    Q, K_, V = ([torch.randn(T, d, generator=gen, device=DEV).bfloat16() for _ in range(L)] for _ in range(3))
+    sel, att = torch.cuda.Stream(), torch.cuda.Stream()
+    flags = pa.FLAG_ATTN_CAUSAL
+    res = pa.ada_pipeline_layers(xs, Q, K_, V, H, 0.1, stream_sel=sel, stream_attn=att, flags=flags)
+    for s in (sel, att):
+        with torch.cuda.stream(s):
+            copy = res["idx"].clone()                           # behind the call on either stream
+        torch.cuda.current_stream().wait_stream(s)
+        assert torch.equal(copy, res["idx"])
+    ref = pa.ada_pipeline_layers(xs, Q, K_, V, H, 0.1, flags=flags)
+    for l in range(L):
+        r = int(ref["counts"][l, 0])
+        assert torch.equal(res["counts"][l], ref["counts"][l]) and torch.equal(res["idx"][l, :r], ref["idx"][l, :r])
+        assert torch.equal(res["assign"][l], ref["assign"][l])
+        one = pa.ada_attention_compressed(Q[l], K_[l], V[l], H, ref["idx"][l, :r].contiguous(), ref["assign"][l].contiguous(), flags=flags)
+        assert torch.equal(res["out"][l], one["out"]) and torch.equal(ref["out"][l], one["out"])
