@@ -311,8 +311,7 @@ int ada_cascade_layers_grouped(const ada_groups* groups, const void* const* X_la
  * nothing from the attention (eq. (1)).  Where layers share their launches (see ada_cascade_layers), they go in batches
  * of up to 16: selection and nearest-representative assignment (Section 2.3) of a batch on stream_sel, its attention in
  * one launch on stream_attn as soon as these are done, beside the selection of the next batch.  With 16 layers and
- * fewer nothing is left to run side by side: from 3 layers on all of it then goes to stream_attn (in order with both
- * streams' work before and after the call), and one stream for both saves the remaining events (about 25 us a call).
+ * fewer nothing is left to run side by side, and one stream saves the events between the two (about 35 us a call).
  * Where every layer has launches of its own, assignment and attention run on stream_attn and wait for that layer's set.
  *   X_layers, Q_layers, K_layers, V_layers   HOST arrays of L device pointers: T x (H * d_h) matrices, leading
  *                dimension ld, dtype as usual; the alignment rules of ada_attention_compressed apply to Q, K, V

@@ -2328,6 +2328,7 @@ int ada_pipeline_layers(const void* const* X_layers, const void* const* Q_layers
         (void)hipEventDestroy(ev);                               // released by the runtime once it has completed
         return ok;
     };
+    if (!fork(main, ss)) return ADA_ERR_DEVICE;
     int rc = ADA_OK;
     // Screened: the sets and assignments of many layers come together, and so does the attention on them (a layer of 16
     // heads and 400 representatives has 112 workgroups for 256 CUs; several layers in one launch fill the chip).  The
@@ -2338,22 +2339,6 @@ int ada_pipeline_layers(const void* const* X_layers, const void* const* Q_layers
     const size_t fit_pos = ws_area_bytes(T) / ((size_t)T * 4) / 2;
     const int most = fit_pos < (size_t)ATTN_LAYERS ? (int)fit_pos : ATTN_LAYERS;
     const int batches = (L + most - 1) / most, batch = (L + batches - 1) / batches;
-    // One batch has nothing to run beside: all of it goes to stream_attn, in order with both streams before and after the
-    // call, and the device waits for two hand-overs between streams instead of three (T=2048, 16 heads x 256, 4 layers: 154.7 -> 145.6
-    // us).  The host has one more to issue: calls of one or two layers wait for the host and stay as they are (one layer: 95 -> 105).
-    // Not under capture, where streams have to be forked from `stream` and the edges cost nothing.
-    const hipStream_t stream_sel_given = ss;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    bool one_stream = screened && batches == 1 && L >= 3 && ss != sa && ss != main && sa != main;
-    if (one_stream) {
-        if (hipStreamIsCapturing(main, &capture) != hipSuccess) return ADA_ERR_DEVICE;
-        one_stream = capture == hipStreamCaptureStatusNone;
-    }
-    if (one_stream) {
-        if (!fork(ss, sa)) return ADA_ERR_DEVICE;
-        ss = sa;
-    }
-    if (!fork(main, ss)) return ADA_ERR_DEVICE;
     hipEvent_t attended[2] = {nullptr, nullptr};                  // behind the attention of the last batches
     for (int k = 0; screened && k < batches && rc == ADA_OK; ++k) {
         const int first = k * batch, n = L - first < batch ? L - first : batch;
@@ -2383,7 +2368,7 @@ int ada_pipeline_layers(const void* const* X_layers, const void* const* Q_layers
     for (hipEvent_t ev : attended)
         if (ev) (void)hipEventDestroy(ev);                        // released by the runtime once it has completed
     if (screened) {                                               // (stream_attn has waited for the whole selection)
-        if (!fork(sa, main) || !fork(sa, stream_sel_given)) return ADA_ERR_DEVICE;
+        if (!fork(sa, main)) return ADA_ERR_DEVICE;
         if (rc != ADA_OK && !fork(ss, main)) return ADA_ERR_DEVICE;
         return rc;
     }
