@@ -442,10 +442,9 @@ def test_pairs_at_the_edges_of_blocks(d, tau, T, L):
 
 
 @pytest.mark.parametrize("L,T,H,dh", [(3, 2048, 16, 256), (4, 2049, 26, 128), (1, 6200, 64, 64)])
-def test_large_attention_outputs_and_one_batch_on_two_streams(L, T, H, dh):
-    """Outputs of 96 MB and more are stored past the caches, and one batch of layers runs on one of the two streams: bit for bit what
-    the same calls give on the caller's stream alone, where every layer's attention is a small launch; and work that the caller
-    has enqueued on either stream before the call, and enqueues after it, keeps its order."""
+def test_large_attention_outputs_on_two_streams(L, T, H, dh):
+    """Outputs of 96 MB and more are stored past the caches: from two streams, from one and from a launch per layer they are the
+    same bit for bit, and work enqueued on either stream after the call sees the sets."""
     gen = torch.Generator(device=DEV).manual_seed(T)
     K, d = T // 9, H * dh
     C = torch.nn.functional.normalize(torch.randn(K, d, generator=gen, device=DEV), dim=1)
