@@ -395,7 +395,7 @@ __global__ __launch_bounds__(256, screen_pair_waves(NCH, TB)) void k_screen_pair
         }
         rd(fa, s);
         if constexpr (NCH > 0) {
-            if ((tb0 + TB) * 32 > T) {                        // tokens that do not exist have no candidates
+            if ((tb0 + TB) * 32 > T) {                        // (see block)
 #pragma unroll
                 for (int b = 0; b < TB; ++b)
                     if ((tb0 + b) * 32 + l32 >= T) {
@@ -435,7 +435,9 @@ __global__ __launch_bounds__(256, screen_pair_waves(NCH, TB)) void k_screen_pair
 #pragma unroll
                 for (int b = 0; b < ACC; ++b) {
                     uint32_t v = screen_bits(acc[b]) & (!diag || s < tb0 + b0 + b ? SCREEN_BITS : s == tb0 + b0 + b ? earlier : 0u);
-                    if (NCH == 0 && (tb0 + b0 + b) * 32 + l32 >= T) v = 0u;
+                    // Tokens that do not exist have no candidates.  Their operands are zero, and so are their products with rows that were
+                    // written; the last block's other rows, which only the diagonal meets, hold anything, and 0 x NaN is NaN.
+                    if ((NCH == 0 || diag) && (tb0 + b0 + b) * 32 + l32 >= T) v = 0u;
                     cand += __popc(v);
                     first[b0 + b] = min(first[b0 + b], screen_first(v) | (uint32_t)s << 5);
                 }

@@ -346,6 +346,45 @@ def test_only_the_front_of_a_workspace_has_to_be_zero(kind, T, d):
             assert torch.equal(a[:r], b[:r])
 
 
+def unit_counts(ws, T, g=0):
+    """Candidates, pairs inside clusters, flags and the dense mark of a sequence's first unit: ScreenUnit's header, which lies behind the
+    workspace's front (csrc/ada_screen.hpp: SU_DENSE, SU_CAND, SU_PART; one line of 32 words per XCD)."""
+    at = g * pa.workspace_bytes(T) + pa.ada_workspace_zero_bytes(T)
+    hdr = ws.view(-1)[at:at + 4 * (32 + 16 * 32)].cpu().numpy().view(np.uint32)
+    part = hdr[32 + 8 * 32:].reshape(8, 32)
+    return int(hdr[32:32 + 8 * 32].reshape(8, 32)[:, 0].sum()), int(part[:, 0].sum()), int(np.bitwise_or.reduce(part[:, 1])), int(hdr[4])
+
+
+@pytest.mark.parametrize("d,tau", [(64, 0.1), (768, 0.1), (4096, 0.1), (768, 0.3), (1000, 0.3)])   # 1 to 5 column groups
+@pytest.mark.parametrize("T,L", [(97, 2), (129, 2), (257, 2), (700, 2), (2049, 2), (2049, 16), (2080, 2)])
+def test_rows_past_the_end_are_no_candidates(d, tau, T, L):
+    """The sketches of a last block that is not whole end in memory that nobody has written.  Whatever lies there (bytes 0xFF are not
+    numbers as 8-bit floats), the candidates of tight clusters are the pairs inside them: nothing is left over that would send a layer
+    through all products again or to the tiles."""
+    print("[case] rows past the end: T=%d L=%d d=%d tau=%g" % (T, L, d, tau), flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(T + d)
+    K, G = T // 8, 2
+    C = torch.nn.functional.normalize(torch.randn(K, d, generator=gen, device=DEV), dim=1)
+    a = torch.randint(K, (T,), generator=gen, device=DEV)
+    pairs = torch.bincount(a, minlength=K)
+    pairs = int((pairs * (pairs - 1) // 2).sum())
+    xs = [(C[a] + torch.randn(G, T, d, generator=gen, device=DEV) * (0.004 / d ** 0.5)).bfloat16() for _ in range(L)]
+    calls = [(G, lambda ws: pa.ada_cascade_layers_grouped(xs, tau, ws=ws)), (1, lambda ws: pa.ada_cascade_layers([x[1] for x in xs], tau, ws=ws))]
+    if T >= 1500 and L == 2:
+        calls.append((1, lambda ws: pa.ada_select_full(xs[0][0], tau, ws=ws, flags=pa.FLAG_GREEDY_COVER)))
+    one, front = pa.workspace_bytes(T), pa.ada_workspace_zero_bytes(T)
+    for n, call in calls:
+        for fill in (0x00, 0x7F, 0xFF):
+            ws = torch.full((n, one), fill, dtype=torch.uint8, device=DEV)
+            ws[:, :front] = 0
+            call(ws.view(-1))
+            torch.cuda.synchronize()
+            for g in range(n):
+                cand, inside, flags, dense = unit_counts(ws, T, g)
+                assert inside == pairs and flags == 0, (n, fill, g)
+                assert cand == pairs and dense == 0, (n, fill, g, cand - pairs)
+
+
 FULL = [
     # kind, T, d, dtype, tau, greedy, big: long enough for the graph, by one rule each (greedy / fp32 / other bf16 rows / whole pieces)
     ("clusters", 1500, 64, "bf16", 0.1, True, 0), ("clusters", 2049, 1001, "bf16", 0.1, True, 0), ("clusters", 4100, 96, "f32", 0.2, True, 0),
