@@ -1128,11 +1128,14 @@ hipError_t launch_attn_regs(const AttnParams& p, const Layers& layers, int n_lay
     return hipGetLastError();
 }
 
-// Outputs of 96 MB and more (the Infinity Cache has 256, and as many bytes of Q, K and V pass through it beside them) are not
-// kept: whoever reads them next would find little of them.  Whole pipelines, us, cached -> streamed: 3 layers of T=2048, 16 heads x 256
-// (96 MB) 122 -> 112, 4 (128 MB) 152 -> 142, 16 of 32 x 128 (512 MB) 388 -> 360, 2 of T=8192 (256 MB) 234 -> 223.
+// Outputs of 192 MB and more are not kept: with the Q, K and V that pass through it beside them the Infinity Cache (256 MB)
+// holds little of them for whoever reads them next.  Smaller ones a reader does find there, and stored past it he pays what the
+// call gains, and more.  Pipelines of T=2048, 16 heads x 256 and of T=8192, us, cached -> streamed, alone and with a copy of the outputs to bf16
+// behind the call: 4 layers (128 MB) 159 -> 146 and 196.3 -> 199.7, 5 (160 MB) 167 -> 156 and 214.2 -> 214.2, 6 (192 MB) 213 -> 202 and
+// 272.1 -> 270.2, 8 (256 MB) 262 -> 250 and 347 -> 337; T=8192, 1 layer (128 MB) 122 -> 106 and 148.7 -> 149.2, 2 (256 MB) 392 -> 379 and
+// 464 -> 451; 16 layers of 32 x 128 (512 MB) 513 -> 490 and 692 -> 673.  The first pass on new buffers, 4 layers: 679 -> 703.
 inline bool attn_streams(const AttnParams& p, int n_layers, int d_h) {
-    return p.ld_out % 32 == 0 && (double)n_layers * p.T * p.H * d_h * 4 >= 96.0 * (1 << 20);
+    return p.ld_out % 32 == 0 && (double)n_layers * p.T * p.H * d_h * 4 >= 192.0 * (1 << 20);
 }
 
 template <typename In, int DH, typename Layers>

@@ -480,12 +480,21 @@ def test_pairs_at_the_edges_of_blocks(d, tau, T, L):
         assert step["gram_ops"] == int(res["gram_ops"][l])
 
 
-@pytest.mark.parametrize("L,T,H,dh", [(3, 2048, 16, 256), (4, 2049, 26, 128), (1, 6200, 64, 64)])
-def test_large_attention_outputs_on_two_streams(L, T, H, dh):
-    """Outputs of 96 MB and more are stored past the caches: from two streams, from one and from a launch per layer they are the
-    same bit for bit, and work enqueued on either stream after the call sees the sets."""
+def past_the_caches(L, T, H, dh, ld):
+    """Whether one attention launch stores its outputs past the caches (attn_streams of csrc/ada_kernels.hip)."""
+    return ld % 32 == 0 and L * T * H * dh * 4 >= 192 << 20
+
+
+@pytest.mark.parametrize("L,T,H,dh,streamed", [(6, 2048, 16, 256, True), (8, 2049, 26, 128, True), (2, 6200, 64, 64, True), (1, 8200, 24, 256, True), (1, 6300, 64, 128, True),
+                                               (3, 2048, 16, 256, False), (4, 2049, 26, 128, False), (1, 6200, 64, 64, False)])
+def test_large_attention_outputs_on_two_streams(L, T, H, dh, streamed):
+    """Outputs of 192 MB and more are stored past the caches: from two streams and from one they are bit for bit what launches that store
+    through the caches give (a layer alone, or rows that are no whole cache lines apart), nothing behind a row is touched, and work
+    enqueued on either stream after the call sees the sets."""
+    print("[case] large outputs: L=%d T=%d %dx%d" % (L, T, H, dh), flush=True)
     gen = torch.Generator(device=DEV).manual_seed(T)
     K, d = T // 9, H * dh
+    assert past_the_caches(L, T, H, dh, d) == streamed and not past_the_caches(1, T, H, dh, d + 4)
     C = torch.nn.functional.normalize(torch.randn(K, d, generator=gen, device=DEV), dim=1)
     xs = [(C[torch.randint(K, (T,), generator=gen, device=DEV)] + torch.randn(T, d, generator=gen, device=DEV) * (0.004 / d ** 0.5)).bfloat16() for _ in range(L)]
     Q, K_, V = ([torch.randn(T, d, generator=gen, device=DEV).bfloat16() for _ in range(L)] for _ in range(3))
@@ -498,9 +507,16 @@ def test_large_attention_outputs_on_two_streams(L, T, H, dh):
         torch.cuda.current_stream().wait_stream(s)
         assert torch.equal(copy, res["idx"])
     ref = pa.ada_pipeline_layers(xs, Q, K_, V, H, 0.1, flags=flags)
+    wide = torch.full((T, d + 4), 7.0, device=DEV)
     for l in range(L):
         r = int(ref["counts"][l, 0])
         assert torch.equal(res["counts"][l], ref["counts"][l]) and torch.equal(res["idx"][l, :r], ref["idx"][l, :r])
         assert torch.equal(res["assign"][l], ref["assign"][l])
-        one = pa.ada_attention_compressed(Q[l], K_[l], V[l], H, ref["idx"][l, :r].contiguous(), ref["assign"][l].contiguous(), flags=flags)
-        assert torch.equal(res["out"][l], one["out"]) and torch.equal(ref["out"][l], one["out"])
+        cached = wide[:, :d] if past_the_caches(1, T, H, dh, d) else torch.empty(T, d, device=DEV)
+        pa.ada_attention_compressed(Q[l], K_[l], V[l], H, ref["idx"][l, :r].contiguous(), ref["assign"][l].contiguous(), flags=flags, out=cached)
+        assert torch.equal(res["out"][l], cached) and torch.equal(ref["out"][l], cached)
+    assert bool((wide[:, d:] == 7.0).all())
+    if T < 2100:
+        r = int(ref["counts"][0, 0])
+        parity.check_attention(Q[0].cpu(), K_[0].cpu(), V[0].cpu(), H, ref["idx"][0, :r].cpu().numpy(), ref["assign"][0].cpu().numpy(),
+                               ref["out"][0].cpu().numpy(), causal=True, what="large outputs")
