@@ -88,14 +88,13 @@ struct FusedParams {
     // cascade step with a gamma output: Algorithm 1's gamma^cross is the maximum over the VALID representatives, which are
     // known only after all products.  The tiles therefore keep, per token, the arg max over all inherited
     // representatives that count for it (p.best, keyed by list position); the workgroup that updates the set lists the tokens
-    // whose nearest representative was removed (fix_list [T]: from the front those whose earliest hit is by a valid representative,
-    // from the back the others), clears their gamma and leaves both
-    // lengths, the set size and a status in the workspace's scalars (fix_meta: META_FIX, META_NONREP, META_R, META_STATUS) and
-    // the validity bits by list position (the workspace's flags, which lie in front of the scalars and which this form does not
-    // use otherwise) for the launch that recomputes those tokens' maxima (k_gamma_fix).
+    // whose nearest representative was removed (fix_list [T]: covered ones from the front, new ones from the back), clears their gamma and
+    // leaves both lengths, the set size and a status in the workspace's scalars (fix_meta: META_FIX, META_NONREP, META_R,
+    // META_STATUS) and the validity bits by list position (fix_valid) for the launch that recomputes those tokens' maxima (k_gamma_fix).
     // inv_norm: the tiles against the first representatives leave the tested tokens' 1/norm for that launch.
     int32_t* fix_list;
     int32_t* fix_meta;
+    uint32_t* fix_valid;
     float* inv_norm;
 };
 
@@ -1380,62 +1379,8 @@ __device__ inline void block_rank3(const bool (&f)[3][U], int (&below)[3], int (
 // across the workgroup, independent of each other and branch-free (indices are clamped, results masked): a whole batch
 // is in flight before the first use.
 
-// gamma for callers that ask for it: unpack the tiles' keys (the table is zero between calls, so they are cleared on the
-// way), and, once validity is known (vmask: one bit per list position), list the non-inherited tokens whose nearest
-// inherited representative was removed -- their maximum over the VALID representatives (step 8) is not the one the tiles
-// accumulated -- and clear their gamma for the recomputation.  hit(t): list position of the token's earliest hit, HIT_NONE
-// if it has none (or it is not known), HIT_INHERITED if the token is on the list.  (Kept out of the way of steps without a
-// gamma output: the update is code that a launch runs once, and what has to be fetched of it is time, 0.6 us when this was
-// woven into it.)
-enum { HIT_NONE = -1, HIT_INHERITED = -2 };
-template <int THREADS, typename Hit>
-__device__ inline void gamma_fix_collect(const FusedParams& p, int r, const uint32_t* vmask, Hit hit) {
-    __shared__ int s_fix, s_far;
-    const int tid = step_tid(p);
-    if (tid == 0) s_fix = s_far = 0;
-    __syncthreads();
-    auto valid = [&](int pos) { return (vmask[pos >> 5] >> (pos & 31)) & 1u; };
-    auto one = [&](int t, unsigned long long key) {
-        if (t >= p.T) return;
-        if (key != 0ull) p.best[t] = 0ull;
-        float m = __uint_as_float((uint32_t)(key >> 32));
-        if (key != 0ull && !valid(min(max(INT_MAX - (int)(uint32_t)key, 0), r - 1))) {
-            const int h = hit(t);
-            if (h != HIT_INHERITED) {
-                if (h != HIT_NONE && valid(h)) p.fix_list[atomicAdd(&s_fix, 1)] = t;
-                else p.fix_list[p.T - 1 - atomicAdd(&s_far, 1)] = t;
-                m = 0.f;                                 // empty max: the recomputation accumulates into it
-            }
-        }
-        p.gamma[t] = m;
-    };
-    for (int base = tid; base < p.T; base += 4 * THREADS) {                 // four keys per thread in flight per trip
-        const int t0 = base, t1 = base + THREADS, t2 = base + 2 * THREADS, t3 = base + 3 * THREADS;
-        const unsigned long long k0 = p.best[min(t0, p.T - 1)], k1 = p.best[min(t1, p.T - 1)];
-        const unsigned long long k2 = p.best[min(t2, p.T - 1)], k3 = p.best[min(t3, p.T - 1)];
-        one(t0, k0);
-        one(t1, k1);
-        one(t2, k2);
-        one(t3, k3);
-    }
-    uint32_t* flags = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(p.fix_meta) - align_up((size_t)p.T, 256));   // (see carve)
-    for (int w = tid; w < (r + 31) >> 5; w += THREADS) flags[w] = vmask[w];
-    __syncthreads();
-    if (tid == 0) {
-        p.fix_meta[META_R] = r;
-        p.fix_meta[META_NONREP] = s_far;
-        p.fix_meta[META_FIX] = s_fix;
-        p.fix_meta[META_STATUS] = ADA_OK;
-    }
-}
-// A rejected step: gamma and the table are cleared, the lists are empty.
-template <int THREADS>
-__device__ inline void gamma_fix_none(const FusedParams& p) {
-    const int tid = step_tid(p);
-#pragma unroll 1
-    for (int t = tid; t < p.T; t += THREADS) { p.best[t] = 0ull; p.gamma[t] = 0.f; }
-    if (tid < 4) p.fix_meta[tid == 0 ? META_R : tid == 1 ? META_NONREP : tid == 2 ? META_FIX : META_STATUS] = tid == 3 ? ADA_OK : 0;
-}
+// What the update leaves in LDS for gamma_fix: per token bit 0 = inherited, bit 1 = kept, from the start; the validity bits from here.
+constexpr int UPDATE_VALID = FUSED_MAX_T * 2;
 
 // Algorithm 1 steps 5, 9, 10 from the first-hit records.  For every token the tiles left, next to its hit words, the
 // smallest list position of a representative that hits it (p.first).  That decides almost everything:
@@ -1453,7 +1398,7 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
     const int T = p.T, T4 = (T + 3) >> 2;               // (up to three records past the end: padding, always zero)
     const int Wa = (r + 31) >> 5;
     uint16_t* pos = reinterpret_cast<uint16_t*>(lds);                        // [T] list position of an inherited token
-    uint32_t* vmask = reinterpret_cast<uint32_t*>(lds + FUSED_MAX_T * 2);    // [Wa] valid bits by list position
+    uint32_t* vmask = reinterpret_cast<uint32_t*>(lds + UPDATE_VALID);       // [Wa] valid bits by list position
     u32x4 key[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
@@ -1482,7 +1427,6 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
     }
     ok = __syncthreads_and(ok);
     if (!ok) {
-        if (p.fix_list) gamma_fix_none<THREADS>(p);
         if (tid == 0) {
             p.counts[0] = 0; p.counts[1] = 0; p.counts[2] = 0; p.counts[3] = ADA_ERR_INDEX;
             if (p.gram_ops) *p.gram_ops = 0ull;
@@ -1506,18 +1450,6 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
         }
     }
     __syncthreads();
-    if (__builtin_expect(p.fix_list != nullptr, 0)) {    // gamma output (uniform)
-        // a token's earliest hit, marked by the top bit, where an inherited token has its place
-#pragma unroll
-        for (int i = 0; i < U; ++i)
-            if (jpos[i] == 0xFFFF && key[i >> 2][i & 3] != 0u)
-                pos[U * tid + i] = (uint16_t)(0x8000u | min(0xFFFFFFFFu - key[i >> 2][i & 3], (uint32_t)(r - 1)));
-        __syncthreads();
-        gamma_fix_collect<THREADS>(p, r, vmask, [&](int t) {
-            const int j = pos[t];
-            return j == 0xFFFF ? (int)HIT_NONE : j & 0x8000 ? j & 0x7FFF : (int)HIT_INHERITED;
-        });
-    }
     // step 9: any other token with a hit on a VALID representative is covered
     bool f[3][U];                                        // in R^(l+1) | added | removed
 #pragma unroll
@@ -1567,6 +1499,19 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
         }
         reset_tickets(p.ticket);
     }
+    if (__builtin_expect(p.fix_list != nullptr, 0)) {    // gamma output (uniform); nobody reads list positions any more
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const int t4 = tid * NV + v;
+            uint32_t f4 = 0u;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = 4 * v + u;
+                f4 |= (uint32_t)((f[0][i] ? 2 : 0) | (f[2][i] || (f[0][i] && !f[1][i]) ? 1 : 0)) << (8 * u);
+            }
+            if (t4 < T4) reinterpret_cast<uint32_t*>(lds)[t4] = f4;
+        }
+    }
     return n_idx;
 }
 
@@ -1584,7 +1529,7 @@ __device__ __forceinline__ int fused_update(const FusedParams& p, int r, bool r_
         return fused_update_rec<THREADS, 8>(p, r, q0, qp0, lds, scan_scratch);
     }
     uint8_t* flag = reinterpret_cast<uint8_t*>(lds);                         // [T]
-    uint32_t* vmask = reinterpret_cast<uint32_t*>(lds + FUSED_MAX_T);        // one bit per inherited representative: valid
+    uint32_t* vmask = reinterpret_cast<uint32_t*>(lds + UPDATE_VALID);       // one bit per inherited representative: valid
     const int Wa = r_ok ? (r + 31) >> 5 : 0;            // hit words in use per token
     for (int t = tid; t < T; t += THREADS) flag[t] = 2;                      // not inherited, kept unless covered
     // the token pass's first batch of hit words does not depend on the validity mask: fetch it now, use it later
@@ -1642,10 +1587,7 @@ __device__ __forceinline__ int fused_update(const FusedParams& p, int r, bool r_
     }
     ok = __syncthreads_and(ok);
     const int status = !r_ok ? ADA_ERR_SHAPE : (!ok ? ADA_ERR_INDEX : ADA_OK);
-    if (p.fix_list && status == ADA_OK)                  // (gamma output only)
-        gamma_fix_collect<THREADS>(p, r, vmask, [&](int t) { return (int)(flag[t] & 1 ? HIT_INHERITED : HIT_NONE); });
     if (status != ADA_OK) {
-        if (p.fix_list) gamma_fix_none<THREADS>(p);
         if (tid == 0) {
             p.counts[0] = 0; p.counts[1] = 0; p.counts[2] = 0; p.counts[3] = status;
             if (p.gram_ops) *p.gram_ops = 0ull;
@@ -1738,6 +1680,58 @@ __device__ __forceinline__ int fused_update(const FusedParams& p, int r, bool r_
         reset_tickets(p.ticket);                                    // leave the workspace ready for the next call
     }
     return n_idx;
+}
+
+// gamma for callers that ask for it, behind the update: unpack the tiles' keys (the table is zero between calls, so they are
+// cleared on the way) and list the tokens outside the inherited set whose nearest inherited representative was removed -- their
+// maximum over the VALID representatives (step 8) is not the one the tiles accumulated -- with their gamma cleared for the
+// recomputation.  ok == false: a rejected step, gamma and the table are cleared, the lists are empty.
+// (Once per kernel and out of the way of steps without a gamma output: the update is code that a launch runs once, and what has to
+// be fetched of it is time.)
+template <int THREADS>
+__device__ inline void gamma_fix(const FusedParams& p, int r, bool ok, const char* lds) {
+    __shared__ int s_len;                                // covered ones, and 2^16 new ones
+    const uint8_t* flag = reinterpret_cast<const uint8_t*>(lds);
+    const uint32_t* vmask = reinterpret_cast<const uint32_t*>(lds + UPDATE_VALID);
+    const int tid = step_tid(p), last = ok ? r - 1 : 0;
+    if (tid == 0) s_len = 0;
+    __syncthreads();
+    for (int base = tid; base < p.T; base += 4 * THREADS) {                 // four tokens per thread in flight, to memory and in LDS
+        unsigned long long key[4];
+        int kind[4];                                     // what the token adds to s_len
+#pragma unroll
+        for (int q = 0; q < 4; ++q) key[q] = p.best[min(base + q * THREADS, p.T - 1)];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int t = min(base + q * THREADS, p.T - 1), pos = min(max(INT_MAX - (int)(uint32_t)key[q], 0), last);
+            const int f = flag[t];
+            const bool lost = ok && base + q * THREADS < p.T && key[q] != 0ull && !(f & 1) && !(vmask[pos >> 5] >> (pos & 31) & 1u);
+            kind[q] = !lost ? 0 : f == 0 ? 1 : 1 << 16;
+        }
+        const int add = kind[0] + kind[1] + kind[2] + kind[3];
+        int at = 0;
+        asm volatile("" : "+v"(at));                     // (at an address known to be uniform the lanes would be summed first, one by one)
+        if (add) at = atomicAdd(&s_len + at, add);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int t = base + q * THREADS;
+            if (kind[q]) p.fix_list[kind[q] == 1 ? at & 0xFFFF : p.T - 1 - (at >> 16)] = t;
+            at += kind[q];
+            if (t < p.T) {
+                if (key[q] != 0ull) p.best[t] = 0ull;
+                p.gamma[t] = kind[q] || !ok ? 0.f : __uint_as_float((uint32_t)(key[q] >> 32));
+            }
+        }
+    }
+    if (ok)
+        for (int w = tid; w < (r + 31) >> 5; w += THREADS) p.fix_valid[w] = vmask[w];
+    __syncthreads();
+    if (tid == 0) {
+        p.fix_meta[META_R] = ok ? r : 0;
+        p.fix_meta[META_NONREP] = s_len >> 16;
+        p.fix_meta[META_FIX] = s_len & 0xFFFF;
+        p.fix_meta[META_STATUS] = ADA_OK;
+    }
 }
 
 // Section 2.3, last step (run by one workgroup): unpack the per-token arg max, make every member of R its own
@@ -1915,7 +1909,10 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_fused(FusedParams p) {
     __syncthreads();
     ADA_CLK_LAST(9);
     if (p.assign_mode) assign_finish<G::THREADS>(p, r, r_ok, q0, qp0);
-    else fused_update<G::THREADS>(p, r, r_ok, q0, qp0, lds + G::META, reinterpret_cast<int*>(lds + G::OFF_SCAN));
+    else {
+        const int r_new = fused_update<G::THREADS>(p, r, r_ok, q0, qp0, lds + G::META, reinterpret_cast<int*>(lds + G::OFF_SCAN));
+        if (__builtin_expect(p.fix_list != nullptr, 0)) gamma_fix<G::THREADS>(p, r, r_new > 0, lds + G::META);   // (a set is never empty)
+    }
     ADA_CLK_LAST(15);
 }
 

@@ -1350,7 +1350,7 @@ int launch_fused_any(const FusedParams& p, int dtype, int prof_class, hipStream_
     return e == hipSuccess ? ADA_OK : ADA_ERR_DEVICE;
 }
 
-// gamma^cross of the tokens whose nearest inherited representative was removed (gamma_fix_collect's lists).
+// gamma^cross of the tokens whose nearest inherited representative was removed (the lists of gamma_fix).
 //   near  tokens that a valid representative hits: any other is further away than those, so the maximum lies among the hits that
 //         the step's tiles left as bits, one as a rule.  One wave per token.
 //   far   the others (new tokens, chains): all valid representatives, in pieces of FIX_REPS products per wave beside the others;
@@ -1488,7 +1488,7 @@ int run_cascade_fused(const void* X, int T, int d, long long ld, int dtype, floa
                      reinterpret_cast<unsigned long long*>(gram_ops), 0, nullptr, nullptr, nullptr, 0, cascade_tile_pick()};
     p.first = w.first;
     if (gamma && !(grp && grp->G > 1)) {                          // Algorithm 1's gamma^cross: see above
-        p.best = w.best; p.fix_list = w.nonrep_idx; p.fix_meta = w.meta; p.inv_norm = w.inv_norm;
+        p.best = w.best; p.fix_list = w.nonrep_idx; p.fix_meta = w.meta; p.fix_valid = reinterpret_cast<uint32_t*>(w.is_rep); p.inv_norm = w.inv_norm;
     }
     if (ctl) {                                                   // Section 8.1: threshold carried on the device
         p.tau_in = tau_in; p.thr_in = thr_in; p.tau_out = tau_out; p.thr_out = thr_out;

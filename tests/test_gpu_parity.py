@@ -1412,6 +1412,35 @@ def test_gamma_of_tokens_whose_nearest_representative_is_removed(T, d, dtype, fl
         step_and_check(x_cpu.to(DEV), x_cpu, tau, inherited, flags, "T=%d d=%d far=%d" % (T, d, far), ws=ws)
 
 
+@pytest.mark.parametrize("T,kgroups", [(5, "2"), (130, "2"), (2048, "2"), (2051, "2"), (4100, "2"), (8200, "2"), (1000, "1"), (8201, "1")])
+def test_gamma_of_tokens_that_a_later_representative_covers(T, kgroups, monkeypatch):
+    """Chains on an arc: a at 0, b at 0.11, t at 0.2 and c at 0.3 rad, a, b, c inherited, pairs up to 0.14 rad apart near.  a removes b, t's
+    nearest and its earliest hit; c, which covers t, is valid.  In every third chain c lies elsewhere, so that t is new and its gamma is
+    that of a.  Lengths on both sides of each form of the update, and a rejected step in between on the same workspace."""
+    monkeypatch.setenv("ADA_KGROUPS", kgroups)
+    say("gamma of chains T=%d kgroups=%s" % (T, kgroups))
+    rng, d, n = np.random.default_rng(T), 64, T // 4
+    u, v = (rng.standard_normal((n, d)) for _ in range(2))
+    u /= np.linalg.norm(u, axis=1, keepdims=True)
+    v -= np.sum(u * v, axis=1, keepdims=True) * u
+    v /= np.linalg.norm(v, axis=1, keepdims=True)
+    X = rng.standard_normal((T, d))
+    order = np.sort(rng.permutation(T)[:4 * n].reshape(n, 4), axis=1)
+    a, b, c, t = order[:, 0], order[:, 1], order[:, 2], order[:, 3]
+    for at, angle in ((a, 0.0), (b, 0.11), (t, 0.2)):
+        X[at] = np.cos(angle) * u + np.sin(angle) * v
+    near = np.arange(n) % 3 != 2
+    X[c[near]] = np.cos(0.3) * u[near] + np.sin(0.3) * v[near]
+    inherited = np.sort(np.concatenate([a, b, c]))
+    x_cpu = wl.to_dtype(X.astype(np.float32), "bf16")
+    x, ws = x_cpu.to(DEV), pa.workspace(T)
+    got, _ = step_and_check(x, x_cpu, 0.1, inherited, 0, "chains T=%d" % T, ws=ws)
+    assert set(b) <= set(got["removes"]) and set(t[~near]) <= set(got["adds"]) and not set(t[near]) & set(got["idx"])
+    bad = pa.ada_cascade_step(x, 0.1, dev_idx(inherited[::-1].copy()), ws=ws)
+    assert bad["counts"].cpu().tolist() == [0, 0, 0, 4] and not bool(bad["gamma"].any())     # ADA_ERR_INDEX
+    step_and_check(x, x_cpu, 0.1, inherited, 0, "chains T=%d, again" % T, ws=ws)
+
+
 @pytest.mark.parametrize("T,d,K,dtype", [(1, 8, 1, "bf16"), (31, 9, 5, "bf16"), (33, 4, 6, "f32"), (64, 97, 9, "f32"), (130, 64, 17, "bf16"),
                                          (333, 1001, 40, "bf16"), (512, 768, 100, "f32"), (700, 4096, 120, "bf16"), (1290, 130, 300, "f32")])
 def test_small_shapes_one_launch_cascade_on_quarter_tiles(T, d, K, dtype, monkeypatch):
