@@ -1382,6 +1382,67 @@ __device__ inline void block_rank3(const bool (&f)[3][U], int (&below)[3], int (
 // What the update leaves in LDS for gamma_fix: per token bit 0 = inherited, bit 1 = kept, from the start; the validity bits from here.
 constexpr int UPDATE_VALID = FUSED_MAX_T * 2;
 
+// gamma for callers that ask for it: unpack the tiles' keys (the table is zero between calls, so they are cleared on the way)
+// and list the tokens outside the inherited set whose nearest inherited representative was removed -- their maximum over the
+// VALID representatives (step 8) is not the one the tiles accumulated -- with their gamma cleared for the recomputation.
+// ok == false: a rejected step, gamma and the table are cleared, the lists are empty.
+// Bound by its chain: keys, validity, and where a nearest one was removed class, place in the list and list.  Four tokens per thread go
+// through it together and take one place for all (before, one after the other: steps of T=4096 and 100 to 370 such tokens 1.5 us slower).
+// It stands behind the ranks and in front of the lists' stores: its loads would wait for those (0.4 to 1 us).
+template <int THREADS>
+__device__ inline void gamma_fix(const FusedParams& p, int r, bool ok, const char* lds) {
+    __shared__ int s_len;                                // covered ones, and 2^16 new ones
+    const uint8_t* flag = reinterpret_cast<const uint8_t*>(lds);
+    const uint32_t* vmask = reinterpret_cast<const uint32_t*>(lds + UPDATE_VALID);
+    const int tid = step_tid(p), last = ok ? r - 1 : 0;
+    if (tid == 0) s_len = 0;
+    __syncthreads();
+    for (int base = tid; base < p.T; base += 4 * THREADS) {                 // four tokens per thread in flight, to memory and in LDS
+        unsigned long long key[4];
+        bool lost[4], any = false;                       // the nearest one was removed
+#pragma unroll
+        for (int q = 0; q < 4; ++q) key[q] = p.best[min(base + q * THREADS, p.T - 1)];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int pos = min(max(INT_MAX - (int)(uint32_t)key[q], 0), last);
+            lost[q] = ok && base + q * THREADS < p.T && key[q] != 0ull && !(vmask[pos >> 5] >> (pos & 31) & 1u);
+            any |= lost[q];
+        }
+        if (any) {
+            int kind[4], at = 0;                         // kind: what the token adds to s_len
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int f = flag[min(base + q * THREADS, p.T - 1)];
+                lost[q] = lost[q] && !(f & 1);
+                kind[q] = !lost[q] ? 0 : f == 0 ? 1 : 1 << 16;
+            }
+            asm volatile("" : "+v"(at));                 // (at an address known to be uniform the lanes would be summed first, one by one)
+            at = atomicAdd(&s_len + at, kind[0] + kind[1] + kind[2] + kind[3]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (kind[q]) p.fix_list[kind[q] == 1 ? at & 0xFFFF : p.T - 1 - (at >> 16)] = base + q * THREADS;
+                at += kind[q];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int t = base + q * THREADS;
+            if (t >= p.T) break;
+            if (key[q] != 0ull) p.best[t] = 0ull;
+            p.gamma[t] = lost[q] || !ok ? 0.f : __uint_as_float((uint32_t)(key[q] >> 32));
+        }
+    }
+    if (ok)
+        for (int w = tid; w < (r + 31) >> 5; w += THREADS) p.fix_valid[w] = vmask[w];
+    __syncthreads();
+    if (tid == 0) {
+        p.fix_meta[META_R] = ok ? r : 0;
+        p.fix_meta[META_NONREP] = s_len >> 16;
+        p.fix_meta[META_FIX] = s_len & 0xFFFF;
+        p.fix_meta[META_STATUS] = ADA_OK;
+    }
+}
+
 // Algorithm 1 steps 5, 9, 10 from the first-hit records.  For every token the tiles left, next to its hit words, the
 // smallest list position of a representative that hits it (p.first).  That decides almost everything:
 //   * an inherited representative is valid (step 5) iff it has no hit at all (its words hold earlier ones only);
@@ -1427,6 +1488,7 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
     }
     ok = __syncthreads_and(ok);
     if (!ok) {
+        if (p.fix_list) gamma_fix<THREADS>(p, r, false, lds);
         if (tid == 0) {
             p.counts[0] = 0; p.counts[1] = 0; p.counts[2] = 0; p.counts[3] = ADA_ERR_INDEX;
             if (p.gram_ops) *p.gram_ops = 0ull;
@@ -1480,6 +1542,20 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
     }
     int below[3], tot[3];
     block_rank3<THREADS, U>(f, below, tot, scan_scratch);
+    if (__builtin_expect(p.fix_list != nullptr, 0)) {    // gamma output (uniform); nobody reads list positions any more
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const int t4 = tid * NV + v;
+            uint32_t f4 = 0u;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = 4 * v + u;
+                f4 |= (uint32_t)((f[0][i] ? 2 : 0) | (f[2][i] || (f[0][i] && !f[1][i]) ? 1 : 0)) << (8 * u);
+            }
+            if (t4 < T4) reinterpret_cast<uint32_t*>(lds)[t4] = f4;
+        }
+        gamma_fix<THREADS>(p, r, true, lds);
+    }
     int o_idx = below[0], o_add = below[1], o_rem = below[2];
     const int n_idx = tot[0], n_add = tot[1], n_rem = tot[2];
 #pragma unroll
@@ -1498,19 +1574,6 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
             *p.gram_ops = rr * rr + (TT - rr) * (unsigned long long)(r - n_rem);   // entries Algorithm 1 needs
         }
         reset_tickets(p.ticket);
-    }
-    if (__builtin_expect(p.fix_list != nullptr, 0)) {    // gamma output (uniform); nobody reads list positions any more
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            const int t4 = tid * NV + v;
-            uint32_t f4 = 0u;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int i = 4 * v + u;
-                f4 |= (uint32_t)((f[0][i] ? 2 : 0) | (f[2][i] || (f[0][i] && !f[1][i]) ? 1 : 0)) << (8 * u);
-            }
-            if (t4 < T4) reinterpret_cast<uint32_t*>(lds)[t4] = f4;
-        }
     }
     return n_idx;
 }
@@ -1588,6 +1651,7 @@ __device__ __forceinline__ int fused_update(const FusedParams& p, int r, bool r_
     ok = __syncthreads_and(ok);
     const int status = !r_ok ? ADA_ERR_SHAPE : (!ok ? ADA_ERR_INDEX : ADA_OK);
     if (status != ADA_OK) {
+        if (p.fix_list) gamma_fix<THREADS>(p, r, false, lds);
         if (tid == 0) {
             p.counts[0] = 0; p.counts[1] = 0; p.counts[2] = 0; p.counts[3] = status;
             if (p.gram_ops) *p.gram_ops = 0ull;
@@ -1650,6 +1714,7 @@ __device__ __forceinline__ int fused_update(const FusedParams& p, int r, bool r_
     }
     __syncthreads();
     ADA_CLK_LAST(13);
+    if (p.fix_list) gamma_fix<THREADS>(p, r, true, lds);
     const int chunk = (T + THREADS - 1) / THREADS;
     const int lo = min(T, tid * chunk), hi = min(T, lo + chunk);
     unsigned long long c = 0;                            // kept | added << 21 | removed << 42
@@ -1680,58 +1745,6 @@ __device__ __forceinline__ int fused_update(const FusedParams& p, int r, bool r_
         reset_tickets(p.ticket);                                    // leave the workspace ready for the next call
     }
     return n_idx;
-}
-
-// gamma for callers that ask for it, behind the update: unpack the tiles' keys (the table is zero between calls, so they are
-// cleared on the way) and list the tokens outside the inherited set whose nearest inherited representative was removed -- their
-// maximum over the VALID representatives (step 8) is not the one the tiles accumulated -- with their gamma cleared for the
-// recomputation.  ok == false: a rejected step, gamma and the table are cleared, the lists are empty.
-// (Once per kernel and out of the way of steps without a gamma output: the update is code that a launch runs once, and what has to
-// be fetched of it is time.)
-template <int THREADS>
-__device__ inline void gamma_fix(const FusedParams& p, int r, bool ok, const char* lds) {
-    __shared__ int s_len;                                // covered ones, and 2^16 new ones
-    const uint8_t* flag = reinterpret_cast<const uint8_t*>(lds);
-    const uint32_t* vmask = reinterpret_cast<const uint32_t*>(lds + UPDATE_VALID);
-    const int tid = step_tid(p), last = ok ? r - 1 : 0;
-    if (tid == 0) s_len = 0;
-    __syncthreads();
-    for (int base = tid; base < p.T; base += 4 * THREADS) {                 // four tokens per thread in flight, to memory and in LDS
-        unsigned long long key[4];
-        int kind[4];                                     // what the token adds to s_len
-#pragma unroll
-        for (int q = 0; q < 4; ++q) key[q] = p.best[min(base + q * THREADS, p.T - 1)];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int t = min(base + q * THREADS, p.T - 1), pos = min(max(INT_MAX - (int)(uint32_t)key[q], 0), last);
-            const int f = flag[t];
-            const bool lost = ok && base + q * THREADS < p.T && key[q] != 0ull && !(f & 1) && !(vmask[pos >> 5] >> (pos & 31) & 1u);
-            kind[q] = !lost ? 0 : f == 0 ? 1 : 1 << 16;
-        }
-        const int add = kind[0] + kind[1] + kind[2] + kind[3];
-        int at = 0;
-        asm volatile("" : "+v"(at));                     // (at an address known to be uniform the lanes would be summed first, one by one)
-        if (add) at = atomicAdd(&s_len + at, add);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int t = base + q * THREADS;
-            if (kind[q]) p.fix_list[kind[q] == 1 ? at & 0xFFFF : p.T - 1 - (at >> 16)] = t;
-            at += kind[q];
-            if (t < p.T) {
-                if (key[q] != 0ull) p.best[t] = 0ull;
-                p.gamma[t] = kind[q] || !ok ? 0.f : __uint_as_float((uint32_t)(key[q] >> 32));
-            }
-        }
-    }
-    if (ok)
-        for (int w = tid; w < (r + 31) >> 5; w += THREADS) p.fix_valid[w] = vmask[w];
-    __syncthreads();
-    if (tid == 0) {
-        p.fix_meta[META_R] = ok ? r : 0;
-        p.fix_meta[META_NONREP] = s_len >> 16;
-        p.fix_meta[META_FIX] = s_len & 0xFFFF;
-        p.fix_meta[META_STATUS] = ADA_OK;
-    }
 }
 
 // Section 2.3, last step (run by one workgroup): unpack the per-token arg max, make every member of R its own
@@ -1909,10 +1922,7 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_fused(FusedParams p) {
     __syncthreads();
     ADA_CLK_LAST(9);
     if (p.assign_mode) assign_finish<G::THREADS>(p, r, r_ok, q0, qp0);
-    else {
-        const int r_new = fused_update<G::THREADS>(p, r, r_ok, q0, qp0, lds + G::META, reinterpret_cast<int*>(lds + G::OFF_SCAN));
-        if (__builtin_expect(p.fix_list != nullptr, 0)) gamma_fix<G::THREADS>(p, r, r_new > 0, lds + G::META);   // (a set is never empty)
-    }
+    else fused_update<G::THREADS>(p, r, r_ok, q0, qp0, lds + G::META, reinterpret_cast<int*>(lds + G::OFF_SCAN));
     ADA_CLK_LAST(15);
 }
 
