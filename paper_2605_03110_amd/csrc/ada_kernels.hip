@@ -1353,9 +1353,8 @@ int launch_fused_any(const FusedParams& p, int dtype, int prof_class, hipStream_
 // gamma^cross of the tokens whose nearest inherited representative was removed (the lists of gamma_fix).
 //   near  tokens that a valid representative hits: any other is further away than those, so the maximum lies among the hits that
 //         the step's tiles left as bits, one as a rule.  One wave per token.
-//   far   the others (new tokens, chains): all valid representatives, in pieces of FIX_REPS products per wave beside the others;
-//         on the tiles of the step's other form where that is more than FIX_PAIRS products (both ways' time grows with the rows'
-//         length; T=4096, d=512, r=980, 17 to 40 such tokens: steps of 33.3 us by products, 36.0 by tiles).
+//   far   the others (new tokens): all valid representatives, in pieces of FIX_REPS products per wave beside the others; on the
+//         tiles of the step's other form where that is more products than fix_pairs.
 // A chain of trips (scalars and list entry, hit words, representative, rows), and code that is fetched as it runs: the products of the
 // far ones in straight lines took 2 us longer.  Steps, us, all of them on the tiles -> now: T=3001, d=1000, K=600 34.9 -> 28.5 (31.0 with
 // far ones), T=2048, d=4096, K=400 52 -> 34.5 (38.5), fp32 T=2048, d=768 50 -> 32.5 (34.4), T=4096, d=512, K=1000 34.3 -> 31 (33.3).
@@ -1364,7 +1363,18 @@ struct GammaFix {
     const uint32_t* valid;
     int grid;                  // of the launch
 };
-constexpr int FIX_PAIRS = 49152, FIX_REPS = 8;
+constexpr int FIX_REPS = 8;
+
+// Products of far tokens and representatives up to which they are formed one by one.  A product reads its representative's row
+// from the L2 and beyond, its cost grows with the row; a round of tiles costs 3 us more to start and grows half as fast.  Steps of T=4096, us,
+// products against tiles: bf16 d=512, 40 thousand products 38.2, 38.9; d=1024, 26 thousand 45.7, 48.0, 57 thousand 52.0, 48.4; d=2048,
+// 8 thousand 37.3, 45.2, 19 thousand 67.4, 67.0, 40 thousand 75.5, 66.9; d=4096, 10 thousand 97.1, 102.6, 34 thousand 91.0, 79.1.  fp32,
+// whose tiles take twice as long: d=512, 45 thousand 107.4, 111.6; d=1024, 39 thousand 106.7, 114.0, 56 thousand 194.5, 187.9; d=2048,
+// 24 thousand 323.4, 339.8, 47 thousand 344.7, 340.0.
+__host__ __device__ inline int fix_pairs(int d, size_t esz) {
+    const int line = (esz == 4 ? 32768 : 16384) + (12 << 20) / d;
+    return line < 49152 ? line : 49152;
+}
 
 // <x, y> by LPR neighbouring lanes, UN pieces of each row in flight per lane; every lane gets it.  (Kept short: a launch of a few
 // microseconds waits for every line of code that it runs for the first time.)
@@ -1402,7 +1412,7 @@ __global__ __launch_bounds__(256) void k_gamma_fix(GramParams p, GammaFix f) {
     const int Wa = (r + 31) >> 5;
     auto row = [&](int t) { return X + (size_t)t * (size_t)p.ld; };
     const int32_t* list = p.nonrep_idx + (p.T - far);
-    const bool tiles = (long long)far * r > FIX_PAIRS;
+    const bool tiles = (long long)far * r > fix_pairs(p.d, sizeof(In));
     const int pieces = (r + 4 * FIX_REPS - 1) / (4 * FIX_REPS), near4 = (near + 3) / 4, items = near4 + (tiles ? 0 : far * pieces);
     for (int i = wg; i < items; i += f.grid) {                // (uniform)
         float best = 0.f;
