@@ -421,12 +421,35 @@ def test_full_selection_on_the_graph_of_near_pairs(kind, T, d, dtype, tau, greed
             assert np.array_equal(step["idx"], got["idx"]) or kind in ("loose", "common")   # (chains: a removed token covers nobody)
 
 
-@pytest.mark.parametrize("T,d,L,groups,dtype", [(2050, 4096, 13, 1, "bf16"),   # 64 lanes per row, two rows each, and past the caches
-                                                (2049, 512, 51, 1, "f32"), (4097, 192, 131, 1, "bf16"), (2047, 1024, 52, 1, "bf16"),
-                                                (8190, 128, 60, 2, "bf16")])
-def test_large_inputs_give_what_small_ones_give(T, d, L, groups, dtype):
-    """Layers of a call on 200 MB and more are read past the caches and their pairs in whole strips; the same layers two at a time, each
-    call going on from a full selection, must give the same sets wherever both start from the same one: layers 0 and 1 of every pair."""
+def exact_pass(T, d, L, groups, esz, tau):
+    """How k_screen_exact reads the layers of a call (run_layers_screened, launch_screen, launch_screen_exact and screen_streams of csrc/):
+    lanes per row, rows per lane group, and whether X goes past the caches.  Rows and matrices start on whole cache lines."""
+    from test_screen_replay import plan                       # (which imports this module)
+
+    def up(n):
+        return (n + 255) // 256 * 256
+    unit = up(544 * 4 + 3 * up(4 * T) + up(2 * T) + up((T + 63) // 64 * 16) + up((T // 2 + 65) // 2 * 2 * 8) + (T + 31) // 32 * plan(d, tau)[0] * 2048)
+    fit = min(min(up(T * 8192 + 65536), 31 << 19) // unit, 64)
+    batches = -(-L // fit)
+    units = groups * -(-L // batches)
+    pieces = (d * esz + 15) // 16
+    lanes = 64 if pieces >= 256 else 32 if pieces >= 128 else 16 if pieces >= 64 else 8
+    rows = 2 if T // (4 * (256 // lanes)) * units >= 2048 else 1
+    return lanes, rows, d * esz % 128 == 0 and units * T * d * esz >= 192 << 20
+
+
+@pytest.mark.parametrize("T,d,L,groups,dtype,form", [
+    (2050, 4096, 16, 1, "bf16", (64, 2, True)), (2050, 4096, 13, 1, "bf16", (64, 1, True)), (2047, 1024, 52, 1, "bf16", (32, 2, True)),
+    (2049, 512, 51, 1, "f32", (32, 2, True)), (1030, 1984, 25, 2, "bf16", (32, 1, True)), (4097, 512, 25, 2, "bf16", (16, 2, True)),
+    (2050, 960, 26, 2, "bf16", (16, 1, True)), (8190, 128, 20, 5, "bf16", (8, 2, True)), (4100, 448, 14, 4, "bf16", (8, 1, True)),
+    (4097, 192, 131, 1, "bf16", (8, 1, False)), (8190, 128, 60, 2, "bf16", (8, 2, False))])
+def test_large_inputs_give_what_small_ones_give(T, d, L, groups, dtype, form):
+    """A launch on 192 MB and more reads its layers past the caches; the first two layers alone, which do not, must give the same sets, and
+    every later layer what a step of its own gives from the call's previous set (one launch, no graph).  Every number of lanes per row
+    with one and two rows per lane group (form: what the case runs), and calls cut into launches that are small again."""
+    print("[case] large inputs: T=%d d=%d L=%d G=%d %s" % (T, d, L, groups, dtype), flush=True)
+    assert exact_pass(T, d, L, groups, 2 if dtype == "bf16" else 4, 0.1) == form
+    assert not exact_pass(T, d, 2, groups, 2 if dtype == "bf16" else 4, 0.1)[2]
     gen = torch.Generator(device=DEV).manual_seed(T)
     K = T // 7
     C = torch.nn.functional.normalize(torch.randn(K, d, generator=gen, device=DEV), dim=1)
