@@ -365,8 +365,8 @@ int ada_cascade_layers_adaptive(const void* const* X_layers, int L, int T, int d
 /*
  * Which tile shape a one-launch cascade step takes when `workgroups` workgroups share its tiles (the CU count for a
  * single problem; that divided by the number of groups for a grouped call) and the rows come in whole aligned
- * 128-byte chunks of bf16: 0 = 64 x 64 (in quarters where each of those has a workgroup of its own), 1 = 64 representatives x 128 tokens, 2 = 128 x 128, 3 = 128 representatives x
- * 256 tokens; -1 for arguments out of range.
+ * 128-byte chunks of bf16: 0 = 64 x 64 (in quarters where d <= 1024 and each of those has a workgroup of its own),
+ * 1 = 64 representatives x 128 tokens, 2 = 128 x 128, 3 = 128 representatives x 256 tokens; -1 for arguments out of range.
  * Host only (no device is touched): the same function the kernel evaluates with the set size it finds.
  */
 int ada_plan_tile_shape(int r, int T, int d, int workgroups);
