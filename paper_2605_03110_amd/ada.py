@@ -58,6 +58,17 @@ class AdaError(RuntimeError):
 # workgroup's code), so the build refuses it instead of letting a benchmark find out.
 SCRATCH_BUDGET = {
     "k_cascade_fusedItLb1ELi2ELi1E": 64,       # bf16, aligned rows, two K-groups, direct-to-LDS: the cascade step
+    "k_cascade_fusedItLb1ELi2ELi2E": 0,        # the same with a last piece that is a part of one, on tiles of 32 x 32, and in fp32
+    "k_cascade_fusedItLb1ELi2ELi3E": 0,
+    "k_cascade_fusedIfLb1ELi2ELi1E": 0,
+    "k_cascade_fusedIfLb1ELi2ELi2E": 0,
+    "k_cascade_fusedIfLb1ELi2ELi3E": 0,
+    "k_gamma_fixI": 0,                         # a step's gamma output
+    "k_screen_sketchI": 0,                     # the graph of near pairs
+    "k_screen_pairsI": 0,
+    "k_screen_exactI": 0,
+    "k_screen_restI": 0,
+    "k_screen_chainI": 0,
     "k_cascade_passI": 0,                      # all steps in one launch: what is spilled there is paid for at every step
     "k_cascade_restItLb1ELi2ELi2E": 0,         # layers that the graph of near pairs leaves to the tiles
     "k_cascade_restIfLb1ELi2ELi2E": 16,
