@@ -83,17 +83,25 @@ def cpu_baseline_extras():
     return out
 
 
-def call_us(call, n):
-    """Time of a call among others: one pair of events around n of them (a pair around every kernel of a call adds its own
-    gaps, a third to two thirds of the time where a call is eight short launches)."""
+def call_spread(call, n, pairs=7):
+    """Time of a call among others, us: median and largest over `pairs` pairs of events around n calls each (a pair around every
+    kernel of a call adds its own gaps, a third to two thirds of the time where a call is eight short launches).  A host that stalls
+    shows in the largest alone, a call that runs another way in both."""
     import torch
-    first, last = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    first.record()
-    for _ in range(n):
-        call()
-    last.record()
-    last.synchronize()
-    return 1e3 * first.elapsed_time(last) / n
+    got = []
+    for _ in range(pairs):
+        first, last = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        first.record()
+        for _ in range(n):
+            call()
+        last.record()
+        last.synchronize()
+        got.append(1e3 * first.elapsed_time(last) / n)
+    return sorted(got)[pairs // 2], max(got)
+
+
+def call_us(call, n):
+    return call_spread(call, n)[0]
 
 
 def recorded_traffic(name):
@@ -495,11 +503,11 @@ def main():
             for _ in range(2):
                 oo = pa.ada_cascade_layers(xo, wo.tau, ws=wso, stream=stream, want_lists=False)
             torch.cuda.synchronize()
-            us_o = call_us(lambda: pa.ada_cascade_layers(xo, wo.tau, ws=wso, stream=stream, want_lists=False, out=oo), 5) / len(xo)
+            us_o, slowest = (us / len(xo) for us in call_spread(lambda: pa.ada_cascade_layers(xo, wo.tau, ws=wso, stream=stream, want_lists=False, out=oo), 5))
             by = wo.T * wo.d * (2 if wo.dtype == "bf16" else 4)
             r_in = float(oo["counts"][:-1, 0].float().mean())         # the sets the timed steps inherited
             other[wo.name] = {"T": wo.T, "d": wo.d, "mean_r": float(oo["counts"][1:, 0].float().mean()),
-                              "mean_r_inherited": r_in, "us_per_layer": us_o,
+                              "mean_r_inherited": r_in, "us_per_layer": us_o, "us_per_layer_slowest": slowest,
                               "hbm_frac": by / (1e-6 * us_o) / 1e9 / HBM_PEAK_GBS}
             del xo, wso, oo
         # configs[4] as the configuration states it: a batch of four sequences, here stacked in one tensor with one
@@ -515,11 +523,11 @@ def main():
             for _ in range(2):
                 o4 = pa.ada_cascade_layers_grouped(x4g, w4b.tau, ws=ws4g, stream=stream, want_lists=False, out=o4)
             torch.cuda.synchronize()
-            us_g = call_us(lambda: pa.ada_cascade_layers_grouped(x4g, w4b.tau, ws=ws4g, stream=stream, want_lists=False, out=o4), 4) / L4
+            us_g, slowest = (us / L4 for us in call_spread(lambda: pa.ada_cascade_layers_grouped(x4g, w4b.tau, ws=ws4g, stream=stream, want_lists=False, out=o4), 4))
             by4 = B4 * w4b.T * w4b.d * 2
             other[w4b.name + "_batch4_stacked"] = {"T": w4b.T, "d": w4b.d, "sequences": B4,
                                                    "mean_r": float(o4["counts"][:, 1:, 0].float().mean()),
-                                                   "us_per_layer": us_g, "us_per_layer_and_sequence": us_g / B4,
+                                                   "us_per_layer": us_g, "us_per_layer_slowest": slowest, "us_per_layer_and_sequence": us_g / B4,
                                                    "hbm_frac": by4 / (1e-6 * us_g) / 1e9 / HBM_PEAK_GBS}
             # the configuration's own schedule on these layers: the cascade at every layer, and the full T x T selection
             # of all four sequences at layer 0 and at every 8th layer (here: layers 0 and L4 - 1 stand for 0 and 8)
