@@ -1129,7 +1129,7 @@ hipError_t launch_attn_regs(const AttnParams& p, const Layers& layers, int n_lay
 }
 
 // Outputs of 192 MB and more are not kept: with the Q, K and V that pass through it beside them the Infinity Cache (256 MB)
-// holds little of them for whoever reads them next.  Smaller ones a reader does find there, and stored past it he pays what the
+// holds little of them for whoever reads them next.  Smaller ones a reader does find there, and stored past it that reader pays what the
 // call gains, and more.  Pipelines of T=2048, 16 heads x 256 and of T=8192, us, cached -> streamed, alone and with a copy of the outputs to bf16
 // behind the call: 4 layers (128 MB) 159 -> 146 and 196.3 -> 199.7, 5 (160 MB) 167 -> 156 and 214.2 -> 214.2, 6 (192 MB) 213 -> 202 and
 // 272.1 -> 270.2, 8 (256 MB) 262 -> 250 and 347 -> 337; T=8192, 1 layer (128 MB) 122 -> 106 and 148.7 -> 149.2, 2 (256 MB) 392 -> 379 and

@@ -347,7 +347,8 @@ struct PairItems {
 // from the L1; there is nothing to stage and no barrier.  TB = 4: two waves share the tokens, and the other two take the
 // second half of the earlier tokens; TB = 2: four waves share the tokens.  The work of one unit is dealt to one XCD
 // (workgroup b runs on XCD b % 8), so that its sketches are read by one L2.
-// Bound by power: 32 x T=8192 with three column groups keep the 8-bit MFMA busy for 65% of 305 thousand cycles, at 1.7 GHz.
+// Bound by the matrix cores at the clock that they leave: 32 x T=8192 with three column groups keep the 8-bit MFMA busy for 66% of
+// 304 thousand cycles, 157 us at 1.94 GHz (the exact pass beside it runs at 2.28): 2.7 PFLOP/s.
 // Calls, us, with two blocks per wave, two instructions per product and two sets of operands (before) and now: 4 x 8 x T=8192,
 // d=4096 619 -> 596, 128 x T=2048, d=256 105 -> 99, 12 x T=2048, d=768 46.7 -> 45.3.  Slower: sketches by way of LDS (607), two
 // waves per SIMD with the operands a whole step ahead (616).
