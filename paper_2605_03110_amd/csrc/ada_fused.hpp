@@ -1389,8 +1389,17 @@ constexpr int UPDATE_VALID = FUSED_MAX_T * 2;
 // Bound by its chain: keys, validity, and where a nearest one was removed class, place in the list and list.  Four tokens per thread go
 // through it together and take one place for all (before, one after the other: steps of T=4096 and 100 to 370 such tokens 1.5 us slower).
 // It stands behind the ranks and in front of the lists' stores: its loads would wait for those (0.4 to 1 us).
+// key: the first trip's keys (gamma_keys).  Steps of one trip (T <= 4 THREADS) ask for them in front of the ranks, longer ones, which wait for
+// the second trip anyway, behind: us per step, behind -> in front, T=197, d=768 18.1 -> 17.6; T=512, d=768 18.6 -> 18.2; T=1000, d=1001
+// 30.9 -> 30.5; fp32 T=700, d=768 30.8 -> 30.4; T=2048, d=512 20.6 -> 20.7, d=4096 33.6 -> 33.9; T=3001, d=1000 29.4 -> 29.8; T=4096, d=1024
+// 31.3 -> 31.6.  (A line at T=1024 instead, known only as the step runs, costs T=2048 and 4096 0.1 to 0.2 more.)
 template <int THREADS>
-__device__ inline void gamma_fix(const FusedParams& p, int r, bool ok, const char* lds) {
+__device__ inline void gamma_keys(const FusedParams& p, int base, unsigned long long (&key)[4]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) key[q] = p.best[min(base + q * THREADS, p.T - 1)];
+}
+template <int THREADS>
+__device__ inline void gamma_fix(const FusedParams& p, int r, bool ok, const char* lds, unsigned long long (&key)[4]) {
     __shared__ int s_len;                                // covered ones, and 2^16 new ones
     const uint8_t* flag = reinterpret_cast<const uint8_t*>(lds);
     const uint32_t* vmask = reinterpret_cast<const uint32_t*>(lds + UPDATE_VALID);
@@ -1398,10 +1407,8 @@ __device__ inline void gamma_fix(const FusedParams& p, int r, bool ok, const cha
     if (tid == 0) s_len = 0;
     __syncthreads();
     for (int base = tid; base < p.T; base += 4 * THREADS) {                 // four tokens per thread in flight, to memory and in LDS
-        unsigned long long key[4];
         bool lost[4], any = false;                       // the nearest one was removed
-#pragma unroll
-        for (int q = 0; q < 4; ++q) key[q] = p.best[min(base + q * THREADS, p.T - 1)];
+        if (base != tid) gamma_keys<THREADS>(p, base, key);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int pos = min(max(INT_MAX - (int)(uint32_t)key[q], 0), last);
@@ -1487,8 +1494,12 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
         else pos[q] = (uint16_t)j;
     }
     ok = __syncthreads_and(ok);
+    unsigned long long best[4] = {0ull, 0ull, 0ull, 0ull};
     if (!ok) {
-        if (p.fix_list) gamma_fix<THREADS>(p, r, false, lds);
+        if (p.fix_list) {
+            gamma_keys<THREADS>(p, tid, best);
+            gamma_fix<THREADS>(p, r, false, lds, best);
+        }
         if (tid == 0) {
             p.counts[0] = 0; p.counts[1] = 0; p.counts[2] = 0; p.counts[3] = ADA_ERR_INDEX;
             if (p.gram_ops) *p.gram_ops = 0ull;
@@ -1512,6 +1523,8 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
         }
     }
     __syncthreads();
+    if constexpr (NV == 1)                               // (see gamma_fix)
+        if (p.fix_list) gamma_keys<THREADS>(p, tid, best);
     // step 9: any other token with a hit on a VALID representative is covered
     bool f[3][U];                                        // in R^(l+1) | added | removed
 #pragma unroll
@@ -1554,7 +1567,8 @@ __device__ inline int fused_update_rec(const FusedParams& p, int r, int q0, int 
             }
             if (t4 < T4) reinterpret_cast<uint32_t*>(lds)[t4] = f4;
         }
-        gamma_fix<THREADS>(p, r, true, lds);
+        if constexpr (NV != 1) gamma_keys<THREADS>(p, tid, best);
+        gamma_fix<THREADS>(p, r, true, lds, best);
     }
     int o_idx = below[0], o_add = below[1], o_rem = below[2];
     const int n_idx = tot[0], n_add = tot[1], n_rem = tot[2];
@@ -1650,8 +1664,12 @@ __device__ __forceinline__ int fused_update(const FusedParams& p, int r, bool r_
     }
     ok = __syncthreads_and(ok);
     const int status = !r_ok ? ADA_ERR_SHAPE : (!ok ? ADA_ERR_INDEX : ADA_OK);
+    unsigned long long best[4] = {0ull, 0ull, 0ull, 0ull};
     if (status != ADA_OK) {
-        if (p.fix_list) gamma_fix<THREADS>(p, r, false, lds);
+        if (p.fix_list) {
+            gamma_keys<THREADS>(p, tid, best);
+            gamma_fix<THREADS>(p, r, false, lds, best);
+        }
         if (tid == 0) {
             p.counts[0] = 0; p.counts[1] = 0; p.counts[2] = 0; p.counts[3] = status;
             if (p.gram_ops) *p.gram_ops = 0ull;
@@ -1714,7 +1732,10 @@ __device__ __forceinline__ int fused_update(const FusedParams& p, int r, bool r_
     }
     __syncthreads();
     ADA_CLK_LAST(13);
-    if (p.fix_list) gamma_fix<THREADS>(p, r, true, lds);
+    if (p.fix_list) {
+        gamma_keys<THREADS>(p, tid, best);
+        gamma_fix<THREADS>(p, r, true, lds, best);
+    }
     const int chunk = (T + THREADS - 1) / THREADS;
     const int lo = min(T, tid * chunk), hi = min(T, lo + chunk);
     unsigned long long c = 0;                            // kept | added << 21 | removed << 42
