@@ -1799,17 +1799,17 @@ int screen_full(const ScreenPlan& plan, const void* X, int T, int d, long long l
     return e == hipSuccess ? ADA_OK : ADA_ERR_DEVICE;
 }
 
-template <int THREADS, int U, bool TWO>
+template <int THREADS, int U, int D>
 hipError_t launch_screen_chain(const ChainParams& c, hipStream_t st) {
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_screen_chain<THREADS, U, TWO>),
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_screen_chain<THREADS, U, D>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, CHAIN_LDS);
     });
     if (attr_err != hipSuccess) return attr_err;
     ProfScope ps(ADA_K_UPDATE, st);
-    hipLaunchKernelGGL((k_screen_chain<THREADS, U, TWO>), dim3((unsigned)c.s.G), dim3(THREADS), ChainGeom(c.s.T, c.s.L, TWO).bytes, st, c);
+    hipLaunchKernelGGL((k_screen_chain<THREADS, U, D>), dim3((unsigned)c.s.G), dim3(THREADS), (chain_lds<THREADS, U>(c.s.T)), st, c);
     return hipGetLastError();
 }
 
@@ -1902,10 +1902,11 @@ int run_layers_screened(const ScreenPlan& plan, const void* const* X_layers, int
         for (int i = 0; i < SCREEN_MAX_LAYERS; ++i) sp.X[i] = i < sp.L ? X_layers[first + i] : nullptr;
         hipError_t e = dtype == ADA_BF16 ? launch_screen<uint16_t>(sp, st) : launch_screen<float>(sp, st);
         if (e != hipSuccess) return ADA_ERR_DEVICE;
-        e = T <= 256 ? launch_screen_chain<256, 1, true>(c, st) : T <= 512 ? launch_screen_chain<512, 1, true>(c, st)
-          : T <= 1024 ? launch_screen_chain<512, 2, true>(c, st) : T <= 2048 ? launch_screen_chain<512, 4, true>(c, st)
-          : T <= 4096 ? launch_screen_chain<512, 8, true>(c, st) : T <= 8192 ? launch_screen_chain<1024, 8, true>(c, st)
-                      : launch_screen_chain<1024, 16, false>(c, st);
+        // (wide workgroups from 1025 tokens on; us, 512 threads -> 1024, 16 layers of d=256: T=1000 6.5 -> 7.2, 1500 8.8 -> 8.3, 4000 13.7 -> 11.4)
+        e = T <= 256 ? launch_screen_chain<256, 1, 8>(c, st) : T <= 512 ? launch_screen_chain<512, 1, 8>(c, st)
+          : T <= 1024 ? launch_screen_chain<512, 2, 8>(c, st) : T <= 2048 ? launch_screen_chain<1024, 2, 8>(c, st)
+          : T <= 4096 ? launch_screen_chain<1024, 4, 4>(c, st) : T <= 8192 ? launch_screen_chain<1024, 8, 2>(c, st)
+                      : launch_screen_chain<1024, 16, 1>(c, st);
         if (e != hipSuccess) return ADA_ERR_DEVICE;
         rp.c = c;
         e = dtype == ADA_BF16 ? (dma ? launch_cascade_rest<uint16_t, true, DMA_RAGGED>(rp, st) : launch_cascade_rest<uint16_t, true, DMA_NONE>(rp, st))

@@ -759,14 +759,18 @@ __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) 
 }
 
 // ------------------------------------------------------------------------------------------------
-// k_screen_chain: the layers, one after the other, on clusters and edges.  One workgroup per sequence; thread tid owns the
-// tokens tid + u THREADS, their membership stays in registers from layer to layer.  The clusters of as many layers as fit
-// are brought into LDS at once, so the walk itself does not touch memory.  Without edges a layer is: every inherited
-// token puts its id under an integer minimum of its cluster (the earliest inherited member is the only valid one), one
-// barrier, every token looks its cluster up, and the new set leaves as ballots (one bit per token).  Cluster slots carry a
-// layer stamp that falls from layer to layer, so they need no clearing, and there are two sets of them in turns (TWO), so
-// that one barrier per layer is enough.  Index lists, counts and Gram operations follow from the bits of a layer and the
-// one before: the launch behind writes them, for all layers at once.
+// k_screen_chain: the layers, one after the other, on clusters and edges.  One workgroup per sequence; a wave owns U words of
+// the set, 64 tokens each, and their membership stays in registers from layer to layer.  Without edges a layer is: every
+// inherited token puts its id under an integer minimum of its cluster (the earliest inherited member is the only valid one),
+// one barrier, every token looks its cluster up, and the new set leaves as ballots (one bit per token).  Cluster slots carry a
+// layer stamp that falls from layer to layer, so they need no clearing, and there are two sets of them in turns, so that one
+// barrier per layer is enough.  Index lists, counts and Gram operations follow from the bits of a layer and the one before: the
+// launch behind writes them, for all layers at once.
+// Bound by the instructions of a wave (about 45 and 22 per token of a lane) and two trips to LDS per layer: nothing else is
+// in the loop.  The clusters come from memory D layers ahead, straight into registers, as buffer loads (a lane address and a
+// scalar one, past the last token zero); tokens outside the set put their id in a place of their own, which takes less than a
+// branch around the minimum; a lane stores a word.  Clusters by way of LDS, all of them there before the first layer, and
+// predicated minima took, us: 12 x T=512 7.7 (now 4.7), 28 x T=2048 24.6 (12.4), 8 x T=8192 24.2 (12.7), 16 x T=12000 77.9 (42.7).
 struct ChainParams {
     ScreenParams s;
     int earlier_only;
@@ -789,22 +793,24 @@ constexpr int LIST_SCRATCH = 3 * 257 * 4;                     // LDS that writin
 constexpr int assign_lds(int T) { return LIST_SCRATCH + (T + 63) / 64 * 64 * 8; }
 static_assert(assign_lds(FUSED_MAX_T) <= CHAIN_LDS && FUSED_MAX_T / 64 + 1 <= 257, "LDS of a layer's lists and assignment");
 
-// LDS of the walk: cluster slots, marks (edges only), and the clusters of the layers in flight.
-struct ChainGeom {
-    int words, off_mark, off_layer, layer_bytes, layers, bytes;
-    __host__ __device__ ChainGeom(int T, int L, bool two) {
-        words = (T + 63) / 64;
-        const int Tp = words * 64;
-        off_mark = (two ? 2 : 1) * Tp * 4;
-        off_layer = off_mark + Tp;
-        layer_bytes = Tp * 2;
-        layers = (CHAIN_LDS - off_layer) / layer_bytes;
-        layers = layers < L ? layers : L;
-        bytes = off_layer + layers * layer_bytes;
-        const int lists = assign_lds(T);
-        bytes = bytes < lists ? lists : bytes;
-    }
-};
+// LDS of the walk: two sets of cluster slots, marks (edges only).
+template <int THREADS, int U>
+__host__ __device__ constexpr int chain_lds(int T) {
+    constexpr int tokens = THREADS * U, walk = (tokens + 64) * 8 + tokens;
+    return walk > assign_lds(T) ? walk : assign_lds(T);
+}
+static_assert(chain_lds<1024, 16>(FUSED_MAX_T) <= CHAIN_LDS, "LDS of the walk");
+
+constexpr int CHAIN_BUFFER = 0x00020000;                      // a buffer of plain bytes: loads past its end give zero, stores are dropped
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+__device__ int chain_writelane(int value, int lane, int old) __asm("llvm.amdgcn.writelane.i32");   // (has no builtin)
+
+// Token u of a lane: a wave owns U words of a layer's set, side by side.
+template <int U> __device__ inline int chain_token(int u) {
+    int t = ((int)threadIdx.x >> 6) * (U * 64) + ((int)threadIdx.x & 63);
+    if constexpr (U > 8) asm volatile("" : "+v"(t));          // (what is formed from all of a lane's tokens in advance is more than there are registers)
+    return t + 64 * u;
+}
 
 // All waves' LDS operations done, and everybody here.  (A fenced barrier would also wait for the stores to memory.)
 __device__ inline void chain_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -885,10 +891,10 @@ __device__ inline void chain_each(uint32_t n_edge, const uint2* edge, F f) {
 template <int THREADS, int U>
 __device__ inline bool chain_alone(uint32_t n_edge, const uint2* edge, uint32_t stamp, uint32_t* slot, uint8_t* mark,
                                    const int (&cid)[U], const unsigned long long (&in)[U], int T) {
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int lane = (int)threadIdx.x & 63;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const int t = u * THREADS + tid;
+        const int t = chain_token<U>(u);
         slot[cid[u]] = 0xFFFFFFFFu;
         if (t < T) mark[t] = (in[u] >> lane) & 1ull ? 1 : 0;
     }
@@ -904,7 +910,7 @@ __device__ inline bool chain_alone(uint32_t n_edge, const uint2* edge, uint32_t 
     int alone = 0;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const int t = u * THREADS + tid;
+        const int t = chain_token<U>(u);
         alone |= t < T && slot[cid[u]] != stamp && mark[min(t, T - 1)] == 0;
     }
     return __syncthreads_or(alone) != 0;
@@ -914,13 +920,13 @@ __device__ inline bool chain_alone(uint32_t n_edge, const uint2* edge, uint32_t 
 template <int THREADS, int U>
 __device__ inline void chain_edges(bool full, int earlier_only, uint32_t n_edge, const uint2* edge, uint32_t stamp,
                                    uint32_t* slot, uint8_t* mark, const int (&cid)[U], unsigned long long (&in)[U], int T) {
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int lane = (int)threadIdx.x & 63;
     if (full) {                                               // Definition 2.2: no earlier token within the threshold
         chain_each<THREADS>(n_edge, edge, [&](int, int t) { mark[t] = 2; });
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int t = u * THREADS + tid;
+            const int t = chain_token<U>(u);
             in[u] = __ballot(t < T && cid[u] == t && !(mark[min(t, T - 1)] & 2));
         }
         __syncthreads();
@@ -928,7 +934,7 @@ __device__ inline void chain_edges(bool full, int earlier_only, uint32_t n_edge,
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const int t = u * THREADS + tid;
+        const int t = chain_token<U>(u);
         const bool inh = (in[u] >> lane) & 1ull;
         if (inh) atomicMin(&slot[cid[u]], stamp | (uint32_t)t);
         if (t < T) mark[t] = inh ? 1 : 0;
@@ -941,7 +947,7 @@ __device__ inline void chain_edges(bool full, int earlier_only, uint32_t n_edge,
     unsigned long long keep[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const int t = u * THREADS + tid;
+        const int t = chain_token<U>(u);
         const uint32_t v = slot[cid[u]];
         low[u] = (v & 0xFFFFC000u) == stamp ? v & 0x3FFFu : 0xFFFFFFFFu;
         keep[u] = __ballot(((in[u] >> lane) & 1ull) && low[u] == (uint32_t)t && mark[min(t, T - 1)] != 3);
@@ -949,7 +955,7 @@ __device__ inline void chain_edges(bool full, int earlier_only, uint32_t n_edge,
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < U; ++u)
-        if (u * THREADS + tid < T) mark[u * THREADS + tid] = (keep[u] >> lane) & 1ull ? 4 : 0;
+        if (chain_token<U>(u) < T) mark[chain_token<U>(u)] = (keep[u] >> lane) & 1ull ? 4 : 0;
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < U; ++u)                               // the cluster's earliest inherited member covers only if valid
@@ -962,7 +968,7 @@ __device__ inline void chain_edges(bool full, int earlier_only, uint32_t n_edge,
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const int t = u * THREADS + tid;
+        const int t = chain_token<U>(u);
         const bool covered = (low[u] != 0xFFFFFFFFu && !(earlier_only && low[u] > (uint32_t)t)) || mark[min(t, T - 1)] == 8;
         in[u] = keep[u] | (__ballot(t < T && !covered) & ~in[u]);        // steps 9 and 10
     }
@@ -1072,39 +1078,60 @@ __device__ inline void screen_assign(const ChainParams& c, const ScreenUnit& SU,
     __syncthreads();
 }
 
-template <int THREADS, int U, bool TWO>
+template <int THREADS, int U, int D>
 __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
     extern __shared__ __align__(16) char lds[];
-    __shared__ uint32_t s_edges[SCREEN_MAX_LAYERS], s_dense[SCREEN_MAX_LAYERS];
+    static_assert(SCREEN_MAX_LAYERS == 64, "a lane per layer");
+    constexpr int TOKENS = THREADS * U, SET = TOKENS + 64;
     unsigned long long alone = 0ull;                          // layers whose assignment is left to the tiles (uniform)
     const ScreenParams& p = c.s;
     const ScreenUnit SU(p.T, p.nch, p.edge_cap);
-    const int tid = threadIdx.x, T = p.T, g = blockIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x, T = p.T, g = blockIdx.x, lane = tid & 63, words = (T + 63) >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const ChainGeom CG(T, p.L, TWO);
-    const int Tp = CG.words * 64;
-    uint32_t* slots = reinterpret_cast<uint32_t*>(lds);       // [TWO ? 2 : 1][Tp] stamp << 14 | earliest inherited member
-    uint8_t* mark = reinterpret_cast<uint8_t*>(lds + CG.off_mark);   // bits: 1 inherited, 2 hit by an earlier inherited token, 4 valid, 8 covered
+    uint32_t* slots = reinterpret_cast<uint32_t*>(lds);       // [2][SET] stamp << 14 | earliest inherited member; the last 64 take what is none
+    uint8_t* mark = reinterpret_cast<uint8_t*>(lds + SET * 8);    // bits: 1 inherited, 2 hit by an earlier inherited token, 4 valid, 8 covered
     int32_t* meta = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(p.meta) + (long long)g * p.area_gs);
     char* area = p.area + (long long)g * p.area_gs;
-    auto cl_of = [&](int k) { return reinterpret_cast<uint16_t*>(lds + CG.off_layer + k * CG.layer_bytes); };
-    auto mask_of = [&](int l) { return reinterpret_cast<unsigned long long*>(area + (long long)l * SU.bytes + SU.o_mask); };
+    auto unit_of = [&](int l) { return area + (uint32_t)l * (uint32_t)SU.bytes; };   // (a sequence's area is 34 MB at most)
+    auto mask_of = [&](int l) { return reinterpret_cast<unsigned long long*>(unit_of(l) + SU.o_mask); };
+    auto tok = [](int u) { return chain_token<U>(u); };
+    auto clusters = [&](int l, int (&cid)[U]) {               // (past the last token: zero, a slot like any other)
+        const auto row = __builtin_amdgcn_make_buffer_rsrc(unit_of(l) + SU.o_cl, 0, 2 * T, CHAIN_BUFFER);
+#pragma unroll
+        for (int u = 0; u < U; ++u) cid[u] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(row, 2 * tok(u), 0, 0);
+    };
+    int ahead[D][U], cid[U];
+    const int skip = p.first == 0 ? 1 : 0;
+    clusters(0, cid);
+#pragma unroll
+    for (int k = 0; k < D; ++k) clusters(min(skip + k, p.L - 1), ahead[k]);
+    int loaded = skip;                                        // the layer that ahead[0] belongs to
 
     const int progress = meta[META_PROGRESS];
-    if (tid < p.L) {
-        const uint32_t* hdr = reinterpret_cast<const uint32_t*>(area + (long long)tid * SU.bytes);
-        s_edges[tid] = hdr[SU_EDGES];
-        s_dense[tid] = hdr[SU_DENSE];
-    }
-    for (int t = tid; t < (TWO ? 2 : 1) * Tp; t += THREADS) slots[t] = 0xFFFFFFFFu;
-    for (int t = tid; t < Tp; t += THREADS) mark[t] = 0;
+    const uint32_t* hdr = reinterpret_cast<const uint32_t*>(area + (long long)min(lane, p.L - 1) * SU.bytes);
+    const uint32_t edges_of = hdr[SU_EDGES];                  // of the layer with this lane's number
+    const unsigned long long dense = __ballot(lane < p.L && hdr[SU_DENSE] != 0u);
+    const unsigned long long edged = __ballot(lane < p.L && edges_of != 0u);
+    for (int t = tid; t < 2 * SET; t += THREADS) slots[t] = 0xFFFFFFFFu;
+    for (int t = tid; t < TOKENS; t += THREADS) mark[t] = 0;
     // membership, one bit per lane and u; a lane whose token does not exist is a member of nothing
-    unsigned long long in[U], exists[U];
+    unsigned long long in[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        in[u] = 0ull;
-        exists[u] = __ballot(u * THREADS + tid < T);
-    }
+    for (int u = 0; u < U; ++u) in[u] = 0ull;
+    auto exists = [&](int u) {                                // (uniform: bits of word u's tokens)
+        const int n = T - (wave * U + u) * 64;
+        return n >= 64 ? ~0ull : n > 0 ? (1ull << n) - 1ull : 0ull;
+    };
+    const int word_at = lane < U ? (wave * U + lane) * 8 : INT_MAX;   // lane u stores word u of its wave
+    auto put = [&](unsigned long long* mask) {
+        i32x2 v = {0, 0};
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            v[0] = chain_writelane((int)(uint32_t)in[u], u, v[0]);
+            v[1] = chain_writelane((int)(uint32_t)(in[u] >> 32), u, v[1]);
+        }
+        __builtin_amdgcn_raw_buffer_store_b64(v, __builtin_amdgcn_make_buffer_rsrc(mask, 0, 8 * words, CHAIN_BUFFER), word_at, 0, 0);
+    };
     if (p.first > 0) {                                        // go on from the set an earlier launch left
         if (progress != p.first) {
             if (tid == 0) *reinterpret_cast<unsigned long long*>(meta + META_ALONE) = 0ull;
@@ -1116,77 +1143,70 @@ __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
         for (int j = tid; j < r; j += THREADS) mark[idx[j]] = 1;
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            in[u] = __ballot(u * THREADS + tid < T && mark[u * THREADS + tid] != 0);
-            const int w = u * (THREADS / 64) + wave;
-            if (lane == 0 && w < CG.words) mask_of(0)[CG.words + w] = in[u];
-        }
+        for (int u = 0; u < U; ++u) in[u] = __ballot(tok(u) < T && mark[tok(u)] != 0);
+        put(mask_of(0) + words);
     }
+    __syncthreads();
     int i = 0;
     bool stop = false;
-    for (int i0 = 0; i0 < p.L && !stop; i0 += CG.layers) {
-        const int n = min(CG.layers, p.L - i0);
-        if (i0 > 0) __syncthreads();
-        {   // clusters of the coming layers (rows of the units are 256-byte aligned), eight loads in flight per thread
-            const int vpl = (T + 7) >> 3, total = n * vpl;
-            for (int v0 = tid; v0 < total; v0 += THREADS * 8) {
-                u32x4 x[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int v = min(v0 + e * THREADS, total - 1), k = v / vpl;
-                    x[e] = *reinterpret_cast<const u32x4*>(area + (long long)(i0 + k) * SU.bytes + SU.o_cl + (v - k * vpl) * 16);
-                }
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int v = min(v0 + e * THREADS, total - 1), k = v / vpl;
-                    *reinterpret_cast<u32x4*>(cl_of(k) + (v - k * vpl) * 8) = x[e];
-                }
-            }
-        }
-        __syncthreads();
-        int cid[U];                                           // clusters of the layer at hand
-#pragma unroll
-        for (int u = 0; u < U; ++u) cid[u] = cl_of(0)[min(u * THREADS + tid, T - 1)];
-        for (int k = 0; k < n; ++k, ++i) {
-            if (s_dense[i]) { stop = true; break; }           // uniform
-            const uint32_t n_edge = s_edges[i];
-            const uint32_t stamp = (uint32_t)(0x3FFFE - i) << 14;   // (the empty slot's own stamp is 0x3FFFF)
-            uint32_t* slot = slots + (TWO && (i & 1) ? Tp : 0);
-            const uint16_t* next = cl_of(min(k + 1, n - 1));
-            if (n_edge) {
+    while (i < p.L) {
+        if ((dense >> i) & 1ull) { stop = true; break; }      // uniform
+        const bool has_edges = (edged >> i) & 1ull;
+        if (has_edges || p.first + i == 0) {
+            if (i > 0 || p.first > 0) clusters(i, cid);
+            if (has_edges) {
+                const uint32_t n_edge = (uint32_t)__builtin_amdgcn_readlane((int)edges_of, i);
+                const uint32_t stamp = (uint32_t)(0x3FFFE - i) << 14;
+                uint32_t* slot = slots + (i & 1 ? SET : 0);
                 const uint2* edge = reinterpret_cast<const uint2*>(area + (long long)i * SU.bytes + SU.o_edge);
+                __syncthreads();
                 chain_edges<THREADS, U>(p.first + i == 0, c.earlier_only, n_edge, edge, stamp, slot, mark, cid, in, T);
                 if (c.assign && chain_alone<THREADS, U>(n_edge, edge, stamp, slot, mark, cid, in, T)) alone |= 1ull << i;
-                for (int t = tid; t < Tp; t += THREADS) mark[t] = 0;
-                __syncthreads();
-            } else if (p.first + i == 0) {                    // Definition 2.2: a cluster's pivot is earlier than its other members
+                for (int t = tid; t < TOKENS; t += THREADS) mark[t] = 0;
 #pragma unroll
-                for (int u = 0; u < U; ++u) in[u] = __ballot(cid[u] == u * THREADS + tid) & exists[u];
-            } else {
+                for (int k = 0; k < D; ++k) clusters(min(i + 1 + k, p.L - 1), ahead[k]);
+                loaded = i + 1;
+                __syncthreads();
+            } else {                                          // Definition 2.2: a cluster's pivot is earlier than its other members
+#pragma unroll
+                for (int u = 0; u < U; ++u) in[u] = __ballot(cid[u] == tok(u)) & exists(u);
+            }
+            put(mask_of(i));
+            ++i;
+            continue;
+        }
+        const unsigned long long other = (dense | edged) >> i;
+        const int end = other ? min(p.L, i + __builtin_ctzll(other)) : p.L;
+        if (loaded != i) {
+#pragma unroll
+            for (int k = 0; k < D; ++k) clusters(min(i + k, p.L - 1), ahead[k]);
+        }
+        const int first_set = i & 1;
+        while (i < end) {
+#pragma unroll
+            for (int k = 0; k < D; ++k) {
+                if (i >= end) break;
+                uint32_t* slot = slots + ((D % 2 ? i & 1 : (first_set + k) & 1) ? SET : 0);   // (D even: always the same for ahead[k])
+                const uint32_t stamp = (uint32_t)(0x3FFFE - i) << 14;   // (the empty slot's own stamp is 0x3FFFF)
                 uint32_t v[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u)
-                    if (__builtin_amdgcn_inverse_ballot_w64(in[u])) atomicMin(&slot[cid[u]], stamp | (uint32_t)(u * THREADS + tid));
+                    atomicMin(&slot[__builtin_amdgcn_inverse_ballot_w64(in[u]) ? ahead[k][u] : TOKENS + lane], stamp | (uint32_t)tok(u));
                 chain_barrier();
 #pragma unroll
-                for (int u = 0; u < U; ++u) v[u] = slot[cid[u]];   // this layer's stamp is the smallest so far
+                for (int u = 0; u < U; ++u) v[u] = slot[ahead[k][u]] - stamp;   // this layer's stamp is the smallest so far
+                clusters(min(i + D, p.L - 1), ahead[k]);
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const uint32_t key = stamp | (uint32_t)(u * THREADS + tid);
-                    const unsigned long long valid = __ballot(v[u] == key);                        // step 5 (if inherited)
-                    const unsigned long long covered = __ballot(c.earlier_only ? v[u] < key : v[u] <= (stamp | 0x3FFFu));   // steps 7-8
-                    in[u] = (in[u] & valid) | (exists[u] & ~in[u] & ~covered);                      // steps 9 and 10
+                    const unsigned long long valid = __ballot(v[u] == (uint32_t)tok(u));   // step 5 (only inherited tokens were there)
+                    const unsigned long long covered = __ballot(v[u] < (c.earlier_only ? (uint32_t)tok(u) : 0x4000u));   // steps 7-8
+                    in[u] = valid | (exists(u) & ~covered);   // steps 9 and 10
                 }
-                if (!TWO) chain_barrier();                    // nobody reads this layer's slots any more
-            }
-            unsigned long long* mask = mask_of(i);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                cid[u] = next[min(u * THREADS + tid, T - 1)];
-                const int w = u * (THREADS / 64) + wave;
-                if (lane == 0 && w < CG.words) mask[w] = in[u];
+                put(mask_of(i));
+                ++i;
             }
         }
+        loaded = -1;
     }
     // lists that the launch behind reads; all of them if it needs the units' memory for its hit table
     if (stop || alone != 0ull) {

@@ -123,6 +123,21 @@ def test_layer_loop_on_the_graph_of_near_pairs(kind, T, d, L, dtype, tau):
     assert int(single["counts"][0]) == int(res["counts"][0, 0])
 
 
+@pytest.mark.parametrize("T,d,L,edged,flags", [
+    # every number of tokens per lane, its last token, one token less and more; layers with edges among the plain ones, so that
+    # the clusters read ahead are used up, left and taken up again at every place
+    (256, 64, 11, (4,), 0), (257, 64, 10, (0, 3, 8), pa.FLAG_CROSS_EARLIER_ONLY), (512, 72, 20, (9, 10), 0), (513, 64, 9, (1,), pa.FLAG_CROSS_EARLIER_ONLY),
+    (1024, 64, 12, (6,), pa.FLAG_CROSS_EARLIER_ONLY), (1025, 64, 7, (5,), 0), (2047, 64, 8, (), 0), (2049, 64, 7, (2,), pa.FLAG_CROSS_EARLIER_ONLY),
+    (4097, 64, 5, (3,), 0), (8191, 64, 3, (), pa.FLAG_CROSS_EARLIER_ONLY), (8193, 64, 4, (2,), 0)])
+def test_walk_over_plain_layers_and_layers_with_edges(T, d, L, edged, flags):
+    print("[case] walk: T=%d d=%d L=%d edges in %s flags %d" % (T, d, L, edged, flags), flush=True)
+    xs_cpu = activations("clusters", T, d, L, "bf16", seed=T)
+    for l in edged:
+        xs_cpu[l] = activations("strays", T, d, 1, "bf16", seed=T + 1 + l)[0]
+    res = pa.ada_cascade_layers([x.to(DEV) for x in xs_cpu], 0.1, flags=flags)
+    check(xs_cpu, 0.1, *(res[k].cpu() for k in ("idx", "counts", "gram_ops", "adds", "removes")), flags, "walk")
+
+
 @pytest.mark.parametrize("kinds,T,d,dtype", [(("clusters", "clusters", "clusters"), 200, 96, "bf16"), (("clusters", "common", "loose"), 260, 320, "bf16"),
                                              (("common", "common", "clusters", "common", "loose"), 600, 256, "bf16"),
                                              (("outliers", "signs"), 131, 1001, "f32")])
