@@ -22,7 +22,7 @@ struct AttnParams {
     const int32_t* idx;        // R, ascending
     const int32_t* r_dev;      // optional device count
     int r_host;
-    const int32_t* pos;        // [T] position of assign[t] in R (k_attn_pos)
+    const int32_t* pos;        // [T] position of assign[t] in R (k_attn_pos); NULL: every workgroup finds and checks them itself (attn_positions)
     float* out;
     long long ld_out;
     float scale;               // 1 / sqrt(d_h)
@@ -30,6 +30,7 @@ struct AttnParams {
     int32_t* info;             // [4]: written by workgroup (0, 0) of the attention kernel
     const int32_t* err;        // [nerr] one status word per workgroup of k_attn_pos
     int nerr;
+    const int32_t* assign;     // read where pos is NULL
 };
 
 // Several layers in one launch (blockIdx.z): what differs between them.  The other pointers of AttnParams are layer 0's; idx
@@ -82,19 +83,74 @@ __global__ __launch_bounds__(256) void k_attn_pos(const int32_t* __restrict__ id
     if (threadIdx.x == 0) err[blockIdx.x] = !r_ok ? (int)ADA_ERR_SHAPE : bad ? (int)ADA_ERR_INDEX : (int)ADA_OK;
 }
 
-// The status of the call (the worst word k_attn_pos left), the same in every thread; workgroup (0, 0) reports it.
-__device__ inline int attn_status(const AttnParams& p, int r) {
-    const int lane = threadIdx.x & 63;
-    int e = (r >= 1 && r <= p.r_host && r <= p.T) ? 0 : (int)ADA_ERR_SHAPE;   // (positions from elsewhere: nerr = 0)
-    for (int i = lane; i < p.nerr; i += 64) e = max(e, p.err[i]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) e = max(e, __shfl_xor(e, o, 64));
+// Workgroup (0, 0) reports the status of the call.
+__device__ inline void attn_report(const AttnParams& p, int r, int e) {
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
         p.info[0] = e == (int)ADA_ERR_SHAPE ? 0 : r;
         p.info[1] = 0;
         p.info[2] = 0;
         p.info[3] = e;
     }
+}
+
+// The status of the call (the worst word k_attn_pos left), the same in every thread.
+__device__ inline int attn_status(const AttnParams& p, int r) {
+    const int lane = threadIdx.x & 63;
+    int e = (r >= 1 && r <= p.r_host && r <= p.T) ? 0 : (int)ADA_ERR_SHAPE;   // (positions from elsewhere: nerr = 0)
+    for (int i = lane; i < p.nerr; i += 64) e = max(e, p.err[i]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) e = max(e, __shfl_xor(e, o, 64));
+    attn_report(p, r, e);
+    return e;
+}
+
+// Up to this many tokens a workgroup finds the positions of all of them itself, from a table in LDS with a place per token: what
+// k_attn_pos takes as a launch of its own (3.7 us and the gap in front of it) costs a workgroup less than 1 us, most of it behind
+// the trip to memory for the set that it makes anyway.  T=512, 12 heads x 64 in fp32, assignment and attention: 37.2 -> 33.5 us.  Twice as many tokens
+// would be as many loads and LDS operations again in each of a hundred workgroups.  (Heads of 256 columns in bf16 keep the launch: their
+// kernel has no registers left.)
+constexpr int ATTN_OWN_POS = 2048;
+constexpr int ATTN_POS_LDS = 2 * ATTN_OWN_POS * 2;
+
+// Positions (0xFFFF: none) to `at` (LDS, ATTN_POS_LDS bytes: positions, then the table); the status of the call, the same in every
+// thread.  The checks are k_attn_pos's.
+template <int THREADS>
+__device__ inline int attn_positions(const AttnParams& p, int r, uint16_t* at) {
+    constexpr int N = ATTN_OWN_POS / THREADS;
+    uint16_t* table = at + ATTN_OWN_POS;
+    const int tid = threadIdx.x;
+    int e = (int)ADA_ERR_SHAPE;
+    if (r >= 1 && r <= p.r_host && r <= p.T) {                 // uniform
+        int a[N], q[N], before[N], bad = 0;
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int i = u * THREADS + tid;
+            a[u] = p.assign[min(i, p.T - 1)];
+            q[u] = p.idx[min(i, r - 1)];
+            before[u] = p.idx[max(min(i, r - 1) - 1, 0)];
+        }
+#pragma unroll
+        for (int u = 0; u < N; ++u) table[u * THREADS + tid] = 0xFFFFu;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int i = u * THREADS + tid;
+            if (i < r) {
+                if (q[u] < 0 || q[u] >= p.T || (i > 0 && !(before[u] < q[u]))) bad = 1;
+                else table[q[u]] = (uint16_t)i;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int t = u * THREADS + tid;
+            const int v = a[u] >= 0 && a[u] < p.T ? table[a[u]] : 0xFFFF;
+            at[t] = (uint16_t)v;
+            if (t < p.T && v == 0xFFFF) bad = 1;
+        }
+        e = __syncthreads_or(bad) ? (int)ADA_ERR_INDEX : (int)ADA_OK;
+    }
+    attn_report(p, r, e);
     return e;
 }
 
@@ -135,10 +191,55 @@ template <typename In, int DH> struct AttnGeom {
     static constexpr int OFF_P = OFF_S + 64 * 65 * 4;                 // weights: bf16 hi then lo (8 KB each), or fp32 (16 KB)
     static constexpr int OFF_ROW = OFF_P + 16384;                     // alpha[64], lsum[64], qtok[64], ktok[64]
     static constexpr int OFF_LIST = OFF_ROW + 4 * 64 * 4;             // int[256] + counter
-    static constexpr int LDS = OFF_LIST + 257 * 4;
+    static constexpr int LDS = (OFF_LIST + 257 * 4 + 15) / 16 * 16;                    // (the positions behind it, if the kernel finds them itself)
     static_assert(PPR == 8 || PPR == 16 || PPR == 32, "head rows of 128, 256 or 512 bytes");
     static_assert(DH % 64 == 0, "head dimension in multiples of 64");
 };
+
+// Hand-over of a block's 64 rows (obuf, OS floats apart) to those of 2048 tokens from tb on that take one: rel, of every thread's tokens tb +
+// u 64 WAVES + thread, is the row, or beyond them.  The takers are collected in one list; a wave then copies 64 lanes x 16 bytes, a row of
+// d_h floats or several, per store, eight in flight.  (Outputs need not start on 16 bytes: the memory pipe takes them at any.)
+// k_attn_rep went through 256 tokens at a time, a row per wave and store: 7.6 of the 20.5 us of 12 heads x 64 at T=512 in fp32 (now 15.8).
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+template <int DH, int WAVES, int OS, bool STREAM>
+__device__ inline void attn_hand_over(const float* obuf, int* takers, int* count, float* outh, long long ld_out, int tb, const int (&rel)[32 / WAVES]) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid == 0) *count = 0;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 32 / WAVES; ++u)
+        if ((unsigned)rel[u] < 64u) takers[atomicAdd(count, 1)] = ((tb + u * WAVES * 64 + tid) << 6) | rel[u];
+    __syncthreads();
+    const int n = *count;
+    constexpr int LPR = DH / 4, RPI = 64 / LPR, NW = WAVES;   // lanes per row (16 bytes each), rows per instruction, waves
+    const int sub = lane / LPR, c4 = (lane % LPR) * 4;
+    // a wave's share of the list (entries wave * RPI + sub + NW RPI k) is read 64 entries at a time, one per lane,
+    // and handed to the lane groups by lane reads; eight rows are in flight per lane group
+    constexpr int KPB = 64 / RPI;                      // steps k per batch
+    const int steps = (n - wave * RPI + NW * RPI - 1) / (NW * RPI);          // k with a first entry below n
+    for (int k0 = 0; k0 < steps; k0 += KPB) {
+        const int mine = takers[min(wave * RPI + (lane % RPI) + NW * RPI * (k0 + lane / RPI), n - 1)];
+        const int kend = min(KPB, steps - k0);
+        for (int kk = 0; kk < kend; kk += 8) {
+            int ent[8];
+            float4 v4[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) ent[u] = __shfl(mine, min(kk + u, KPB - 1) * RPI + sub, 64);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                v4[u] = *reinterpret_cast<const float4*>(obuf + (ent[u] & 63) * OS + c4);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (kk + u < kend && wave * RPI + sub + NW * RPI * (k0 + kk + u) < n) {
+                    f32x4_any* at = reinterpret_cast<f32x4_any*>(outh + (size_t)(ent[u] >> 6) * (size_t)ld_out + c4);
+                    const f32x4_any v = {v4[u].x, v4[u].y, v4[u].z, v4[u].w};
+                    if constexpr (STREAM) __builtin_nontemporal_store(v, at);   // (rows of whole cache lines)
+                    else *at = v;
+                }
+        }
+    }
+    __syncthreads();
+}
 
 #ifdef ADA_PHASE_CLOCKS
 #define ATTN_CLK(k) do { if (threadIdx.x == 0 && (k) < 8) g_pass_clk[((blockIdx.y * gridDim.x + blockIdx.x) & 511) * 8 + ((k) & 7)] = __builtin_amdgcn_s_memrealtime(); } while (0)
@@ -162,11 +263,14 @@ __global__ __launch_bounds__(256) void k_attn_rep(AttnParams p, Layers layers) {
     float* lsum = alpha + 64;
     int* qtok = reinterpret_cast<int*>(lsum + 64);
     int* ktok = qtok + 64;
-    int* list = reinterpret_cast<int*>(lds + G::OFF_LIST);
+    int* list = reinterpret_cast<int*>(lds + G::OFF_LIST);                 // the takers' counter
 
     ATTN_CLK(0);
     const int r = p.r_dev ? *p.r_dev : p.r_host;
-    if (attn_status(p, r) != ADA_OK) return;               // k_attn_pos rejected the set or the assignment
+    constexpr bool ONE = std::is_same<Layers, AttnOne>::value;
+    const uint16_t* own_pos = reinterpret_cast<const uint16_t*>(lds + G::LDS);   // (one layer only: several come with their positions)
+    const bool own = ONE && !p.pos;                        // uniform
+    if ((own ? attn_positions<256>(p, r, reinterpret_cast<uint16_t*>(lds + G::LDS)) : attn_status(p, r)) != ADA_OK) return;   // the set or the assignment is rejected
     const AttnWho who = attn_who(p.H);
     const int h = who.h;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
@@ -370,31 +474,17 @@ __global__ __launch_bounds__(256) void k_attn_rep(AttnParams p, Layers layers) {
     }
     __syncthreads();
     ATTN_CLK(7);
-    // ---- hand-over: every token whose representative sits in this block takes that row (tokens in chunks of 256)
+    // ---- hand-over: every token whose representative sits in this block takes that row
     float* outh = p.out + (size_t)h * DH;
-    for (int tb = 0; tb < p.T; tb += 8 * 256) {            // positions of 2048 tokens at a time, one trip to memory
+    static_assert(64 * G::ROWB >= 2048 * 4 && 64 * DH * 4 <= G::OFF_VT, "the list of takers lies where V^T was, behind the rows");
+    for (int tb = 0; tb < p.T; tb += 2048) {               // positions of 2048 tokens at a time, one trip to memory
         int rel[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const int t = tb + u * 256 + tid;
-            rel[u] = t < p.T ? p.pos[t] - q0 : -1;
+            rel[u] = t < p.T ? (own ? (int)own_pos[t] : p.pos[t]) - q0 : -1;
         }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            if (tb + u * 256 >= p.T) break;                // uniform
-            if (tid == 0) list[256] = 0;
-            __syncthreads();
-            if ((unsigned)rel[u] < 64u) list[atomicAdd(&list[256], 1)] = ((tb + u * 256 + tid) << 6) | rel[u];
-            __syncthreads();
-            const int n = list[256];
-            for (int j = wave; j < n; j += 4) {            // one wave per token row
-                const int e = list[j], tt = e >> 6, row = e & 63;
-                float* dst = outh + (size_t)tt * (size_t)p.ld_out;
-#pragma unroll
-                for (int c = 0; c < DH; c += 64) dst[c + lane] = obuf[row * DH + c + lane];
-            }
-            __syncthreads();
-        }
+        attn_hand_over<DH, 4, DH, false>(obuf, reinterpret_cast<int*>(vtbuf), list, outh, p.ld_out, tb, rel);
     }
     ATTN_CLK(4);
     }
@@ -435,7 +525,7 @@ template <int DH> struct AttnGeom2 {
     static constexpr int MAIN = (4 * 64 * ROWB > OFF_TAKERS + 2048 * 4) ? 4 * 64 * ROWB : OFF_TAKERS + 2048 * 4;
     static constexpr int OFF_ROW = MAIN;                                               // qtok[64], ktok[64], m[2][64], l[2][64]
     static constexpr int OFF_LIST = OFF_ROW + 6 * 64 * 4;
-    static constexpr int LDS = OFF_LIST + 257 * 4;
+    static constexpr int LDS = (OFF_LIST + 257 * 4 + 15) / 16 * 16;                    // (the positions behind it, if the kernel finds them itself)
 };
 
 // EIGHT waves: waves 0 .. 3 multiply as described and never touch memory inside the key-block loop; waves 4 .. 7 fetch
@@ -468,7 +558,10 @@ __global__ __launch_bounds__(512) void k_attn_rep2(AttnParams p, Layers layers) 
     int* takers = reinterpret_cast<int*>(lds + G::OFF_TAKERS);            // up to 2048 (token, row) pairs
 
     const int r = p.r_dev ? *p.r_dev : p.r_host;
-    if (attn_status(p, r) != ADA_OK) return;               // k_attn_pos rejected the set or the assignment
+    constexpr bool ONE = std::is_same<Layers, AttnOne>::value && DH <= 128;   // (see attention_run)
+    const uint16_t* own_pos = reinterpret_cast<const uint16_t*>(lds + G::LDS);   // (one layer only: several come with their positions)
+    const bool own = ONE && !p.pos;                        // uniform
+    if ((own ? attn_positions<512>(p, r, reinterpret_cast<uint16_t*>(lds + G::LDS)) : attn_status(p, r)) != ADA_OK) return;   // the set or the assignment is rejected
     const AttnWho who = attn_who(p.H);
     const int h = who.h;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
@@ -690,7 +783,7 @@ __global__ __launch_bounds__(512) void k_attn_rep2(AttnParams p, Layers layers) 
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int t = tb + u * 512 + tid;
-            rel[u] = t < p.T ? p.pos[t] - q0 : -1;
+            rel[u] = t < p.T ? (own ? (int)own_pos[t] : p.pos[t]) - q0 : -1;
         }
     };
     load_rel(0);                                           // in flight behind the merge
@@ -747,41 +840,7 @@ __global__ __launch_bounds__(512) void k_attn_rep2(AttnParams p, Layers layers) 
     float* outh = p.out + (size_t)h * DH;
     for (int tb = 0; tb < p.T; tb += 4 * 512) {
         if (tb > 0) load_rel(tb);                          // (the first 2048 were asked for before the merge)
-        if (tid == 0) list[0] = 0;
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if ((unsigned)rel[u] < 64u) takers[atomicAdd(&list[0], 1)] = ((tb + u * 512 + tid) << 6) | rel[u];
-        __syncthreads();
-        const int n = list[0];
-        constexpr int LPR = DH / 4, RPI = 64 / LPR, NW = 8; // lanes per row (a float4 each), rows per instruction, waves
-        const int sub = lane / LPR, c4 = (lane % LPR) * 4;
-        // a wave's share of the list (entries wave8 * RPI + sub + NW RPI k) is read 64 entries at a time, one per lane,
-        // and handed to the lane groups by lane reads; eight rows are in flight per lane group
-        constexpr int KPB = 64 / RPI;                      // steps k per batch
-        const int steps = (n - wave8 * RPI + NW * RPI - 1) / (NW * RPI);          // k with a first entry below n
-        for (int k0 = 0; k0 < steps; k0 += KPB) {
-            const int mine = takers[min(wave8 * RPI + (lane % RPI) + NW * RPI * (k0 + lane / RPI), n - 1)];
-            const int kend = min(KPB, steps - k0);
-            for (int kk = 0; kk < kend; kk += 8) {
-                int ent[8];
-                float4 v4[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) ent[u] = __shfl(mine, min(kk + u, KPB - 1) * RPI + sub, 64);
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    v4[u] = *reinterpret_cast<const float4*>(obuf + (ent[u] & 63) * G::OS + c4);
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (kk + u < kend && wave8 * RPI + sub + NW * RPI * (k0 + kk + u) < n) {
-                        f32x4* at = reinterpret_cast<f32x4*>(outh + (size_t)(ent[u] >> 6) * (size_t)p.ld_out + c4);
-                        const f32x4 v = {v4[u].x, v4[u].y, v4[u].z, v4[u].w};
-                        if constexpr (STREAM) __builtin_nontemporal_store(v, at);
-                        else *at = v;
-                    }
-            }
-        }
-        __syncthreads();
+        attn_hand_over<DH, 8, G::OS, STREAM>(obuf, takers, list, outh, p.ld_out, tb, rel);
     }
     }
     ATTN_CLK(7);

@@ -1116,10 +1116,11 @@ template <int DH, bool STREAM, typename Layers>
 hipError_t launch_attn_regs(const AttnParams& p, const Layers& layers, int n_layers, hipStream_t st) {
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
-    constexpr int lds = AttnGeom2<DH>::LDS;
+    constexpr int most = AttnGeom2<DH>::LDS + ATTN_POS_LDS;
+    const int lds = AttnGeom2<DH>::LDS + (p.pos ? 0 : ATTN_POS_LDS);
     std::call_once(once, [] {
         attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_rep2<DH, Layers, STREAM>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, most);
     });
     if (attr_err != hipSuccess) return attr_err;
     ProfScope ps(ADA_K_ATTN, st);
@@ -1154,10 +1155,11 @@ hipError_t launch_attn(const AttnParams& p, const Layers& layers, int n_layers, 
     }
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
-    constexpr int lds = AttnGeom<In, DH>::LDS;
+    constexpr int most = AttnGeom<In, DH>::LDS + ATTN_POS_LDS;
+    const int lds = AttnGeom<In, DH>::LDS + (p.pos ? 0 : ATTN_POS_LDS);
     std::call_once(once, [] {
         attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_rep<In, DH, Layers>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, most);
     });
     if (attr_err != hipSuccess) return attr_err;
     ProfScope ps(ADA_K_ATTN, st);
@@ -2039,15 +2041,17 @@ static int attention_run(const void* Q, const void* K, const void* V, int T, int
     if (ws_bytes < ws_bytes_for(T) || ((uintptr_t)ws % 256) != 0) return ADA_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     const Workspace w = carve(ws, T);
-    // positions and validation; its workgroups' status words go to the (otherwise unused) row-maximum array
-    const int nerr = pos_given ? 0 : (T + 255) / 256;      // (r <= T)
+    // positions and validation (long sequences: see ATTN_OWN_POS); its workgroups' status words go to the (otherwise unused)
+    // row-maximum array
+    const bool own = !pos_given && T <= ATTN_OWN_POS && d_h <= 128;
+    const int nerr = pos_given || own ? 0 : (T + 255) / 256;   // (r <= T)
     int32_t* err = reinterpret_cast<int32_t*>(w.gamma);
-    if (!pos_given) {
+    if (nerr > 0) {
         hipLaunchKernelGGL(k_attn_pos, dim3(nerr), dim3(256), 0, st, idx, r_dev, r, assign, T, w.nonrep_idx, err);
         if (hipGetLastError() != hipSuccess) return ADA_ERR_DEVICE;
     }
-    const AttnParams p = {Q, K, V, ld, T, H, idx, r_dev, r, w.nonrep_idx, out, ld_out,
-                          (float)(1.0 / sqrt((double)d_h)), (flags & ADA_FLAG_ATTN_CAUSAL) ? 1 : 0, info, err, nerr};
+    const AttnParams p = {Q, K, V, ld, T, H, idx, r_dev, r, own ? nullptr : w.nonrep_idx, out, ld_out,
+                          (float)(1.0 / sqrt((double)d_h)), (flags & ADA_FLAG_ATTN_CAUSAL) ? 1 : 0, info, err, nerr, assign};
     return attention_launch(p, AttnOne(), 1, d_h, dtype, st);
 }
 

@@ -1371,6 +1371,30 @@ def test_attention_rejects_bad_sets_and_assignments():
     assert pa.ada_attention_compressed(q, k, v, 2, good_idx, assign, r_dev=zero)["info"].cpu().tolist()[3] == 2
 
 
+@pytest.mark.parametrize("T,d,H,K,dtype", [(1, 64, 1, 1, "f32"), (255, 64, 1, 255, "f32"), (513, 128, 1, 80, "f32"), (2047, 128, 2, 300, "f32"),
+                                           (2048, 128, 1, 70, "bf16"), (2049, 128, 2, 90, "bf16"), (2048, 256, 1, 60, "bf16")])
+def test_attention_finds_positions_by_itself_up_to_2048_tokens(T, d, H, K, dtype):
+    """Every number of tokens around the table's limits (and heads that leave the positions to a launch of their own): the result
+    against the oracle, and one bad entry at either end of the assignment or the set refuses the call and leaves the output alone."""
+    say("attention positions T=%d d=%d H=%d %s" % (T, d, H, dtype))
+    attention_case(T, d, H, K, dtype, 3 * T + 1, False, "attention T=%d" % T)
+    w = wl.small(T=T, d=d, K=K, L=1, dtype=dtype, seed=T, p=0.1)
+    q, k, v = (m.to(DEV) for m in wl.qkv(w, H))
+    idx = torch.arange(0, T, 3, dtype=torch.int32, device=DEV)
+    assign = (torch.arange(T, dtype=torch.int32, device=DEV) // 3) * 3
+    out = torch.full((T, d), -7.0, dtype=torch.float32, device=DEV)
+    bad = [(idx, at, value) for at in (0, T - 1) for value in (-1, T, 1 << 30)]
+    for what, at, value in bad:
+        a = assign.clone(); a[at] = value
+        assert pa.ada_attention_compressed(q, k, v, H, what, a, out=out)["info"].cpu().tolist()[3] == 4
+    for at, value in ((0, -1), (idx.numel() - 1, T), (idx.numel() - 1, 0 if T > 3 else -5)):
+        i = idx.clone(); i[at] = value
+        assert pa.ada_attention_compressed(q, k, v, H, i, assign, out=out)["info"].cpu().tolist()[3] == 4
+    assert bool((out == -7.0).all())
+    assert pa.ada_attention_compressed(q, k, v, H, idx, assign, out=out)["info"].cpu().tolist() == [idx.numel(), 0, 0, 0]
+    assert not bool((out == -7.0).any())
+
+
 def test_attention_at_config2_size():
     say("attention config 2")
     w = wl.config(2)
