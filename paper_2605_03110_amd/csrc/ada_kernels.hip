@@ -1364,7 +1364,11 @@ struct GammaFix {
     const uint32_t* hits;
     const uint32_t* valid;
     int grid;                  // of the launch
+    int32_t* meta;             // the workspace's scalars
+    int zero;                  // words from there on that this launch leaves at zero, all but those it reads itself (ada_cascade_step_static)
 };
+// The words of a workspace that a step relies on being zero: scalars, arg-max keys and first-hit records, side by side.
+inline int zero_words(const Workspace& w, int T) { return (int)(w.first + T - reinterpret_cast<uint32_t*>(w.meta)); }
 constexpr int FIX_REPS = 8;
 
 // Products of far tokens and representatives up to which they are formed one by one.  A product reads its representative's row
@@ -1414,6 +1418,8 @@ __global__ __launch_bounds__(256) void k_gamma_fix(GramParams p, GammaFix f) {
     const int Wa = (r + 31) >> 5;
     auto row = [&](int t) { return X + (size_t)t * (size_t)p.ld; };
     const int32_t* list = p.nonrep_idx + (p.T - far);
+    for (int i = META_WORDS + 1 + (int)(blockIdx.x * 256 + threadIdx.x); i < f.zero; i += f.grid * 256) f.meta[i] = 0;
+    if (f.zero && blockIdx.x == 0 && threadIdx.x < META_FIX && threadIdx.x >= META_TICKET) f.meta[threadIdx.x] = 0;
     const bool tiles = (long long)far * r > fix_pairs(p.d, sizeof(In));
     const int pieces = (r + 4 * FIX_REPS - 1) / (4 * FIX_REPS), near4 = (near + 3) / 4, items = near4 + (tiles ? 0 : far * pieces);
     for (int i = wg; i < items; i += f.grid) {                // (uniform)
@@ -1492,8 +1498,8 @@ int run_cascade_fused(const void* X, int T, int d, long long ld, int dtype, floa
                       const int32_t* r_dev, int32_t* idx, int32_t* adds, int32_t* removes, int32_t* counts,
                       uint64_t* gram_ops, float* gamma, void* ws, hipStream_t st, unsigned flags,
                       const ada_groups* grp = nullptr, const ada_tau_control* ctl = nullptr, const double* tau_in = nullptr,
-                      const float* thr_in = nullptr, double* tau_out = nullptr, float* thr_out = nullptr) {
-    const Workspace w = carve(ws, T);
+                      const float* thr_in = nullptr, double* tau_out = nullptr, float* thr_out = nullptr, int static_T = 0) {
+    const Workspace w = carve(ws, static_T ? static_T : T);
     FusedParams p = {X, ld, T, d, prev_idx, r_dev, r, threshold_of(tau),
                      (flags & ADA_FLAG_CROSS_EARLIER_ONLY) ? 1 : 0, w.hits, hit_words(r), gamma,
                      w.meta + META_TICKET, idx, adds, removes, counts,
@@ -1522,7 +1528,7 @@ int run_cascade_fused(const void* X, int T, int d, long long ld, int dtype, floa
                               (flags & ADA_FLAG_CROSS_EARLIER_ONLY) ? 1 : 0};
     const hipError_t e = dispatch(dtype, d, [&](auto v) {
         using V = decltype(v);
-        return launch_gamma_fix<typename V::In, V::wide>(cross, GammaFix{w.hits, reinterpret_cast<const uint32_t*>(w.is_rep), 0}, r, st);
+        return launch_gamma_fix<typename V::In, V::wide>(cross, GammaFix{w.hits, reinterpret_cast<const uint32_t*>(w.is_rep), 0, w.meta, static_T ? zero_words(w, static_T) : 0}, r, st);
     });
     return e == hipSuccess ? ADA_OK : ADA_ERR_DEVICE;
 }
@@ -1922,11 +1928,11 @@ int run_layers_screened(const ScreenPlan& plan, const void* const* X_layers, int
 // gamma holds the exact gamma^cross of step 8.  Arguments checked by the caller; adds / removes / gram_ops / gamma may be NULL.
 int run_cascade(const void* X, int T, int d, long long ld, int dtype, float tau, const int32_t* prev_idx, int r,
                 const int32_t* r_dev, int32_t* idx, int32_t* adds, int32_t* removes, int32_t* counts,
-                uint64_t* gram_ops, float* gamma, void* ws, hipStream_t st, unsigned flags) {
+                uint64_t* gram_ops, float* gamma, void* ws, hipStream_t st, unsigned flags, int static_T = 0) {
     if (!(flags & ADA_FLAG_TWO_PASS) && T <= FUSED_MAX_T)
         return run_cascade_fused(X, T, d, ld, dtype, tau, prev_idx, r, r_dev, idx, adds, removes, counts, gram_ops,
-                                 gamma, ws, st, flags);
-    const Workspace w = carve(ws, T);
+                                 gamma, ws, st, flags, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, static_T);
+    const Workspace w = carve(ws, static_T ? static_T : T);
     float* g = gamma ? gamma : w.gamma;
     const float thr = threshold_of(tau);
     const PrepParams prep = {prev_idx, r_dev, r, 1};
@@ -2116,13 +2122,15 @@ int ada_cascade_step_static(const void* X, int T, int d, int64_t ld, int dtype, 
     const size_t ws_bytes = ws_bytes_for(ADA_STATIC_MAX_T);   // (what a step uses of a workspace is what the array holds)
     if (int e = check_common(X, T, d, ld, dtype, tau, ws, ws_bytes)) return e;
     if (r < 1 || r > T) return ADA_ERR_SHAPE;
-    // The counters a step relies on being zero (tickets, queue, hand-over word) are cleared by a fill kernel, so the
-    // array is good whatever an earlier call left behind; everything else a step reads it writes first.
-    // (scalars, arg-max keys and first-hit records lie side by side: one launch)
-    const Workspace w = carve(ws, T);
-    if (fill_u32(w.meta, (size_t)(w.first + T - (uint32_t*)w.meta), 0u, (hipStream_t)stream) != hipSuccess) return ADA_ERR_DEVICE;
+    // The array is laid out for its largest T whatever the call's, so what a call leaves at zero is what the next one needs at zero.
+    // With a gamma output the call's last launch (k_gamma_fix) clears it besides, whatever the call found there; without one
+    // nothing runs behind the step, and a fill in front of it does.  (With one there was a fill in front as well: 2.4 us on the
+    // device and on the host, of 16.8 at T=197, d=768.)
+    const Workspace w = carve(ws, ADA_STATIC_MAX_T);
+    if ((!gamma || (flags & ADA_FLAG_TWO_PASS)) &&
+        fill_u32(w.meta, (size_t)zero_words(w, ADA_STATIC_MAX_T), 0u, (hipStream_t)stream) != hipSuccess) return ADA_ERR_DEVICE;
     return run_cascade(X, T, d, ld, dtype, tau, prev_idx, r, r_dev, idx, adds, removes, counts, gram_ops, gamma, ws,
-                       (hipStream_t)stream, flags);
+                       (hipStream_t)stream, flags, ADA_STATIC_MAX_T);
 }
 
 namespace {

@@ -51,6 +51,34 @@ def test_static_scratch_matches_the_workspace_form_on_two_calls_in_a_row(flags):
     both_forms(wl.small(T=300, d=96, K=40, L=2, dtype="f32", seed=33, p=0.1), flags)
 
 
+@pytest.mark.parametrize("seed", [0, 1])
+def test_every_call_leaves_the_scratch_as_the_next_one_needs_it(seed):
+    """Calls of all sizes, with and without gamma, in one and in two launches, refused ones among them, one behind the other: the
+    array is laid out once for all of them and nothing clears it in front of a call with gamma."""
+    print("[case] no-alloc entry point, calls in a row, seed %d" % seed, flush=True)
+    rng = np.random.default_rng(seed)
+    for n, T in enumerate((4096, 64, 1000, 2049, 7, 4095, 333, 513)):
+        w = wl.small(T=T, d=64, K=max(1, T // 6), L=2, dtype="bf16", seed=100 + T, p=0.1)
+        xs = [x.to(DEV) for x in wl.layer_list(w)]
+        full = pa.fetch(pa.ada_select_full(xs[0], w.tau))
+        prev = torch.from_numpy(full["idx"]).to(DEV)
+        for gamma, flags, refused in rng.permutation([(1, 0, 0), (0, 0, 0), (1, 0, 1), (1, pa.FLAG_TWO_PASS, 0), (1, 0, 0)]).tolist():
+            want = pa.ada_cascade_step(xs[1], w.tau, prev, flags=flags)
+            out = {k: torch.full_like(v, -1) for k, v in want.items() if isinstance(v, torch.Tensor)}
+            if not gamma:
+                del out["gamma"]
+            if refused:                                       # the count on the device is out of range: reported there
+                pa.ada_cascade_step_static(xs[1], w.tau, prev, out, r_dev=torch.full((1,), T + 1, dtype=torch.int32, device=DEV), flags=flags)
+                assert int(out["counts"][3]) == 2 and int(out["counts"][0]) == 0
+                continue
+            pa.ada_cascade_step_static(xs[1], w.tau, prev, out, flags=flags)
+            r, na, nr, status = out["counts"].cpu().tolist()
+            assert status == 0 and torch.equal(out["counts"], want["counts"]) and torch.equal(out["gram_ops"], want["gram_ops"]), (n, T)
+            for k, m in (("idx", r), ("adds", na), ("removes", nr)):
+                assert torch.equal(out[k][:m], want[k][:m]), (n, T, k)
+            assert not gamma or torch.equal(out["gamma"], want["gamma"]), (n, T)
+
+
 def test_static_scratch_rejects_what_does_not_fit():
     T = pa.STATIC_MAX_T + 1
     x = torch.zeros((T, 64), dtype=torch.bfloat16, device=DEV)
