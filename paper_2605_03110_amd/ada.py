@@ -257,7 +257,8 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream(stream) -> int:
-    return torch.cuda.current_stream().cuda_stream if stream is None else stream.cuda_stream
+    # torch.cuda.current_stream() makes a Stream object of it: 2.8 us, this 0.2 (a call of three launches is 15 us on the host)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) if stream is None else stream.cuda_stream
 
 
 def _check_layers(Xs: Sequence[torch.Tensor], check):
