@@ -1649,7 +1649,7 @@ bool screen_streams(const ScreenParams& sp, size_t esz) {
     return odd % 128 == 0 && (double)sp.G * sp.L * sp.T * sp.d * esz >= 192.0 * (1 << 20);
 }
 
-template <typename In, int LPR>
+template <typename In, int LPR, int UN, bool WHOLE>
 hipError_t launch_screen_exact(const ScreenParams& sp, hipStream_t st) {
     // two rows per lane group where that leaves enough workgroups to fill the chip, one where it does not
     const int rows = 256 / LPR, units = sp.G * sp.L;
@@ -1658,11 +1658,26 @@ hipError_t launch_screen_exact(const ScreenParams& sp, hipStream_t st) {
     const dim3 grid((unsigned)((total + 7) / 8 * 8));
     ProfScope ps(ADA_K_SCREEN, st);
     const bool stream = screen_streams(sp, sizeof(In));
-    if (passes == 2 && stream) hipLaunchKernelGGL((k_screen_exact<In, LPR, 2, true>), grid, dim3(256), 0, st, sp, rb, total);
-    else if (passes == 2) hipLaunchKernelGGL((k_screen_exact<In, LPR, 2, false>), grid, dim3(256), 0, st, sp, rb, total);
-    else if (stream) hipLaunchKernelGGL((k_screen_exact<In, LPR, 1, true>), grid, dim3(256), 0, st, sp, rb, total);
-    else hipLaunchKernelGGL((k_screen_exact<In, LPR, 1, false>), grid, dim3(256), 0, st, sp, rb, total);
+    if (passes == 2 && stream) hipLaunchKernelGGL((k_screen_exact<In, LPR, UN, WHOLE, 2, true>), grid, dim3(256), 0, st, sp, rb, total);
+    else if (passes == 2) hipLaunchKernelGGL((k_screen_exact<In, LPR, UN, WHOLE, 2, false>), grid, dim3(256), 0, st, sp, rb, total);
+    else if (stream) hipLaunchKernelGGL((k_screen_exact<In, LPR, UN, WHOLE, 1, true>), grid, dim3(256), 0, st, sp, rb, total);
+    else hipLaunchKernelGGL((k_screen_exact<In, LPR, UN, WHOLE, 1, false>), grid, dim3(256), 0, st, sp, rb, total);
     return hipGetLastError();
+}
+
+// Pieces of a row in flight per lane: as many of four, three or two as rows are whole numbers of (see screen_products), else four.  Rows of
+// 32 and 16 pieces go over twice the lanes, two pieces each: 16 heads x 256, 8 layers 34.3 -> 28.0 us, all that changed in the pass.
+template <typename In, int LPR>
+hipError_t launch_screen_exact_any(const ScreenParams& sp, int np, hipStream_t st) {
+    if (sp.d * (int)sizeof(In) % 16 == 0) {
+        if constexpr (LPR == 8) {
+            if (np == 32) return launch_screen_exact<In, 16, 2, true>(sp, st);
+            if (np == 16) return launch_screen_exact<In, 8, 2, true>(sp, st);
+        }
+        if (np % (LPR * 4) == 0) return launch_screen_exact<In, LPR, 4, true>(sp, st);
+        if (np % (LPR * 3) == 0) return launch_screen_exact<In, LPR, 3, true>(sp, st);
+    }
+    return launch_screen_exact<In, LPR, 4, false>(sp, st);
 }
 
 template <typename In, int LPR>
@@ -1673,7 +1688,7 @@ hipError_t launch_screen_rest(const ScreenParams& sp, hipStream_t st) {
     k = k < 8 ? 8 : k;
     k = k > ntile ? ntile : k;
     ProfScope ps(ADA_K_SCREEN, st);
-    hipLaunchKernelGGL((k_screen_rest<In, LPR>), dim3((unsigned)(k * units)), dim3(256), 0, st, sp, ntile);
+    hipLaunchKernelGGL((k_screen_rest<In, LPR>), dim3((unsigned)(k * units)), dim3(256), sp.count_pairs ? 0 : (sp.T + 3) / 4 * 8, st, sp, ntile);
     return hipGetLastError();
 }
 
@@ -1690,8 +1705,12 @@ void launch_screen_pairs(const ScreenParams& sp, const PairItems& it, dim3 grid,
 
 // The graph of near pairs of every unit of sp.
 template <typename In>
-hipError_t launch_screen(const ScreenParams& sp, hipStream_t st) {
+hipError_t launch_screen(ScreenParams& sp, hipStream_t st) {
     const int units = sp.G * sp.L;
+    // Who counts the pairs inside clusters.  The exact pass takes an atomic with a return per token for it, 20 thousand of them a microsecond
+    // from the whole chip, which short rows do not hide; each workgroup of k_screen_rest a histogram of its unit in LDS, 1 us.  16 heads
+    // x 256, 8 layers of T=2048 (262 thousand tokens): the pass 32.0 -> 28.0 us, k_screen_rest 4.7 -> 5.6.
+    sp.count_pairs = (sp.d * (int)sizeof(In) + 15) / 16 >= 128 || (long long)units * sp.T < 65536;
     {
         ProfScope ps(ADA_K_SCREEN, st);
         switch (sp.nch) {
@@ -1721,8 +1740,8 @@ hipError_t launch_screen(const ScreenParams& sp, hipStream_t st) {
     }
     // four pieces of a row in flight per lane, at least eight lanes (a cache line) side by side
     const int np = (sp.d * (int)sizeof(In) + 15) / 16;
-    hipError_t e = np >= 256 ? launch_screen_exact<In, 64>(sp, st) : np >= 128 ? launch_screen_exact<In, 32>(sp, st)
-                 : np >= 64 ? launch_screen_exact<In, 16>(sp, st) : launch_screen_exact<In, 8>(sp, st);
+    hipError_t e = np >= 256 ? launch_screen_exact_any<In, 64>(sp, np, st) : np >= 128 ? launch_screen_exact_any<In, 32>(sp, np, st)
+                 : np > 32 ? launch_screen_exact_any<In, 16>(sp, np, st) : launch_screen_exact_any<In, 8>(sp, np, st);
     if (e != hipSuccess) return e;
     return np >= 256 ? launch_screen_rest<In, 64>(sp, st) : np >= 128 ? launch_screen_rest<In, 32>(sp, st)
          : np >= 64 ? launch_screen_rest<In, 16>(sp, st) : launch_screen_rest<In, 8>(sp, st);

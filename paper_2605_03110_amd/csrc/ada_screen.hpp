@@ -153,6 +153,7 @@ struct ScreenParams {
     float f2, safe, thr, cos_tight;
     uint32_t open;             // unexplained candidates of a unit above which it is dense
     int edge_cap;              // see ScreenUnit
+    int count_pairs;           // the exact pass counts the pairs inside clusters (else k_screen_rest does)
     float* gamma;              // one unit: largest |cos| of the pairs multiplied out (bits under an integer max), or NULL
     float* inv_norm;           // one unit: inverse norms of the rows, or NULL
     const void* X[SCREEN_MAX_LAYERS];
@@ -511,38 +512,36 @@ template <> __device__ inline float screen_dot<uint16_t>(u32x4 a, u32x4 b, float
     return s;
 }
 
-// <x, y>, <x, x> and <y, y> by LPR neighbouring lanes (li: this lane's place among them); every lane gets the sums.
-// Four pieces of each row are requested before the first is used (eight leave fewer waves room: 465 us instead of 444 at
-// 32 units of T = 8192, d = 4096).  STREAM: x is read once and not kept in the caches.
-template <typename In, int LPR, bool STREAM = false>
-__device__ inline void screen_products(const In* x, const In* y, bool two, int d, int li, float* xy, float* xx, float* yy) {
-    constexpr int EPP = 16 / (int)sizeof(In), UN = 4;
+// <x, y>, <x, x> and <y, y> (TWO; else <x, x> alone) by LPR neighbouring lanes (li: this lane's place among them); every lane gets the sums.
+// UN pieces of each row are requested before the first is used (four; eight leave fewer waves room: 465 us instead of 444 at
+// 32 units of T = 8192, d = 4096).  STREAM: x is read once and not kept in the caches.  WHOLE: a row is so many times UN pieces of all
+// lanes, so no piece is pulled back into it, cut or left out.
+template <typename In, int LPR, bool STREAM = false, int UN = 4, bool WHOLE = false, bool TWO = true>
+__device__ inline void screen_products(const In* x, const In* y, int d, int li, float* xy, float* xx, float* yy) {
+    constexpr int EPP = 16 / (int)sizeof(In);
     const int np = (d + EPP - 1) / EPP;
     float sxy = 0.f, sxx = 0.f, syy = 0.f;
     for (int p0 = li; p0 < np; p0 += LPR * UN) {
         u32x4 a[UN], b[UN];
+        auto from = [&](int u) { return WHOLE ? (p0 + u * LPR) * EPP : min(min(p0 + u * LPR, np - 1) * EPP, d - EPP); };
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
-            const int e = min(min(p0 + u * LPR, np - 1) * EPP, d - EPP);
-            const auto* piece = reinterpret_cast<const u32x4_any*>(x + e);
+            const auto* piece = reinterpret_cast<const u32x4_any*>(x + from(u));
             if constexpr (STREAM) a[u] = __builtin_nontemporal_load(piece);
             else a[u] = *piece;
         }
-        if (two) {
+        if constexpr (TWO) {
 #pragma unroll
-            for (int u = 0; u < UN; ++u) {
-                const int e = min(min(p0 + u * LPR, np - 1) * EPP, d - EPP);
-                b[u] = *reinterpret_cast<const u32x4_any*>(y + e);
-            }
+            for (int u = 0; u < UN; ++u) b[u] = *reinterpret_cast<const u32x4_any*>(y + from(u));
         }
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
             const int pc = p0 + u * LPR;
-            if (pc < np) {
-                const int cut = pc * EPP - min(pc * EPP, d - EPP);
+            if (WHOLE || pc < np) {
+                const int cut = WHOLE ? 0 : pc * EPP - min(pc * EPP, d - EPP);
                 const u32x4 va = cut > 0 ? clear_head<In>(a[u], cut) : a[u];
                 sxx = screen_dot<In>(va, va, sxx);
-                if (two) {
+                if constexpr (TWO) {
                     sxy = screen_dot<In>(va, b[u], sxy);
                     const u32x4 vb = cut > 0 ? clear_head<In>(b[u], cut) : b[u];
                     syy = screen_dot<In>(vb, vb, syy);
@@ -552,9 +551,11 @@ __device__ inline void screen_products(const In* x, const In* y, bool two, int d
     }
 #pragma unroll
     for (int o = LPR / 2; o > 0; o >>= 1) {
-        sxy += __shfl_xor(sxy, o, 64);
         sxx += __shfl_xor(sxx, o, 64);
-        syy += __shfl_xor(syy, o, 64);
+        if constexpr (TWO) {
+            sxy += __shfl_xor(sxy, o, 64);
+            syy += __shfl_xor(syy, o, 64);
+        }
     }
     *xy = sxy;
     *xx = sxx;
@@ -565,6 +566,9 @@ __device__ inline float screen_cos(float xy, float xx, float yy) {
     const float ix = xx > 0.f ? 1.0f / sqrtf(xx) : 0.f, iy = yy > 0.f ? 1.0f / sqrtf(yy) : 0.f;
     return (fabsf(xy) * ix) * iy;                             // a zero row normalises to zero: all its cosines are 0
 }
+
+// All waves' LDS operations done, and everybody here.  (A fenced barrier would also wait for the stores to memory.)
+__device__ inline void screen_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // (k_screen_rest has to agree: a quarter of the pairs is more than SCREEN_OPEN per token.  The full selection needs the norms
 // in any case.  Nobody writes the counts while they are read here, so scalar loads will do; for short rows and sequences the
@@ -582,16 +586,19 @@ __device__ inline bool screen_crowded(const ScreenParams& p, const char* unit) {
 // k_screen_exact: norm of every row, product with its pivot, cluster.  HBM: X once.  Every XCD takes a contiguous range of
 // the rows of all units, so that a unit's pivots (a few hundred rows, a few MB) are read into one L2 and not into eight.
 // What a row needs besides X (pivot, sketch norm, the pivot's own pivot) is requested for all of a lane group's rows at
-// once, and the places that the cluster sizes hand back are summed after the last row: a row waits for X alone.
+// once, a row's sums go to a lane of their own, and what follows from them is done once for all of them; no wave waits for its
+// stores.  Instructions bind short rows and cost long ones waves in flight: 28 x T=2048, d=4096 86.8 -> 83.7 us, 32 x T=8192 389 -> 380,
+// 16 heads x 256, 8 layers 34.3 -> 28.0 (before: pieces clamped, cut and left out one by one, every row's divisions, fenced barriers).
+// X alone would take 67 us of the first (7.0 TB/s), X and the pivots in any order 77.
 // A unit whose candidates are a quarter of all pairs and more is left alone, for k_screen_rest to call dense: its rows share
 // a direction (or a few columns), which the sketch cannot tell from being near.
 // Two rows per lane group: the rows in flight on an XCD (256 workgroups of 8 at d = 4096) then stay about within one unit, whose
 // pivots its L2 can hold; four rows spread over two units (STREAM, 28 x T=2048, d=4096: call 150 us against 143; 32 x T=8192:
 // 632 against 619), one row starts more workgroups (145, 619).
 // STREAM: see screen_streams.
-template <typename In, int LPR, int PASSES, bool STREAM>
+template <typename In, int LPR, int UN, bool WHOLE, int PASSES, bool STREAM>
 __global__ __launch_bounds__(256) void k_screen_exact(ScreenParams p, int row_blocks, int total) {
-    __shared__ uint32_t s_pairs, s_flags;
+    __shared__ uint32_t s_pairs;
     const int per = (total + 7) >> 3;
     const int w = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
     if (w >= total || (int)(blockIdx.x >> 3) >= per) return;
@@ -605,56 +612,81 @@ __global__ __launch_bounds__(256) void k_screen_exact(ScreenParams p, int row_bl
     float* rho = reinterpret_cast<float*>(base + U.o_rho);
     uint16_t* cl = reinterpret_cast<uint16_t*>(base + U.o_cl);
     const bool crowded = LPR == 64 && screen_crowded(p, base);
-    if (threadIdx.x == 0) { s_pairs = 0u; s_flags = 0u; }
-    __syncthreads();
+    if (threadIdx.x == 0) s_pairs = 0u;
+    screen_barrier();
     const int li = threadIdx.x & (LPR - 1);
     const int t0 = rb * PASSES * (256 / LPR) + (int)threadIdx.x / LPR;
-    int q[PASSES], qq[PASSES];
-    float ss[PASSES];
-    uint32_t place[PASSES], fl = 0u;
+    // lane k of a group keeps what row k's sums are wanted for: they are looked at once, after the last row
+    static_assert(PASSES <= LPR, "a lane per row");
+    const int rows = 256 / LPR, mine = t0 + min(li, PASSES - 1) * rows, t_mine = min(mine, p.T - 1);
+    const int q_mine = piv[t_mine];
+    const float ss = rho[t_mine];
+    int q[PASSES];
 #pragma unroll
-    for (int k = 0; k < PASSES; ++k) {
-        const int t = min(t0 + k * (256 / LPR), p.T - 1);
-        q[k] = piv[t];
-        ss[k] = rho[t];
-    }
+    for (int k = 0; k < PASSES; ++k) q[k] = PASSES == 1 ? q_mine : piv[min(t0 + k * rows, p.T - 1)];
     if (crowded) return;                                      // uniform
-#pragma unroll
-    for (int k = 0; k < PASSES; ++k) { qq[k] = piv[q[k]]; place[k] = 0u; }
+    const int qq = piv[q_mine];
+    float xy = 0.f, xx = 0.f, yy = 0.f;
+    uint32_t place = 0u, fl = 0u;
 #pragma unroll
     for (int k = 0; k < PASSES; ++k) {
-        const int t = t0 + k * (256 / LPR);
+        // (a wave's row: scalars.  Shorter rows take the second product with themselves where they have no pivot, and not a branch.)
+        const int t = LPR == 64 ? __builtin_amdgcn_readfirstlane(t0 + k * rows) : t0 + k * rows;
+        const int s = LPR == 64 ? __builtin_amdgcn_readfirstlane(q[k]) : q[k];
         if (t < p.T) {
-            float xy, xx, yy;
-            screen_products<In, LPR, STREAM>(X + (size_t)t * (size_t)p.ld, X + (size_t)q[k] * (size_t)p.ld, q[k] != t, p.d, li, &xy, &xx, &yy);
-            if (li == 0) {
-                const float r2 = xx > 0.f ? ss[k] / xx : 1.f;     // (a zero row has no cosines: nothing to bound)
-                rho[t] = r2;
-                if (p.inv_norm) p.inv_norm[t] = xx > 0.f ? 1.0f / sqrtf(xx) : 0.f;
-                fl |= r2 < p.f2 ? (uint32_t)SF_LOW : 0u;
-                int c = t;
-                if (q[k] != t && screen_cos(xy, xx, yy) >= p.cos_tight) {
-                    c = q[k];
-                    if (qq[k] != q[k]) fl |= SF_MESH;             // the pivot may not be a member of its own cluster
-                    place[k] = (uint32_t)atomicAdd(size + q[k], 1) + 1u;   // pairs with the pivot and with earlier arrivals
-                }
-                cl[t] = (uint16_t)c;
-            }
+            const In *x = X + (size_t)t * (size_t)p.ld, *y = X + (size_t)s * (size_t)p.ld;
+            float a, b, c;
+            if (LPR < 64 || s != t) screen_products<In, LPR, STREAM, UN, WHOLE>(x, y, p.d, li, &a, &b, &c);
+            else screen_products<In, LPR, STREAM, UN, WHOLE, false>(x, y, p.d, li, &a, &b, &c);
+            if (li == k) { xy = a; xx = b; yy = c; }
         }
     }
-    if (li == 0) {
-        uint32_t n = 0u;
-#pragma unroll
-        for (int k = 0; k < PASSES; ++k) n += place[k];
-        if (n) atomicAdd(&s_pairs, n);
-        if (fl) atomicOr(&s_flags, fl);
+    if (li < PASSES && mine < p.T) {
+        const float r2 = xx > 0.f ? ss / xx : 1.f;            // (a zero row has no cosines: nothing to bound)
+        rho[mine] = r2;
+        if (p.inv_norm) p.inv_norm[mine] = xx > 0.f ? 1.0f / sqrtf(xx) : 0.f;
+        fl |= r2 < p.f2 ? (uint32_t)SF_LOW : 0u;
+        int c = mine;
+        if (q_mine != mine && screen_cos(xy, xx, yy) >= p.cos_tight) {
+            c = q_mine;
+            if (qq != q_mine) fl |= SF_MESH;                  // the pivot may not be a member of its own cluster
+            if (p.count_pairs) place = (uint32_t)atomicAdd(size + q_mine, 1) + 1u;   // pairs with the pivot and with earlier arrivals
+        }
+        cl[mine] = (uint16_t)c;
     }
+    uint32_t* hdr = reinterpret_cast<uint32_t*>(base) + SU_PART + (blockIdx.x & 7) * 32;
+    fl = (__ballot(fl & SF_LOW) != 0ull ? (uint32_t)SF_LOW : 0u) | (__ballot(fl & SF_MESH) != 0ull ? (uint32_t)SF_MESH : 0u);
+    if (fl && (threadIdx.x & 63) == 0 && (__hip_atomic_load(hdr + SU_FLAGS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & fl) != fl)
+        atomicOr(hdr + SU_FLAGS, fl);
+    if (!p.count_pairs) return;                               // uniform
+    if (place) atomicAdd(&s_pairs, place);
+    screen_barrier();
+    if (threadIdx.x == 0 && s_pairs) atomicAdd(hdr + SU_PAIRS, s_pairs);
+}
+
+// Pairs inside the clusters of a unit, by 256 threads: how many tokens of its cluster came before, summed (in any order).
+__device__ inline uint32_t screen_pairs_inside(const uint16_t* cl, int T) {
+    extern __shared__ __align__(16) char lds[];               // [T] counts, two per word
+    __shared__ uint32_t s_sum;
+    uint32_t* count = reinterpret_cast<uint32_t*>(lds);
+    const int tid = threadIdx.x;
+    uint32_t sum = 0u;
+    if (tid == 0) s_sum = 0u;
+    for (int w = tid; w < (T + 1) / 2; w += 256) count[w] = 0u;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t* hdr = reinterpret_cast<uint32_t*>(base) + SU_PART + (blockIdx.x & 7) * 32;
-        if (s_pairs) atomicAdd(hdr + SU_PAIRS, s_pairs);
-        if (s_flags) atomicOr(hdr + SU_FLAGS, s_flags);
+    for (int t0 = tid; t0 < T; t0 += 256 * 8) {
+        int c[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) c[u] = cl[min(t0 + 256 * u, T - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (t0 + 256 * u < T) sum += atomicAdd(&count[c[u] >> 1], 1u << (16 * (c[u] & 1))) >> (16 * (c[u] & 1)) & 0xFFFFu;
     }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if ((tid & 63) == 0) atomicAdd(&s_sum, sum);
+    __syncthreads();
+    return s_sum;
 }
 
 // k_screen_rest: the candidates that no cluster explains.  Units without any (the counts agree) are left at once, and so are
@@ -675,7 +707,11 @@ __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) 
     int layer, group;
     char* base = screen_unit(p, U, unit, &layer, &group);
     uint32_t* hdr = reinterpret_cast<uint32_t*>(base);
-    const ScreenCounts n_unit = screen_counts(hdr);
+    ScreenCounts n_unit = screen_counts(hdr);
+    if (!p.count_pairs) {
+        n_unit.pairs = screen_pairs_inside(reinterpret_cast<const uint16_t*>(base + U.o_cl), p.T);
+        if ((int)blockIdx.x < units && threadIdx.x == 0) hdr[SU_PART + SU_PAIRS] = n_unit.pairs;   // (where the exact pass leaves its counts)
+    }
     if (n_unit.flags == 0u && n_unit.cand == n_unit.pairs) return;
     if (n_unit.cand > n_unit.pairs + p.open) {
         if ((int)blockIdx.x < units && tid == 0) __hip_atomic_store(hdr + SU_DENSE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -741,7 +777,7 @@ __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) 
             const uint32_t e = s_pair[k];
             const int s = (int)(e >> 16), t = (int)(e & 0xFFFFu);
             float xy, xx, yy;
-            screen_products<In, LPR>(X + (size_t)t * (size_t)p.ld, X + (size_t)s * (size_t)p.ld, true, p.d, li, &xy, &xx, &yy);
+            screen_products<In, LPR>(X + (size_t)t * (size_t)p.ld, X + (size_t)s * (size_t)p.ld, p.d, li, &xy, &xx, &yy);
             const float c = screen_cos(xy, xx, yy);
             if (p.gamma && li == 0 && c > 0.f) atomicMax(reinterpret_cast<uint32_t*>(p.gamma) + t, __float_as_uint(c));
             if (li == 0 && c >= p.thr) s_edge[atomicAdd(&s_edges, 1)] = uint2{e, __float_as_uint(c)};
@@ -811,9 +847,6 @@ template <int U> __device__ inline int chain_token(int u) {
     if constexpr (U > 8) asm volatile("" : "+v"(t));          // (what is formed from all of a lane's tokens in advance is more than there are registers)
     return t + 64 * u;
 }
-
-// All waves' LDS operations done, and everybody here.  (A fenced barrier would also wait for the stores to memory.)
-__device__ inline void chain_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // One layer's lists, counts and Gram operations from the bits of its set and of the one before (any workgroup size up to
 // 1024; scratch: LIST_SCRATCH bytes of LDS).
@@ -1063,10 +1096,10 @@ __device__ inline void screen_assign(const ChainParams& c, const ScreenUnit& SU,
                     float xy, xx, yy;
                     if (c.f32) {
                         const float* X = screen_x<float>(p, l, g);
-                        screen_products<float, 64>(X + (size_t)t * (size_t)p.ld, X + (size_t)q * (size_t)p.ld, true, p.d, lane, &xy, &xx, &yy);
+                        screen_products<float, 64>(X + (size_t)t * (size_t)p.ld, X + (size_t)q * (size_t)p.ld, p.d, lane, &xy, &xx, &yy);
                     } else {
                         const uint16_t* X = screen_x<uint16_t>(p, l, g);
-                        screen_products<uint16_t, 64>(X + (size_t)t * (size_t)p.ld, X + (size_t)q * (size_t)p.ld, true, p.d, lane, &xy, &xx, &yy);
+                        screen_products<uint16_t, 64>(X + (size_t)t * (size_t)p.ld, X + (size_t)q * (size_t)p.ld, p.d, lane, &xy, &xx, &yy);
                     }
                     const unsigned long long cand = ((unsigned long long)__float_as_uint(screen_cos(xy, xx, yy)) << 32) | (uint32_t)(INT_MAX - q);
                     best = cand > best ? cand : best;
@@ -1192,7 +1225,7 @@ __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
 #pragma unroll
                 for (int u = 0; u < U; ++u)
                     atomicMin(&slot[__builtin_amdgcn_inverse_ballot_w64(in[u]) ? ahead[k][u] : TOKENS + lane], stamp | (uint32_t)tok(u));
-                chain_barrier();
+                screen_barrier();
 #pragma unroll
                 for (int u = 0; u < U; ++u) v[u] = slot[ahead[k][u]] - stamp;   // this layer's stamp is the smallest so far
                 clusters(min(i + D, p.L - 1), ahead[k]);

@@ -138,6 +138,33 @@ def test_walk_over_plain_layers_and_layers_with_edges(T, d, L, edged, flags):
     check(xs_cpu, 0.1, *(res[k].cpu() for k in ("idx", "counts", "gram_ops", "adds", "removes")), flags, "walk")
 
 
+@pytest.mark.parametrize("d,dtype", [(d, t) for d in (64, 128, 192, 200, 256, 264, 384, 512, 520, 768, 1024, 1032, 1536, 2048, 3072, 3080, 1001) for t in ("bf16", "f32")])
+def test_rows_of_every_length(d, dtype):
+    """Rows that are so many whole pieces per lane, one piece more, and rows that end inside one: every form of the products."""
+    print("[case] row lengths: d=%d %s" % (d, dtype), flush=True)
+    xs_cpu = activations("clusters", 131, d, 2, dtype, seed=d)
+    res = pa.ada_cascade_layers([x.to(DEV) for x in xs_cpu], 0.1)
+    check(xs_cpu, 0.1, *(res[k].cpu() for k in ("idx", "counts", "gram_ops", "adds", "removes")), 0, "d=%d" % d)
+
+
+@pytest.mark.parametrize("T,d,G,L", [(701, 64, 24, 4), (2050, 128, 4, 8)])
+def test_pairs_counted_behind_the_exact_pass(T, d, G, L):
+    """Short rows of many units: the pairs inside clusters are counted by the launch behind.  Each sequence alone, whose pairs the exact
+    pass counts, gives the same; plain sequences, some with edges, dense ones."""
+    print("[case] pairs counted behind: T=%d d=%d G=%d L=%d" % (T, d, G, L), flush=True)
+    assert G * L * T >= 65536 and L * T < 65536
+    kinds = ("clusters", "loose", "strays", "common", "clusters", "signs")
+    per = [[x.to(DEV) for x in activations(kinds[g % len(kinds)], T, d, L, "bf16", seed=g)] for g in range(G)]
+    res = pa.ada_cascade_layers_grouped([torch.stack([p[l] for p in per]) for l in range(L)], 0.1, want_lists=True)
+    for g in range(G):
+        one = pa.ada_cascade_layers(per[g], 0.1)
+        assert torch.equal(res["counts"][g], one["counts"]) and torch.equal(res["gram_ops"][g], one["gram_ops"]), g
+        for k, c in (("idx", 0), ("adds", 1), ("removes", 2)):
+            for l in range(1 if c else 0, L):
+                n = int(one["counts"][l, c])
+                assert torch.equal(res[k][g, l, :n], one[k][l, :n]), (g, l, k)
+
+
 @pytest.mark.parametrize("kinds,T,d,dtype", [(("clusters", "clusters", "clusters"), 200, 96, "bf16"), (("clusters", "common", "loose"), 260, 320, "bf16"),
                                              (("common", "common", "clusters", "common", "loose"), 600, 256, "bf16"),
                                              (("outliers", "signs"), 131, 1001, "f32")])
