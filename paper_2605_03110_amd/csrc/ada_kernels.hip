@@ -1725,7 +1725,7 @@ hipError_t launch_screen(ScreenParams& sp, hipStream_t st) {
         }
     }
     {
-        const PairItems it(sp.T, units);
+        const PairItems it(sp.T, units, sp.nch);
         const int total = it.per_unit * units;
         const dim3 grid((unsigned)((total + 7) / 8 * 8));
         ProfScope ps(ADA_K_SCREEN, st);

@@ -193,6 +193,10 @@ template <> __device__ inline void screen_load8<float>(const float* row, int e0,
     }
 }
 
+// All waves' LDS operations done, and everybody here.  (A fenced barrier would also wait for
+// the loads and stores in flight to memory, a microsecond or two in which a finished workgroup keeps its place.)
+__device__ inline void screen_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // ------------------------------------------------------------------------------------------------
 // k_screen_sketch: eight lanes per row, eight columns per lane and column group.  Reads n1 / d of X, one cache line (two
 // for fp32) per row and group; all that a lane needs is requested before the first of it is used.  NCH: column groups, or 0:
@@ -311,14 +315,15 @@ __device__ inline uint32_t screen_first(uint32_t bits) {      // position of the
 // Work items of a unit: strips of 256 tokens, each against its earlier tokens in pieces.  A piece is 256 x `wide` tokens, or
 // 256 / `cut` of them: long pieces spend less of their time on starting up (a piece of 256 took about half of it for
 // that), short ones are needed to fill the chip.  Two workgroups per CU fill it: halved pieces up to four per CU cost a layer
-// loop of 12 x T=2048, d=768 50.8 us instead of 48.7, 2 x T=4096, d=512 36.0 instead of 34.0.  Strips come in groups of
+// loop of 12 x T=2048, d=768 50.8 us instead of 48.7, 2 x T=4096, d=512 36.0 instead of 34.0.  With one column group a piece has a
+// third of the products: 128 x T=2048, d=256 29.3 us in pieces of 256, 26.5 of 512, 27.0 of 1024.  Strips come in groups of
 // `wide` with the same number of pieces.
 struct PairItems {
     int wide, cut, per_unit;
-    __host__ __device__ PairItems(int T, int units) {
+    __host__ __device__ PairItems(int T, int units, int nch) {
         const int nb = (T + 255) / 256;
         const long long tiles = (long long)nb * (nb + 1) / 2 * units;
-        wide = tiles >= 12288 ? 4 : tiles >= 6144 ? 2 : 1;
+        wide = tiles >= 12288 ? 4 : tiles >= (nch == 1 ? 2048 : 6144) ? 2 : 1;
         cut = tiles >= 512 ? 1 : tiles >= 256 ? 2 : 4;
         const int q = (nb + wide - 1) / wide;
         per_unit = wide * (q * (q + 1) / 2) * cut;
@@ -369,7 +374,7 @@ __global__ __launch_bounds__(256, screen_pair_waves(NCH, TB)) void k_screen_pair
     char* base = screen_unit(p, U, unit, &layer, &group);
     it.get(w - unit * it.per_unit, &tb, &s_lo, &sblk);
     if (threadIdx.x == 0) s_cand = 0;
-    __syncthreads();
+    screen_barrier();
     const int T = p.T, nch = NCH > 0 ? NCH : p.nch, nblk = (T + 31) >> 5;
     const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -458,7 +463,7 @@ __global__ __launch_bounds__(256, screen_pair_waves(NCH, TB)) void k_screen_pair
         for (int o = 32; o > 0; o >>= 1) cand += __shfl_xor(cand, o, 64);
         if (lane == 0 && cand) atomicAdd(&s_cand, cand);
     }
-    __syncthreads();
+    screen_barrier();
     if (threadIdx.x == 0 && s_cand)
         atomicAdd(reinterpret_cast<uint32_t*>(base) + SU_CAND + (blockIdx.x & 7) * 32, (uint32_t)s_cand);
 }
@@ -566,9 +571,6 @@ __device__ inline float screen_cos(float xy, float xx, float yy) {
     const float ix = xx > 0.f ? 1.0f / sqrtf(xx) : 0.f, iy = yy > 0.f ? 1.0f / sqrtf(yy) : 0.f;
     return (fabsf(xy) * ix) * iy;                             // a zero row normalises to zero: all its cosines are 0
 }
-
-// All waves' LDS operations done, and everybody here.  (A fenced barrier would also wait for the stores to memory.)
-__device__ inline void screen_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // (k_screen_rest has to agree: a quarter of the pairs is more than SCREEN_OPEN per token.  The full selection needs the norms
 // in any case.  Nobody writes the counts while they are read here, so scalar loads will do; for short rows and sequences the

@@ -147,7 +147,7 @@ def test_rows_of_every_length(d, dtype):
     check(xs_cpu, 0.1, *(res[k].cpu() for k in ("idx", "counts", "gram_ops", "adds", "removes")), 0, "d=%d" % d)
 
 
-@pytest.mark.parametrize("T,d,G,L", [(701, 64, 24, 4), (2050, 128, 4, 8)])
+@pytest.mark.parametrize("T,d,G,L", [(701, 64, 24, 4), (2050, 128, 8, 8)])
 def test_pairs_counted_behind_the_exact_pass(T, d, G, L):
     """Short rows of many units: the pairs inside clusters are counted by the launch behind.  Each sequence alone, whose pairs the exact
     pass counts, gives the same; plain sequences, some with edges, dense ones."""
