@@ -47,7 +47,7 @@ enum { META_R = 0, META_NONREP = 1, META_STATUS = 2, META_GATE = 3 /* k_screen_s
        // screened selection: layers done so far; hand-over word, sign-off counter and claim words (one per XCD, in the lines of the
        // ticket counters) of k_cascade_rest, zero between calls
        META_PROGRESS = 8, META_REST_EPOCH = 10, META_REST_LEFT = 11,
-       META_ALONE = 12 /* and 13: layers of a launch whose assignment the graph leaves open, one bit each */, META_FIX = 14, META_WORDS = 15,
+       META_ALONE = 12 /* and 13: layers of a launch whose assignment the graph leaves open, one bit each */, META_FIX = 14, META_WALK = 15 /* k_screen_chain; zero between calls */, META_WORDS = 16,
        META_REST_CLAIM = META_TICKET + 64 + 8 /* and 32, 64 .. 224 further on */ };
 static_assert((META_REST_CLAIM + 7 * 32 + 1) * 4 <= META_BYTES, "claim words");
 
@@ -1418,7 +1418,7 @@ __global__ __launch_bounds__(256) void k_gamma_fix(GramParams p, GammaFix f) {
     const int Wa = (r + 31) >> 5;
     auto row = [&](int t) { return X + (size_t)t * (size_t)p.ld; };
     const int32_t* list = p.nonrep_idx + (p.T - far);
-    for (int i = META_WORDS + 1 + (int)(blockIdx.x * 256 + threadIdx.x); i < f.zero; i += f.grid * 256) f.meta[i] = 0;
+    for (int i = META_WORDS + (int)(blockIdx.x * 256 + threadIdx.x); i < f.zero; i += f.grid * 256) f.meta[i] = 0;
     if (f.zero && blockIdx.x == 0 && threadIdx.x < META_FIX && threadIdx.x >= META_TICKET) f.meta[threadIdx.x] = 0;
     const bool tiles = (long long)far * r > fix_pairs(p.d, sizeof(In));
     const int pieces = (r + 4 * FIX_REPS - 1) / (4 * FIX_REPS), near4 = (near + 3) / 4, items = near4 + (tiles ? 0 : far * pieces);
@@ -1680,13 +1680,17 @@ hipError_t launch_screen_exact_any(const ScreenParams& sp, int np, hipStream_t s
     return launch_screen_exact<In, LPR, 4, false>(sp, st);
 }
 
+// 128 x 128 tiles of a unit, and the workgroups (up to `side` tiles side by side) that go through them: a unit with nothing to do takes its
+// workgroups one read each, a busy one should have enough of them, on CUs of their own while there are some.
+int rest_tiles(int T) { const int nb = (T + 127) / 128; return nb * (nb + 1) / 2; }
+int rest_workgroups(int ntile, int units, int side) {
+    const int k = std::min(std::max(1024 / units, 8), ntile);
+    return std::max((k + side - 1) / side, std::min(k, device_cus() / units));
+}
+
 template <typename In, int LPR>
 hipError_t launch_screen_rest(const ScreenParams& sp, hipStream_t st) {
-    const int nb = (sp.T + 127) / 128, ntile = nb * (nb + 1) / 2, units = sp.G * sp.L;
-    // (a unit with nothing to do takes its workgroups one read each; a busy one should have enough of them)
-    int k = 1024 / units;
-    k = k < 8 ? 8 : k;
-    k = k > ntile ? ntile : k;
+    const int units = sp.G * sp.L, ntile = rest_tiles(sp.T), k = rest_workgroups(ntile, units, 1);
     ProfScope ps(ADA_K_SCREEN, st);
     hipLaunchKernelGGL((k_screen_rest<In, LPR>), dim3((unsigned)(k * units)), dim3(256), sp.count_pairs ? 0 : (sp.T + 3) / 4 * 8, st, sp, ntile);
     return hipGetLastError();
@@ -1703,9 +1707,13 @@ void launch_screen_pairs(const ScreenParams& sp, const PairItems& it, dim3 grid,
     hipLaunchKernelGGL((k_screen_pairs<NCH, TB>), grid, dim3(256), 0, st, sp, it, total);
 }
 
-// The graph of near pairs of every unit of sp.
+// Lanes per product of whole rows: four pieces of a row in flight per lane, at least eight lanes (a cache line) side by side.
+inline int screen_lanes(int np) { return np >= 256 ? 64 : np >= 128 ? 32 : np >= 64 ? 16 : 8; }
+
+// The graph of near pairs of every unit of sp; rest: the unexplained candidates too (else the launch behind sees to them, if the exact pass
+// counts the pairs).
 template <typename In>
-hipError_t launch_screen(ScreenParams& sp, hipStream_t st) {
+hipError_t launch_screen(ScreenParams& sp, bool rest, hipStream_t st) {
     const int units = sp.G * sp.L;
     // Who counts the pairs inside clusters.  The exact pass takes an atomic with a return per token for it, 20 thousand of them a microsecond
     // from the whole chip, which short rows do not hide; each workgroup of k_screen_rest a histogram of its unit in LDS, 1 us.  16 heads
@@ -1743,8 +1751,10 @@ hipError_t launch_screen(ScreenParams& sp, hipStream_t st) {
     hipError_t e = np >= 256 ? launch_screen_exact_any<In, 64>(sp, np, st) : np >= 128 ? launch_screen_exact_any<In, 32>(sp, np, st)
                  : np > 32 ? launch_screen_exact_any<In, 16>(sp, np, st) : launch_screen_exact_any<In, 8>(sp, np, st);
     if (e != hipSuccess) return e;
-    return np >= 256 ? launch_screen_rest<In, 64>(sp, st) : np >= 128 ? launch_screen_rest<In, 32>(sp, st)
-         : np >= 64 ? launch_screen_rest<In, 16>(sp, st) : launch_screen_rest<In, 8>(sp, st);
+    if (!rest && sp.count_pairs) return hipSuccess;
+    const int lanes = screen_lanes(np);
+    return lanes == 64 ? launch_screen_rest<In, 64>(sp, st) : lanes == 32 ? launch_screen_rest<In, 32>(sp, st)
+         : lanes == 16 ? launch_screen_rest<In, 16>(sp, st) : launch_screen_rest<In, 8>(sp, st);
 }
 
 // The full selection of one sequence (ada_screen_full.hpp).
@@ -1812,7 +1822,7 @@ int screen_full(const ScreenPlan& plan, const void* X, int T, int d, long long l
                                        screen_sort_lds(FUSED_MAX_T));
     });
     if (attr_err != hipSuccess) return ADA_ERR_DEVICE;
-    hipError_t e = dtype == ADA_BF16 ? launch_screen<uint16_t>(sp, st) : launch_screen<float>(sp, st);
+    hipError_t e = dtype == ADA_BF16 ? launch_screen<uint16_t>(sp, true, st) : launch_screen<float>(sp, true, st);
     if (e != hipSuccess) return ADA_ERR_DEVICE;
     {
         ProfScope ps(ADA_K_UPDATE, st);
@@ -1827,7 +1837,7 @@ int screen_full(const ScreenPlan& plan, const void* X, int T, int d, long long l
 }
 
 template <int THREADS, int U, int D>
-hipError_t launch_screen_chain(const ChainParams& c, hipStream_t st) {
+hipError_t launch_screen_chain(ChainParams& c, hipStream_t st) {
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
@@ -1836,7 +1846,9 @@ hipError_t launch_screen_chain(const ChainParams& c, hipStream_t st) {
     });
     if (attr_err != hipSuccess) return attr_err;
     ProfScope ps(ADA_K_UPDATE, st);
-    hipLaunchKernelGGL((k_screen_chain<THREADS, U, D>), dim3((unsigned)c.s.G), dim3(THREADS), (chain_lds<THREADS, U>(c.s.T)), st, c);
+    const int units = c.s.G * c.s.L;
+    c.rest = c.s.count_pairs ? rest_workgroups(c.ntile, units, THREADS / 256) : 0;
+    hipLaunchKernelGGL((k_screen_chain<THREADS, U, D>), dim3((unsigned)(c.s.G + c.rest * units)), dim3(THREADS), (chain_lds<THREADS, U>(c.s.T)), st, c);
     return hipGetLastError();
 }
 
@@ -1927,9 +1939,11 @@ int run_layers_screened(const ScreenPlan& plan, const void* const* X_layers, int
         sp.first = first;
         sp.L = end - first < per ? end - first : per;
         for (int i = 0; i < SCREEN_MAX_LAYERS; ++i) sp.X[i] = i < sp.L ? X_layers[first + i] : nullptr;
-        hipError_t e = dtype == ADA_BF16 ? launch_screen<uint16_t>(sp, st) : launch_screen<float>(sp, st);
+        hipError_t e = dtype == ADA_BF16 ? launch_screen<uint16_t>(sp, false, st) : launch_screen<float>(sp, false, st);
         if (e != hipSuccess) return ADA_ERR_DEVICE;
         // (wide workgroups from 1025 tokens on; us, 512 threads -> 1024, 16 layers of d=256: T=1000 6.5 -> 7.2, 1500 8.8 -> 8.3, 4000 13.7 -> 11.4)
+        c.ntile = rest_tiles(T);
+        c.lanes = screen_lanes((d * (dtype == ADA_BF16 ? 2 : 4) + 15) / 16);
         e = T <= 256 ? launch_screen_chain<256, 1, 8>(c, st) : T <= 512 ? launch_screen_chain<512, 1, 8>(c, st)
           : T <= 1024 ? launch_screen_chain<512, 2, 8>(c, st) : T <= 2048 ? launch_screen_chain<1024, 2, 8>(c, st)
           : T <= 4096 ? launch_screen_chain<1024, 4, 4>(c, st) : T <= 8192 ? launch_screen_chain<1024, 8, 2>(c, st)

@@ -20,9 +20,9 @@
 //   rest    candidate pairs that no cluster explains are multiplied out one by one and become EDGES (a pair
 //           and its cosine).  Whether there are
 //           any is a matter of counting: with every rho^2 >= f2 all pairs inside clusters are candidates, so if there are
-//           exactly as many candidates as pairs inside clusters there is nothing else, and the launch leaves at once.
+//           exactly as many candidates as pairs inside clusters there is nothing else.
 //   chain   one workgroup per sequence walks through the layers: Definition 2.2 at layer 0, Algorithm 1 afterwards, on the
-//           clusters and edges alone.
+//           clusters and edges alone.  One launch with `rest`, whose workgroups leave at once as a rule.
 // Nothing here is approximate: a pair is decided by its full product, by the metric or by the bound, with margins
 // (1e-4 on |cos| and more) far above the rounding of any of them.  Where the data do not cooperate -- so many pairs near the
 // threshold that listing them is no saving -- a layer is marked DENSE and the launch behind the chain runs it and the
@@ -468,35 +468,33 @@ __global__ __launch_bounds__(256, screen_pair_waves(NCH, TB)) void k_screen_pair
         atomicAdd(reinterpret_cast<uint32_t*>(base) + SU_CAND + (blockIdx.x & 7) * 32, (uint32_t)s_cand);
 }
 
-// Sketch products of a 128 x 128 tile: four waves in a 2 x 2 grid of 64 x 64.
+// Sketch products of a 128 x 128 tile: four waves in a 2 x 2 grid of 64 x 64, 32 NB tokens (blocks b0 ..) at a time.
 struct ScreenTile { int s0, t0; bool any; };                  // this wave's first rows; any: some s < t
-__device__ inline ScreenTile screen_tile(const char* z, int T, int nch, int sb, int tb, f32x16 (&acc)[2][2]) {
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+__device__ inline ScreenTile screen_tile(int T, int sb, int tb, int wave) {
     const int s0 = sb * 128 + (wave >> 1) * 64, t0 = tb * 128 + (wave & 1) * 64;
-    const ScreenTile me = {s0, t0, s0 <= t0 && t0 < T};
-    if (!me.any) return me;                                   // (above the diagonal, or past the end)
-    const u32x4* Z = reinterpret_cast<const u32x4*>(z) + lane;
+    return {s0, t0, s0 <= t0 && t0 < T};                      // (not any: above the diagonal, or past the end)
+}
+template <int NB>
+__device__ inline void screen_tile_products(const char* z, int T, int nch, const ScreenTile& me, int b0, f32x16 (&acc)[2][NB]) {
+    const u32x4* Z = reinterpret_cast<const u32x4*>(z) + (threadIdx.x & 63);
     const int last = (T - 1) >> 5;
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
     for (int j = 0; j < nch; ++j) {
-        i32x8 fa[2], fb[2];
+        i32x8 fa[2], fb[NB];
 #pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            fa[a] = screen_operand(Z + (size_t)(min((s0 >> 5) + a, last) * nch + j) * 128);
-            fb[a] = screen_operand(Z + (size_t)(min((t0 >> 5) + a, last) * nch + j) * 128);
-        }
+        for (int a = 0; a < 2; ++a) fa[a] = screen_operand(Z + (size_t)(min((me.s0 >> 5) + a, last) * nch + j) * 128);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) fb[b] = screen_operand(Z + (size_t)(min((me.t0 >> 5) + b0 + b, last) * nch + j) * 128);
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
-            for (int b = 0; b < 2; ++b) screen_mma(acc[a][b], fa[a], fb[b]);
+            for (int b = 0; b < NB; ++b) screen_mma(acc[a][b], fa[a], fb[b]);
     }
-    return me;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -572,7 +570,7 @@ __device__ inline float screen_cos(float xy, float xx, float yy) {
     return (fabsf(xy) * ix) * iy;                             // a zero row normalises to zero: all its cosines are 0
 }
 
-// (k_screen_rest has to agree: a quarter of the pairs is more than SCREEN_OPEN per token.  The full selection needs the norms
+// (screen_state has to agree: a quarter of the pairs is more than SCREEN_OPEN per token.  The full selection needs the norms
 // in any case.  Nobody writes the counts while they are read here, so scalar loads will do; for short rows and sequences the
 // wait for them is not worth the pass they may save: 0.5 of 8 us at 12 x 512 x 768 in fp32, 1 of 34 us at 128 x 2048 x 256.)
 __device__ inline bool screen_crowded(const ScreenParams& p, const char* unit) {
@@ -592,7 +590,7 @@ __device__ inline bool screen_crowded(const ScreenParams& p, const char* unit) {
 // stores.  Instructions bind short rows and cost long ones waves in flight: 28 x T=2048, d=4096 86.8 -> 83.7 us, 32 x T=8192 389 -> 380,
 // 16 heads x 256, 8 layers 34.3 -> 28.0 (before: pieces clamped, cut and left out one by one, every row's divisions, fenced barriers).
 // X alone would take 67 us of the first (7.0 TB/s), X and the pivots in any order 77.
-// A unit whose candidates are a quarter of all pairs and more is left alone, for k_screen_rest to call dense: its rows share
+// A unit whose candidates are a quarter of all pairs and more is left alone, for screen_state to call dense: its rows share
 // a direction (or a few columns), which the sketch cannot tell from being near.
 // Two rows per lane group: the rows in flight on an XCD (256 workgroups of 8 at d = 4096) then stay about within one unit, whose
 // pivots its L2 can hold; four rows spread over two units (STREAM, 28 x T=2048, d=4096: call 150 us against 143; 32 x T=8192:
@@ -691,21 +689,138 @@ __device__ inline uint32_t screen_pairs_inside(const uint16_t* cl, int T) {
     return s_sum;
 }
 
-// k_screen_rest: the candidates that no cluster explains.  Units without any (the counts agree) are left at once, and so are
-// units with so many that the tiles behind are the better way (p.open).  LPR lanes per product, as
-// in k_screen_exact.  A tile's edges are counted in LDS and take their places in the unit's list with one atomic: one per
-// edge, all to one address at 25 ns each, was most of this launch (T=2048, d=768 in fp32, clusters of five as wide as the
-// threshold: 187 us).
+// What a unit's counts say: every candidate is explained by a cluster (PLAIN); so many are not that the tiles behind are the better
+// way (DENSE: p.open); or they are to be multiplied out (OPEN).
+enum { UNIT_PLAIN, UNIT_OPEN, UNIT_DENSE };
+__device__ inline int screen_state(const ScreenParams& p, const ScreenCounts& n) {
+    return n.flags == 0u && n.cand == n.pairs ? UNIT_PLAIN : n.cand > n.pairs + p.open ? UNIT_DENSE : UNIT_OPEN;
+}
+
+// The candidates of an open unit that no cluster explains, by workgroup `slot` of `slots` (all threads; lanes: per product, a power of two).
+// 256 threads go through a 128 x 128 tile, several tiles side by side in larger workgroups.  A tile's edges are counted in LDS and take
+// their places in the unit's list with one atomic: one per edge, all to one address at 25 ns each, was most of this (T=2048, d=768 in
+// fp32, clusters of five as wide as the threshold: 187 us).  Edges and counts go past the caches: the walk may be in the same launch.
+struct RestTile {
+    int n, edges, at, stop;
+    uint32_t pair[SCREEN_TILE_PAIRS];
+    uint2 edge[SCREEN_TILE_PAIRS];
+    float rho[256];
+    uint16_t cl[256];
+};
+template <int THREADS>
+__device__ inline void screen_rest_tiles(const ScreenParams& p, const ScreenUnit& U, char* base, int layer, int group, bool low, int slot,
+                                         int slots, int ntile, int lanes, bool f32, char* lds) {
+    constexpr int SUB = THREADS / 256;
+    const int tid = (int)threadIdx.x & 255, sub = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8), lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    RestTile* tiles = reinterpret_cast<RestTile*>(lds);
+    RestTile& my = tiles[sub];
+    uint32_t* hdr = reinterpret_cast<uint32_t*>(base);
+    const float* rho = reinterpret_cast<const float*>(base + U.o_rho);
+    const uint16_t* cl = reinterpret_cast<const uint16_t*>(base + U.o_cl);
+    unsigned long long* edge = reinterpret_cast<unsigned long long*>(base + U.o_edge);
+    const int side = slots < ntile ? SUB : 1;                 // (with a workgroup per tile the other threads have none)
+    for (int tile0 = slot * side; tile0 < ntile; tile0 += slots * side) {
+        const int tile = tile0 + sub;
+        const bool exists = sub < side && tile < ntile;       // (uniform per tile; the barriers are everybody's)
+        int sb, tb;
+        screen_blocks(min(tile, ntile - 1), &sb, &tb);
+        __syncthreads();
+        if (tid == 0) {
+            my.n = my.edges = 0;
+            if (sub == 0) tiles[0].stop = __hip_atomic_load(hdr + SU_DENSE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
+        }
+        {
+            const int tok = min(tid < 128 ? sb * 128 + tid : tb * 128 + tid - 128, p.T - 1);
+            my.rho[tid] = fminf(rho[tok], 1.f);
+            my.cl[tid] = cl[tok];
+        }
+        __syncthreads();
+        if (tiles[0].stop) break;                             // given up already (uniform)
+        const ScreenTile me = screen_tile(p.T, sb, tb, __builtin_amdgcn_readfirstlane(tid >> 6));
+        if (me.any && exists) {
+            constexpr int NB = THREADS <= 512 ? 2 : 1;        // (a thread of 1024 has 128 registers)
+#pragma unroll 1
+            for (int b0 = 0; b0 < 2; b0 += NB) {
+                f32x16 acc[2][NB];
+                screen_tile_products<NB>(base + U.o_z, p.T, p.nch, me, b0, acc);
+#pragma unroll
+                for (int bb = 0; bb < NB; ++bb) {
+                    const int b = b0 + bb;
+                    const int tl = me.t0 - tb * 128 + b * 32 + l32, t = tb * 128 + tl;
+                    const int ct = my.cl[128 + tl];
+                    auto row = [&](int i) { return me.s0 - sb * 128 + (i >> 4) * 32 + 4 * half + screen_row(i); };
+                    uint64_t near = 0u;                           // bit 62 - 2 i: register i of the two blocks' 32
+                    if (!low) {
+                        near = (uint64_t)(screen_bits(acc[0][bb]) & SCREEN_BITS) << 32 | (screen_bits(acc[1][bb]) & SCREEN_BITS);
+                    } else {                                      // some row holds little in its sketch: the pair's own bound
+                        const float rt = my.rho[128 + tl];
+#pragma unroll
+                        for (int i = 0; i < 32; ++i) {
+                            const float rs = my.rho[row(i)];
+                            if (fabsf(acc[i >> 4][bb][i & 15]) >= 2.f ||
+                                p.kap1 * sqrtf(rs * rt) + sqrtf((1.f - rs) * (1.f - rt)) + 1e-5f >= p.safe) near |= 1ull << (62 - 2 * i);
+                        }
+                    }
+                    while (__builtin_amdgcn_ballot_w64(near != 0u) != 0ull)
+                        if (near != 0u) {
+                            const int i = __clzll((long long)near) >> 1, sl = row(i), s = sb * 128 + sl;
+                            near &= ~(1ull << (62 - 2 * i));
+                            if (s < t && t < p.T && my.cl[sl] != ct) {
+                                const int n = atomicAdd(&my.n, 1);
+                                if (n < SCREEN_TILE_PAIRS) my.pair[n] = (uint32_t)s << 16 | (uint32_t)t;
+                            }
+                        }
+                }
+            }
+        }
+        __syncthreads();
+        int n = my.n;
+        if (n > SCREEN_TILE_PAIRS) {                          // no saving in listing these
+            if (tid == 0) __hip_atomic_store(hdr + SU_DENSE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            n = 0;
+        }
+        auto products = [&](auto lpr, auto in) {
+            constexpr int LPR = decltype(lpr)::value;
+            using In = decltype(in);
+            const In* X = screen_x<In>(p, layer, group);
+            const int li = tid & (LPR - 1);
+            for (int k = tid / LPR; k < n; k += 256 / LPR) {
+                const uint32_t e = my.pair[k];
+                const int s = (int)(e >> 16), t = (int)(e & 0xFFFFu);
+                float xy, xx, yy;
+                screen_products<In, LPR>(X + (size_t)t * (size_t)p.ld, X + (size_t)s * (size_t)p.ld, p.d, li, &xy, &xx, &yy);
+                const float c = screen_cos(xy, xx, yy);
+                if (p.gamma && li == 0 && c > 0.f) atomicMax(reinterpret_cast<uint32_t*>(p.gamma) + t, __float_as_uint(c));
+                if (li == 0 && c >= p.thr) my.edge[atomicAdd(&my.edges, 1)] = uint2{e, __float_as_uint(c)};
+            }
+        };
+        auto pick = [&](auto in) {
+            if (lanes == 64) products(std::integral_constant<int, 64>{}, in);
+            else if (lanes == 32) products(std::integral_constant<int, 32>{}, in);
+            else if (lanes == 16) products(std::integral_constant<int, 16>{}, in);
+            else products(std::integral_constant<int, 8>{}, in);
+        };
+        if (f32) pick(float{});
+        else pick(uint16_t{});
+        __syncthreads();
+        const int ne = my.edges;
+        if (tid == 0 && ne > 0) my.at = (int)atomicAdd(hdr + SU_EDGES, (uint32_t)ne);
+        __syncthreads();
+        const int at = my.at;
+        for (int k = tid; k < ne; k += 256)
+            if (at + k < U.edge_cap)
+                __hip_atomic_store(edge + at + k, (unsigned long long)my.edge[k].y << 32 | my.edge[k].x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0 && ne > 0 && at + ne > U.edge_cap) __hip_atomic_store(hdr + SU_DENSE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// k_screen_rest: the unexplained candidates of all units as a launch of its own, in front of k_screen_sort and where the pairs inside
+// clusters are counted here.  Units without any are left at once.
 template <typename In, int LPR>
 __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) {
-    __shared__ int s_n, s_edges, s_at;
-    __shared__ uint32_t s_pair[SCREEN_TILE_PAIRS];
-    __shared__ uint2 s_edge[SCREEN_TILE_PAIRS];
-    __shared__ float s_rho[256];
-    __shared__ uint16_t s_cl[256];
+    __shared__ RestTile tile;
     const ScreenUnit U(p.T, p.nch, p.edge_cap);
     const int units = p.G * p.L, unit = (int)blockIdx.x % units;
-    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     int layer, group;
     char* base = screen_unit(p, U, unit, &layer, &group);
     uint32_t* hdr = reinterpret_cast<uint32_t*>(base);
@@ -714,86 +829,12 @@ __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) 
         n_unit.pairs = screen_pairs_inside(reinterpret_cast<const uint16_t*>(base + U.o_cl), p.T);
         if ((int)blockIdx.x < units && threadIdx.x == 0) hdr[SU_PART + SU_PAIRS] = n_unit.pairs;   // (where the exact pass leaves its counts)
     }
-    if (n_unit.flags == 0u && n_unit.cand == n_unit.pairs) return;
-    if (n_unit.cand > n_unit.pairs + p.open) {
-        if ((int)blockIdx.x < units && tid == 0) __hip_atomic_store(hdr + SU_DENSE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return;
-    }
-    const bool low = (n_unit.flags & SF_LOW) != 0u;
-    const In* X = screen_x<In>(p, layer, group);
-    const float* rho = reinterpret_cast<const float*>(base + U.o_rho);
-    const uint16_t* cl = reinterpret_cast<const uint16_t*>(base + U.o_cl);
-    uint2* edge = reinterpret_cast<uint2*>(base + U.o_edge);
-    for (int tile = (int)blockIdx.x / units; tile < ntile; tile += (int)gridDim.x / units) {
-        int sb, tb;
-        screen_blocks(tile, &sb, &tb);
-        __syncthreads();
-        if (tid == 0) { s_n = __hip_atomic_load(hdr + SU_DENSE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? -1 : 0; s_edges = 0; }
-        {
-            const int tok = min(tid < 128 ? sb * 128 + tid : tb * 128 + tid - 128, p.T - 1);
-            s_rho[tid] = fminf(rho[tok], 1.f);
-            s_cl[tid] = cl[tok];
-        }
-        __syncthreads();
-        if (s_n < 0) break;                               // given up already (uniform)
-        f32x16 acc[2][2];
-        const ScreenTile me = screen_tile(base + U.o_z, p.T, p.nch, sb, tb, acc);
-        if (me.any) {
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const int tl = me.t0 - tb * 128 + b * 32 + l32, t = tb * 128 + tl;
-                const int ct = s_cl[128 + tl];
-                auto row = [&](int i) { return me.s0 - sb * 128 + (i >> 4) * 32 + 4 * half + screen_row(i); };
-                uint64_t near = 0u;                       // bit 62 - 2 i: register i of the two blocks' 32
-                if (!low) {
-                    near = (uint64_t)(screen_bits(acc[0][b]) & SCREEN_BITS) << 32 | (screen_bits(acc[1][b]) & SCREEN_BITS);
-                } else {                                  // some row holds little in its sketch: the pair's own bound
-                    const float rt = s_rho[128 + tl];
-#pragma unroll
-                    for (int i = 0; i < 32; ++i) {
-                        const float rs = s_rho[row(i)];
-                        if (fabsf(acc[i >> 4][b][i & 15]) >= 2.f ||
-                            p.kap1 * sqrtf(rs * rt) + sqrtf((1.f - rs) * (1.f - rt)) + 1e-5f >= p.safe) near |= 1ull << (62 - 2 * i);
-                    }
-                }
-                while (__builtin_amdgcn_ballot_w64(near != 0u) != 0ull)
-                    if (near != 0u) {
-                        const int i = __clzll((long long)near) >> 1, sl = row(i), s = sb * 128 + sl;
-                        near &= ~(1ull << (62 - 2 * i));
-                        if (s < t && t < p.T && s_cl[sl] != ct) {
-                            const int n = atomicAdd(&s_n, 1);
-                            if (n < SCREEN_TILE_PAIRS) s_pair[n] = (uint32_t)s << 16 | (uint32_t)t;
-                        }
-                    }
-            }
-        }
-        __syncthreads();
-        const int n = s_n;
-        if (n > SCREEN_TILE_PAIRS) {                      // no saving in listing these (uniform)
-            if (tid == 0) __hip_atomic_store(hdr + SU_DENSE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            break;
-        }
-        if (n == 0) continue;                             // (uniform)
-        const int li = tid & (LPR - 1);
-        for (int k = tid / LPR; k < n; k += 256 / LPR) {
-            const uint32_t e = s_pair[k];
-            const int s = (int)(e >> 16), t = (int)(e & 0xFFFFu);
-            float xy, xx, yy;
-            screen_products<In, LPR>(X + (size_t)t * (size_t)p.ld, X + (size_t)s * (size_t)p.ld, p.d, li, &xy, &xx, &yy);
-            const float c = screen_cos(xy, xx, yy);
-            if (p.gamma && li == 0 && c > 0.f) atomicMax(reinterpret_cast<uint32_t*>(p.gamma) + t, __float_as_uint(c));
-            if (li == 0 && c >= p.thr) s_edge[atomicAdd(&s_edges, 1)] = uint2{e, __float_as_uint(c)};
-        }
-        __syncthreads();
-        const int ne = s_edges;
-        if (ne == 0) continue;                            // (uniform)
-        if (tid == 0) s_at = (int)atomicAdd(hdr + SU_EDGES, (uint32_t)ne);
-        __syncthreads();
-        const int at = s_at;
-        for (int k = tid; k < ne; k += 256)
-            if (at + k < U.edge_cap) edge[at + k] = s_edge[k];
-        if (tid == 0 && at + ne > U.edge_cap) __hip_atomic_store(hdr + SU_DENSE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    const int state = screen_state(p, n_unit);
+    if (state == UNIT_DENSE && (int)blockIdx.x < units && threadIdx.x == 0)
+        __hip_atomic_store(hdr + SU_DENSE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (state == UNIT_OPEN)
+        screen_rest_tiles<256>(p, U, base, layer, group, (n_unit.flags & SF_LOW) != 0u, (int)blockIdx.x / units, (int)gridDim.x / units, ntile, LPR,
+                               sizeof(In) == 4, reinterpret_cast<char*>(&tile));
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -824,6 +865,7 @@ struct ChainParams {
     int32_t* pos;
     int32_t* info;
     int f32;                   // rows are fp32 (else bf16)
+    int rest, ntile, lanes;    // workgroups per unit for the unexplained candidates (0: a launch of their own was), see screen_rest_tiles
 };
 
 constexpr int LIST_SCRATCH = 3 * 257 * 4;                     // LDS that writing a layer's lists takes
@@ -834,8 +876,8 @@ static_assert(assign_lds(FUSED_MAX_T) <= CHAIN_LDS && FUSED_MAX_T / 64 + 1 <= 25
 // LDS of the walk: two sets of cluster slots, marks (edges only).
 template <int THREADS, int U>
 __host__ __device__ constexpr int chain_lds(int T) {
-    constexpr int tokens = THREADS * U, walk = (tokens + 64) * 8 + tokens;
-    return walk > assign_lds(T) ? walk : assign_lds(T);
+    constexpr int tokens = THREADS * U, walk = (tokens + 64) * 8 + tokens, rest = THREADS / 256 * (int)sizeof(RestTile), most = walk > rest ? walk : rest;
+    return most > assign_lds(T) ? most : assign_lds(T);
 }
 static_assert(chain_lds<1024, 16>(FUSED_MAX_T) <= CHAIN_LDS, "LDS of the walk");
 
@@ -1113,6 +1155,10 @@ __device__ inline void screen_assign(const ChainParams& c, const ScreenUnit& SU,
     __syncthreads();
 }
 
+__device__ inline unsigned long long uniform64(unsigned long long v) {
+    return (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+}
+
 template <int THREADS, int U, int D>
 __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
     extern __shared__ __align__(16) char lds[];
@@ -1121,7 +1167,27 @@ __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
     unsigned long long alone = 0ull;                          // layers whose assignment is left to the tiles (uniform)
     const ScreenParams& p = c.s;
     const ScreenUnit SU(p.T, p.nch, p.edge_cap);
-    const int tid = threadIdx.x, T = p.T, g = blockIdx.x, lane = tid & 63, words = (T + 63) >> 6;
+    const int tid = threadIdx.x, T = p.T, lane = tid & 63, words = (T + 63) >> 6;
+    int g = blockIdx.x;
+    // Workgroups from G on see to the unexplained candidates of a unit each.  Where there are any, the last one of a sequence to be done
+    // walks (its walker counts as one of them): nobody waits for anybody.  (As a launch of its own in front of the walk they took 2.4 to
+    // 4.8 us, and 3 us of the host, to find nothing: calls of 12 x T=512, d=768 in fp32 28.8 -> 25.6 us, 12 x T=2048, d=768 39.9 -> 37.6, 28 x
+    // T=2048, d=4096 128.4 -> 126.7.  Loose clusters, one token in ten and all of them: 12 x T=512 62.9 -> 64.8 and 106 -> 111, 12 x T=2048
+    // 97.5 -> 95.8 and 149 -> 132, 28 x T=2048, d=4096 288 -> 276 and 645 -> 553, 4 x T=8192 304 -> 251 and 447 -> 376.)
+    if (g >= p.G) {
+        const int units = p.G * p.L, b = g - p.G;
+        int layer;
+        char* base = screen_unit(p, SU, b % units, &layer, &g);
+        __shared__ int s_unit;
+        if (tid < 64) {
+            const ScreenCounts n = screen_counts(reinterpret_cast<const uint32_t*>(base));
+            s_unit = screen_state(p, n) | ((n.flags & SF_LOW) ? 16 : 0);
+        }
+        screen_barrier();
+        const int state = __builtin_amdgcn_readfirstlane(s_unit);
+        if ((state & 15) != UNIT_OPEN) return;
+        screen_rest_tiles<THREADS>(p, SU, base, layer, g, (state & 16) != 0, b / units, c.rest, c.ntile, c.lanes, c.f32 != 0, lds);
+    }
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     uint32_t* slots = reinterpret_cast<uint32_t*>(lds);       // [2][SET] stamp << 14 | earliest inherited member; the last 64 take what is none
     uint8_t* mark = reinterpret_cast<uint8_t*>(lds + SET * 8);    // bits: 1 inherited, 2 hit by an earlier inherited token, 4 valid, 8 covered
@@ -1143,9 +1209,40 @@ __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
     int loaded = skip;                                        // the layer that ahead[0] belongs to
 
     const int progress = meta[META_PROGRESS];
-    const uint32_t* hdr = reinterpret_cast<const uint32_t*>(area + (long long)min(lane, p.L - 1) * SU.bytes);
-    const uint32_t edges_of = hdr[SU_EDGES];                  // of the layer with this lane's number
-    const unsigned long long dense = __ballot(lane < p.L && hdr[SU_DENSE] != 0u);
+    const uint32_t* hdr = reinterpret_cast<const uint32_t*>(area + (long long)min(lane, p.L - 1) * SU.bytes);   // of the layer with this lane's number
+    unsigned long long open = 0ull, closed = 0ull;            // layers with unexplained candidates; with too many of them
+    if (c.rest) {                                             // (one wave looks: sixteen took 3 us longer over 28 layers' lines)
+        __shared__ unsigned long long s_state[2];
+        if (wave == 0) {
+            const int state = screen_state(p, screen_counts(hdr));
+            open = __ballot(lane < p.L && state == UNIT_OPEN);
+            closed = __ballot(lane < p.L && state == UNIT_DENSE);
+            if (lane == 0) { s_state[0] = open; s_state[1] = closed; }
+        }
+        screen_barrier();
+        open = uniform64(s_state[0]);
+        closed = uniform64(s_state[1]);
+    }
+    if (open) {
+        __shared__ int s_last;
+        drain_stores();
+        __syncthreads();
+        if (tid == 0) s_last = atomicAdd(meta + META_WALK, 1) == __popcll(open) * c.rest;
+        __syncthreads();
+        if (!s_last) return;                                  // uniform
+        if (tid == 0) {
+            __hip_atomic_store(meta + META_WALK, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        }
+        __syncthreads();
+    }
+    uint32_t edges_of = 0u;
+    bool is_dense = (closed >> lane) & 1ull;
+    if (open || !c.rest) {                                    // (plain units have neither)
+        edges_of = __hip_atomic_load(hdr + SU_EDGES, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        is_dense |= __hip_atomic_load(hdr + SU_DENSE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
+    }
+    const unsigned long long dense = __ballot(lane < p.L && is_dense);
     const unsigned long long edged = __ballot(lane < p.L && edges_of != 0u);
     for (int t = tid; t < 2 * SET; t += THREADS) slots[t] = 0xFFFFFFFFu;
     for (int t = tid; t < TOKENS; t += THREADS) mark[t] = 0;

@@ -165,6 +165,30 @@ def test_pairs_counted_behind_the_exact_pass(T, d, G, L):
                 assert torch.equal(res[k][g, l, :n], one[k][l, :n]), (g, l, k)
 
 
+@pytest.mark.parametrize("T,d,L,dtype", [(200, 128, 5, "f32"), (500, 256, 6, "bf16"), (900, 768, 4, "bf16"), (1700, 512, 3, "bf16"), (4100, 520, 2, "bf16")])
+def test_unexplained_candidates_in_front_of_the_walk(T, d, L, dtype):
+    """Whoever is done last with a sequence's unexplained candidates walks (or sorts): every number of threads; sequences with and
+    without such candidates beside each other; the same again and again, and every counter left as it was found."""
+    print("[case] candidates in front of the walk: T=%d d=%d L=%d %s" % (T, d, L, dtype), flush=True)
+    kinds = ("loose", "clusters", "strays", "loose")
+    per = [activations(k, T, d, L, dtype, seed=5 + i) for i, k in enumerate(kinds)]
+    xg = [torch.stack([p[l] for p in per]).to(DEV) for l in range(L)]
+    ws = pa.workspace_batched(T, len(kinds), DEV)
+    first = None
+    for _ in range(25):
+        res = pa.ada_cascade_layers_grouped(xg, 0.1, ws=ws, want_lists=True)
+        got = [res["counts"].clone(), res["gram_ops"].clone()] + [torch.cat([res["idx"][g, l, :int(res["counts"][g, l, 0])] for g in range(len(kinds)) for l in range(L)])]
+        first = got if first is None else first
+        assert all(torch.equal(a, b) for a, b in zip(first, got))
+    for g, kind in enumerate(kinds):
+        check(per[g], 0.1, *(res[k][g].cpu() for k in ("idx", "counts", "gram_ops", "adds", "removes")), 0, "group %d %s" % (g, kind))
+    one = pa.workspace_bytes(T)
+    if T >= 1500:
+        x = xg[0][0].contiguous()
+        full = [pa.ada_select_full(x, 0.1, ws=ws.view(len(kinds), one)[0], flags=pa.FLAG_GREEDY_COVER) for _ in range(5)]
+        assert all(torch.equal(full[0][k], f[k]) for f in full for k in ("mask", "counts", "gamma"))
+
+
 @pytest.mark.parametrize("kinds,T,d,dtype", [(("clusters", "clusters", "clusters"), 200, 96, "bf16"), (("clusters", "common", "loose"), 260, 320, "bf16"),
                                              (("common", "common", "clusters", "common", "loose"), 600, 256, "bf16"),
                                              (("outliers", "signs"), 131, 1001, "f32")])
