@@ -1749,7 +1749,7 @@ hipError_t launch_screen(ScreenParams& sp, bool rest, hipStream_t st) {
     // four pieces of a row in flight per lane, at least eight lanes (a cache line) side by side
     const int np = (sp.d * (int)sizeof(In) + 15) / 16;
     hipError_t e = np >= 256 ? launch_screen_exact_any<In, 64>(sp, np, st) : np >= 128 ? launch_screen_exact_any<In, 32>(sp, np, st)
-                 : np > 32 ? launch_screen_exact_any<In, 16>(sp, np, st) : launch_screen_exact_any<In, 8>(sp, np, st);
+                 : np >= 64 ? launch_screen_exact_any<In, 16>(sp, np, st) : launch_screen_exact_any<In, 8>(sp, np, st);
     if (e != hipSuccess) return e;
     if (!rest && sp.count_pairs) return hipSuccess;
     const int lanes = screen_lanes(np);

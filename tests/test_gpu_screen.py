@@ -499,7 +499,7 @@ def exact_pass(T, d, L, groups, esz, tau):
     batches = -(-L // fit)
     units = groups * -(-L // batches)
     pieces = (d * esz + 15) // 16
-    lanes = 64 if pieces >= 256 else 32 if pieces >= 128 else 16 if pieces >= 64 else 8
+    lanes = 64 if pieces >= 256 else 32 if pieces >= 128 else 16 if pieces >= 64 or pieces == 32 else 8
     rows = 2 if T // (4 * (256 // lanes)) * units >= 2048 else 1
     return lanes, rows, d * esz % 128 == 0 and units * T * d * esz >= 192 << 20
 
