@@ -868,10 +868,11 @@ struct ChainParams {
     int rest, ntile, lanes;    // workgroups per unit for the unexplained candidates (0: a launch of their own was), see screen_rest_tiles
 };
 
-constexpr int LIST_SCRATCH = 3 * 257 * 4;                     // LDS that writing a layer's lists takes
+constexpr int LIST_WORDS = FUSED_MAX_T / 64;
+constexpr int LIST_SCRATCH = LIST_WORDS * (3 * 4 + 2 * 8);    // LDS that writing a layer's lists takes: places per word, the set's words and the ones before
 // ... and its assignment (screen_assign): two words per token besides
 constexpr int assign_lds(int T) { return LIST_SCRATCH + (T + 63) / 64 * 64 * 8; }
-static_assert(assign_lds(FUSED_MAX_T) <= CHAIN_LDS && FUSED_MAX_T / 64 + 1 <= 257, "LDS of a layer's lists and assignment");
+static_assert(assign_lds(FUSED_MAX_T) <= CHAIN_LDS, "LDS of a layer's lists and assignment");
 
 // LDS of the walk: two sets of cluster slots, marks (edges only).
 template <int THREADS, int U>
@@ -893,26 +894,38 @@ template <int U> __device__ inline int chain_token(int u) {
 }
 
 // One layer's lists, counts and Gram operations from the bits of its set and of the one before (any workgroup size up to
-// 1024; scratch: LIST_SCRATCH bytes of LDS).
-__device__ inline void screen_lists(const ChainParams& c, const ScreenUnit& SU, int l, int g, int* scratch) {
+// 1024; scratch: LIST_SCRATCH bytes of LDS); part of parts: its share of the tokens.  One wave reads the bits and sums over the words before; they stay in LDS for the
+// others (Read from memory by each
+// of them again, behind the stores of the tokens before, and a layer by one workgroup: 28 layers of T=2048 7.0 us, now 5.5, 8 layers of four sequences
+// of T=8192 11.4, now 7.1.)
+struct ListScratch {
+    unsigned long long *now, *was;                            // [words] the set, and the one inherited
+    int* start;                                               // [3][LIST_WORDS] members in the words before: the set, added, removed
+    __device__ explicit ListScratch(int* scratch) {
+        now = reinterpret_cast<unsigned long long*>(scratch);
+        was = now + LIST_WORDS;
+        start = reinterpret_cast<int*>(was + LIST_WORDS);
+    }
+};
+__device__ inline int list_rank(unsigned long long m) {       // members before this lane
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+}
+__device__ inline void screen_lists(const ChainParams& c, const ScreenUnit& SU, int l, int g, int* scratch, int part = 0, int parts = 1) {
     const ScreenParams& p = c.s;
     const int T = p.T, words = (T + 63) >> 6, tid = threadIdx.x, lane = tid & 63;
-    const char* unit = p.area + (long long)g * p.area_gs + (long long)l * SU.bytes;
-    const unsigned long long* now = reinterpret_cast<const unsigned long long*>(unit + SU.o_mask);
-    const unsigned long long* was = l > 0 ? reinterpret_cast<const unsigned long long*>(unit - SU.bytes + SU.o_mask) : now + words;
+    const ListScratch s(scratch);
     const bool full = p.first + l == 0;
     const size_t row = (size_t)(p.first + l);
-    int32_t* idx = c.idx + (long long)g * c.list_gs + row * T;
-    int32_t* adds = c.adds && !full ? c.adds + (long long)g * c.list_gs + row * T : nullptr;
-    int32_t* removes = c.removes && !full ? c.removes + (long long)g * c.list_gs + row * T : nullptr;
-    int* start = scratch;                                     // [3][words + 1]: members in the words before
     if (tid < 64) {                                           // one wave: prefix sums over the words
-        int tot[3] = {0, 0, 0}, r_was = 0;
+        const char* unit = p.area + (long long)g * p.area_gs + (long long)l * SU.bytes;
+        const unsigned long long* now = reinterpret_cast<const unsigned long long*>(unit + SU.o_mask);
+        const unsigned long long* was = l > 0 ? reinterpret_cast<const unsigned long long*>(unit - SU.bytes + SU.o_mask) : now + words;
+        int tot[3] = {0, 0, 0};
         for (int w0 = 0; w0 < words; w0 += 64) {
             const int w = w0 + lane;
             const unsigned long long a = w < words ? now[w] : 0ull, b = w < words && !full ? was[w] : 0ull;
             const unsigned long long m[3] = {a, a & ~b, b & ~a};
-            int rw = __popcll(b);
+            if (w < words) { s.now[w] = a; s.was[w] = b; }
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
                 const int pc = __popcll(m[k]);
@@ -922,33 +935,32 @@ __device__ inline void screen_lists(const ChainParams& c, const ScreenUnit& SU, 
                     const int x = __shfl_up(inc, o, 64);
                     if (lane >= o) inc += x;
                 }
-                if (w < words) start[k * 257 + w] = tot[k] + inc - pc;
+                if (w < words) s.start[k * LIST_WORDS + w] = tot[k] + inc - pc;
                 tot[k] += __builtin_amdgcn_readlane(inc, 63);
             }
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) rw += __shfl_xor(rw, o, 64);
-            r_was += rw;
         }
-        if (lane == 0) {
-            const unsigned long long TT = (unsigned long long)T, rr = (unsigned long long)r_was;
+        if (lane == 0 && part == 0) {
+            const unsigned long long TT = (unsigned long long)T, rr = (unsigned long long)(tot[0] - tot[1] + tot[2]);   // (kept ones and the removed)
             *reinterpret_cast<int4*>(c.counts + (long long)g * c.counts_gs + row * 4) =
                 full ? int4{tot[0], tot[0], 0, ADA_OK} : int4{tot[0], tot[1], tot[2], ADA_OK};
             c.ops[(long long)g * c.ops_gs + row] = full ? TT * TT : rr * rr + (TT - rr) * (rr - (unsigned long long)tot[2]);   // Table 6 / eq. (6)
         }
     }
-    __syncthreads();
-    for (int t = tid; t < words * 64; t += blockDim.x) {
+    screen_barrier();
+    int32_t* idx = c.idx + (long long)g * c.list_gs + row * T;
+    int32_t* adds = c.adds && !full ? c.adds + (long long)g * c.list_gs + row * T : nullptr;
+    int32_t* removes = c.removes && !full ? c.removes + (long long)g * c.list_gs + row * T : nullptr;
+    for (int t = part * (int)blockDim.x + tid; t < words * 64; t += parts * (int)blockDim.x) {
         const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-        const unsigned long long a = now[w], b = full ? 0ull : was[w];
+        const unsigned long long a = s.now[w], b = s.was[w];
         auto put = [&](int32_t* dst, int k, unsigned long long m) {
-            if (dst && ((m >> lane) & 1ull))
-                dst[start[k * 257 + w] + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = t;
+            if (dst && ((m >> lane) & 1ull)) dst[s.start[k * LIST_WORDS + w] + list_rank(m)] = t;
         };
         put(idx, 0, a);
         put(adds, 1, a & ~b);
         put(removes, 2, b & ~a);
     }
-    __syncthreads();
+    screen_barrier();
 }
 
 // f(both ends) for every edge.
@@ -1057,7 +1069,7 @@ __device__ inline void chain_edges(bool full, int earlier_only, uint32_t n_edge,
 // and nothing has to be multiplied.  Layers with a token that has none (chain_alone; only layers with edges can) do not come
 // here: their assignment takes the products with the whole set, on the tiles of k_cascade_rest.  (any workgroup size up to
 // 1024; scratch: assign_lds(T) bytes of LDS)
-__device__ inline void screen_assign(const ChainParams& c, const ScreenUnit& SU, int l, int g, int* scratch) {
+__device__ inline void screen_assign(const ChainParams& c, const ScreenUnit& SU, int l, int g, int* scratch, int part = 0, int parts = 1) {
     const ScreenParams& p = c.s;
     const int T = p.T, words = (T + 63) >> 6, tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;
     char* unit = p.area + (long long)g * p.area_gs + (long long)l * SU.bytes;
@@ -1065,33 +1077,35 @@ __device__ inline void screen_assign(const ChainParams& c, const ScreenUnit& SU,
     const uint16_t* cl = reinterpret_cast<const uint16_t*>(unit + SU.o_cl);
     const uint2* edge = reinterpret_cast<const uint2*>(unit + SU.o_edge);
     const int n_edge = (int)reinterpret_cast<const uint32_t*>(unit)[SU_EDGES];
+    if (n_edge > 0 && part > 0) return;                       // (uniform; with edges one workgroup sees to all tokens)
     const size_t row = (size_t)(p.first + l);
     int32_t* assign = c.assign + row * T;
     int32_t* pos = c.pos + row * T;
-    int* start = scratch;                                     // [words]: representatives in the words before
+    const ListScratch ls(scratch);                            // (start: representatives in the words before)
     uint32_t* member = reinterpret_cast<uint32_t*>(scratch) + LIST_SCRATCH / 4;    // [64 words] earliest representative of a cluster
     uint32_t* n_member = member + words * 64;                 // [64 words] how many it has
     for (int t = tid; t < words * 64; t += nthr) { member[t] = 0xFFFFFFFFu; n_member[t] = 0u; }
     if (tid < 64) {
         int tot = 0;
         for (int w0 = 0; w0 < words; w0 += 64) {
-            const int pc = w0 + lane < words ? __popcll(now[w0 + lane]) : 0;
+            const unsigned long long a = w0 + lane < words ? now[w0 + lane] : 0ull;
+            const int pc = __popcll(a);
             int inc = pc;
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) {
                 const int x = __shfl_up(inc, o, 64);
                 if (lane >= o) inc += x;
             }
-            if (w0 + lane < words) start[w0 + lane] = tot + inc - pc;
+            if (w0 + lane < words) { ls.now[w0 + lane] = a; ls.start[w0 + lane] = tot + inc - pc; }
             tot += __builtin_amdgcn_readlane(inc, 63);
         }
-        if (lane == 0) *reinterpret_cast<int4*>(c.info + row * 8) = int4{T - tot, 0, 0, ADA_OK};
+        if (lane == 0 && part == 0) *reinterpret_cast<int4*>(c.info + row * 8) = int4{T - tot, 0, 0, ADA_OK};
     }
     __syncthreads();
-    auto is_in = [&](int t) { return (now[t >> 6] >> (t & 63)) & 1ull; };
+    auto is_in = [&](int t) { return (ls.now[t >> 6] >> (t & 63)) & 1ull; };
     auto put = [&](int t, int a) {
         assign[t] = a;
-        pos[t] = start[a >> 6] + __popcll(now[a >> 6] & ((1ull << (a & 63)) - 1ull));
+        pos[t] = ls.start[a >> 6] + __popcll(ls.now[a >> 6] & ((1ull << (a & 63)) - 1ull));
     };
     for (int t = tid; t < T; t += nthr)
         if (is_in(t)) {
@@ -1100,7 +1114,16 @@ __device__ inline void screen_assign(const ChainParams& c, const ScreenUnit& SU,
         }
     __syncthreads();
     if (n_edge == 0) {
-        for (int t = tid; t < T; t += nthr) put(t, is_in(t) ? t : (int)min(member[cl[t]], (uint32_t)(T - 1)));
+        for (int t0 = part * 4 * nthr + tid; t0 < T; t0 += parts * 4 * nthr) {   // (a load behind a store waits for it)
+            int ct[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) ct[u] = cl[min(t0 + u * nthr, T - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int t = t0 + u * nthr;
+                if (t < T) put(t, is_in(t) ? t : (int)min(member[ct[u]], (uint32_t)(T - 1)));
+            }
+        }
         __syncthreads();
         return;
     }
@@ -1389,11 +1412,12 @@ __global__ __launch_bounds__(256 * KG) void k_cascade_rest(RestParams rp) {
     const unsigned long long alone = *reinterpret_cast<const unsigned long long*>(meta + META_ALONE);
     if (start >= first + n_layers) {
         const ScreenUnit SU(T, rp.c.s.nch, rp.c.s.edge_cap);
-        for (int j = worker; j < n_layers * (rp.c.assign ? 2 : 1); j += workers) {
-            const int l = j < n_layers ? j : j - n_layers;
+        const int items = n_layers * (rp.c.assign ? 2 : 1), parts = max(workers / items, 1);
+        for (int i = worker; i < items * parts; i += workers) {
+            const int j = i % items, part = i / items, l = j < n_layers ? j : j - n_layers;
             if ((alone >> l) & 1ull) continue;
-            if (j < n_layers) screen_lists(rp.c, SU, l, g, reinterpret_cast<int*>(lds));
-            else screen_assign(rp.c, SU, l, g, reinterpret_cast<int*>(lds));
+            if (j < n_layers) screen_lists(rp.c, SU, l, g, reinterpret_cast<int*>(lds), part, parts);
+            else screen_assign(rp.c, SU, l, g, reinterpret_cast<int*>(lds), part, parts);
         }
         if (alone == 0ull) return;
     }
