@@ -1710,10 +1710,9 @@ void launch_screen_pairs(const ScreenParams& sp, const PairItems& it, dim3 grid,
 // Lanes per product of whole rows: four pieces of a row in flight per lane, at least eight lanes (a cache line) side by side.
 inline int screen_lanes(int np) { return np >= 256 ? 64 : np >= 128 ? 32 : np >= 64 ? 16 : 8; }
 
-// The graph of near pairs of every unit of sp; rest: the unexplained candidates too (else the launch behind sees to them, if the exact pass
-// counts the pairs).
+// The graph of near pairs of every unit of sp.  Where the exact pass counts the pairs the launch behind sees to the unexplained candidates.
 template <typename In>
-hipError_t launch_screen(ScreenParams& sp, bool rest, hipStream_t st) {
+hipError_t launch_screen(ScreenParams& sp, hipStream_t st) {
     const int units = sp.G * sp.L;
     // Who counts the pairs inside clusters.  The exact pass takes an atomic with a return per token for it, 20 thousand of them a microsecond
     // from the whole chip, which short rows do not hide; each workgroup of k_screen_rest a histogram of its unit in LDS, 1 us.  16 heads
@@ -1751,7 +1750,7 @@ hipError_t launch_screen(ScreenParams& sp, bool rest, hipStream_t st) {
     hipError_t e = np >= 256 ? launch_screen_exact_any<In, 64>(sp, np, st) : np >= 128 ? launch_screen_exact_any<In, 32>(sp, np, st)
                  : np >= 64 ? launch_screen_exact_any<In, 16>(sp, np, st) : launch_screen_exact_any<In, 8>(sp, np, st);
     if (e != hipSuccess) return e;
-    if (!rest && sp.count_pairs) return hipSuccess;
+    if (sp.count_pairs) return hipSuccess;
     const int lanes = screen_lanes(np);
     return lanes == 64 ? launch_screen_rest<In, 64>(sp, st) : lanes == 32 ? launch_screen_rest<In, 32>(sp, st)
          : lanes == 16 ? launch_screen_rest<In, 16>(sp, st) : launch_screen_rest<In, 8>(sp, st);
@@ -1822,11 +1821,15 @@ int screen_full(const ScreenPlan& plan, const void* X, int T, int d, long long l
                                        screen_sort_lds(FUSED_MAX_T));
     });
     if (attr_err != hipSuccess) return ADA_ERR_DEVICE;
-    hipError_t e = dtype == ADA_BF16 ? launch_screen<uint16_t>(sp, true, st) : launch_screen<float>(sp, true, st);
+    hipError_t e = dtype == ADA_BF16 ? launch_screen<uint16_t>(sp, st) : launch_screen<float>(sp, st);
     if (e != hipSuccess) return ADA_ERR_DEVICE;
     {
         ProfScope ps(ADA_K_UPDATE, st);
-        hipLaunchKernelGGL(k_screen_sort, dim3(1), dim3(SCREEN_SORT_THREADS), screen_sort_lds(T), st, f);
+        f.ntile = rest_tiles(T);
+        f.lanes = screen_lanes((d * (dtype == ADA_BF16 ? 2 : 4) + 15) / 16);
+        f.f32 = dtype == ADA_F32;
+        const int rest = rest_workgroups(f.ntile, 1, SCREEN_SORT_THREADS / 256);   // (T < 65536: the exact pass counts the pairs)
+        hipLaunchKernelGGL(k_screen_sort, dim3((unsigned)(1 + rest)), dim3(SCREEN_SORT_THREADS), screen_sort_lds(T), st, f);
         if (hipGetLastError() != hipSuccess) return ADA_ERR_DEVICE;
     }
     if (!gamma) return ADA_OK;
@@ -1939,7 +1942,7 @@ int run_layers_screened(const ScreenPlan& plan, const void* const* X_layers, int
         sp.first = first;
         sp.L = end - first < per ? end - first : per;
         for (int i = 0; i < SCREEN_MAX_LAYERS; ++i) sp.X[i] = i < sp.L ? X_layers[first + i] : nullptr;
-        hipError_t e = dtype == ADA_BF16 ? launch_screen<uint16_t>(sp, false, st) : launch_screen<float>(sp, false, st);
+        hipError_t e = dtype == ADA_BF16 ? launch_screen<uint16_t>(sp, st) : launch_screen<float>(sp, st);
         if (e != hipSuccess) return ADA_ERR_DEVICE;
         // (wide workgroups from 1025 tokens on; us, 512 threads -> 1024, 16 layers of d=256: T=1000 6.5 -> 7.2, 1500 8.8 -> 8.3, 4000 13.7 -> 11.4)
         c.ntile = rest_tiles(T);

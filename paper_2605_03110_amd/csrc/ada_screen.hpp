@@ -814,8 +814,25 @@ __device__ inline void screen_rest_tiles(const ScreenParams& p, const ScreenUnit
     }
 }
 
-// k_screen_rest: the unexplained candidates of all units as a launch of its own, in front of k_screen_sort and where the pairs inside
-// clusters are counted here.  Units without any are left at once.
+// Whether this workgroup is the last of n to come here (all threads; the counter is zero before and after), what the others stored before is
+// seen from here on.
+__device__ inline bool screen_last(int32_t* counter, int n) {
+    __shared__ int s_last;
+    drain_stores();
+    __syncthreads();
+    if (threadIdx.x == 0) s_last = atomicAdd(counter, 1) == n - 1;
+    __syncthreads();
+    if (!s_last) return false;                                // uniform
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+    __syncthreads();
+    return true;
+}
+
+// k_screen_rest: the unexplained candidates of all units as a launch of its own, where the pairs inside clusters are counted
+// here.  Units without any are left at once.
 template <typename In, int LPR>
 __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) {
     __shared__ RestTile tile;
@@ -894,10 +911,9 @@ template <int U> __device__ inline int chain_token(int u) {
 }
 
 // One layer's lists, counts and Gram operations from the bits of its set and of the one before (any workgroup size up to
-// 1024; scratch: LIST_SCRATCH bytes of LDS); part of parts: its share of the tokens.  One wave reads the bits and sums over the words before; they stay in LDS for the
-// others (Read from memory by each
-// of them again, behind the stores of the tokens before, and a layer by one workgroup: 28 layers of T=2048 7.0 us, now 5.5, 8 layers of four sequences
-// of T=8192 11.4, now 7.1.)
+// 1024; scratch: LIST_SCRATCH bytes of LDS); part of parts: its share of the tokens.  One wave reads the bits and sums over
+// the words before; they stay in LDS for the others.  (Read from memory by each of them again, behind the stores of the tokens
+// before, and a layer by one workgroup: 28 layers of T=2048 7.0 us, now 5.5, 8 layers of four sequences of T=8192 11.4, now 7.1.)
 struct ListScratch {
     unsigned long long *now, *was;                            // [words] the set, and the one inherited
     int* start;                                               // [3][LIST_WORDS] members in the words before: the set, added, removed
@@ -1246,19 +1262,7 @@ __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
         open = uniform64(s_state[0]);
         closed = uniform64(s_state[1]);
     }
-    if (open) {
-        __shared__ int s_last;
-        drain_stores();
-        __syncthreads();
-        if (tid == 0) s_last = atomicAdd(meta + META_WALK, 1) == __popcll(open) * c.rest;
-        __syncthreads();
-        if (!s_last) return;                                  // uniform
-        if (tid == 0) {
-            __hip_atomic_store(meta + META_WALK, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        }
-        __syncthreads();
-    }
+    if (open && !screen_last(meta + META_WALK, __popcll(open) * c.rest + 1)) return;   // uniform
     uint32_t edges_of = 0u;
     bool is_dense = (closed >> lane) & 1ull;
     if (open || !c.rest) {                                    // (plain units have neither)

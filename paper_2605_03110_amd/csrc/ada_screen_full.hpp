@@ -3,7 +3,7 @@
 //
 // The set follows from clusters and edges alone.  A token's largest |cos| to an earlier token does as well, up to the few
 // products that compete for it: a token of a cluster is closer to its pivot than any pair that is no candidate can be, so
-// its maximum lies among the earlier members of its cluster (and the pairs k_screen_rest multiplies out); only a token
+// its maximum lies among the earlier members of its cluster (and the unexplained candidates multiplied out); only a token
 // that is in no earlier token's cluster, a HEAD, has to meet all earlier tokens.  With K centres among T tokens heads come
 // early -- a new centre is met for the first time after about K tokens -- so their rows of the triangle are short:
 // 0.5% of it at T = 8192, K = 400, a third at K = T / 2.
@@ -27,6 +27,7 @@ struct ScreenFullParams {
     ScreenParams s;            // one unit
     int want_gamma, greedy, big_tiles;   // big_tiles: 64 x 64 tiles of heads from which on they are cut into 128 x 128
     float most_heads;          // share of the triangle above which the heads' tiles are no saving
+    int ntile, lanes, f32;     // of the unexplained candidates, see screen_rest_tiles
     int32_t* gate;             // out: 1 = the graph does not decide, the launches behind run the full Gram
     uint8_t* mask;             // may be NULL
     int32_t* idx;              // may be NULL
@@ -41,7 +42,9 @@ __device__ inline ScreenLists screen_full_lists(const ScreenParams& p, const Scr
 }
 
 constexpr int SCREEN_SORT_THREADS = 1024;
-inline int screen_sort_lds(int T) { return (T + 63) / 64 * 64 * 8; }   // counts (4 bytes), clusters and members (2 bytes each)
+inline int screen_sort_lds(int T) {                           // counts (4 bytes), clusters and members (2 bytes each)
+    return std::max((T + 63) / 64 * 64 * 8, SCREEN_SORT_THREADS / 256 * (int)sizeof(RestTile));
+}
 
 // Exclusive sums of two words over the workgroup (sums: one int2 per wave, not used before).
 __device__ inline int2 screen_scan(int2 v, int2* total, int2* sums) {
@@ -77,15 +80,39 @@ __global__ __launch_bounds__(SCREEN_SORT_THREADS) void k_screen_sort(ScreenFullP
     const int tid = threadIdx.x, T = p.T, Tp = (T + 63) & ~63;
     const uint32_t* hdr = reinterpret_cast<const uint32_t*>(p.area);
     const ScreenLists L = screen_full_lists(p, U);
+    // The first workgroup sorts.  The others see to the unexplained candidates, if there are any: then the last one to be done sorts, as in
+    // k_screen_chain.  (As a launch in front that left at once as a rule it took 2 to 4 us; looking at the counts here takes 0.6.  Full
+    // selection, T=8192, d=4096 87.1 -> 83.9 us, greedy covering, T=2048, d=4096 50.8 -> 49.0.)
+    __shared__ int s_state;
+    __shared__ uint32_t s_pairs;
     uint32_t* cnt = reinterpret_cast<uint32_t*>(lds);         // members of a cluster; then the next free place in the list
     uint32_t* cl2 = cnt + Tp;                                 // two clusters per word; bit 15: an edge to an earlier token
     uint16_t* cl = reinterpret_cast<uint16_t*>(cl2);
     uint16_t* list = cl + Tp;
-    const uint32_t n_edge = hdr[SU_EDGES];
-    const bool dense = hdr[SU_DENSE] != 0u;
-    const uint32_t pairs = screen_counts(hdr).pairs;
-    for (int t = tid; t < Tp; t += SCREEN_SORT_THREADS) cnt[t] = 0u;
-    for (int w = tid; w < Tp / 2; w += SCREEN_SORT_THREADS) cl2[w] = reinterpret_cast<const uint32_t*>(p.area + U.o_cl)[w];
+    auto take = [&] {
+        for (int t = tid; t < Tp; t += SCREEN_SORT_THREADS) cnt[t] = 0u;
+        for (int w = tid; w < Tp / 8; w += SCREEN_SORT_THREADS) reinterpret_cast<uint4*>(cl2)[w] = reinterpret_cast<const uint4*>(p.area + U.o_cl)[w];
+    };
+    if (blockIdx.x == 0) take();                              // (no candidate changes the clusters; the last wave has the header besides)
+    if (tid >= SCREEN_SORT_THREADS - 64) {
+        const ScreenCounts n = screen_counts(hdr);
+        s_state = screen_state(p, n) | ((n.flags & SF_LOW) ? 16 : 0);
+        s_pairs = n.pairs;
+    }
+    screen_barrier();
+    const int state = __builtin_amdgcn_readfirstlane(s_state) & 15;
+    const uint32_t pairs = s_pairs;
+    if (state != UNIT_OPEN && blockIdx.x > 0) return;         // uniform
+    if (state == UNIT_OPEN) {
+        if (blockIdx.x > 0)
+            screen_rest_tiles<SCREEN_SORT_THREADS>(p, U, p.area, 0, 0, (s_state & 16) != 0, (int)blockIdx.x - 1, (int)gridDim.x - 1, f.ntile, f.lanes,
+                                                   f.f32 != 0, lds);
+        if (!screen_last(p.meta + META_WALK, (int)gridDim.x)) return;
+        if (blockIdx.x > 0) take();
+    }
+    const uint32_t n_edge = state == UNIT_OPEN ? __hip_atomic_load(hdr + SU_EDGES, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    const bool dense = state == UNIT_DENSE ||
+                       (state == UNIT_OPEN && __hip_atomic_load(hdr + SU_DENSE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u);
     // (the greedy covering takes a token that only covered tokens cover: with edges it is resolved from the pair bits)
     if (dense || (f.greedy && n_edge) || (f.want_gamma && pairs > SCREEN_FULL_PAIRS * (uint32_t)T)) {
         if (tid == 0) { *f.gate = 1; L.work[SW_TILES] = 0; L.work[SW_TILES128] = 0; }
