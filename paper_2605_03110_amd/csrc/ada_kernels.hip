@@ -1783,7 +1783,7 @@ hipError_t launch_screen_gram(const ScreenParams& sp, const GramParams& p, hipSt
 //   fp32: 2048 x 768 63 -> 52 (3.2e9), 1500 x 768 44 -> 50 (1.7e9); T=1100 d=4096 105 -> 123 (one tile takes 100)
 //   greedy covering, which also saves its resolution: 1536 x 768 59 -> 37, 2048 x 4096 93 -> 54, 1100 x 4096 53 -> 51
 bool screen_full_eligible(const void* X, int T, int d, long long ld, int dtype, float tau, bool greedy, ScreenPlan* plan) {
-    if (T < 1500 || T > FUSED_MAX_T) return false;
+    if (T < SCREEN_FULL_MIN_T || T > FUSED_MAX_T) return false;
     const char* e = dev_switch("ADA_SCREEN");
     if ((e && e[0] == '0') || dev_switch("ADA_GRAM") || dev_switch("ADA_TILE")) return false;
     const bool pieces = dtype == ADA_BF16 && d % DmaGeom::HC == 0 && rows16(dtype, X, ld);
@@ -1804,6 +1804,7 @@ int screen_full(const ScreenPlan& plan, const void* X, int T, int d, long long l
     f.want_gamma = gamma != nullptr;
     f.greedy = greedy;
     f.big_tiles = 1024;
+    f.whole_from = 20 * device_cus();                         // as they come: two tiles per 64 members, on five eighths of the CUs
     // A greedy covering goes to the full Gram with its first edge, and a token with unexplained candidates is a head as a rule.
     screen_room(sp, ScreenUnit(T, plan.nch, screen_edges(T)), 1);
     sp.open = std::min(sp.open, (uint32_t)(greedy ? T / 16 + 16 : T));

@@ -487,6 +487,21 @@ def test_full_selection_on_the_graph_of_near_pairs(kind, T, d, dtype, tau, greed
             assert np.array_equal(step["idx"], got["idx"]) or kind in ("loose", "common")   # (chains: a removed token covers nobody)
 
 
+@pytest.mark.parametrize("sizes,T", [((33, 32), 5196), ((64,), 5184), ((65,), 5201), ((40, 30, 2), 5121), ((63, 2), 5120), ((1, 128, 3), 5280),
+                                     ((31, 34, 64, 1, 1), 5249), ((200, 5, 7), 5300), ((33, 32), 2050), ((2,), 5300), ((1, 128, 3), 2111), ((200, 5, 7), 5119)])
+def test_blocks_of_the_members(sizes, T):
+    """The members' list cut between clusters from 5120 members in clusters of eight on, every 64 below: sizes that fill a block, that miss it by one, that never
+    share one, and clusters of several blocks; every token's largest correlation against the oracle."""
+    print("[case] blocks of the members: sizes %s T=%d" % (sizes, T), flush=True)
+    rng, d = np.random.default_rng(T), 768
+    of = np.repeat(np.arange(T), np.resize(sizes, T))[:T]
+    C = rng.standard_normal((of.max() + 1, d))
+    C /= np.linalg.norm(C, axis=1, keepdims=True)
+    x_cpu = torch.from_numpy((C[rng.permutation(of)] + 0.004 * rng.standard_normal((T, d)) / np.sqrt(d)).astype(np.float32))
+    got = pa.fetch(pa.ada_select_full(x_cpu.to(DEV), 0.1))
+    parity.check_full(x_cpu, 0.1, got, "sizes %s" % (sizes,))
+
+
 def exact_pass(T, d, L, groups, esz, tau):
     """How k_screen_exact reads the layers of a call (run_layers_screened, launch_screen, launch_screen_exact and screen_streams of csrc/):
     lanes per row, rows per lane group, and whether X goes past the caches.  Rows and matrices start on whole cache lines."""

@@ -159,3 +159,37 @@ def test_steps_behind_a_dense_layer_end_however_few_workgroups_run(groups, worke
     for _ in range(10):
         n = int(rng.integers(1, 5))
         claims(rng, groups, workers, [workers if groups > 1 else int(rng.integers(1, workers // 8 + 1)) * 8 for _ in range(n)], at_once)
+
+
+def member_blocks(sizes):
+    """sort_blocks of csrc/ada_screen_full.hpp: (start, first block of its cluster) of every block of members."""
+    edges = np.concatenate([[0], np.cumsum(sizes)])
+    mem, starts = int(edges[-1]), edges[:-1]
+    last = lambda p: int(starts[np.searchsorted(starts, p, side="right") - 1])
+    out = []
+    for lo in range(0, mem, 512):
+        p, up, of = last(lo), last(lo + 512) if lo + 512 < mem else mem, 0
+        while p < up:
+            if p in starts:
+                of = len(out)
+            out.append((p, of))
+            if p + 64 >= up:
+                break
+            p = last(p + 64) if last(p + 64) > p else p + 64
+    return out, mem
+
+
+@pytest.mark.parametrize("sizes", [(33, 32), (64,), (65,), (2,), (63, 2), (2, 128, 3), (33, 32) * 7 + (2, 2, 49), (1000, 3), (16384,), (40, 25, 2, 63), (31, 34)])
+def test_blocks_of_members(sizes):
+    """No more blocks than the work list has room for, up to 64 members each; a cluster of up to 64 lies in one block, a larger one starts one."""
+    sizes = np.resize(sizes, 16384)
+    sizes = sizes[np.cumsum(sizes) <= 16384]
+    blocks, mem = member_blocks(sizes)
+    starts = np.array([b[0] for b in blocks] + [mem])
+    assert len(blocks) <= 16384 // 32 + 16384 // 512
+    assert starts[0] == 0 and (np.diff(starts) > 0).all() and (np.diff(starts) <= 64).all()
+    at = np.concatenate([[0], np.cumsum(sizes)])
+    for c, n in enumerate(sizes):
+        lo, hi = np.searchsorted(starts, at[c], side="right") - 1, np.searchsorted(starts, at[c] + n - 1, side="right") - 1
+        assert lo == hi or (n > 64 and starts[lo] == at[c])
+        assert all(blocks[b][1] == lo for b in range(lo + 1, hi + 1)), "every later block of a cluster goes back to its first"
