@@ -33,7 +33,7 @@ struct AttnParams {
     const int32_t* assign;     // read where pos is NULL
 };
 
-// Several layers in one launch (blockIdx.z): what differs between them.  The other pointers of AttnParams are layer 0's; idx
+// Several layers in one launch (z, see attn_who): what differs between them.  The other pointers of AttnParams are layer 0's; idx
 // and pos rows lie T apart, set sizes 4 and infos 8 integers.
 constexpr int ATTN_LAYERS = 16;
 struct AttnLayers {
@@ -41,9 +41,8 @@ struct AttnLayers {
     float* out[ATTN_LAYERS];
 };
 struct AttnOne {};            // one layer: AttnParams says it all (500 bytes less of arguments: 16 x 128 fp32 at T=2048 67.3 -> 67.0 us)
-__device__ inline void attn_layer(AttnParams&, const AttnOne&) {}
-__device__ inline void attn_layer(AttnParams& p, const AttnLayers& a) {
-    const int z = blockIdx.z;
+__device__ inline void attn_layer(AttnParams&, const AttnOne&, int) {}
+__device__ inline void attn_layer(AttnParams& p, const AttnLayers& a, int z) {
     p.Q = a.Q[z]; p.K = a.K[z]; p.V = a.V[z]; p.out = a.out[z];
     p.idx += (size_t)z * p.T;
     p.pos += (size_t)z * p.T;
@@ -83,9 +82,9 @@ __global__ __launch_bounds__(256) void k_attn_pos(const int32_t* __restrict__ id
     if (threadIdx.x == 0) err[blockIdx.x] = !r_ok ? (int)ADA_ERR_SHAPE : bad ? (int)ADA_ERR_INDEX : (int)ADA_OK;
 }
 
-// Workgroup (0, 0) reports the status of the call.
-__device__ inline void attn_report(const AttnParams& p, int r, int e) {
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+// A layer's first workgroup reports its status.
+__device__ inline void attn_report(const AttnParams& p, bool first, int r, int e) {
+    if (first && threadIdx.x == 0) {
         p.info[0] = e == (int)ADA_ERR_SHAPE ? 0 : r;
         p.info[1] = 0;
         p.info[2] = 0;
@@ -94,13 +93,13 @@ __device__ inline void attn_report(const AttnParams& p, int r, int e) {
 }
 
 // The status of the call (the worst word k_attn_pos left), the same in every thread.
-__device__ inline int attn_status(const AttnParams& p, int r) {
+__device__ inline int attn_status(const AttnParams& p, bool first, int r) {
     const int lane = threadIdx.x & 63;
     int e = (r >= 1 && r <= p.r_host && r <= p.T) ? 0 : (int)ADA_ERR_SHAPE;   // (positions from elsewhere: nerr = 0)
     for (int i = lane; i < p.nerr; i += 64) e = max(e, p.err[i]);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) e = max(e, __shfl_xor(e, o, 64));
-    attn_report(p, r, e);
+    attn_report(p, first, r, e);
     return e;
 }
 
@@ -115,7 +114,7 @@ constexpr int ATTN_POS_LDS = 2 * ATTN_OWN_POS * 2;
 // Positions (0xFFFF: none) to `at` (LDS, ATTN_POS_LDS bytes: positions, then the table); the status of the call, the same in every
 // thread.  The checks are k_attn_pos's.
 template <int THREADS>
-__device__ inline int attn_positions(const AttnParams& p, int r, uint16_t* at) {
+__device__ inline int attn_positions(const AttnParams& p, bool first, int r, uint16_t* at) {
     constexpr int N = ATTN_OWN_POS / THREADS;
     uint16_t* table = at + ATTN_OWN_POS;
     const int tid = threadIdx.x;
@@ -150,21 +149,27 @@ __device__ inline int attn_positions(const AttnParams& p, int r, uint16_t* at) {
         }
         e = __syncthreads_or(bad) ? (int)ADA_ERR_INDEX : (int)ADA_OK;
     }
-    attn_report(p, r, e);
+    attn_report(p, first, r, e);
     return e;
 }
 
-// Workgroup -> (head, first query block).  Workgroups go to the eight XCDs in turn by their linear index, and every
+// Workgroup -> (head, first query block, layer).  Workgroups go to the eight XCDs in turn by their linear index, and every
 // XCD has an L2 of its own: with the launch's natural order the query blocks of one head would sit on eight different
 // XCDs and each of them would pull that head's K and V rows from memory.  When the head count is a multiple of 8 the
 // index is re-read so that a head's workgroups share an XCD (head % 8).  Query blocks run slowest, so that under the
-// causal mask, which takes them from the last one down (attn_block), the long ones start first.
-struct AttnWho { int h, qblk; };
-__device__ inline AttnWho attn_who(int H) {
-    const int lin = blockIdx.y * gridDim.x + blockIdx.x;
-    if (H % 8 != 0) return {lin % H, lin / H};
-    const int xcd = lin & 7, slot = lin >> 3, hx = H >> 3;
-    return {(slot % hx) * 8 + xcd, slot / hx};
+// causal mask, which takes them from the last one down (attn_block), the long ones start first: those of all layers, as the
+// long ones of the last layer would end alone.  16 heads x 256, T=2048, causal: 4 layers of r=434 70.1 -> 56.8 us; calls of 6 layers 189 -> 165,
+// 8 layers 200 -> 203, 10 layers 245 -> 239, 4 layers of T=4096 264 -> 229.  Without the mask they are alike, and a layer's K and V are done with
+// before the next one's.
+struct AttnWho {
+    int h, qblk, layer;
+    __device__ bool first() const { return h == 0 && qblk == 0; }
+};
+__device__ inline AttnWho attn_who(int H, int causal) {
+    int lin = blockIdx.y * gridDim.x + blockIdx.x, n = 1, z = blockIdx.z;
+    if (causal) { n = gridDim.z; lin += z * (int)(gridDim.x * gridDim.y); z = 0; }
+    const int side = H % 8 ? 1 : 8, hx = H / side, of = lin % side, slot = lin / side, row = slot % (hx * n);
+    return {(row % hx) * side + of, slot / (hx * n), z + row / hx};
 }
 __device__ inline int attn_block(int b, int nq, int causal) { return causal ? nq - 1 - b : b; }
 
@@ -250,7 +255,8 @@ __device__ inline void attn_hand_over(const float* obuf, int* takers, int* count
 // Layers: AttnOne or AttnLayers.
 template <typename In, int DH, typename Layers>
 __global__ __launch_bounds__(256) void k_attn_rep(AttnParams p, Layers layers) {
-    attn_layer(p, layers);
+    const AttnWho who = attn_who(p.H, p.causal);
+    attn_layer(p, layers, who.layer);
     using G = AttnGeom<In, DH>;
     constexpr int EPP = G::EPP, PPR = G::PPR, PPRV = G::PPRV, NB = DH / 64;
     extern __shared__ __align__(16) char lds[];
@@ -270,8 +276,7 @@ __global__ __launch_bounds__(256) void k_attn_rep(AttnParams p, Layers layers) {
     constexpr bool ONE = std::is_same<Layers, AttnOne>::value;
     const uint16_t* own_pos = reinterpret_cast<const uint16_t*>(lds + G::LDS);   // (one layer only: several come with their positions)
     const bool own = ONE && !p.pos;                        // uniform
-    if ((own ? attn_positions<256>(p, r, reinterpret_cast<uint16_t*>(lds + G::LDS)) : attn_status(p, r)) != ADA_OK) return;   // the set or the assignment is rejected
-    const AttnWho who = attn_who(p.H);
+    if ((own ? attn_positions<256>(p, who.first(), r, reinterpret_cast<uint16_t*>(lds + G::LDS)) : attn_status(p, who.first(), r)) != ADA_OK) return;   // the set or the assignment is rejected
     const int h = who.h;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -542,7 +547,8 @@ template <int DH> struct AttnGeom2 {
 // STREAM: outputs are stored past the caches (see launch_attn_regs).
 template <int DH, typename Layers, bool STREAM>
 __global__ __launch_bounds__(512) void k_attn_rep2(AttnParams p, Layers layers) {
-    attn_layer(p, layers);
+    const AttnWho who = attn_who(p.H, p.causal);
+    attn_layer(p, layers, who.layer);
     using In = uint16_t;
     using G = AttnGeom2<DH>;
     constexpr int EPP = 8, PPR = G::PPR, NB = DH / 32, KS = DH / 16, NP = PPR / 4;
@@ -561,8 +567,7 @@ __global__ __launch_bounds__(512) void k_attn_rep2(AttnParams p, Layers layers) 
     constexpr bool ONE = std::is_same<Layers, AttnOne>::value && DH <= 128;   // (see attention_run)
     const uint16_t* own_pos = reinterpret_cast<const uint16_t*>(lds + G::LDS);   // (one layer only: several come with their positions)
     const bool own = ONE && !p.pos;                        // uniform
-    if ((own ? attn_positions<512>(p, r, reinterpret_cast<uint16_t*>(lds + G::LDS)) : attn_status(p, r)) != ADA_OK) return;   // the set or the assignment is rejected
-    const AttnWho who = attn_who(p.H);
+    if ((own ? attn_positions<512>(p, who.first(), r, reinterpret_cast<uint16_t*>(lds + G::LDS)) : attn_status(p, who.first(), r)) != ADA_OK) return;   // the set or the assignment is rejected
     const int h = who.h;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -87,10 +87,11 @@ __device__ inline int sort_start(const unsigned long long* edge, int p) {
     return m ? w * 64 + 63 - __clzll((long long)m) : 0;
 }
 
-// Cuts the members' list into blocks of up to 64, between clusters where it can be (one wave; first, blocks: out, see SW_FIRST).  From a block's
-// start on, the next one starts at the last cluster that starts within 64 members.  Each lane goes through about 512 members like this, from a cluster's start to one, so a chain of ten
-// steps takes the place of one of mem / 60; half a block more per lane is the price.  (A larger cluster starts a block, as no other starts
-// within the 64 behind it.)
+// Cuts the members' list into blocks of up to 64, between clusters where it can be (one wave; first, blocks: out, see
+// SW_FIRST).  From a block's start on, the next one starts at the last cluster that starts within 64 members.  Each lane goes
+// through about 512 members like this, from a cluster's start to one, so a chain of ten steps takes the place of one of
+// mem / 60; half a block more per lane is the price.  (A larger cluster starts a block, as no other starts within the 64
+// behind it.)
 __device__ inline void sort_blocks(const unsigned long long* edge, int mem, uint32_t* first, int* blocks) {
     const int lane = threadIdx.x & 63;
     const int lo = lane * SORT_LANE < mem ? sort_start(edge, lane * SORT_LANE) : mem,

@@ -502,6 +502,24 @@ def test_blocks_of_the_members(sizes, T):
     parity.check_full(x_cpu, 0.1, got, "sizes %s" % (sizes,))
 
 
+@pytest.mark.parametrize("T,H,dh,L,dtype", [(700, 3, 64, 3, "bf16"), (1100, 16, 64, 5, "bf16"), (900, 8, 128, 2, "f32"), (2100, 16, 128, 12, "bf16"),
+                                            (640, 12, 64, 16, "f32")])
+def test_layers_side_by_side_under_the_causal_mask(T, H, dh, L, dtype):
+    """Attention of several layers in one launch, their longest query blocks first: outputs and reports are those of one call per layer.  Heads that
+    are and are not a multiple of eight, fewer workgroups than query blocks and more, up to as many layers as a launch takes."""
+    print("[case] layers side by side T=%d H=%d d_h=%d L=%d %s" % (T, H, dh, L, dtype), flush=True)
+    w = wl.small(T=T, d=H * dh, K=T // 5, L=L, dtype=dtype, seed=17 + T, p=0.1)
+    xs = [x.to(DEV) for x in wl.layer_list(w)]
+    qs, ks, vs = ([t[i].to(DEV) for t in [wl.qkv(w, H, layer=l) for l in range(L)]] for i in range(3))
+    flags = pa.FLAG_ATTN_CAUSAL
+    res = pa.ada_pipeline_layers(xs, qs, ks, vs, H, w.tau, flags=flags)
+    assert res["info"].cpu()[:, 7].tolist() == [0] * L
+    for l in range(L):
+        r = int(res["counts"][l, 0])
+        one = pa.ada_attention_compressed(qs[l], ks[l], vs[l], H, res["idx"][l, :r].contiguous(), res["assign"][l].contiguous(), flags=flags)
+        assert int(res["info"][l, 4]) == r and torch.equal(one["out"], res["out"][l]), "layer %d" % l
+
+
 def exact_pass(T, d, L, groups, esz, tau):
     """How k_screen_exact reads the layers of a call (run_layers_screened, launch_screen, launch_screen_exact and screen_streams of csrc/):
     lanes per row, rows per lane group, and whether X goes past the caches.  Rows and matrices start on whole cache lines."""
