@@ -713,23 +713,25 @@ __device__ inline void screen_rest_tiles(const ScreenParams& p, const ScreenUnit
     constexpr int SUB = THREADS / 256;
     const int tid = (int)threadIdx.x & 255, sub = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8), lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     RestTile* tiles = reinterpret_cast<RestTile*>(lds);
-    RestTile& my = tiles[sub];
     uint32_t* hdr = reinterpret_cast<uint32_t*>(base);
     const float* rho = reinterpret_cast<const float*>(base + U.o_rho);
     const uint16_t* cl = reinterpret_cast<const uint16_t*>(base + U.o_cl);
     unsigned long long* edge = reinterpret_cast<unsigned long long*>(base + U.o_edge);
-    const int side = slots < ntile ? SUB : 1;                 // (with a workgroup per tile the other threads have none)
+    // With a workgroup per tile its first 256 threads find the pairs and all of them form the products: 12 layers of T=512, d=768 in fp32, all
+    // tokens loose, with 512 threads 88.7 -> 65.1 us (and the walk).
+    const int side = slots < ntile ? SUB : 1, mine = side > 1 ? tid : (int)threadIdx.x, many = side > 1 ? 256 : THREADS;
+    RestTile& my = tiles[side > 1 ? sub : 0];
     for (int tile0 = slot * side; tile0 < ntile; tile0 += slots * side) {
         const int tile = tile0 + sub;
         const bool exists = sub < side && tile < ntile;       // (uniform per tile; the barriers are everybody's)
         int sb, tb;
         screen_blocks(min(tile, ntile - 1), &sb, &tb);
         __syncthreads();
-        if (tid == 0) {
+        if (mine == 0) {
             my.n = my.edges = 0;
             if (sub == 0) tiles[0].stop = __hip_atomic_load(hdr + SU_DENSE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
         }
-        {
+        if (sub < side) {
             const int tok = min(tid < 128 ? sb * 128 + tid : tb * 128 + tid - 128, p.T - 1);
             my.rho[tid] = fminf(rho[tok], 1.f);
             my.cl[tid] = cl[tok];
@@ -776,7 +778,7 @@ __device__ inline void screen_rest_tiles(const ScreenParams& p, const ScreenUnit
         __syncthreads();
         int n = my.n;
         if (n > SCREEN_TILE_PAIRS) {                          // no saving in listing these
-            if (tid == 0) __hip_atomic_store(hdr + SU_DENSE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (mine == 0) __hip_atomic_store(hdr + SU_DENSE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             n = 0;
         }
         auto products = [&](auto lpr, auto in) {
@@ -784,7 +786,7 @@ __device__ inline void screen_rest_tiles(const ScreenParams& p, const ScreenUnit
             using In = decltype(in);
             const In* X = screen_x<In>(p, layer, group);
             const int li = tid & (LPR - 1);
-            for (int k = tid / LPR; k < n; k += 256 / LPR) {
+            for (int k = mine / LPR; k < n; k += many / LPR) {
                 const uint32_t e = my.pair[k];
                 const int s = (int)(e >> 16), t = (int)(e & 0xFFFFu);
                 float xy, xx, yy;
@@ -804,13 +806,13 @@ __device__ inline void screen_rest_tiles(const ScreenParams& p, const ScreenUnit
         else pick(uint16_t{});
         __syncthreads();
         const int ne = my.edges;
-        if (tid == 0 && ne > 0) my.at = (int)atomicAdd(hdr + SU_EDGES, (uint32_t)ne);
+        if (mine == 0 && ne > 0) my.at = (int)atomicAdd(hdr + SU_EDGES, (uint32_t)ne);
         __syncthreads();
         const int at = my.at;
-        for (int k = tid; k < ne; k += 256)
+        for (int k = mine; k < ne; k += many)
             if (at + k < U.edge_cap)
                 __hip_atomic_store(edge + at + k, (unsigned long long)my.edge[k].y << 32 | my.edge[k].x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (tid == 0 && ne > 0 && at + ne > U.edge_cap) __hip_atomic_store(hdr + SU_DENSE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (mine == 0 && ne > 0 && at + ne > U.edge_cap) __hip_atomic_store(hdr + SU_DENSE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
