@@ -156,8 +156,8 @@ int ada_cascade_step(const void* X, int T, int d, int64_t ld, int dtype, float t
  * own image, one copy per GPU for the life of the process.  The call allocates nothing and frees nothing.
  *   T <= ADA_STATIC_MAX_T, else ADA_ERR_SHAPE (nothing is enqueued).
  * Every call on a GPU uses that GPU's one array: calls that overlap in time on one GPU (different streams, or threads)
- * race and must be ordered by the caller.  Every call leaves at zero what the next one needs at zero (without a gamma output
- * a small kernel clears it at the start of the call besides, with one the call's last kernel does).
+ * race and must be ordered by the caller; a call ordered behind them is right again.  What must start at zero is cleared by each
+ * call's last kernel (so the call can be captured), whatever the call found there.
  */
 #define ADA_STATIC_MAX_T 4096
 int ada_cascade_step_static(const void* X, int T, int d, int64_t ld, int dtype, float tau,

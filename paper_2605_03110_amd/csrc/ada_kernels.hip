@@ -2159,15 +2159,16 @@ int ada_cascade_step_static(const void* X, int T, int d, int64_t ld, int dtype, 
     const size_t ws_bytes = ws_bytes_for(ADA_STATIC_MAX_T);   // (what a step uses of a workspace is what the array holds)
     if (int e = check_common(X, T, d, ld, dtype, tau, ws, ws_bytes)) return e;
     if (r < 1 || r > T) return ADA_ERR_SHAPE;
-    // The array is laid out for its largest T whatever the call's, so what a call leaves at zero is what the next one needs at zero.
-    // With a gamma output the call's last launch (k_gamma_fix) clears it besides, whatever the call found there; without one
-    // nothing runs behind the step, and a fill in front of it does.  (With one there was a fill in front as well: 2.4 us on the
-    // device and on the host, of 16.8 at T=197, d=768.)
+    // The array is laid out for its largest T whatever the call's, and the last launch of every call clears what the next one needs at
+    // zero: k_gamma_fix where there is one, else a fill.  Of calls that overlapped the clearing that starts last starts behind the steps of
+    // all of them, so whatever they did to each other a call ordered behind them finds the array clear.  (A fill in front of calls
+    // with a gamma output as well: 2.4 us on the device and on the host, of 16.8 at T=197, d=768.)
     const Workspace w = carve(ws, ADA_STATIC_MAX_T);
-    if ((!gamma || (flags & ADA_FLAG_TWO_PASS)) &&
-        fill_u32(w.meta, (size_t)zero_words(w, ADA_STATIC_MAX_T), 0u, (hipStream_t)stream) != hipSuccess) return ADA_ERR_DEVICE;
-    return run_cascade(X, T, d, ld, dtype, tau, prev_idx, r, r_dev, idx, adds, removes, counts, gram_ops, gamma, ws,
-                       (hipStream_t)stream, flags, ADA_STATIC_MAX_T);
+    int rc = run_cascade(X, T, d, ld, dtype, tau, prev_idx, r, r_dev, idx, adds, removes, counts, gram_ops, gamma, ws,
+                         (hipStream_t)stream, flags, ADA_STATIC_MAX_T);
+    if ((rc != ADA_OK || !gamma || (flags & ADA_FLAG_TWO_PASS)) &&
+        fill_u32(w.meta, (size_t)zero_words(w, ADA_STATIC_MAX_T), 0u, (hipStream_t)stream) != hipSuccess && rc == ADA_OK) rc = ADA_ERR_DEVICE;
+    return rc;
 }
 
 namespace {
