@@ -47,7 +47,7 @@ enum { META_R = 0, META_NONREP = 1, META_STATUS = 2, META_GATE = 3 /* k_screen_s
        // screened selection: layers done so far; hand-over word, sign-off counter and claim words (one per XCD, in the lines of the
        // ticket counters) of k_cascade_rest, zero between calls
        META_PROGRESS = 8, META_REST_EPOCH = 10, META_REST_LEFT = 11,
-       META_ALONE = 12 /* and 13: layers of a launch whose assignment the graph leaves open, one bit each */, META_FIX = 14, META_WALK = 15 /* k_screen_chain; zero between calls */, META_WORDS = 16,
+       META_ALONE = 12 /* and 13: layers of a launch whose assignment the graph leaves open, one bit each */, META_FIX = 14, META_WALK = 15 /* screen_last; zero between calls */, META_WORDS = 16,
        META_REST_CLAIM = META_TICKET + 64 + 8 /* and 32, 64 .. 224 further on */ };
 static_assert((META_REST_CLAIM + 7 * 32 + 1) * 4 <= META_BYTES, "claim words");
 

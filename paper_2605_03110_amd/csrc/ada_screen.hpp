@@ -50,7 +50,7 @@ enum { SU_EDGES = 3, SU_DENSE = 4, SU_CAND = 32, SU_PART = SU_CAND + 8 * 32, SU_
 // What every workgroup of the pair and exact passes adds to is kept once per XCD, a cache line each, from words SU_CAND and
 // SU_PART on (lines of their own: the exact pass reads the candidates while it counts the pairs): one address takes an atomic every 25 ns from the whole chip, which was most of these passes where one unit has all the
 // workgroups (T = 8192, d = 4096: pairs 18.6 -> 13.6 us, exact 35.4 -> 20.7 us; T = 2048: 5.6 -> 5.2 and 11.8 -> 9.0).
-enum { SU_PAIRS = 0, SU_FLAGS = 1 };
+enum { SU_PAIRS = 0, SU_FLAGS = 1, SU_DONE = 2 /* sign-offs of the unit's workgroups, see screen_last */ };
 enum { SF_LOW = 1, SF_MESH = 2 };                             // SU_FLAGS: a row below f2; a pivot that has a pivot itself
 
 struct ScreenCounts { uint32_t cand, pairs, flags; };
@@ -816,21 +816,27 @@ __device__ inline void screen_rest_tiles(const ScreenParams& p, const ScreenUnit
     }
 }
 
-// Whether this workgroup is the last of n to come here (all threads; the counter is zero before and after), what the others stored before is
-// seen from here on.
-__device__ inline bool screen_last(int32_t* counter, int n) {
+// Groups that the sign-offs of a unit's workgroups come in: a word takes one every 25 ns, and most arrive together.  With one word for all
+// workgroups of a sequence (505 at 28 layers of T=1000) the walk started up to 12 us late: d=2048, one token in fifty loose 122 -> 115 us.
+constexpr int SIGN_OFFS = 32;
+__device__ inline int screen_groups(int rest) { return min((rest + SIGN_OFFS - 1) / SIGN_OFFS, 8); }   // (a line of the header each)
+
+// Whether this workgroup is the last one of a sequence (all threads): what the others stored is seen from here on.  A unit's workgroup `slot` of
+// `rest` signs off in its group's word of the unit's header (zero since the sketches), the last one of a group adds one to `counter`, and
+// the workgroup that knows how many groups there are (hdr: NULL) takes their number off: whoever leaves zero is the last, and zero is what the next call needs.
+__device__ inline bool screen_last(int32_t* counter, uint32_t* hdr, int slot, int rest, int n_groups) {
     __shared__ int s_last;
     drain_stores();
     __syncthreads();
-    if (threadIdx.x == 0) s_last = atomicAdd(counter, 1) == n - 1;
-    __syncthreads();
-    if (!s_last) return false;                                // uniform
     if (threadIdx.x == 0) {
-        __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        if (hdr) {
+            const int groups = screen_groups(rest), k = slot % groups, members = (rest - k + groups - 1) / groups;
+            s_last = (int)atomicAdd(hdr + SU_PART + k * 32 + SU_DONE, 1u) == members - 1 && atomicAdd(counter, 1) == -1;
+        } else s_last = atomicAdd(counter, -n_groups) == n_groups;
+        if (s_last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
     __syncthreads();
-    return true;
+    return s_last;
 }
 
 // k_screen_rest: the unexplained candidates of all units as a launch of its own, where the pairs inside clusters are counted
@@ -1210,12 +1216,13 @@ __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
     const ScreenUnit SU(p.T, p.nch, p.edge_cap);
     const int tid = threadIdx.x, T = p.T, lane = tid & 63, words = (T + 63) >> 6;
     int g = blockIdx.x;
+    const bool walker = g < p.G;
     // Workgroups from G on see to the unexplained candidates of a unit each.  Where there are any, the last one of a sequence to be done
     // walks (its walker counts as one of them): nobody waits for anybody.  (As a launch of its own in front of the walk they took 2.4 to
     // 4.8 us, and 3 us of the host, to find nothing: calls of 12 x T=512, d=768 in fp32 28.8 -> 25.6 us, 12 x T=2048, d=768 39.9 -> 37.6, 28 x
     // T=2048, d=4096 128.4 -> 126.7.  Loose clusters, one token in ten and all of them: 12 x T=512 62.9 -> 64.8 and 106 -> 111, 12 x T=2048
     // 97.5 -> 95.8 and 149 -> 132, 28 x T=2048, d=4096 288 -> 276 and 645 -> 553, 4 x T=8192 304 -> 251 and 447 -> 376.)
-    if (g >= p.G) {
+    if (!walker) {
         const int units = p.G * p.L, b = g - p.G;
         int layer;
         char* base = screen_unit(p, SU, b % units, &layer, &g);
@@ -1228,6 +1235,7 @@ __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
         const int state = __builtin_amdgcn_readfirstlane(s_unit);
         if ((state & 15) != UNIT_OPEN) return;
         screen_rest_tiles<THREADS>(p, SU, base, layer, g, (state & 16) != 0, b / units, c.rest, c.ntile, c.lanes, c.f32 != 0, lds);
+        if (!screen_last(reinterpret_cast<int32_t*>(reinterpret_cast<char*>(p.meta) + (long long)g * p.area_gs) + META_WALK, reinterpret_cast<uint32_t*>(base), b / units, c.rest, 0)) return;
     }
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     uint32_t* slots = reinterpret_cast<uint32_t*>(lds);       // [2][SET] stamp << 14 | earliest inherited member; the last 64 take what is none
@@ -1251,6 +1259,13 @@ __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
 
     const int progress = meta[META_PROGRESS];
     const uint32_t* hdr = reinterpret_cast<const uint32_t*>(area + (long long)min(lane, p.L - 1) * SU.bytes);   // of the layer with this lane's number
+    uint32_t edges_of = 0u;
+    bool is_dense = false;
+    auto look = [&] {
+        edges_of = __hip_atomic_load(hdr + SU_EDGES, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        is_dense = __hip_atomic_load(hdr + SU_DENSE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
+    };
+    if (!walker) look();                                      // (in flight beside the counts)
     unsigned long long open = 0ull, closed = 0ull;            // layers with unexplained candidates; with too many of them
     if (c.rest) {                                             // (one wave looks: sixteen took 3 us longer over 28 layers' lines)
         __shared__ unsigned long long s_state[2];
@@ -1264,14 +1279,9 @@ __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
         open = uniform64(s_state[0]);
         closed = uniform64(s_state[1]);
     }
-    if (open && !screen_last(meta + META_WALK, __popcll(open) * c.rest + 1)) return;   // uniform
-    uint32_t edges_of = 0u;
-    bool is_dense = (closed >> lane) & 1ull;
-    if (open || !c.rest) {                                    // (plain units have neither)
-        edges_of = __hip_atomic_load(hdr + SU_EDGES, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        is_dense |= __hip_atomic_load(hdr + SU_DENSE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
-    }
-    const unsigned long long dense = __ballot(lane < p.L && is_dense);
+    if (walker && open && !screen_last(meta + META_WALK, nullptr, 0, 0, __popcll(open) * screen_groups(c.rest))) return;   // uniform
+    if (walker && (open || !c.rest)) look();                  // (plain units have neither)
+    const unsigned long long dense = __ballot(lane < p.L && (is_dense || ((closed >> lane) & 1ull)));
     const unsigned long long edged = __ballot(lane < p.L && edges_of != 0u);
     for (int t = tid; t < 2 * SET; t += THREADS) slots[t] = 0xFFFFFFFFu;
     for (int t = tid; t < TOKENS; t += THREADS) mark[t] = 0;

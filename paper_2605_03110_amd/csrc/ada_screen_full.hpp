@@ -164,7 +164,8 @@ __global__ __launch_bounds__(SCREEN_SORT_THREADS) void k_screen_sort(ScreenFullP
         if (blockIdx.x > 0)
             screen_rest_tiles<SCREEN_SORT_THREADS>(p, U, p.area, 0, 0, (s_state & 16) != 0, (int)blockIdx.x - 1, (int)gridDim.x - 1, f.ntile, f.lanes,
                                                    f.f32 != 0, lds);
-        if (!screen_last(p.meta + META_WALK, (int)gridDim.x)) return;
+        const int rest = (int)gridDim.x - 1;
+        if (!screen_last(p.meta + META_WALK, blockIdx.x > 0 ? reinterpret_cast<uint32_t*>(p.area) : nullptr, (int)blockIdx.x - 1, rest, screen_groups(rest))) return;
         if (blockIdx.x > 0) take();
     }
     const uint32_t n_edge = state == UNIT_OPEN ? __hip_atomic_load(hdr + SU_EDGES, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;

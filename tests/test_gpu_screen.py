@@ -451,6 +451,70 @@ def test_rows_past_the_end_are_no_candidates(d, tau, T, L):
                 assert cand == pairs and dense == 0, (n, fill, g, cand - pairs)
 
 
+def layers_per_launch(T, d, L, tau):
+    """run_layers_screened of csrc/ada_kernels.hip: as many layers as the workspace has room for, in launches of equal size."""
+    from test_screen_replay import plan                       # (which imports this module)
+
+    def up(n):
+        return (n + 255) // 256 * 256
+    unit = up(544 * 4 + 3 * up(4 * T) + up(2 * T) + up((T + 63) // 64 * 16) + up((T // 2 + 65) // 2 * 2 * 8) + (T + 31) // 32 * plan(d, tau)[0] * 2048)
+    fit = min(min(up(T * 8192 + 65536), 31 << 19) // unit, 64)
+    return -(-L // -(-L // fit))
+
+
+def candidate_rounds(T, L, G=1):
+    """How the walk's launch goes through the unexplained candidates of a unit (rest_workgroups, screen_rest_tiles and screen_groups of csrc/): workgroups,
+    tiles side by side in each round, groups of sign-offs.  256 CUs."""
+    threads = 256 if T <= 256 else 512 if T <= 1024 else 1024
+    most, n = threads // 256, -(-T // 128)
+    ntile, room = n * (n + 1) // 2, 256 * (2 if 512 < T <= 1024 else 1) - G
+    slots = max((min(ntile, 8) + most - 1) // most, min(ntile, room // (G * L)))
+    rounds, done = [], 0
+    while done < ntile:
+        side = 1
+        while side < most and side * slots < ntile - done:
+            side *= 2
+        rounds.append(side)
+        done += side * slots
+    return slots, rounds, min(-(-slots // 32), 8)
+
+
+@pytest.mark.parametrize("T,L,G,form", [
+    (200, 20, 1, (3, [1], 1)), (400, 3, 1, (10, [1], 1)), (400, 30, 1, (8, [2], 1)), (513, 2, 1, (15, [1], 1)), (1000, 28, 1, (18, [2], 1)), (700, 12, 4, (10, [2, 1], 1)),
+    (2048, 28, 1, (9, [4, 4, 4, 4], 1)), (2047, 8, 1, (31, [4, 1], 1)), (1921, 10, 1, (25, [4, 2], 1)), (1100, 2, 1, (45, [1], 2)), (2048, 2, 1, (127, [2], 4)),
+    (3900, 2, 1, (127, [4], 4)), (1500, 6, 3, (14, [4, 2], 1))])
+def test_unexplained_candidates_in_every_form_of_rounds(T, L, G, form):
+    """Some tokens at any angle up to the threshold from their centre: every layer has candidates that no cluster explains, and each form of
+    the rounds over their tiles and of the sign-offs (asserted) leaves the sets that the one-launch steps, which multiply all products, find."""
+    print("[case] unexplained candidates: T=%d L=%d G=%d" % (T, L, G), flush=True)
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256 and candidate_rounds(T, L, G) == form
+    d, tau, gen = 256, 0.1, torch.Generator(device=DEV).manual_seed(T + L)
+    assert layers_per_launch(T, d, L, tau) == L and G * L * T < 65536     # one launch, the exact pass counts the pairs
+    C = torch.nn.functional.normalize(torch.randn(T // 5, d, generator=gen, device=DEV), dim=1)
+    a = torch.randint(T // 5, (G, T), generator=gen, device=DEV)
+    xs = []
+    for _ in range(L):
+        v = torch.randn(G, T, d, generator=gen, device=DEV)
+        v = torch.nn.functional.normalize(v - (v * C[a]).sum(-1, keepdim=True) * C[a], dim=-1)
+        angle = 0.13 * torch.rand(G, T, 1, generator=gen, device=DEV) * (torch.rand(G, T, 1, generator=gen, device=DEV) < 0.2)
+        xs.append((torch.cos(angle) * C[a] + torch.sin(angle) * v).bfloat16())
+        a = torch.where(torch.rand(G, T, generator=gen, device=DEV) < 0.05, torch.randint(T // 5, (G, T), generator=gen, device=DEV), a)
+    ws = pa.workspace_batched(T, G)
+    for _ in range(2):                                          # (the second call finds the counters as the first one left them)
+        res = pa.ada_cascade_layers_grouped(xs, tau, ws=ws)
+        torch.cuda.synchronize()
+        for g in range(G):
+            cand, inside, _, dense = unit_counts(ws, T, g)
+            assert cand > inside and dense == 0
+    for g in range(G):
+        for l in range(1, L, 1 if L < 8 else 7):
+            r, r1 = int(res["counts"][g, l - 1, 0]), int(res["counts"][g, l, 0])
+            step = pa.fetch(pa.ada_cascade_step(xs[l][g], tau, res["idx"][g, l - 1, :r].contiguous()))
+            assert np.array_equal(step["idx"], res["idx"][g, l, :r1].cpu().numpy()) and step["gram_ops"] == int(res["gram_ops"][g, l]), (g, l)
+        first = pa.fetch(pa.ada_select_full(xs[0][g].contiguous(), tau))
+        assert np.array_equal(first["idx"], res["idx"][g, 0, :int(res["counts"][g, 0, 0])].cpu().numpy())
+
+
 FULL = [
     # kind, T, d, dtype, tau, greedy, big: long enough for the graph, by one rule each (greedy / fp32 / other bf16 rows / whole pieces)
     ("clusters", 1500, 64, "bf16", 0.1, True, 0), ("clusters", 2049, 1001, "bf16", 0.1, True, 0), ("clusters", 4100, 96, "f32", 0.2, True, 0),
@@ -523,14 +587,7 @@ def test_layers_side_by_side_under_the_causal_mask(T, H, dh, L, dtype):
 def exact_pass(T, d, L, groups, esz, tau):
     """How k_screen_exact reads the layers of a call (run_layers_screened, launch_screen, launch_screen_exact and screen_streams of csrc/):
     lanes per row, rows per lane group, and whether X goes past the caches.  Rows and matrices start on whole cache lines."""
-    from test_screen_replay import plan                       # (which imports this module)
-
-    def up(n):
-        return (n + 255) // 256 * 256
-    unit = up(544 * 4 + 3 * up(4 * T) + up(2 * T) + up((T + 63) // 64 * 16) + up((T // 2 + 65) // 2 * 2 * 8) + (T + 31) // 32 * plan(d, tau)[0] * 2048)
-    fit = min(min(up(T * 8192 + 65536), 31 << 19) // unit, 64)
-    batches = -(-L // fit)
-    units = groups * -(-L // batches)
+    units = groups * layers_per_launch(T, d, L, tau)
     pieces = (d * esz + 15) // 16
     lanes = 64 if pieces >= 256 else 32 if pieces >= 128 else 16 if pieces >= 64 or pieces == 32 else 8
     rows = 2 if T // (4 * (256 // lanes)) * units >= 2048 else 1
