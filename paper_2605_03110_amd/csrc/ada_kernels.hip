@@ -1680,17 +1680,17 @@ hipError_t launch_screen_exact_any(const ScreenParams& sp, int np, hipStream_t s
     return launch_screen_exact<In, LPR, 4, false>(sp, st);
 }
 
-// 128 x 128 tiles of a unit, and the workgroups (up to `side` tiles side by side) that go through them: a unit with nothing to do takes its
-// workgroups one read each, a busy one should have enough of them, on CUs of their own while there are some.
+// 128 x 128 tiles of a unit, and the workgroups (up to `side` tiles side by side) that go through them in a launch that has room for `room` of
+// them at once: a unit with nothing to do takes its workgroups one read each, a busy one should have enough of them, on CUs of their own
+// while there are some.
 int rest_tiles(int T) { const int nb = (T + 127) / 128; return nb * (nb + 1) / 2; }
-int rest_workgroups(int ntile, int units, int side) {
-    const int k = std::min(std::max(1024 / units, 8), ntile);
-    return std::max((k + side - 1) / side, std::min(k, device_cus() / units));
+int rest_workgroups(int ntile, int units, int side, int room) {
+    return std::max((std::min(ntile, 8) + side - 1) / side, std::min(ntile, room / units));
 }
 
 template <typename In, int LPR>
 hipError_t launch_screen_rest(const ScreenParams& sp, hipStream_t st) {
-    const int units = sp.G * sp.L, ntile = rest_tiles(sp.T), k = rest_workgroups(ntile, units, 1);
+    const int units = sp.G * sp.L, ntile = rest_tiles(sp.T), k = std::min(std::max(1024 / units, 8), ntile);
     ProfScope ps(ADA_K_SCREEN, st);
     hipLaunchKernelGGL((k_screen_rest<In, LPR>), dim3((unsigned)(k * units)), dim3(256), sp.count_pairs ? 0 : (sp.T + 3) / 4 * 8, st, sp, ntile);
     return hipGetLastError();
@@ -1829,7 +1829,7 @@ int screen_full(const ScreenPlan& plan, const void* X, int T, int d, long long l
         f.ntile = rest_tiles(T);
         f.lanes = screen_lanes((d * (dtype == ADA_BF16 ? 2 : 4) + 15) / 16);
         f.f32 = dtype == ADA_F32;
-        const int rest = rest_workgroups(f.ntile, 1, SCREEN_SORT_THREADS / 256);   // (T < 65536: the exact pass counts the pairs)
+        const int rest = rest_workgroups(f.ntile, 1, SCREEN_SORT_THREADS / 256, device_cus() - 1);   // (T < 65536: the exact pass counts the pairs)
         hipLaunchKernelGGL(k_screen_sort, dim3((unsigned)(1 + rest)), dim3(SCREEN_SORT_THREADS), screen_sort_lds(T), st, f);
         if (hipGetLastError() != hipSuccess) return ADA_ERR_DEVICE;
     }
@@ -1851,7 +1851,7 @@ hipError_t launch_screen_chain(ChainParams& c, hipStream_t st) {
     if (attr_err != hipSuccess) return attr_err;
     ProfScope ps(ADA_K_UPDATE, st);
     const int units = c.s.G * c.s.L;
-    c.rest = c.s.count_pairs ? rest_workgroups(c.ntile, units, THREADS / 256) : 0;
+    c.rest = c.s.count_pairs ? rest_workgroups(c.ntile, units, THREADS / 256, device_cus() * chain_places<THREADS, U>() - c.s.G) : 0;
     hipLaunchKernelGGL((k_screen_chain<THREADS, U, D>), dim3((unsigned)(c.s.G + c.rest * units)), dim3(THREADS), (chain_lds<THREADS, U>(c.s.T)), st, c);
     return hipGetLastError();
 }

@@ -696,8 +696,13 @@ __device__ inline int screen_state(const ScreenParams& p, const ScreenCounts& n)
     return n.flags == 0u && n.cand == n.pairs ? UNIT_PLAIN : n.cand > n.pairs + p.open ? UNIT_DENSE : UNIT_OPEN;
 }
 
-// The candidates of an open unit that no cluster explains, by workgroup `slot` of `slots` (all threads; lanes: per product, a power of two).
-// 256 threads go through a 128 x 128 tile, several tiles side by side in larger workgroups.  A tile's edges are counted in LDS and take
+// The candidates of an open unit that no cluster explains, by workgroup `slot` of `slots` (all threads; lanes: per product, a power of two; NB:
+// blocks of 32 tokens at a time, 1 where a thread has 128 registers).  A round takes 128 x 128 tiles side by side, a power of two of them per
+// workgroup and only as many as are needed for what is left: 256 threads of each find its pairs, all threads it has form the
+// products (12 layers of T=512, d=768 in fp32, all tokens loose, with a workgroup per tile 88.7 -> 65.1 us and the walk).  Side by side they wait for
+// each other, so a last round of few tiles, dealt to few workgroups four at a time, was as long as a whole one: 8 layers of T=2048, d=4096, all
+// tokens loose 191 -> 184 us with a CU for every workgroup (one too many is a round more), 169 with sides by what is left; with 128 registers
+// two workgroups of 512 threads share a CU: 28 layers of T=1000, d=2048 238 -> 218.  A tile's edges are counted in LDS and take
 // their places in the unit's list with one atomic: one per edge, all to one address at 25 ns each, was most of this (T=2048, d=768 in
 // fp32, clusters of five as wide as the threshold: 187 us).  Edges and counts go past the caches: the walk may be in the same launch.
 struct RestTile {
@@ -707,23 +712,23 @@ struct RestTile {
     float rho[256];
     uint16_t cl[256];
 };
-template <int THREADS>
+template <int THREADS, int NB>
 __device__ inline void screen_rest_tiles(const ScreenParams& p, const ScreenUnit& U, char* base, int layer, int group, bool low, int slot,
                                          int slots, int ntile, int lanes, bool f32, char* lds) {
     constexpr int SUB = THREADS / 256;
-    const int tid = (int)threadIdx.x & 255, sub = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8), lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     RestTile* tiles = reinterpret_cast<RestTile*>(lds);
     uint32_t* hdr = reinterpret_cast<uint32_t*>(base);
     const float* rho = reinterpret_cast<const float*>(base + U.o_rho);
     const uint16_t* cl = reinterpret_cast<const uint16_t*>(base + U.o_cl);
     unsigned long long* edge = reinterpret_cast<unsigned long long*>(base + U.o_edge);
-    // With a workgroup per tile its first 256 threads find the pairs and all of them form the products: 12 layers of T=512, d=768 in fp32, all
-    // tokens loose, with 512 threads 88.7 -> 65.1 us (and the walk).
-    const int side = slots < ntile ? SUB : 1, mine = side > 1 ? tid : (int)threadIdx.x, many = side > 1 ? 256 : THREADS;
-    RestTile& my = tiles[side > 1 ? sub : 0];
-    for (int tile0 = slot * side; tile0 < ntile; tile0 += slots * side) {
-        const int tile = tile0 + sub;
-        const bool exists = sub < side && tile < ntile;       // (uniform per tile; the barriers are everybody's)
+    for (int done = 0; done + slot < ntile;) {
+        int side = 1;                                         // (uniform, the same in all of a unit's workgroups)
+        while (side < SUB && side * slots < ntile - done) side *= 2;
+        const int many = THREADS / side, sub = __builtin_amdgcn_readfirstlane((int)threadIdx.x / many), mine = (int)threadIdx.x & (many - 1);
+        const int lane = mine & 63, l32 = lane & 31, half = lane >> 5, tile = done + sub * slots + slot;
+        const bool exists = tile < ntile;                     // (uniform per tile; the barriers are everybody's)
+        done += side * slots;
+        RestTile& my = tiles[sub];
         int sb, tb;
         screen_blocks(min(tile, ntile - 1), &sb, &tb);
         __syncthreads();
@@ -731,16 +736,15 @@ __device__ inline void screen_rest_tiles(const ScreenParams& p, const ScreenUnit
             my.n = my.edges = 0;
             if (sub == 0) tiles[0].stop = __hip_atomic_load(hdr + SU_DENSE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
         }
-        if (sub < side) {
-            const int tok = min(tid < 128 ? sb * 128 + tid : tb * 128 + tid - 128, p.T - 1);
-            my.rho[tid] = fminf(rho[tok], 1.f);
-            my.cl[tid] = cl[tok];
+        if (mine < 256) {
+            const int tok = min(mine < 128 ? sb * 128 + mine : tb * 128 + mine - 128, p.T - 1);
+            my.rho[mine] = fminf(rho[tok], 1.f);
+            my.cl[mine] = cl[tok];
         }
         __syncthreads();
         if (tiles[0].stop) break;                             // given up already (uniform)
-        const ScreenTile me = screen_tile(p.T, sb, tb, __builtin_amdgcn_readfirstlane(tid >> 6));
-        if (me.any && exists) {
-            constexpr int NB = THREADS <= 512 ? 2 : 1;        // (a thread of 1024 has 128 registers)
+        const ScreenTile me = screen_tile(p.T, sb, tb, __builtin_amdgcn_readfirstlane(mine >> 6));
+        if (mine < 256 && me.any && exists) {
 #pragma unroll 1
             for (int b0 = 0; b0 < 2; b0 += NB) {
                 f32x16 acc[2][NB];
@@ -785,7 +789,7 @@ __device__ inline void screen_rest_tiles(const ScreenParams& p, const ScreenUnit
             constexpr int LPR = decltype(lpr)::value;
             using In = decltype(in);
             const In* X = screen_x<In>(p, layer, group);
-            const int li = tid & (LPR - 1);
+            const int li = mine & (LPR - 1);
             for (int k = mine / LPR; k < n; k += many / LPR) {
                 const uint32_t e = my.pair[k];
                 const int s = (int)(e >> 16), t = (int)(e & 0xFFFFu);
@@ -817,7 +821,7 @@ __device__ inline void screen_rest_tiles(const ScreenParams& p, const ScreenUnit
 }
 
 // Groups that the sign-offs of a unit's workgroups come in: a word takes one every 25 ns, and most arrive together.  With one word for all
-// workgroups of a sequence (505 at 28 layers of T=1000) the walk started up to 12 us late: d=2048, one token in fifty loose 122 -> 115 us.
+// workgroups of a sequence the walk started up to 12 us late: 28 layers of T=1000, d=2048 (505 workgroups), one token in fifty loose 128.8 -> 121.5 us.
 constexpr int SIGN_OFFS = 32;
 __device__ inline int screen_groups(int rest) { return min((rest + SIGN_OFFS - 1) / SIGN_OFFS, 8); }   // (a line of the header each)
 
@@ -858,7 +862,7 @@ __global__ __launch_bounds__(256) void k_screen_rest(ScreenParams p, int ntile) 
     if (state == UNIT_DENSE && (int)blockIdx.x < units && threadIdx.x == 0)
         __hip_atomic_store(hdr + SU_DENSE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (state == UNIT_OPEN)
-        screen_rest_tiles<256>(p, U, base, layer, group, (n_unit.flags & SF_LOW) != 0u, (int)blockIdx.x / units, (int)gridDim.x / units, ntile, LPR,
+        screen_rest_tiles<256, 2>(p, U, base, layer, group, (n_unit.flags & SF_LOW) != 0u, (int)blockIdx.x / units, (int)gridDim.x / units, ntile, LPR,
                                sizeof(In) == 4, reinterpret_cast<char*>(&tile));
 }
 
@@ -1206,8 +1210,11 @@ __device__ inline unsigned long long uniform64(unsigned long long v) {
     return (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
 }
 
+// Workgroups of the walk's launch that a CU holds at once: registers.  (Up to 512 tokens a unit's tiles have a workgroup each, on CUs of
+// their own, and the registers are worth more.)
+template <int THREADS, int U> constexpr int chain_places() { return THREADS == 512 && U > 1 ? 2 : 1; }
 template <int THREADS, int U, int D>
-__global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
+__global__ __launch_bounds__(THREADS, (THREADS / 256 * chain_places<THREADS, U>())) void k_screen_chain(ChainParams c) {
     extern __shared__ __align__(16) char lds[];
     static_assert(SCREEN_MAX_LAYERS == 64, "a lane per layer");
     constexpr int TOKENS = THREADS * U, SET = TOKENS + 64;
@@ -1234,7 +1241,7 @@ __global__ __launch_bounds__(THREADS) void k_screen_chain(ChainParams c) {
         screen_barrier();
         const int state = __builtin_amdgcn_readfirstlane(s_unit);
         if ((state & 15) != UNIT_OPEN) return;
-        screen_rest_tiles<THREADS>(p, SU, base, layer, g, (state & 16) != 0, b / units, c.rest, c.ntile, c.lanes, c.f32 != 0, lds);
+        screen_rest_tiles<THREADS, THREADS / 256 * chain_places<THREADS, U>() < 4 ? 2 : 1>(p, SU, base, layer, g, (state & 16) != 0, b / units, c.rest, c.ntile, c.lanes, c.f32 != 0, lds);
         if (!screen_last(reinterpret_cast<int32_t*>(reinterpret_cast<char*>(p.meta) + (long long)g * p.area_gs) + META_WALK, reinterpret_cast<uint32_t*>(base), b / units, c.rest, 0)) return;
     }
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -162,7 +162,7 @@ __global__ __launch_bounds__(SCREEN_SORT_THREADS) void k_screen_sort(ScreenFullP
     if (state != UNIT_OPEN && blockIdx.x > 0) return;         // uniform
     if (state == UNIT_OPEN) {
         if (blockIdx.x > 0)
-            screen_rest_tiles<SCREEN_SORT_THREADS>(p, U, p.area, 0, 0, (s_state & 16) != 0, (int)blockIdx.x - 1, (int)gridDim.x - 1, f.ntile, f.lanes,
+            screen_rest_tiles<SCREEN_SORT_THREADS, 1>(p, U, p.area, 0, 0, (s_state & 16) != 0, (int)blockIdx.x - 1, (int)gridDim.x - 1, f.ntile, f.lanes,
                                                    f.f32 != 0, lds);
         const int rest = (int)gridDim.x - 1;
         if (!screen_last(p.meta + META_WALK, blockIdx.x > 0 ? reinterpret_cast<uint32_t*>(p.area) : nullptr, (int)blockIdx.x - 1, rest, screen_groups(rest))) return;
