@@ -1715,9 +1715,13 @@ template <typename In>
 hipError_t launch_screen(ScreenParams& sp, hipStream_t st) {
     const int units = sp.G * sp.L;
     // Who counts the pairs inside clusters.  The exact pass takes an atomic with a return per token for it, 20 thousand of them a microsecond
-    // from the whole chip, which short rows do not hide; each workgroup of k_screen_rest a histogram of its unit in LDS, 1 us.  16 heads
-    // x 256, 8 layers of T=2048 (262 thousand tokens): the pass 32.0 -> 28.0 us, k_screen_rest 4.7 -> 5.6.
-    sp.count_pairs = (sp.d * (int)sizeof(In) + 15) / 16 >= 128 || (long long)units * sp.T < 65536;
+    // from the whole chip, which rows of less than 2 KB do not hide; each workgroup of k_screen_rest, a launch more, a histogram of its whole unit in
+    // LDS.  That launch also sees to unexplained candidates, where there are many units as fast as the walk's launch or faster, where
+    // there are few slower.  Sequences side by side, us, counted by the exact pass -> by k_screen_rest, tight clusters and with one token in fifty loose: d=256,
+    // T=2048, 32 units 41.9 -> 41.7 and 91.9 -> 91.9, 128 units 86.5 -> 80.3, T=1000, 72 and 128 units 41.6 -> 40.4, 54.0 -> 49.5, T=3000, 24 units 47.4
+    // -> 49.8 and 118 -> 126, 88 units 94.3 -> 91.0 and 341 -> 295, T=8192, 8 units 54.5 -> 62.5 and 166 -> 200, 32 units 123 -> 129; d=128, T=2048,
+    // 64 units 53.0 -> 48.9; d=448, T=4096, 32 units 81.3 -> 84.7 and 242 -> 244; d=512, T=2048, 64 units 68.4 -> 69.3 and 171 -> 160.
+    sp.count_pairs = (sp.d * (int)sizeof(In) + 15) / 16 >= 128 || units < 64 || (long long)units * sp.T < 65536;
     {
         ProfScope ps(ADA_K_SCREEN, st);
         switch (sp.nch) {

@@ -152,7 +152,7 @@ def test_pairs_counted_behind_the_exact_pass(T, d, G, L):
     """Short rows of many units: the pairs inside clusters are counted by the launch behind.  Each sequence alone, whose pairs the exact
     pass counts, gives the same; plain sequences, some with edges, dense ones."""
     print("[case] pairs counted behind: T=%d d=%d G=%d L=%d" % (T, d, G, L), flush=True)
-    assert G * L * T >= 65536 and L * T < 65536
+    assert G * L >= 64 and G * L * T >= 65536 and 2 * d < 2048 and L < 64
     kinds = ("clusters", "loose", "strays", "common", "clusters", "signs")
     per = [[x.to(DEV) for x in activations(kinds[g % len(kinds)], T, d, L, "bf16", seed=g)] for g in range(G)]
     res = pa.ada_cascade_layers_grouped([torch.stack([p[l] for p in per]) for l in range(L)], 0.1, want_lists=True)
