@@ -1666,15 +1666,15 @@ hipError_t launch_screen_exact(const ScreenParams& sp, hipStream_t st) {
 }
 
 // Pieces of a row in flight per lane: as many of four, three or two as rows are whole numbers of (see screen_products), else four.  Rows of
-// 32 and 16 pieces go over twice the lanes, two pieces each: 16 heads x 256, 8 layers 34.3 -> 28.0 us, all that changed in the pass.
+// 32 pieces go over sixteen lanes and of 16 over eight, two pieces each: 16 heads x 256, 8 layers 34.3 -> 28.0 us, all that changed in the
+// pass.  (Rows of five rounds, bf16 of 1280, 2560 or 5120 columns, take the form with clamps.)
 template <typename In, int LPR>
 hipError_t launch_screen_exact_any(const ScreenParams& sp, int np, hipStream_t st) {
     if (sp.d * (int)sizeof(In) % 16 == 0) {
-        if constexpr (LPR == 8) {
+        if constexpr (LPR == 8) {                             // (fewer than 64 pieces)
             if (np == 32) return launch_screen_exact<In, 16, 2, true>(sp, st);
             if (np == 16) return launch_screen_exact<In, 8, 2, true>(sp, st);
-        }
-        if (np % (LPR * 4) == 0) return launch_screen_exact<In, LPR, 4, true>(sp, st);
+        } else if (np % (LPR * 4) == 0) return launch_screen_exact<In, LPR, 4, true>(sp, st);
         if (np % (LPR * 3) == 0) return launch_screen_exact<In, LPR, 3, true>(sp, st);
     }
     return launch_screen_exact<In, LPR, 4, false>(sp, st);
@@ -1692,7 +1692,7 @@ template <typename In, int LPR>
 hipError_t launch_screen_rest(const ScreenParams& sp, hipStream_t st) {
     const int units = sp.G * sp.L, ntile = rest_tiles(sp.T), k = std::min(std::max(1024 / units, 8), ntile);
     ProfScope ps(ADA_K_SCREEN, st);
-    hipLaunchKernelGGL((k_screen_rest<In, LPR>), dim3((unsigned)(k * units)), dim3(256), sp.count_pairs ? 0 : (sp.T + 3) / 4 * 8, st, sp, ntile);
+    hipLaunchKernelGGL((k_screen_rest<In, LPR>), dim3((unsigned)(k * units)), dim3(256), (sp.T + 3) / 4 * 8, st, sp, ntile);
     return hipGetLastError();
 }
 
@@ -1754,10 +1754,7 @@ hipError_t launch_screen(ScreenParams& sp, hipStream_t st) {
     hipError_t e = np >= 256 ? launch_screen_exact_any<In, 64>(sp, np, st) : np >= 128 ? launch_screen_exact_any<In, 32>(sp, np, st)
                  : np >= 64 ? launch_screen_exact_any<In, 16>(sp, np, st) : launch_screen_exact_any<In, 8>(sp, np, st);
     if (e != hipSuccess) return e;
-    if (sp.count_pairs) return hipSuccess;
-    const int lanes = screen_lanes(np);
-    return lanes == 64 ? launch_screen_rest<In, 64>(sp, st) : lanes == 32 ? launch_screen_rest<In, 32>(sp, st)
-         : lanes == 16 ? launch_screen_rest<In, 16>(sp, st) : launch_screen_rest<In, 8>(sp, st);
+    return sp.count_pairs ? hipSuccess : np >= 64 ? launch_screen_rest<In, 16>(sp, st) : launch_screen_rest<In, 8>(sp, st);   // (see screen_lanes)
 }
 
 // The full selection of one sequence (ada_screen_full.hpp).
