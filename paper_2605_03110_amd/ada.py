@@ -69,12 +69,17 @@ SCRATCH_BUDGET = {
     "k_screen_exactI": 0,
     "k_screen_restI": 0,
     "k_screen_chainI": 0,
+    "k_screen_sortE": 0,                       # full selection on that graph
+    "k_screen_gramI": 0,
     "k_cascade_passI": 0,                      # all steps in one launch: what is spilled there is paid for at every step
     "k_cascade_restItLb1ELi2ELi2E": 0,         # layers that the graph of near pairs leaves to the tiles
     "k_cascade_restIfLb1ELi2ELi2E": 16,
     "k_gram_dmaILb1E": 0,                      # one-launch full selection
     "k_gram_dmaILb0E": 0,                      # full Gram beyond T = 4096
     "k_attn_rep2ILi256E": 64,                  # attention on the representative set, d_h = 256
+    "k_attn_rep2ILi128E": 0,
+    "k_attn_rep2ILi64E": 0,
+    "k_attn_repIfL": 0,                        # and in fp32
 }
 
 

@@ -551,19 +551,27 @@ def test_full_selection_on_the_graph_of_near_pairs(kind, T, d, dtype, tau, greed
             assert np.array_equal(step["idx"], got["idx"]) or kind in ("loose", "common")   # (chains: a removed token covers nobody)
 
 
-@pytest.mark.parametrize("sizes,T", [((33, 32), 5196), ((64,), 5184), ((65,), 5201), ((40, 30, 2), 5121), ((63, 2), 5120), ((1, 128, 3), 5280),
-                                     ((31, 34, 64, 1, 1), 5249), ((200, 5, 7), 5300), ((33, 32), 2050), ((2,), 5300), ((1, 128, 3), 2111), ((200, 5, 7), 5119)])
-def test_blocks_of_the_members(sizes, T):
-    """The members' list cut between clusters from 5120 members in clusters of eight on, every 64 below: sizes that fill a block, that miss it by one, that never
-    share one, and clusters of several blocks; every token's largest correlation against the oracle."""
-    print("[case] blocks of the members: sizes %s T=%d" % (sizes, T), flush=True)
-    rng, d = np.random.default_rng(T), 768
+@pytest.mark.parametrize("sizes,T,whole", [
+    ((33, 32), 5196, True), ((64,), 5184, True), ((65,), 5201, True), ((40, 30, 2), 5121, True), ((63, 2), 5120, True), ((1, 128, 3), 5280, True),
+    ((31, 34, 64, 1, 1), 5249, True), ((33, 32), 2050, False), ((2,), 5300, False), ((1, 128, 3), 2111, False),
+    ((200,) + (20,) * 40, 5300, True), ((200,) + (20,) * 40, 5119, False),                  # clusters of four blocks
+    ((650, 200) + (20,) * 400, 8192, True), ((20,) * 100 + (700, 1) + (30,) * 300, 8190, True),      # of eleven, over a whole lane of 512 members
+    ((1300, 200, 65) + (20,) * 800, 16383, True), ((513, 1, 512, 3) + (20,) * 800, 16384, True)])      # over two of them; lanes up to the last
+def test_blocks_of_the_members(sizes, T, whole):
+    """The members' list cut between clusters where there are 5120 members in clusters of eight on (whole), every 64 below: sizes that fill a block,
+    that miss it by one, that never share one, and clusters of several blocks; every token's largest correlation against the oracle."""
+    print("[case] blocks of the members: sizes %s T=%d" % (sizes[:4], T), flush=True)
+    rng, d = np.random.default_rng(T), 768 if T < 8000 else 128
     of = np.repeat(np.arange(T), np.resize(sizes, T))[:T]
+    n = np.bincount(of)
+    assert (n * (n - 1) // 2).sum() <= 64 * T                  # (SCREEN_FULL_PAIRS: the call does not go to the full Gram)
+    members = int(n[n > 1].sum())
+    assert (members >= 20 * torch.cuda.get_device_properties(0).multi_processor_count and len(n) * 8 <= members) == whole
     C = rng.standard_normal((of.max() + 1, d))
     C /= np.linalg.norm(C, axis=1, keepdims=True)
     x_cpu = torch.from_numpy((C[rng.permutation(of)] + 0.004 * rng.standard_normal((T, d)) / np.sqrt(d)).astype(np.float32))
     got = pa.fetch(pa.ada_select_full(x_cpu.to(DEV), 0.1))
-    parity.check_full(x_cpu, 0.1, got, "sizes %s" % (sizes,))
+    parity.check_full(x_cpu, 0.1, got, "sizes %s" % (sizes[:4],))
 
 
 @pytest.mark.parametrize("T,H,dh,L,dtype", [(700, 3, 64, 3, "bf16"), (1100, 16, 64, 5, "bf16"), (900, 8, 128, 2, "f32"), (2100, 16, 128, 12, "bf16"),
@@ -585,13 +593,16 @@ def test_layers_side_by_side_under_the_causal_mask(T, H, dh, L, dtype):
 
 
 def exact_pass(T, d, L, groups, esz, tau):
-    """How k_screen_exact reads the layers of a call (run_layers_screened, launch_screen, launch_screen_exact and screen_streams of csrc/):
-    lanes per row, rows per lane group, and whether X goes past the caches.  Rows and matrices start on whole cache lines."""
+    """How k_screen_exact reads the layers of a call (run_layers_screened, launch_screen, launch_screen_exact_any, launch_screen_exact and screen_streams
+    of csrc/): lanes per row, rows per lane group, and whether X goes past the caches (rows and matrices start on whole cache lines); pieces in
+    flight per lane, and whether rows are whole numbers of them."""
     units = groups * layers_per_launch(T, d, L, tau)
     pieces = (d * esz + 15) // 16
     lanes = 64 if pieces >= 256 else 32 if pieces >= 128 else 16 if pieces >= 64 or pieces == 32 else 8
     rows = 2 if T // (4 * (256 // lanes)) * units >= 2048 else 1
-    return lanes, rows, d * esz % 128 == 0 and units * T * d * esz >= 192 << 20
+    at_once, even = 2 if pieces in (16, 32) else 4 if pieces % (4 * lanes) == 0 else 3 if pieces % (3 * lanes) == 0 else 4, d * esz % 16 == 0
+    whole = even and (pieces in (16, 32) or pieces % (lanes * at_once) == 0)
+    return lanes, rows, d * esz % 128 == 0 and units * T * d * esz >= 192 << 20, at_once if even else 4, whole
 
 
 @pytest.mark.parametrize("T,d,L,groups,dtype,form", [
@@ -604,7 +615,7 @@ def test_large_inputs_give_what_small_ones_give(T, d, L, groups, dtype, form):
     every later layer what a step of its own gives from the call's previous set (one launch, no graph).  Every number of lanes per row
     with one and two rows per lane group (form: what the case runs), and calls cut into launches that are small again."""
     print("[case] large inputs: T=%d d=%d L=%d G=%d %s" % (T, d, L, groups, dtype), flush=True)
-    assert exact_pass(T, d, L, groups, 2 if dtype == "bf16" else 4, 0.1) == form
+    assert exact_pass(T, d, L, groups, 2 if dtype == "bf16" else 4, 0.1)[:3] == form
     assert not exact_pass(T, d, 2, groups, 2 if dtype == "bf16" else 4, 0.1)[2]
     gen = torch.Generator(device=DEV).manual_seed(T)
     K = T // 7
@@ -634,6 +645,44 @@ def test_large_inputs_give_what_small_ones_give(T, d, L, groups, dtype, form):
             step = pa.fetch(pa.ada_cascade_step(x, 0.1, at(big, "idx", l - 1).reshape(groups, T)[g, :int(c0[0])].contiguous()))
             assert int(c1[3]) == 0
             assert np.array_equal(step["idx"], at(big, "idx", l).reshape(groups, T)[g, :int(c1[0])].cpu().numpy())
+
+
+@pytest.mark.parametrize("T,d,L,groups,dtype,form", [
+    (2050, 4096, 16, 1, "bf16", (64, 2, 4, True)), (2050, 4096, 13, 1, "bf16", (64, 1, 4, True)), (2050, 3072, 16, 1, "bf16", (64, 2, 3, True)),
+    (1039, 3072, 33, 1, "bf16", (64, 2, 3, True)), (511, 3072, 33, 2, "bf16", (64, 1, 3, True)), (2050, 2560, 20, 1, "bf16", (64, 2, 4, False)),
+    (2050, 1280, 20, 1, "f32", (64, 2, 4, False)), (2047, 1024, 52, 1, "bf16", (32, 2, 4, True)), (2050, 1536, 32, 1, "bf16", (32, 2, 3, True)),
+    (1055, 1536, 21, 3, "bf16", (32, 1, 3, True)), (2050, 768, 32, 1, "f32", (32, 2, 3, True)), (4100, 1984, 16, 1, "bf16", (32, 2, 4, False)),
+    (1030, 1984, 25, 2, "bf16", (32, 1, 4, False)), (4097, 512, 25, 2, "bf16", (16, 2, 4, True)), (2050, 768, 32, 2, "bf16", (16, 2, 3, True)),
+    (2047, 768, 33, 2, "bf16", (16, 1, 3, True)), (4100, 960, 16, 2, "bf16", (16, 2, 4, False)), (2050, 960, 26, 2, "bf16", (16, 1, 4, False)),
+    (8200, 256, 12, 4, "bf16", (16, 2, 2, True)), (8200, 128, 12, 4, "f32", (16, 2, 2, True)), (8200, 192, 16, 4, "bf16", (8, 2, 3, True)),
+    (8190, 384, 9, 4, "bf16", (8, 2, 3, True)), (8060, 384, 11, 3, "bf16", (8, 1, 3, True)), (8190, 448, 8, 5, "bf16", (8, 2, 4, False)),
+    (4100, 448, 14, 4, "bf16", (8, 1, 4, False)), (8190, 128, 20, 5, "bf16", (8, 2, 2, True))])
+def test_every_form_of_the_exact_pass(T, d, L, groups, dtype, form):
+    """Lanes per row, rows per lane group, pieces in flight and whole rows or not (asserted), past the caches and, the rows 16 bytes apart, through them: the
+    same sets, which at every fifth layer are those of a step that multiplies all products."""
+    print("[case] exact pass: T=%d d=%d L=%d G=%d %s" % (T, d, L, groups, dtype), flush=True)
+    esz, dt = (2, torch.bfloat16) if dtype == "bf16" else (4, torch.float32)
+    lanes, rows, past, at_once, whole = exact_pass(T, d, L, groups, esz, 0.1)
+    assert (lanes, rows, at_once, whole) == form and past
+    gen = torch.Generator(device=DEV).manual_seed(T + d)
+    K, ld = T // 6, d + 16 // esz
+    C = torch.nn.functional.normalize(torch.randn(K, d, generator=gen, device=DEV), dim=1)
+    a = torch.randint(K, (groups, T), generator=gen, device=DEV)
+    xs, apart = [], []
+    for _ in range(L):
+        a = torch.where(torch.rand(groups, T, generator=gen, device=DEV) < 0.05, torch.randint(K, (groups, T), generator=gen, device=DEV), a)
+        xs.append((C[a] + torch.randn(groups, T, d, generator=gen, device=DEV) * (0.004 / d ** 0.5)).to(dt))
+        apart.append(torch.zeros(groups, T, ld, dtype=dt, device=DEV)[:, :, :d])
+        apart[-1].copy_(xs[-1])
+    got, through = (pa.ada_cascade_layers_grouped(m, 0.1) for m in (xs, apart))
+    assert torch.equal(got["counts"], through["counts"]) and bool((got["counts"][:, :, 3] == 0).all())
+    for g in range(groups):
+        for l in range(L):
+            r = int(got["counts"][g, l, 0])
+            assert torch.equal(got["idx"][g, l, :r], through["idx"][g, l, :r]) and 0 < r < T
+            if l % 5 == 1 and g == l % groups:
+                prev = got["idx"][g, l - 1, :int(got["counts"][g, l - 1, 0])].contiguous()
+                assert np.array_equal(pa.fetch(pa.ada_cascade_step(xs[l][g], 0.1, prev))["idx"], got["idx"][g, l, :r].cpu().numpy()), (g, l)
 
 
 @pytest.mark.parametrize("d,tau", [(64, 0.1), (768, 0.1), (4096, 0.1), (768, 0.3), (1000, 0.3), (3000, 0.2)])   # 1, 2, 3, 4, 5 and 6 column groups
