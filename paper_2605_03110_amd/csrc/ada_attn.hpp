@@ -195,8 +195,8 @@ template <typename In, int DH> struct AttnGeom {
     static constexpr int OFF_S = 3 * 64 * ROWB;                       // float[64][65]
     static constexpr int OFF_P = OFF_S + 64 * 65 * 4;                 // weights: bf16 hi then lo (8 KB each), or fp32 (16 KB)
     static constexpr int OFF_ROW = OFF_P + 16384;                     // alpha[64], lsum[64], qtok[64], ktok[64]
-    static constexpr int OFF_LIST = OFF_ROW + 4 * 64 * 4;             // int[256] + counter
-    static constexpr int LDS = (OFF_LIST + 257 * 4 + 15) / 16 * 16;                    // (the positions behind it, if the kernel finds them itself)
+    static constexpr int OFF_COUNT = OFF_ROW + 4 * 64 * 4;            // takers' counter
+    static constexpr int LDS = OFF_COUNT + 16;                        // (the positions behind it, if the kernel finds them itself)
     static_assert(PPR == 8 || PPR == 16 || PPR == 32, "head rows of 128, 256 or 512 bytes");
     static_assert(DH % 64 == 0, "head dimension in multiples of 64");
 };
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(256) void k_attn_rep(AttnParams p, Layers layers) {
     float* lsum = alpha + 64;
     int* qtok = reinterpret_cast<int*>(lsum + 64);
     int* ktok = qtok + 64;
-    int* list = reinterpret_cast<int*>(lds + G::OFF_LIST);                 // the takers' counter
+    int* count = reinterpret_cast<int*>(lds + G::OFF_COUNT);               // the takers' counter
 
     ATTN_CLK(0);
     const int r = p.r_dev ? *p.r_dev : p.r_host;
@@ -489,7 +489,7 @@ __global__ __launch_bounds__(256) void k_attn_rep(AttnParams p, Layers layers) {
             const int t = tb + u * 256 + tid;
             rel[u] = t < p.T ? (own ? (int)own_pos[t] : p.pos[t]) - q0 : -1;
         }
-        attn_hand_over<DH, 4, DH, false>(obuf, reinterpret_cast<int*>(vtbuf), list, outh, p.ld_out, tb, rel);
+        attn_hand_over<DH, 4, DH, false>(obuf, reinterpret_cast<int*>(vtbuf), count, outh, p.ld_out, tb, rel);
     }
     ATTN_CLK(4);
     }
@@ -529,8 +529,8 @@ template <int DH> struct AttnGeom2 {
     static constexpr int OFF_TAKERS = (64 * OS * 4 + 15) / 16 * 16;                    // behind the output block
     static constexpr int MAIN = (4 * 64 * ROWB > OFF_TAKERS + 2048 * 4) ? 4 * 64 * ROWB : OFF_TAKERS + 2048 * 4;
     static constexpr int OFF_ROW = MAIN;                                               // qtok[64], ktok[64], m[2][64], l[2][64]
-    static constexpr int OFF_LIST = OFF_ROW + 6 * 64 * 4;
-    static constexpr int LDS = (OFF_LIST + 257 * 4 + 15) / 16 * 16;                    // (the positions behind it, if the kernel finds them itself)
+    static constexpr int OFF_COUNT = OFF_ROW + 6 * 64 * 4;                             // takers' counter
+    static constexpr int LDS = OFF_COUNT + 16;                                         // (the positions behind it, if the kernel finds them itself)
 };
 
 // EIGHT waves: waves 0 .. 3 multiply as described and never touch memory inside the key-block loop; waves 4 .. 7 fetch
@@ -560,7 +560,7 @@ __global__ __launch_bounds__(512) void k_attn_rep2(AttnParams p, Layers layers) 
     int* ktok = qtok + 64;
     float* mrow = reinterpret_cast<float*>(ktok + 64);     // [2][64] running maxima and sums of the two key halves
     float* lrow = mrow + 128;
-    int* list = reinterpret_cast<int*>(lds + G::OFF_LIST);                 // the takers' counter
+    int* count = reinterpret_cast<int*>(lds + G::OFF_COUNT);               // the takers' counter
     int* takers = reinterpret_cast<int*>(lds + G::OFF_TAKERS);            // up to 2048 (token, row) pairs
 
     const int r = p.r_dev ? *p.r_dev : p.r_host;
@@ -845,7 +845,7 @@ __global__ __launch_bounds__(512) void k_attn_rep2(AttnParams p, Layers layers) 
     float* outh = p.out + (size_t)h * DH;
     for (int tb = 0; tb < p.T; tb += 4 * 512) {
         if (tb > 0) load_rel(tb);                          // (the first 2048 were asked for before the merge)
-        attn_hand_over<DH, 8, G::OS, STREAM>(obuf, takers, list, outh, p.ld_out, tb, rel);
+        attn_hand_over<DH, 8, G::OS, STREAM>(obuf, takers, count, outh, p.ld_out, tb, rel);
     }
     }
     ATTN_CLK(7);

@@ -1146,7 +1146,9 @@ hipError_t launch_attn(const AttnParams& p, const Layers& layers, int n_layers, 
             const char* e = dev_switch("ADA_ATTN");
             return e && std::string(e) == "lds";
         }();
-        // its hand-over stores 16 bytes per lane
+        // Outputs at other than 16 bytes stay with the first kernel: not for the hand-over, which takes them at any address, but because the register
+        // kernel is further from 64 bits.  Relative 2-norm, first kernel and register kernel: 16 x 256, T=2048, scores of size one 2.1e-6 and 2.4e-6,
+        // of size eight 0.85e-6 and 1.65e-6; us, one float off, 12 x 64, T=512 11.6 and 10.9, 32 x 128, T=2048 33.3 and 20.0, 16 x 256 55.7 and 32.6.
         bool out16 = p.ld_out % 4 == 0 && (uintptr_t)p.out % 16 == 0;
         if constexpr (std::is_same<Layers, AttnLayers>::value)
             for (int l = 0; l < n_layers; ++l) out16 = out16 && (uintptr_t)layers.out[l] % 16 == 0;
