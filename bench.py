@@ -85,7 +85,7 @@ def cpu_baseline_extras():
 
 def call_spread(call, n, pairs=7):
     """Time of a call among others, us: median and largest over `pairs` pairs of events around n calls each (a pair around every
-    kernel of a call adds its own gaps, a third to two thirds of the time where a call is eight short launches).  A host that stalls
+    kernel of a call adds its own gaps, a third to two thirds of the time where a call is five to seven short launches).  A host that stalls
     shows in the largest alone, a call that runs another way in both."""
     import torch
     got = []

@@ -198,13 +198,14 @@ int ada_assign_nearest(const void* X, int T, int d, int64_t ld, int dtype,
  *   assign   [T] int32, the representative of every token (the output of ada_assign_nearest for the same R)
  * Outputs
  *   out   [T x (H * d_h)] float, leading dimension ld_out (elements), any alignment (a 16-byte aligned base with
- *         ld_out a multiple of 4 lets the bf16 kernel store whole rows per instruction)
+ *         ld_out a multiple of 4 takes the faster of the two bf16 kernels)
  *   info  [4] int32  {|R|, 0, 0, status}; status is ADA_OK, or ADA_ERR_INDEX (idx not strictly ascending / out of
  *                    range, or an assign entry that is not a member of R) / ADA_ERR_SHAPE (bad r_dev), and then out
  *                    is not written
  * Scores and weights are fp32 (a per-row reference close to the running maximum subtracted, so no weight exceeds
  * 2^10); bf16 weights enter the second product as hi + lo pairs.
- * ADA_FLAG_ATTN_CAUSAL masks later members of R.  Two launches (positions and validation, attention).
+ * ADA_FLAG_ATTN_CAUSAL masks later members of R.  One launch up to T = 2048 with d_h <= 128, else two (positions and validation,
+ * attention).
  */
 int ada_attention_compressed(const void* Q, const void* K, const void* V, int T, int H, int d_h, int64_t ld, int dtype,
                              const int32_t* idx, int r, const int32_t* r_dev, const int32_t* assign,
@@ -219,7 +220,7 @@ int ada_attention_compressed(const void* Q, const void* K, const void* V, int T,
  *   counts_all   device [L*4] int32   row l as in ada_cascade_step (layer 0: {r, r, 0, 0})
  *   gram_ops_all device [L]   uint64  layer 0: T*T
  *   adds_all / removes_all  device [L*T] int32 each, or NULL to skip reporting them
- * Up to 64 layers at a time share six launches: which pairs of tokens are within the threshold of each other does not
+ * Up to 64 layers at a time share five launches (six with many short rows): which pairs of tokens are within the threshold of each other does not
  * depend on the inherited set, so it is found for all of them at once (8-bit sketches of the rows and a bound exclude most
  * pairs, full products decide the rest) and the sets follow from a walk over those pairs.  Layers with too many pairs near
  * the threshold for a list run on the tiles of ada_cascade_step, with those behind them, in the last of these launches.

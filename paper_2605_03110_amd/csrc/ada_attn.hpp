@@ -158,9 +158,9 @@ __device__ inline int attn_positions(const AttnParams& p, bool first, int r, uin
 // XCDs and each of them would pull that head's K and V rows from memory.  When the head count is a multiple of 8 the
 // index is re-read so that a head's workgroups share an XCD (head % 8).  Query blocks run slowest, so that under the
 // causal mask, which takes them from the last one down (attn_block), the long ones start first: those of all layers, as the
-// long ones of the last layer would end alone.  16 heads x 256, T=2048, causal: 4 layers of r=434 70.1 -> 56.8 us; calls of 6 layers 189 -> 165,
-// 8 layers 200 -> 203, 10 layers 245 -> 239, 4 layers of T=4096 264 -> 229.  Without the mask they are alike, and a layer's K and V are done with
-// before the next one's.
+// long ones of the last layer would end alone.  16 heads x 256, T=2048, causal: 4 layers of r=434 70.1 -> 56.8 us; calls of 4 layers 148 -> 128,
+// 6 layers 171 -> 155, 8 layers 199 -> 194, 10 layers 247 -> 242, 12 layers 277 -> 261, 16 layers 343 -> 345, 4 layers of T=4096 248 -> 215.  Without the mask
+// they are alike, and a layer's K and V are done with before the next one's.
 struct AttnWho {
     int h, qblk, layer;
     __device__ bool first() const { return h == 0 && qblk == 0; }

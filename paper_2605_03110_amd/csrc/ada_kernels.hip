@@ -1776,15 +1776,21 @@ hipError_t launch_screen_gram(const ScreenParams& sp, const GramParams& p, hipSt
     return hipGetLastError();
 }
 
-// Where the graph is the better way: seven launches and two single-workgroup passes cost 40 to 50 us whatever the products,
-// so the triangle has to be worth more, at the rate of the tiles that would run it.  Measured, us, full Gram -> graph (K =
-// distinct rows):
-//   bf16, whole 64-byte pieces, T > 4096 (a norm and an update launch as well): T=8192 d=512 65 -> 58 (3.4e10), d=256
-//     48 -> 56 (1.7e10), 6000 x 512 54 -> 56 (1.8e10), 6000 x 1024 75 -> 66 (3.7e10), 8192 x 4096 297 -> 105 (K = T / 20), 284 -> 210 (T / 2)
-//   the same, T <= 4096 (one launch): 4096 x 4096 107 -> 65 and 108 -> 98 (6.9e10), 3500 x 4096 84 -> 60 and 85 -> 87 (5e10)
-//   other bf16 rows: 3001 x 1000 49 -> 43 (9e9), 8191 x 130 99 -> 65 (8.7e9), 2400 x 1000 37 -> 50 (5.8e9)
-//   fp32: 2048 x 768 63 -> 52 (3.2e9), 1500 x 768 44 -> 50 (1.7e9); T=1100 d=4096 105 -> 123 (one tile takes 100)
-//   greedy covering, which also saves its resolution: 1536 x 768 59 -> 37, 2048 x 4096 93 -> 54, 1100 x 4096 53 -> 51
+// Where the graph is the better way: six launches (seven for a greedy covering), two of them behind the gate, and a single-workgroup pass cost 40 to 50 us
+// whatever the products, so the triangle has to be worth more, at the rate of the tiles that would run it.  Measured, us, full Gram -> graph with
+// K = T / 20 and T / 2 distinct rows (T^2 d):
+//   bf16, whole 64-byte pieces, T > 4096 (a norm and an update launch as well): 8192 x 128 (8.6e9) 40 -> 48, 47; 8192 x 256 (1.7e10) 45 -> 47, 49;
+//     6000 x 512 (1.8e10) 49 -> 44, 48; 8192 x 384 (2.6e10) 53 -> 49, 54; 5000 x 1024 (2.6e10) 43 -> 47, 62; 8192 x 512 (3.4e10) 60 -> 51, 59; 6000 x 1024
+//     (3.7e10) 71 -> 46, 59
+//   the same, T <= 4096 (one launch): 2048 x 4096 (1.7e10) 34 -> 48, 48; 4096 x 2048 (3.4e10) 58 -> 46, 61; 3000 x 4096 (3.7e10) 70 -> 53, 64;
+//     3500 x 4096 (5e10) 77 -> 54, 82; 4096 x 3072 (5.2e10) 80 -> 51, 85; 4096 x 4096 (6.9e10) 102 -> 56, 90
+//   other bf16 rows: 5000 x 200 (5e9) 45 -> 44, 61; 2400 x 1000 (5.8e9) 34 -> 40, 47; 8191 x 100 (6.7e9) 79 -> 51, 60; 2800 x 1000 (7.8e9)
+//     29 -> 41, 48; 3001 x 1000 (9e9) 45 -> 42, 49
+//   fp32: 1500 x 768 (1.7e9) 42 -> 49, 47; 3000 x 256 (2.3e9) 56 -> 41, 48; 1800 x 768 (2.5e9) 44 -> 50, 48; 1600 x 1024 (2.6e9) 53 -> 55, 53;
+//     2048 x 768 (3.2e9) 61 -> 50, 48
+//   greedy covering, which also saves its resolution: 1536 x 768 59 -> 37, 2048 x 4096 93 -> 49, 1100 x 4096 53 -> 51
+// The lines stand where few distinct rows and many meet; T^2 d is not all that counts: long narrow matrices below them (8191 x 100, 3000 x 256 in
+// fp32) and 3000 and 4096 x 2048 to 3072 with few distinct rows would be up to a third faster on the graph.
 bool screen_full_eligible(const void* X, int T, int d, long long ld, int dtype, float tau, bool greedy, ScreenPlan* plan) {
     if (T < SCREEN_FULL_MIN_T || T > FUSED_MAX_T) return false;
     const char* e = dev_switch("ADA_SCREEN");
@@ -1878,14 +1884,15 @@ hipError_t launch_cascade_rest(const RestParams& rp, hipStream_t st) {
 }
 
 // Whether a call over L layers of G problems is screened: every layer at the one threshold (known here), T within the range
-// of the one-launch step (cluster ids and list positions in 16 bits), a sketch that is a saving, and more to do than six
-// launches take (23 to 27 us): two layers always are, one layer unless its Gram is a single short round of the chip.
+// of the one-launch step (cluster ids and list positions in 16 bits), a sketch that is a saving, and more to do than five
+// launches take (26 to 29 us from the host): two layers always are, one layer unless its Gram is a single short round of the chip.
 // Measured, us, one layer, full Gram -> graph:
-//   64 x 64 tiles, one round of them (T <= 1536), bf16: d=128 15 -> 23, 768 16 -> 23, 2304 22 -> 24, 4096 29 -> 23;
-//     four at a time, T=512 d=768: 16 -> 24; fp32: d=128 15 -> 23, 768 28 -> 23; two rounds, 2048 x 770: 30 -> 25
-//   bf16 in whole 64-byte pieces from T = 1536 on: 1536 x 2304 21 -> 24 (5.4e9), 2048 x 768 14 -> 25, 2048 x 4096 32 -> 26
-//     (1.7e10), 3000 x 768 25 -> 25 (6.9e9), 4096 x 128 20 -> 27, 4096 x 768 33 -> 26 (1.3e10)
-//   two layers: T=197 d=768 30 -> 24, T=2048 d=768 28 -> 28
+//   64 x 64 tiles, one round of them (T <= 1536), bf16: 512 x 768 21 -> 28, 512 x 4096 29 -> 29, 1000 x 128 21 -> 27, 1400 x 2304 25 -> 27, 1500 x 2304
+//     30 -> 27, 1400 x 4096 33 -> 28; fp32: 1000 x 128 21 -> 29, x 384 22 -> 27, x 768 30 -> 28; two rounds, 2048 x 770: 32 -> 27
+//   bf16 in whole 64-byte pieces from T = 1536 on: 1536 x 768 15 -> 27, 4096 x 128 (2.1e9) 21 -> 28, 2048 x 768 15 -> 27, 3000 x 512 (4.6e9) 23 -> 27,
+//     1536 x 2304 (5.4e9) 22 -> 27, 4096 x 384 (6.4e9) 27 -> 27, 3000 x 768 (6.9e9) 26 -> 27, 2048 x 2048 (8.6e9) 22 -> 27, 4096 x 768 (1.3e10)
+//     34 -> 27, 2048 x 4096 (1.7e10) 37 -> 27
+//   two layers: 512 x 768 29 -> 29, 1000 x 128 28 -> 28, 1536 x 768 30 -> 28, 2048 x 768 30 -> 27; fp32, 1000 x 128 30 -> 28, x 384 41 -> 28
 bool screen_eligible(const void* X, int L, int G, int T, int d, long long ld, int dtype, float tau, unsigned flags, ScreenPlan* plan) {
     if ((flags & (ADA_FLAG_TWO_PASS | ADA_FLAG_RESIDENT_PASS)) || T > FUSED_MAX_T) return false;
     const char* e = dev_switch("ADA_SCREEN");

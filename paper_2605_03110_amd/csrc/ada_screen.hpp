@@ -316,7 +316,8 @@ __device__ inline uint32_t screen_first(uint32_t bits) {      // position of the
 // 256 / `cut` of them: long pieces spend less of their time on starting up (a piece of 256 took about half of it for
 // that), short ones are needed to fill the chip.  Two workgroups per CU fill it: halved pieces up to four per CU cost a layer
 // loop of 12 x T=2048, d=768 50.8 us instead of 48.7, 2 x T=4096, d=512 36.0 instead of 34.0.  With one column group a piece has a
-// third of the products: 128 x T=2048, d=256 29.3 us in pieces of 256, 26.5 of 512, 27.0 of 1024.  Strips come in groups of
+// third of the products: 128 x T=2048, d=256 29.3 us in pieces of 256, 26.5 of 512, 27.0 of 1024; calls in pieces of 256 and of 512, by their tiles: T=2048,
+// 1152 42.5 and 42.3, 2016 52.9 and 52.3, 2304 55.8 and 54.2, 4608 81.6 and 77.6, T=8192, 2112 40.2 and 38.9, 4224 62.6 and 60.1.  Strips come in groups of
 // `wide` with the same number of pieces.
 struct PairItems {
     int wide, cut, per_unit;
@@ -1229,8 +1230,9 @@ __global__ __launch_bounds__(THREADS, (THREADS / 256 * chain_places<THREADS, U>(
     // Workgroups from G on see to the unexplained candidates of a unit each.  Where there are any, the last one of a sequence to be done
     // walks (its walker counts as one of them): nobody waits for anybody.  (As a launch of its own in front of the walk they took 2.4 to
     // 4.8 us, and 3 us of the host, to find nothing: calls of 12 x T=512, d=768 in fp32 28.8 -> 25.6 us, 12 x T=2048, d=768 39.9 -> 37.6, 28 x
-    // T=2048, d=4096 128.4 -> 126.7.  Loose clusters, one token in ten and all of them: 12 x T=512 62.9 -> 64.8 and 106 -> 111, 12 x T=2048
-    // 97.5 -> 95.8 and 149 -> 132, 28 x T=2048, d=4096 288 -> 276 and 645 -> 553, 4 x T=8192 304 -> 251 and 447 -> 376.)
+    // T=2048, d=4096 128.4 -> 126.7.  With one token in ten loose, and all of them, a launch of their own with the walk of that time -> now: 16 x T=300, d=256
+    // 51.4 -> 52.6 and 66.5 -> 64.8, 12 x T=512 60.3 -> 55.5 and 105.5 -> 83.5, 12 x T=1000 60.6 -> 60.8 and 87.6 -> 85.9, 12 x T=2048, d=768 96.4 -> 83.3
+    // and 148 -> 117, 28 x T=2048, d=4096 285 -> 260 and 665 -> 543, 4 x T=8192, d=512 220 -> 152 and 240 -> 191.)
     if (!walker) {
         const int units = p.G * p.L, b = g - p.G;
         int layer;
@@ -1408,7 +1410,7 @@ __global__ __launch_bounds__(THREADS, (THREADS / 256 * chain_places<THREADS, U>(
 }
 
 // ------------------------------------------------------------------------------------------------
-// k_cascade_rest: the lists of all layers, one workgroup per layer -- or, when the chain stopped at a dense layer (and wrote
+// k_cascade_rest: the lists of all layers, a layer's shared by its workgroups -- or, when the chain stopped at a dense layer (and wrote
 // the lists before it), that layer and all after it on the tiles of k_cascade_fused.  Before those the assignments that the
 // graph leaves open (META_ALONE; the chain wrote these layers' lists), on the same tiles.  Layer 0 is a step that inherits
 // every token: Algorithm 1's step 5 on the identity list is Definition 2.2.

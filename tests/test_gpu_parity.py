@@ -1334,8 +1334,8 @@ def test_attention_with_steep_scores_moves_the_reference(gain):
 
 
 def test_attention_into_a_strided_unaligned_output():
-    """An output view whose rows start at odd float offsets (the vector stores of the bf16 kernel do not apply: the
-    general kernel runs) gives the same rows as the contiguous output, and leaves the padding alone."""
+    """An output view whose rows start at odd float offsets (the general kernel runs) gives the same rows as the contiguous
+    output, and leaves the padding alone."""
     say("attention strided output")
     w = wl.small(T=400, d=256, K=60, L=1, dtype="bf16", seed=12, p=0.1)
     x = wl.layer_list(w)[0]
