@@ -152,7 +152,8 @@ def test_pairs_counted_behind_the_exact_pass(T, d, G, L):
     """Short rows of many units: the pairs inside clusters are counted by the launch behind.  Each sequence alone, whose pairs the exact
     pass counts, gives the same; plain sequences, some with edges, dense ones."""
     print("[case] pairs counted behind: T=%d d=%d G=%d L=%d" % (T, d, G, L), flush=True)
-    assert G * L >= 64 and G * L * T >= 65536 and 2 * d < 2048 and L < 64
+    assert G * L * T >= 65536 and L * T < 65536
+    assert G * L >= 64 and 2 * d < 2048 and L < 64            # (the other sides of the rule)
     kinds = ("clusters", "loose", "strays", "common", "clusters", "signs")
     per = [[x.to(DEV) for x in activations(kinds[g % len(kinds)], T, d, L, "bf16", seed=g)] for g in range(G)]
     res = pa.ada_cascade_layers_grouped([torch.stack([p[l] for p in per]) for l in range(L)], 0.1, want_lists=True)
@@ -551,16 +552,29 @@ def test_full_selection_on_the_graph_of_near_pairs(kind, T, d, dtype, tau, greed
             assert np.array_equal(step["idx"], got["idx"]) or kind in ("loose", "common")   # (chains: a removed token covers nobody)
 
 
+@pytest.mark.parametrize("sizes,T", [((33, 32), 5196), ((64,), 5184), ((65,), 5201), ((40, 30, 2), 5121), ((63, 2), 5120), ((1, 128, 3), 5280),
+                                     ((31, 34, 64, 1, 1), 5249), ((200, 5, 7), 5300), ((33, 32), 2050), ((2,), 5300), ((1, 128, 3), 2111), ((200, 5, 7), 5119)])
+def test_blocks_of_the_members(sizes, T):
+    """The members' list cut between clusters from 5120 members in clusters of eight on, every 64 below: sizes that fill a block, that miss it by one, that never
+    share one, and clusters of several blocks; every token's largest correlation against the oracle."""
+    print("[case] blocks of the members: sizes %s T=%d" % (sizes, T), flush=True)
+    rng, d = np.random.default_rng(T), 768
+    of = np.repeat(np.arange(T), np.resize(sizes, T))[:T]
+    C = rng.standard_normal((of.max() + 1, d))
+    C /= np.linalg.norm(C, axis=1, keepdims=True)
+    x_cpu = torch.from_numpy((C[rng.permutation(of)] + 0.004 * rng.standard_normal((T, d)) / np.sqrt(d)).astype(np.float32))
+    got = pa.fetch(pa.ada_select_full(x_cpu.to(DEV), 0.1))
+    parity.check_full(x_cpu, 0.1, got, "sizes %s" % (sizes,))
+
+
 @pytest.mark.parametrize("sizes,T,whole", [
-    ((33, 32), 5196, True), ((64,), 5184, True), ((65,), 5201, True), ((40, 30, 2), 5121, True), ((63, 2), 5120, True), ((1, 128, 3), 5280, True),
-    ((31, 34, 64, 1, 1), 5249, True), ((33, 32), 2050, False), ((2,), 5300, False), ((1, 128, 3), 2111, False),
     ((200,) + (20,) * 40, 5300, True), ((200,) + (20,) * 40, 5119, False),                  # clusters of four blocks
     ((650, 200) + (20,) * 400, 8192, True), ((20,) * 100 + (700, 1) + (30,) * 300, 8190, True),      # of eleven, over a whole lane of 512 members
     ((1300, 200, 65) + (20,) * 800, 16383, True), ((513, 1, 512, 3) + (20,) * 800, 16384, True)])      # over two of them; lanes up to the last
-def test_blocks_of_the_members(sizes, T, whole):
-    """The members' list cut between clusters where there are 5120 members in clusters of eight on (whole), every 64 below: sizes that fill a block,
-    that miss it by one, that never share one, and clusters of several blocks; every token's largest correlation against the oracle."""
-    print("[case] blocks of the members: sizes %s T=%d" % (sizes[:4], T), flush=True)
+def test_clusters_of_several_blocks(sizes, T, whole):
+    """Clusters of three blocks and more, the members' list cut between clusters (whole) or every 64, with few enough pairs for the graph to answer
+    (asserted); every token's largest correlation against the oracle."""
+    print("[case] clusters of several blocks: sizes %s T=%d" % (sizes[:4], T), flush=True)
     rng, d = np.random.default_rng(T), 768 if T < 8000 else 128
     of = np.repeat(np.arange(T), np.resize(sizes, T))[:T]
     n = np.bincount(of)
@@ -592,7 +606,7 @@ def test_layers_side_by_side_under_the_causal_mask(T, H, dh, L, dtype):
         assert int(res["info"][l, 4]) == r and torch.equal(one["out"], res["out"][l]), "layer %d" % l
 
 
-def exact_pass(T, d, L, groups, esz, tau):
+def exact_form(T, d, L, groups, esz, tau):
     """How k_screen_exact reads the layers of a call (run_layers_screened, launch_screen, launch_screen_exact_any, launch_screen_exact and screen_streams
     of csrc/): lanes per row, rows per lane group, and whether X goes past the caches (rows and matrices start on whole cache lines); pieces in
     flight per lane, and whether rows are whole numbers of them."""
@@ -605,6 +619,11 @@ def exact_pass(T, d, L, groups, esz, tau):
     return lanes, rows, d * esz % 128 == 0 and units * T * d * esz >= 192 << 20, at_once if even else 4, whole
 
 
+def exact_pass(T, d, L, groups, esz, tau):
+    """Its lanes per row, rows per lane group, and whether X goes past the caches."""
+    return exact_form(T, d, L, groups, esz, tau)[:3]
+
+
 @pytest.mark.parametrize("T,d,L,groups,dtype,form", [
     (2050, 4096, 16, 1, "bf16", (64, 2, True)), (2050, 4096, 13, 1, "bf16", (64, 1, True)), (2047, 1024, 52, 1, "bf16", (32, 2, True)),
     (2049, 512, 51, 1, "f32", (32, 2, True)), (1030, 1984, 25, 2, "bf16", (32, 1, True)), (4097, 512, 25, 2, "bf16", (16, 2, True)),
@@ -615,7 +634,7 @@ def test_large_inputs_give_what_small_ones_give(T, d, L, groups, dtype, form):
     every later layer what a step of its own gives from the call's previous set (one launch, no graph).  Every number of lanes per row
     with one and two rows per lane group (form: what the case runs), and calls cut into launches that are small again."""
     print("[case] large inputs: T=%d d=%d L=%d G=%d %s" % (T, d, L, groups, dtype), flush=True)
-    assert exact_pass(T, d, L, groups, 2 if dtype == "bf16" else 4, 0.1)[:3] == form
+    assert exact_pass(T, d, L, groups, 2 if dtype == "bf16" else 4, 0.1) == form
     assert not exact_pass(T, d, 2, groups, 2 if dtype == "bf16" else 4, 0.1)[2]
     gen = torch.Generator(device=DEV).manual_seed(T)
     K = T // 7
@@ -662,7 +681,7 @@ def test_every_form_of_the_exact_pass(T, d, L, groups, dtype, form):
     same sets, which at every fifth layer are those of a step that multiplies all products."""
     print("[case] exact pass: T=%d d=%d L=%d G=%d %s" % (T, d, L, groups, dtype), flush=True)
     esz, dt = (2, torch.bfloat16) if dtype == "bf16" else (4, torch.float32)
-    lanes, rows, past, at_once, whole = exact_pass(T, d, L, groups, esz, 0.1)
+    lanes, rows, past, at_once, whole = exact_form(T, d, L, groups, esz, 0.1)
     assert (lanes, rows, at_once, whole) == form and past
     gen = torch.Generator(device=DEV).manual_seed(T + d)
     K, ld = T // 6, d + 16 // esz
